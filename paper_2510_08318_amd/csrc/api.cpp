@@ -28,12 +28,9 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   if (P < 1) P = 1;
   if (P > tiles) P = tiles;
   int tiles_per = (tiles + P - 1) / P;
-  r.chunk = tiles_per * kTile;
-  r.P = (n + r.chunk - 1) / r.chunk;
-  r.QP = r.P;
-  r.qchunk = r.chunk;
-  if (dtype == LINATTN_BF16) {
-    // query pass: 12-wavefront workgroups, one per compute unit, 32-token blocks dealt round-robin
+  r.P = (tiles + tiles_per - 1) / tiles_per;
+  {
+    // query pass of the bf16 kernels: 12-wavefront workgroups, one per compute unit, 32-token blocks dealt round-robin
     const int nblk = (n + 31) / 32;
     int QP = kCUs / (int)BH;
     if (QP < 1) QP = 1;
@@ -46,6 +43,7 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
     sp.ntile = tiles;
     sp.T = (long long)BH * tiles;
     sp.G = BH > kSlots ? (int)BH : (int)(sp.T < kSlots ? sp.T : kSlots);
+    sp.small = sp.T * sp.G < (1LL << 31);
     sp.PS = 1;
     for (long long bh = 0; bh < BH; ++bh) {
       const int cnt = split_owner(sp, (bh + 1) * tiles - 1) - split_owner(sp, bh * tiles) + 1;
@@ -190,26 +188,17 @@ int run_fwd(const linattn_phi_desc& desc, const Plan& plan, const void* q, const
   hipError_t e;
   const StageEvents ev = stage_events();
   ev.mark(0, s);
-  if (desc.dtype != LINATTN_BF16) {
-    e = launch_state_partials_f32(k, v, desc.wk, partials, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-    ev.mark(1, s);
-    e = launch_state_reduce(partials, state, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-    ev.mark(2, s);
-    e = launch_apply_f32(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-  } else {
-    const bool relu = desc.kind == LINATTN_PHI_RELU;
-    e = relu ? launch_relu_state_bf16(k, v, partials, plan, s) : launch_state_partials_bf16(k, v, desc.wk, partials, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-    ev.mark(1, s);
-    e = launch_state_reduce_split(partials, state, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-    ev.mark(2, s);
-    e = launch_apply_bf16(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s);
-    if (e != hipSuccess) return LINATTN_E_HIP;
-  }
+  const bool f32_math = desc.dtype != LINATTN_BF16, relu = desc.kind == LINATTN_PHI_RELU;
+  e = f32_math ? launch_state_partials_f32(k, v, desc.wk, partials, plan, s)
+      : relu ? launch_relu_state_bf16(k, v, partials, plan, s) : launch_state_partials_bf16(k, v, desc.wk, partials, plan, s);
+  if (e != hipSuccess) return LINATTN_E_HIP;
+  ev.mark(1, s);
+  e = launch_state_reduce_split(partials, state, plan, s);
+  if (e != hipSuccess) return LINATTN_E_HIP;
+  ev.mark(2, s);
+  e = f32_math ? launch_apply_f32(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s)
+               : launch_apply_bf16(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s);
+  if (e != hipSuccess) return LINATTN_E_HIP;
   ev.mark(3, s);
   return LINATTN_OK;
 }

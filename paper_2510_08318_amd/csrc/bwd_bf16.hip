@@ -932,10 +932,6 @@ constexpr size_t k_smem() {
                           + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64) + (D + 8) * sizeof(float)
        + (DW ? (size_t)kTile * D * 2 + DwTile<D, NTK / 64>::DU_BYTES : 0);
 }
-template <auto Kernel>
-struct KernelTag {
-  static constexpr auto value = Kernel;
-};
 template <int D, bool CENTRE>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;

@@ -1,308 +1,466 @@
-// fp32-arithmetic backward path: plain FMA on LDS tiles of 16 tokens, on fp32 tensors (no bf16/fp16
-// anywhere: the 1e-5 accuracy contract) or on bf16 tensors widened on load and rounded on store
-// (LINATTN_BF16_F32MATH).  Same mathematics as bwd_bf16.hip (chain rule through Eq. 3 and Eq. 5); not
-// tuned for bandwidth.
+// fp32-arithmetic backward path, on fp32 tensors (the 1e-5 accuracy contract) or on bf16 tensors (LINATTN_BF16_F32MATH), every
+// product on exact bf16 pieces (f32_split.h).  Same mathematics as bwd_bf16.hip (chain rule through Eq. 3 and Eq. 5):
+//   grad_f32_kernel, query side : phi(q), den, G = dO S^T, delta = phi . G / den, dL/dphi = (G - delta z) / den, du, dq
+//   state_f32_kernel (weighted) : dS = sum phi(q)^T dO / den, dz = -sum phi(q) delta / den; split-n partials, reduced
+//   apply_f32_kernel (dv)       : dv = phi(k) dS
+//   grad_f32_kernel, key side   : phi(k), dL/dphi = v dS^T + dz, du, dk
+//   dw_f32_kernel               : dW~ = sum x^T du, both sides, from the du rows the two passes above leave in the workspace
+// The three pieces of one state image and of W~ fill the LDS of a compute unit (144 KB at width 128), which is why the sum over
+// tokens and dv are passes of their own.  delta needs no o: phi . (S dO) is o . dO times den.
 #include "kernels.h"
-#include "f32_common.h"
+#include "f32_split.h"
+#include "f32_state.h"
+#include "f32_apply.h"
 
 namespace linattn {
 namespace {
 
 using namespace f32;
-constexpr int TB = 16;        // tokens per tile
-constexpr int TPT = NT / TB;  // threads per token (16)
 
-// du for a tile: sG [TB][D] = dL/dphi, sPhi [TB][D] = phi; writes sDU [TB][D/2].
-// Contains __syncthreads(); sC: [TB][2] scratch.
+// W~ of one head -> pieces of the B operands of dX = dU W~^T in LDS: entry (ks, mb, lane = (c, g)) holds
+// W~[channel_cols(mb, c)][g*LOC + 8ks + e], e = 0..7.  The same entries serve the projection: a transposing read of four of them
+// gives four channels of four adjacent features.  The lane index is XORed so that both kinds of read spread over the banks.
 template <int D>
-__device__ __forceinline__ void jacobian_tile(const float* sG, const float* sPhi, float* sDU, float* sC, int tid) {
-  constexpr int HALF = D / 2;
-  if (tid < 2 * TB) {
-    const int tt = tid / 2, half = tid % 2;
-    float c = 0.f;
-    for (int a = 0; a < HALF; ++a) c = fmaf(sG[tt * D + half * HALF + a], sPhi[tt * D + half * HALF + a], c);
-    sC[tt * 2 + half] = c;
+struct WImage {
+  using C = Cfg<D>;
+  using L = ApplyLayout<D>;
+  static constexpr int KS = C::LOC / 8;
+  static constexpr int IMG = KS * L::MB * 64;                     // 16-byte entries of one piece (= Cfg<D>::W_IMG)
+  static __device__ __forceinline__ int place(int ks, int mb, int lane) {
+    return (ks * L::MB + mb) * 64 + (lane ^ (2 * mb + lane / 32 + 8 * (ks & 1)));
   }
-  __syncthreads();
-  for (int i = tid; i < TB * HALF; i += NT) {
-    const int tt = i / HALF, a = i % HALF;
-    sDU[tt * HALF + a] = sPhi[tt * D + a] * (sG[tt * D + a] - sC[tt * 2])
-                       - sPhi[tt * D + HALF + a] * (sG[tt * D + HALF + a] - sC[tt * 2 + 1]);
-  }
-  __syncthreads();
-}
-
-// dx[tt][c] = sum_a du[tt][a] W[c][a], stored for valid tokens; optional copy of du to the workspace.
-template <int D, typename T>
-__device__ __forceinline__ void dx_tile(const float* sDU, const float* sW, T* xout, size_t sn, float* du_ws,
-                                        int t0, int n_valid, int tid) {
-  constexpr int HALF = D / 2;
-  const int tt = tid / TPT, cb = tid % TPT;
-  if (tt < n_valid) {
-#pragma unroll 1
-    for (int j = 0; j < D / TPT; ++j) {
-      const int c = cb + TPT * j;
-      float acc = 0.f;
-      for (int a = 0; a < HALF; ++a) acc = fmaf(sDU[tt * HALF + a], sW[c * HALF + a], acc);
-      stf(xout, (size_t)(t0 + tt) * sn + c, acc);
+  template <typename T, int NTHREADS>
+  static __device__ __forceinline__ void build(const T* __restrict__ w, uint4* sW, int tid) {
+    for (int it = tid; it < IMG; it += NTHREADS) {
+      const int lane = it % 64, mb = (it / 64) % L::MB, ks = it / (64 * L::MB);
+      const T* src = w + L::channel_cols(mb, lane % 32) * C::HALF + (lane / 32) * C::LOC + 8 * ks;
+      uint4* dst = sW + place(ks, mb, lane);
+      if constexpr (sizeof(T) == 2) {
+        *dst = *reinterpret_cast<const uint4*>(src);
+      } else {
+        float v[8];
+        unpack_f32x4(reinterpret_cast<const uint4*>(src)[0], v);
+        unpack_f32x4(reinterpret_cast<const uint4*>(src)[1], v + 4);
+        uint4 p[3];
+        split8(v, p);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) dst[i * IMG] = p[i];
+      }
     }
-    if (du_ws)
-      for (int a = cb; a < HALF; a += TPT) du_ws[(size_t)(t0 + tt) * HALF + a] = sDU[tt * HALF + a];
+  }
+  // A operand (ks, mbu) of U^T = W~^T X^T, piece p.  Lane (s = lane%16, j = (lane/16)%2, g = lane/32) points at channel
+  // 16ks + 8g + 4h + s/4 and the four features (s%2)*LOC + 16mbu + 8j + 4*((s/2)%2) of the half h of the operand.
+  static __device__ __forceinline__ uint4 project_operand(const uint4* sW, int p, int ks, int mbu, int lane) {
+    const int s = lane % 16, j = (lane / 16) % 2, g = lane / 32;
+    const int fixed = (2 * mbu + j) * L::MB * 64 * 16 + 8 * ((s / 2) % 2) + 512 * (s % 2);
+    int off[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int channel = 16 * ks + 8 * g + 4 * h + s / 4;
+      const int mb = channel % L::MB, c = channel / L::MB;
+      off[h] = fixed + mb * 1024 + ((c ^ (2 * mb + s % 2 + 8 * j)) << 4);
+    }
+    return __builtin_bit_cast(uint4, read_tr(reinterpret_cast<const char*>(sW + p * IMG), off[0], off[1]));
+  }
+  template <typename T>
+  static __device__ __forceinline__ void project(const RowOctets<D, T>& x, const uint4* sW, int lane, f32x16 (&u)[C::UM][1]) {
+    constexpr int NX = kPieces<T>;
+#pragma unroll
+    for (int mb = 0; mb < C::UM; ++mb) u[mb][0] = zero16();
+#pragma unroll
+    for (int ks = 0; ks < C::UK; ++ks) {
+      uint4 b[1][NX], a[C::UM][NX];
+      x.pieces(ks, b[0]);
+#pragma unroll
+      for (int mb = 0; mb < C::UM; ++mb)
+#pragma unroll
+        for (int i = 0; i < NX; ++i) a[mb][i] = project_operand(sW, i, ks, mb, lane);
+      mfma_pieces<NX, NX>(a, b, u);
+    }
+  }
+};
+
+// State (S or dS) of one head -> pieces of the A operands of G^T = M Y^T in LDS: entry (ks, mb, lane = (m, g)) holds
+// M[row(mb, m)][16ks + 8g + e]; the rows are ordered so that accumulator register r of block mb is element 16mb + r of the lane's phi.
+template <int D, int KIND, int NTHREADS>
+__device__ __forceinline__ void build_g_pieces(const float* __restrict__ M, uint4* sG, int tid) {
+  constexpr int MB = D / 32, IMG = (D / 16) * MB * 64;
+  for (int it = tid; it < IMG; it += NTHREADS) {
+    const int lane = it % 64, mb = (it / 64) % MB, ks = it / (64 * MB);
+    const int m = lane % 32, r = 4 * (m / 8) + m % 4;
+    const int row = phi_feature<D, KIND>(2 * mb + r / 8, (m / 4) % 2) + r % 8;
+    const uint4* src = reinterpret_cast<const uint4*>(M + row * D + 16 * ks + 8 * (lane / 32));
+    float v[8];
+    unpack_f32x4(src[0], v);
+    unpack_f32x4(src[1], v + 4);
+    uint4 p[3];
+    split8(v, p);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) sG[i * IMG + it] = p[i];
   }
 }
 
 template <int D, int KIND, typename T>
-__global__ __launch_bounds__(NT) void bwd_q_f32_kernel(const T* __restrict__ q, const T* __restrict__ dout,
-                                                       const T* __restrict__ wq, const float* __restrict__ state,
-                                                       T* __restrict__ dq, float* __restrict__ partials,
-                                                       float* __restrict__ du_ws,
-                                                       const T* __restrict__ blend, const float* __restrict__ rptr,
-                                                       float* __restrict__ dr_part,
-                                                       int H, int n, int P, int chunk, Rows rw) {
-  constexpr int HALF = D / 2;
-  constexpr int BLK = D / 16;
-  constexpr int SS = D + 1;                 // row stride of the state copy (bank spread)
-  extern __shared__ float smem[];
-  float* sW = smem;                         // [D][HALF]
-  float* sS = sW + D * HALF;                // [D+1][SS]
-  float* sX = sS + (D + 1) * SS;            // [TB][D+1]
-  float* sPhi = sX + TB * (D + 1);          // [TB][D]
-  float* sDO = sPhi + TB * D;               // [TB][D]   dO, later dO / den
-  float* sG = sDO + TB * D;                 // [TB][D]   o, then g
-  float* sDU = sG + TB * D;                 // [TB][HALF]
-  float* sDen = sDU + TB * HALF;            // [TB]
-  float* sDel = sDen + TB;                  // [TB]
-  float* sC = sDel + TB;                    // [TB][2]
+constexpr size_t grad_smem() {
+  return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * (D / 16) * (D / 32) * 64) * sizeof(uint4) + (D + 8) * sizeof(float);
+}
 
-  const int tid = threadIdx.x;
-  const int bh = blockIdx.y, p = blockIdx.x, h = bh % H;
-  const int t_begin = p * chunk, t_end = min(n, t_begin + chunk);
-  const T* qb = q + head_base(rw, bh, H);
-  const T* dob = dout + head_base(rw, bh, H);
-  T* dqb = dq + head_base(rw, bh, H);
-  // mixed attention (Eq. 6), off when blend is null: dout is the gradient of the mixed output
-  const T* bb = blend ? blend + head_base(rw, bh, H) : nullptr;
-  const float om = blend ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;
+// 8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks (a lane pair owns a token).
+// QSIDE: x = q, y = dO, M = (S, z); leaves the weights of the sum over tokens, {om / den, -om delta / den}, in weights[bh][t] and
+// (BLEND) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.
+// Key side: x = k, y = v, M = (dS, dz).  du_ws (nullable): dL/du rows for dW~.
+template <int D, int KIND, typename T, bool QSIDE, bool BLEND>
+__global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
+                                                       const float* __restrict__ state, T* __restrict__ dx, float* __restrict__ du_ws,
+                                                       float2* __restrict__ weights, const T* __restrict__ blend,
+                                                       const float* __restrict__ rptr, float* __restrict__ dr_part,
+                                                       int H, int n, Rows rw) {
+  using C = Cfg<D>;
+  using L = ApplyLayout<D>;
+  using W = WImage<D>;
+  constexpr int MB = L::MB, IMG = (D / 16) * MB * 64, NX = kPieces<T>;
+  extern __shared__ uint4 smem[];
+  uint4* sW = smem;
+  uint4* sG = sW + (KIND == kPhiRelu ? 0 : NX * W::IMG);
+  float* sZ = reinterpret_cast<float*>(sG + 3 * IMG);
+  float* sRed = sZ + D;
+
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int g = lane / 32, c = lane % 32;
+  const int bh = blockIdx.y, h = bh % H;
+  const T* xb = x + head_base(rw, bh, H);
+  const T* yb = y + head_base(rw, bh, H);
+  T* dxb = dx + head_base(rw, bh, H);
+  const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+  const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;
   float dr_acc = 0.f;
-  const T* wb = wq + (size_t)h * D * HALF;
   const float* sb = state + (size_t)bh * (D + 1) * D;
-  if constexpr (KIND == kPhiHedgehog)
-    for (int i = tid; i < D * HALF; i += NT) sW[i] = ldf(wb, i);
-  for (int i = tid; i < (D + 1) * D; i += NT) sS[(i / D) * SS + (i % D)] = sb[i];
 
-  float acc[BLK][BLK];
-#pragma unroll
-  for (int i = 0; i < BLK; ++i)
-#pragma unroll
-    for (int j = 0; j < BLK; ++j) acc[i][j] = 0.f;
-  float zacc = 0.f;
-  const int f0 = (tid / 16) * BLK, c0 = (tid % 16) * BLK;
-  const int tt = tid / TPT, cb = tid % TPT;
+  const int nblk = (n + 31) / 32, stride = gridDim.x * (NT8 / 64);
+  RowOctets<D, T> xr, yr;
+  auto row_of = [&](const T* base, int b) {
+    const int t = b * 32 + c;
+    return base + (size_t)(t < n ? t : n - 1) * rw.sn;
+  };
+  int b = blockIdx.x * (NT8 / 64) + w;
+  const int b_first = b < nblk ? b : nblk - 1;
+  xr.load(row_of(xb, b_first), g);
+  if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
+  build_g_pieces<D, KIND, NT8>(sb, sG, tid);
+  build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
+  __syncthreads();
 
-  for (int t0 = t_begin; t0 < t_end; t0 += TB) {
-    const int n_valid = min(TB, t_end - t0);
-    __syncthreads();
-    for (int i = tid; i < TB * D; i += NT) {
-      const int r = i / D, c = i % D;
-      const bool valid = r < n_valid;
-      sX[r * (D + 1) + c] = valid ? ldf(qb, (size_t)(t0 + r) * rw.sn + c) : 0.f;
-      sDO[r * D + c] = valid ? ldf(dob, (size_t)(t0 + r) * rw.sn + c) : 0.f;
-    }
-    __syncthreads();
-    phi_tile<D, TB, KIND>(sX, sW, sPhi, tid, n_valid);     // rows >= n_valid are zero
-    // o = phi S / den  -> sG, den -> sDen
-    {
-      float den = 0.f;
-      for (int f = 0; f < D; ++f) den = fmaf(sPhi[tt * D + f], sS[D * SS + f], den);
-      if constexpr (KIND == kPhiRelu) den += kReluEps;
-      const float inv = tt < n_valid ? 1.0f / den : 0.f;
-#pragma unroll 1
-      for (int j = 0; j < D / TPT; ++j) {
-        const int c = cb + TPT * j;
-        float a = 0.f;
-        for (int f = 0; f < D; ++f) a = fmaf(sPhi[tt * D + f], sS[f * SS + c], a);
-        sG[tt * D + c] = a * inv;
-      }
-      if (cb == 0) sDen[tt] = tt < n_valid ? den : 1.f;
-    }
-    __syncthreads();
-    if (tid < TB) {
-      float dl = 0.f;
-      for (int c = 0; c < D; ++c) dl = fmaf(sDO[tid * D + c], sG[tid * D + c], dl);
-      if (bb) {
-        if (tid < n_valid) {
-          float ds = 0.f;
-          for (int c = 0; c < D; ++c) ds = fmaf(sDO[tid * D + c], ldf(bb, (size_t)(t0 + tid) * rw.sn + c), ds);
-          dr_acc += ds - dl;
-        }
-        for (int c = 0; c < D; ++c) sDO[tid * D + c] *= om;
-        dl *= om;
-      }
-      sDel[tid] = dl;
-    }
-    __syncthreads();
-    // g = (dO S^T - delta z) / den  -> sG (o is dead)
-    {
-      const float inv = 1.0f / sDen[tt];
-      const float dl = sDel[tt];
-      float gv[D / TPT];
-#pragma unroll 1
-      for (int j = 0; j < D / TPT; ++j) {
-        const int f = cb + TPT * j;
-        float a = 0.f;
-        for (int c = 0; c < D; ++c) a = fmaf(sDO[tt * D + c], sS[f * SS + c], a);
-        gv[j] = (a - dl * sS[D * SS + f]) * inv;
-      }
-      __syncthreads();
+  for (; b < nblk; b += stride) {
+    const int t = b * 32 + c;
+    const bool valid = t < n;
+    yr.load(row_of(yb, b), g);
+    float ds = 0.f;                                                // dO . s on the lane's channels, while few registers are live
+    if constexpr (BLEND) {
+      RowOctets<D, T> sr;
+      sr.load(row_of(bb, b), g);
 #pragma unroll
-      for (int j = 0; j < D / TPT; ++j) sG[tt * D + cb + TPT * j] = gv[j];
-      // dO / den in place (operand of dS); delta / den
-#pragma unroll 1
-      for (int j = 0; j < D / TPT; ++j) sDO[tt * D + cb + TPT * j] *= inv;
-      if (cb == 0) sDel[tt] = dl * inv;
+      for (int ks = 0; ks < D / 16; ++ks) {
+        float a[8], s8[8];
+        yr.values(ks, a);
+        sr.values(ks, s8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ds = fmaf(a[e], s8[e], ds);
+      }
     }
-    __syncthreads();
-    if constexpr (KIND == kPhiRelu) {
-      // dq = g where q > 0 (this thread wrote these entries of sG itself)
-      if (tt < n_valid)
-        for (int j = 0; j < D / TPT; ++j) {
-          const int c = cb + TPT * j;
-          stf(dqb, (size_t)(t0 + tt) * rw.sn + c, sX[tt * (D + 1) + c] > 0.f ? sG[tt * D + c] : 0.f);
+    float f[D / 2];
+    if constexpr (KIND == kPhiHedgehog) {
+      f32x16 u[C::UM][1];
+      W::template project<T>(xr, sW, lane + opaque_zero(), u);
+      softmax_octets<D>(u, f);
+    } else {
+      phi_octets<D, KIND, T>(xr, nullptr, lane, f);
+    }
+    float inv = 0.f;
+    const float* z = sZ + opaque_zero();
+    if constexpr (QSIDE) inv = 1.0f / (octet_dot<D>(f, z, g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+
+    // G = y M^T on the lane's features
+    f32x16 ga[MB][1];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) ga[mb][0] = zero16();
+    const uint4* sg = sG + lane + opaque_zero();
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      uint4 a[MB][3], yp[1][NX];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) a[mb][i] = sg[i * IMG + (ks * MB + mb) * 64];
+      yr.pieces(ks, yp[0]);
+      mfma_pieces<3, NX>(a, yp, ga);
+    }
+    float gr[D / 2];
+    if constexpr (QSIDE) {
+      float part = 0.f;
+#pragma unroll
+      for (int i = 0; i < D / 2; ++i) part = fmaf(f[i], ga[i / 16][0][i % 16], part);
+      part *= inv;
+      if constexpr (BLEND) {
+        if (valid) dr_acc += ds - part;
+      }
+      float lo, hi;
+      pair32(part, lo, hi);
+      const float delta = lo + hi;
+      const float a = inv * om;
+      if (valid && g == 0) weights[(size_t)bh * n + t] = make_float2(a, -delta * a);
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int i = 8 * ks + e;
+          gr[i] = (ga[i / 16][0][i % 16] - delta * z[(2 * ks + g) * 8 + e]) * a;
         }
     } else {
-      jacobian_tile<D>(sG, sPhi, sDU, sC, tid);
-      dx_tile<D, T>(sDU, sW, dqb, rw.sn, du_ws ? du_ws + (size_t)bh * n * HALF : nullptr, t0, n_valid, tid);
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int i = 8 * ks + e;
+          gr[i] = ga[i / 16][0][i % 16] + z[(2 * ks + g) * 8 + e];
+        }
     }
-    // dS += phi^T (dO / den), dz -= phi * (delta / den)
-    for (int r = 0; r < TB; ++r) {
-      float a[BLK], b[BLK];
-#pragma unroll
-      for (int i = 0; i < BLK; ++i) a[i] = sPhi[r * D + f0 + i];
-#pragma unroll
-      for (int j = 0; j < BLK; ++j) b[j] = sDO[r * D + c0 + j];
-#pragma unroll
-      for (int i = 0; i < BLK; ++i)
-#pragma unroll
-        for (int j = 0; j < BLK; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    if (tid < D)
-      for (int r = 0; r < TB; ++r) zacc = fmaf(-sPhi[r * D + tid], sDel[r], zacc);
-  }
 
-  float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
+    if constexpr (KIND == kPhiRelu) {
+      // the derivative of max(x, 0) at 0 is 0; the lane's octets of its own row
+      if (valid) {
+        T* row = dxb + (size_t)t * rw.sn;
 #pragma unroll
-  for (int i = 0; i < BLK; ++i)
+        for (int ks = 0; ks < D / 16; ++ks) {
+          float v[8];
 #pragma unroll
-    for (int j = 0; j < BLK; ++j) dst[(f0 + i) * D + c0 + j] = acc[i][j];
-  if (tid < D) dst[D * D + tid] = zacc;
-  if (bb) {
-    __syncthreads();
-    if (tid < TB) sC[tid] = dr_acc;
+          for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] > 0.f ? gr[8 * ks + e] : 0.f;
+          uint4* dst = reinterpret_cast<uint4*>(row + 16 * ks + 8 * g);
+          if constexpr (sizeof(T) == 2) {
+            *dst = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+          } else {
+            float4* d4 = reinterpret_cast<float4*>(dst);
+            d4[0] = make_float4(v[0], v[1], v[2], v[3]);
+            d4[1] = make_float4(v[4], v[5], v[6], v[7]);
+          }
+        }
+      }
+      xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
+    } else {
+      xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
+      // softmax Jacobian of Eq. 5
+      float cp = 0.f, cm = 0.f;
+#pragma unroll
+      for (int j = 0; j < C::LOC; ++j) { cp = fmaf(gr[j], f[j], cp); cm = fmaf(gr[C::LOC + j], f[C::LOC + j], cm); }
+      float lo, hi;
+      pair32(cp, lo, hi); cp = lo + hi;
+      pair32(cm, lo, hi); cm = lo + hi;
+      float du[C::LOC];
+#pragma unroll
+      for (int j = 0; j < C::LOC; ++j) du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
+      if (du_ws != nullptr && valid) {
+        float4* dst = reinterpret_cast<float4*>(du_ws + ((size_t)bh * n + t) * C::HALF + g * C::LOC);
+#pragma unroll
+        for (int j = 0; j < C::LOC / 4; ++j) dst[j] = make_float4(du[4 * j], du[4 * j + 1], du[4 * j + 2], du[4 * j + 3]);
+      }
+      // dx = du W~^T, tokens on the accumulator rows
+      f32x16 xa[1][MB];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) xa[0][mb] = zero16();
+      const int lz = lane + opaque_zero();
+#pragma unroll
+      for (int ks = 0; ks < W::KS; ++ks) {
+        uint4 a[1][3], wb[MB][NX];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int i = 0; i < NX; ++i) wb[mb][i] = sW[i * W::IMG + W::place(ks, mb, lz)];
+        split8(du + 8 * ks, a[0]);
+        mfma_pieces<3, NX>(a, wb, xa);
+      }
+      store_rows<D, T>(dxb, rw.sn, b * 32, n, lane, [&](int r, int mb) { return xa[0][mb][r]; });
+    }
+  }
+  if constexpr (BLEND) {
+    for (int m = 32; m >= 1; m >>= 1) dr_acc += __shfl_xor(dr_acc, m, 64);
+    if (lane == 0) sRed[w] = dr_acc;
     __syncthreads();
     if (tid == 0) {
-      float t = 0.f;
-      for (int i = 0; i < TB; ++i) t += sC[i];
-      dr_part[(size_t)bh * P + p] = t;
+      float s = 0.f;
+      for (int i = 0; i < NT8 / 64; ++i) s += sRed[i];
+      dr_part[(size_t)bh * gridDim.x + blockIdx.x] = s;
     }
   }
 }
 
-template <int D, int KIND, typename T>
-__global__ __launch_bounds__(NT) void bwd_k_f32_kernel(const T* __restrict__ k, const T* __restrict__ v,
-                                                       const T* __restrict__ wk, const float* __restrict__ dstate,
-                                                       T* __restrict__ dk, T* __restrict__ dv,
-                                                       float* __restrict__ du_ws, int H, int n, int chunk, Rows rw) {
-  constexpr int HALF = D / 2;
-  constexpr int SS = D + 1;
-  extern __shared__ float smem[];
-  float* sW = smem;
-  float* sS = sW + D * HALF;                // dS, dz  [D+1][SS]
-  float* sX = sS + (D + 1) * SS;            // [TB][D+1]
-  float* sPhi = sX + TB * (D + 1);
-  float* sV = sPhi + TB * D;
-  float* sG = sV + TB * D;
-  float* sDU = sG + TB * D;
-  float* sC = sDU + TB * HALF;
+// Partial dW~ = sum over a share of the tokens of x^T du; grid (P, BH, 2): z = 0 the query side, 1 the key side.  A wavefront takes
+// steps of 16 tokens: its lanes read eight tokens of MB adjacent channels and of NB adjacent features straight from memory, which
+// is the operand layout of both, so nothing goes through LDS before the wavefronts' sums are combined.
+template <int D, typename T>
+__global__ __launch_bounds__(NT8) void dw_f32_kernel(const T* __restrict__ q, const T* __restrict__ k, const float* __restrict__ du_q,
+                                                     const float* __restrict__ du_k, float* __restrict__ part_q,
+                                                     float* __restrict__ part_k, int H, int n, Rows rw) {
+  using C = Cfg<D>;
+  constexpr int MB = D / 32, NB = C::HALF / 32, NX = kPieces<T>;
+  const float* du = blockIdx.z ? du_k : du_q;
+  if (du == nullptr) return;
+  extern __shared__ uint4 smem[];
+  float* sAcc = reinterpret_cast<float*>(smem);                   // [4 wavefronts][MB*NB*16][64]
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int g = lane / 32, c = lane % 32;
+  const int bh = blockIdx.y;
+  const T* xb = (blockIdx.z ? k : q) + head_base(rw, bh, H) + MB * c;
+  const float* ub = du + (size_t)bh * n * C::HALF + NB * c;
+  typedef float cols __attribute__((ext_vector_type(NB)));
+  typedef float xf __attribute__((ext_vector_type(MB)));
+  typedef unsigned xh __attribute__((ext_vector_type(MB / 2)));
 
-  const int tid = threadIdx.x;
-  const int bh = blockIdx.y, p = blockIdx.x, h = bh % H;
-  const int t_begin = p * chunk, t_end = min(n, t_begin + chunk);
-  const T* kb = k + head_base(rw, bh, H);
-  const T* vb = v + head_base(rw, bh, H);
-  T* dkb = dk + head_base(rw, bh, H);
-  T* dvb = dv + head_base(rw, bh, H);
-  const T* wb = wk + (size_t)h * D * HALF;
-  const float* sb = dstate + (size_t)bh * (D + 1) * D;
-  if constexpr (KIND == kPhiHedgehog)
-    for (int i = tid; i < D * HALF; i += NT) sW[i] = ldf(wb, i);
-  for (int i = tid; i < (D + 1) * D; i += NT) sS[(i / D) * SS + (i % D)] = sb[i];
-  const int tt = tid / TPT, cb = tid % TPT;
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = zero16();
 
-  for (int t0 = t_begin; t0 < t_end; t0 += TB) {
-    const int n_valid = min(TB, t_end - t0);
-    __syncthreads();
-    for (int i = tid; i < TB * D; i += NT) {
-      const int r = i / D, c = i % D;
-      const bool valid = r < n_valid;
-      sX[r * (D + 1) + c] = valid ? ldf(kb, (size_t)(t0 + r) * rw.sn + c) : 0.f;
-      sV[r * D + c] = valid ? ldf(vb, (size_t)(t0 + r) * rw.sn + c) : 0.f;
+  const int steps = (n + 15) / 16, stride = gridDim.x * (NT8 / 64);
+  constexpr int XW = MB * sizeof(T) / 4;
+  struct Step { uint32_t x[8][XW]; cols u[8]; };
+  Step cur, nxt;
+  auto load = [&](Step& s, int st) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int t = 16 * st + 8 * g + e;
+      const size_t tc = t < n ? t : n - 1;
+      if constexpr (sizeof(T) == 4) {
+        const xf r = *reinterpret_cast<const xf*>(xb + tc * rw.sn);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) s.x[e][i] = __builtin_bit_cast(uint32_t, (float)r[i]);
+      } else {
+        const xh r = *reinterpret_cast<const xh*>(xb + tc * rw.sn);
+#pragma unroll
+        for (int i = 0; i < MB / 2; ++i) s.x[e][i] = r[i];
+      }
+      s.u[e] = *reinterpret_cast<const cols*>(ub + tc * C::HALF);
     }
-    __syncthreads();
-    phi_tile<D, TB, KIND>(sX, sW, sPhi, tid, n_valid);
-    // dv = phi dS ; g = v dS^T + dz
-#pragma unroll 1
-    for (int j = 0; j < D / TPT; ++j) {
-      const int c = cb + TPT * j;
-      float a = 0.f, gsum = 0.f;
-      for (int f = 0; f < D; ++f) a = fmaf(sPhi[tt * D + f], sS[f * SS + c], a);
-      if (tt < n_valid) stf(dvb, (size_t)(t0 + tt) * rw.sn + c, a);
-      const int f = c;
-      for (int cc = 0; cc < D; ++cc) gsum = fmaf(sV[tt * D + cc], sS[f * SS + cc], gsum);
-      sG[tt * D + f] = gsum + sS[D * SS + f];
-    }
-    __syncthreads();
-    if constexpr (KIND == kPhiRelu) {
-      if (tt < n_valid)
-        for (int j = 0; j < D / TPT; ++j) {
-          const int c = cb + TPT * j;
-          stf(dkb, (size_t)(t0 + tt) * rw.sn + c, sX[tt * (D + 1) + c] > 0.f ? sG[tt * D + c] : 0.f);
-        }
+  };
+  const float sign = w % 2 ? -1.f : 1.f;         // odd wavefronts sum the negated products (see the head of f32_split.h)
+  int st = blockIdx.x * (NT8 / 64) + w;
+  load(cur, st < steps ? st : steps - 1);
+  for (; st < steps; st += stride) {
+    load(nxt, st + stride < steps ? st + stride : st);
+    uint4 a[MB][NX], b[NB][3];
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(float, cur.x[e][i]);
+        split8(v, a[i]);
+      }
     } else {
-      jacobian_tile<D>(sG, sPhi, sDU, sC, tid);
-      dx_tile<D, T>(sDU, sW, dkb, rw.sn, du_ws ? du_ws + (size_t)bh * n * HALF : nullptr, t0, n_valid, tid);
+#pragma unroll
+      for (int i = 0; i < MB / 2; ++i) {
+        uint32_t lo[4], hi[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          lo[e] = (cur.x[2 * e][i] & 0xffffu) | (cur.x[2 * e + 1][i] << 16);
+          hi[e] = (cur.x[2 * e][i] >> 16) | (cur.x[2 * e + 1][i] & 0xffff0000u);
+        }
+        a[2 * i][0] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        a[2 * i + 1][0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = 16 * st + 8 * g + e < n ? cur.u[e][j] * sign : 0.f;
+      split8(v, b[j]);
+    }
+    mfma_pieces<NX, 3>(a, b, acc);
+    cur = nxt;
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] *= sign;
+  // sums of the eight wavefronts, pairwise
+  constexpr int PER = MB * NB * 16;
+#pragma unroll
+  for (int half = 4; half >= 1; half >>= 1) {
+    __syncthreads();
+    if (w >= half && w < 2 * half) {
+      float* dst = sAcc + (size_t)(w - half) * PER * 64 + lane;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dst[((i * NB + j) * 16 + r) * 64] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (w < half) {
+      const float* src = sAcc + (size_t)w * PER * 64 + lane;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += src[((i * NB + j) * 16 + r) * 64];
     }
   }
+  if (w == 0) {
+    float* part = (blockIdx.z ? part_k : part_q) + ((size_t)bh * gridDim.x + blockIdx.x) * (size_t)D * C::HALF;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int channel = MB * (8 * (r / 4) + 4 * g + (r % 4)) + i;
+        cols v;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) v[j] = acc[i][j][r];
+        *reinterpret_cast<cols*>(part + channel * C::HALF + NB * c) = v;
+      }
+  }
 }
-
 template <int D>
-constexpr size_t q_smem() {
-  return sizeof(float) * (D * (D / 2) + (D + 1) * (D + 1) + TB * (D + 1) + 3 * TB * D + TB * (D / 2) + 4 * TB);
-}
-template <int D>
-constexpr size_t k_smem() {
-  return sizeof(float) * (D * (D / 2) + (D + 1) * (D + 1) + TB * (D + 1) + 3 * TB * D + TB * (D / 2) + 2 * TB);
-}
+constexpr size_t dw_smem() { return (size_t)4 * (D / 32) * (D / 64) * 16 * 64 * sizeof(float); }
 
 template <int D, int KIND, typename T>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  const dim3 grid(p.P, p.BH);
-  constexpr bool kBf16 = sizeof(T) == 2;
-  if ((e = set_smem_once<bwd_q_f32_kernel<D, KIND, T>>(q_smem<D>())) != hipSuccess) return e;
-  bwd_q_f32_kernel<D, KIND, T><<<grid, NT, q_smem<D>(), s>>>((const T*)a.q, (const T*)a.dout, (const T*)a.wq, a.state,
-                                                    (T*)a.dq, a.partials, a.dwq ? a.du_q : nullptr,
-                                                    (const T*)a.blend_in, a.blend_r, a.dr_part, p.H, p.n, p.P, p.chunk, p.rows);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (a.blend_in && a.blend_dr && (e = launch_dr_reduce(a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr, s)) != hipSuccess) return e;
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_state_reduce(a.partials, a.dstate, p, s)) != hipSuccess) return e;
-  if ((e = set_smem_once<bwd_k_f32_kernel<D, KIND, T>>(k_smem<D>())) != hipSuccess) return e;
-  bwd_k_f32_kernel<D, KIND, T><<<grid, NT, k_smem<D>(), s>>>((const T*)a.k, (const T*)a.v, (const T*)a.wk, a.dstate,
-                                                    (T*)a.dk, (T*)a.dv, a.dwk ? a.du_k : nullptr, p.H, p.n, p.chunk, p.rows);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const dim3 grid(p.KP, p.BH);
+  constexpr size_t smem = grad_smem<D, KIND, T>();
+  // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which is written last
+  float2* weights = static_cast<float2*>(a.dv);
+  auto grad = [&](auto kernel, const void* x, const void* y, const void* wx, const float* state, void* dx, float* du) -> hipError_t {
+    hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
+    if (e2 != hipSuccess) return e2;
+    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, du, weights,
+                                                    (const T*)a.blend_in, a.blend_r, a.dr_part, p.H, p.n, p.rows);
+    return hipGetLastError();
+  };
+  float* du_q = a.dwq ? a.du_q : nullptr;
+  float* du_k = a.dwk ? a.du_k : nullptr;
+  if (KIND == kPhiHedgehog && a.blend_in)
+    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, KIND == kPhiHedgehog>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
+  else
+    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, false>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
+  if (e != hipSuccess) return e;
+  if (a.blend_in && a.blend_dr && (e = launch_dr_reduce(a.dr_part, p.BH * p.KP, a.blend_r, a.blend_dr, s)) != hipSuccess) return e;
+  if ((e = run_state_pass<D, KIND, T, true>(a.q, a.dout, a.wq, weights, a.partials, p, s)) != hipSuccess) return e;
+  if ((e = launch_state_reduce_split(a.partials, a.dstate, p, s)) != hipSuccess) return e;
+  e = grad(KernelTag<grad_f32_kernel<D, KIND, T, false, false>>{}, a.k, a.v, a.wk, a.dstate, a.dk, du_k);
+  if (e != hipSuccess) return e;
+  if ((e = run_apply_pass<D, KIND, T, false, false>(a.k, a.wk, a.dstate, a.dv, nullptr, nullptr, p, s)) != hipSuccess) return e;
   if constexpr (KIND == kPhiHedgehog) {
-    if (a.dwq && (e = launch_dw(a.q, kBf16, a.du_q, a.dw_part, a.dwq, p, s)) != hipSuccess) return e;
-    if (a.dwk && (e = launch_dw(a.k, kBf16, a.du_k, a.dw_part, a.dwk, p, s)) != hipSuccess) return e;
+    if (du_q || du_k) {
+      if ((e = set_smem_once<dw_f32_kernel<D, T>>(dw_smem<D>())) != hipSuccess) return e;
+      float* part_k = a.dw_part + (size_t)p.BH * p.P * D * (D / 2);
+      dw_f32_kernel<D, T><<<dim3(p.P, p.BH, 2), NT8, dw_smem<D>(), s>>>((const T*)a.q, (const T*)a.k, du_q, du_k, a.dw_part, part_k, p.H, p.n, p.rows);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if ((e = launch_dw_reduce2(a.dw_part, a.dwq, p.P, part_k, a.dwk, p.P, p, s)) != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }

@@ -1,0 +1,101 @@
+// phi(x_i) M for every token, in fp32 arithmetic on the bf16 matrix cores (f32_split.h).
+#pragma once
+#include "f32_split.h"
+
+namespace linattn {
+namespace f32 {
+
+// out = phi(x) M, with NORM divided by phi(x) . z: the query pass (M = S), and without NORM dv = phi(k) dS of the backward.  8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks; LDS holds
+// the pieces of W~_q and of the S image (144 KB for fp32 tensors of width 128).  The normaliser is an in-lane dot product (a
+// lane pair owns the token) and goes into phi before it is split, so the product with S is the output and leaves the
+// accumulators as whole rows.
+template <int D, int KIND, typename T>
+constexpr size_t apply_smem() {
+  return ((KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG) + 3 * ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64) * sizeof(uint4) + D * sizeof(float);
+}
+template <int D, int KIND, typename T, bool NORM, bool BLEND>
+__global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q, const T* __restrict__ wq,
+                                                        const float* __restrict__ state, T* __restrict__ out,
+                                                        const T* __restrict__ blend, const float* __restrict__ rptr,
+                                                        int H, int n, Rows rw) {
+  using L = ApplyLayout<D>;
+  constexpr int IMG = L::KS * L::MB * 64;
+  extern __shared__ uint4 smem[];
+  uint4* sW = smem;
+  uint4* sS = sW + (KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG);
+  float* sZ = reinterpret_cast<float*>(sS + 3 * IMG);
+
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int g = lane / 32, c = lane % 32;
+  const int bh = blockIdx.y, h = bh % H;
+  const T* qb = q + head_base(rw, bh, H);
+  T* ob = out + head_base(rw, bh, H);
+  // mixed attention (Eq. 6): out = r' s + (1 - r') o with r' = clip(r, 0, 1)
+  const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+  const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
+  const float* sb = state + (size_t)bh * (D + 1) * D;
+
+  const int nblk = (n + 31) / 32, stride = gridDim.x * (NT8 / 64);
+  RowOctets<D, T> x;
+  auto load = [&](int b) {
+    const int t = b * 32 + c;
+    x.load(qb + (size_t)(t < n ? t : n - 1) * rw.sn, g);
+  };
+  int b = blockIdx.x * (NT8 / 64) + w;
+  load(b < nblk ? b : nblk - 1);
+  if constexpr (KIND == kPhiHedgehog) build_w_pieces<D, T, NT8>(wq + (size_t)h * D * (D / 2), sW, tid);
+  build_s_pieces<D, KIND, NT8>(sb, sS, tid);
+  if constexpr (NORM) build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
+  __syncthreads();
+
+  for (; b < nblk; b += stride) {
+    float f[D / 2];
+    phi_octets<D, KIND, T>(x, sW, lane, f);
+    load(b + stride < nblk ? b + stride : b);
+    float inv = 1.f;
+    if constexpr (NORM) inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+    f32x16 o[1][L::MB];
+#pragma unroll
+    for (int mb = 0; mb < L::MB; ++mb) o[0][mb] = zero16();
+    const uint4* ss = sS + lane + opaque_zero();
+#pragma unroll
+    for (int ks = 0; ks < L::KS; ++ks) {
+      uint4 a[1][3], s[L::MB][3];
+#pragma unroll
+      for (int mb = 0; mb < L::MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s[mb][i] = ss[i * IMG + (ks * L::MB + mb) * 64];
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = NORM ? f[8 * ks + e] * inv : f[8 * ks + e];
+      split8(v, a[0]);
+      mfma_pieces<3, 3>(a, s, o);
+    }
+    if constexpr (BLEND) {
+      const int t0 = b * 32;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int t = t0 + 8 * (r / 4) + 4 * g + (r % 4);
+        const T* srow = bb + (size_t)(t < n ? t : n - 1) * rw.sn + L::MB * c;
+#pragma unroll
+        for (int mb = 0; mb < L::MB; ++mb) o[0][mb][r] = fmaf(rb, ldf(srow, mb) - o[0][mb][r], o[0][mb][r]);
+      }
+    }
+    store_rows<D, T>(ob, rw.sn, b * 32, n, lane, [&](int r, int mb) { return o[0][mb][r]; });
+  }
+}
+
+template <int D, int KIND, typename T, bool NORM, bool BLEND>
+hipError_t run_apply_pass(const void* q, const void* wq, const float* state, void* out,
+                     const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
+  constexpr size_t smem = apply_smem<D, KIND, T>();
+  const hipError_t e = set_smem_once<apply_f32_kernel<D, KIND, T, NORM, BLEND>>(smem);
+  if (e != hipSuccess) return e;
+  apply_f32_kernel<D, KIND, T, NORM, BLEND><<<dim3(p.KP, p.BH), NT8, smem, s>>>(
+      (const T*)q, (const T*)wq, state, (T*)out, (const T*)blend_in, blend_r, p.H, p.n, p.rows);
+  return hipGetLastError();
+}
+
+}  // namespace f32
+}  // namespace linattn

@@ -506,7 +506,7 @@ __global__ __launch_bounds__(NT1) void state_partials_ws_kernel(const uint16_t* 
   long long lo = split_lo(sp, g);
   const long long hi = split_lo(sp, g + 1);
   while (lo < hi) {
-    const int bh = (int)(lo / sp.ntile);
+    const int bh = split_head(sp, lo);
     const long long head0 = (long long)bh * sp.ntile;
     const long long seg_hi = hi < head0 + sp.ntile ? hi : head0 + sp.ntile;
     const int slot = g - split_owner(sp, head0);

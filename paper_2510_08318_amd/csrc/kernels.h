@@ -43,11 +43,22 @@ struct Split {
   int ntile;        // tiles per (b,h)
   long long T;      // tiles in all
   int PS;           // partial slots per (b,h) (the largest number of workgroups touching one head)
+  bool small;       // T * G < 2^31: the index arithmetic fits 32 bits (a 64-bit division is a hundred dependent instructions, in
+                    // the prologue of every workgroup)
 };
-__host__ __device__ inline long long split_lo(const Split& s, int g) { return (long long)g * s.T / s.G; }
+// a * b / c, all positive
+__host__ __device__ inline long long split_muldiv(const Split& s, long long a, long long b, long long c) {
+  if (s.small) return (long long)((unsigned)a * (unsigned)b / (unsigned)c);
+  return a * b / c;
+}
+__host__ __device__ inline long long split_lo(const Split& s, int g) { return split_muldiv(s, g, s.T, s.G); }
+// the head that tile x belongs to
+__host__ __device__ inline int split_head(const Split& s, long long x) {
+  return s.small ? (int)((unsigned)x / (unsigned)s.ntile) : (int)(x / s.ntile);
+}
 // the workgroup whose range holds tile x
 __host__ __device__ inline int split_owner(const Split& s, long long x) {
-  int g = (int)(x * s.G / s.T);
+  int g = (int)split_muldiv(s, x, s.G, s.T);
   while (g + 1 < s.G && split_lo(s, g + 1) <= x) ++g;
   while (g > 0 && split_lo(s, g) > x) --g;
   return g;
@@ -61,17 +72,15 @@ struct Plan {
   bool centred;      // LINATTN_FLAG_CENTRED (set by the dispatch): phi minus its mean in the sums over tokens, centred operand images
   int BH;
   Rows rows;        // memory layout of the token tensors
-  Split split;      // bf16 forward state pass
-  int P;            // split-n factor (partials per (b,h)) of the fp32 state pass and of the backward
-  int chunk;        // tokens per split, a multiple of kTile (fp32 kernels; the bf16 ones deal tiles round-robin)
-  int QP;           // workgroups per (b,h) of the query pass
-  int qchunk;       // tokens per workgroup of the fp32 query pass
+  Split split;      // state passes (and the weighted one of the fp32-arithmetic backward)
+  int P;            // split-n factor (partials per (b,h)) of the query-side backward and of dW~
+  int QP;           // workgroups per (b,h) of the bf16 query pass
   size_t state_elems;     // (d+1)*d
   size_t off_partials;    // fp32 [BH][max(P, split.PS)][(d+1)*d]
   size_t off_state;       // fp32 [BH][(d+1)*d]   (used when the caller gave no state buffer)
   size_t fwd_bytes;       // end of the two regions above: all the scratch a forward call touches
   // backward only
-  int KP;                 // workgroups per (b,h) of the key-side backward pass
+  int KP;                 // workgroups per (b,h) of the passes with 8 wavefronts, each on its own 32-token blocks
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
   size_t off_gimg;        // fp16 [BH][d*d]       operand image of S for dL/dphi(q) (bf16 mode)
   // operand images built once per head by the backward's prep kernels (bf16 mode)
@@ -114,6 +123,12 @@ struct BwdArgs {
   float* dr_part;
 };
 
+// A kernel instantiation as a value, for launch code shared by several.
+template <auto Kernel>
+struct KernelTag {
+  static constexpr auto value = Kernel;
+};
+
 // Raises a kernel's dynamic-LDS limit to `bytes`, once per kernel instantiation and device: the
 // attribute call is a driver call, and the launchers sit on the enqueue path of every step.
 template <auto Kernel>
@@ -146,17 +161,12 @@ hipError_t launch_apply_bf16(const void* q, const void* wq, const float* state, 
                              const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s);
 
 // ---- backward launchers (enqueue only) --------------------------------------------------
-// dw[H][d][d/2] = sum over batch and tokens of x^T du; x is [B,H,n,d] bf16 or fp32, du fp32 [B,H,n,d/2].
-// dw[h][e] = sum over b, then over the P splits, of part[(b*H+h)][p][e].
-hipError_t launch_dw_reduce(const float* part, float* dw, const Plan& p, hipStream_t s);
-// The same for two (partials, output, partials per (b,h)) triples in one launch; a triple whose output is null is skipped.
+// dw0[h][e] = sum over b, then over the P0 splits, of part0[(b*H+h)][p][e], and the same for the second triple in one launch; a
+// triple whose output is null is skipped.
 hipError_t launch_dw_reduce2(const float* part0, float* dw0, int P0, const float* part1, float* dw1, int P1, const Plan& p, hipStream_t s);
-hipError_t launch_dw(const void* x, bool x_is_bf16, const float* du, float* part, float* dw, const Plan& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
 hipError_t launch_bwd_f32(const BwdArgs& a, const Plan& p, hipStream_t s);
 hipError_t launch_relu_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
-// part[0 .. kDotParts-1] = partial sums of sum_i a[i] * b[i] over two contiguous bf16 arrays (elems % 8 == 0).
-hipError_t launch_dot_bf16(const void* a, const void* b, size_t elems, float* part, hipStream_t s);
 // part[0 .. kDotParts-1] = partial sums of sum_i a[i] * (b[i] - vbar[bh(i)][channel(i)]) over two bf16 token tensors in the
 // plan's layout; vbar fp32 [BH][d].
 hipError_t launch_dot_centred_bf16(const void* a, const void* b, const float* vbar, float* part, const Plan& p, hipStream_t s);

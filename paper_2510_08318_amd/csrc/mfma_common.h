@@ -526,6 +526,18 @@ __device__ __forceinline__ float wave_max_paired(float x) {
   return fmaxf(a, b);
 }
 
+// Sum of x over the 32 lanes that share lane/32 (every one of them receives it): DPP inside each
+// row of 16 lanes, then the two rows of a half are exchanged with one permlane16 swap.
+__device__ __forceinline__ float half_wave_sum(float x) {
+  x += dpp_move<0xB1>(x);      // quad_perm [1,0,3,2]
+  x += dpp_move<0x4E>(x);      // quad_perm [2,3,0,1]
+  x += dpp_move<0x124>(x);     // row_ror 4
+  x += dpp_move<0x128>(x);     // row_ror 8
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 1, 3 of the first <-> rows 0, 2 of the second
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
 // Where the stores of token rows past the end of a head go (8 bytes per lane; the contents mean nothing).
 static __device__ __attribute__((aligned(256))) unsigned char g_store_sink[64 * 8];
 

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(NT) void relu_state_kernel(const uint16_t* __restri
   long long lo = split_lo(sp, gi);
   const long long hi = split_lo(sp, gi + 1);
   while (lo < hi) {
-    const int bh = (int)(lo / sp.ntile);
+    const int bh = split_head(sp, lo);
     const long long head0 = (long long)bh * sp.ntile;
     const long long seg_hi = hi < head0 + sp.ntile ? hi : head0 + sp.ntile;
     const int slot = gi - split_owner(sp, head0);
@@ -241,18 +241,6 @@ __global__ __launch_bounds__(PT) void relu_prep_kernel(const float* __restrict__
     r.z = pack_f16x2(scale * row[4], scale * row[5]); r.w = pack_f16x2(scale * row[6], scale * row[7]);
     timg[(size_t)bh * TIMG + idx] = r;
   }
-}
-
-// Sum of x over the 32 lanes that share lane/32 (every one of them receives it): DPP inside each
-// row of 16 lanes, then the two rows of a half are exchanged with one permlane16 swap.
-__device__ __forceinline__ float half_wave_sum(float x) {
-  x += dpp_move<0xB1>(x);      // quad_perm [1,0,3,2]
-  x += dpp_move<0x4E>(x);      // quad_perm [2,3,0,1]
-  x += dpp_move<0x124>(x);     // row_ror 4
-  x += dpp_move<0x128>(x);     // row_ror 8
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 1, 3 of the first <-> rows 0, 2 of the second
-  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
 // One channel (0..3, or 0..1 for d = 64) of a lane's piece of a row, as float.
