@@ -31,12 +31,24 @@ __global__ __launch_bounds__(256) void state_reduce_kernel(const float4* __restr
   auto add = [](float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   float4 acc = zero;
-  for (int p = p_lo; p < p_hi; p += 8) {
+  auto sum8 = [&](const float4 (&t)[8]) {
+    acc = add(acc, add(add(add(t[0], t[1]), add(t[2], t[3])), add(add(t[4], t[5]), add(t[6], t[7]))));
+  };
+  int p = p_lo;
+  for (; p + 8 <= p_hi; p += 8) {
     float4 t[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = p + i < p_hi ? src[(size_t)(p + i) * elems4] : zero;
-    acc = add(acc, add(add(add(t[0], t[1]), add(t[2], t[3])), add(add(t[4], t[5]), add(t[6], t[7]))));
+    for (int i = 0; i < 8; ++i) t[i] = src[(size_t)(p + i) * elems4];
+    sum8(t);
   }
+  if (p + 4 <= p_hi) {
+    float4 t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = src[(size_t)(p + i) * elems4];
+    acc = add(acc, add(add(t[0], t[1]), add(t[2], t[3])));
+    p += 4;
+  }
+  for (; p < p_hi; ++p) acc = add(acc, src[(size_t)p * elems4]);
   if constexpr (GROUPS > 1) {
     red[threadIdx.x] = acc;
 #pragma unroll
@@ -159,16 +171,15 @@ void run_state_reduce(const float* partials, float* state, const Plan& p, hipStr
   state_reduce_kernel<GROUPS, SPLIT><<<dim3((elems4 + EL - 1) / EL, p.BH), 256, 0, s>>>(
       reinterpret_cast<const float4*>(partials), reinterpret_cast<float4*>(state), p.split, p.P, elems4);
 }
-// One thread per four elements where that makes at least 128 workgroups; with fewer heads, more threads per element (measured
-// after a fresh write of the partials, with about 5 us of event overhead, one / four / sixteen threads: 12 heads of 22 slots,
-// width 128: 8.2 / 8.5 / 18.2 us; 4 heads of 64: 10.4 / 8.0 / 9.7; 2 of 128: 14.9 / 9.5 / 8.0; 1 of 256: 24.3 / 11.5 / 8.4;
-// 1 of 32: 7.6 / 6.2 / 7.1).
+// One thread per four elements while its slots fit one batch of loads, more threads with more slots.  Measured after a fresh
+// write of the partials, with about 4 us of event overhead, one / four / sixteen threads, width 128: 40 heads of 8 slots 7.9 /
+// 8.8 / 15.6 us; 20 of 14: 8.0 / 7.7 / 10.4; 12 of 22: 7.8 / 7.4 / 9.1; 4 of 64: 8.6 / 7.6 / 7.5; 2 of 128: 11.9 / 8.3 / 7.3;
+// 1 of 256: 18.0 / 9.1 / 7.5.
 template <bool SPLIT>
 hipError_t state_reduce_any(const float* partials, float* state, const Plan& p, hipStream_t s) {
   const int slots = SPLIT ? p.split.PS : p.P;
-  const size_t groups1 = (size_t)p.BH * (p.state_elems / 4) / 256;      // workgroups with one thread per four elements
-  if (groups1 >= 128 || slots <= 8) run_state_reduce<1, SPLIT>(partials, state, p, s);
-  else if (groups1 >= 48 || slots <= 32) run_state_reduce<4, SPLIT>(partials, state, p, s);
+  if (slots <= 8) run_state_reduce<1, SPLIT>(partials, state, p, s);
+  else if (slots <= 32) run_state_reduce<4, SPLIT>(partials, state, p, s);
   else run_state_reduce<16, SPLIT>(partials, state, p, s);
   return hipGetLastError();
 }
