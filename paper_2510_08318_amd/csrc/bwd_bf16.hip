@@ -8,7 +8,7 @@
 //   through phi  du = p+ (g+ - <g+,p+>) - p- (g- - <g-,p->),   dx = du W~^T,   dW~ = sum x^T du
 //
 // bwd_prep_kernel : fp16 operand image of S for g (rows = features, contraction over channels)
-// bwd_q_kernel    : per 128-token tile: phi(Q), o, delta, g, du, dq; dS, dz partials (split-n); dW~_q partials
+// bwd_q_kernel    : per 128-token tile: phi(Q), G = dO S^T, delta, du, dq; dS, dz partials (split-n); dW~_q partials
 // bwd_k_kernel    : per 32-token block: phi(K), g, du, dk, dv; dW~_k partials
 // (the partials are reduced in state_reduce.hip)
 //
@@ -34,17 +34,16 @@ namespace {
 // kernels copy them into LDS with coalesced 16-byte loads.
 //   grid (B*H, 8): slice blockIdx.y of the entries of (b,h); the workgroups of batch item 0 also
 //   build the W~ images of their head (WQK = true: both W~_q and W~_k images into wimg).
-//   WQK = true is the pass over S (image simg in the A-operand order of the query pass: the query
-//   side wants o on the lane's own token); WQK = false is the pass over dS, whose image is in the
-//   B-operand order of dv = phi(k) dS with the tokens on the accumulator rows.
+//   Both passes write gimg, the A operands of G^T = S Y^T; WQK = false, the pass over dS, also writes simg, the B operands of
+//   dv = phi(k) dS with the tokens on the accumulator rows.
 // 512 threads: staging the state is latency, not bandwidth (256 threads: 16.8 + 10.8 us for the two
 // passes at config 5, 512: 11.9 + 8.3 us, 1024 the same; more slices per head change nothing).
 constexpr int PT = 512, PREP_Y = 8;
 // Both passes centre the state before it is rounded to fp16 operands (exact in real arithmetic; the roundings
 // then act on what the gradients are made of instead of on a common part that cancels):
 //   pass over S:  S^c = S - z vbar^T with vbar = sum_j v_j / n (the + half of S sums to sum_j v_j, the + half
-//                 of z to n).  The query-side kernel then works with o - vbar and delta^c = delta - dO . vbar, g is
-//                 unchanged, and its dz comes out as dz^c = dz + dS vbar.
+//                 of z to n).  The query-side kernel then has delta^c = delta - dO . vbar, g is unchanged, and its dz comes
+//                 out as dz^c = dz + dS vbar.
 //   pass over dS: the key-side dz is completed against the ROUNDED image: dzc[f] = dz^c[f] - vbar . r(dS[f]), so
 //                 that v_j . r(dS[f]) + dzc[f] = (v_j - vbar) . r(dS[f]) + dz^c[f] holds exactly and the rounding
 //                 of the image acts on v_j - vbar, not on v_j (values with a common offset cost nothing).
@@ -173,16 +172,9 @@ __global__ __launch_bounds__(PT) void bwd_prep_kernel(const float* __restrict__ 
     }
   }
   const int first = blockIdx.y * PT + tid, step = PT * gridDim.y;
-  if constexpr (WQK) {
-    // one tile for both products of the query side, then the z block (together as large as an image of S)
-    constexpr int TILE = D * D / 8;
-    static_assert(TILE + L::KS * 64 == SIMG, "tile + z block fill the image region");
-    for (int idx = first; idx < TILE; idx += step) simg[(size_t)bh * SIMG + idx] = state_tile_entry<D>(S, scale, idx);
-    for (int idx = first; idx < L::KS * 64; idx += step) simg[(size_t)bh * SIMG + TILE + idx] = state_z_entry<D>(S, scale, idx);
-  } else {
-    for (int idx = first; idx < G::IMG; idx += step) gimg[(size_t)bh * G::IMG + idx] = grad_image_entry<D>(S, scale, idx);
-    for (int idx = first; idx < SIMG; idx += step) simg[(size_t)bh * SIMG + idx] = state_image_entry<D, true>(S, scale, idx);
-  }
+  for (int idx = first; idx < G::IMG; idx += step) gimg[(size_t)bh * G::IMG + idx] = grad_image_entry<D>(S, scale, idx);
+  if constexpr (!WQK)
+    for (int idx = first; idx < SIMG; idx += step) simg[(size_t)bh * SIMG + idx] = state_image_entry<D>(S, scale, idx);
   if constexpr (WQK) {
     if (bh < H) {
       static_assert(C::W_IMG == WB_IMG, "the four W~ images have one size");
@@ -275,7 +267,7 @@ struct DwTile {
   static constexpr int RB = (D / 32) * NB >= NW ? (D / 32) * NB / NW : 1;   // row blocks per wavefront
   static constexpr int BPT = kTile / 32;                   // du blocks per parked tile
   static constexpr int KSN = kTile / 16;
-  static constexpr int KBATCH = NW > 4 ? KSN / 2 : KSN;     // k-steps whose operands are in flight together
+  static constexpr int KBATCH = NW > 4 ? KSN / 2 : KSN / 4;     // k-steps whose operands are in flight together
   static constexpr int DU_BYTES = kTile * RSU;
   f32x16 acc[RB];
   float gamma;
@@ -341,8 +333,7 @@ struct DwTile {
 #pragma unroll
       for (int i = 0; i < RB; ++i) offA[i][j] = tr_offset_g4<D>(32 * (row0 + i), lane, j);
     }
-    // the operands of KBATCH k-steps are requested before their first MFMA: one LDS latency per batch instead of one
-    // per k-step (the whole tile at once where the wavefront has 512 registers, half of it where it has 256)
+    // the operands of KBATCH k-steps are requested before their first MFMA: one LDS latency per batch instead of one per k-step
 #pragma unroll
     for (int k0 = 0; k0 < KSN; k0 += KBATCH) {
       f16x8 a[KBATCH][RB], b[KBATCH];
@@ -375,42 +366,45 @@ struct DwTile {
 };
 
 // ---- query side --------------------------------------------------------------------------
-// LDS operands of the query-side kernel's MFMA phases are requested QAHEAD MFMAs before their use (one more for g):
-// with one wavefront per SIMD nothing else hides an LDS latency.  3 (4 for g) against 5 (6): 296 -> 293 us per
-// backward call at the training shape; 8 measures between the two.
-constexpr int QAHEAD = 5;
+// LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use (one more for g).
+constexpr int QAHEAD = 3;
+constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
 // BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives
 // (1 - r') dout, and the workgroup's part of -sum dout . o goes to dr_part (dL/dr = sum dout . (s - o);
 // the sum dout . s is a separate streaming dot product, taken only when dL/dr is asked for).
-// DW: dW~_q is accumulated here as well (DwTile): after the tile's dS contraction the phi and dO tiles in LDS
-// are dead, and the tile's q rows (read again: the registers that held them are long reused) and du images
-// take their place.
+// DW: dW~_q is accumulated here as well (DwTile).
+//
+// Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
+// A+- = sum G phi and Z+- = sum z phi over the two halves of the features, den = Z+ + Z-, delta = (A+ + A-) / den and the two sums
+// of the softmax Jacobian are combinations of the same four, so dots of what the lane holds in fp32 stand in for 40 of the
+// MFMAs and for a second image of S.  Wavefronts 4-7 ("acc") contract the tile's phi, dO / den and delta / den into dS, dz
+// and its x, du into dW~ meanwhile: the accumulators (112 registers) are theirs, so the tok wavefronts do with 256 registers and a
+// SIMD hosts one wavefront of each kind, whose MFMA and vector work overlap.  The tiles are single (64 KB of images leave room for
+// one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO / den are parked between two barriers and dS contracts them
+// while du and dx are formed; (DW) x takes phi's place and du its tile between two more, and dW~ contracts those beside the next
+// tile's first half.
 template <int D, bool BLEND, bool CENTRE, bool DW>
-__global__ __launch_bounds__(NT) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
-                                                   const uint16_t* __restrict__ wq, const float* __restrict__ state,
-                                                   const uint4* __restrict__ simg,
-                                                   const uint4* __restrict__ wimg, const float* __restrict__ scales,
-                                                   uint16_t* __restrict__ dq,
-                                                   float* __restrict__ partials, float* __restrict__ dw_part,
-                                                   const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
-                                                   float* __restrict__ dr_part,
-                                                   float* __restrict__ cs_part,
-                                                   int H, int n, int P, Rows rw) {
+__global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
+                                                    const float* __restrict__ state, const uint4* __restrict__ gimg,
+                                                    const uint4* __restrict__ wimg, const float* __restrict__ scales,
+                                                    uint16_t* __restrict__ dq,
+                                                    float* __restrict__ partials, float* __restrict__ dw_part,
+                                                    const float* __restrict__ rptr, float* __restrict__ dr_part,
+                                                    float* __restrict__ cs_part,
+                                                    int H, int n, int P, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
   using G = GradLayout<D>;
   constexpr int RS = D * 2;
   constexpr int WMN = D / 64;
-  constexpr int SA_IMG = L::KS * L::MBZ * 64;
   constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
   constexpr float kMean = 2.0f / D;                        // mean of phi over its features
-  using DWT = DwTile<D, NT / 64>;
+  using DWT = DwTile<D, 4>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
-  uint4* sSA = sWA + C::W_IMG;                             // the state tile (state_tile_entry), then its z block
-  const char* sT = reinterpret_cast<const char*>(sSA);
-  uint4* sWB = sSA + SA_IMG;
-  char* sPhi = reinterpret_cast<char*>(sWB + WB_IMG);      // [kTile][D] fp16: phi(q) (CENTRE: phi(q) - 2/D)
+  uint4* sGA = sWA + C::W_IMG;
+  uint4* sWB = sGA + G::IMG;
+  char* sPhi = reinterpret_cast<char*>(sWB + WB_IMG);      // [kTile][D] fp16: phi(q) (CENTRE: phi(q) - 2/D), then (DW) the q rows
   char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: gamma * dO / den
   uint16_t* sW16 = reinterpret_cast<uint16_t*>(sDO + kTile * RS);   // [kTile] fp16: -gamma * delta / den
   float* sZ = reinterpret_cast<float*>(sW16 + kTile);      // [D] z, unscaled
@@ -419,167 +413,245 @@ __global__ __launch_bounds__(NT) void bwd_q_kernel(const uint16_t* __restrict__ 
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int role = w / 4, pw = w % 4;
   const int g = lane / 32;
-  const int mi = w / 2, ni = w % 2;
   const int bh = blockIdx.y, p = blockIdx.x, h = bh % H;
-  const uint16_t* qb = q + head_base(rw, bh, H);
-  const uint16_t* dob = dout + head_base(rw, bh, H);
-  uint16_t* dqb = dq + head_base(rw, bh, H);
   const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;      // 1 - r'
-  float dr_acc = 0.f;
   const float* sb = state + (size_t)bh * (D + 1) * D;
   const int ntile = (n + kTile - 1) / kTile;
-  const int nblk = (n + 31) / 32;
 
-  copy_image<NT>(wimg + (size_t)h * 4 * C::W_IMG, sWA, C::W_IMG, tid);
-  copy_image<NT>(wimg + (size_t)h * 4 * C::W_IMG + C::W_IMG, sWB, WB_IMG, tid);
-  copy_image<NT>(simg + (size_t)bh * SA_IMG, sSA, SA_IMG, tid);
-  const float scale = scales[2 * bh];
-  for (int i = tid; i < D; i += NT) sZ[i] = sb[D * D + i];
+  copy_image<NTQ>(wimg + (size_t)h * 4 * C::W_IMG, sWA, C::W_IMG, tid);
+  copy_image<NTQ>(wimg + (size_t)h * 4 * C::W_IMG + C::W_IMG, sWB, WB_IMG, tid);
+  copy_image<NTQ>(gimg + (size_t)bh * G::IMG, sGA, G::IMG, tid);
+  for (int i = tid; i < D; i += NTQ) sZ[i] = sb[D * D + i];
   __syncthreads();
 
-  float csum[WMN], wsum = 0.f;                     // column sums of the dO/den operand, sum of the -delta/den operand
+  // running power-of-two scale of the sums over tokens, the same in every wavefront; returns the factor for the accumulators
+  float gamma = kGammaUnset;
+  auto next_gamma = [&]() -> float {
+    const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
+    float gnext = gamma;
+    const float ratio = gamma_step(gnext, gamma_for(m));
+    // the same in every lane: kept in scalar registers
+    gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
+  };
+
+  if (role == 0) {
+    const uint16_t* qb = q + head_base(rw, bh, H);
+    const uint16_t* dob = dout + head_base(rw, bh, H);
+    uint16_t* dqb = dq + head_base(rw, bh, H);
+    const float scale = scales[2 * bh];
+    const int prow = 32 * pw + (lane % 32);
+    float dr_acc = 0.f;
+    uint4 xq[C::UK], xr[C::UK], dor[D / 16];
+    auto load_rows = [&](int tile) {
+      const int t = tile * kTile + prow;
+      const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+      const uint4* row = reinterpret_cast<const uint4*>(qb + at);
 #pragma unroll
-  for (int j = 0; j < WMN; ++j) csum[j] = 0.f;
-  f32x16 s[WMN][WMN], zacc;
+      for (int ks = 0; ks < C::UK; ++ks) xq[ks] = row[2 * ks + g];
+    };
+    auto load_do = [&](int tile) {
+      const int t = tile * kTile + prow;
+      const uint4* drow = reinterpret_cast<const uint4*>(dob + (size_t)(t < n ? t : n - 1) * rw.sn);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    zacc[r] = 0.f;
+      for (int i = 0; i < D / 16; ++i) dor[i] = drow[2 * i + g];
+    };
+    load_rows(p < ntile ? p : 0);
+    // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
+    // for the first tile too, would be a wait for the previous tile's stores
 #pragma unroll
-    for (int i = 0; i < WMN; ++i)
+    for (int ks = 0; ks < C::UK; ++ks) asm volatile("" : "+v"(xq[ks].x), "+v"(xq[ks].y), "+v"(xq[ks].z), "+v"(xq[ks].w));
+    for (int tile = p; tile < ntile; tile += P) {
+      const int t = tile * kTile + prow;
+      const bool valid = t < n;
+      load_do(tile);
+      f32x16 u[C::UM];
+      project<D, QAHEAD>(xq, sWA, lane, u);
+      if constexpr (DW) {
 #pragma unroll
-      for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
-  }
-  const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
-  const bool do_z = (WMN == 2) || (ni == 0);
-  // read offsets of the dS contraction; DW: worked out again in every tile (registers are what is short there)
-  int offA[WMN][2], offB[WMN][2];
-  auto set_offsets = [&](int ln) {
+        for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xq[ks];   // rows past n repeat row n - 1: their du is zero
+      }
+      float pp[C::LOC], pm[C::LOC];
+      {
+        uint32_t unused[C::NPK];
+        softmax_full<D>(u, pp, pm, unused);
+      }
+      // the token's largest |dO|: magnitudes of bf16 compare as integers
+      float dmax;
+      {
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        u16x2 m2 = {0, 0};
+        auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) { take(dor[i].x); take(dor[i].y); take(dor[i].z); take(dor[i].w); }
+        const uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
+        dmax = __builtin_bit_cast(float, m << 16);
+      }
+      float lo, hi;
+      pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
+      const float stok = pow2_normaliser(dmax);
+
+      // G = dO S^T (times scale * stok), rows laid out like phi
+      f32x16 ga[G::GM];
+#pragma unroll
+      for (int mb = 0; mb < G::GM; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
+      const uint4* sga = sGA + lane + opaque_zero();
+      pipelined_operands<G::KS * G::GM, QAHEAD + 1>(
+          [&](int i) { return sga[i * 64]; },
+          [&](int i, uint4 a) {
+            const int ks = i / G::GM, mb = i % G::GM;
+            float f[8];
+            unpack_bf16x8(dor[ks], f);
+            uint4 bq;
+            bq.x = pack_f16x2(f[0] * stok, f[1] * stok); bq.y = pack_f16x2(f[2] * stok, f[3] * stok);
+            bq.z = pack_f16x2(f[4] * stok, f[5] * stok); bq.w = pack_f16x2(f[6] * stok, f[7] * stok);
+            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
+          });
+      // dO stays packed until it is parked: seen as the same values, its unpacked form would be kept (and spilled) from here to there
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) asm volatile("" : "+v"(dor[i].x), "+v"(dor[i].y), "+v"(dor[i].z), "+v"(dor[i].w));
+      // A+-, Z+-; feature g*LOC + j of each half
+      const int z_at = g * C::LOC / 4 + opaque_zero();
+      auto z4 = [&](int q) { return reinterpret_cast<const float4*>(sZ)[z_at + q]; };
+      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f;
+#pragma unroll
+      for (int q = 0; q < C::LOC / 4; ++q) {
+        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+        const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int j = 4 * q + i;
+          ap = fmaf(ga[j / 16][j % 16], pp[j], ap); am = fmaf(ga[G::GM / 2 + j / 16][j % 16], pm[j], am);
+          Zp = fmaf(zp[i], pp[j], Zp); Zm = fmaf(zm[i], pm[j], Zm);
+        }
+      }
+      pair32(Zp, lo, hi); Zp = lo + hi;
+      pair32(Zm, lo, hi); Zm = lo + hi;
+      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
+      const float unscale = __builtin_amdgcn_rcpf(scale * stok);          // exact: powers of two
+      if constexpr (BLEND) {
+        // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
+        // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
+        if (valid) dr_acc -= (ap + am) * (unscale * inv_den);
+      }
+      pair32(ap, lo, hi); ap = lo + hi;
+      pair32(am, lo, hi); am = lo + hi;
+      const float delta = (ap + am) * (unscale * inv_den);
+      {
+        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
+        float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_den * om : 0.f;
+        m = wave_max_paired(m);
+        if (lane == 0) sRed[pw] = m;
+      }
+      __syncthreads();                                   // the previous tile has been read
+      next_gamma();
+      {
+        // (addresses from a lane index that the optimiser cannot hoist: held across the loop they end up in scratch memory)
+        const int lz = lane + opaque_zero();
+        const int row = 32 * pw + lz % 32, psw = swz<D>(row), gz = lz / 32;
+        char* rowp = sPhi + row * RS;
+        constexpr int CPH = C::LOC / 8;
+        // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
+        // on the deviation from the uniform map; (2/D) x the column sums are added back by the prep kernel
+        const float mean = CENTRE ? kMean : 0.f;
+        auto pack4 = [&](const float* f) {
+          return make_uint4(pack_f16x2(f[0] - mean, f[1] - mean), pack_f16x2(f[2] - mean, f[3] - mean),
+                            pack_f16x2(f[4] - mean, f[5] - mean), pack_f16x2(f[6] - mean, f[7] - mean));
+        };
+#pragma unroll
+        for (int c = 0; c < CPH; ++c) {
+          uint4 a = pack4(pp + 8 * c), b = pack4(pm + 8 * c);
+          if (!valid) { a = make_uint4(0, 0, 0, 0); b = a; }
+          *reinterpret_cast<uint4*>(rowp + (((gz * CPH + c) ^ psw) * 16)) = a;
+          *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + gz * CPH + c) ^ psw) * 16)) = b;
+        }
+        const float sc = valid ? inv_den * gamma * om : 0.f;
+        char* drowp = sDO + row * RS;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+          float f[8];
+          unpack_bf16x8(dor[c], f);
+          uint4 a;
+          a.x = pack_f16x2(f[0] * sc, f[1] * sc); a.y = pack_f16x2(f[2] * sc, f[3] * sc);
+          a.z = pack_f16x2(f[4] * sc, f[5] * sc); a.w = pack_f16x2(f[6] * sc, f[7] * sc);
+          *reinterpret_cast<uint4*>(drowp + (((2 * c + gz) ^ psw) * 16)) = a;
+        }
+        if (g == 0) sW16[row] = (uint16_t)(pack_f16x2(valid ? -delta * sc : 0.f, 0.f) & 0xffffu);
+      }
+      __syncthreads();
+      // g = (1 - r') (G - delta z) / den, its sums cp, cm against phi, and du
+      const float r1 = om * inv_den * unscale, r2 = om * inv_den * delta;
+      const float cp = ap * r1 - r2 * Zp, cm = am * r1 - r2 * Zm;
+      float du[C::LOC];
+#pragma unroll
+      for (int q = 0; q < C::LOC / 4; ++q) {
+        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+        const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int j = 4 * q + i;
+          const float gp = fmaf(ga[j / 16][j % 16], r1, fmaf(-r2, zp[i], -cp));
+          const float gm = fmaf(ga[G::GM / 2 + j / 16][j % 16], r1, fmaf(-r2, zm[i], -cm));
+          du[j] = pp[j] * gp - pm[j] * gm;
+        }
+      }
+      // The next tile's rows go out before the dq stores: loads and stores retire in order, and a wait for a load issued behind
+      // the stores would wait for the stores as well.
+      load_rows(tile + P < ntile ? tile + P : tile);
+      uint32_t dub[C::LOC / 2];
+      float blk_its = 0.f;
+      {
+        f32x16 xa[L::MB];
+        float its;
+        du_to_dx<D, QAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
+        store_token_rows<D>(dqb, rw.sn, tile * kTile + 32 * pw, n, lane, xa, its);
+      }
+      if constexpr (DW) {
+        __syncthreads();                                 // dS has read the tile's phi
+        const int lz = lane + opaque_zero();
+        DWT::park_x(xr, sPhi, pw, lz);
+        DWT::park_du(dub, blk_its, sDU, sRed + 4, pw, lz);
+        __syncthreads();
+      }
+    }
+    if constexpr (BLEND) {
+      for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
+      if (lane == 0) sRed[pw] = dr_acc;                  // (read for the last time before the last tile's second barrier)
+    }
+  } else {
+    float csum[WMN], wsum = 0.f;                         // column sums of the dO/den operand, sum of the -delta/den operand
+#pragma unroll
+    for (int j = 0; j < WMN; ++j) csum[j] = 0.f;
+    f32x16 s[WMN][WMN], zacc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      zacc[r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < WMN; ++i)
+#pragma unroll
+        for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
+    }
+    const int mi = pw / 2, ni = pw % 2;
+    const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
+    const bool do_z = (WMN == 2) || (ni == 0);
+    int offA[WMN][2], offB[WMN][2];
 #pragma unroll
     for (int i = 0; i < WMN; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), ln, j);
-        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), ln, j);
+        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
+        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
       }
-  };
-  if constexpr (!DW) set_offsets(lane);
-  const int prow = 32 * w + (lane % 32);
-  const int psw = swz<D>(prow);
-  float gamma = kGammaUnset;
-  DWT dwt;
-  if constexpr (DW) dwt.init(w);
-
-  // the lane's q rows of the next tile are requested late in this tile, behind the softmax Jacobian: the
-  // middle of the chain is where registers are short (never behind a branch: after the last tile the rows
-  // are simply read again); its dO rows are requested at the top of the tile and first needed after the
-  // projection, the softmaxes and o
-  uint4 xq[C::UK];
-  auto load_rows = [&](uint4 (&x)[C::UK], int tile) {
-    const int t = tile * kTile + prow;
-    const uint4* row = reinterpret_cast<const uint4*>(qb + (size_t)(t < n ? t : n - 1) * rw.sn);
-#pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
-  };
-  auto load_q = [&](int tile) { load_rows(xq, tile); };
-  load_q(p < ntile ? p : 0);
-  for (int tile = p; tile < ntile; tile += P) {
-    const int t = tile * kTile + prow;
-    const bool valid = t < n;
-    const int tc = valid ? t : (n - 1);
-    uint4 dor[D / 16];
-    {
-      const uint4* drow = reinterpret_cast<const uint4*>(dob + (size_t)tc * rw.sn + g * (D / 2));
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) dor[i] = drow[i];
-    }
-    // dL/dr gets dout . (s - o) = dout . s - delta, from the unscaled dout; everything downstream is
-    // linear in dout, so the factor 1 - r' is applied to the scalars that carry it (om below).
-    // dout . s is taken here, while few registers are live.
-    f32x16 u[C::UM];
-    project<D, QAHEAD>(xq, sWA, lane, u);
-    uint4 xr[C::UK];                              // this tile's rows once more, for dW~ (rows past n repeat row n - 1: their du is zero)
-    if constexpr (DW) {
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xq[ks];
-    }
-    float pp[C::LOC], pm[C::LOC];
-    uint32_t pk[C::NPK];
-    softmax_full<D>(u, pp, pm, pk);
-
-    // o = phi(q) S / den on the lane's channels g*D/2 + 16*mb + r
-    float o[D / 2];
-    float den_s;                                   // scale * den
-    {
-      f32x16 oa[L::MB], dn;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        dn[r] = 0.f;
-#pragma unroll
-        for (int mb = 0; mb < L::MB; ++mb) oa[mb][r] = 0.f;
-      }
-      const int lz = lane + opaque_zero();
-      const uint4* szi = sSA + D * D / 8 + lz;     // the z block behind the tile
-      int offT[L::MB][2];
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) offT[mb][j] = tr_offset<D>(32 * mb, lz, j);
-      pipelined_operands<L::KS * L::MBZ, QAHEAD>(
-          [&](int i) {
-            const int ks = i / L::MBZ, mb = i % L::MBZ;
-            if (mb == L::MB) return szi[ks * 64];
-            return __builtin_bit_cast(uint4, read_tr(sT + ks * 16 * RS, offT[mb < L::MB ? mb : 0][0], offT[mb < L::MB ? mb : 0][1]));
-          },
-          [&](int i, uint4 a) {
-            const int ks = i / L::MBZ, mb = i % L::MBZ;
-            uint4 bq; bq.x = pk[4 * ks]; bq.y = pk[4 * ks + 1]; bq.z = pk[4 * ks + 2]; bq.w = pk[4 * ks + 3];
-            if (mb < L::MB) oa[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), oa[mb], 0, 0, 0);
-            else dn = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), dn, 0, 0, 0);
-          });
-      den_s = dn[0];
-      const float inv = __builtin_amdgcn_rcpf(den_s);
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[16 * mb + r] = oa[mb][r] * inv;
-    }
-    const float inv_den = scale * __builtin_amdgcn_rcpf(den_s);     // 1 / den
-
-    // dO on the same channels, delta = dO . o
-    float dof[D / 2];
-#pragma unroll
-    for (int i = 0; i < D / 16; ++i) unpack_bf16x8(dor[i], dof + 8 * i);
-    float delta = 0.f, dmax = 0.f;
-#pragma unroll
-    for (int c = 0; c < D / 2; ++c) { delta = fmaf(dof[c], o[c], delta); dmax = fmaxf(dmax, fabsf(dof[c])); }
-    if constexpr (BLEND) {
-      // the -dout . o part of dout . (s - o), on this lane's channels; the images are centred, so o here is
-      // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
-      if (valid) dr_acc -= delta;
-    }
-    float lo, hi;
-    pair32(delta, lo, hi); delta = lo + hi;
-    pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
-    const float stok = pow2_normaliser(dmax);
-
-    // operands of the sums over tokens, parked now so that phi and dO need not stay in registers
-    // through the rest of the block
-    {
-      // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
-      float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_den * om : 0.f;
-      m = wave_max_paired(m);
-      if (lane == 0) sRed[w] = m;
-    }
-    __syncthreads();                             // previous tile's operand reads are done
-    {
-      const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
-      float gnext = gamma;
-      float ratio = gamma_step(gnext, gamma_for(m));
-      // the same in every lane: kept in scalar registers
-      gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
-      ratio = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
-      if (ratio != 1.f) {                        // this tile is larger than every earlier one
+    DWT dwt;
+    if constexpr (DW) dwt.init(pw);
+    for (int tile = p; tile < ntile; tile += P) {
+      __syncthreads();
+      const float ratio = next_gamma();
+      if (ratio != 1.f) {                                // this tile is larger than every earlier one
         if constexpr (CENTRE) {
           wsum *= ratio;
 #pragma unroll
@@ -594,148 +666,48 @@ __global__ __launch_bounds__(NT) void bwd_q_kernel(const uint16_t* __restrict__ 
             for (int j = 0; j < WMN; ++j) s[i][j][r] *= ratio;
         }
       }
-    }
-    {
-      char* rowp = sPhi + prow * RS;
-      constexpr int CPH = C::LOC / 8;
-#pragma unroll
-      for (int c = 0; c < CPH; ++c) {
-        // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
-        // on the deviation from the uniform map; (2/D) x the column sums are added back by the prep kernel
-        uint4 a, b;
-        if constexpr (CENTRE) {
-          a.x = pack_f16x2(pp[8 * c] - kMean, pp[8 * c + 1] - kMean);     a.y = pack_f16x2(pp[8 * c + 2] - kMean, pp[8 * c + 3] - kMean);
-          a.z = pack_f16x2(pp[8 * c + 4] - kMean, pp[8 * c + 5] - kMean); a.w = pack_f16x2(pp[8 * c + 6] - kMean, pp[8 * c + 7] - kMean);
-          b.x = pack_f16x2(pm[8 * c] - kMean, pm[8 * c + 1] - kMean);     b.y = pack_f16x2(pm[8 * c + 2] - kMean, pm[8 * c + 3] - kMean);
-          b.z = pack_f16x2(pm[8 * c + 4] - kMean, pm[8 * c + 5] - kMean); b.w = pack_f16x2(pm[8 * c + 6] - kMean, pm[8 * c + 7] - kMean);
-        } else {
-          a.x = pk[4 * c]; a.y = pk[4 * c + 1]; a.z = pk[4 * c + 2]; a.w = pk[4 * c + 3];
-          b.x = pk[C::LOC / 2 + 4 * c]; b.y = pk[C::LOC / 2 + 4 * c + 1];
-          b.z = pk[C::LOC / 2 + 4 * c + 2]; b.w = pk[C::LOC / 2 + 4 * c + 3];
-        }
-        if (!valid) { a = make_uint4(0, 0, 0, 0); b = a; }
-        *reinterpret_cast<uint4*>(rowp + (((g * CPH + c) ^ psw) * 16)) = a;
-        *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + g * CPH + c) ^ psw) * 16)) = b;
+      __syncthreads();
+      contract_tile<D, false, CENTRE>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
+                       [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); }, csum, &wsum);
+      if constexpr (DW) {
+        __syncthreads();
+        __syncthreads();
+        dwt.contract(sPhi, sDU, sRed + 4, lane + opaque_zero());
       }
-      const float sc = valid ? inv_den * gamma * om : 0.f;
-      char* drowp = sDO + prow * RS;
-#pragma unroll
-      for (int c = 0; c < D / 16; ++c) {
-        uint4 a;
-        a.x = pack_f16x2(dof[8 * c] * sc, dof[8 * c + 1] * sc);     a.y = pack_f16x2(dof[8 * c + 2] * sc, dof[8 * c + 3] * sc);
-        a.z = pack_f16x2(dof[8 * c + 4] * sc, dof[8 * c + 5] * sc); a.w = pack_f16x2(dof[8 * c + 6] * sc, dof[8 * c + 7] * sc);
-        *reinterpret_cast<uint4*>(drowp + (((g * (C::CH / 2) + c) ^ psw) * 16)) = a;
-      }
-      if (g == 0) sW16[prow] = (uint16_t)(pack_f16x2(valid ? -delta * sc : 0.f, 0.f) & 0xffffu);
     }
+    if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
 
-    // g = (dO S^T - delta z) / den, rows laid out like phi
-    float gp[C::LOC], gm[C::LOC];
-    {
-      f32x16 ga[G::GM];
+    const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
+    if constexpr (CENTRE) {
+      // column sums of dO/den (the wavefronts mi = 0 hold every channel block once) and the sum of -delta/den
+      float* cs = cs_part + ((size_t)bh * P + p) * (D + 8);
 #pragma unroll
-      for (int mb = 0; mb < G::GM; ++mb)
+      for (int j = 0; j < WMN; ++j) {
+        float lo, hi;
+        pair32(csum[j], lo, hi);
+        if (mi == 0 && g == 0) cs[32 * (ni * WMN + j) + (lane % 32)] = (lo + hi) * ig;
+      }
+      float lo, hi;
+      pair32(wsum, lo, hi);
+      if (pw == 0 && lane == 0) cs[D] = (lo + hi) * ig;
+    }
+    float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
+    const int c = lane % 32;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
-      // A operand (ks, mb): the lane's feature row of block mb, channels g*D/2 + 8ks .. +7 = chunks 2ks and 2ks+1
-      // of that row, the lane group's 8 bytes of each (state_tile_entry)
-      const int lz = lane + opaque_zero();
-      const char* grow = sT + state_tile_grad_row<D>(lz);
-      const int sw16 = swz<D>((state_tile_grad_row<D>(lz) / RS) % 16) * 16;
-      pipelined_operands<G::KS * G::GM, QAHEAD + 1>(
-          [&](int i) {
-            const int ks = i / G::GM, mb = i % G::GM;
-            const char* rowp = grow + 32 * mb * RS;
-            const uint2 lo = *reinterpret_cast<const uint2*>(rowp + ((32 * ks) ^ sw16));
-            const uint2 hi = *reinterpret_cast<const uint2*>(rowp + ((32 * ks + 16) ^ sw16));
-            return make_uint4(lo.x, lo.y, hi.x, hi.y);
-          },
-          [&](int i, uint4 a) {
-            const int ks = i / G::GM, mb = i % G::GM;
-            uint4 bq;
-            bq.x = pack_f16x2(dof[8 * ks] * stok, dof[8 * ks + 1] * stok);     bq.y = pack_f16x2(dof[8 * ks + 2] * stok, dof[8 * ks + 3] * stok);
-            bq.z = pack_f16x2(dof[8 * ks + 4] * stok, dof[8 * ks + 5] * stok); bq.w = pack_f16x2(dof[8 * ks + 6] * stok, dof[8 * ks + 7] * stok);
-            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
-          });
-      const float r1 = om * __builtin_amdgcn_rcpf(den_s * stok);     // (1 - r') / (scale * stok * den)
-      const float r2 = om * delta * inv_den;
+    for (int i = 0; i < WMN; ++i)
 #pragma unroll
-      for (int mb = 0; mb < G::GM; ++mb) {
-        const int f0 = (mb < G::GM / 2 ? 0 : C::HALF) + g * C::LOC + 16 * (mb % (G::GM / 2));
+      for (int j = 0; j < WMN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float val = ga[mb][r] * r1 - r2 * sZ[f0 + r];
-          if (mb < G::GM / 2) gp[16 * mb + r] = val; else gm[16 * (mb - G::GM / 2) + r] = val;
+          const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
+          dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
         }
-      }
+    if (do_z && c == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
     }
-    float du[C::LOC];
-    phi_jacobian<D>(gp, gm, pp, pm, du);
-
-    // The next tile's q rows, and (DW) this tile's rows once more for dW~, wanted after the dS contraction.  Both go
-    // out before the dq stores: loads and stores retire in order, and a wait for a load issued behind the
-    // stores would wait for the stores as well.
-    load_q(tile + P < ntile ? tile + P : tile);
-
-    {
-      f32x16 xa[L::MB];
-      float its;
-      const int blk = tile * (kTile / 32) + w;
-      uint32_t dub[C::LOC / 2];
-      float blk_its = 0.f;
-      du_to_dx<D, QAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
-      // the previous tile's dW~ contraction has read its du tile: every wavefront has passed this tile's first barrier since
-      if constexpr (DW) DWT::park_du(dub, blk_its, sDU, sRed + 4, w, lane);
-      store_token_rows<D>(dqb, rw.sn, blk * 32, n, lane, xa, its);
-    }
-
-    __syncthreads();
-    if constexpr (DW) set_offsets(lane + opaque_zero());
-    contract_tile<D, false, CENTRE>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
-                     [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); }, csum, &wsum);
-    if constexpr (DW) {
-      __syncthreads();                           // every wavefront is done with the phi and dO tiles
-      DWT::park_x(xr, sPhi, w, lane);
-      __syncthreads();
-      dwt.contract(sPhi, sDU, sRed + 4, lane + opaque_zero());
-      // the next tile's barrier before it parks phi and dO covers these reads
-    }
-  }
-  if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
-
-  const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
-  if constexpr (CENTRE) {
-    // column sums of dO/den (the wavefronts mi = 0 hold every channel block once) and the sum of -delta/den
-    float* cs = cs_part + ((size_t)bh * P + p) * (D + 8);
-#pragma unroll
-    for (int j = 0; j < WMN; ++j) {
-      float lo, hi;
-      pair32(csum[j], lo, hi);
-      if (mi == 0 && g == 0) cs[32 * (ni * WMN + j) + (lane % 32)] = (lo + hi) * ig;
-    }
-    float lo, hi;
-    pair32(wsum, lo, hi);
-    if (w == 0 && lane == 0) cs[D] = (lo + hi) * ig;
-  }
-  float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
-  const int c = lane % 32;
-#pragma unroll
-  for (int i = 0; i < WMN; ++i)
-#pragma unroll
-    for (int j = 0; j < WMN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
-        dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
-      }
-  if (do_z && c == 0) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
   }
   if constexpr (BLEND) {
-    for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
-    __syncthreads();
-    if (lane == 0) sRed[w] = dr_acc;
     __syncthreads();
     if (tid == 0) dr_part[(size_t)bh * P + p] = (sRed[0] + sRed[1]) + (sRed[2] + sRed[3]);
   }
@@ -815,9 +787,9 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
   auto load_v = [&](int b) {
     const int t = b * 32 + (lane % 32);
     const int tc = t < n ? t : (n - 1);
-    const uint4* vrow = reinterpret_cast<const uint4*>(vb + (size_t)tc * rw.sn + g * (D / 2));
+    const uint4* vrow = reinterpret_cast<const uint4*>(vb + (size_t)tc * rw.sn);
 #pragma unroll
-    for (int i = 0; i < D / 16; ++i) vr[i] = vrow[i];
+    for (int i = 0; i < D / 16; ++i) vr[i] = vrow[2 * i + g];
   };
   DWT dwt;
   if constexpr (DW) dwt.init(w);
@@ -923,8 +895,8 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
 
 template <int D, bool DW>
 constexpr size_t q_smem() {
-  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64 + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64)
-       + 2 * (size_t)kTile * D * 2 + kTile * 2 + (D + 8) * sizeof(float) + (DW ? DwTile<D, NT / 64>::DU_BYTES : 0);
+  return sizeof(uint4) * (Cfg<D>::W_IMG + GradLayout<D>::IMG + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64)
+       + 2 * (size_t)kTile * D * 2 + kTile * 2 + (D + 8) * sizeof(float) + (DW ? DwTile<D, 4>::DU_BYTES : 0);
 }
 template <int D, bool DW>
 constexpr size_t k_smem() {
@@ -937,7 +909,7 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
   if ((e = set_smem_once<bwd_prep_kernel<D, true, CENTRE>>(prep_smem_bytes<D>())) != hipSuccess) return e;
   if ((e = set_smem_once<bwd_prep_kernel<D, false, CENTRE>>(prep_smem_bytes<D>())) != hipSuccess) return e;
-  bwd_prep_kernel<D, true, CENTRE><<<dim3(p.BH, PREP_Y), PT, prep_smem_bytes<D>(), s>>>(a.state, nullptr, (uint4*)a.simg, a.scales,
+  bwd_prep_kernel<D, true, CENTRE><<<dim3(p.BH, PREP_Y), PT, prep_smem_bytes<D>(), s>>>(a.state, (uint4*)a.gimg, nullptr, a.scales,
                                                        (const uint16_t*)a.wq, (const uint16_t*)a.wk, (uint4*)a.wimg, p.H,
                                                        a.vbar, nullptr, nullptr, nullptr, p.P);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -947,11 +919,9 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     const size_t smem = a.dwq ? q_smem<D, true>() : q_smem<D, false>();
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
-    decltype(kernel)::value<<<dim3(p.P, p.BH), NT, smem, s>>>(
-        (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state,
-        (const uint4*)a.simg, (const uint4*)a.wimg, a.scales,
-        (uint16_t*)a.dq, a.partials, a.dw_part,
-        (const uint16_t*)a.blend_in, a.blend_r, a.blend_in ? a.dr_part : nullptr, a.cs_part, p.H, p.n, p.P, p.rows);
+    decltype(kernel)::value<<<dim3(p.P, p.BH), NTQ, smem, s>>>(
+        (const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, (const uint4*)a.gimg, (const uint4*)a.wimg, a.scales,
+        (uint16_t*)a.dq, a.partials, a.dw_part, a.blend_r, a.blend_in ? a.dr_part : nullptr, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
   if (a.blend_in) {

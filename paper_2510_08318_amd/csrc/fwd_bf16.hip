@@ -103,7 +103,7 @@ __global__ __launch_bounds__(NT3) void apply_bf16_kernel(const uint16_t* __restr
     __syncthreads();
     scale = head_scale<D, NT3>(stS, red, tid);
     if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(stW, sWA, tid);
-    build_state_image<D, NT3, true, KIND>(stS, sSA, scale, tid);
+    build_state_image<D, NT3, KIND>(stS, sSA, scale, tid);
   }
   __syncthreads();
   const float den_eps = KIND == kPhiRelu ? scale * kReluEps : 0.f;    // the image carries scale * z

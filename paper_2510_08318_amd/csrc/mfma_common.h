@@ -294,15 +294,11 @@ __device__ __forceinline__ float head_scale(const float* __restrict__ S, float* 
   return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
 }
 
-// fp32 state [D+1][D] of one (b,h) -> LDS image of the fp16 A operands of Y^T = S^T phi^T
-// (contraction over the features of phi): entry (ks, mb, lane=(m,g)) holds
-// scale * S[feature(ks,g,e)][channel(mb,m)], e = 0..7; the extra row block mb = MB holds
-// scale * z[feature] in rows 0 and 4 (one per lane group) and zeros elsewhere.
-// COLS: the same registers read as B operands of Y = phi S (lane (c,g) holds column c), with the
-// channels dealt out by ApplyLayout::channel_cols; the extra block then holds scale * z[feature] in
-// every column, so each lane of the product receives phi . z of its own token rows.
-// KIND = kPhiRelu: the features are the d channels in their plain order, 16ks + 8g + e.
-template <int D, bool COLS = false, int KIND = kPhiHedgehog>
+// fp32 state [D+1][D] of one (b,h) -> LDS image of the fp16 B operands of Y = phi S (contraction over the features of phi, tokens
+// on the accumulator rows): entry (ks, mb, lane=(c,g)) holds scale * S[feature(ks,g,e)][channel_cols(mb,c)], e = 0..7; the
+// extra column block mb = MB holds scale * z[feature] in every column, so each lane of the product receives phi . z of its
+// own token rows.  KIND = kPhiRelu: the features are the d channels in their plain order, 16ks + 8g + e.
+template <int D, int KIND = kPhiHedgehog>
 __device__ __forceinline__ uint4 state_image_entry(const float* __restrict__ S, float scale, int idx) {
   using L = ApplyLayout<D>;
   const int lane = idx % 64, mb = (idx / 64) % L::MBZ, ks = idx / (64 * L::MBZ);
@@ -311,23 +307,23 @@ __device__ __forceinline__ uint4 state_image_entry(const float* __restrict__ S, 
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int f = KIND == kPhiRelu ? 16 * ks + 8 * g + e : L::feature(ks, g, e);
-    if (mb < L::MB) x[e] = scale * S[f * D + (COLS ? L::channel_cols(mb, m) : L::channel(mb, m))];
-    else x[e] = (COLS || m == 0 || m == 4) ? scale * S[D * D + f] : 0.f;
+    x[e] = scale * (mb < L::MB ? S[f * D + L::channel_cols(mb, m)] : S[D * D + f]);
   }
   uint4 r;
   r.x = pack_f16x2(x[0], x[1]); r.y = pack_f16x2(x[2], x[3]);
   r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
   return r;
 }
-template <int D, int NTHREADS, bool COLS = false, int KIND = kPhiHedgehog>
+template <int D, int NTHREADS, int KIND = kPhiHedgehog>
 __device__ __forceinline__ void build_state_image(const float* __restrict__ S, uint4* sSA, float scale, int tid) {
   using L = ApplyLayout<D>;
-  for (int idx = tid; idx < L::KS * L::MBZ * 64; idx += NTHREADS) sSA[idx] = state_image_entry<D, COLS, KIND>(S, scale, idx);
+  for (int idx = tid; idx < L::KS * L::MBZ * 64; idx += NTHREADS) sSA[idx] = state_image_entry<D, KIND>(S, scale, idx);
 }
 
 // Index maps of G^T = S Y^T (contraction over the d channels; rows = features of phi), used by the
-// backward kernels.  The B operand is a token's half row: lane (t, g) feeds channels
-// g*D/2 + 8*ks + e in k-step ks.  The accumulator rows are laid out like phi itself: lane (t, g),
+// backward kernels.  The B operand is a token's row as the projections read it: lane (t, g) feeds channels
+// 16*ks + 8*g + e in k-step ks, so that a load instruction reads 32 adjacent bytes of each of 32 rows (with half rows per lane
+// group, 16 bytes of 64 lines, the lines of two tensors did not survive in the L1 until their last piece was read).  The accumulator rows are laid out like phi itself: lane (t, g),
 // row block mb, register r holds the softmax(+u) feature g*LOC + 16*mb + r for mb < GM/2 and
 // the softmax(-u) feature HALF + g*LOC + 16*(mb - GM/2) + r otherwise.
 template <int D>
@@ -337,7 +333,7 @@ struct GradLayout {
   static constexpr int KS = D / 16;       // k-steps over the channels
   static constexpr int GM = D / 32;       // row blocks over the D features
   static constexpr int IMG = KS * GM * 64;
-  __device__ static constexpr int channel(int ks, int g, int e) { return g * (D / 2) + 8 * ks + e; }
+  __device__ static constexpr int channel(int ks, int g, int e) { return 16 * ks + 8 * g + e; }
   __device__ static constexpr int feature(int mb, int m) {
     const int gg = (m / 4) % 2, r = 4 * (m / 8) + (m % 4);
     return (mb < GM / 2 ? 0 : HALF) + gg * LOC + 16 * (mb % (GM / 2)) + r;
@@ -355,45 +351,6 @@ __device__ __forceinline__ uint4 grad_image_entry(const float* __restrict__ S, f
   r.x = pack_f16x2(scale * row[0], scale * row[1]); r.y = pack_f16x2(scale * row[2], scale * row[3]);
   r.z = pack_f16x2(scale * row[4], scale * row[5]); r.w = pack_f16x2(scale * row[6], scale * row[7]);
   return r;
-}
-
-// One fp16 tile of the state that serves both products of the query-side backward, o = phi S (contraction over
-// the features) and g = dO S^T (contraction over the channels).  Row rho = 16ks + 8g + e holds the feature
-// that lane group g feeds as element e of k-step ks of phi (ApplyLayout::feature), column position
-// p = 32mb + i holds the channel behind accumulator row i of row block mb (ApplyLayout::channel): a
-// transposing read of rows 16ks .. 16ks+15, columns 32mb .. 32mb+31 is then the A operand (ks, mb) of o, and
-// the 8 channels g*D/2 + 8ks' .. +7 that a lane group feeds to g in k-step ks' sit in one row as two runs of
-// four positions, 16*ks' + 4g .. +3 and 8 further on: two 8-byte reads.  The 16-byte chunks of a row are
-// XOR-swizzled with swz<D>(rho), like every tile that is read with transposing reads.
-// idx = rho * (D/8) + (chunk as stored).
-template <int D>
-__device__ __forceinline__ uint4 state_tile_entry(const float* __restrict__ S, float scale, int idx) {
-  using L = ApplyLayout<D>;
-  const int rho = idx / (D / 8), c = (idx % (D / 8)) ^ swz<D>(rho);
-  const int f = L::feature(rho / 16, (rho / 8) % 2, rho % 8);
-  float x[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int pos = 8 * c + e;
-    x[e] = scale * S[f * D + L::channel(pos / 32, pos % 32)];
-  }
-  uint4 r;
-  r.x = pack_f16x2(x[0], x[1]); r.y = pack_f16x2(x[2], x[3]);
-  r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
-  return r;
-}
-// The z block of the image built by state_image_entry alone: entry (ks, lane).
-template <int D>
-__device__ __forceinline__ uint4 state_z_entry(const float* __restrict__ S, float scale, int idx) {
-  using L = ApplyLayout<D>;
-  return state_image_entry<D>(S, scale, ((idx / 64) * L::MBZ + L::MB) * 64 + idx % 64);
-}
-// Byte offset, inside the tile, of the row that holds feature GradLayout::feature(0, m) for this lane
-// (m = lane % 32), plus the lane group's 8 bytes inside a chunk; row block mb of g is 32*mb rows further on.
-template <int D>
-__device__ __forceinline__ int state_tile_grad_row(int lane) {
-  const int m = lane % 32, gg = (m / 4) % 2, r = 4 * (m / 8) + (m % 4);
-  return (16 * (r / 8) + 8 * gg + (r % 8)) * (D * 2) + 8 * (lane / 32);
 }
 
 // W~ [D][D/2] bf16 (one head) -> LDS image (fp16, exact) of the B operands of dX = dU W~^T
@@ -414,15 +371,6 @@ __device__ __forceinline__ uint4 w_image_t_entry(const uint16_t* __restrict__ w,
   r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
   return r;
 }
-template <int D, int NTHREADS>
-__device__ __forceinline__ void build_w_image_t(const uint16_t* __restrict__ w, uint4* sWB, int tid) {
-  constexpr int N = (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64;
-  for (int idx = tid; idx < N; idx += NTHREADS) sWB[idx] = w_image_t_entry<D>(w, idx);
-}
-
-template <int D>
-__device__ __forceinline__ int swz_out(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
-
 // Transposing LDS read: from a [row][column] fp16 tile, lane l of a wavefront receives
 // tile[row0 + 8*(l/32) + 0..7][col0 + l%32] -- an MFMA A or B operand whose contraction index
 // is the tile row.  Two ds_read_b64_tr_b16: within each group of 16 lanes, lane s supplies the

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(NT) void relu_state_kernel(const uint16_t* __restri
 
 // ---- operand images of a state, built once per head ------------------------------------------------
 // For M = S or dS ([D+1][D] fp32, row D = z or dz), both scaled by one power of two per head:
-//   cimg: B operands of Y = phi M (contraction over the features): state_image_entry<D, true, kPhiRelu>
+//   cimg: B operands of Y = phi M (contraction over the features): state_image_entry<D, kPhiRelu>
 //   timg: B operands of G = X M^T (contraction over the channels, columns = features):
 //         entry (ks, mb, lane=(c,g)) holds M[channel_cols(mb,c)][16ks + 8g + e], e = 0..7
 // grid (BH, 8): slice blockIdx.y of the entries.
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(PT) void relu_prep_kernel(const float* __restrict__
     }
   }
   const int first = blockIdx.y * PT + tid, step = PT * gridDim.y;
-  for (int idx = first; idx < CIMG; idx += step) cimg[(size_t)bh * CIMG + idx] = state_image_entry<D, true, kPhiRelu>(S, scale, idx);
+  for (int idx = first; idx < CIMG; idx += step) cimg[(size_t)bh * CIMG + idx] = state_image_entry<D, kPhiRelu>(S, scale, idx);
   for (int idx = first; idx < TIMG; idx += step) {
     const int lane = idx % 64, mb = (idx / 64) % L::MB, ks = idx / (64 * L::MB);
     const int c = lane % 32, g = lane / 32;
