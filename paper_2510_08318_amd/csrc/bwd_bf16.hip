@@ -7,7 +7,6 @@
 //   key side     g_j  = dL/dphi(k_j) = v_j dS^T + dz           dv_j = phi(k_j) dS
 //   through phi  du = p+ (g+ - <g+,p+>) - p- (g- - <g-,p->),   dx = du W~^T,   dW~ = sum x^T du
 //
-// bwd_prep_kernel : fp16 operand image of S for g (rows = features, contraction over channels)
 // bwd_q_kernel    : per 128-token tile: phi(Q), G = dO S^T, delta, du, dq; dS, dz partials (split-n); dW~_q partials
 // bwd_k_kernel    : per 32-token block: phi(K), g, du, dk, dv; dW~_k partials
 // (the partials are reduced in state_reduce.hip)
@@ -27,24 +26,17 @@
 namespace linattn {
 namespace {
 
-// ---- operand images, built once per head ---------------------------------------------------
-// The two main kernels need, per (b,h), MFMA operand images of S (resp. dS) in two index orders
-// and, per head, two images of W~.  Building them costs scattered reads; done by every workgroup
-// of a head it dominated the kernels' fixed cost, so they are built once here and the main
-// kernels copy them into LDS with coalesced 16-byte loads.
-//   grid (B*H, 8): slice blockIdx.y of the entries of (b,h); the workgroups of batch item 0 also
-//   build the W~ images of their head (WQK = true: both W~_q and W~_k images into wimg).
-//   Both passes write gimg, the A operands of G^T = S Y^T; WQK = false, the pass over dS, also writes simg, the B operands of
-//   dv = phi(k) dS with the tokens on the accumulator rows.
-// 512 threads: staging the state is latency, not bandwidth (256 threads: 16.8 + 10.8 us for the two
-// passes at config 5, 512: 11.9 + 8.3 us, 1024 the same; more slices per head change nothing).
-constexpr int PT = 512, PREP_Y = 8;
-// Both passes centre the state before it is rounded to fp16 operands (exact in real arithmetic; the roundings
+// ---- operand images ------------------------------------------------------------------------
+// Each workgroup of the two main kernels builds the images it needs in LDS, straight from the fp32 state and W~: the state is held
+// in registers (StateRegs) while the statistics below are taken, a microsecond or two of prologue.  As kernels of their own, once
+// per head, the images cost 11.5 + 11.5 us per call (12 heads of width 128, latency) and the main kernels as long a prologue to
+// copy them in.
+// Both sides centre the state before it is rounded to fp16 operands (exact in real arithmetic; the roundings
 // then act on what the gradients are made of instead of on a common part that cancels):
-//   pass over S:  S^c = S - z vbar^T with vbar = sum_j v_j / n (the + half of S sums to sum_j v_j, the + half
-//                 of z to n).  The query-side kernel then has delta^c = delta - dO . vbar, g is unchanged, and its dz comes
+//   query side:   S^c = S - z vbar^T with vbar = sum_j v_j / n (the + half of S sums to sum_j v_j, the + half
+//                 of z to n).  The kernel then has delta^c = delta - dO . vbar, g is unchanged, and its dz comes
 //                 out as dz^c = dz + dS vbar.
-//   pass over dS: the key-side dz is completed against the ROUNDED image: dzc[f] = dz^c[f] - vbar . r(dS[f]), so
+//   key side:     dz is completed against the ROUNDED image: dzc[f] = dz^c[f] - vbar . r(dS[f]), so
 //                 that v_j . r(dS[f]) + dzc[f] = (v_j - vbar) . r(dS[f]) + dz^c[f] holds exactly and the rounding
 //                 of the image acts on v_j - vbar, not on v_j (values with a common offset cost nothing).
 //   CENTRE (LINATTN_FLAG_CENTRED): the query-side kernel accumulated dS' = sum (phi - 2/D)^T dO/den and dz' likewise;
@@ -54,143 +46,126 @@ constexpr int PT = 512, PREP_Y = 8;
 //                 is constant over a half, and dv gets the constant row mean_+ + mean_- back.  (Without the flag
 //                 this last step is left out: where phi is spiky the rows of dS differ by orders of magnitude and
 //                 a common shift only adds rounding error to the small ones.)
-template <int D, bool WQK, bool CENTRE>
-__global__ __launch_bounds__(PT) void bwd_prep_kernel(const float* __restrict__ state, uint4* __restrict__ gimg,
-                                                       uint4* __restrict__ simg, float* __restrict__ scale_out,
-                                                       const uint16_t* __restrict__ wq, const uint16_t* __restrict__ wk,
-                                                       uint4* __restrict__ wimg, int H,
-                                                       float* __restrict__ vbar, float* __restrict__ dv_row, float* __restrict__ dzc,
-                                                       const float* __restrict__ cs_part, int P) {
-  using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  using G = GradLayout<D>;
-  constexpr int SIMG = L::KS * L::MBZ * 64;
-  constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
-  // the state (and W~) is staged in LDS with coalesced loads; the scattered reads of the image
-  // entries then hit LDS
-  extern __shared__ uint4 prep_smem[];
-  float* S = reinterpret_cast<float*>(prep_smem);                         // [(D+1)*D]
-  uint16_t* sWq = reinterpret_cast<uint16_t*>(S + (D + 1) * D);          // [D*HALF], then W~_k
-  uint16_t* sWk = sWq + D * C::HALF;
-  __shared__ float red[PT / 64];
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  {
-    const uint4* g = reinterpret_cast<const uint4*>(state + (size_t)bh * (D + 1) * D);
-    for (int i = tid; i < (D + 1) * D / 4; i += PT) reinterpret_cast<uint4*>(S)[i] = g[i];
-    if constexpr (WQK) {
-      if (bh < H) {
-        const uint4* gq = reinterpret_cast<const uint4*>(wq + (size_t)bh * D * C::HALF);
-        const uint4* gk = reinterpret_cast<const uint4*>(wk + (size_t)bh * D * C::HALF);
-        for (int i = tid; i < D * C::HALF / 8; i += PT) {
-          reinterpret_cast<uint4*>(sWq)[i] = gq[i];
-          reinterpret_cast<uint4*>(sWk)[i] = gk[i];
-        }
-      }
+
+// Query side: image of S^c, z in sZ[D]; returns the image's scale.  vbar_out: non-null in one workgroup per head.
+// scratch: FO*D + D + NTHREADS/64 floats of LDS.  Ends before the barrier that the caller needs after building its images.
+template <int D, int NTHREADS>
+__device__ __forceinline__ float build_query_state(const float* __restrict__ state, uint4* sGA, float* sZ, float* scratch,
+                                                   float* __restrict__ vbar_out, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(state, tid);
+  float* part = scratch;
+  float* vb = part + R::FO * D;
+  float* red = vb + D;
+  if (tid < D) sZ[tid] = state[D * D + tid];
+  S.octet_sums(part);
+  __syncthreads();
+  if (tid < D) {
+    // column sums of the + half of S; the + half of z sums to n
+    float sv = 0.f, nt = 0.f;
+#pragma unroll
+    for (int o = 0; o < R::FO / 2; ++o) sv += part[o * D + tid];
+#pragma unroll
+    for (int q = 0; q < D / 8; ++q) {
+      const float4 z = reinterpret_cast<const float4*>(sZ)[q];
+      nt += (z.x + z.y) + (z.z + z.w);
     }
+    const float c = sv / nt;
+    vb[tid] = c;
+    if (vbar_out != nullptr) vbar_out[tid] = c;
   }
   __syncthreads();
-  __shared__ float cA[D], cB[D], cC[D];
-  constexpr int HF = D / 2;
-  constexpr int PARTS = PT / D;                    // threads per channel (or feature) in the sums below
-  __shared__ float part[PT];
-  if constexpr (WQK) {
-    {
-      // column sums of the + half of S, PARTS threads per channel over HF / PARTS rows each; the + half of z sums to n
-      const int ch = tid % D, q = tid / D;
-      float sv = 0.f;
-      for (int f = q * (HF / PARTS); f < (q + 1) * (HF / PARTS); ++f) sv += S[f * D + ch];
-      part[tid] = sv;
-    }
-    __syncthreads();
-    if (tid < D) {
-      float sv = 0.f, nt = 0.f;
-      for (int q = 0; q < PARTS; ++q) sv += part[q * D + tid];
-      for (int f = 0; f < HF; ++f) nt += S[D * D + f];
-      const float vb = sv / nt;
-      cA[tid] = vb;
-      if (blockIdx.y == 0) vbar[(size_t)bh * D + tid] = vb;
-    }
-    __syncthreads();
-    for (int i = tid; i < D * D; i += PT) S[i] -= S[D * D + i / D] * cA[i % D];
-    __syncthreads();
-  } else {
-    // colsum (cA) and wsum of the query-side workgroups, in a fixed order (CENTRE only); vbar (cC)
-    if (tid < D) {
-      float t = 0.f;
-      if constexpr (CENTRE)
-        for (int p = 0; p < P; ++p) t += cs_part[((size_t)bh * P + p) * (D + 8) + tid];
-      cA[tid] = t;
-      cC[tid] = vbar[(size_t)bh * D + tid];
-    } else if (tid == D) {
-      float t = 0.f;
-      if constexpr (CENTRE)
-        for (int p = 0; p < P; ++p) t += cs_part[((size_t)bh * P + p) * (D + 8) + D];
-      red[0] = t;
-    }
-    __syncthreads();
-    const float wsum = red[0];
-    // means over each half: of dS per channel (thread = channel); dz^c (cB)
-    float m0 = 0.f, m1 = 0.f;
-    if (tid < D) {
-      for (int f = 0; f < HF; ++f) { m0 += S[f * D + tid]; m1 += S[(HF + f) * D + tid]; }
-      m0 *= 1.0f / HF; m1 *= 1.0f / HF;
-      if constexpr (!CENTRE) { m0 = 0.f; m1 = 0.f; }
-      if (blockIdx.y == 0) dv_row[(size_t)bh * D + tid] = (m0 + m1) + (4.0f / D) * cA[tid];
-      cB[tid] = S[D * D + tid] + (2.0f / D) * wsum;
-    }
-    __syncthreads();
-    if (tid < D) cA[tid] = m0;
-    __syncthreads();
-    for (int i = tid; i < HF * D; i += PT) S[i] -= cA[i % D];
-    __syncthreads();
-    if (tid < D) cA[tid] = m1;
-    if (tid == D) {
-      float a = 0.f, b = 0.f;
-      for (int f = 0; f < HF; ++f) { a += cB[f]; b += cB[HF + f]; }
-      red[0] = CENTRE ? a * (1.0f / HF) : 0.f; red[1] = CENTRE ? b * (1.0f / HF) : 0.f;
-    }
-    __syncthreads();
-    for (int i = HF * D + tid; i < D * D; i += PT) S[i] -= cA[i % D];
-    if (tid < D) {
-      cB[tid] -= tid < HF ? red[0] : red[1];
-      S[D * D + tid] = 0.f;            // the image's z block is not used on the key side and stays out of the scale
-    }
-    __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S.v[e][i] -= sZ[8 * S.fo + e] * vb[4 * S.cq + i];
+  if (!S.active) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S.v[e][i] = 0.f;
   }
-  const float scale = head_scale<D, PT>(S, red, tid);      // every block of a head computes the same value
-  if (blockIdx.y == 0 && tid == 0) scale_out[2 * bh] = scale;
-  if constexpr (!WQK) {
-    if (blockIdx.y == 0) {
-      // PARTS adjacent threads per feature, D / PARTS channels each, combined inside the wavefront
-      const int f = tid / PARTS, q = tid % PARTS;
-      const float inv = __builtin_amdgcn_rcpf(scale);       // exact: a power of two
-      float dot = 0.f;
-      for (int ch = q * (D / PARTS); ch < (q + 1) * (D / PARTS); ++ch)
-        dot = fmaf((float)(_Float16)(scale * S[f * D + ch]), cC[ch], dot);
-      for (int m = 1; m < PARTS; m <<= 1) dot += __shfl_xor(dot, m, 64);
-      if (q == 0) dzc[(size_t)bh * D + f] = cB[f] - dot * inv;
-    }
-  }
-  const int first = blockIdx.y * PT + tid, step = PT * gridDim.y;
-  for (int idx = first; idx < G::IMG; idx += step) gimg[(size_t)bh * G::IMG + idx] = grad_image_entry<D>(S, scale, idx);
-  if constexpr (!WQK)
-    for (int idx = first; idx < SIMG; idx += step) simg[(size_t)bh * SIMG + idx] = state_image_entry<D>(S, scale, idx);
-  if constexpr (WQK) {
-    if (bh < H) {
-      static_assert(C::W_IMG == WB_IMG, "the four W~ images have one size");
-      uint4* dst = wimg + (size_t)bh * 4 * C::W_IMG;
-      for (int idx = first; idx < C::W_IMG; idx += step) {
-        dst[idx] = w_image_entry<D>(sWq, idx);
-        dst[C::W_IMG + idx] = w_image_t_entry<D>(sWq, idx);
-        dst[2 * C::W_IMG + idx] = w_image_entry<D>(sWk, idx);
-        dst[3 * C::W_IMG + idx] = w_image_t_entry<D>(sWk, idx);
-      }
-    }
-  }
+  const float scale = S.scale(red, tid);
+  S.write_grad_image(sGA, scale);
+  return scale;
 }
 
-template <int D>
-constexpr size_t prep_smem_bytes() { return (size_t)(D + 1) * D * sizeof(float) + 2 * (size_t)D * (D / 2) * 2; }
+// Key side: the two images of dS, the matched dz in sZ[D], the constant row of dv in sRow[D] (zero without CENTRE); returns the scale.
+// scratch: FO*D + 4*D + NTHREADS/64 + 4 floats of LDS.
+template <int D, int NTHREADS, bool CENTRE>
+__device__ __forceinline__ float build_key_state(const float* __restrict__ dstate, uint4* sVA, uint4* sGA, float* sZ, float* sRow,
+                                                 float* scratch, const float* __restrict__ vbar, const float* __restrict__ cs_part,
+                                                 int P, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(dstate, tid);
+  float* part = scratch;
+  float* vb = part + R::FO * D;
+  float* m0 = vb + D;
+  float* m1 = m0 + D;
+  float* cB = m1 + D;
+  float* red = cB + D;                                      // [NTHREADS/64], then wsum and the two means of dz
+  float* misc = red + NTHREADS / 64;
+  if (tid < D) {
+    vb[tid] = vbar[tid];
+    cB[tid] = dstate[D * D + tid];
+  }
+  if constexpr (CENTRE) {
+    // column sums and wsum of the query-side workgroups, in a fixed order
+    float colsum = 0.f;
+    if (tid <= D)
+      for (int p = 0; p < P; p += 8) {
+        float t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = p + i < P ? cs_part[(size_t)(p + i) * (D + 8) + tid] : 0.f;
+        colsum += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+      }
+    if (tid == D) misc[0] = colsum;
+    S.octet_sums(part);
+    __syncthreads();
+    const float wsum = misc[0];
+    if (tid < D) {
+      float a = 0.f, b = 0.f;
+#pragma unroll
+      for (int o = 0; o < R::FO / 2; ++o) { a += part[o * D + tid]; b += part[(R::FO / 2 + o) * D + tid]; }
+      a *= 2.0f / D; b *= 2.0f / D;
+      m0[tid] = a; m1[tid] = b;
+      sRow[tid] = (a + b) + (4.0f / D) * colsum;
+      cB[tid] += (2.0f / D) * wsum;
+    }
+    __syncthreads();
+    if (tid < 128) {
+      // the mean of each half of dz^c, one wavefront each
+      float t = tid % 64 < D / 2 ? cB[(tid / 64) * (D / 2) + tid % 64] : 0.f;
+      for (int k = 32; k >= 1; k >>= 1) t += __shfl_xor(t, k, 64);
+      if (tid % 64 == 0) misc[1 + tid / 64] = t * (2.0f / D);
+    }
+    const float* m = S.fo < R::FO / 2 ? m0 : m1;
+    if (S.active) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S.v[e][i] -= m[4 * S.cq + i];
+    }
+  } else {
+    if (tid < D) sRow[tid] = 0.f;
+  }
+  const float scale = S.scale(red, tid);                    // (its barrier covers vb, cB and misc as well)
+  S.write_grad_image(sGA, scale);
+  S.template write_apply_image<ApplyLayout<D>::MB>(sVA, scale);
+  const float inv = __builtin_amdgcn_rcpf(scale);           // exact: a power of two
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dot = fmaf((float)(_Float16)(scale * S.v[e][i]), vb[4 * S.cq + i], dot);
+    for (int k = R::CQ / 2; k >= 1; k >>= 1) dot += __shfl_xor(dot, k, 64);
+    const int f = 8 * S.fo + e;
+    if (S.active && S.cq == 0) sZ[f] = cB[f] - (CENTRE ? misc[f < D / 2 ? 1 : 2] : 0.f) - dot * inv;
+  }
+  return scale;
+}
 
 // Softmax Jacobian of Eq. 5 for one token spread over a lane pair: gacc holds g in the GradLayout
 // row order (first GM/2 blocks the softmax(+u) half, then the softmax(-u) half), already scaled.
@@ -385,9 +360,8 @@ constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
 // tile's first half.
 template <int D, bool BLEND, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
-                                                    const float* __restrict__ state, const uint4* __restrict__ gimg,
-                                                    const uint4* __restrict__ wimg, const float* __restrict__ scales,
-                                                    uint16_t* __restrict__ dq,
+                                                    const uint16_t* __restrict__ wq, const float* __restrict__ state,
+                                                    float* __restrict__ vbar, uint16_t* __restrict__ dq,
                                                     float* __restrict__ partials, float* __restrict__ dw_part,
                                                     const float* __restrict__ rptr, float* __restrict__ dr_part,
                                                     float* __restrict__ cs_part,
@@ -420,10 +394,9 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   const float* sb = state + (size_t)bh * (D + 1) * D;
   const int ntile = (n + kTile - 1) / kTile;
 
-  copy_image<NTQ>(wimg + (size_t)h * 4 * C::W_IMG, sWA, C::W_IMG, tid);
-  copy_image<NTQ>(wimg + (size_t)h * 4 * C::W_IMG + C::W_IMG, sWB, WB_IMG, tid);
-  copy_image<NTQ>(gimg + (size_t)bh * G::IMG, sGA, G::IMG, tid);
-  for (int i = tid; i < D; i += NTQ) sZ[i] = sb[D * D + i];
+  build_w_image<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
+  build_w_image_t<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
+  const float scale = build_query_state<D, NTQ>(sb, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
   __syncthreads();
 
   // running power-of-two scale of the sums over tokens, the same in every wavefront; returns the factor for the accumulators
@@ -441,7 +414,6 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     const uint16_t* qb = q + head_base(rw, bh, H);
     const uint16_t* dob = dout + head_base(rw, bh, H);
     uint16_t* dqb = dq + head_base(rw, bh, H);
-    const float scale = scales[2 * bh];
     const int prow = 32 * pw + (lane % 32);
     float dr_acc = 0.f;
     uint4 xq[C::UK], xr[C::UK], dor[D / 16];
@@ -532,7 +504,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       pair32(Zp, lo, hi); Zp = lo + hi;
       pair32(Zm, lo, hi); Zm = lo + hi;
       const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
-      const float unscale = __builtin_amdgcn_rcpf(scale * stok);          // exact: powers of two
+      const float unscale = __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);     // exact: powers of two
       if constexpr (BLEND) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
         // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
@@ -723,20 +695,18 @@ constexpr int KAHEAD = 0;
 // DW: dW~_k is accumulated here as well (DwTile).  The eight wavefronts then walk their blocks in step: after each
 // round of eight blocks the wavefronts 0-3 park their k rows (read again) and du, all eight contract over those
 // 128 tokens (one 32 x 32 block of dW~_k each), then the same for the blocks of the wavefronts 4-7.
-template <int D, bool DW>
+template <int D, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                     const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
-                                                    const uint4* __restrict__ dsimg, const uint4* __restrict__ dgimg,
-                                                    const uint4* __restrict__ wimg, const float* __restrict__ scales,
                                                     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                     float* __restrict__ dw_part,
-                                                    const float* __restrict__ dzc, const float* __restrict__ dv_row,
-                                                    int H, int n, Rows rw) {
+                                                    const float* __restrict__ vbar, const float* __restrict__ cs_part,
+                                                    int H, int n, int P, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
   using G = GradLayout<D>;
   constexpr int NW = NTK / 64;
-  constexpr int SA_IMG = L::KS * L::MBZ * 64;
+  constexpr int SA_IMG = L::KS * L::MB * 64;
   constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
   using DWT = DwTile<D, NW>;
   extern __shared__ uint4 smem[];
@@ -746,7 +716,8 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
   uint4* sWB = sGA + G::IMG;
   float* sZ = reinterpret_cast<float*>(sWB + WB_IMG);   // [D] dz, unscaled
   float* sRed = sZ + D;                                 // [8]: DW: 0..3 the parked du blocks' inverse scales
-  char* sX = reinterpret_cast<char*>(sRed + 8);         // DW: [kTile][D] fp16, k rows of four blocks
+  float* sRow = sRed + 8;                               // [D] constant row of dv, then the scratch of the prologue
+  char* sX = reinterpret_cast<char*>(sRow + D);         // DW: [kTile][D] fp16, k rows of four blocks
   char* sU = sX + kTile * D * 2;                        // DW: [kTile][D/2] fp16, their du
 
   const int tid = threadIdx.x, lane = tid % 64;
@@ -757,21 +728,17 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
   const uint16_t* vb = v + head_base(rw, bh, H);
   uint16_t* dkb = dk + head_base(rw, bh, H);
   uint16_t* dvb = dv + head_base(rw, bh, H);
-  const float* ds = dstate + (size_t)bh * (D + 1) * D;
 
-  copy_image<NTK>(wimg + (size_t)h * 4 * C::W_IMG + 2 * C::W_IMG, sWA, C::W_IMG, tid);
-  copy_image<NTK>(wimg + (size_t)h * 4 * C::W_IMG + 3 * C::W_IMG, sWB, WB_IMG, tid);
-  copy_image<NTK>(dsimg + (size_t)bh * SA_IMG, sVA, SA_IMG, tid);
-  copy_image<NTK>(dgimg + (size_t)bh * G::IMG, sGA, G::IMG, tid);
-  const float scale = scales[2 * bh + 1];
-  // dzc is dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the
-  // features, for which dv gets a constant row back): see bwd_prep_kernel
-  for (int i = tid; i < D; i += NTK) sZ[i] = dzc[(size_t)bh * D + i];
+  build_w_image<D, NTK>(wk + (size_t)h * D * C::HALF, sWA, tid);
+  build_w_image_t<D, NTK>(wk + (size_t)h * D * C::HALF, sWB, tid);
+  // sZ: dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the features)
+  const float scale = build_key_state<D, NTK, CENTRE>(dstate + (size_t)bh * (D + 1) * D, sVA, sGA, sZ, sRow, sRow + D, vbar + (size_t)bh * D,
+                                                      CENTRE ? cs_part + (size_t)bh * P * (D + 8) : nullptr, P, tid);
   __syncthreads();
   const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
   float dv_add[L::MB];
 #pragma unroll
-  for (int mb = 0; mb < L::MB; ++mb) dv_add[mb] = dv_row[(size_t)bh * D + L::MB * (lane % 32) + mb];
+  for (int mb = 0; mb < L::MB; ++mb) dv_add[mb] = CENTRE ? sRow[L::MB * (lane % 32) + mb] : 0.f;
 
   const int nblk = (n + 31) / 32;
   const int stride = gridDim.x * NW;
@@ -820,7 +787,7 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
         for (int r = 0; r < 16; ++r) va[mb][r] = 0.f;
       const uint4* sva = sVA + lane + opaque_zero();
       pipelined_operands<L::KS * L::MB, KAHEAD>(
-          [&](int i) { return sva[((i / L::MB) * L::MBZ + i % L::MB) * 64]; },
+          [&](int i) { return sva[i * 64]; },
           [&](int i, uint4 b) {
             const int ks = i / L::MB, mb = i % L::MB;
             uint4 aq; aq.x = pk[4 * ks]; aq.y = pk[4 * ks + 1]; aq.z = pk[4 * ks + 2]; aq.w = pk[4 * ks + 3];
@@ -900,19 +867,16 @@ constexpr size_t q_smem() {
 }
 template <int D, bool DW>
 constexpr size_t k_smem() {
-  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64 + GradLayout<D>::IMG
-                          + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64) + (D + 8) * sizeof(float)
-       + (DW ? (size_t)kTile * D * 2 + DwTile<D, NTK / 64>::DU_BYTES : 0);
+  // the prologue's scratch lies where the DW tiles are afterwards
+  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + NTK / 64 + 4) * sizeof(float);
+  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, NTK / 64>::DU_BYTES : 0;
+  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64 + GradLayout<D>::IMG
+                          + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64) + (2 * D + 8) * sizeof(float)
+       + (scratch > tiles ? scratch : tiles);
 }
 template <int D, bool CENTRE>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  if ((e = set_smem_once<bwd_prep_kernel<D, true, CENTRE>>(prep_smem_bytes<D>())) != hipSuccess) return e;
-  if ((e = set_smem_once<bwd_prep_kernel<D, false, CENTRE>>(prep_smem_bytes<D>())) != hipSuccess) return e;
-  bwd_prep_kernel<D, true, CENTRE><<<dim3(p.BH, PREP_Y), PT, prep_smem_bytes<D>(), s>>>(a.state, (uint4*)a.gimg, nullptr, a.scales,
-                                                       (const uint16_t*)a.wq, (const uint16_t*)a.wk, (uint4*)a.wimg, p.H,
-                                                       a.vbar, nullptr, nullptr, nullptr, p.P);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   // dW~ partials: [BH][P] blocks of the query side, then [BH][KP] of the key side
   const size_t side_elems = (size_t)p.BH * p.P * D * (D / 2);
   auto launch_q = [&](auto kernel) -> hipError_t {
@@ -920,8 +884,7 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
     decltype(kernel)::value<<<dim3(p.P, p.BH), NTQ, smem, s>>>(
-        (const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, (const uint4*)a.gimg, (const uint4*)a.wimg, a.scales,
-        (uint16_t*)a.dq, a.partials, a.dw_part, a.blend_r, a.blend_in ? a.dr_part : nullptr, a.cs_part, p.H, p.n, p.P, p.rows);
+        (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state, a.vbar, (uint16_t*)a.dq, a.partials, a.dw_part, a.blend_r, a.blend_in ? a.dr_part : nullptr, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
   if (a.blend_in) {
@@ -936,20 +899,15 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   if ((e = launch_state_reduce(a.partials, a.dstate, p, s)) != hipSuccess) return e;
-  // images of dS: the second half of the scales array, no W~ images
-  bwd_prep_kernel<D, false, CENTRE><<<dim3(p.BH, PREP_Y), PT, prep_smem_bytes<D>(), s>>>(a.dstate, (uint4*)a.dgimg, (uint4*)a.dsimg, a.scales + 1,
-                                                        nullptr, nullptr, nullptr, p.H, a.vbar, a.dv_row, a.dzc, a.cs_part, p.P);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   auto launch_k = [&](auto kernel, size_t smem) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
     decltype(kernel)::value<<<dim3(p.KP, p.BH), NTK, smem, s>>>(
-        (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.wk, a.dstate,
-        (const uint4*)a.dsimg, (const uint4*)a.dgimg, (const uint4*)a.wimg, a.scales,
-        (uint16_t*)a.dk, (uint16_t*)a.dv, a.dw_part + side_elems, a.dzc, a.dv_row, p.H, p.n, p.rows);
+        (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.wk, a.dstate, (uint16_t*)a.dk, (uint16_t*)a.dv,
+        a.dw_part + side_elems, a.vbar, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
-  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, true>>{}, k_smem<D, true>()) : launch_k(KernelTag<bwd_k_kernel<D, false>>{}, k_smem<D, false>());
+  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, CENTRE, true>>{}, k_smem<D, true>()) : launch_k(KernelTag<bwd_k_kernel<D, CENTRE, false>>{}, k_smem<D, false>());
   if (e != hipSuccess) return e;
   if (a.dwq || a.dwk) {
     if ((e = launch_dw_reduce2(a.dwq ? a.dw_part : nullptr, a.dwq, p.P, a.dwk ? a.dw_part + side_elems : nullptr, a.dwk, p.KP, p, s)) != hipSuccess) return e;

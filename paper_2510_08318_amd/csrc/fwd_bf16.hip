@@ -90,19 +90,15 @@ __global__ __launch_bounds__(NT3) void apply_bf16_kernel(const uint16_t* __restr
 
   float scale;
   {
-    // The state and W~ of this (b,h) are first copied into LDS with coalesced 16-byte loads,
-    // then turned into the operand images from there: the scattered reads the images need would cost tens of microseconds from global memory.
+    // The state of this (b,h) is first copied into LDS with coalesced 16-byte loads,
+    // then turned into the operand image from there: the scattered reads the image needs would cost tens of microseconds from global memory.
     float* stS = reinterpret_cast<float*>(sStage);
-    uint16_t* stW = reinterpret_cast<uint16_t*>(stS + (D + 1) * D);
-    float* red = reinterpret_cast<float*>(stW + D * C::HALF);
+    float* red = stS + (D + 1) * D;
     const uint4* gS = reinterpret_cast<const uint4*>(state + (size_t)bh * (D + 1) * D);
-    const uint4* gW = reinterpret_cast<const uint4*>(wq + (size_t)h * D * C::HALF);
     for (int i = tid; i < (D + 1) * D / 4; i += NT3) reinterpret_cast<uint4*>(stS)[i] = gS[i];
-    if constexpr (KIND == kPhiHedgehog)
-      for (int i = tid; i < D * C::HALF / 8; i += NT3) reinterpret_cast<uint4*>(stW)[i] = gW[i];
+    if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
     __syncthreads();
     scale = head_scale<D, NT3>(stS, red, tid);
-    if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(stW, sWA, tid);
     build_state_image<D, NT3, KIND>(stS, sSA, scale, tid);
   }
   __syncthreads();
@@ -522,9 +518,9 @@ constexpr size_t state_ws_smem() { return sizeof(uint4) * Cfg<D>::W_IMG + 4 * (s
 
 template <int D>
 constexpr size_t apply_smem() {
-  // the images, then the prologue's staging of the fp32 state, W~ and a few reduction slots
+  // the images, then the prologue's staging of the fp32 state and a few reduction slots
   return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64)
-       + (size_t)(D + 1) * D * sizeof(float) + (size_t)D * (D / 2) * 2 + 64 * sizeof(float);
+       + (size_t)(D + 1) * D * sizeof(float) + 64 * sizeof(float);
 }
 
 }  // namespace

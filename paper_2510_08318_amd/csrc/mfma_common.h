@@ -59,24 +59,25 @@ __device__ __forceinline__ void pair32(float x, float& lo, float& hi) {
 }
 
 // W~ [D][D/2] bf16 (one head) -> LDS image of the A operands of U^T = W~^T X^T:
-// entry (ks, mb, lane=(m,g)) holds W~[16ks + 8g + e][owned_row<HALF>(mb, m)], e = 0..7.
-template <int D>
-__device__ __forceinline__ uint4 w_image_entry(const uint16_t* __restrict__ w, int idx) {
-  using C = Cfg<D>;
-  const int lane = idx % 64, mb = (idx / 64) % C::UM, ks = idx / (64 * C::UM);
-  const int m = lane % 32, g = lane / 32;
-  const int uf = owned_row<C::HALF>(mb, m);
-  uint32_t x[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = w[(16 * ks + 8 * g + e) * C::HALF + uf];
-  uint4 r;
-  r.x = x[0] | (x[1] << 16); r.y = x[2] | (x[3] << 16);
-  r.z = x[4] | (x[5] << 16); r.w = x[6] | (x[7] << 16);
-  return r;
-}
+// entry (ks, mb, lane=(m,g)) holds W~[16ks + 8g + e][owned_row<HALF>(mb, m)], e = 0..7.  A thread reads four adjacent features of
+// eight channels (8 bytes a load, all in flight together) and writes the four entries they fill.
 template <int D, int NTHREADS>
 __device__ __forceinline__ void build_w_image(const uint16_t* __restrict__ w, uint4* sWA, int tid) {
-  for (int idx = tid; idx < Cfg<D>::W_IMG; idx += NTHREADS) sWA[idx] = w_image_entry<D>(w, idx);
+  using C = Cfg<D>;
+  for (int it = tid; it < C::W_IMG / 4; it += NTHREADS) {
+    const int mq = it % 8, mb = (it / 8) % C::UM, g = (it / (8 * C::UM)) % 2, ks = it / (16 * C::UM);
+    const uint16_t* src = w + (16 * ks + 8 * g) * C::HALF + owned_row<C::HALF>(mb, 4 * mq);
+    uint2 r[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = *reinterpret_cast<const uint2*>(src + e * C::HALF);
+    auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
+    auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
+    uint4* dst = sWA + (ks * C::UM + mb) * 64 + 32 * g + 4 * mq;
+    dst[0] = make_uint4(lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x));
+    dst[1] = make_uint4(hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x));
+    dst[2] = make_uint4(lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y));
+    dst[3] = make_uint4(hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y));
+  }
 }
 
 // N uses (MFMAs) of 16-byte operands that come from LDS or global memory, each requested AHEAD uses
@@ -270,6 +271,9 @@ __device__ __forceinline__ void softmax_pair_ratio(const f32x16 (&u)[Cfg<D>::UM]
   }
 }
 
+__device__ __forceinline__ float state_scale(float amax) {
+  return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
+}
 // Power of two that brings the largest magnitude of a (b,h) state [D+1][D] (S rows, then z) into
 // [2^13, 2^14): fp16 operand images of the state are scaled by it.  Every consumer forms a ratio
 // or divides the scale out again.  red: >= NTHREADS/64 floats of LDS.  Contains __syncthreads().
@@ -291,7 +295,7 @@ __device__ __forceinline__ float head_scale(const float* __restrict__ S, float* 
 #pragma unroll
   for (int i = 1; i < NTHREADS / 64; ++i) amax = fmaxf(amax, red[i]);
   __syncthreads();                       // red may be reused by the caller
-  return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
+  return state_scale(amax);
 }
 
 // fp32 state [D+1][D] of one (b,h) -> LDS image of the fp16 B operands of Y = phi S (contraction over the features of phi, tokens
@@ -340,37 +344,91 @@ struct GradLayout {
   }
 };
 
-// One A-operand entry (ks, mb, lane) of the image of G^T = S Y^T: scale * S[feature][channel .. +7].
-template <int D>
-__device__ __forceinline__ uint4 grad_image_entry(const float* __restrict__ S, float scale, int idx) {
-  using G = GradLayout<D>;
-  const int lane = idx % 64, mb = (idx / 64) % G::GM, ks = idx / (64 * G::GM);
-  const int m = lane % 32, g = lane / 32;
-  const float* row = S + G::feature(mb, m) * D + G::channel(ks, g, 0);
-  uint4 r;
-  r.x = pack_f16x2(scale * row[0], scale * row[1]); r.y = pack_f16x2(scale * row[2], scale * row[3]);
-  r.z = pack_f16x2(scale * row[4], scale * row[5]); r.w = pack_f16x2(scale * row[6], scale * row[7]);
-  return r;
-}
-
 // W~ [D][D/2] bf16 (one head) -> LDS image (fp16, exact) of the B operands of dX = dU W~^T
 // (contraction over the d/2 pre-softmax features, tokens on the accumulator rows): entry
 // (ks, mb, lane=(c,g)) holds W~[channel_cols(mb,c)][g*LOC + 8ks + e], e = 0..7; ks < LOC/8, mb < D/32.
-template <int D>
-__device__ __forceinline__ uint4 w_image_t_entry(const uint16_t* __restrict__ w, int idx) {
+template <int D, int NTHREADS>
+__device__ __forceinline__ void build_w_image_t(const uint16_t* __restrict__ w, uint4* sWB, int tid) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
-  const int lane = idx % 64, mb = (idx / 64) % L::MB, ks = idx / (64 * L::MB);
-  const int m = lane % 32, g = lane / 32;
-  const uint16_t* row = w + L::channel_cols(mb, m) * C::HALF + g * C::LOC + 8 * ks;
-  float x[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(float, (uint32_t)row[e] << 16);
-  uint4 r;
-  r.x = pack_f16x2(x[0], x[1]); r.y = pack_f16x2(x[2], x[3]);
-  r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
-  return r;
+  for (int idx = tid; idx < (C::LOC / 8) * L::MB * 64; idx += NTHREADS) {
+    const int lane = idx % 64, mb = (idx / 64) % L::MB, ks = idx / (64 * L::MB);
+    const uint4 r = *reinterpret_cast<const uint4*>(w + L::channel_cols(mb, lane % 32) * C::HALF + (lane / 32) * C::LOC + 8 * ks);
+    sWB[idx] = make_uint4(bf16x2_to_f16x2(r.x), bf16x2_to_f16x2(r.y), bf16x2_to_f16x2(r.z), bf16x2_to_f16x2(r.w));
+  }
 }
+
+// A state (S, dS) [D][D] fp32 of one head in the registers of a workgroup: thread tid < ITEMS holds features 8*fo .. +7 x channels
+// 4*cq .. +3.  Eight 16-byte loads in flight per thread, and every operand image is written from here: the statistics an image
+// needs first (means, the largest magnitude) are taken on the registers, with no pass through LDS or memory for the state itself.
+template <int D, int NTHREADS>
+struct StateRegs {
+  using L = ApplyLayout<D>;
+  using G = GradLayout<D>;
+  static constexpr int CQ = D / 4, FO = D / 8, ITEMS = CQ * FO;
+  static_assert(ITEMS <= NTHREADS, "one item per thread");
+  float v[8][4];
+  int fo, cq;
+  bool active;
+  __device__ __forceinline__ void load(const float* __restrict__ S, int tid) {
+    active = tid < ITEMS;
+    cq = tid % CQ; fo = (tid / CQ) % FO;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float4 r = active ? *reinterpret_cast<const float4*>(S + (8 * fo + e) * D + 4 * cq) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[e][0] = r.x; v[e][1] = r.y; v[e][2] = r.z; v[e][3] = r.w;
+    }
+  }
+  // part[FO][D]: sums over each octet of features
+  __device__ __forceinline__ void octet_sums(float* part) const {
+    if (!active) return;
+    float s[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      s[i] = ((v[0][i] + v[1][i]) + (v[2][i] + v[3][i])) + ((v[4][i] + v[5][i]) + (v[6][i] + v[7][i]));
+    *reinterpret_cast<float4*>(part + fo * D + 4 * cq) = make_float4(s[0], s[1], s[2], s[3]);
+  }
+  // Power of two that brings the largest magnitude into [2^13, 2^14) (see head_scale); red: NTHREADS/64 floats.  Contains a barrier.
+  __device__ __forceinline__ float scale(float* red, int tid) const {
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(v[e][i]));
+    for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+    if (tid % 64 == 0) red[tid / 64] = amax;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NTHREADS / 64; ++i) amax = fmaxf(amax, red[i]);
+    return state_scale(amax);
+  }
+  // A operands of G^T = S Y^T (GradLayout): entry (ks, mb, lane = (m, g)) holds scale * S[feature(mb, m)][channel(ks, g, 0) ..].
+  __device__ __forceinline__ void write_grad_image(uint4* img, float sc) const {
+    if (!active) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int f = 8 * fo + e, q = f % (D / 4), r = q % 16;
+      const int mb = f / (D / 2) * (G::GM / 2) + q / 16, m = 8 * (r / 4) + 4 * ((f / (D / 4)) % 2) + r % 4;
+      const int ks = cq / 4, g = (cq / 2) % 2;
+      uint2* dst = reinterpret_cast<uint2*>(img + (ks * G::GM + mb) * 64 + 32 * g + m) + cq % 2;
+      *dst = make_uint2(pack_f16x2(sc * v[e][0], sc * v[e][1]), pack_f16x2(sc * v[e][2], sc * v[e][3]));
+    }
+  }
+  // B operands of Y = phi S: entry (ks, mb, lane = (c, g)) of row length MBS column blocks holds scale * S[feature(ks, g, e)][channel_cols(mb, c)].
+  template <int MBS>
+  __device__ __forceinline__ void write_apply_image(uint4* img, float sc) const {
+    if (!active) return;
+    const int half = fo / (D / 16), g = (fo / (D / 32)) % 2, ks = half * (L::KS / 2) + fo % (D / 32);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ch = 4 * cq + i;
+      img[(ks * MBS + ch % L::MB) * 64 + 32 * g + ch / L::MB] =
+          make_uint4(pack_f16x2(sc * v[0][i], sc * v[1][i]), pack_f16x2(sc * v[2][i], sc * v[3][i]),
+                     pack_f16x2(sc * v[4][i], sc * v[5][i]), pack_f16x2(sc * v[6][i], sc * v[7][i]));
+    }
+  }
+};
+
 // Transposing LDS read: from a [row][column] fp16 tile, lane l of a wavefront receives
 // tile[row0 + 8*(l/32) + 0..7][col0 + l%32] -- an MFMA A or B operand whose contraction index
 // is the tile row.  Two ds_read_b64_tr_b16: within each group of 16 lanes, lane s supplies the
