@@ -42,12 +42,16 @@ __device__ __forceinline__ void st_nt(uint32_t* p, uint32_t v) { __builtin_nonte
 
 constexpr int NT3 = 768;         // 12 wavefronts, one workgroup per compute unit
 
+// The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
+// us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 (the workgroup fills three of a
+// SIMD's wavefront slots whatever it is) keeps the loop's schedule from spreading into the prologue's registers: without it the
+// CogVideoX-2B shape loses 2 us.
 // BLEND: mixed attention (Sec. 4.1, Eq. 6): out = r' s + (1 - r') o with the softmax-branch output
 // s read in the same pieces as out is stored, and r' = clip(*rptr, 0, 1).
 // KIND = kPhiRelu: phi(q) = max(q, 0) straight from the loaded rows (no projection, no W~), features
 // in channel order, kReluEps in the denominator.
 template <int D, bool BLEND, int KIND>
-__global__ __launch_bounds__(NT3) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+__global__ __launch_bounds__(NT3, D == 64 ? (BLEND ? 4 : 5) : 3) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ state, uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
                                                          int H, int n, Rows rw) {
@@ -60,7 +64,7 @@ __global__ __launch_bounds__(NT3) void apply_bf16_kernel(const uint16_t* __restr
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
   uint4* sSA = sWA + C::W_IMG;
-  char* sStage = reinterpret_cast<char*>(sSA + SA_IMG); // staging area of the prologue
+  char* sStage = reinterpret_cast<char*>(sSA + SA_IMG); // z and reduction slots of the prologue
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -90,16 +94,17 @@ __global__ __launch_bounds__(NT3) void apply_bf16_kernel(const uint16_t* __restr
 
   float scale;
   {
-    // The state of this (b,h) is first copied into LDS with coalesced 16-byte loads,
-    // then turned into the operand image from there: the scattered reads the image needs would cost tens of microseconds from global memory.
-    float* stS = reinterpret_cast<float*>(sStage);
-    float* red = stS + (D + 1) * D;
-    const uint4* gS = reinterpret_cast<const uint4*>(state + (size_t)bh * (D + 1) * D);
-    for (int i = tid; i < (D + 1) * D / 4; i += NT3) reinterpret_cast<uint4*>(stS)[i] = gS[i];
+    using R = StateRegs<D, NT3>;
+    const float* sb = state + (size_t)bh * (D + 1) * D;
+    float* sZ = reinterpret_cast<float*>(sStage);
+    R S;
+    S.load(sb, tid);
+    const float zv = tid < D ? sb[D * D + tid] : 0.f;
+    if (tid < D) sZ[tid] = zv;
     if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
-    __syncthreads();
-    scale = head_scale<D, NT3>(stS, red, tid);
-    build_state_image<D, NT3, KIND>(stS, sSA, scale, tid);
+    scale = S.scale(sZ + D, tid, fabsf(zv));            // (its barrier covers z as well)
+    S.template write_apply_image<L::MBZ, KIND>(sSA, scale);
+    R::template write_z_block<KIND>(sZ, sSA, scale, tid);
   }
   __syncthreads();
   const float den_eps = KIND == kPhiRelu ? scale * kReluEps : 0.f;    // the image carries scale * z
@@ -518,9 +523,8 @@ constexpr size_t state_ws_smem() { return sizeof(uint4) * Cfg<D>::W_IMG + 4 * (s
 
 template <int D>
 constexpr size_t apply_smem() {
-  // the images, then the prologue's staging of the fp32 state and a few reduction slots
-  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64)
-       + (size_t)(D + 1) * D * sizeof(float) + 64 * sizeof(float);
+  // the images, then z and a few reduction slots of the prologue
+  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64) + (D + 64) * sizeof(float);
 }
 
 }  // namespace

@@ -318,12 +318,6 @@ __device__ __forceinline__ uint4 state_image_entry(const float* __restrict__ S, 
   r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
   return r;
 }
-template <int D, int NTHREADS, int KIND = kPhiHedgehog>
-__device__ __forceinline__ void build_state_image(const float* __restrict__ S, uint4* sSA, float scale, int tid) {
-  using L = ApplyLayout<D>;
-  for (int idx = tid; idx < L::KS * L::MBZ * 64; idx += NTHREADS) sSA[idx] = state_image_entry<D, KIND>(S, scale, idx);
-}
-
 // Index maps of G^T = S Y^T (contraction over the d channels; rows = features of phi), used by the
 // backward kernels.  The B operand is a token's row as the projections read it: lane (t, g) feeds channels
 // 16*ks + 8*g + e in k-step ks, so that a load instruction reads 32 adjacent bytes of each of 32 rows (with half rows per lane
@@ -359,7 +353,7 @@ __device__ __forceinline__ void build_w_image_t(const uint16_t* __restrict__ w, 
 }
 
 // A state (S, dS) [D][D] fp32 of one head in the registers of a workgroup: thread tid < ITEMS holds features 8*fo .. +7 x channels
-// 4*cq .. +3.  Eight 16-byte loads in flight per thread, and every operand image is written from here: the statistics an image
+// 4*cq .. +3, the others zeros.  Eight 16-byte loads in flight per thread, and every operand image is written from here: the statistics an image
 // needs first (means, the largest magnitude) are taken on the registers, with no pass through LDS or memory for the state itself.
 template <int D, int NTHREADS>
 struct StateRegs {
@@ -388,9 +382,20 @@ struct StateRegs {
       s[i] = ((v[0][i] + v[1][i]) + (v[2][i] + v[3][i])) + ((v[4][i] + v[5][i]) + (v[6][i] + v[7][i]));
     *reinterpret_cast<float4*>(part + fo * D + 4 * cq) = make_float4(s[0], s[1], s[2], s[3]);
   }
-  // Power of two that brings the largest magnitude into [2^13, 2^14) (see head_scale); red: NTHREADS/64 floats.  Contains a barrier.
-  __device__ __forceinline__ float scale(float* red, int tid) const {
-    float amax = 0.f;
+  // The column block that carries z (column block MB of MBS = MB + 1): entry (ks, MB, lane = (c, g)) holds scale * z[feature(ks, g, e)]
+  // whatever c is, so each lane of the product receives phi . z of its own token rows.
+  template <int KIND = kPhiHedgehog>
+  static __device__ __forceinline__ void write_z_block(const float* z, uint4* img, float sc, int tid) {
+    for (int it = tid; it < L::KS * 64; it += NTHREADS) {
+      const int ks = it / 64, g = (it / 32) % 2;
+      const float* f = z + (KIND == kPhiRelu ? 16 * ks + 8 * g : L::feature(ks, g, 0));
+      img[(ks * L::MBZ + L::MB) * 64 + it % 64] = make_uint4(pack_f16x2(sc * f[0], sc * f[1]), pack_f16x2(sc * f[2], sc * f[3]),
+                                                             pack_f16x2(sc * f[4], sc * f[5]), pack_f16x2(sc * f[6], sc * f[7]));
+    }
+  }
+  // Power of two that brings the largest magnitude (of amax and the state) into [2^13, 2^14): fp16 operand images of the state are
+  // scaled by it; every consumer forms a ratio or divides the scale out again.  red: NTHREADS/64 floats.  Contains a barrier.
+  __device__ __forceinline__ float scale(float* red, int tid, float amax = 0.f) const {
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
@@ -414,11 +419,14 @@ struct StateRegs {
       *dst = make_uint2(pack_f16x2(sc * v[e][0], sc * v[e][1]), pack_f16x2(sc * v[e][2], sc * v[e][3]));
     }
   }
-  // B operands of Y = phi S: entry (ks, mb, lane = (c, g)) of row length MBS column blocks holds scale * S[feature(ks, g, e)][channel_cols(mb, c)].
-  template <int MBS>
+  // B operands of Y = phi S (contraction over the features of phi, tokens on the accumulator rows): entry (ks, mb, lane = (c, g)), MBS
+  // column blocks to a k-step, holds scale * S[feature(ks, g, e)][channel_cols(mb, c)].
+  // KIND = kPhiRelu: the features are the d channels in their plain order, 16ks + 8g + e.
+  template <int MBS, int KIND = kPhiHedgehog>
   __device__ __forceinline__ void write_apply_image(uint4* img, float sc) const {
     if (!active) return;
-    const int half = fo / (D / 16), g = (fo / (D / 32)) % 2, ks = half * (L::KS / 2) + fo % (D / 32);
+    const int g = KIND == kPhiRelu ? fo % 2 : (fo / (D / 32)) % 2;
+    const int ks = KIND == kPhiRelu ? fo / 2 : fo / (D / 16) * (L::KS / 2) + fo % (D / 32);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int ch = 4 * cq + i;
