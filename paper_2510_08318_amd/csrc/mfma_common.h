@@ -274,50 +274,6 @@ __device__ __forceinline__ void softmax_pair_ratio(const f32x16 (&u)[Cfg<D>::UM]
 __device__ __forceinline__ float state_scale(float amax) {
   return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
 }
-// Power of two that brings the largest magnitude of a (b,h) state [D+1][D] (S rows, then z) into
-// [2^13, 2^14): fp16 operand images of the state are scaled by it.  Every consumer forms a ratio
-// or divides the scale out again.  red: >= NTHREADS/64 floats of LDS.  Contains __syncthreads().
-template <int D, int NTHREADS>
-__device__ __forceinline__ float head_scale(const float* __restrict__ S, float* red, int tid) {
-  constexpr int N = (D + 1) * D;
-  float amax = 0.f;
-  for (int i0 = tid; i0 < N; i0 += 8 * NTHREADS) {
-    float t[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { const int i = i0 + j * NTHREADS; t[j] = i < N ? fabsf(S[i]) : 0.f; }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) amax = fmaxf(amax, t[j]);
-  }
-  for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
-  if (tid % 64 == 0) red[tid / 64] = amax;
-  __syncthreads();
-  amax = red[0];
-#pragma unroll
-  for (int i = 1; i < NTHREADS / 64; ++i) amax = fmaxf(amax, red[i]);
-  __syncthreads();                       // red may be reused by the caller
-  return state_scale(amax);
-}
-
-// fp32 state [D+1][D] of one (b,h) -> LDS image of the fp16 B operands of Y = phi S (contraction over the features of phi, tokens
-// on the accumulator rows): entry (ks, mb, lane=(c,g)) holds scale * S[feature(ks,g,e)][channel_cols(mb,c)], e = 0..7; the
-// extra column block mb = MB holds scale * z[feature] in every column, so each lane of the product receives phi . z of its
-// own token rows.  KIND = kPhiRelu: the features are the d channels in their plain order, 16ks + 8g + e.
-template <int D, int KIND = kPhiHedgehog>
-__device__ __forceinline__ uint4 state_image_entry(const float* __restrict__ S, float scale, int idx) {
-  using L = ApplyLayout<D>;
-  const int lane = idx % 64, mb = (idx / 64) % L::MBZ, ks = idx / (64 * L::MBZ);
-  const int m = lane % 32, g = lane / 32;
-  float x[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int f = KIND == kPhiRelu ? 16 * ks + 8 * g + e : L::feature(ks, g, e);
-    x[e] = scale * (mb < L::MB ? S[f * D + L::channel_cols(mb, m)] : S[D * D + f]);
-  }
-  uint4 r;
-  r.x = pack_f16x2(x[0], x[1]); r.y = pack_f16x2(x[2], x[3]);
-  r.z = pack_f16x2(x[4], x[5]); r.w = pack_f16x2(x[6], x[7]);
-  return r;
-}
 // Index maps of G^T = S Y^T (contraction over the d channels; rows = features of phi), used by the
 // backward kernels.  The B operand is a token's row as the projections read it: lane (t, g) feeds channels
 // 16*ks + 8*g + e in k-step ks, so that a load instruction reads 32 adjacent bytes of each of 32 rows (with half rows per lane
@@ -408,12 +364,17 @@ struct StateRegs {
     return state_scale(amax);
   }
   // A operands of G^T = S Y^T (GradLayout): entry (ks, mb, lane = (m, g)) holds scale * S[feature(mb, m)][channel(ks, g, 0) ..].
+  // KIND = kPhiRelu: the rows are ordered so that register r of block mb in a lane of group g is feature 16*(2mb + r/8) + 8g + r%8,
+  // the channels which that lane holds of its token's row.
+  template <int KIND = kPhiHedgehog>
   __device__ __forceinline__ void write_grad_image(uint4* img, float sc) const {
     if (!active) return;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int f = 8 * fo + e, q = f % (D / 4), r = q % 16;
-      const int mb = f / (D / 2) * (G::GM / 2) + q / 16, m = 8 * (r / 4) + 4 * ((f / (D / 4)) % 2) + r % 4;
+      const int f = 8 * fo + e, q = f % (D / 4);
+      const int r = KIND == kPhiRelu ? 8 * ((fo / 2) % 2) + e : q % 16;
+      const int mb = KIND == kPhiRelu ? fo / 4 : f / (D / 2) * (G::GM / 2) + q / 16;
+      const int m = 8 * (r / 4) + 4 * (KIND == kPhiRelu ? fo % 2 : (f / (D / 4)) % 2) + r % 4;
       const int ks = cq / 4, g = (cq / 2) % 2;
       uint2* dst = reinterpret_cast<uint2*>(img + (ks * G::GM + mb) * 64 + 32 * g + m) + cq % 2;
       *dst = make_uint2(pack_f16x2(sc * v[e][0], sc * v[e][1]), pack_f16x2(sc * v[e][2], sc * v[e][3]));
@@ -516,12 +477,6 @@ __device__ __forceinline__ uint4 relu_f16x8(uint4 x) {
   r.x = bf16x2_to_f16x2(relu_bf16x2(x.x)); r.y = bf16x2_to_f16x2(relu_bf16x2(x.y));
   r.z = bf16x2_to_f16x2(relu_bf16x2(x.z)); r.w = bf16x2_to_f16x2(relu_bf16x2(x.w));
   return r;
-}
-
-// Copy n16 16-byte entries from global memory into LDS (all threads of the workgroup).
-template <int NTHREADS>
-__device__ __forceinline__ void copy_image(const uint4* __restrict__ src, uint4* dst, int n16, int tid) {
-  for (int i = tid; i < n16; i += NTHREADS) dst[i] = src[i];
 }
 
 // Maximum of x over the wavefront, given x already equal in lanes l and l^32: DPP steps inside each

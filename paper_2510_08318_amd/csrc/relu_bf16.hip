@@ -8,7 +8,6 @@
 // the state pass (K and V as stored: exact products, no conversion), fp16 where a state or a
 // gradient is an operand (the query pass and the backward):
 //   relu_state_kernel  : S_p = sum_j phi(k_j)^T v_j, z_p = sum_j phi(k_j) over the tiles of a split
-//   relu_prep_kernel   : MFMA operand images of a state (S or dS), built once per head
 //   relu_bwd_q_kernel  : den, G = dO S^T, delta, dq; split-n partials of dS, dz
 //   relu_bwd_k_kernel  : dv = phi(k) dS, dk = (v dS^T + dz) where k > 0
 // Gradients (chain rule through Eq. 3, then the mask of max(x, 0), whose derivative at 0 is taken as 0):
@@ -175,299 +174,329 @@ __global__ __launch_bounds__(NT) void relu_state_kernel(const uint16_t* __restri
   }
 }
 
-// ---- operand images of a state, built once per head ------------------------------------------------
-// For M = S or dS ([D+1][D] fp32, row D = z or dz), both scaled by one power of two per head:
-//   cimg: B operands of Y = phi M (contraction over the features): state_image_entry<D, kPhiRelu>
-//   timg: B operands of G = X M^T (contraction over the channels, columns = features):
-//         entry (ks, mb, lane=(c,g)) holds M[channel_cols(mb,c)][16ks + 8g + e], e = 0..7
-// grid (BH, 8): slice blockIdx.y of the entries.
-constexpr int PT = 512;      // threads of the image builder (staging the state is latency-bound)
-// The images are built with the head's mean value row taken out, as in the Eq. 5 path (exact in real
-// arithmetic; values with a common offset then cost the gradients nothing):
-//   pass over S (DS = false): S^c = S - z c^T with c = sum_f S[f] / sum_f z[f], the phi-weighted mean of v (any
-//     row c would do: the query side then works with o - c and delta - dO . c, dq is unchanged up to
-//     eps / den, and its dz comes out as dz + dS c); c is written to `mean_row`;
-//   pass over dS (DS = true): dzc[f] = dz[f] - c . r(dS[f]) with r the fp16 rounding of the image, so that
-//     v_j . r(dS[f]) + dzc[f] = (v_j - c) . r(dS[f]) + (dz + dS c)[f] holds exactly on the key side.
-template <int D, bool DS>
-__global__ __launch_bounds__(PT) void relu_prep_kernel(const float* __restrict__ state, uint4* __restrict__ cimg,
-                                                        uint4* __restrict__ timg, float* __restrict__ scale_out,
-                                                        float* __restrict__ mean_row, float* __restrict__ dzc) {
-  using L = ApplyLayout<D>;
-  constexpr int CIMG = L::KS * L::MBZ * 64, TIMG = L::KS * L::MB * 64;
-  extern __shared__ uint4 prep_stage[];
-  float* S = reinterpret_cast<float*>(prep_stage);                        // [(D+1)*D]
-  __shared__ float red[PT / 64];
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  {
-    const uint4* gsrc = reinterpret_cast<const uint4*>(state + (size_t)bh * (D + 1) * D);
-    for (int i = tid; i < (D + 1) * D / 4; i += PT) reinterpret_cast<uint4*>(S)[i] = gsrc[i];
+// ---- backward ----------------------------------------------------------------------------------
+// Both sides work with the head's phi-weighted mean value row c = sum_f S[f] / sum_f z[f] taken out (exact in real arithmetic, any row
+// would do; values with a common offset then cost the gradients nothing):
+//   query side: S^c = S - z c^T; o - c and delta - dO . c take the places of o and delta, dq is unchanged up to eps / den, and its dz
+//     comes out as dz + dS c;
+//   key side: dzc[f] = dz[f] - c . r(dS[f]) with r the fp16 rounding of the image, so that
+//     v_j . r(dS[f]) + dzc[f] = (v_j - c) . r(dS[f]) + (dz + dS c)[f] holds exactly.
+// Each workgroup builds the operand images it needs in its prologue, from the state in registers (StateRegs).  Built by a kernel
+// of their own and copied, they cost two launches of 9.4 us more (12 heads x 32760 x 128).
+//
+// The image of S^c in sG, z in sZ[D]; returns the scale.  scratch: FO*D + D + NTHREADS/64 floats of LDS.
+template <int D, int NTHREADS>
+__device__ __forceinline__ float build_relu_query_state(const float* __restrict__ state, uint4* sG, float* sZ, float* scratch,
+                                                        float* __restrict__ mean_out, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(state, tid);
+  float* part = scratch;
+  float* mean = part + R::FO * D;
+  float* red = mean + D;
+  if (tid < D) sZ[tid] = state[D * D + tid];
+  S.octet_sums(part);
+  __syncthreads();
+  if (tid < D) {
+    float sv = 0.f, zt = 0.f;
+#pragma unroll
+    for (int o = 0; o < R::FO; ++o) sv += part[o * D + tid];
+#pragma unroll
+    for (int q = 0; q < D / 4; ++q) {
+      const float4 z = reinterpret_cast<const float4*>(sZ)[q];
+      zt += (z.x + z.y) + (z.z + z.w);
+    }
+    const float c = zt > 0.f ? sv / zt : 0.f;
+    mean[tid] = c;
+    if (mean_out != nullptr) mean_out[tid] = c;
   }
   __syncthreads();
-  __shared__ float cM[D];
-  if constexpr (!DS) {
-    if (tid < D) {
-      float sv = 0.f, zt = 0.f;
-      for (int f = 0; f < D; ++f) { sv += S[f * D + tid]; zt += S[D * D + f]; }
-      const float c = zt > 0.f ? sv / zt : 0.f;
-      cM[tid] = c;
-      if (blockIdx.y == 0) mean_row[(size_t)bh * D + tid] = c;
-    }
-    __syncthreads();
-    for (int i = tid; i < D * D; i += PT) S[i] -= S[D * D + i / D] * cM[i % D];
-    __syncthreads();
-  } else {
-    if (tid < D) cM[tid] = mean_row[(size_t)bh * D + tid];
-    __syncthreads();
-  }
-  const float scale = head_scale<D, PT>(S, red, tid);      // every block of a head computes the same value
-  if (blockIdx.y == 0 && tid == 0) scale_out[2 * bh] = scale;      // [BH][2]: S, dS
-  if constexpr (DS) {
-    if (blockIdx.y == 0 && tid < D) {
-      const float inv = __builtin_amdgcn_rcpf(scale);       // exact: a power of two
-      float dot = 0.f;
-      for (int ch = 0; ch < D; ++ch) dot = fmaf((float)(_Float16)(scale * S[tid * D + ch]), cM[ch], dot);
-      dzc[(size_t)bh * D + tid] = S[D * D + tid] - dot * inv;
-    }
-  }
-  const int first = blockIdx.y * PT + tid, step = PT * gridDim.y;
-  for (int idx = first; idx < CIMG; idx += step) cimg[(size_t)bh * CIMG + idx] = state_image_entry<D, kPhiRelu>(S, scale, idx);
-  for (int idx = first; idx < TIMG; idx += step) {
-    const int lane = idx % 64, mb = (idx / 64) % L::MB, ks = idx / (64 * L::MB);
-    const int c = lane % 32, g = lane / 32;
-    const float* row = S + L::channel_cols(mb, c) * D + 16 * ks + 8 * g;
-    uint4 r;
-    r.x = pack_f16x2(scale * row[0], scale * row[1]); r.y = pack_f16x2(scale * row[2], scale * row[3]);
-    r.z = pack_f16x2(scale * row[4], scale * row[5]); r.w = pack_f16x2(scale * row[6], scale * row[7]);
-    timg[(size_t)bh * TIMG + idx] = r;
-  }
-}
-
-// One channel (0..3, or 0..1 for d = 64) of a lane's piece of a row, as float.
-__device__ __forceinline__ float piece_elem(const uint2& p, int i) {
-  const uint32_t wv = i < 2 ? p.x : p.y;
-  return (i % 2) ? __builtin_bit_cast(float, wv & 0xffff0000u) : __builtin_bit_cast(float, wv << 16);
-}
-__device__ __forceinline__ float piece_elem(const uint32_t& p, int i) {
-  return i ? __builtin_bit_cast(float, p & 0xffff0000u) : __builtin_bit_cast(float, p << 16);
-}
-template <int MB> struct RowPieceT;
-template <> struct RowPieceT<4> { typedef uint2 type; };
-template <> struct RowPieceT<2> { typedef uint32_t type; };
-
-// Rows of x (bf16) in the layout of an accumulator with the tokens on its rows: piece r of lane (c,g)
-// is token t0 + 8*(r/4) + 4g + r%4, channels MB*c .. MB*c + MB-1.  Rows past n read as row n-1.
-template <int D, typename Piece>
-__device__ __forceinline__ void load_row_pieces(const uint16_t* base, size_t sn, int t0, int n, int lane, Piece (&out)[16]) {
-  constexpr int MB = D / 32;
-  const int c = lane % 32, g = lane / 32;
+  if (S.active) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    int t = t0 + 8 * (r / 4) + 4 * g + (r % 4);
-    t = t < n ? t : n - 1;
-    out[r] = *reinterpret_cast<const Piece*>(base + (size_t)t * sn + MB * c);
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S.v[e][i] -= sZ[8 * S.fo + e] * mean[4 * S.cq + i];
   }
+  const float scale = S.scale(red, tid);
+  S.template write_grad_image<kPhiRelu>(sG, scale);
+  return scale;
 }
+
+// The two images of dS and dzc in sZ[D]; returns the scale.  red: NTHREADS/64 floats of LDS.
+template <int D, int NTHREADS>
+__device__ __forceinline__ float build_relu_key_state(const float* __restrict__ dstate, uint4* sC, uint4* sG, float* sZ, float* red,
+                                                      const float* __restrict__ mean, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(dstate, tid);
+  const float4 cm = *reinterpret_cast<const float4*>(mean + 4 * S.cq);
+  const float scale = S.scale(red, tid);
+  S.template write_grad_image<kPhiRelu>(sG, scale);
+  S.template write_apply_image<ApplyLayout<D>::MB, kPhiRelu>(sC, scale);
+  const float inv = __builtin_amdgcn_rcpf(scale);           // exact: a power of two
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    auto img = [&](int i) { return (float)(_Float16)(scale * S.v[e][i]); };
+    float dot = fmaf(img(3), cm.w, fmaf(img(2), cm.z, fmaf(img(1), cm.y, img(0) * cm.x)));
+    for (int k = R::CQ / 2; k >= 1; k >>= 1) dot += __shfl_xor(dot, k, 64);
+    const int f = 8 * S.fo + e;
+    if (S.active && S.cq == 0) sZ[f] = dstate[D * D + f] - dot * inv;
+  }
+  return scale;
+}
+
+// G^T = M X^T for the 32 tokens of a wavefront: x(ks) is the lane's piece of its token's row (fp16, channels 16ks + 8g ..) and img an
+// image of write_grad_image<kPhiRelu>; register 8*(ks%2) + e of ga[ks/2] is then feature 16ks + 8g + e of the lane's token, the element e
+// of piece ks.
+template <int D, int AHEAD, typename Piece>
+__device__ __forceinline__ void relu_grad(const uint4* img, int lane, Piece x, f32x16 (&ga)[D / 32]) {
+  constexpr int MB = D / 32;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
+  const uint4* a = img + lane + opaque_zero();
+  uint4 b;
+  pipelined_operands<(D / 16) * MB, AHEAD>(
+      [&](int i) { return a[i * 64]; },
+      [&](int i, uint4 op) {
+        if (i % MB == 0) b = x(i / MB);
+        ga[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(op), as_f16x8(b), ga[i % MB], 0, 0, 0);
+      });
+}
+
+// A lane's row pieces (bf16, channels 16ks + 8g .. of its token) -> 32 rows of base, a wavefront's tokens t0 ..: through `buf`
+// ([32][D] bf16 of LDS, the wavefront's own), so that an instruction stores 1 KB of whole rows.  Stored as the lanes hold them,
+// 32 bytes of a row at a time, the query side took 95 us and the key side 96 where they take 91 and 88 (12 heads x
+// 32760 x 128).  Rows past n hold the bits of row n - 1 and go there.
+template <int D>
+struct RowStore {
+  static constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks of a row, rows per store
+  char* buf;
+  int lane;
+  __device__ __forceinline__ void put(int ks, uint4 x) const {
+    const int row = lane % 32;
+    *reinterpret_cast<uint4*>(buf + row * D * 2 + (((2 * ks + lane / 32) ^ swz<D>(row)) * 16)) = x;
+  }
+  __device__ __forceinline__ void flush(uint16_t* base, size_t sn, int t0, int n) const {
+    __builtin_amdgcn_wave_barrier();
+    const int c = lane % CH;
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int row = i * RPI + lane / CH, t = t0 + row;
+      const uint4 x = *reinterpret_cast<const uint4*>(buf + row * D * 2 + ((c ^ swz<D>(row)) * 16));
+      *reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c) = x;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+};
 
 // ---- query side of the backward -------------------------------------------------------------------
-// grid (P, BH), 4 wavefronts; wavefront w of a tile owns its tokens 32w .. 32w+31.  Per block:
-//   A operands straight from the loaded rows (a lane owns a token): phi(q) and ts * dO (ts: one power
-//   of two per block);  dn = phi(q) . (scale z) on the accumulator rows (one MFMA column block of z),
-//   ga = ts * scale * dO S^T with the tokens on the rows and the features on the lanes; q once more in
-//   that layout for the mask and for delta = sum_f G_f phi_f / den (a sum over the 32 lanes); dq rows
-//   are stored from the accumulators.  Then phi(q) and gamma * dO / den go to LDS as fp16 and the
-//   four wavefronts contract them over the tile's tokens into dS (dz: one more MFMA per k-step).
+// grid (P, BH), 8 wavefronts, one workgroup per compute unit.  Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile, two
+// lanes a token: G = dO S^T with the tokens on the accumulator columns and the features in the order in which the lane holds
+// its token's channels, so den = phi . z and delta = phi . G / den are dots of registers, the mask of dq is the lane's own row and dq
+// leaves in the pieces in which q came.  They park phi(q) and gamma * dO / den as fp16 and form dq while wavefronts 4-7 ("acc") contract
+// the tile over its tokens into dS (dz: one more MFMA per k-step).  The kernel is bound by its instruction stream (its rows take 51 us
+// at the memory's rate): with four wavefronts that did all of this one after another, read q a second time for the mask and summed delta
+// across lanes it took 119 us at 12 heads x 32760 x 128, 91 now.
+constexpr int NTQ = 512;
 template <int D>
-__global__ __launch_bounds__(NT) void relu_bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
-                                                        const float* __restrict__ state, const uint4* __restrict__ cimg,
-                                                        const uint4* __restrict__ timg, const float* __restrict__ scale_ptr,
-                                                        uint16_t* __restrict__ dq, float* __restrict__ partials,
-                                                        int H, int n, int P, Rows rw) {
+__global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
+                                                         const float* __restrict__ state, float* __restrict__ mean_row,
+                                                         uint16_t* __restrict__ dq, float* __restrict__ partials,
+                                                         int H, int n, int P, Rows rw) {
   using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  using Piece = typename RowPieceT<L::MB>::type;
+  using G = GradLayout<D>;
   constexpr int RS = D * 2;
   constexpr int WMN = D / 64;
-  constexpr int CIMG = L::KS * L::MBZ * 64, TIMG = L::KS * L::MB * 64;
   extern __shared__ uint4 smem[];
-  uint4* sZB = smem;                                       // [KS][64] the z column block of cimg
-  uint4* sT = sZB + L::KS * 64;                            // [KS][MB][64] timg
-  char* sPhi = reinterpret_cast<char*>(sT + TIMG);         // [kTile][D] fp16: phi(q)
+  uint4* sG = smem;                                        // [KS][GM][64] image of S^c
+  char* sPhi = reinterpret_cast<char*>(sG + G::IMG);       // [kTile][D] fp16: phi(q)
   char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: gamma * dO / den
   uint16_t* sW16 = reinterpret_cast<uint16_t*>(sDO + kTile * RS);   // [kTile] fp16: -gamma * delta / den
-  float* sRow = reinterpret_cast<float*>(sW16 + kTile);    // [4 wavefronts][2][32] per-token scalars
-  float* sRed = sRow + 4 * 64;                             // [8]
+  float* sZ = reinterpret_cast<float*>(sW16 + kTile);      // [D] z, unscaled
+  float* sRed = sZ + D;                                    // [4] the tile's operand maxima
+  char* sOut = reinterpret_cast<char*>(sRed + 4);          // [4][32][D] bf16: RowStore
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32, c = lane % 32;
-  const int mi = w / 2, ni = w % 2;
+  const int role = w / 4, pw = w % 4;
+  const int g = lane / 32;
   const int bh = blockIdx.y, p = blockIdx.x;
-  const uint16_t* qb = q + head_base(rw, bh, H);
-  const uint16_t* dob = dout + head_base(rw, bh, H);
-  uint16_t* dqb = dq + head_base(rw, bh, H);
-  const float* sb = state + (size_t)bh * (D + 1) * D;
   const int ntile = (n + kTile - 1) / kTile;
 
-  for (int i = tid; i < L::KS * 64; i += NT)
-    sZB[i] = cimg[(size_t)bh * CIMG + ((i / 64) * L::MBZ + L::MB) * 64 + (i % 64)];
-  copy_image<NT>(timg + (size_t)bh * TIMG, sT, TIMG, tid);
-  const float scale = scale_ptr[2 * bh];
-  float zl[L::MB];                                         // z of the lane's features
-#pragma unroll
-  for (int mb = 0; mb < L::MB; ++mb) zl[mb] = sb[D * D + L::channel_cols(mb, c)];
+  const float scale = build_relu_query_state<D, NTQ>(state + (size_t)bh * (D + 1) * D, sG, sZ, reinterpret_cast<float*>(sPhi),
+                                                     p == 0 ? mean_row + (size_t)bh * D : nullptr, tid);
   __syncthreads();
 
-  f32x16 s[WMN][WMN], zacc;
+  // running power-of-two scale of the sums over tokens (see gamma_for), the same in every wavefront; returns the factor for the
+  // accumulators
+  float gamma = kGammaUnset;
+  auto next_gamma = [&]() -> float {
+    const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
+    float gnext = gamma;
+    const float ratio = gamma_step(gnext, gamma_for(m));
+    gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
+  };
+
+  if (role == 0) {
+    const uint16_t* qb = q + head_base(rw, bh, H);
+    const uint16_t* dob = dout + head_base(rw, bh, H);
+    uint16_t* dqb = dq + head_base(rw, bh, H);
+    const int prow = 32 * pw + (lane % 32);
+    // Rows past n read as row n - 1, and their lanes store its dq once more: the same bits.
+    auto row_at = [&](int tile) {
+      const int t = tile * kTile + prow;
+      return (size_t)(t < n ? t : n - 1) * rw.sn;
+    };
+    uint4 xq[C::UK], dor[C::UK], xn[C::UK];
+    auto load = [&](const uint16_t* base, int tile, uint4 (&x)[C::UK]) {
+      const uint4* row = reinterpret_cast<const uint4*>(base + row_at(tile));
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    zacc[r] = 0.f;
+      for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
+    };
+    load(qb, p < ntile ? p : 0, xn);
+    load(dob, p < ntile ? p : 0, dor);
+    // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
+    // for the first tile too, would be a wait for the previous tile's stores
+#pragma unroll
+    for (int ks = 0; ks < C::UK; ++ks) {
+      asm volatile("" : "+v"(xn[ks].x), "+v"(xn[ks].y), "+v"(xn[ks].z), "+v"(xn[ks].w));
+      asm volatile("" : "+v"(dor[ks].x), "+v"(dor[ks].y), "+v"(dor[ks].z), "+v"(dor[ks].w));
+    }
+    for (int tile = p; tile < ntile; tile += P) {
+      const bool valid = tile * kTile + prow < n;
+      // phi(q); whether it has any feature above zero; the token's largest |dO| (magnitudes of bf16 compare as integers)
+      uint32_t any = 0;
+      typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+      u16x2 m2 = {0, 0};
+      auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) {
+        xq[ks] = make_uint4(relu_bf16x2(xn[ks].x), relu_bf16x2(xn[ks].y), relu_bf16x2(xn[ks].z), relu_bf16x2(xn[ks].w));
+        any |= (xq[ks].x | xq[ks].y) | (xq[ks].z | xq[ks].w);
+        take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w);
+      }
+      float lo, hi;
+      float dmax = __builtin_bit_cast(float, (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16);
+      pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
+      const float stok = pow2_normaliser(dmax);
+      // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
+      // common scale gamma and push every other token's operand into the fp16 subnormals
+      auto any2 = __builtin_amdgcn_permlane32_swap(any, any, false, false);
+      const bool live = valid && ((uint32_t)any2[0] | (uint32_t)any2[1]) != 0;
+
+      // G (times scale * stok)
+      f32x16 ga[G::GM];
+      relu_grad<D, 4>(sG, lane, [&](int ks) {
+        float f[8];
+        unpack_bf16x8(dor[ks], f);
+        return make_uint4(pack_f16x2(f[0] * stok, f[1] * stok), pack_f16x2(f[2] * stok, f[3] * stok),
+                          pack_f16x2(f[4] * stok, f[5] * stok), pack_f16x2(f[6] * stok, f[7] * stok));
+      }, ga);
+      // the rows stay packed until their next use: seen as the same values, their unpacked form would be kept (and spilled)
+      auto repack = [&](uint4 (&x)[C::UK]) {
+#pragma unroll
+        for (int ks = 0; ks < C::UK; ++ks) asm volatile("" : "+v"(x[ks].x), "+v"(x[ks].y), "+v"(x[ks].z), "+v"(x[ks].w));
+      };
+      repack(dor);
+      const int z_at = 2 * g + opaque_zero();
+      auto z8 = [&](int ks, float (&z)[8]) {
+        const float4 a = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks], b = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks + 1];
+        z[0] = a.x; z[1] = a.y; z[2] = a.z; z[3] = a.w; z[4] = b.x; z[5] = b.y; z[6] = b.z; z[7] = b.w;
+      };
+      float A[2] = {0.f, 0.f}, Z[2] = {0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) {
+        float f[8], z[8];
+        unpack_bf16x8(xq[ks], f);
+        z8(ks, z);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          A[e % 2] = fmaf(ga[ks / 2][8 * (ks % 2) + e], f[e], A[e % 2]);
+          Z[e % 2] = fmaf(z[e], f[e], Z[e % 2]);
+        }
+      }
+      repack(xq);
+      pair32(A[0] + A[1], lo, hi); const float a_sum = lo + hi;
+      pair32(Z[0] + Z[1], lo, hi);
+      const float inv_den = __builtin_amdgcn_rcpf((lo + hi) + kReluEps);
+      // 1 / (scale * stok * den); scale and stok are powers of two
+      const float r1 = (inv_den * __builtin_amdgcn_rcpf(scale)) * __builtin_amdgcn_rcpf(stok);
+      const float delta = a_sum * r1;
+      {
+        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
+        float m = live ? fmaxf(dmax, fabsf(delta)) * inv_den : 0.f;
+        m = wave_max_paired(m);
+        if (lane == 0) sRed[pw] = m;
+      }
+      __syncthreads();                                   // the previous tile has been read
+      next_gamma();
+      {
+        const int lz = lane + opaque_zero();
+        const int row = 32 * pw + lz % 32, psw = swz<D>(row), gz = lz / 32;
+        char* rowp = sPhi + row * RS;
+        char* drowp = sDO + row * RS;
+        const float sc = live ? inv_den * gamma : 0.f;
+#pragma unroll
+        for (int ks = 0; ks < C::UK; ++ks) {
+          uint4 a = make_uint4(bf16x2_to_f16x2(xq[ks].x), bf16x2_to_f16x2(xq[ks].y), bf16x2_to_f16x2(xq[ks].z), bf16x2_to_f16x2(xq[ks].w));
+          if (!live) a = make_uint4(0, 0, 0, 0);
+          *reinterpret_cast<uint4*>(rowp + (((2 * ks + gz) ^ psw) * 16)) = a;
+          float f[8];
+          unpack_bf16x8(dor[ks], f);
+          *reinterpret_cast<uint4*>(drowp + (((2 * ks + gz) ^ psw) * 16)) =
+              make_uint4(pack_f16x2(f[0] * sc, f[1] * sc), pack_f16x2(f[2] * sc, f[3] * sc),
+                         pack_f16x2(f[4] * sc, f[5] * sc), pack_f16x2(f[6] * sc, f[7] * sc));
+        }
+        if (g == 0) sW16[row] = (uint16_t)(pack_f16x2(live ? -delta * sc : 0.f, 0.f) & 0xffffu);
+      }
+      repack(xq);
+      // the next tile's rows, before the dq stores: loads and stores retire in order
+      const int next = tile + P < ntile ? tile + P : tile;
+      load(qb, next, xn);
+      load(dob, next, dor);
+      __syncthreads();
+      // dq = (G - delta z) / den where q > 0
+      const float r2 = inv_den * delta;
+      const RowStore<D> out{sOut + pw * 32 * RS, lane + opaque_zero()};
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) {
+        float f[8], z[8], v[8];
+        unpack_bf16x8(xq[ks], f);
+        z8(ks, z);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], r1, -(r2 * z[e])) : 0.f;
+        out.put(ks, make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])));
+      }
+      out.flush(dqb, rw.sn, tile * kTile + 32 * pw, n);
+    }
+  } else {
+    f32x16 s[WMN][WMN], zacc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      zacc[r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < WMN; ++i)
+#pragma unroll
+        for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
+    }
+    const int mi = pw / 2, ni = pw % 2;
+    const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
+    const bool do_z = (WMN == 2) || (ni == 0);
+    int offA[WMN][2], offB[WMN][2];
 #pragma unroll
     for (int i = 0; i < WMN; ++i)
 #pragma unroll
-      for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
-  }
-  const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
-  const bool do_z = (WMN == 2) || (ni == 0);
-  int offA[WMN][2], offB[WMN][2];
-#pragma unroll
-  for (int i = 0; i < WMN; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
-      offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
-    }
-  const int prow = 32 * w + (lane % 32);
-  const int psw = swz<D>(prow);
-  float* myRow = sRow + w * 64;
-  float gamma = kGammaUnset;
-
-  // The rows of a tile are requested inside the tile before it, each set as soon as its registers are free (the
-  // accumulator-layout q rows before the dq stores, the operand-layout q and dO rows behind the parking of phi
-  // and dO): with one wavefront per SIMD nothing else hides the latency of a load at the top of a tile.  Never
-  // behind a branch: after the last tile its rows are simply read again.
-  uint4 xq[C::UK], dor[C::UK];
-  Piece qrow[16];
-  auto load_operand_rows = [&](int tile) {
-    const int t = tile * kTile + prow;
-    const int tc = t < n ? t : (n - 1);
-    const uint4* row = reinterpret_cast<const uint4*>(qb + (size_t)tc * rw.sn);
-    const uint4* drow = reinterpret_cast<const uint4*>(dob + (size_t)tc * rw.sn);
-#pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) { xq[ks] = row[2 * ks + g]; dor[ks] = drow[2 * ks + g]; }
-  };
-  load_operand_rows(p < ntile ? p : 0);
-  load_row_pieces<D>(qb, rw.sn, (p < ntile ? p : 0) * kTile + 32 * w, n, lane, qrow);
-  for (int tile = p; tile < ntile; tile += P) {
-    const int t0 = tile * kTile + 32 * w;
-    const int t = tile * kTile + prow;
-    const bool valid = t < n;
-    const int next = tile + P < ntile ? tile + P : tile;
-
-    // block scale of dO
-    float dmax = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) {
-      float f[8];
-      unpack_bf16x8(dor[ks], f);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dmax = fmaxf(dmax, fabsf(f[e]));
-    }
-    if (!valid) dmax = 0.f;
-    float lo, hi;
-    pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);              // the token's largest |dO|
-    const float ts = pow2_normaliser(wave_max_paired(dmax));
-
-    // den and G on the accumulator rows
-    f32x16 ga[L::MB], dn;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      dn[r] = 0.f;
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb) ga[mb][r] = 0.f;
-    }
-    const uint4* szb = sZB + lane + opaque_zero();
-    const uint4* st = sT + lane + opaque_zero();
-    pipelined_operands<L::KS, 3>(
-        [&](int ks) { return szb[ks * 64]; },
-        [&](int ks, uint4 b) {
-          dn = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(relu_f16x8(xq[ks])), as_f16x8(b), dn, 0, 0, 0);
-        });
-    pipelined_operands<L::KS * L::MB, 3>(
-        [&](int i) { return st[i * 64]; },
-        [&](int i, uint4 b) {
-          const int ks = i / L::MB, mb = i % L::MB;
-          float f[8];
-          unpack_bf16x8(dor[ks], f);
-          uint4 aq;
-          aq.x = pack_f16x2(f[0] * ts, f[1] * ts); aq.y = pack_f16x2(f[2] * ts, f[3] * ts);
-          aq.z = pack_f16x2(f[4] * ts, f[5] * ts); aq.w = pack_f16x2(f[6] * ts, f[7] * ts);
-          ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(aq), as_f16x8(b), ga[mb], 0, 0, 0);
-        });
-    // per row: a = 1 / (scale * den), delta = (sum_f G_f phi_f) / den; dq = (G - delta z) / den where q > 0
-    const float its = __builtin_amdgcn_rcpf(ts);                // exact: a power of two
-    const float den_eps = scale * kReluEps;
-    float arow[16], drow_[16];
-    f32x16 dqa[L::MB];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float part = 0.f;
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb) part = fmaf(ga[mb][r], fmaxf(piece_elem(qrow[r], mb), 0.f), part);
-      const float sum = half_wave_sum(part);                    // ts * scale * dO . (phi S)
-      const float a = __builtin_amdgcn_rcpf(dn[r] + den_eps);   // 1 / (scale * den)
-      const float delta = sum * a * its;
-      arow[r] = a;
-      drow_[r] = delta;
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb) {
-        const float val = ga[mb][r] * (a * its) - delta * (scale * a) * zl[mb];
-        dqa[mb][r] = piece_elem(qrow[r], mb) > 0.f ? val : 0.f;
+      for (int j = 0; j < 2; ++j) {
+        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
+        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
       }
-    }
-    load_row_pieces<D>(qb, rw.sn, next * kTile + 32 * w, n, lane, qrow);
-    store_token_rows<D>(dqb, rw.sn, t0, n, lane, dqa, 1.f);
-
-    // the per-token scalars back onto the lanes that own the tokens
-    if (c == 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r / 4) + 4 * g + (r % 4);
-        myRow[row] = arow[r];
-        myRow[32 + row] = drow_[r];
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    const float a_t = myRow[lane % 32];
-    const float delta_t = myRow[32 + (lane % 32)];
-    __builtin_amdgcn_wave_barrier();
-    const float inv_den = scale * a_t;                          // 1 / den
-    // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
-    // common scale gamma and push every other token's operand into the fp16 subnormals
-    bool live;
-    {
-      uint32_t any = 0;
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
-        const uint4 f = relu_f16x8(xq[ks]);
-        any |= f.x | f.y | f.z | f.w;
-      }
-      auto r2 = __builtin_amdgcn_permlane32_swap(any, any, false, false);
-      live = valid && (((uint32_t)r2[0] | (uint32_t)r2[1]) != 0);
-    }
-
-    // operands of the sums over tokens
-    {
-      float m = live ? fmaxf(dmax, fabsf(delta_t)) * inv_den : 0.f;
-      m = wave_max_paired(m);
-      if (lane == 0) sRed[w] = m;
-    }
-    __syncthreads();                             // previous tile's operand reads are done
-    {
-      // running power-of-two scale of the two sums over tokens (see gamma_for)
-      const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
-      const float ratio = gamma_step(gamma, gamma_for(m));
-      if (ratio != 1.f) {
+    for (int tile = p; tile < ntile; tile += P) {
+      __syncthreads();
+      const float ratio = next_gamma();
+      if (ratio != 1.f) {                                // this tile is larger than every earlier one
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           zacc[r] *= ratio;
@@ -477,98 +506,75 @@ __global__ __launch_bounds__(NT) void relu_bwd_q_kernel(const uint16_t* __restri
             for (int j = 0; j < WMN; ++j) s[i][j][r] *= ratio;
         }
       }
+      __syncthreads();
+      contract_tile<D>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
+                       [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); });
     }
-    {
-      char* rowp = sPhi + prow * RS;
-      char* drowp = sDO + prow * RS;
-      const float sc = live ? inv_den * gamma : 0.f;
+    const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
+    float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
+    const int c = lane % 32;
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
-        uint4 a = relu_f16x8(xq[ks]);
-        if (!live) a = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4*>(rowp + (((2 * ks + g) ^ psw) * 16)) = a;
-        float f[8];
-        unpack_bf16x8(dor[ks], f);
-        uint4 b;
-        b.x = pack_f16x2(f[0] * sc, f[1] * sc); b.y = pack_f16x2(f[2] * sc, f[3] * sc);
-        b.z = pack_f16x2(f[4] * sc, f[5] * sc); b.w = pack_f16x2(f[6] * sc, f[7] * sc);
-        *reinterpret_cast<uint4*>(drowp + (((2 * ks + g) ^ psw) * 16)) = b;
-      }
-      if (g == 0) sW16[prow] = (uint16_t)(pack_f16x2(live ? -delta_t * sc : 0.f, 0.f) & 0xffffu);
+    for (int i = 0; i < WMN; ++i)
+#pragma unroll
+      for (int j = 0; j < WMN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
+          dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
+        }
+    if (do_z && c == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
     }
-    load_operand_rows(next);
-    __syncthreads();
-    contract_tile<D>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
-                     [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); });
-  }
-
-  const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
-  float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
-#pragma unroll
-  for (int i = 0; i < WMN; ++i)
-#pragma unroll
-    for (int j = 0; j < WMN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
-        dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
-      }
-  if (do_z && c == 0) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
   }
 }
 
 // ---- key side of the backward ---------------------------------------------------------------------
-// grid (KP, BH), 8 wavefronts, each on its own 32-token blocks.  Both products have the tokens on
-// the accumulator rows: dv = phi(k) dS (B operands: cimg of dS) and g = v dS^T + dz (timg of dS);
-// dk = g where k > 0, with k read once more in the accumulator layout for the mask.
+// grid (KP, BH), 8 wavefronts, each on its own 32-token blocks: dv = phi(k) dS with the tokens on the accumulator rows, and
+// g = v dS^T + dz with the tokens on the columns (relu_grad), dk = g where k > 0 in the pieces in which k came.  88 us at 12 heads x 32760 x
+// 128 (81 + 9 for the images in a kernel of their own, with k read twice); the rows take 69 us at the memory's rate.  The next block's
+// rows requested a block ahead: 93 us.
 constexpr int NTK = 512;
 template <int D>
 __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                                                         const float* __restrict__ dstate, const uint4* __restrict__ cimg,
-                                                         const uint4* __restrict__ timg, const float* __restrict__ scale_ptr,
+                                                         const float* __restrict__ dstate, const float* __restrict__ mean_row,
                                                          uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
-                                                         const float* __restrict__ dzc, int H, int n, Rows rw) {
+                                                         int H, int n, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
-  using Piece = typename RowPieceT<L::MB>::type;
+  using G = GradLayout<D>;
   constexpr int NW = NTK / 64;
-  constexpr int CIMG = L::KS * L::MBZ * 64, TIMG = L::KS * L::MB * 64;
   extern __shared__ uint4 smem[];
-  uint4* sC = smem;
-  uint4* sT = sC + CIMG;
+  uint4* sC = smem;                                        // [KS][MB][64] image of dS for dv
+  uint4* sG = sC + L::KS * L::MB * 64;                     // image of dS for g
+  float* sZ = reinterpret_cast<float*>(sG + G::IMG);       // [D] dzc
+  float* sRed = sZ + D;                                    // [NW]
+  char* sOut = reinterpret_cast<char*>(sRed + NW);         // [NW][32][D] bf16: RowStore
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32, c = lane % 32;
+  const int g = lane / 32;
   const int bh = blockIdx.y;
   const uint16_t* kb = k + head_base(rw, bh, H);
   const uint16_t* vb = v + head_base(rw, bh, H);
   uint16_t* dkb = dk + head_base(rw, bh, H);
   uint16_t* dvb = dv + head_base(rw, bh, H);
-  copy_image<NTK>(cimg + (size_t)bh * CIMG, sC, CIMG, tid);
-  copy_image<NTK>(timg + (size_t)bh * TIMG, sT, TIMG, tid);
-  const float inv_scale = __builtin_amdgcn_rcpf(scale_ptr[2 * bh]);    // exact: power of two
-  float dzl[L::MB];
-#pragma unroll
-  for (int mb = 0; mb < L::MB; ++mb) dzl[mb] = dzc[(size_t)bh * D + L::channel_cols(mb, c)];   // dz matched to the image (relu_prep_kernel)
+  const float scale = build_relu_key_state<D, NTK>(dstate + (size_t)bh * (D + 1) * D, sC, sG, sZ, sRed, mean_row + (size_t)bh * D, tid);
+  const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
   __syncthreads();
 
   const int nblk = (n + 31) / 32;
   const int stride = gridDim.x * NW;
   for (int b = blockIdx.x * NW + w; b < nblk; b += stride) {
     const int t = b * 32 + (lane % 32);
-    const int tc = t < n ? t : (n - 1);
+    const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;   // rows past n: row n - 1 once more, the same bits
     uint4 xk[C::UK], xv[C::UK];
     {
-      const uint4* row = reinterpret_cast<const uint4*>(kb + (size_t)tc * rw.sn);
-      const uint4* vrow = reinterpret_cast<const uint4*>(vb + (size_t)tc * rw.sn);
+      const uint4* row = reinterpret_cast<const uint4*>(kb + at);
+      const uint4* vrow = reinterpret_cast<const uint4*>(vb + at);
 #pragma unroll
       for (int ks = 0; ks < C::UK; ++ks) { xk[ks] = row[2 * ks + g]; xv[ks] = vrow[2 * ks + g]; }
     }
-    Piece krow[16];
-    load_row_pieces<D>(kb, rw.sn, b * 32, n, lane, krow);
     {
       f32x16 va[L::MB];
 #pragma unroll
@@ -581,33 +587,28 @@ __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restr
         const f16x8 aop = as_f16x8(relu_f16x8(xk[ks]));
 #pragma unroll
         for (int mb = 0; mb < L::MB; ++mb)
-          va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(sc[(ks * L::MBZ + mb) * 64]), va[mb], 0, 0, 0);
+          va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(sc[(ks * L::MB + mb) * 64]), va[mb], 0, 0, 0);
       }
       store_token_rows<D>(dvb, rw.sn, b * 32, n, lane, va, inv_scale);
     }
     {
-      f32x16 ga[L::MB];
+      f32x16 ga[G::GM];
+      relu_grad<D, 0>(sG, lane, [&](int ks) {
+        return make_uint4(bf16x2_to_f16x2(xv[ks].x), bf16x2_to_f16x2(xv[ks].y), bf16x2_to_f16x2(xv[ks].z), bf16x2_to_f16x2(xv[ks].w));
+      }, ga);
+      const RowStore<D> out{sOut + w * 32 * D * 2, lane + opaque_zero()};
+      const int z_at = 2 * g + opaque_zero();
 #pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
+      for (int ks = 0; ks < C::UK; ++ks) {
+        const float4 za = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks], zb = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks + 1];
+        const float z[8] = {za.x, za.y, za.z, za.w, zb.x, zb.y, zb.z, zb.w};
+        float f[8], u[8];
+        unpack_bf16x8(xk[ks], f);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
-      const uint4* st = sT + lane + opaque_zero();
-#pragma unroll
-      for (int ks = 0; ks < L::KS; ++ks) {
-        uint4 aq;
-        aq.x = bf16x2_to_f16x2(xv[ks].x); aq.y = bf16x2_to_f16x2(xv[ks].y);
-        aq.z = bf16x2_to_f16x2(xv[ks].z); aq.w = bf16x2_to_f16x2(xv[ks].w);
-        const f16x8 aop = as_f16x8(aq);
-#pragma unroll
-        for (int mb = 0; mb < L::MB; ++mb)
-          ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(st[(ks * L::MB + mb) * 64]), ga[mb], 0, 0, 0);
+        for (int e = 0; e < 8; ++e) u[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], inv_scale, z[e]) : 0.f;
+        out.put(ks, make_uint4(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]), pack_bf16x2(u[6], u[7])));
       }
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          ga[mb][r] = piece_elem(krow[r], mb) > 0.f ? fmaf(ga[mb][r], inv_scale, dzl[mb]) : 0.f;
-      store_token_rows<D>(dkb, rw.sn, b * 32, n, lane, ga, 1.f);
+      out.flush(dkb, rw.sn, b * 32, n);
     }
   }
 }
@@ -615,15 +616,13 @@ __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restr
 template <int D>
 constexpr size_t state_smem() { return 2 * (size_t)kTile * D * 2; }
 template <int D>
-constexpr size_t prep_smem() { return (size_t)(D + 1) * D * sizeof(float); }
-template <int D>
 constexpr size_t q_smem() {
-  return sizeof(uint4) * (ApplyLayout<D>::KS * 64 + ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64)
-       + 2 * (size_t)kTile * D * 2 + kTile * 2 + (4 * 64 + 8) * sizeof(float);
+  return sizeof(uint4) * GradLayout<D>::IMG + 3 * (size_t)kTile * D * 2 + kTile * 2 + (D + 4) * sizeof(float);
 }
 template <int D>
 constexpr size_t k_smem() {
-  return sizeof(uint4) * (ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64 + ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64);
+  return sizeof(uint4) * (ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64 + GradLayout<D>::IMG) + (D + NTK / 64) * sizeof(float)
+       + (NTK / 64) * 32 * (size_t)D * 2;
 }
 
 template <int D>
@@ -638,22 +637,14 @@ hipError_t run_state(const void* k, const void* v, float* partials, const Plan& 
 template <int D>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  if ((e = set_smem_once<relu_prep_kernel<D, false>>(prep_smem<D>())) != hipSuccess) return e;
-  if ((e = set_smem_once<relu_prep_kernel<D, true>>(prep_smem<D>())) != hipSuccess) return e;
-  relu_prep_kernel<D, false><<<dim3(p.BH, 8), PT, prep_smem<D>(), s>>>(a.state, (uint4*)a.simg, (uint4*)a.gimg, a.scales, a.vbar, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = set_smem_once<relu_bwd_q_kernel<D>>(q_smem<D>())) != hipSuccess) return e;
-  relu_bwd_q_kernel<D><<<dim3(p.P, p.BH), NT, q_smem<D>(), s>>>(
-      (const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, (const uint4*)a.simg, (const uint4*)a.gimg, a.scales,
-      (uint16_t*)a.dq, a.partials, p.H, p.n, p.P, p.rows);
+  relu_bwd_q_kernel<D><<<dim3(p.P, p.BH), NTQ, q_smem<D>(), s>>>((const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, a.vbar,
+                                                                (uint16_t*)a.dq, a.partials, p.H, p.n, p.P, p.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, s)) != hipSuccess) return e;
-  relu_prep_kernel<D, true><<<dim3(p.BH, 8), PT, prep_smem<D>(), s>>>(a.dstate, (uint4*)a.dsimg, (uint4*)a.dgimg, a.scales + 1, a.vbar, a.dzc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = set_smem_once<relu_bwd_k_kernel<D>>(k_smem<D>())) != hipSuccess) return e;
-  relu_bwd_k_kernel<D><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>(
-      (const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, (const uint4*)a.dsimg, (const uint4*)a.dgimg, a.scales + 1,
-      (uint16_t*)a.dk, (uint16_t*)a.dv, a.dzc, p.H, p.n, p.rows);
+  relu_bwd_k_kernel<D><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>((const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar,
+                                                                 (uint16_t*)a.dk, (uint16_t*)a.dv, p.H, p.n, p.rows);
   return hipGetLastError();
 }
 
