@@ -193,11 +193,13 @@ int run_fwd(const linattn_phi_desc& desc, const Plan& plan, const void* q, const
       : relu ? launch_relu_state_bf16(k, v, partials, plan, s) : launch_state_partials_bf16(k, v, desc.wk, partials, plan, s);
   if (e != hipSuccess) return LINATTN_E_HIP;
   ev.mark(1, s);
-  e = launch_state_reduce_split(partials, state, plan, s);
-  if (e != hipSuccess) return LINATTN_E_HIP;
+  if (f32_math || !sum_in_apply(plan)) {
+    e = launch_state_reduce_split(partials, state, plan, s);
+    if (e != hipSuccess) return LINATTN_E_HIP;
+  }
   ev.mark(2, s);
   e = f32_math ? launch_apply_f32(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s)
-               : launch_apply_bf16(q, desc.wq, state, out, desc.blend_in, desc.blend_r, plan, s);
+               : launch_apply_bf16(q, desc.wq, partials, state, out, desc.blend_in, desc.blend_r, plan, s);
   if (e != hipSuccess) return LINATTN_E_HIP;
   ev.mark(3, s);
   return LINATTN_OK;

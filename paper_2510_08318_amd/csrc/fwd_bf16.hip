@@ -42,6 +42,51 @@ __device__ __forceinline__ void st_nt(uint32_t* p, uint32_t v) { __builtin_nonte
 
 constexpr int NT3 = 768;         // 12 wavefronts, one workgroup per compute unit
 
+// The state of head bh as the sum of its workgroups' partials, pairwise, to sum[(D+1)*D/4] in LDS and, if given, to dst.  16 loads of
+// a thread are in flight; those of a missing slot repeat the last one's and count as zero (branch-free).
+template <int D> constexpr int kSumSlots = D == 64 ? 8 : 2;      // see sum_in_apply
+template <int N, int NTHREADS, int NS>
+__device__ __forceinline__ void sum_slots_of(const float4* __restrict__ src, int cnt, float4* sum, float4* __restrict__ dst, int tid) {
+  constexpr int EB = 16 / NS;
+  auto add = [](float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
+#pragma unroll 1
+  for (int e0 = tid; e0 < N; e0 += EB * NTHREADS) {
+    float4 t[EB][NS];
+#pragma unroll
+    for (int j = 0; j < EB; ++j) {
+      const int e = e0 + j * NTHREADS < N ? e0 + j * NTHREADS : N - 1;
+#pragma unroll
+      for (int p = 0; p < NS; ++p) t[j][p] = src[(size_t)(p < cnt ? p : cnt - 1) * N + e];
+    }
+#pragma unroll
+    for (int j = 0; j < EB; ++j) {
+#pragma unroll
+      for (int p = 1; p < NS; ++p)
+        if (p >= cnt) t[j][p] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int m = 1; m < NS; m *= 2)
+#pragma unroll
+        for (int p = 0; p < NS; p += 2 * m) t[j][p] = add(t[j][p], t[j][p + m]);
+      if (e0 + j * NTHREADS < N) {
+        sum[e0 + j * NTHREADS] = t[j][0];
+        if (dst != nullptr) dst[e0 + j * NTHREADS] = t[j][0];
+      }
+    }
+  }
+}
+template <int D, int NTHREADS>
+__device__ __forceinline__ void sum_slots(const float* __restrict__ partials, float4* sum, float4* __restrict__ dst, const Split& sp,
+                                          int bh, int tid) {
+  constexpr int N = (D + 1) * D / 4;
+  const int cnt = split_owner(sp, (long long)(bh + 1) * sp.ntile - 1) - split_owner(sp, (long long)bh * sp.ntile) + 1;
+  const float4* src = reinterpret_cast<const float4*>(partials) + (size_t)bh * sp.PS * N;
+  if constexpr (kSumSlots<D> > 2) {
+    if (cnt > 4) { sum_slots_of<N, NTHREADS, kSumSlots<D>>(src, cnt, sum, dst, tid); return; }
+    if (cnt > 2) { sum_slots_of<N, NTHREADS, 4>(src, cnt, sum, dst, tid); return; }
+  }
+  sum_slots_of<N, NTHREADS, 2>(src, cnt, sum, dst, tid);
+}
+
 // The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
 // us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 (the workgroup fills three of a
 // SIMD's wavefront slots whatever it is) keeps the loop's schedule from spreading into the prologue's registers: without it the
@@ -50,11 +95,14 @@ constexpr int NT3 = 768;         // 12 wavefronts, one workgroup per compute uni
 // s read in the same pieces as out is stored, and r' = clip(*rptr, 0, 1).
 // KIND = kPhiRelu: phi(q) = max(q, 0) straight from the loaded rows (no projection, no W~), features
 // in channel order, kReluEps in the denominator.
-template <int D, bool BLEND, int KIND>
-__global__ __launch_bounds__(NT3, D == 64 ? (BLEND ? 4 : 5) : 3) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
-                                                         const float* __restrict__ state, uint16_t* __restrict__ out,
+// SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
+// sum_in_apply); the first workgroup of a head writes it to `state`.
+template <int D, bool BLEND, int KIND, bool SUM>
+__global__ __launch_bounds__(NT3, D == 64 && !SUM ? (BLEND ? 4 : 5) : 3) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+                                                         const float* __restrict__ partials, float* __restrict__ state,
+                                                         uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
-                                                         int H, int n, Rows rw) {
+                                                         int H, int n, Split sp, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
   constexpr int NW = NT3 / 64;
@@ -95,11 +143,21 @@ __global__ __launch_bounds__(NT3, D == 64 ? (BLEND ? 4 : 5) : 3) void apply_bf16
   float scale;
   {
     using R = StateRegs<D, NT3>;
-    const float* sb = state + (size_t)bh * (D + 1) * D;
+    float* sb = state + (size_t)bh * (D + 1) * D;
     float* sZ = reinterpret_cast<float*>(sStage);
     R S;
-    S.load(sb, tid);
-    const float zv = tid < D ? sb[D * D + tid] : 0.f;
+    float zv;
+    if constexpr (SUM) {
+      float4* sSum = reinterpret_cast<float4*>(sZ + D + 64);
+      sum_slots<D, NT3>(partials, sSum, blockIdx.x == 0 ? reinterpret_cast<float4*>(sb) : nullptr, sp, bh, tid);
+      __syncthreads();
+      const float* sum = reinterpret_cast<const float*>(sSum);
+      S.load(sum, tid);
+      zv = tid < D ? sum[D * D + tid] : 0.f;
+    } else {
+      S.load(sb, tid);
+      zv = tid < D ? sb[D * D + tid] : 0.f;
+    }
     if (tid < D) sZ[tid] = zv;
     if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
     scale = S.scale(sZ + D, tid, fabsf(zv));            // (its barrier covers z as well)
@@ -522,9 +580,10 @@ template <int D>
 constexpr size_t state_ws_smem() { return sizeof(uint4) * Cfg<D>::W_IMG + 4 * (size_t)kTile * D * 2 + 4 * D * sizeof(float); }
 
 template <int D>
-constexpr size_t apply_smem() {
-  // the images, then z and a few reduction slots of the prologue
-  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64) + (D + 64) * sizeof(float);
+constexpr size_t apply_smem(bool sum) {
+  // the images, then z and a few reduction slots of the prologue, then (sum) the state
+  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MBZ * 64) + (D + 64) * sizeof(float)
+       + (sum ? (size_t)(D + 1) * D * sizeof(float) : 0);
 }
 
 }  // namespace
@@ -549,28 +608,41 @@ hipError_t launch_state_partials_bf16(const void* k, const void* v, const void* 
 
 namespace {
 
-template <int D, bool BLEND, int KIND>
-hipError_t run_apply(const void* q, const void* wq, const float* state, void* out, const void* blend_in,
+template <int D, bool BLEND, int KIND, bool SUM>
+hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   hipError_t e;
-  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND>>(apply_smem<D>())) != hipSuccess) return e;
-  apply_bf16_kernel<D, BLEND, KIND><<<dim3(p.QP, p.BH), NT3, apply_smem<D>(), s>>>(
-      (const uint16_t*)q, (const uint16_t*)wq, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, p.rows);
+  constexpr size_t smem = apply_smem<D>(SUM);
+  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM>>(smem)) != hipSuccess) return e;
+  apply_bf16_kernel<D, BLEND, KIND, SUM><<<dim3(p.QP, p.BH), NT3, smem, s>>>(
+      (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, p.split, p.rows);
   return hipGetLastError();
+}
+
+template <int D, bool SUM>
+hipError_t pick_apply(const void* q, const void* wq, const float* partials, float* state, void* out,
+                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
+  if (p.kind == kPhiRelu)      // the dispatch has refused a blend with this map
+    return run_apply<D, false, kPhiRelu, SUM>(q, nullptr, partials, state, out, nullptr, nullptr, p, s);
+  return blend_in ? run_apply<D, true, kPhiHedgehog, SUM>(q, wq, partials, state, out, blend_in, blend_r, p, s)
+                  : run_apply<D, false, kPhiHedgehog, SUM>(q, wq, partials, state, out, nullptr, nullptr, p, s);
 }
 
 }  // namespace
 
-hipError_t launch_apply_bf16(const void* q, const void* wq, const float* state, void* out,
+// Short calls, where a launch is a fifth of the time: the query pass sums the partials itself, up to eight tiles a head at width 64 and
+// two at 128 (at least as many as slots), where each of the at most three workgroups of a head reads them.  A call, reduction launched / summed
+// here, us: width 64, 4 heads x 1000 15.4 / 13.7, 128 x 1000 24.9 / 21.5, 1 x 100 15.0 / 12.9; width 128, 1 x 100 15.6 / 14.4,
+// 128 x 100 24.4 / 17.8; but 4 x 300 21.1 / 21.5 and 12 x 1000 24.7 / 28.7: a state of 66 KB takes a workgroup that long to sum.
+bool sum_in_apply(const Plan& p) { return p.split.ntile <= (p.d == 64 ? kSumSlots<64> : kSumSlots<128>); }
+
+hipError_t launch_apply_bf16(const void* q, const void* wq, const float* partials, float* state, void* out,
                              const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
-  if (p.kind == kPhiRelu)      // the dispatch has refused a blend with this map
-    return p.d == 128 ? run_apply<128, false, kPhiRelu>(q, nullptr, state, out, nullptr, nullptr, p, s)
-                      : run_apply<64, false, kPhiRelu>(q, nullptr, state, out, nullptr, nullptr, p, s);
-  if (p.d == 128)
-    return blend_in ? run_apply<128, true, kPhiHedgehog>(q, wq, state, out, blend_in, blend_r, p, s)
-                    : run_apply<128, false, kPhiHedgehog>(q, wq, state, out, nullptr, nullptr, p, s);
-  return blend_in ? run_apply<64, true, kPhiHedgehog>(q, wq, state, out, blend_in, blend_r, p, s)
-                  : run_apply<64, false, kPhiHedgehog>(q, wq, state, out, nullptr, nullptr, p, s);
+  if (sum_in_apply(p))
+    return p.d == 128 ? pick_apply<128, true>(q, wq, partials, state, out, blend_in, blend_r, p, s)
+                      : pick_apply<64, true>(q, wq, partials, state, out, blend_in, blend_r, p, s);
+  return p.d == 128 ? pick_apply<128, false>(q, wq, partials, state, out, blend_in, blend_r, p, s)
+                    : pick_apply<64, false>(q, wq, partials, state, out, blend_in, blend_r, p, s);
 }
 
 }  // namespace linattn

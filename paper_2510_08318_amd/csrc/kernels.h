@@ -157,7 +157,9 @@ hipError_t launch_state_reduce_split(const float* partials, float* state, const 
 // phi(Q) S / (phi(Q) . z) and the store of out (Eq. 3, right-hand side).
 hipError_t launch_apply_f32(const void* q, const void* wq, const float* state, void* out,
                             const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s);
-hipError_t launch_apply_bf16(const void* q, const void* wq, const float* state, void* out,
+// bf16: from the state, or (sum_in_apply) from the partials of the state pass, writing the state as well.
+bool sum_in_apply(const Plan& p);
+hipError_t launch_apply_bf16(const void* q, const void* wq, const float* partials, float* state, void* out,
                              const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s);
 
 // ---- backward launchers (enqueue only) --------------------------------------------------

@@ -1,0 +1,77 @@
+"""The bf16 kernels where a workgroup's share changes its form: several heads' worth of tiles to a workgroup in the backward, the
+lengths at which the query pass stops summing the partial states itself, and the numbers of partial states at which the
+reduction changes its threads per element.
+
+Bar: 1e-2 element by element for the bf16 tensors and weight gradients, the bar of the mode.  For the fp32 state, 2-norm: phi and W~
+enter its matrix products rounded to 2^-11 (fp16), or 2^-9 (bf16 rows, exact); independent roundings of n terms leave 2^-11 of the norm,
+and two of them (phi, and the softmax argument's products) stay below 2^-10."""
+import numpy as np
+import pytest
+
+from oracle import linattn_oracle as O
+from oracle import relu_oracle as R
+from paper_2510_08318_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(x, relu, wgrads, centred=False):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    q, k, v, do = [G.to_device(t) for t in (x.q, x.k, x.v, x.dout)]
+    if relu:
+        lay = G.ReluLayer(x.H, x.d, x.B, x.n, q.dtype)
+    else:
+        lay = G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n, want_wgrads=wgrads, centred=centred)
+    got = {"out": lay.forward(q, k, v), "state": lay.state}
+    got.update(zip(("dq", "dk", "dv"), lay.backward(q, k, v, do)))
+    if wgrads and not relu:
+        got.update(dwq=lay.dwq, dwk=lay.dwk)
+    torch.cuda.synchronize()
+    got = {name: G.to_host_f64(t) for name, t in got.items()}
+    lay.close()
+    return got
+
+
+def _check(x, relu=False, wgrads=True, centred=False):
+    got = _run(x, relu, wgrads, centred)
+    if relu:
+        ref = {"out": R.relu_fwd_bh(x.q, x.k, x.v)}
+        ref.update(zip(("dq", "dk", "dv"), R.relu_bwd_bh(x.q, x.k, x.v, x.dout)))
+    else:
+        ref = {"out": O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk), "state": O.state_bh(x.k, x.v, x.wk)}
+        ref.update(zip(("dq", "dk", "dv", "dwq", "dwk"), O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)))
+    for name, r in ref.items():
+        if name not in got:
+            continue
+        if name == "state":
+            assert np.linalg.norm(got[name] - r) <= 2.0 ** -10 * np.linalg.norm(r), name
+        else:
+            assert O.err_metric(got[name], r)[0] <= 1e-2, name
+
+
+@pytest.mark.parametrize("mode", ["weight gradients", "frozen map", "centred", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_workgroups_of_several_tiles(d, mode):
+    # 300 heads: one workgroup a head, four tiles (the last ragged) each
+    _check(synth.generate("C5", n=400, H=100, B=3, d=d, dtype="bf16"), relu=mode == "relu",
+           wgrads=mode != "frozen map", centred=mode == "centred")
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+@pytest.mark.parametrize("n,H,d", [(1, 1, 64), (129, 2, 64), (300, 3, 64), (640, 2, 64), (1024, 5, 64), (1025, 5, 64), (1000, 100, 64),
+                                   (128, 3, 128), (256, 3, 128), (257, 3, 128), (200, 300, 128)])
+def test_query_pass_that_sums_the_partials(n, H, d, relu):
+    if n == 1:        # one token: the state is phi(k)^T v and the gradients of q and k vanish
+        x = synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16")
+        got = _run(x, relu, False)
+        if not relu:
+            assert np.linalg.norm(got["state"] - O.state_bh(x.k, x.v, x.wk)) <= 2.0 ** -10 * np.linalg.norm(O.state_bh(x.k, x.v, x.wk))
+            assert O.err_metric(got["out"], O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk))[0] <= 1e-2
+        return
+    _check(synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16"), relu=relu)
+
+
+@pytest.mark.parametrize("n,H", [(129 * 8, 1), (129 * 9, 1), (128 * 32, 1), (128 * 33, 1), (128 * 150, 1), (5000, 7)])
+def test_reduction_of_few_and_many_partials(n, H):
+    _check(synth.generate("C5", n=n, H=H, B=1, d=128, dtype="bf16"))
