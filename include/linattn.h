@@ -19,7 +19,7 @@
  *     64-bit indexing inside.
  *   - element type of those tensors and of W~ is the descriptor's dtype: bf16 (LINATTN_BF16 and
  *     LINATTN_BF16_F32MATH) or fp32 (LINATTN_F32).  All accumulation is fp32.  The fp32 mode never
- *     rounds through bf16.
+ *     rounds to bf16 (it splits fp32 values exactly into bf16 pieces).
  *   - all pointers are borrowed: the caller keeps them alive until the stream work is done.
  *   - calls only enqueue work on `stream` (a hipStream_t passed as void*, NULL = default
  *     stream).  They never synchronise and never allocate.
@@ -53,11 +53,12 @@
  *     differences of nearly equal rows of S and dS and come out up to 0.2 off; out and dv keep 1e-2.
  *     LINATTN_FLAG_CENTRED removes this exception (not the first) at a cost of 3-5 %.
  *   - LINATTN_BF16_F32MATH reads and writes the same bf16 tensors but does all arithmetic in fp32
- *     (the kernels of the fp32 mode, no matrix cores, no fp16 operands): none of the limits above
- *     applies, |v| may be any finite bf16 value, and the only rounding that matters is the bf16
- *     store of the results.  It is about 50x slower than LINATTN_BF16 (5.5 ms against 0.11 ms for the
- *     forward at the Wan-1.3B 480p shape): a device-side reference and a mode for numerically
- *     delicate inputs, not the fast path.
+ *     (the kernels of the fp32 mode, no fp16 operands): none of the limits above applies, |v| may be
+ *     any finite bf16 value, and the only rounding that matters is the bf16 store of the results.  A
+ *     training step costs about 1.7x LINATTN_BF16, a forward call 2.4x (Wan-1.3B 480p shape).
+ *   - fp32 arithmetic (this mode and LINATTN_F32) runs on the matrix cores as sums of exact products of bf16
+ *     pieces with fp32 accumulation.  Operands below about 2^-102 lose relative precision; a non-finite
+ *     input gives Inf or NaN in the outputs it reaches.
  */
 #ifndef LINATTN_H
 #define LINATTN_H
@@ -177,8 +178,8 @@ size_t linattn_workspace_bytes_wgrads(int B, int H, int n, int d, int kind, int 
 
 /*
  * Forward, Eq. 3 with the descriptor's phi (Eq. 5, or the ReLU map).  Three stages on `stream`: phi(K) fused with a split-n
- * partial state, a fixed-order reduction of the partials, phi(Q) S / (phi(Q) . z) with the
- * store of out.  Writes out [B,H,n,d] and, if the descriptor has one, state.
+ * partial state, a fixed-order reduction of the partials (in the third stage's kernel where a bf16 call is short), phi(Q) S /
+ * (phi(Q) . z) with the store of out.  Writes out [B,H,n,d] and, if the descriptor has one, state.
  * Errors: E_PHI, E_NULL, E_SHAPE (also H or d different from the descriptor), E_ALIGN,
  * E_WORKSPACE, E_STATE (state buffer smaller than this B needs), E_ALIAS, E_HIP.
  */

@@ -16,9 +16,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 # Per-file extras.  bwd_bf16.hip: MFMA results go to ordinary registers where they fit instead of
-# always to the accumulation registers (the query-side backward kernel uses all 512 registers of a
-# lane and spent a quarter of its vector instructions moving results between the two files:
-# 149 -> 134 us at the config-5 shape; neutral or slightly worse for the other files).
+# always to the accumulation registers (measured on the query-side backward kernel when it used all 512
+# registers of a lane and spent a quarter of its vector instructions moving results between the two files:
+# 149 -> 134 us at 12 heads x 32760 x 128; neutral or slightly worse for the other files).
 EXTRA = {"bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

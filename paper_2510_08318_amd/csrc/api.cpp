@@ -367,16 +367,8 @@ int linattn_bwd(const void* q, const void* k, const void* v, const void* dout,
   a.dwk = static_cast<float*>(desc.dwk);
   a.partials = reinterpret_cast<float*>(ws + plan.off_partials);
   a.dstate = reinterpret_cast<float*>(ws + plan.off_dstate);
-  a.gimg = ws + plan.off_gimg;
-  a.simg = ws + plan.off_simg;
-  a.dsimg = ws + plan.off_dsimg;
-  a.dgimg = ws + plan.off_dgimg;
-  a.wimg = ws + plan.off_wimg;
-  a.scales = reinterpret_cast<float*>(ws + plan.off_scales);
   a.vbar = reinterpret_cast<float*>(ws + plan.off_centre);
-  a.dv_row = a.vbar + (size_t)plan.BH * d;
-  a.dzc = a.dv_row + (size_t)plan.BH * d;
-  a.cs_part = a.dzc + (size_t)plan.BH * d;
+  a.cs_part = a.vbar + 3 * (size_t)plan.BH * d;
   a.blend_in = desc.blend_in; a.blend_r = desc.blend_r; a.blend_dr = desc.blend_dr;
   a.dr_part = reinterpret_cast<float*>(ws + plan.off_drpart);
   a.dw_part = reinterpret_cast<float*>(ws + plan.off_dwpart);

@@ -528,7 +528,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         char* rowp = sPhi + row * RS;
         constexpr int CPH = C::LOC / 8;
         // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
-        // on the deviation from the uniform map; (2/D) x the column sums are added back by the prep kernel
+        // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
         const float mean = CENTRE ? kMean : 0.f;
         auto pack4 = [&](const float* f) {
           return make_uint4(pack_f16x2(f[0] - mean, f[1] - mean), pack_f16x2(f[2] - mean, f[3] - mean),

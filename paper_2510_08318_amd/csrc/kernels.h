@@ -82,15 +82,16 @@ struct Plan {
   // backward only
   int KP;                 // workgroups per (b,h) of the passes with 8 wavefronts, each on its own 32-token blocks
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
-  size_t off_gimg;        // fp16 [BH][d*d]       operand image of S for dL/dphi(q) (bf16 mode)
-  // operand images built once per head by the backward's prep kernels (bf16 mode)
-  size_t img_state_bytes; // bytes of one query-pass-style image of a (d+1) x d state
-  size_t off_simg;        // [BH] image of S (as in the query pass), for the recomputed o
-  size_t off_dsimg;       // [BH] the same image of dS, for dv
-  size_t off_dgimg;       // fp16 [BH][d*d]       operand image of dS for dL/dphi(k)
-  size_t off_wimg;        // [H][4][d*d bytes]    W~_q image, W~_q transposed image, then the same for W~_k
-  size_t off_scales;      // fp32 [BH][2]         power-of-two scales of the S and dS images
-  size_t off_centre;      // centred backward: fp32 [BH][3][d] (mean value row vbar, constant row of dv, centred dz), then
+  // Regions of the bf16 backward that nothing uses any more (operand images, which the kernels build in LDS, and their scales); they
+  // keep their bytes, so that a workspace sized by an earlier call or a stored size stays what it was.
+  size_t off_gimg;
+  size_t img_state_bytes;
+  size_t off_simg;
+  size_t off_dsimg;
+  size_t off_dgimg;
+  size_t off_wimg;
+  size_t off_scales;
+  size_t off_centre;      // bf16 backward: fp32 [BH][3][d] (mean value row vbar; the other two rows unused), then
                           // [BH][P][d+8] per-workgroup column sums of dO/den (d) and the sum of -delta/den (1)
   size_t off_drpart;      // fp32 [BH][P] + [kDotParts]: per-workgroup parts of dL/dr (mixed attention, Eq. 6)
   size_t off_dwpart;      // fp32 [BH][P][d*d/2] partial dW~_q, then [BH][max(P, KP)][d*d/2] partial dW~_k (weight gradients only)
@@ -112,10 +113,7 @@ struct BwdArgs {
   const float* state;     // [BH][d+1][d] from the forward
   float *dwq, *dwk;       // nullable
   float *partials, *dstate, *dw_part, *du_q, *du_k;
-  void* gimg;
-  void *simg, *dsimg, *dgimg, *wimg;
-  float* scales;
-  float *vbar, *dv_row, *dzc, *cs_part;   // centred backward (Plan::off_centre)
+  float *vbar, *cs_part;   // Plan::off_centre
   // mixed attention (Eq. 6): softmax-branch output, the layer's r, dL/dr; all null when off
   const void* blend_in;
   const float* blend_r;
