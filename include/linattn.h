@@ -55,7 +55,7 @@
  *   - LINATTN_BF16_F32MATH reads and writes the same bf16 tensors but does all arithmetic in fp32
  *     (the kernels of the fp32 mode, no fp16 operands): none of the limits above applies, |v| may be
  *     any finite bf16 value, and the only rounding that matters is the bf16 store of the results.  A
- *     training step costs about 1.7x LINATTN_BF16, a forward call 2.4x (Wan-1.3B 480p shape).
+ *     training step costs about 1.7x LINATTN_BF16, a forward call 1.5x (Wan-1.3B 480p shape).
  *   - fp32 arithmetic (this mode and LINATTN_F32) runs on the matrix cores as sums of exact products of bf16
  *     pieces with fp32 accumulation.  Operands below about 2^-102 lose relative precision; a non-finite
  *     input gives Inf or NaN in the outputs it reaches.
