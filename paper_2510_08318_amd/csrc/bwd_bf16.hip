@@ -372,7 +372,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   constexpr int RS = D * 2;
   constexpr int WMN = D / 64;
   constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
-  constexpr float kMean = 2.0f / D;                        // mean of phi over its features
+  constexpr float mean = CENTRE ? 2.0f / D : 0.f;          // what is taken out of phi before it is rounded: its mean over the features
   using DWT = DwTile<D, 4>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
@@ -416,6 +416,11 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     uint16_t* dqb = dq + head_base(rw, bh, H);
     const int prow = 32 * pw + (lane % 32);
     float dr_acc = 0.f;
+    float z_mean = 0.f;                                    // mean * the sum of z over the lane's features
+    if constexpr (CENTRE) {
+      for (int j = 0; j < C::LOC; ++j) z_mean += sZ[g * C::LOC + j] + sZ[C::HALF + g * C::LOC + j];
+      z_mean *= mean;
+    }
     uint4 xq[C::UK], xr[C::UK], dor[D / 16];
     auto load_rows = [&](int tile) {
       const int t = tile * kTile + prow;
@@ -449,6 +454,11 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       {
         uint32_t unused[C::NPK];
         softmax_full<D>(u, pp, pm, unused);
+      }
+      if constexpr (CENTRE) {
+        // (as values of their own: folded with the mean taken out below, the unnormalised exponentials would be kept beside them)
+#pragma unroll
+        for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
       }
       // the token's largest |dO|: magnitudes of bf16 compare as integers
       float dmax;
@@ -489,7 +499,10 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       // A+-, Z+-; feature g*LOC + j of each half
       const int z_at = g * C::LOC / 4 + opaque_zero();
       auto z4 = [&](int q) { return reinterpret_cast<const float4*>(sZ)[z_at + q]; };
-      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f;
+      // Zr: the normaliser of phi as the sum dS takes it, rounded to fp16 (CENTRE: rounded after its mean is taken out).  dS adds
+      // phi / den: with the same rounded phi above and below, what the roundings of a token's features have in common drops out
+      // (with den from the fp32 phi dW~_k was 1 % further off, 2 % with CENTRE).  dq has fp32 phi on both sides.
+      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f, Zr = z_mean;
 #pragma unroll
       for (int q = 0; q < C::LOC / 4; ++q) {
         const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
@@ -500,10 +513,22 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
           ap = fmaf(ga[j / 16][j % 16], pp[j], ap); am = fmaf(ga[G::GM / 2 + j / 16][j % 16], pm[j], am);
           Zp = fmaf(zp[i], pp[j], Zp); Zm = fmaf(zm[i], pm[j], Zm);
         }
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const int j = 4 * q + i;
+          const f16x2 rp = __builtin_bit_cast(f16x2, pack_f16x2(pp[j] - mean, pp[j + 1] - mean));
+          const f16x2 rm = __builtin_bit_cast(f16x2, pack_f16x2(pm[j] - mean, pm[j + 1] - mean));
+          Zr = fmaf((float)rp[0], zp[i], Zr); Zr = fmaf((float)rp[1], zp[i + 1], Zr);
+          Zr = fmaf((float)rm[0], zm[i], Zr); Zr = fmaf((float)rm[1], zm[i + 1], Zr);
+        }
       }
+      // (phi is rounded again when it is parked: seen as the same values, the 32 packed registers would be kept, and spilled)
+#pragma unroll
+      for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
       pair32(Zp, lo, hi); Zp = lo + hi;
       pair32(Zm, lo, hi); Zm = lo + hi;
-      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
+      pair32(Zr, lo, hi);
+      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm), inv_r = __builtin_amdgcn_rcpf(lo + hi);
       const float unscale = __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);     // exact: powers of two
       if constexpr (BLEND) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
@@ -515,7 +540,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       const float delta = (ap + am) * (unscale * inv_den);
       {
         // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
-        float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_den * om : 0.f;
+        float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_r * om : 0.f;
         m = wave_max_paired(m);
         if (lane == 0) sRed[pw] = m;
       }
@@ -529,7 +554,6 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         constexpr int CPH = C::LOC / 8;
         // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
         // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
-        const float mean = CENTRE ? kMean : 0.f;
         auto pack4 = [&](const float* f) {
           return make_uint4(pack_f16x2(f[0] - mean, f[1] - mean), pack_f16x2(f[2] - mean, f[3] - mean),
                             pack_f16x2(f[4] - mean, f[5] - mean), pack_f16x2(f[6] - mean, f[7] - mean));
@@ -541,7 +565,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
           *reinterpret_cast<uint4*>(rowp + (((gz * CPH + c) ^ psw) * 16)) = a;
           *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + gz * CPH + c) ^ psw) * 16)) = b;
         }
-        const float sc = valid ? inv_den * gamma * om : 0.f;
+        const float sc = valid ? inv_r * gamma * om : 0.f;
         char* drowp = sDO + row * RS;
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) {
