@@ -528,7 +528,9 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       pair32(Zp, lo, hi); Zp = lo + hi;
       pair32(Zm, lo, hi); Zm = lo + hi;
       pair32(Zr, lo, hi);
-      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm), inv_r = __builtin_amdgcn_rcpf(lo + hi);
+      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
+      // (a token whose features with a key behind them all round to zero adds nothing but must not spread Inf)
+      const float inv_r = lo + hi > 0.f ? __builtin_amdgcn_rcpf(lo + hi) : inv_den;
       const float unscale = __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);     // exact: powers of two
       if constexpr (BLEND) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is

@@ -29,3 +29,23 @@ def test_rounding_common_to_a_token_drops_out_of_dS(d, centred):
     # per head, so that no head's scale decides
     slope = np.mean([np.sum(a * r) / np.sum(r * r) for a, r in zip(dwk, ref)]) - 1.0
     assert abs(slope) <= 2.0 ** -13, slope
+
+
+@pytest.mark.parametrize("centred", [False, True], ids=["plain", "centred"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_token_whose_keyed_features_round_to_zero(d, centred):
+    """The keys all sit on one feature of each half, one query on others: its phi at the keys' features is exp(-30), zero in fp16.  Its
+    rounded normaliser is zero; the gradients that sum over the queries stay finite."""
+    x = synth.generate("C5", n=300, H=2, d=d, dtype="bf16")
+    w = np.zeros((x.H, d, d // 2), np.float32)
+    w[:, 0, 0], w[:, 0, 1], w[:, 1, 2], w[:, 1, 3] = 30.0, -30.0, 30.0, -30.0
+    x.wq = x.wk = synth._pack(w, x.dtype)
+    for name in ("q", "k"):
+        t = O.to_f64(getattr(x, name)).astype(np.float32)
+        t[..., :2] = [1.0, 0.0]
+        if name == "q":
+            t[:, :, 7, :2] = [0.0, 1.0]
+        setattr(x, name, synth._pack(t, x.dtype))
+    got = _run(x, False, True, centred)
+    for name in ("dk", "dv", "dwk"):
+        assert np.isfinite(got[name]).all(), name
