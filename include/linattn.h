@@ -57,8 +57,10 @@
  *     any finite bf16 value, and the only rounding that matters is the bf16 store of the results.  A
  *     training step costs about 1.7x LINATTN_BF16, a forward call 1.5x (Wan-1.3B 480p shape).
  *   - fp32 arithmetic (this mode and LINATTN_F32) runs on the matrix cores as sums of exact products of bf16
- *     pieces with fp32 accumulation.  Operands below about 2^-102 lose relative precision; a non-finite
- *     input gives Inf or NaN in the outputs it reaches.
+ *     pieces with fp32 accumulation.  Operands below 2^-110 lose the bits below 2^-133.  What the pieces cannot
+ *     carry (finite values above 3.3895e38, which round to Inf as bf16, infinities and NaN) comes out as plain fp32 FMA
+ *     gives it: the workgroups that meet such a value run their share once more that way, at about the time per
+ *     token of a scalar kernel (10 to 30 times the usual).
  */
 #ifndef LINATTN_H
 #define LINATTN_H

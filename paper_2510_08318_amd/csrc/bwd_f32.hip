@@ -9,6 +9,7 @@
 // tokens and dv are passes of their own.  delta needs no o: phi . (S dO) is o . dO times den.
 #include "kernels.h"
 #include "f32_split.h"
+#include "f32_plain.h"
 #include "f32_state.h"
 #include "f32_apply.h"
 
@@ -82,9 +83,11 @@ struct WImage {
 
 // State (S or dS) of one head -> pieces of the A operands of G^T = M Y^T in LDS: entry (ks, mb, lane = (m, g)) holds
 // M[row(mb, m)][16ks + 8g + e]; the rows are ordered so that accumulator register r of block mb is element 16mb + r of the lane's phi.
+// Returns whether every value the thread met splits (see build_s_pieces).
 template <int D, int KIND, int NTHREADS>
-__device__ __forceinline__ void build_g_pieces(const float* __restrict__ M, uint4* sG, int tid) {
+__device__ __forceinline__ bool build_g_pieces(const float* __restrict__ M, uint4* sG, int tid) {
   constexpr int MB = D / 32, IMG = (D / 16) * MB * 64;
+  bool all = true;
   for (int it = tid; it < IMG; it += NTHREADS) {
     const int lane = it % 64, mb = (it / 64) % MB, ks = it / (64 * MB);
     const int m = lane % 32, r = 4 * (m / 8) + m % 4;
@@ -95,14 +98,16 @@ __device__ __forceinline__ void build_g_pieces(const float* __restrict__ M, uint
     unpack_f32x4(src[1], v + 4);
     uint4 p[3];
     split8(v, p);
+    all = all && splits8(v);
 #pragma unroll
     for (int i = 0; i < 3; ++i) sG[i * IMG + it] = p[i];
   }
+  return all;
 }
 
 template <int D, int KIND, typename T>
 constexpr size_t grad_smem() {
-  return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * (D / 16) * (D / 32) * 64) * sizeof(uint4) + (D + 8) * sizeof(float);
+  return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * (D / 16) * (D / 32) * 64) * sizeof(uint4) + (D + 2 * NT8 / 64) * sizeof(float);
 }
 
 // 8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks (a lane pair owns a token).
@@ -124,6 +129,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   uint4* sG = sW + (KIND == kPhiRelu ? 0 : NX * W::IMG);
   float* sZ = reinterpret_cast<float*>(sG + 3 * IMG);
   float* sRed = sZ + D;
+  int* sPlain = reinterpret_cast<int*>(sRed + NT8 / 64);   // [8] the wavefront has met a state value that does not split (f32_plain.h)
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -147,10 +153,15 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   const int b_first = b < nblk ? b : nblk - 1;
   xr.load(row_of(xb, b_first), g);
   if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
-  build_g_pieces<D, KIND, NT8>(sb, sG, tid);
+  const bool state_splits = build_g_pieces<D, KIND, NT8>(sb, sG, tid);
+  if (lane == 0) sPlain[w] = 0;
+  if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
   build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
   __syncthreads();
 
+  const int b_own = b;
+  const bool state_plain = any_of_8(sPlain);
+  float chk = 0.f;                                         // NaN once the lane has met what does not split
   for (; b < nblk; b += stride) {
     const int t = b * 32 + c;
     const bool valid = t < n;
@@ -195,6 +206,9 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
       yr.pieces(ks, yp[0]);
       mfma_pieces<3, NX>(a, yp, ga);
     }
+    // a y that does not split makes every feature of its token NaN or Inf, phi from an x that does not is NaN: one value tells
+    // (Hedgehog: the sums of the Jacobian, below)
+    if constexpr (KIND == kPhiRelu) chk = fmaf(ga[0][0][0], 0.f, chk);
     float gr[D / 2];
     if constexpr (QSIDE) {
       float part = 0.f;
@@ -255,6 +269,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
       float lo, hi;
       pair32(cp, lo, hi); cp = lo + hi;
       pair32(cm, lo, hi); cm = lo + hi;
+      chk = fmaf(cp + cm, 0.f, chk);
       float du[C::LOC];
 #pragma unroll
       for (int j = 0; j < C::LOC; ++j) du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
@@ -282,6 +297,23 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
       }
       store_rows<D, T>(dxb, rw.sn, b * 32, n, lane, [&](int r, int mb) { return xa[0][mb][r]; });
     }
+  }
+  if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
+    __threadfence();                                       // what is stored above is written again
+    dr_acc = 0.f;
+    float dr = 0.f;
+#pragma unroll 1
+    for (b = b_own; b < nblk; b += stride)
+#pragma unroll 1
+      for (int tt = 0; tt < 32 && 32 * b + tt < n; ++tt) {
+        const int t = 32 * b + tt;
+        const size_t at = (size_t)t * rw.sn;
+        float* du = du_ws != nullptr ? du_ws + ((size_t)bh * n + b * 32) * C::HALF + 4 * tt : nullptr;
+        Plain<D, KIND, T>::template grad<QSIDE, BLEND>(xb + at, yb + at, wx + (size_t)h * D * C::HALF, sb, dxb + at, du,
+                                                       n - b * 32 < 32 ? n - b * 32 : 32, QSIDE ? weights + (size_t)bh * n + t : nullptr,
+                                                       BLEND ? bb + at : nullptr, om, &dr, lane);
+      }
+    if (lane == 0) dr_acc = dr;
   }
   if constexpr (BLEND) {
     for (int m = 32; m >= 1; m >>= 1) dr_acc += __shfl_xor(dr_acc, m, 64);
@@ -366,7 +398,7 @@ __global__ __launch_bounds__(NT8) void dw_f32_kernel(const T* __restrict__ q, co
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(float, cur.x[e][i]);
-        split8(v, a[i]);
+        split8<true>(v, a[i]);                     // (an infinite x has made du NaN already)
       }
     } else {
 #pragma unroll

@@ -1,6 +1,7 @@
 // phi(x_i) M for every token, in fp32 arithmetic on the bf16 matrix cores (f32_split.h).
 #pragma once
 #include "f32_split.h"
+#include "f32_plain.h"
 
 namespace linattn {
 namespace f32 {
@@ -11,7 +12,7 @@ namespace f32 {
 // accumulators as whole rows.
 template <int D, int KIND, typename T>
 constexpr size_t apply_smem() {
-  return ((KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG) + 3 * ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64) * sizeof(uint4) + D * sizeof(float);
+  return ((KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG) + 3 * ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64) * sizeof(uint4) + (D + NT8 / 64) * sizeof(float);
 }
 template <int D, int KIND, typename T, bool NORM, bool BLEND>
 __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q, const T* __restrict__ wq,
@@ -24,6 +25,7 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
   uint4* sW = smem;
   uint4* sS = sW + (KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG);
   float* sZ = reinterpret_cast<float*>(sS + 3 * IMG);
+  int* sPlain = reinterpret_cast<int*>(sZ + D);            // [8] the wavefront has met a state value that does not split (f32_plain.h)
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -45,16 +47,23 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
   int b = blockIdx.x * (NT8 / 64) + w;
   load(b < nblk ? b : nblk - 1);
   if constexpr (KIND == kPhiHedgehog) build_w_pieces<D, T, NT8>(wq + (size_t)h * D * (D / 2), sW, tid);
-  build_s_pieces<D, KIND, NT8>(sb, sS, tid);
+  const bool state_splits = build_s_pieces<D, KIND, NT8>(sb, sS, tid);
+  if (lane == 0) sPlain[w] = 0;
+  if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
   if constexpr (NORM) build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
   __syncthreads();
 
+  const int b_own = b;
+  const bool state_plain = any_of_8(sPlain);
+  float chk = 0.f;                                         // NaN once the lane has met what does not split
   for (; b < nblk; b += stride) {
     float f[D / 2];
     phi_octets<D, KIND, T>(x, sW, lane, f);
     load(b + stride < nblk ? b + stride : b);
     float inv = 1.f;
     if constexpr (NORM) inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+    // phi is at most 1 and splits, unless an x or u that did not made its half NaN (and with it den)
+    if constexpr (KIND == kPhiHedgehog) chk = fmaf(NORM ? inv * 0x1p8f : f[0] + f[D / 4], 0.f, chk);
     f32x16 o[1][L::MB];
 #pragma unroll
     for (int mb = 0; mb < L::MB; ++mb) o[0][mb] = zero16();
@@ -72,6 +81,11 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
       split8(v, a[0]);
       mfma_pieces<3, 3>(a, s, o);
     }
+    if constexpr (KIND == kPhiRelu) {
+      // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
+#pragma unroll
+      for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
+    }
     if constexpr (BLEND) {
       const int t0 = b * 32;
 #pragma unroll
@@ -83,6 +97,16 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
       }
     }
     store_rows<D, T>(ob, rw.sn, b * 32, n, lane, [&](int r, int mb) { return o[0][mb][r]; });
+  }
+  if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
+    __threadfence();                                       // the rows stored above are written again
+#pragma unroll 1
+    for (b = b_own; b < nblk; b += stride)
+#pragma unroll 1
+      for (int t = 32 * b; t < 32 * b + 32 && t < n; ++t) {
+        const size_t at = (size_t)t * rw.sn;
+        Plain<D, KIND, T>::template apply<NORM, BLEND>(qb + at, wq + (size_t)h * D * (D / 2), sb, ob + at, BLEND ? bb + at : nullptr, rb, lane);
+      }
   }
 }
 

@@ -4,7 +4,8 @@
 // 2^-24 |a b|, the size of one fp32 rounding.  A tensor stored as bf16 is its own single piece, so a product with it is
 // three piece products and one of two such tensors is exact.  The accumulators are fp32 and take the 16 products of a step
 // together, so a sum over n tokens sees n/16 roundings per piece product where a chain of scalar FMAs sees n.  bf16 has the
-// exponent range of fp32: nothing needs scaling (the third piece of a value below 2^-110 leaves it: such values carry 16 bits).
+// exponent range of fp32: nothing needs scaling.  Values below 2^-110 lose the bits below 2^-133, the smallest bf16; infinities and
+// finite values that round to Inf are left to f32_plain.h.
 // The step's sum is cut, not rounded, below 1/16 unit of a larger accumulator: a bias of -1/32 unit per instruction, which a
 // sum over many tokens would show (it is the same for every feature, so it does not average out in phi(q) S).  Such sums are
 // therefore taken with alternating sign, tile by tile or wavefront by wavefront.
@@ -29,19 +30,23 @@ __device__ __forceinline__ float ldf(const uint16_t* p, size_t i) { return __bui
 __device__ __forceinline__ float lo_f32(uint32_t pair) { return __builtin_bit_cast(float, pair << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t pair) { return __builtin_bit_cast(float, pair & 0xffff0000u); }
 
-// Two fp32 values -> three packed bf16 pairs whose sums are the values.
+// Two fp32 values -> three packed bf16 pairs whose sums are the values.  WIDE: also for finite values that round to Inf as bf16 (their
+// first piece is then the largest bf16), one more operation a value.
+template <bool WIDE = false>
 __device__ __forceinline__ void split2(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
-  p0 = pack_bf16x2(a, b);
+  constexpr float top = 0x1.fep127f;
+  p0 = WIDE ? pack_bf16x2(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top)) : pack_bf16x2(a, b);
   const float a1 = a - lo_f32(p0), b1 = b - hi_f32(p0);
   p1 = pack_bf16x2(a1, b1);
   p2 = pack_bf16x2(a1 - lo_f32(p1), b1 - hi_f32(p1));
 }
 // Eight values -> the three pieces of an MFMA operand.
+template <bool WIDE = false>
 __device__ __forceinline__ void split8(const float* v, uint4 (&p)[3]) {
-  split2(v[0], v[1], p[0].x, p[1].x, p[2].x);
-  split2(v[2], v[3], p[0].y, p[1].y, p[2].y);
-  split2(v[4], v[5], p[0].z, p[1].z, p[2].z);
-  split2(v[6], v[7], p[0].w, p[1].w, p[2].w);
+  split2<WIDE>(v[0], v[1], p[0].x, p[1].x, p[2].x);
+  split2<WIDE>(v[2], v[3], p[0].y, p[1].y, p[2].y);
+  split2<WIDE>(v[4], v[5], p[0].z, p[1].z, p[2].z);
+  split2<WIDE>(v[6], v[7], p[0].w, p[1].w, p[2].w);
 }
 __device__ __forceinline__ void unpack_f32x4(uint4 r, float* v) {
   v[0] = __builtin_bit_cast(float, r.x); v[1] = __builtin_bit_cast(float, r.y);
@@ -137,12 +142,21 @@ __device__ __forceinline__ void build_w_pieces(const T* __restrict__ w, uint4* s
   }
 }
 
+// Whether an fp32 value's first piece is finite (f32_plain.h has the rest).
+__device__ __forceinline__ bool splits(float v) { return fabsf(v) < 0x1.ffp127f; }
+__device__ __forceinline__ bool splits8(const float* v) {
+  return splits(fmaxf(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))),
+                      fmaxf(fmaxf(fabsf(v[4]), fabsf(v[5])), fmaxf(fabsf(v[6]), fabsf(v[7])))));
+}
+
 // State [D+1][D] of one head -> pieces of the B operands of Y = phi S in LDS: entry (ks, mb, lane = (c, g)) of a piece holds
 // S[phi_feature(ks, g) + e][channel_cols(mb, c)].  A thread reads the MB adjacent channels of eight features at a time.
+// Returns whether every value the thread met splits (a NaN passes: it stays one).
 template <int D, int KIND, int NTHREADS>
-__device__ __forceinline__ void build_s_pieces(const float* __restrict__ S, uint4* sS, int tid) {
+__device__ __forceinline__ bool build_s_pieces(const float* __restrict__ S, uint4* sS, int tid) {
   using L = ApplyLayout<D>;
   constexpr int IMG = L::KS * L::MB * 64;
+  bool all = true;
   for (int it = tid; it < L::KS * 64; it += NTHREADS) {
     const int lane = it % 64, ks = it / 64;
     const float* src = S + phi_feature<D, KIND>(ks, lane / 32) * D + L::MB * (lane % 32);
@@ -161,10 +175,12 @@ __device__ __forceinline__ void build_s_pieces(const float* __restrict__ S, uint
     for (int mb = 0; mb < L::MB; ++mb) {
       uint4 p[3];
       split8(v[mb], p);
+      all = all && splits8(v[mb]);
 #pragma unroll
       for (int i = 0; i < 3; ++i) sS[i * IMG + (ks * L::MB + mb) * 64 + lane] = p[i];
     }
   }
+  return all;
 }
 
 // U^T = W~^T X^T for the 32 tokens of a wavefront (see project): u[mb][r] = pre-softmax feature g*LOC + 16mb + r of the lane's token.

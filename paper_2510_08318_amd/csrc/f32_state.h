@@ -2,6 +2,7 @@
 // the forward (x = k, y = v) and, with per-token weights, the sums dS and dz of the backward (x = q, y = dO).
 #pragma once
 #include "f32_split.h"
+#include "f32_plain.h"
 
 namespace linattn {
 namespace f32 {
@@ -26,7 +27,7 @@ struct StatePass {
   static constexpr int PT = kTile * RS;                            // bytes of one piece tile
   static constexpr int W_BYTES = KIND == kPhiRelu ? 0 : NX * C::W_IMG * 16;
   static constexpr int Y_BYTES = NX == 1 ? PT : 0;
-  static constexpr size_t SMEM = (size_t)W_BYTES + NP * PT + Y_BYTES + 4 * D * sizeof(float);
+  static constexpr size_t SMEM = (size_t)W_BYTES + NP * PT + Y_BYTES + (4 * D + 4) * sizeof(float);
 
   // Tiles tile0 .. tile0+nt-1 of one (b,h); xb, yb: its first rows; every thread of the workgroup calls it.
   static __device__ __forceinline__ void segment(const T* __restrict__ xb, const T* __restrict__ yb, const T* __restrict__ wh,
@@ -37,6 +38,7 @@ struct StatePass {
     char* sPhi = reinterpret_cast<char*>(smem) + W_BYTES;
     char* sY = sPhi + NP * PT;
     float* zred = reinterpret_cast<float*>(sY + Y_BYTES);          // [4][D]
+    int* sPlain = reinterpret_cast<int*>(zred + 4 * D);            // [4] the acc wavefront's sum is not finite
     const int tid = threadIdx.x, lane = tid % 64;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int role = w / 4, pw = w % 4, g = lane / 32, c = lane % 32;
@@ -237,6 +239,17 @@ struct StatePass {
           contract(it);
         }
       }
+      // a y that does not split makes its column NaN or Inf; so does, for both halves of the Hedgehog map, an x: one row of a block
+      // tells (ReLU: an x that does not split makes its feature's row so)
+      float chk = 0.f;
+#pragma unroll
+      for (int i = 0; i < FW; ++i)
+#pragma unroll
+        for (int r = 0; r < (KIND == kPhiRelu ? 16 : 1); ++r)
+#pragma unroll
+          for (int j = 0; j < CW; ++j) chk = fmaf(s[i][j][r], 0.f, chk);
+      const bool bad = __any(chk != chk);
+      if (lane == 0) sPlain[pw] = bad;
 #pragma unroll
       for (int i = 0; i < FW; ++i)
 #pragma unroll
@@ -248,7 +261,15 @@ struct StatePass {
     }
     __syncthreads();
     if (tid < D) dst[D * D + tid] = (zred[tid] + zred[2 * D + tid]) + (zred[D + tid] + zred[3 * D + tid]);
+    const int4 bad4 = *reinterpret_cast<const int4*>(sPlain);
+    const bool plain = __builtin_amdgcn_readfirstlane((bad4.x | bad4.y) | (bad4.z | bad4.w)) != 0;       // the same in every wavefront
+    if (__builtin_expect(plain, 0)) __threadfence();                                    // what is stored above is written again, by other wavefronts
     __syncthreads();                                               // the next segment reuses every LDS region
+    if (__builtin_expect(plain, 0)) {
+      const int t1 = (tile0 + nt) * kTile;
+      Plain<D, KIND, T>::template state<WEIGHTED>(xb, yb, wh, weights, dst, tile0 * kTile, t1 < n ? t1 : n, rw.sn,
+                                                    reinterpret_cast<float*>(sPhi), w, lane);
+    }
   }
 };
 

@@ -1,0 +1,207 @@
+"""The fp32-arithmetic modes over the whole range of fp32: finite values that round to Inf as bf16 (above 3.3895e38), infinities, and
+values so small that their low pieces leave the range of bf16.  The products of these modes are sums of bf16 piece products;
+what the pieces cannot carry has to come out as fp32 arithmetic gives it all the same.
+
+Reference: the fp64 oracle; where it holds infinities or NaN the result holds the same, elsewhere the bar of the mode, 1e-5 of the
+largest magnitude of its row or column (bf16 results: 2^-8 for their store)."""
+import numpy as np
+import pytest
+
+from oracle import linattn_oracle as O
+from oracle import relu_oracle as R
+from paper_2510_08318_amd import synth
+
+pytestmark = pytest.mark.gpu
+HUGE = 3.4e38            # finite in fp32, Inf when rounded to bf16
+INF = np.inf
+
+
+def _layer(x, relu, wgrads=True):
+    from paper_2510_08318_amd import torch_glue as G
+    bf16 = x.dtype == "bf16"
+    if relu:
+        return G.ReluLayer(x.H, x.d, x.B, x.n, G.to_device(x.q[:, :1, :1, :1]).dtype, f32_math=bf16)
+    return G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n, want_wgrads=wgrads, f32_math=bf16)
+
+
+def _run(x, relu, backward=True):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    q, k, v, do = [G.to_device(t) for t in (x.q, x.k, x.v, x.dout)]
+    lay = _layer(x, relu)
+    got = {"out": lay.forward(q, k, v), "state": lay.state}
+    if backward:
+        got.update(zip(("dq", "dk", "dv"), lay.backward(q, k, v, do)))
+        if not relu:
+            got.update(dwq=lay.dwq, dwk=lay.dwk)
+    torch.cuda.synchronize()
+    got = {name: G.to_host_f64(t) for name, t in got.items()}
+    lay.close()
+    return got
+
+
+def _set(x, name, index, value):
+    t = O.to_f64(getattr(x, name)).astype(np.float32)
+    t[index] = value
+    setattr(x, name, synth._pack(t, x.dtype))
+
+
+def _inputs(dtype, d, n=200, H=2):
+    return synth.generate("C5", n=n, H=H, d=d, dtype=dtype)
+
+
+def _phi(x, relu):
+    def one(t, w):
+        return np.maximum(t, 0) if relu else O.phi(t, w)
+    q, k, wq, wk = [O.to_f64(t) for t in (x.q, x.k, x.wq, x.wk)]
+    return [np.stack([one(t[0, h], w[h]) for h in range(x.H)]) for t, w in ((q, wq), (k, wk))]
+
+
+def _forward(x, relu):
+    """out and state per head in fp64, infinities included."""
+    fq, fk = _phi(x, relu)
+    v = O.to_f64(x.v)[0]
+    with np.errstate(all="ignore"):
+        # term by term: a BLAS product may meet 0 * Inf in its padding
+        S = (fk[:, :, :, None] * v[:, :, None, :]).sum(1)
+        z = fk.sum(1)
+        den = (fq * z[:, None, :]).sum(-1, keepdims=True) + (1e-6 if relu else 0.0)
+        out = (fq[:, :, :, None] * S[:, None]).sum(2) / den
+    return out[None], np.concatenate([S, z[:, None]], 1)[None]
+
+
+def _same(got, ref, bar, what):
+    """Equal kinds (Inf, NaN), and finite values within bar of the largest finite magnitude of their channel."""
+    kinds = (np.isnan(ref), np.isposinf(ref), np.isneginf(ref))
+    for kind, fn in zip(kinds, (np.isnan, np.isposinf, np.isneginf)):
+        assert np.array_equal(fn(got), kind), (what, int((fn(got) != kind).sum()))
+    ok = np.isfinite(ref)
+    scale = np.max(np.abs(np.where(ok, ref, 0.0)), axis=-2, keepdims=True)
+    err = np.abs(np.where(ok, got, 0.0) - np.where(ok, ref, 0.0)) / np.where(scale > 0, scale, 1.0)
+    assert err.max() <= bar, (what, err.max())
+
+
+BARS = {"f32": 1e-5, "bf16": 2.0 ** -8}
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype,value", [("f32", HUGE), ("f32", -HUGE), ("f32", INF), ("f32", -INF), ("bf16", INF), ("bf16", -INF)])
+def test_forward_of_huge_and_infinite_values(dtype, value, d, relu):
+    x = _inputs(dtype, d)
+    _set(x, "v", (0, 0, 130, 5), value)
+    if relu and not np.isinf(value):        # features that do not add up to 2: small enough for phi(q) S to stay in range
+        _set(x, "k", (0, 0, 130), 1e-3 * O.to_f64(x.k)[0, 0, 130].astype(np.float32))
+    got = _run(x, relu, backward=False)
+    out, state = _forward(x, relu)
+    _same(got["state"], state, 1e-5, "state")
+    _same(got["out"], out, BARS[dtype], "out")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_infinities_of_both_signs_meet(dtype):
+    x = _inputs(dtype, 128)
+    _set(x, "v", (0, 0, 130, 5), INF)
+    _set(x, "v", (0, 0, 7, 5), -INF)
+    got = _run(x, False, backward=False)
+    out, state = _forward(x, False)
+    _same(got["state"], state, 1e-5, "state")
+    _same(got["out"], out, BARS[dtype], "out")
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinite_gradient_rows(d, dtype, relu):
+    """dv = phi(k) dS is Inf in the column that the gradient's infinity is in and as ever in the others; the dq of every other token
+    does not see it."""
+    x = _inputs(dtype, d)
+    clean = _run(x, relu)
+    _set(x, "dout", (0, 0, 130, 5), INF)
+    got = _run(x, relu)
+    fq, fk = _phi(x, relu)
+    with np.errstate(all="ignore"):
+        kind = (fk[0] * (fq[0, 130] * np.inf)[None]).sum(-1)      # Inf, or NaN where a ReLU feature is zero
+    assert np.array_equal(np.isposinf(got["dv"][0, 0, :, 5]), np.isposinf(kind))
+    assert np.array_equal(np.isnan(got["dv"][0, 0, :, 5]), np.isnan(kind))
+    keep = np.arange(x.n) != 130
+    assert np.array_equal(got["dv"][0, 1], clean["dv"][0, 1]) and np.array_equal(got["dq"][0, 1], clean["dq"][0, 1])
+    assert np.abs(got["dq"][0, 0, keep] - clean["dq"][0, 0, keep]).max() <= BARS[dtype] * np.abs(clean["dq"][0, 0]).max()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("where", ["q", "k"])
+def test_huge_rows_of_q_and_k(where, d):
+    """A huge channel that W~ barely reads: u is finite, and so is everything else."""
+    x = _inputs("f32", d)
+    side = "w" + where
+    _set(x, side, (0, 3), 1e-38 * O.to_f64(getattr(x, side))[0, 3].astype(np.float32))
+    _set(x, where, (0, 0, 130, 3), HUGE)
+    got = _run(x, False)
+    out, state = _forward(x, False)
+    _same(got["state"], state, 1e-5, "state")
+    _same(got["out"], out, 1e-5, "out")
+    ref = dict(zip(("dq", "dk", "dv", "dwq", "dwk"), O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)))
+    for name, r in ref.items():
+        bar = 2e-5
+        if name == "d" + side:
+            g, r3 = got[name], r.copy()
+            row = np.abs(g[0, 3] - r3[0, 3]).max() / np.abs(r3[0, 3]).max()
+            assert row <= bar, (name, row)
+            g, r3 = np.delete(g, 3, 1), np.delete(r3, 3, 1)
+            assert np.abs(g - r3).max() <= bar * np.abs(r3).max(), name
+        else:
+            assert np.abs(got[name] - r).max() <= bar * np.abs(r).max(), name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_huge_gradient_rows(d):
+    """Gradients near the top of fp32 on values small enough that nothing overflows."""
+    x = _inputs("f32", d)
+    v = (O.to_f64(x.v) * 1e-4).astype(np.float32)
+    x.v = v
+    _set(x, "dout", (0, 0, 130, 5), HUGE)
+    got = _run(x, False)
+    ref = dict(zip(("dq", "dk", "dv", "dwq", "dwk"), O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)))
+    for name, r in ref.items():
+        assert np.isfinite(got[name]).all(), name
+        err = np.abs(got[name][..., 0, :, :] - r[..., 0, :, :]).max() / np.abs(r[..., 0, :, :]).max()
+        assert err <= 2e-5, (name, err)
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+def test_softmax_arguments_and_features_near_the_top(relu):
+    """u = x W~ of 2.4e38 and more, where u log2(e) leaves the range; ReLU: a feature that rounds to Inf as bf16."""
+    x = _inputs("f32", 64)
+    if not relu:
+        for name in ("wq", "wk"):
+            w = np.zeros((x.H, 64, 32), np.float32)
+            w[:, 0, 4] = 1.0
+            w[:, 1:, :] = O.to_f64(getattr(x, name))[:, 1:, :]
+            setattr(x, name, w)
+        _set(x, "q", (0, 0, 130), 0.0)
+        _set(x, "q", (0, 0, 130, 0), 2.5e38)
+        out, state = _forward(x, relu)
+        got = _run(x, relu, backward=False)
+        _same(got["state"], state, 1e-5, "state")
+        _same(got["out"], out, 1e-5, "out")
+    else:
+        _set(x, "k", (0, 0, 130), 0.0)
+        _set(x, "k", (0, 0, 130, 0), HUGE)
+        _set(x, "v", (0, 0, 130), 2.0 ** -20 * O.to_f64(x.v)[0, 0, 130].astype(np.float32))
+        got = _run(x, relu, backward=False)
+        _, state = _forward(x, relu)
+        _same(got["state"], state, 1e-5, "state")
+
+
+@pytest.mark.parametrize("exponent,bar", [(-90, 1e-5), (-100, 1e-5), (-115, 2.0 ** -11)])
+def test_tiny_values_keep_what_their_pieces_hold(exponent, bar):
+    """Values below 2^-110 lose the bits below 2^-133, the smallest bf16: each is off by up to 2^-134.  At 2^-115, in the head of scale
+    0.5 (v of 2^-119.5 rms, n = 200, sums of phi near 3, den near 6): out, an average of v and then of S, is off by up to 4/3 of that against channels of
+    2^-122 at their largest, S by up to 4 of it against 2^-119.6: 2^-11 covers both."""
+    x = _inputs("f32", 128)
+    x.v = (O.to_f64(x.v) * 2.0 ** exponent).astype(np.float32)
+    got = _run(x, False, backward=False)
+    out, state = _forward(x, False)
+    _same(got["out"], out, bar, "out")
+    _same(got["state"][:, :, :128], state[:, :, :128], bar, "state")
