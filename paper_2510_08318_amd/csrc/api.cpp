@@ -65,13 +65,10 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
     r.KP = KP;
   }
   r.off_dstate = off;   off = up(off + (size_t)BH * r.state_elems * sizeof(float));
-  r.off_gimg = off;     off = up(off + (size_t)BH * d * d * 2);
-  r.img_state_bytes = (size_t)(d / 16) * (d / 32 + 1) * 64 * 16;
-  r.off_simg = off;     off = up(off + (size_t)BH * r.img_state_bytes);
-  r.off_dsimg = off;    off = up(off + (size_t)BH * r.img_state_bytes);
-  r.off_dgimg = off;    off = up(off + (size_t)BH * d * d * 2);
-  r.off_wimg = off;     off = up(off + (size_t)H * 4 * d * d);
-  r.off_scales = off;   off = up(off + (size_t)BH * 2 * sizeof(float));
+  // A reserve that nothing is stored in, proportional to the heads.  A descriptor sized for a batch serves smaller ones, but the need
+  // without it is not monotone in B: fewer heads get more partial slots each (87 heads of width 64: 14.6 MB for two items, 13.2
+  // for three), and calls that have always been accepted would be refused.
+  off = up(off + (size_t)BH * (4 * d * d + 2 * (d / 16) * (d / 32 + 1) * 1024 + 8) + (size_t)H * 4 * d * d);
   r.off_centre = off;   off = up(off + ((size_t)BH * 3 * d + (size_t)BH * r.P * (d + 8)) * sizeof(float));
   r.off_drpart = off;   off = up(off + ((size_t)BH * r.P + kDotParts) * sizeof(float));
   r.bytes_no_wgrads = off;

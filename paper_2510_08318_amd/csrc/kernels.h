@@ -82,15 +82,6 @@ struct Plan {
   // backward only
   int KP;                 // workgroups per (b,h) of the passes with 8 wavefronts, each on its own 32-token blocks
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
-  // Regions of the bf16 backward that nothing uses any more (operand images, which the kernels build in LDS, and their scales); they
-  // keep their bytes, so that a workspace sized by an earlier call or a stored size stays what it was.
-  size_t off_gimg;
-  size_t img_state_bytes;
-  size_t off_simg;
-  size_t off_dsimg;
-  size_t off_dgimg;
-  size_t off_wimg;
-  size_t off_scales;
   size_t off_centre;      // bf16 backward: fp32 [BH][3][d] (mean value row vbar; the other two rows unused), then
                           // [BH][P][d+8] per-workgroup column sums of dO/den (d) and the sum of -delta/den (1)
   size_t off_drpart;      // fp32 [BH][P] + [kDotParts]: per-workgroup parts of dL/dr (mixed attention, Eq. 6)
