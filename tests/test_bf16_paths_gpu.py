@@ -36,7 +36,7 @@ def _run(x, relu, wgrads, centred=False):
 def _check(x, relu=False, wgrads=True, centred=False):
     got = _run(x, relu, wgrads, centred)
     if relu:
-        ref = {"out": R.relu_fwd_bh(x.q, x.k, x.v)}
+        ref = {"out": R.relu_fwd_bh(x.q, x.k, x.v), "state": R.relu_state_bh(x.k, x.v)}
         ref.update(zip(("dq", "dk", "dv"), R.relu_bwd_bh(x.q, x.k, x.v, x.dout)))
     else:
         ref = {"out": O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk), "state": O.state_bh(x.k, x.v, x.wk)}
@@ -62,14 +62,34 @@ def test_backward_workgroups_of_several_tiles(d, mode):
 @pytest.mark.parametrize("n,H,d", [(1, 1, 64), (129, 2, 64), (300, 3, 64), (640, 2, 64), (1024, 5, 64), (1025, 5, 64), (1000, 100, 64),
                                    (128, 3, 128), (256, 3, 128), (257, 3, 128), (200, 300, 128)])
 def test_query_pass_that_sums_the_partials(n, H, d, relu):
-    if n == 1:        # one token: the state is phi(k)^T v and the gradients of q and k vanish
+    if n == 1:        # one token: the state is phi(k)^T v; out is v whatever q and k are, so dq and dk vanish (ReLU: up to its eps)
         x = synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16")
         got = _run(x, relu, False)
-        if not relu:
-            assert np.linalg.norm(got["state"] - O.state_bh(x.k, x.v, x.wk)) <= 2.0 ** -10 * np.linalg.norm(O.state_bh(x.k, x.v, x.wk))
-            assert O.err_metric(got["out"], O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk))[0] <= 1e-2
+        state = R.relu_state_bh(x.k, x.v) if relu else O.state_bh(x.k, x.v, x.wk)
+        out = R.relu_fwd_bh(x.q, x.k, x.v) if relu else O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk)
+        dq, dk, dv = (R.relu_bwd_bh(x.q, x.k, x.v, x.dout) if relu else O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout))[:3]
+        assert np.linalg.norm(got["state"] - state) <= 2.0 ** -10 * np.linalg.norm(state)
+        assert O.err_metric(got["out"], out)[0] <= 1e-2 and O.err_metric(got["dv"], dv)[0] <= 1e-2
+        for name, r in (("dq", dq), ("dk", dk)):
+            assert np.abs(got[name] - r).max() <= 1e-2 * np.abs(dv).max(), name
         return
     _check(synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16"), relu=relu)
+
+
+@pytest.mark.parametrize("n,d", [(100, 128), (200, 128), (257, 128), (1000, 64)])
+def test_mixed_attention_where_the_query_pass_sums_the_partials(n, d):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    x = synth.generate("C5", n=n, H=3, B=1, d=d, dtype="bf16")
+    s = synth._pack((np.random.default_rng(n).standard_normal(x.q.shape) * 0.1).astype(np.float32), x.dtype)
+    lay = G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n)
+    lay.set_blend(G.to_device(s), torch.tensor([0.37], device="cuda"))
+    out = G.to_host_f64(lay.forward(*[G.to_device(t) for t in (x.q, x.k, x.v)]))
+    state = G.to_host_f64(lay.state)
+    lay.close()
+    assert O.err_metric(out, O.blend_fwd_bh(x.q, x.k, x.v, x.wq, x.wk, s, 0.37))[0] <= 1e-2
+    ref = O.state_bh(x.k, x.v, x.wk)
+    assert np.linalg.norm(state - ref) <= 2.0 ** -10 * np.linalg.norm(ref)
 
 
 @pytest.mark.parametrize("n,H", [(129 * 8, 1), (129 * 9, 1), (128 * 32, 1), (128 * 33, 1), (128 * 150, 1), (5000, 7)])
