@@ -221,6 +221,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
       float lo, hi;
       pair32(part, lo, hi);
       const float delta = lo + hi;
+      if constexpr (KIND == kPhiRelu) chk = fmaf(delta, 0.f, chk);
       const float a = inv * om;
       if (valid && g == 0) weights[(size_t)bh * n + t] = make_float2(a, -delta * a);
 #pragma unroll

@@ -102,14 +102,16 @@ struct Plain {
       for (int c = 0; c < D; ++c) g[j] = fmaf(ldf(yrow, c), state[(lane + 64 * j) * D + c], g[j]);
     }
     if constexpr (QSIDE) {
+      // delta as dO . o: o is an average of values, where phi . (dO S^T) may leave the range on the way
       const float inv = 1.f / (dot(f, z, lane) + (KIND == kPhiRelu ? kReluEps : 0.f));
-      float part = 0.f, ds = 0.f;
+      float part = 0.f, ds = 0.f, o[L];
+      times(f, state, lane, o);
 #pragma unroll
       for (int j = 0; j < L; ++j) {
-        part = fmaf(f[j], g[j], part);
+        part = fmaf(ldf(yrow, lane + 64 * j), o[j] * inv, part);
         if constexpr (BLEND) ds = fmaf(ldf(yrow, lane + 64 * j), ldf(blend, lane + 64 * j), ds);
       }
-      const float delta = wave_sum(part) * inv;
+      const float delta = wave_sum(part);
       if constexpr (BLEND) *dr += wave_sum(ds) - delta;
       const float a = inv * om;
       if (lane == 0) *wt = make_float2(a, -delta * a);

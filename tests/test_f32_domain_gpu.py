@@ -169,6 +169,28 @@ def test_huge_gradient_rows(d):
         assert err <= 2e-5, (name, err)
 
 
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -10], ids=["huge", "large"])
+def test_gradient_whose_products_with_the_state_overflow(scale):
+    """dO S^T leaves the range in some features while dO . o, and with it dz and what dk gets from it, does not: Inf in those features of
+    that token's dq (ReLU), finite values everywhere else."""
+    x = _inputs("f32", 64, n=3000, H=1)
+    x.q, x.k = [np.abs(t) for t in (x.q, x.k)]
+    x.v = (x.v / scale).astype(np.float32)
+    _set(x, "dout", (0, 0, 130, 5), scale * HUGE)
+    _set(x, "dout", (0, 0, 130, 6), 0.0)
+    got = _run(x, True)
+    S, z = R.relu_state(O.to_f64(x.k)[0, 0], O.to_f64(x.v)[0, 0])
+    big = np.abs(scale * HUGE * S[:, 5]) > 2.0 ** 128
+    assert big.any() and not big.all()
+    row = got["dq"][0, 0, 130]
+    assert np.array_equal(np.isinf(row), big & (x.q[0, 0, 130] > 0))
+    assert np.isfinite(np.delete(got["dq"][0, 0], 130, 0)).all()
+    dk, dv = R.relu_bwd_bh(x.q, x.k, x.v, x.dout)[1:]
+    for name, r in (("dk", dk), ("dv", dv)):
+        ok = np.abs(r) < 2.0 ** 126
+        assert np.isfinite(got[name][ok]).all() and np.abs((got[name] - r)[ok]).max() <= 2e-5 * np.abs(r[ok]).max(), name
+
+
 @pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
 def test_softmax_arguments_and_features_near_the_top(relu):
     """u = x W~ of 2.4e38 and more, where u log2(e) leaves the range; ReLU: a feature that rounds to Inf as bf16."""
