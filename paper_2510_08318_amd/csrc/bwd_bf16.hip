@@ -473,7 +473,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
       float lo, hi;
       pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
-      const float stok = pow2_normaliser(dmax);
+      const float stok = pow2_normaliser(fminf(dmax, kTokenMax));
 
       // G = dO S^T (times scale * stok), rows laid out like phi
       f32x16 ga[G::GM];
@@ -531,15 +531,16 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
       // (a token whose features with a key behind them all round to zero adds nothing but must not spread Inf)
       const float inv_r = lo + hi > 0.f ? __builtin_amdgcn_rcpf(lo + hi) : inv_den;
-      const float unscale = __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);     // exact: powers of two
+      // 1 / (scale * stok * den), in an order that keeps in range what is; scale and stok are powers of two
+      const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);
       if constexpr (BLEND) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
         // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
-        if (valid) dr_acc -= (ap + am) * (unscale * inv_den);
+        if (valid) dr_acc -= (ap + am) * r0;
       }
       pair32(ap, lo, hi); ap = lo + hi;
       pair32(am, lo, hi); am = lo + hi;
-      const float delta = (ap + am) * (unscale * inv_den);
+      const float delta = (ap + am) * r0;
       {
         // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
         float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_r * om : 0.f;
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
       __syncthreads();
       // g = (1 - r') (G - delta z) / den, its sums cp, cm against phi, and du
-      const float r1 = om * inv_den * unscale, r2 = om * inv_den * delta;
+      const float r1 = om * r0, r2 = om * inv_den * delta;
       const float cp = ap * r1 - r2 * Zp, cm = am * r1 - r2 * Zm;
       float du[C::LOC];
 #pragma unroll

@@ -438,6 +438,10 @@ __device__ __forceinline__ float pow2_normaliser(float m) {
   return (m >= 0x1p-100f && m < 3.0e38f) ? ldexpf(1.0f, -ilogbf(m)) : 1.0f;
 }
 
+// A token's largest gradient is normalised as if it were no larger than this: the scale is then at least 2^-126, a normal number whose
+// reciprocal v_rcp_f32 gives exactly (values from 2^127 would ask for 2^-127), and the operand stays below 8.
+constexpr float kTokenMax = 0x1.8p126f;
+
 // Running power-of-two scale of a workgroup's sums over tokens (fp16 MFMA operands, fp32
 // accumulators).  A tile whose largest operand magnitude is m wants the scale gamma_for(m), which
 // puts m into [16, 32).  The workgroup keeps the smallest scale any of its tiles has asked for and,

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
       float lo, hi;
       float dmax = __builtin_bit_cast(float, (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16);
       pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
-      const float stok = pow2_normaliser(dmax);
+      const float stok = pow2_normaliser(fminf(dmax, kTokenMax));
       // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
       // common scale gamma and push every other token's operand into the fp16 subnormals
       auto any2 = __builtin_amdgcn_permlane32_swap(any, any, false, false);
