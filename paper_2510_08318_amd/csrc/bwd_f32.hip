@@ -112,7 +112,8 @@ constexpr size_t grad_smem() {
 
 // 8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks (a lane pair owns a token).
 // QSIDE: x = q, y = dO, M = (S, z); leaves the weights of the sum over tokens, {om / den, -om delta / den}, in weights[bh][t] and
-// (BLEND) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.
+// (BLEND, dr_part not null) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.  s is read for
+// that alone.
 // Key side: x = k, y = v, M = (dS, dz).  du_ws (nullable): dL/du rows for dW~.
 template <int D, int KIND, typename T, bool QSIDE, bool BLEND>
 __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
@@ -168,15 +169,23 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
     yr.load(row_of(yb, b), g);
     float ds = 0.f;                                                // dO . s on the lane's channels, while few registers are live
     if constexpr (BLEND) {
-      RowOctets<D, T> sr;
-      sr.load(row_of(bb, b), g);
+      if (dr_part != nullptr) {
+        // two octets at a time: a third row beside those of x and y does not fit the registers
+        const T* srow = row_of(bb, b);
+        RowOctets<D, T> sr;
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        float a[8], s8[8];
-        yr.values(ks, a);
-        sr.values(ks, s8);
+        for (int k0 = 0; k0 < D / 16; k0 += 2) {
+          sr.load(srow, g, k0, k0 + 2);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ds = fmaf(a[e], s8[e], ds);
+          for (int ks = k0; ks < k0 + 2; ++ks) {
+            float a[8], s8[8];
+            yr.values(ks, a);
+            sr.values(ks, s8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ds = fmaf(a[e], s8[e], ds);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
     float f[D / 2];
@@ -312,11 +321,11 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
         float* du = du_ws != nullptr ? du_ws + ((size_t)bh * n + b * 32) * C::HALF + 4 * tt : nullptr;
         Plain<D, KIND, T>::template grad<QSIDE, BLEND>(xb + at, yb + at, wx + (size_t)h * D * C::HALF, sb, dxb + at, du,
                                                        n - b * 32 < 32 ? n - b * 32 : 32, QSIDE ? weights + (size_t)bh * n + t : nullptr,
-                                                       BLEND ? bb + at : nullptr, om, &dr, lane);
+                                                       BLEND && dr_part != nullptr ? bb + at : nullptr, om, &dr, lane);
       }
     if (lane == 0) dr_acc = dr;
   }
-  if constexpr (BLEND) {
+  if (BLEND && dr_part != nullptr) {
     for (int m = 32; m >= 1; m >>= 1) dr_acc += __shfl_xor(dr_acc, m, 64);
     if (lane == 0) sRed[w] = dr_acc;
     __syncthreads();
@@ -481,7 +490,7 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
     decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, du, weights,
-                                                    (const T*)a.blend_in, a.blend_r, a.dr_part, p.H, p.n, p.rows);
+                                                    (const T*)a.blend_in, a.blend_r, a.blend_dr ? a.dr_part : nullptr, p.H, p.n, p.rows);
     return hipGetLastError();
   };
   float* du_q = a.dwq ? a.du_q : nullptr;

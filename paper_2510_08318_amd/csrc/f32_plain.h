@@ -87,7 +87,7 @@ struct Plain {
     }
   }
 
-  // One token of grad_f32_kernel.  QSIDE: *wt receives its weights, *dr its part of dL/dr.  du: element (feature a) of the token's dL/du
+  // One token of grad_f32_kernel.  QSIDE: *wt receives its weights, *dr (blend not null) its part of dL/dr.  du: element (feature a) of the token's dL/du
   // is du[(a's piece) * du_stride + a % 4], see dw_f32_kernel; nullable.
   template <bool QSIDE, bool BLEND>
   static __device__ __forceinline__ void grad(const T* xrow, const T* yrow, const T* w, const float* state, T* dx, float* du_tok, int nb,
@@ -109,7 +109,7 @@ struct Plain {
 #pragma unroll
       for (int j = 0; j < L; ++j) {
         part = fmaf(ldf(yrow, lane + 64 * j), o[j] * inv, part);
-        if constexpr (BLEND) ds = fmaf(ldf(yrow, lane + 64 * j), ldf(blend, lane + 64 * j), ds);
+        if (BLEND && blend != nullptr) ds = fmaf(ldf(yrow, lane + 64 * j), ldf(blend, lane + 64 * j), ds);
       }
       const float delta = wave_sum(part);
       if constexpr (BLEND) *dr += wave_sum(ds) - delta;

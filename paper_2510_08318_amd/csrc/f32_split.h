@@ -84,10 +84,11 @@ struct RowOctets {
   static constexpr int NU = sizeof(T) / 2;       // 16-byte words per octet
   uint4 r[D / 16 * NU];
   template <int LO = 0, int HI = D / 16>
-  __device__ __forceinline__ void load(const T* row, int g) {
+  __device__ __forceinline__ void load(const T* row, int g) { load(row, g, LO, HI); }
+  __device__ __forceinline__ void load(const T* row, int g, int lo, int hi) {        // constants after inlining
     const uint4* p = reinterpret_cast<const uint4*>(row);
 #pragma unroll
-    for (int ks = LO; ks < HI; ++ks)
+    for (int ks = lo; ks < hi; ++ks)
 #pragma unroll
       for (int i = 0; i < NU; ++i) r[ks * NU + i] = p[(2 * ks + g) * NU + i];
   }
@@ -112,7 +113,8 @@ __device__ __forceinline__ constexpr int phi_feature(int ks, int g) {
 }
 
 // W~ of one head (D x D/2, stored as T) -> pieces of the A operands of U^T = W~^T X^T in LDS, entry (ks, mb, lane = (m, g)) of
-// a piece as in w_image_entry.  A thread reads four adjacent features of eight channels at a time.
+// a piece holds
+// W~[16ks + 8g + e][owned_row<D/2>(mb, m)], e = 0..7.  A thread reads four adjacent features of eight channels at a time.
 template <int D, typename T, int NTHREADS>
 __device__ __forceinline__ void build_w_pieces(const T* __restrict__ w, uint4* sW, int tid) {
   using C = Cfg<D>;

@@ -97,6 +97,29 @@ def test_wavefronts_of_several_blocks(n, H, d, layout, dtype, kind):
     assert abs(float(got["dr"][0]) - grads[6]) <= 1e-5 * scale
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_mixed_backward_reads_s_for_the_mixing_gradient_alone(d, dtype):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    x = synth.generate("C5", n=500, H=2, d=d, dtype=dtype)
+    q, k, v, do = [G.to_device(t) for t in (x.q, x.k, x.v, x.dout)]
+    s, r, dr = torch.randn_like(q) * 0.1, torch.tensor([0.37], device="cuda"), torch.zeros(1, device="cuda")
+    grads = []
+    for want in (True, False):
+        lay = G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n, want_wgrads=True, f32_math=dtype == "bf16")
+        lay.set_blend(s, r, dr if want else None)
+        lay.forward(q, k, v)
+        if not want:
+            s.fill_(float("nan"))
+        grads.append([t.clone() for t in lay.backward(q, k, v, do)] + [lay.dwq.clone(), lay.dwk.clone()])
+        torch.cuda.synchronize()
+        lay.close()
+    assert torch.isfinite(dr).all()
+    for a, b in zip(*grads):
+        assert torch.equal(a, b) and torch.isfinite(a).all()
+
+
 def test_long_sum_has_no_common_error():
     """The matrix instruction cuts the low end of a step's sum, always downwards; tiles summed with alternating sign keep that
     out of S.  Errors that are independent over the 128 features leave REL / sqrt(128) in their mean; the bias of 300 tiles
