@@ -218,7 +218,9 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
     // a y that does not split makes every feature of its token NaN or Inf, phi from an x that does not is NaN: one value tells
     // (Hedgehog: the sums of the Jacobian, below)
     if constexpr (KIND == kPhiRelu) chk = fmaf(ga[0][0][0], 0.f, chk);
-    float gr[D / 2];
+    // dL/dphi / gscale.  The factor om / den of the query side is applied to du: fewer products, and the gr that the sums of the Jacobian take
+    // is the one they are subtracted from (a product fused into that subtraction is not), so that a saturated token's du is zero.
+    float gr[D / 2], gscale = 1.f;
     if constexpr (QSIDE) {
       float part = 0.f;
 #pragma unroll
@@ -238,8 +240,9 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int i = 8 * ks + e;
-          gr[i] = (ga[i / 16][0][i % 16] - delta * z[(2 * ks + g) * 8 + e]) * a;
+          gr[i] = ga[i / 16][0][i % 16] - delta * z[(2 * ks + g) * 8 + e];
         }
+      gscale = a;
     } else {
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks)
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
         for (int ks = 0; ks < D / 16; ++ks) {
           float v[8];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] > 0.f ? gr[8 * ks + e] : 0.f;
+          for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] > 0.f ? (QSIDE ? gr[8 * ks + e] * gscale : gr[8 * ks + e]) : 0.f;
           uint4* dst = reinterpret_cast<uint4*>(row + 16 * ks + 8 * g);
           if constexpr (sizeof(T) == 2) {
             *dst = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
@@ -282,7 +285,10 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
       chk = fmaf(cp + cm, 0.f, chk);
       float du[C::LOC];
 #pragma unroll
-      for (int j = 0; j < C::LOC; ++j) du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
+      for (int j = 0; j < C::LOC; ++j) {
+        du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
+        if constexpr (QSIDE) du[j] *= gscale;
+      }
       if (du_ws != nullptr && valid) {
         // blocks of 32 tokens as the lanes hold them, 1 KB a store (see dw_f32_kernel)
         float4* dst = reinterpret_cast<float4*>(du_ws + ((size_t)bh * n + b * 32) * C::HALF);

@@ -1,6 +1,5 @@
 // The passes of the fp32-arithmetic modes in plain fp32 FMA, a wavefront to a token, for what the bf16 pieces of f32_split.h do not carry:
-// infinities (their pieces are Inf and NaN), finite values that round to Inf as bf16 (above 3.3895e38) and softmax arguments above
-// 2.3e38.  Each of these makes a product of pieces NaN or Inf, which the kernels notice on the accumulators, a few instructions a block;
+// infinities (their pieces are Inf and NaN) and finite values that round to Inf as bf16 (above 3.3895e38).  Each of these makes a product of pieces NaN or Inf, which the kernels notice on the accumulators, a few instructions a block;
 // they then run their share once more through here.  Results are those of IEEE fp32 arithmetic; 12 heads x 32760 x 128 of NaN take 4 ms
 // forward, 19 backward (0.3 and 0.9 without).
 #pragma once
@@ -93,7 +92,7 @@ struct Plain {
   static __device__ __forceinline__ void grad(const T* xrow, const T* yrow, const T* w, const float* state, T* dx, float* du_tok, int nb,
                                               float2* wt, const T* blend, float om, float* dr, int lane) {
     const float* z = state + D * D;
-    float f[L], g[L];
+    float f[L], g[L], gscale = 1.f;                                // dL/dphi / gscale
     phi(xrow, w, lane, f);
 #pragma unroll
     for (int j = 0; j < L; ++j) {
@@ -116,14 +115,15 @@ struct Plain {
       const float a = inv * om;
       if (lane == 0) *wt = make_float2(a, -delta * a);
 #pragma unroll
-      for (int j = 0; j < L; ++j) g[j] = (g[j] - delta * z[lane + 64 * j]) * a;
+      for (int j = 0; j < L; ++j) g[j] -= delta * z[lane + 64 * j];
+      gscale = a;
     } else {
 #pragma unroll
       for (int j = 0; j < L; ++j) g[j] += z[lane + 64 * j];
     }
     if constexpr (KIND == kPhiRelu) {
 #pragma unroll
-      for (int j = 0; j < L; ++j) stf(dx, lane + 64 * j, f[j] > 0.f ? g[j] : 0.f);
+      for (int j = 0; j < L; ++j) stf(dx, lane + 64 * j, f[j] > 0.f ? g[j] * gscale : 0.f);
     } else {
       float du;                                                    // of feature lane % HALF
       if constexpr (L == 2) {
@@ -135,6 +135,7 @@ struct Plain {
         const float d = f[0] * (g[0] - c), other = __shfl_xor(d, 32, 64);
         du = lane < HALF ? d - other : other - d;
       }
+      du *= gscale;
       if (du_tok != nullptr && lane < HALF) {
         const int grp = lane / (D / 4), j = lane % (D / 4) / 4;
         du_tok[(size_t)(2 * j + grp) * nb * 4 + lane % 4] = du;

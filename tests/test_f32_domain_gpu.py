@@ -169,6 +169,24 @@ def test_huge_gradient_rows(d):
         assert err <= 2e-5, (name, err)
 
 
+@pytest.mark.parametrize("side", ["q", "k"])
+@pytest.mark.parametrize("scale", [1e6, 1e30])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_saturated_maps_have_no_gradient(dtype, d, scale, side):
+    """The features of u are hundreds apart: phi is one feature of each half to the last bit (exp(-200) is zero in fp32), and the gradients of
+    that side are zero."""
+    x = _inputs(dtype, d)
+    setattr(x, side, synth._pack((O.to_f64(getattr(x, side)) * scale).astype(np.float32), dtype))
+    u = np.sort(O.to_f64(getattr(x, side)) @ O.to_f64(getattr(x, "w" + side))[None], axis=-1)
+    assert min((u[..., 1] - u[..., 0]).min(), (u[..., -1] - u[..., -2]).min()) > 200
+    got = _run(x, False)
+    ref = dict(zip(("dq", "dk", "dv", "dwq", "dwk"), O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)))
+    for name in ("d" + side, "dw" + side):
+        assert np.abs(ref[name]).max() < 1e-50 and not got[name].any(), name
+    for name in ("dq", "dk", "dv"):
+        assert np.abs(got[name] - ref[name]).max() <= BARS[dtype] * max(np.abs(ref[name]).max(), 1e-50), name
+
+
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -10], ids=["huge", "large"])
 def test_gradient_whose_products_with_the_state_overflow(scale):
     """dO S^T leaves the range in some features while dO . o, and with it dz and what dk gets from it, does not: Inf in those features of
