@@ -35,7 +35,9 @@
  *     matrix cores as fp16 (11-bit significand) with fp32 accumulation.  phi, the states, dout and
  *     every gradient operand are rescaled by exact powers of two first (per token, per 32-token
  *     block, per head, or per workgroup following the running maximum), so their magnitude does
- *     not matter: any finite bf16 q, k, dout is in the domain.
+ *     not matter: any finite bf16 dout is in the domain, and any finite q, k with |x W~| below 2^26 (the
+ *     exponent of the softmax, u log2 e minus its maximum, is rounded once at that magnitude; the
+ *     fp32-arithmetic modes take the difference first and have no such limit).
  *   - v is widened to fp16 unscaled: |v| must be below 65504 (fp16's largest finite value).  Larger
  *     entries become infinite inside the kernels and the call returns LINATTN_OK with Inf/NaN in
  *     out, state and the gradients; the library does not scan for them.  Entries with
