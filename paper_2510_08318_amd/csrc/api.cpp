@@ -29,21 +29,13 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   if (P > tiles) P = tiles;
   int tiles_per = (tiles + P - 1) / P;
   r.P = (tiles + tiles_per - 1) / tiles_per;
-  {
-    // query pass of the bf16 kernels: 12-wavefront workgroups, one per compute unit, 32-token blocks dealt round-robin
-    const int nblk = (n + 31) / 32;
-    int QP = kCUs / (int)BH;
-    if (QP < 1) QP = 1;
-    if (QP > (nblk + 11) / 12) QP = (nblk + 11) / 12;
-    r.QP = QP;
-  }
   r.state_elems = (size_t)(d + 1) * d;
   {
     Split sp{};
     sp.ntile = tiles;
     sp.T = (long long)BH * tiles;
     sp.G = BH > kSlots ? (int)BH : (int)(sp.T < kSlots ? sp.T : kSlots);
-    sp.small = sp.T * sp.G < (1LL << 31);
+    finish_split(sp);
     sp.PS = 1;
     for (long long bh = 0; bh < BH; ++bh) {
       const int cnt = split_owner(sp, (bh + 1) * tiles - 1) - split_owner(sp, bh * tiles) + 1;

@@ -21,8 +21,8 @@ namespace linattn {
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// Query pass.  A wavefront owns 32-token blocks b = p*NW + w, stepping by (gridDim.x * NW), so
-// the workgroups of a head sweep its tokens together.  Per block: load Q rows straight into the
+// Query pass.  Units of NW 32-token blocks, one to a wavefront, are dealt to one workgroup per compute unit (make_deal), and
+// the workgroups of a head sweep its tokens together (next_share).  Per block: load Q rows straight into the
 // B operand of the projection (a lane owns a token), phi; phi then is the A operand of
 // out = phi S, which puts the tokens on the accumulator rows and the channels on the lanes: a lane
 // holds MB adjacent channels of 16 tokens and every store instruction writes two whole rows.  One
@@ -40,7 +40,12 @@ __device__ __forceinline__ void st_nt(uint2* p, uint2 v) {
 }
 __device__ __forceinline__ void st_nt(uint32_t* p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 
-constexpr int NT3 = 768;         // 12 wavefronts, one workgroup per compute unit
+// Wavefronts of a workgroup of the query pass, one workgroup per compute unit.  With 8 a unit is small enough for an even deal and a lane
+// has up to 256 registers (with 12, 168: the blend at width 128 spilled).  12 with per-head shares / 8 dealt evenly, us: 12 heads x 32760 x
+// 128 52.0 / 49.5, with blend 84.7 / 77.2, ReLU 56.9 / 53.9; 40 x 75600 x 128 326 / 327; 12 x 8190 x 128 16.8 / 17.2; 30 x 17550 x 64 31.2 /
+// 30.6; 12 x 4133 x 64 8.6 / 7.6.  The blend at width 64 needs 131 registers either way and is no faster with 8 (26 x 2222 x 64 9.8 / 10.1, 7 x
+// 20000 x 64 13.9 / 14.3).
+constexpr int apply_waves(int d, bool blend) { return d == 64 && blend ? 12 : 8; }
 
 // The state of head bh as the sum of its workgroups' partials, pairwise, to sum[(D+1)*D/4] in LDS and, if given, to dst.  16 loads of
 // a thread are in flight; those of a missing slot repeat the last one's and count as zero (branch-free).
@@ -88,9 +93,8 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
 }
 
 // The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
-// us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 (the workgroup fills three of a
-// SIMD's wavefront slots whatever it is) keeps the loop's schedule from spreading into the prologue's registers: without it the
-// CogVideoX-2B shape loses 2 us.
+// us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 keeps the loop's schedule from spreading
+// into the prologue's registers: without it the CogVideoX-2B shape loses 2 us.
 // BLEND: mixed attention (Sec. 4.1, Eq. 6): out = r' s + (1 - r') o with the softmax-branch output
 // s read in the same pieces as out is stored, and r' = clip(*rptr, 0, 1).
 // KIND = kPhiRelu: phi(q) = max(q, 0) straight from the loaded rows (no projection, no W~), features
@@ -98,14 +102,14 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
 // SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
 // sum_in_apply); the first workgroup of a head writes it to `state`.
 template <int D, bool BLEND, int KIND, bool SUM>
-__global__ __launch_bounds__(NT3, D == 64 && !SUM ? (BLEND ? 4 : 5) : 3) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+__global__ __launch_bounds__(64 * apply_waves(D, BLEND), D == 64 ? (BLEND ? 3 : 4) : 2) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ partials, float* __restrict__ state,
                                                          uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
-                                                         int H, int n, Split sp, Rows rw) {
+                                                         int H, int n, Split deal, Split sp, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
-  constexpr int NW = NT3 / 64;
+  constexpr int NW = apply_waves(D, BLEND), NT3 = 64 * NW;
   constexpr int SA_IMG = L::KS * L::MBZ * 64;
   constexpr int HB = L::MB / 2;             // channel column blocks per accumulation pass (two passes)
   using Piece = typename RowPiece<L::MB>::type;   // a lane's MB adjacent bf16 channels of one token
@@ -117,162 +121,165 @@ __global__ __launch_bounds__(NT3, D == 64 && !SUM ? (BLEND ? 4 : 5) : 3) void ap
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 32;
-  const int bh = blockIdx.y, h = bh % H;
-  const uint16_t* qb = q + head_base(rw, bh, H);
-  uint16_t* ob = out + head_base(rw, bh, H);
-  const uint16_t* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
-  const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
+  for (Share sh = first_share(deal, blockIdx.x, blockIdx.y); sh.there; sh = next_share(deal, blockIdx.x, sh)) {
+    const int bh = sh.bh, h = bh % H;
+    const uint16_t* qb = q + head_base(rw, bh, H);
+    uint16_t* ob = out + head_base(rw, bh, H);
+    const uint16_t* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+    const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
 
-  const int nblk = (n + 31) / 32;
-  const int stride = gridDim.x * NW;
-  const int c = lane % 32;
-  const uint32_t lane_off = ((uint32_t)(4 * g) * (uint32_t)rw.sn + (uint32_t)(L::MB * c)) * 2u;   // bytes
+    const int nblk = (n + 31) / 32 < sh.end * NW ? (n + 31) / 32 : sh.end * NW;
+    const int stride = sh.step * NW;
+    const int c = lane % 32;
+    const uint32_t lane_off = ((uint32_t)(4 * g) * (uint32_t)rw.sn + (uint32_t)(L::MB * c)) * 2u;   // bytes
 
-  uint4 x[C::UK];
-  auto load_block = [&](int b) {
-    const int t = b * 32 + (lane % 32);
-    const int tc = t < n ? t : (n - 1);
-    const uint4* row = reinterpret_cast<const uint4*>(qb + (size_t)tc * rw.sn);
+    uint4 x[C::UK];
+    auto load_block = [&](int b) {
+      const int t = b * 32 + (lane % 32);
+      const int tc = t < n ? t : (n - 1);
+      const uint4* row = reinterpret_cast<const uint4*>(qb + (size_t)tc * rw.sn);
 #pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
-  };
-  // the first block's rows are requested before the prologue, so that they arrive under it
-  int b = blockIdx.x * NW + w;
-  if (b < nblk) load_block(b);
+      for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
+    };
+    // the first block's rows are requested before the prologue, so that they arrive under it
+    int b = sh.u * NW + w;
+    if (b < nblk) load_block(b);
 
-  float scale;
-  {
-    using R = StateRegs<D, NT3>;
-    float* sb = state + (size_t)bh * (D + 1) * D;
-    float* sZ = reinterpret_cast<float*>(sStage);
-    R S;
-    float zv;
-    if constexpr (SUM) {
-      float4* sSum = reinterpret_cast<float4*>(sZ + D + 64);
-      sum_slots<D, NT3>(partials, sSum, blockIdx.x == 0 ? reinterpret_cast<float4*>(sb) : nullptr, sp, bh, tid);
-      __syncthreads();
-      const float* sum = reinterpret_cast<const float*>(sSum);
-      S.load(sum, tid);
-      zv = tid < D ? sum[D * D + tid] : 0.f;
-    } else {
-      S.load(sb, tid);
-      zv = tid < D ? sb[D * D + tid] : 0.f;
-    }
-    if (tid < D) sZ[tid] = zv;
-    if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
-    scale = S.scale(sZ + D, tid, fabsf(zv));            // (its barrier covers z as well)
-    S.template write_apply_image<L::MBZ, KIND>(sSA, scale);
-    R::template write_z_block<KIND>(sZ, sSA, scale, tid);
-  }
-  __syncthreads();
-  const float den_eps = KIND == kPhiRelu ? scale * kReluEps : 0.f;    // the image carries scale * z
-
-  for (; b < nblk; b += stride) {
-    uint32_t pk[C::NPK];
-    if constexpr (KIND == kPhiRelu) {
-      static_assert(C::NPK == 4 * C::UK, "one 16-byte piece of phi per piece of the row");
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
-        const uint4 f = relu_f16x8(x[ks]);
-        pk[4 * ks] = f.x; pk[4 * ks + 1] = f.y; pk[4 * ks + 2] = f.z; pk[4 * ks + 3] = f.w;
+    float scale;
+    {
+      using R = StateRegs<D, NT3>;
+      float* sb = state + (size_t)bh * (D + 1) * D;
+      float* sZ = reinterpret_cast<float*>(sStage);
+      R S;
+      float zv;
+      if constexpr (SUM) {
+        float4* sSum = reinterpret_cast<float4*>(sZ + D + 64);
+        sum_slots<D, NT3>(partials, sSum, sh.u == 0 ? reinterpret_cast<float4*>(sb) : nullptr, sp, bh, tid);
+        __syncthreads();
+        const float* sum = reinterpret_cast<const float*>(sSum);
+        S.load(sum, tid);
+        zv = tid < D ? sum[D * D + tid] : 0.f;
+      } else {
+        S.load(sb, tid);
+        zv = tid < D ? sb[D * D + tid] : 0.f;
       }
-      if constexpr (!BLEND) load_block(b + stride < nblk ? b + stride : b);
-    } else {
-      f32x16 u[C::UM];
-      project<D>(x, sWA, lane, u);
-      // next block's rows fly during the rest of this one (BLEND: the pieces of s take their
-      // registers, so each 16-byte piece of the next rows is requested in the second pass as the
-      // k-step that frees a piece of phi has been issued)
-      if constexpr (!BLEND) load_block(b + stride < nblk ? b + stride : b);
-      softmax_pair_ratio<D>(u, pk);
+      if (tid < D) sZ[tid] = zv;
+      if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
+      scale = S.scale(sZ + D, tid, fabsf(zv));            // (its barrier covers z as well)
+      S.template write_apply_image<L::MBZ, KIND>(sSA, scale);
+      R::template write_z_block<KIND>(sZ, sSA, scale, tid);
     }
-    // register r of an accumulator is token b*32 + 8*(r/4) + 4g + r%4; the lane's MB channels of it
-    // are MB*c .. MB*c + MB-1, two bytes each
-    const bool full = b * 32 + 32 <= n;
-    Piece sv[BLEND ? 16 : 1];               // the same pieces of the softmax branch
-    if constexpr (BLEND) {
-      const char* sb = reinterpret_cast<const char*>(bb + (size_t)(b * 32) * rw.sn) + lane_off;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r / 4) + (r % 4);
-        const bool there = full || b * 32 + row + 4 * g < n;
-        sv[r] = there ? *reinterpret_cast<const Piece*>(sb + (size_t)row * rw.sn * 2) : Piece{};
-      }
-    }
+    __syncthreads();
+    const float den_eps = KIND == kPhiRelu ? scale * kReluEps : 0.f;    // the image carries scale * z
 
-    const uint4* next_row = nullptr;
-    if constexpr (BLEND) {
-      const int bn = b + stride < nblk ? b + stride : b;
-      const int t = bn * 32 + (lane % 32);
-      next_row = reinterpret_cast<const uint4*>(qb + (size_t)(t < n ? t : n - 1) * rw.sn);
-    }
-    // out = phi S in two passes over the lane's channels; the first also carries the block whose
-    // every column is z, so each lane gets the normalisers of its 16 tokens
-    const uint4* ssa = sSA + lane + opaque_zero();
-    float inv[16], keep[16];
-    Piece word[16];
+    for (; b < nblk; b += stride) {
+      uint32_t pk[C::NPK];
+      if constexpr (KIND == kPhiRelu) {
+        static_assert(C::NPK == 4 * C::UK, "one 16-byte piece of phi per piece of the row");
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      f32x16 o[HB], dn;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        dn[r] = 0.f;
-#pragma unroll
-        for (int i = 0; i < HB; ++i) o[i][r] = 0.f;
+        for (int ks = 0; ks < C::UK; ++ks) {
+          const uint4 f = relu_f16x8(x[ks]);
+          pk[4 * ks] = f.x; pk[4 * ks + 1] = f.y; pk[4 * ks + 2] = f.z; pk[4 * ks + 3] = f.w;
+        }
+        if constexpr (!BLEND) load_block(b + stride < nblk ? b + stride : b);
+      } else {
+        f32x16 u[C::UM];
+        project<D>(x, sWA, lane, u);
+        // next block's rows fly during the rest of this one (BLEND: the pieces of s take their
+        // registers, so each 16-byte piece of the next rows is requested in the second pass as the
+        // k-step that frees a piece of phi has been issued)
+        if constexpr (!BLEND) load_block(b + stride < nblk ? b + stride : b);
+        softmax_pair_ratio<D>(u, pk);
       }
+      // register r of an accumulator is token b*32 + 8*(r/4) + 4g + r%4; the lane's MB channels of it
+      // are MB*c .. MB*c + MB-1, two bytes each
+      const bool full = b * 32 + 32 <= n;
+      Piece sv[BLEND ? 16 : 1];               // the same pieces of the softmax branch
+      if constexpr (BLEND) {
+        const char* sb = reinterpret_cast<const char*>(bb + (size_t)(b * 32) * rw.sn) + lane_off;
 #pragma unroll
-      for (int ks = 0; ks < L::KS; ++ks) {
-        uint4 aq; aq.x = pk[4 * ks]; aq.y = pk[4 * ks + 1]; aq.z = pk[4 * ks + 2]; aq.w = pk[4 * ks + 3];
-        const f16x8 aop = as_f16x8(aq);
-#pragma unroll
-        for (int i = 0; i < HB; ++i)
-          o[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(ssa[(ks * L::MBZ + pass * HB + i) * 64]), o[i], 0, 0, 0);
-        if (pass == 0) dn = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(ssa[(ks * L::MBZ + L::MB) * 64]), dn, 0, 0, 0);
-        if constexpr (BLEND) {
-          static_assert(C::UK == L::KS, "one piece of x per k-step");
-          if (pass == 1) x[ks] = next_row[2 * ks + g];
+        for (int r = 0; r < 16; ++r) {
+          const int row = 8 * (r / 4) + (r % 4);
+          const bool there = full || b * 32 + row + 4 * g < n;
+          sv[r] = there ? *reinterpret_cast<const Piece*>(sb + (size_t)row * rw.sn * 2) : Piece{};
         }
       }
-      if (pass == 0) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) inv[r] = __builtin_amdgcn_rcpf(KIND == kPhiRelu ? dn[r] + den_eps : dn[r]);
+
+      const uint4* next_row = nullptr;
+      if constexpr (BLEND) {
+        const int bn = b + stride < nblk ? b + stride : b;
+        const int t = bn * 32 + (lane % 32);
+        next_row = reinterpret_cast<const uint4*>(qb + (size_t)(t < n ? t : n - 1) * rw.sn);
       }
+      // out = phi S in two passes over the lane's channels; the first also carries the block whose
+      // every column is z, so each lane gets the normalisers of its 16 tokens
+      const uint4* ssa = sSA + lane + opaque_zero();
+      float inv[16], keep[16];
+      Piece word[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float y[HB];
+      for (int pass = 0; pass < 2; ++pass) {
+        f32x16 o[HB], dn;
 #pragma unroll
-        for (int i = 0; i < HB; ++i) {
-          y[i] = o[i][r] * inv[r];
+        for (int r = 0; r < 16; ++r) {
+          dn[r] = 0.f;
+#pragma unroll
+          for (int i = 0; i < HB; ++i) o[i][r] = 0.f;
+        }
+#pragma unroll
+        for (int ks = 0; ks < L::KS; ++ks) {
+          uint4 aq; aq.x = pk[4 * ks]; aq.y = pk[4 * ks + 1]; aq.z = pk[4 * ks + 2]; aq.w = pk[4 * ks + 3];
+          const f16x8 aop = as_f16x8(aq);
+#pragma unroll
+          for (int i = 0; i < HB; ++i)
+            o[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(ssa[(ks * L::MBZ + pass * HB + i) * 64]), o[i], 0, 0, 0);
+          if (pass == 0) dn = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(ssa[(ks * L::MBZ + L::MB) * 64]), dn, 0, 0, 0);
           if constexpr (BLEND) {
-            const int ch = pass * HB + i;                         // which of the lane's MB channels
-            const uint32_t sw = piece_word(sv[r], ch / 2);
-            const float sf = (ch % 2) ? __builtin_bit_cast(float, sw & 0xffff0000u) : __builtin_bit_cast(float, sw << 16);
-            y[i] = fmaf(rb, sf - y[i], y[i]);
+            static_assert(C::UK == L::KS, "one piece of x per k-step");
+            if (pass == 1) x[ks] = next_row[2 * ks + g];
           }
         }
-        if constexpr (HB == 2) {
-          set_piece_word(word[r], pass, pack_bf16x2(y[0], y[1]));
-        } else {
-          if (pass == 0) keep[r] = y[0];
-          else set_piece_word(word[r], 0, pack_bf16x2(keep[r], y[0]));
+        if (pass == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) inv[r] = __builtin_amdgcn_rcpf(KIND == kPhiRelu ? dn[r] + den_eps : dn[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float y[HB];
+#pragma unroll
+          for (int i = 0; i < HB; ++i) {
+            y[i] = o[i][r] * inv[r];
+            if constexpr (BLEND) {
+              const int ch = pass * HB + i;                         // which of the lane's MB channels
+              const uint32_t sw = piece_word(sv[r], ch / 2);
+              const float sf = (ch % 2) ? __builtin_bit_cast(float, sw & 0xffff0000u) : __builtin_bit_cast(float, sw << 16);
+              y[i] = fmaf(rb, sf - y[i], y[i]);
+            }
+          }
+          if constexpr (HB == 2) {
+            set_piece_word(word[r], pass, pack_bf16x2(y[0], y[1]));
+          } else {
+            if (pass == 0) keep[r] = y[0];
+            else set_piece_word(word[r], 0, pack_bf16x2(keep[r], y[0]));
+          }
+        }
+      }
+      {
+        // Every store instruction writes two whole rows.  The stores are non-temporal: with ordinary
+        // stores the tail of out stays dirty in the last-level cache and is written back under
+        // whatever kernel runs next (measured: the next call's state pass loses 30 us, this pass
+        // gains 20 us)
+        // No branch around any of them: rows past n go to a sink instead (a select), see store_token_rows.
+        char* ub = reinterpret_cast<char*>(ob + (size_t)(b * 32) * rw.sn) + lane_off;
+        char* sink = reinterpret_cast<char*>(g_store_sink) + lane * 8;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = 8 * (r / 4) + (r % 4);
+          const bool there = full || b * 32 + row + 4 * g < n;
+          st_nt(reinterpret_cast<Piece*>(there ? ub + (size_t)row * rw.sn * 2 : sink), word[r]);
         }
       }
     }
-    {
-      // Every store instruction writes two whole rows.  The stores are non-temporal: with ordinary
-      // stores the tail of out stays dirty in the last-level cache and is written back under
-      // whatever kernel runs next (measured: the next call's state pass loses 30 us, this pass
-      // gains 20 us)
-      // No branch around any of them: rows past n go to a sink instead (a select), see store_token_rows.
-      char* ub = reinterpret_cast<char*>(ob + (size_t)(b * 32) * rw.sn) + lane_off;
-      char* sink = reinterpret_cast<char*>(g_store_sink) + lane * 8;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r / 4) + (r % 4);
-        const bool there = full || b * 32 + row + 4 * g < n;
-        st_nt(reinterpret_cast<Piece*>(there ? ub + (size_t)row * rw.sn * 2 : sink), word[r]);
-      }
-    }
+    if (sh.rest < sh.hi) __syncthreads();                // the next head's images take the place of these
   }
 }
 
@@ -608,14 +615,18 @@ hipError_t launch_state_partials_bf16(const void* k, const void* v, const void* 
 
 namespace {
 
+// The prologue of the query pass in eighths of a unit: 3 to 4 us against 8 at 12 heads x 32760 x 128.
+constexpr int kApplyPrologue = 3;
 template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   hipError_t e;
   constexpr size_t smem = apply_smem<D>(SUM);
   if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM>>(smem)) != hipSuccess) return e;
-  apply_bf16_kernel<D, BLEND, KIND, SUM><<<dim3(p.QP, p.BH), NT3, smem, s>>>(
-      (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, p.split, p.rows);
+  constexpr int NW = apply_waves(D, BLEND);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NW - 1) / NW, kApplyPrologue);
+  apply_bf16_kernel<D, BLEND, KIND, SUM><<<grid_of(deal), 64 * NW, smem, s>>>(
+      (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, deal, p.split, p.rows);
   return hipGetLastError();
 }
 

@@ -43,25 +43,108 @@ struct Split {
   int ntile;        // tiles per (b,h)
   long long T;      // tiles in all
   int PS;           // partial slots per (b,h) (the largest number of workgroups touching one head)
-  bool small;       // T * G < 2^31: the index arithmetic fits 32 bits (a 64-bit division is a hundred dependent instructions, in
-                    // the prologue of every workgroup)
+  // The index arithmetic runs in the prologue of every workgroup.  It has no division: as 64-bit divisions (a hundred dependent
+  // instructions each, thousands with their copies, which the instruction cache has to bring in) it took 0.5 us of a state pass and
+  // 1.3 us of a kernel that calls next_share.
+  int share;        // not 0: G = B*H*share and no workgroup has tiles of two heads (next_share)
+  int quot, rem;    // T / G, T % G
+  float inv_G, per_T, inv_ntile;      // 1 / G, G / T, 1 / ntile
 };
-// a * b / c, all positive
-__host__ __device__ inline long long split_muldiv(const Split& s, long long a, long long b, long long c) {
-  if (s.small) return (long long)((unsigned)a * (unsigned)b / (unsigned)c);
-  return a * b / c;
+inline void finish_split(Split& s) {
+  s.quot = (int)(s.T / s.G); s.rem = (int)(s.T % s.G);
+  s.inv_G = 1.0f / (float)s.G; s.per_T = (float)s.G / (float)s.T; s.inv_ntile = 1.0f / (float)s.ntile;
 }
-__host__ __device__ inline long long split_lo(const Split& s, int g) { return split_muldiv(s, g, s.T, s.G); }
-// the head that tile x belongs to
+// floor(g T / G).  The quotient of g * rem (below 2^18: rem is 0 where G exceeds 512) is estimated in fp32 to within one and corrected.
+__host__ __device__ inline long long split_lo(const Split& s, int g) {
+  const int x = g * s.rem;
+  int q = (int)((float)x * s.inv_G);
+  if (q * s.G > x) --q;
+  if ((q + 1) * s.G <= x) ++q;
+  return (long long)g * s.quot + q;
+}
+// the head that tile x belongs to (the estimate is off by at most one: at most 65535 heads)
 __host__ __device__ inline int split_head(const Split& s, long long x) {
-  return s.small ? (int)((unsigned)x / (unsigned)s.ntile) : (int)(x / s.ntile);
+  int h = (int)((float)x * s.inv_ntile);
+  if ((long long)h * s.ntile > x) --h;
+  if ((long long)(h + 1) * s.ntile <= x) ++h;
+  return h;
 }
 // the workgroup whose range holds tile x
 __host__ __device__ inline int split_owner(const Split& s, long long x) {
-  int g = (int)split_muldiv(s, x, s.G, s.T);
-  while (g + 1 < s.G && split_lo(s, g + 1) <= x) ++g;
-  while (g > 0 && split_lo(s, g) > x) --g;
+  int g = (int)((float)x * s.per_T);
+  g = g < s.G ? g : s.G - 1;
+  if (split_lo(s, g) > x) --g;
+  if (g + 1 < s.G && split_lo(s, g + 1) <= x) ++g;
   return g;
+}
+
+// A workgroup's share of one head: units u, u + step, .. below end (head-relative).  The workgroups that have units of this head
+// alone take them in turn, so that they sweep the head together (in one piece each, the query pass of 40 heads x 75600 x 128 took 340
+// us where it takes 327); those at its ends, which have units of two heads, take theirs in one piece.
+// for (Share sh = first_share(s, blockIdx.x, blockIdx.y); sh.there; sh = next_share(s, blockIdx.x, sh)) visits the one or two shares of
+// a workgroup.
+struct Share {
+  bool there;
+  int bh, u, step, end;
+  long long rest, hi;      // the workgroup's tiles beyond this share
+};
+__host__ __device__ inline Share next_share(const Split& s, int g, const Share& prev) {
+  Share r = prev;
+  r.there = prev.rest < prev.hi;
+  if (!r.there) return r;
+  const long long lo = prev.rest, hi = prev.hi;
+  r.bh = split_head(s, lo);
+  const long long head0 = (long long)r.bh * s.ntile, head1 = head0 + s.ntile;
+  if (hi <= head1 && lo == split_lo(s, g)) {
+    int g0 = split_owner(s, head0), g1 = split_owner(s, head1 - 1);
+    if (split_lo(s, g0) < head0) ++g0;
+    if (split_lo(s, g1 + 1) > head1) --g1;
+    r.u = (int)(split_lo(s, g0) - head0) + (g - g0);
+    r.step = g1 - g0 + 1;
+    r.end = (int)(split_lo(s, g1 + 1) - head0);
+    r.rest = hi;
+  } else {
+    const long long stop = hi < head1 ? hi : head1;
+    r.u = (int)(lo - head0);
+    r.step = 1;
+    r.end = (int)(stop - head0);
+    r.rest = stop;
+  }
+  return r;
+}
+// gx, gy: the workgroup's place in the grid that grid_of(s) is.  (With one grid dimension, and the head divided out of it, a pass of 8 us takes 0.4
+// us longer.)
+__host__ __device__ inline Share first_share(const Split& s, int gx, int gy) {
+  Share r{};
+  if (s.share) {
+    r.there = true;
+    r.bh = gy; r.u = gx; r.step = s.share; r.end = s.ntile;
+    return r;
+  }
+  r.rest = split_lo(s, gx); r.hi = split_lo(s, gx + 1);
+  return next_share(s, gx, r);
+}
+inline dim3 grid_of(const Split& s) { return s.share ? dim3(s.share, s.G / s.share) : dim3(s.G); }
+
+// The deal of a kernel that builds a head's operand images in its prologue: `per_head` units of each head to at most kCUs workgroups,
+// either the same number of workgroups to every head (each then has one head) or the units of all heads evenly (a workgroup may
+// then have the end of one head and the start of the next, and builds images twice).  prologue8: what a prologue takes, in eighths
+// of a unit's time.
+inline Split make_deal(int BH, int per_head, int prologue8) {
+  Split s{};
+  s.ntile = per_head;
+  s.T = (long long)BH * per_head;
+  s.PS = 1;
+  s.share = kCUs / BH < per_head ? (BH < kCUs ? kCUs / BH : 1) : per_head;
+  s.G = BH * s.share;
+  if (BH < kCUs) {
+    const int even = s.T < kCUs ? (int)s.T : kCUs;
+    const long long cost_share = 8LL * ((per_head + s.share - 1) / s.share) + prologue8;
+    const long long cost_even = 8 * ((s.T + even - 1) / even) + 2 * prologue8;
+    if (cost_even < cost_share) { s.G = even; s.share = 0; }
+  }
+  finish_split(s);
+  return s;
 }
 
 // How one call is cut into workgroups and where its scratch regions sit in the workspace.
@@ -74,7 +157,6 @@ struct Plan {
   Rows rows;        // memory layout of the token tensors
   Split split;      // state passes (and the weighted one of the fp32-arithmetic backward)
   int P;            // split-n factor (partials per (b,h)) of the query-side backward and of dW~
-  int QP;           // workgroups per (b,h) of the bf16 query pass
   size_t state_elems;     // (d+1)*d
   size_t off_partials;    // fp32 [BH][max(P, split.PS)][(d+1)*d]
   size_t off_state;       // fp32 [BH][(d+1)*d]   (used when the caller gave no state buffer)

@@ -1,0 +1,78 @@
+"""Kernels whose workgroups take the end of one head and the start of the next (make_deal's even deal): a whole step in every mode at a
+number of heads that does not divide the compute units, with a ragged last unit.  129 heads of 600 tokens are 3 units of 8 blocks and 5
+tiles each: one workgroup a head would leave half of the compute units idle, so units are dealt evenly, 1 to 2 (2 to 3 tiles) a workgroup.
+
+Bars: 1e-2 element by element for bf16 results, 1e-5 for fp32 ones (2e-5 for their weight gradients, sums over all tokens)."""
+import functools
+
+import numpy as np
+import pytest
+
+from oracle import linattn_oracle as O
+from oracle import relu_oracle as R
+from paper_2510_08318_amd import synth
+
+pytestmark = pytest.mark.gpu
+REL_R = 0.37
+
+
+@functools.lru_cache(None)
+def _case(d, dtype):
+    return synth.generate("C5", n=600, H=43, B=3, d=d, dtype=dtype)
+
+
+def _softmax_branch(x):
+    return synth._pack((np.random.default_rng(x.d).standard_normal(x.q.shape) * 0.1).astype(np.float32), x.dtype)
+
+
+@functools.lru_cache(None)
+def _reference(d, dtype, form):
+    x = _case(d, dtype)
+    if form == "relu":
+        return (("out", R.relu_fwd_bh(x.q, x.k, x.v)), *zip(("dq", "dk", "dv"), R.relu_bwd_bh(x.q, x.k, x.v, x.dout)))
+    names = ("dq", "dk", "dv", "dwq", "dwk")
+    if form == "blend":
+        s = _softmax_branch(x)
+        *grads, _, dr = O.blend_bwd_bh(x.q, x.k, x.v, x.wq, x.wk, s, REL_R, x.dout)
+        return (("out", O.blend_fwd_bh(x.q, x.k, x.v, x.wq, x.wk, s, REL_R)), ("dr", dr), *zip(names, grads))
+    return (("out", O.fwd_bh(x.q, x.k, x.v, x.wq, x.wk)), *zip(names, O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)))
+
+
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("form", ["weight gradients", "frozen map", "blend", "centred", "relu"])
+@pytest.mark.parametrize("mode,d", [("bf16", 64), ("bf16", 128), ("f32math", 64), ("f32math", 128), ("f32", 64), ("f32", 128)])
+def test_step_with_heads_that_share_workgroups(mode, d, form, layout):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    if form == "centred" and mode != "bf16":
+        pytest.skip("the flag belongs to the bf16 mode")
+    if layout == "bnhd" and form in ("frozen map", "centred"):
+        pytest.skip("covered by the other forms")
+    relu, f32_math = form == "relu", mode == "f32math"
+    x = _case(d, "f32" if mode == "f32" else "bf16")
+    perm = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
+    back = (lambda t: t.permute(0, 2, 1, 3)) if layout == "bnhd" else (lambda t: t)
+    q, k, v, do = [perm(G.to_device(t)) for t in (x.q, x.k, x.v, x.dout)]
+    if relu:
+        lay = G.ReluLayer(x.H, x.d, x.B, x.n, q.dtype, layout=layout, f32_math=f32_math)
+    else:
+        lay = G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n, want_wgrads=form != "frozen map", layout=layout, f32_math=f32_math,
+                      centred=form == "centred")
+    if form == "blend":
+        s = _softmax_branch(x)
+        dr = torch.zeros(1, device="cuda")
+        lay.set_blend(perm(G.to_device(s)), torch.tensor([REL_R], device="cuda"), dr)
+    got = {"out": back(lay.forward(q, k, v))}
+    got.update(zip(("dq", "dk", "dv"), (back(t) for t in lay.backward(q, k, v, do))))
+    if not relu and form != "frozen map":
+        got.update(dwq=lay.dwq, dwk=lay.dwk)
+    got = {name: G.to_host_f64(t) for name, t in got.items()}
+    ref = dict(_reference(d, x.dtype, form if form in ("relu", "blend") else "plain"))
+    if form == "blend":
+        # dL/dr is a sum of products of random sign: 1e-2 of its spread
+        assert abs(float(dr) - ref.pop("dr")) <= 1e-2 * np.sqrt(np.square(O.to_f64(x.dout) * O.to_f64(s)).sum())
+    lay.close()
+    for name, r in ref.items():
+        if name in got:
+            bar = (2e-5 if name in ("dwq", "dwk") else 1e-5) if mode == "f32" or (f32_math and name in ("dwq", "dwk")) else 1e-2
+            assert O.err_metric(got[name], r)[0] <= bar, name
