@@ -2,16 +2,14 @@
 // product on exact bf16 pieces (f32_split.h).  Same mathematics as bwd_bf16.hip (chain rule through Eq. 3 and Eq. 5):
 //   grad_f32_kernel, query side : phi(q), den, G = dO S^T, delta = phi . G / den, dL/dphi = (G - delta z) / den, du, dq
 //   state_f32_kernel (weighted) : dS = sum phi(q)^T dO / den, dz = -sum phi(q) delta / den; split-n partials, reduced
-//   apply_f32_kernel (dv)       : dv = phi(k) dS
-//   grad_f32_kernel, key side   : phi(k), dL/dphi = v dS^T + dz, du, dk
+//   grad_f32_kernel, key side   : phi(k), dv = phi(k) dS, dL/dphi = v dS^T + dz, du, dk
 //   dw_f32_kernel               : dW~ = sum x^T du, both sides, from the du rows the two passes above leave in the workspace
 // The three pieces of one state image and of W~ fill the LDS of a compute unit (144 KB at width 128), which is why the sum over
-// tokens and dv are passes of their own.  delta needs no o: phi . (S dO) is o . dO times den.
+// tokens is a pass of its own.  delta needs no o: phi . (S dO) is o . dO times den.
 #include "kernels.h"
 #include "f32_split.h"
 #include "f32_plain.h"
 #include "f32_state.h"
-#include "f32_apply.h"
 
 namespace linattn {
 namespace {
@@ -81,54 +79,125 @@ struct WImage {
   }
 };
 
-// State (S or dS) of one head -> pieces of the A operands of G^T = M Y^T in LDS: entry (ks, mb, lane = (m, g)) holds
-// M[row(mb, m)][16ks + 8g + e]; the rows are ordered so that accumulator register r of block mb is element 16mb + r of the lane's phi.
-// Returns whether every value the thread met splits (see build_s_pieces).
-template <int D, int KIND, int NTHREADS>
-__device__ __forceinline__ bool build_g_pieces(const float* __restrict__ M, uint4* sG, int tid) {
-  constexpr int MB = D / 32, IMG = (D / 16) * MB * 64;
-  bool all = true;
-  for (int it = tid; it < IMG; it += NTHREADS) {
-    const int lane = it % 64, mb = (it / 64) % MB, ks = it / (64 * MB);
-    const int m = lane % 32, r = 4 * (m / 8) + m % 4;
-    const int row = phi_feature<D, KIND>(2 * mb + r / 8, (m / 4) % 2) + r % 8;
-    const uint4* src = reinterpret_cast<const uint4*>(M + row * D + 16 * ks + 8 * (lane / 32));
-    float v[8];
-    unpack_f32x4(src[0], v);
-    unpack_f32x4(src[1], v + 4);
-    uint4 p[3];
-    split8(v, p);
-    all = all && splits8(v);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) sG[i * IMG + it] = p[i];
+// State M (S or dS) of one head -> pieces of the A operands of G^T = M Y^T in LDS: entry (ks, mb, lane = (m, g)) holds
+// M[row(mb, m)][channel(ks, g, e)], e = 0..7; the rows are ordered so that accumulator register r of block mb is element 16mb + r of the lane's phi.
+// The same entries serve Y = phi M as B operands (column_operand): a transposing read gives four lanes the four channels of half an
+// entry, so the channels of a half are those that four lanes want for one column block, MB channels apart, among the ones that a lane
+// group of Y holds.  The lane index and the halves are XORed so that both kinds of read spread over the banks.
+// COLUMNS = false: channels in their order, for an image that is read by rows only.
+template <int D, bool COLUMNS>
+struct GImage {
+  static constexpr int MB = D / 32, KS = D / 16;
+  static constexpr int IMG = KS * MB * 64;                        // 16-byte entries of one piece
+  static constexpr int KP = COLUMNS ? D / 64 : 1;                               // k-steps that share the octets of a lane group
+  // Element e of k-step ks is value index(ks, e) of the KP octets KP*(ks/KP) .. of the lane group.
+  static constexpr int index(int ks, int e) { return COLUMNS ? MB * (e % 4) + 2 * (ks % KP) + e / 4 : e; }
+  static __device__ __forceinline__ int place(int ks, int mb, int lane) {
+    return (ks * MB + mb) * 64 + (COLUMNS ? lane ^ (8 * (lane / 32)) ^ (16 * (ks / KP >> 1)) : lane);
   }
-  return all;
-}
+  static __device__ __forceinline__ uint4 halves(int ks, uint4 v) { return COLUMNS && ks / KP % 2 ? make_uint4(v.z, v.w, v.x, v.y) : v; }
+  // Returns whether every value the thread met splits (see build_s_pieces).
+  template <int KIND, int NTHREADS>
+  static __device__ __forceinline__ bool build(const float* __restrict__ M, uint4* sG, int tid) {
+    bool all = true;
+    for (int it = tid; it < IMG / KP; it += NTHREADS) {
+      const int lane = it % 64, mb = (it / 64) % MB, p = it / (64 * MB);
+      const int m = lane % 32, r = 4 * (m / 8) + m % 4;
+      const int row = phi_feature<D, KIND>(2 * mb + r / 8, (m / 4) % 2) + r % 8;
+      float v[8 * KP];
+#pragma unroll
+      for (int o = 0; o < KP; ++o) {
+        const uint4* src = reinterpret_cast<const uint4*>(M + row * D + 16 * (KP * p + o) + 8 * (lane / 32));
+        unpack_f32x4(src[0], v + 8 * o);
+        unpack_f32x4(src[1], v + 8 * o + 4);
+        all = all && splits8(v + 8 * o);
+      }
+#pragma unroll
+      for (int t = 0; t < KP; ++t) {
+        float w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = v[index(t, e)];
+        uint4 q[3];
+        split8(w, q);
+        uint4* dst = sG + place(KP * p + t, mb, lane);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) dst[i * IMG] = halves(KP * p, q[i]);
+      }
+    }
+    return all;
+  }
+  static __device__ __forceinline__ uint4 row_operand(const uint4* sG, int piece, int ks, int mb, int lane) {
+    return halves(ks, sG[piece * IMG + place(ks, mb, lane)]);
+  }
+  // Pieces of k-step ks of Y, channels in the order of the entries.
+  template <typename T>
+  static __device__ __forceinline__ void y_pieces(const RowOctets<D, T>& y, int ks, uint4 (&p)[kPieces<T>]) {
+    if constexpr (!COLUMNS) { y.pieces(ks, p); return; }
+    const int o0 = KP * (ks / KP), t = ks % KP;
+    if constexpr (sizeof(T) == 2) {
+      uint32_t w[4 * KP];
+#pragma unroll
+      for (int o = 0; o < KP; ++o) {
+        w[4 * o] = y.r[o0 + o].x; w[4 * o + 1] = y.r[o0 + o].y; w[4 * o + 2] = y.r[o0 + o].z; w[4 * o + 3] = y.r[o0 + o].w;
+      }
+      auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
+      auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
+      const uint32_t a = w[t], b = w[MB / 2 + t], c = w[MB + t], d = w[3 * MB / 2 + t];       // values MB q + 2t, + 1
+      p[0] = make_uint4(lo(a, b), lo(c, d), hi(a, b), hi(c, d));
+    } else {
+      float v[8 * KP], w[8];
+#pragma unroll
+      for (int o = 0; o < KP; ++o) y.values(o0 + o, v + 8 * o);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = v[index(ks, e)];
+      split8(w, p);
+    }
+  }
+  // B operand (ks, mb) of Y = phi M: lane (c, g) receives M[phi octet ks of group g][MB * column(c) + mb].  Lane (s = lane%16, j = (lane/16)%2, g)
+  // points at row s/4 of half h of the octet and at four channels of the quad of columns 4j + s%4.
+  static __device__ __forceinline__ int column_base(int lane) {
+    const int s = lane % 16, j = (lane / 16) % 2, g = lane / 32;
+    const int quad = 4 * j + s % 4, p = quad / 2, gl = quad % 2;
+    return KP * p * MB * 1024 + 512 * gl + 16 * ((s / 4 + 4 * g) ^ (8 * gl) ^ (16 * (p >> 1))) + 8 * (p & 1);
+  }
+  static __device__ __forceinline__ uint4 column_operand(const uint4* sG, int piece, int ks, int mb, int base) {
+    const char* img = reinterpret_cast<const char*>(sG + piece * IMG) + (mb / 2 * MB + ks / 2) * 1024;
+    const int at = base ^ (256 * (ks % 2) + 8 * (mb % 2));
+    return __builtin_bit_cast(uint4, read_tr(img, at, at ^ 128));
+  }
+  static __device__ __forceinline__ int column(int c) {
+    return MB == 4 ? 8 * (c / 8) + 2 * (c / 4 % 2) + 4 * (c / 2 % 2) + c % 2 : c;
+  }
+};
 
 template <int D, int KIND, typename T>
 constexpr size_t grad_smem() {
-  return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * (D / 16) * (D / 32) * 64) * sizeof(uint4) + (D + 2 * NT8 / 64) * sizeof(float);
+  return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * GImage<D, false>::IMG) * sizeof(uint4) + (D + 2 * NT8 / 64) * sizeof(float);
 }
 
 // 8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks (a lane pair owns a token).
 // QSIDE: x = q, y = dO, M = (S, z); leaves the weights of the sum over tokens, {om / den, -om delta / den}, in weights[bh][t] and
 // (BLEND, dr_part not null) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.  s is read for
 // that alone.
-// Key side: x = k, y = v, M = (dS, dz).  du_ws (nullable): dL/du rows for dW~.
+// Key side: x = k, y = v, M = (dS, dz); dv = phi(k) dS as well, from the same image.  As a pass of its own it read k, formed phi and built an
+// image once more; two passes / this one, us: 12 heads x 32760 x 128 with bf16 tensors 97 + 80 / 161, 5 x 20000 x 128 fp32 61 + 37 / 84, 2 x
+// 1024 x 64 fp32 12.3 + 7.8 / 15.4.  du_ws (nullable): dL/du rows for dW~.
 template <int D, int KIND, typename T, bool QSIDE, bool BLEND>
 __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
-                                                       const float* __restrict__ state, T* __restrict__ dx, float* __restrict__ du_ws,
+                                                       const float* __restrict__ state, T* __restrict__ dx, T* __restrict__ dv,
+                                                       float* __restrict__ du_ws,
                                                        float2* __restrict__ weights, const T* __restrict__ blend,
                                                        const float* __restrict__ rptr, float* __restrict__ dr_part,
                                                        int H, int n, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
   using W = WImage<D>;
-  constexpr int MB = L::MB, IMG = (D / 16) * MB * 64, NX = kPieces<T>;
+  using GI = GImage<D, !QSIDE>;
+  constexpr int MB = L::MB, NX = kPieces<T>;
   extern __shared__ uint4 smem[];
   uint4* sW = smem;
   uint4* sG = sW + (KIND == kPhiRelu ? 0 : NX * W::IMG);
-  float* sZ = reinterpret_cast<float*>(sG + 3 * IMG);
+  float* sZ = reinterpret_cast<float*>(sG + 3 * GI::IMG);
   float* sRed = sZ + D;
   int* sPlain = reinterpret_cast<int*>(sRed + NT8 / 64);   // [8] the wavefront has met a state value that does not split (f32_plain.h)
 
@@ -139,6 +208,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   const T* xb = x + head_base(rw, bh, H);
   const T* yb = y + head_base(rw, bh, H);
   T* dxb = dx + head_base(rw, bh, H);
+  T* dvb = QSIDE ? nullptr : dv + head_base(rw, bh, H);
   const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
   const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;
   float dr_acc = 0.f;
@@ -154,7 +224,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   const int b_first = b < nblk ? b : nblk - 1;
   xr.load(row_of(xb, b_first), g);
   if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
-  const bool state_splits = build_g_pieces<D, KIND, NT8>(sb, sG, tid);
+  const bool state_splits = GI::template build<KIND, NT8>(sb, sG, tid);
   if (lane == 0) sPlain[w] = 0;
   if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
   build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
@@ -166,7 +236,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   for (; b < nblk; b += stride) {
     const int t = b * 32 + c;
     const bool valid = t < n;
-    yr.load(row_of(yb, b), g);
+    if constexpr (QSIDE || NX == 1) yr.load(row_of(yb, b), g);
     float ds = 0.f;                                                // dO . s on the lane's channels, while few registers are live
     if constexpr (BLEND) {
       if (dr_part != nullptr) {
@@ -196,6 +266,30 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
     } else {
       phi_octets<D, KIND, T>(xr, nullptr, lane, f);
     }
+    if constexpr (!QSIDE) {
+      f32x16 o[1][MB];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) o[0][mb] = zero16();
+      const int base = GI::column_base(lane + opaque_zero());
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) {
+        uint4 a[1][3], m[MB][3];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 3; ++i) m[mb][i] = GI::column_operand(sG, i, ks, mb, base);
+        split8(f + 8 * ks, a[0]);
+        mfma_pieces<3, 3>(a, m, o);
+      }
+      if constexpr (KIND == kPhiRelu) {
+        // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
+#pragma unroll
+        for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
+      }
+      // (fp32 rows do not fit the registers beside the accumulators; before the stores: a wait for them must not wait for the stores)
+      if constexpr (NX != 1) yr.load(row_of(yb, b), g);
+      store_rows<D, T>(dvb, rw.sn, b * 32, n, (lane & 32) + GI::column(c), [&](int r, int mb) { return o[0][mb][r]; });
+    }
     float inv = 0.f;
     const float* z = sZ + opaque_zero();
     if constexpr (QSIDE) inv = 1.0f / (octet_dot<D>(f, z, g) + (KIND == kPhiRelu ? kReluEps : 0.f));
@@ -204,15 +298,15 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
     f32x16 ga[MB][1];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) ga[mb][0] = zero16();
-    const uint4* sg = sG + lane + opaque_zero();
+    const int lg = lane + opaque_zero();
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
       uint4 a[MB][3], yp[1][NX];
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int i = 0; i < 3; ++i) a[mb][i] = sg[i * IMG + (ks * MB + mb) * 64];
-      yr.pieces(ks, yp[0]);
+        for (int i = 0; i < 3; ++i) a[mb][i] = GI::row_operand(sG, i, ks, mb, lg);
+      GI::template y_pieces<T>(yr, ks, yp[0]);
       mfma_pieces<3, NX>(a, yp, ga);
     }
     // a y that does not split makes every feature of its token NaN or Inf, phi from an x that does not is NaN: one value tells
@@ -328,6 +422,8 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
         Plain<D, KIND, T>::template grad<QSIDE, BLEND>(xb + at, yb + at, wx + (size_t)h * D * C::HALF, sb, dxb + at, du,
                                                        n - b * 32 < 32 ? n - b * 32 : 32, QSIDE ? weights + (size_t)bh * n + t : nullptr,
                                                        BLEND && dr_part != nullptr ? bb + at : nullptr, om, &dr, lane);
+        if constexpr (!QSIDE)
+          Plain<D, KIND, T>::template apply<false, false>(xb + at, wx + (size_t)h * D * C::HALF, sb, dvb + at, nullptr, 0.f, lane);
       }
     if (lane == 0) dr_acc = dr;
   }
@@ -490,12 +586,12 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
   const dim3 grid(p.KP, p.BH);
   constexpr size_t smem = grad_smem<D, KIND, T>();
-  // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which is written last
+  // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which the last pass writes
   float2* weights = static_cast<float2*>(a.dv);
   auto grad = [&](auto kernel, const void* x, const void* y, const void* wx, const float* state, void* dx, float* du) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
-    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, du, weights,
+    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, (T*)a.dv, du, weights,
                                                     (const T*)a.blend_in, a.blend_r, a.blend_dr ? a.dr_part : nullptr, p.H, p.n, p.rows);
     return hipGetLastError();
   };
@@ -511,7 +607,6 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   if ((e = launch_state_reduce_split(a.partials, a.dstate, p, s)) != hipSuccess) return e;
   e = grad(KernelTag<grad_f32_kernel<D, KIND, T, false, false>>{}, a.k, a.v, a.wk, a.dstate, a.dk, du_k);
   if (e != hipSuccess) return e;
-  if ((e = run_apply_pass<D, KIND, T, false, false>(a.k, a.wk, a.dstate, a.dv, nullptr, nullptr, p, s)) != hipSuccess) return e;
   if constexpr (KIND == kPhiHedgehog) {
     if (du_q || du_k) {
       if ((e = set_smem_once<dw_f32_kernel<D, T>>(dw_smem<D>())) != hipSuccess) return e;

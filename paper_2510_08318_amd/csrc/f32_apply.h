@@ -6,7 +6,7 @@
 namespace linattn {
 namespace f32 {
 
-// out = phi(x) M, with NORM divided by phi(x) . z: the query pass (M = S), and without NORM dv = phi(k) dS of the backward.  8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks; LDS holds
+// The query pass, out = phi(q) S / (phi(q) . z).  8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks; LDS holds
 // the pieces of W~_q and of the S image (144 KB for fp32 tensors of width 128).  The normaliser is an in-lane dot product (a
 // lane pair owns the token) and goes into phi before it is split, so the product with S is the output and leaves the
 // accumulators as whole rows.
@@ -14,7 +14,7 @@ template <int D, int KIND, typename T>
 constexpr size_t apply_smem() {
   return ((KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG) + 3 * ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64) * sizeof(uint4) + (D + NT8 / 64) * sizeof(float);
 }
-template <int D, int KIND, typename T, bool NORM, bool BLEND>
+template <int D, int KIND, typename T, bool BLEND>
 __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q, const T* __restrict__ wq,
                                                         const float* __restrict__ state, T* __restrict__ out,
                                                         const T* __restrict__ blend, const float* __restrict__ rptr,
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
   const bool state_splits = build_s_pieces<D, KIND, NT8>(sb, sS, tid);
   if (lane == 0) sPlain[w] = 0;
   if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
-  if constexpr (NORM) build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
+  build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
   __syncthreads();
 
   const int b_own = b;
@@ -60,10 +60,9 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
     float f[D / 2];
     phi_octets<D, KIND, T>(x, sW, lane, f);
     load(b + stride < nblk ? b + stride : b);
-    float inv = 1.f;
-    if constexpr (NORM) inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+    const float inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
     // phi is at most 1 and splits, unless an x or u that did not made its half NaN (and with it den)
-    if constexpr (KIND == kPhiHedgehog) chk = fmaf(NORM ? inv * 0x1p8f : f[0] + f[D / 4], 0.f, chk);
+    if constexpr (KIND == kPhiHedgehog) chk = fmaf(inv * 0x1p8f, 0.f, chk);
     f32x16 o[1][L::MB];
 #pragma unroll
     for (int mb = 0; mb < L::MB; ++mb) o[0][mb] = zero16();
@@ -77,7 +76,7 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
         for (int i = 0; i < 3; ++i) s[mb][i] = ss[i * IMG + (ks * L::MB + mb) * 64];
       float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = NORM ? f[8 * ks + e] * inv : f[8 * ks + e];
+      for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] * inv;
       split8(v, a[0]);
       mfma_pieces<3, 3>(a, s, o);
     }
@@ -105,18 +104,18 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
 #pragma unroll 1
       for (int t = 32 * b; t < 32 * b + 32 && t < n; ++t) {
         const size_t at = (size_t)t * rw.sn;
-        Plain<D, KIND, T>::template apply<NORM, BLEND>(qb + at, wq + (size_t)h * D * (D / 2), sb, ob + at, BLEND ? bb + at : nullptr, rb, lane);
+        Plain<D, KIND, T>::template apply<true, BLEND>(qb + at, wq + (size_t)h * D * (D / 2), sb, ob + at, BLEND ? bb + at : nullptr, rb, lane);
       }
   }
 }
 
-template <int D, int KIND, typename T, bool NORM, bool BLEND>
+template <int D, int KIND, typename T, bool BLEND>
 hipError_t run_apply_pass(const void* q, const void* wq, const float* state, void* out,
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
-  const hipError_t e = set_smem_once<apply_f32_kernel<D, KIND, T, NORM, BLEND>>(smem);
+  const hipError_t e = set_smem_once<apply_f32_kernel<D, KIND, T, BLEND>>(smem);
   if (e != hipSuccess) return e;
-  apply_f32_kernel<D, KIND, T, NORM, BLEND><<<dim3(p.KP, p.BH), NT8, smem, s>>>(
+  apply_f32_kernel<D, KIND, T, BLEND><<<dim3(p.KP, p.BH), NT8, smem, s>>>(
       (const T*)q, (const T*)wq, state, (T*)out, (const T*)blend_in, blend_r, p.H, p.n, p.rows);
   return hipGetLastError();
 }

@@ -23,13 +23,13 @@ template <typename T>
 hipError_t apply_any(const void* q, const void* wq, const float* state, void* out,
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   if (p.kind == kPhiRelu)      // the descriptor check has refused a blend with this map
-    return p.d == 128 ? run_apply_pass<128, kPhiRelu, T, true, false>(q, wq, state, out, nullptr, nullptr, p, s)
-                      : run_apply_pass<64, kPhiRelu, T, true, false>(q, wq, state, out, nullptr, nullptr, p, s);
+    return p.d == 128 ? run_apply_pass<128, kPhiRelu, T, false>(q, wq, state, out, nullptr, nullptr, p, s)
+                      : run_apply_pass<64, kPhiRelu, T, false>(q, wq, state, out, nullptr, nullptr, p, s);
   if (blend_in)
-    return p.d == 128 ? run_apply_pass<128, kPhiHedgehog, T, true, true>(q, wq, state, out, blend_in, blend_r, p, s)
-                      : run_apply_pass<64, kPhiHedgehog, T, true, true>(q, wq, state, out, blend_in, blend_r, p, s);
-  return p.d == 128 ? run_apply_pass<128, kPhiHedgehog, T, true, false>(q, wq, state, out, nullptr, nullptr, p, s)
-                    : run_apply_pass<64, kPhiHedgehog, T, true, false>(q, wq, state, out, nullptr, nullptr, p, s);
+    return p.d == 128 ? run_apply_pass<128, kPhiHedgehog, T, true>(q, wq, state, out, blend_in, blend_r, p, s)
+                      : run_apply_pass<64, kPhiHedgehog, T, true>(q, wq, state, out, blend_in, blend_r, p, s);
+  return p.d == 128 ? run_apply_pass<128, kPhiHedgehog, T, false>(q, wq, state, out, nullptr, nullptr, p, s)
+                    : run_apply_pass<64, kPhiHedgehog, T, false>(q, wq, state, out, nullptr, nullptr, p, s);
 }
 
 }  // namespace
