@@ -788,8 +788,8 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
   DWT dwt;
   if constexpr (DW) dwt.init(w);
   // DW: every wavefront of the workgroup makes the same number of rounds (there are barriers inside); a wavefront
-  // whose block does not exist works on tokens past n: its loads repeat row n - 1, its du is zero, its stores go
-  // to the sink
+  // whose block does not exist works on tokens past n: its loads repeat row n - 1, its du is zero, its stores are
+  // out of bounds
   int b = blockIdx.x * NW + w;
   if (DW || b < nblk) load_k(b);
   for (int b0 = blockIdx.x * NW; DW ? b0 < nblk : b < nblk; b0 += stride, b += stride) {

@@ -271,24 +271,14 @@ __device__ __forceinline__ float octet_dot(const float (&f)[D / 2], const float*
   return lo + hi;
 }
 
-// Where the stores of token rows past the end of a head go (16 bytes per lane; the contents mean nothing).
-static __device__ __attribute__((aligned(256))) unsigned char g_row_sink[64 * 16];
-
 // Rows of an accumulator with the tokens on its rows (lane (c, g), register r: token t0 + 8*(r/4) + 4g + r%4, channels MB*c .. +MB-1):
-// value(r, mb) is stored as T.  No branch around a store (rows past n go to a sink), see store_token_rows.
+// value(r, mb) is stored as T.
 template <int D, typename T, typename Value>
 __device__ __forceinline__ void store_rows(T* base, size_t sn, int t0, int n, int lane, Value value) {
   constexpr int MB = D / 32;
-  const int c = lane % 32, g = lane / 32;
-  char* ub = reinterpret_cast<char*>(base + (size_t)t0 * sn);
-  const uint32_t lo = ((uint32_t)(4 * g) * (uint32_t)sn + (uint32_t)(MB * c)) * (uint32_t)sizeof(T);
-  char* sink = reinterpret_cast<char*>(g_row_sink) + lane * 16;
-  const bool full = t0 + 32 <= n;
+  const TokenRows<MB * (int)sizeof(T), true> rows(base, sn * sizeof(T), t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int row = 8 * (r / 4) + (r % 4);
-    const bool there = full || t0 + row + 4 * g < n;
-    char* dst = there ? ub + (size_t)row * sn * sizeof(T) + lo : sink;
     float y[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) y[mb] = value(r, mb);
@@ -297,13 +287,11 @@ __device__ __forceinline__ void store_rows(T* base, size_t sn, int t0, int n, in
       vec v;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) v[mb] = y[mb];
-      __builtin_nontemporal_store(v, reinterpret_cast<vec*>(dst));
+      rows.store(r, v);
+    } else if constexpr (MB == 4) {
+      rows.store(r, make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])));
     } else {
-      typedef unsigned vec __attribute__((ext_vector_type(MB / 2)));
-      vec v;
-#pragma unroll
-      for (int mb = 0; mb < MB / 2; ++mb) v[mb] = pack_bf16x2(y[2 * mb], y[2 * mb + 1]);
-      __builtin_nontemporal_store(v, reinterpret_cast<vec*>(dst));
+      rows.store(r, pack_bf16x2(y[0], y[1]));
     }
   }
 }

@@ -34,11 +34,6 @@ __device__ __forceinline__ uint32_t piece_word(const uint2& p, int i) { return i
 __device__ __forceinline__ uint32_t piece_word(const uint32_t& p, int) { return p; }
 __device__ __forceinline__ void set_piece_word(uint2& p, int i, uint32_t v) { if (i) p.y = v; else p.x = v; }
 __device__ __forceinline__ void set_piece_word(uint32_t& p, int, uint32_t v) { p = v; }
-__device__ __forceinline__ void st_nt(uint2* p, uint2 v) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  __builtin_nontemporal_store(__builtin_bit_cast(u32x2, v), reinterpret_cast<u32x2*>(p));
-}
-__device__ __forceinline__ void st_nt(uint32_t* p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 
 // Wavefronts of a workgroup of the query pass, one workgroup per compute unit.  With 8 a unit is small enough for an even deal and a lane
 // has up to 256 registers (with 12, 168: the blend at width 128 spilled).  12 with per-head shares / 8 dealt evenly, us: 12 heads x 32760 x
@@ -268,15 +263,9 @@ __global__ __launch_bounds__(64 * apply_waves(D, BLEND), D == 64 ? (BLEND ? 3 : 
         // stores the tail of out stays dirty in the last-level cache and is written back under
         // whatever kernel runs next (measured: the next call's state pass loses 30 us, this pass
         // gains 20 us)
-        // No branch around any of them: rows past n go to a sink instead (a select), see store_token_rows.
-        char* ub = reinterpret_cast<char*>(ob + (size_t)(b * 32) * rw.sn) + lane_off;
-        char* sink = reinterpret_cast<char*>(g_store_sink) + lane * 8;
+        const TokenRows<sizeof(Piece), true> rows(ob, rw.sn * 2, b * 32, n, lane);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = 8 * (r / 4) + (r % 4);
-          const bool there = full || b * 32 + row + 4 * g < n;
-          st_nt(reinterpret_cast<Piece*>(there ? ub + (size_t)row * rw.sn * 2 : sink), word[r]);
-        }
+        for (int r = 0; r < 16; ++r) rows.store(r, word[r]);
       }
     }
     if (sh.rest < sh.hi) __syncthreads();                // the next head's images take the place of these

@@ -38,6 +38,7 @@ __device__ __forceinline__ int opaque_zero() {
   return z;
 }
 
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // Streaming (non-temporal) 16-byte global load / store, for fully coalesced accesses only: with
 // the operand-layout loads (two 16-byte pieces of a row per instruction, four instructions per
@@ -511,37 +512,53 @@ __device__ __forceinline__ float half_wave_sum(float x) {
   return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
-// Where the stores of token rows past the end of a head go (8 bytes per lane; the contents mean nothing).
-static __device__ __attribute__((aligned(256))) unsigned char g_store_sink[64 * 8];
+// The 32 rows from token t0 of a head of n tokens, as the accumulators with tokens on the rows hold them: lane (c, g), register r has PIECE
+// bytes of token t0 + 8*(r/4) + 4g + r%4, at byte PIECE*c of the row, so that every store instruction writes two whole rows.
+// The stores are buffer stores bounded to the rows that exist: the hardware drops those past n.  No branch (behind one the compiler cannot count the
+// stores in flight, and a later wait for a load that was requested before them, the next block's rows, turns into a wait for the
+// stores as well), and one vector instruction for an address.  Choosing between the row and a sink by a select took five, 64 more a block: a pass
+// of 4 x 1000 x 64 8.5 us, now 8.0, of 12 x 4133 x 64 7.7, now 6.9; the fp32-arithmetic key side, which that kept from spilling, 164 -> 156
+// at 12 x 32760 x 128; nothing where the memory or the barriers of dW~ are what is waited for.
+// All arguments but the lane are uniform.  NT: non-temporal.
+template <int PIECE, bool NT = false>
+struct TokenRows {
+  __amdgpu_buffer_rsrc_t rows;
+  uint32_t at, pitch;
+  __device__ __forceinline__ TokenRows(void* base, size_t pitch_bytes, int t0, int n, int lane) {
+    const int left = n - t0 < 32 ? n - t0 : 32;
+    pitch = (uint32_t)pitch_bytes;
+    rows = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(base) + (size_t)t0 * pitch_bytes, 0, left > 0 ? (uint32_t)left * pitch : 0, 0x00020000);
+    const int lz = lane + opaque_zero();                   // (the sixteen offsets are not held across a caller's loop)
+    at = (uint32_t)(4 * (lz / 32)) * pitch + (uint32_t)(PIECE * (lz % 32));
+  }
+  template <typename V>
+  __device__ __forceinline__ void store(int r, V v) const {
+    static_assert(sizeof(V) == PIECE, "a lane's piece of a row");
+    const uint32_t off = at + (uint32_t)(8 * (r / 4) + r % 4) * pitch;
+    constexpr int aux = NT ? 2 : 0;
+    if constexpr (PIECE == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rows, off, 0, aux);
+    else if constexpr (PIECE == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rows, off, 0, aux);
+    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, off, 0, aux);
+  }
+};
 
 // Accumulators with tokens on the rows (lane (c,g), register r: token t0 + 8*(r/4) + 4g + r%4,
-// channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.  Every store
-// instruction writes two whole rows of d channels.
+// channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.
 template <int D>
 __device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
                                                  const f32x16 (&acc)[D / 32], float mul, const float (&add)[D / 32]) {
   constexpr int MB = D / 32;
   static_assert(MB == 2 || MB == 4, "head width 64 or 128");
-  const int c = lane % 32, g = lane / 32;
-  char* ub = reinterpret_cast<char*>(base + (size_t)t0 * sn);
-  const uint32_t lo = ((uint32_t)(4 * g) * (uint32_t)sn + (uint32_t)(MB * c)) * 2u;
-  // No branch around any of the stores: rows past n go to a sink instead (a select).  Behind branches the
-  // compiler cannot count the stores in flight, and a later wait for a load that was requested before them
-  // (the next block's rows) turns into a wait for the stores as well.
-  const bool full = t0 + 32 <= n;
-  char* sink = reinterpret_cast<char*>(g_store_sink) + lane * 8;
+  const TokenRows<2 * MB> rows(base, sn * 2, t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int row = 8 * (r / 4) + (r % 4);
-    const bool there = full || t0 + row + 4 * g < n;
-    char* dst = there ? ub + (size_t)row * sn * 2 + lo : sink;
     if constexpr (MB == 4) {
       uint2 v;
       v.x = pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1]));
       v.y = pack_bf16x2(fmaf(acc[2][r], mul, add[2]), fmaf(acc[3][r], mul, add[3]));
-      *reinterpret_cast<uint2*>(dst) = v;
+      rows.store(r, v);
     } else {
-      *reinterpret_cast<uint32_t*>(dst) = pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1]));
+      rows.store(r, pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1])));
     }
   }
 }
