@@ -35,13 +35,6 @@ __device__ __forceinline__ uint32_t piece_word(const uint32_t& p, int) { return 
 __device__ __forceinline__ void set_piece_word(uint2& p, int i, uint32_t v) { if (i) p.y = v; else p.x = v; }
 __device__ __forceinline__ void set_piece_word(uint32_t& p, int, uint32_t v) { p = v; }
 
-// Wavefronts of a workgroup of the query pass, one workgroup per compute unit.  With 8 a unit is small enough for an even deal and a lane
-// has up to 256 registers (with 12, 168: the blend at width 128 spilled).  12 with per-head shares / 8 dealt evenly, us: 12 heads x 32760 x
-// 128 52.0 / 49.5, with blend 84.7 / 77.2, ReLU 56.9 / 53.9; 40 x 75600 x 128 326 / 327; 12 x 8190 x 128 16.8 / 17.2; 30 x 17550 x 64 31.2 /
-// 30.6; 12 x 4133 x 64 8.6 / 7.6.  The blend at width 64 needs 131 registers either way and is no faster with 8 (26 x 2222 x 64 9.8 / 10.1, 7 x
-// 20000 x 64 13.9 / 14.3).
-constexpr int apply_waves(int d, bool blend) { return d == 64 && blend ? 12 : 8; }
-
 // The state of head bh as the sum of its workgroups' partials, pairwise, to sum[(D+1)*D/4] in LDS and, if given, to dst.  16 loads of
 // a thread are in flight; those of a missing slot repeat the last one's and count as zero (branch-free).
 template <int D> constexpr int kSumSlots = D == 64 ? 8 : 2;      // see sum_in_apply
@@ -96,15 +89,15 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
 // in channel order, kReluEps in the denominator.
 // SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
 // sum_in_apply); the first workgroup of a head writes it to `state`.
-template <int D, bool BLEND, int KIND, bool SUM>
-__global__ __launch_bounds__(64 * apply_waves(D, BLEND), D == 64 ? (BLEND ? 3 : 4) : 2) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+template <int D, bool BLEND, int KIND, bool SUM, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 12 ? (D == 64 && !BLEND && !SUM ? 4 : 3) : D == 64 && !BLEND ? 4 : 2) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ partials, float* __restrict__ state,
                                                          uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
                                                          int H, int n, Split deal, Split sp, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
-  constexpr int NW = apply_waves(D, BLEND), NT3 = 64 * NW;
+  constexpr int NT3 = 64 * NW;
   constexpr int SA_IMG = L::KS * L::MBZ * 64;
   constexpr int HB = L::MB / 2;             // channel column blocks per accumulation pass (two passes)
   using Piece = typename RowPiece<L::MB>::type;   // a lane's MB adjacent bf16 channels of one token
@@ -604,19 +597,31 @@ hipError_t launch_state_partials_bf16(const void* k, const void* v, const void* 
 
 namespace {
 
-// The prologue of the query pass in eighths of a unit: 3 to 4 us against 8 at 12 heads x 32760 x 128.
+// 8 wavefronts to a workgroup, one workgroup per compute unit: a unit is small enough for an even deal.  12 where the call is so short that they
+// save a round, since few rounds are bound by the latency of each.  Rounds with 8 / 12, and us: 1 head x 75600 x 128 2 / 1, 14.5 / 12.9, with blend
+// 19.4 / 17.2; 5 x 15000 x 128 2 / 1, 14.6 / 13.2; 7 x 20000 x 64 3 / 2, 10.3 / 10.3, with blend 14.6 / 13.9; but 12 x 8190 x 128 2 / 2, 15.5 / 15.4;
+// 26 x 2222 x 64 1 / 1, 7.2 / 7.7; 3 x 500 x 128 1 / 1, 9.7 / 11.7; 4 x 1000 x 64 1 / 1, 8.0 / 8.8; 12 x 32760 x 128 6 / 5, with blend 67 / 73,
+// ReLU 36.7 / 37.7.
+// The prologue in eighths of a unit: 3 to 4 us against 8 at 12 heads x 32760 x 128.
 constexpr int kApplyPrologue = 3;
+template <int D, bool BLEND, int KIND, bool SUM, int NW>
+hipError_t run_apply_waves(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
+                           const float* blend_r, const Plan& p, const Split& deal, hipStream_t s) {
+  hipError_t e;
+  constexpr size_t smem = apply_smem<D>(SUM);
+  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM, NW>>(smem)) != hipSuccess) return e;
+  apply_bf16_kernel<D, BLEND, KIND, SUM, NW><<<grid_of(deal), 64 * NW, smem, s>>>(
+      (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, deal, p.split, p.rows);
+  return hipGetLastError();
+}
 template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
-  hipError_t e;
-  constexpr size_t smem = apply_smem<D>(SUM);
-  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM>>(smem)) != hipSuccess) return e;
-  constexpr int NW = apply_waves(D, BLEND);
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NW - 1) / NW, kApplyPrologue);
-  apply_bf16_kernel<D, BLEND, KIND, SUM><<<grid_of(deal), 64 * NW, smem, s>>>(
-      (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, deal, p.split, p.rows);
-  return hipGetLastError();
+  const int blocks = (p.n + 31) / 32;
+  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyPrologue), d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyPrologue);
+  const int r8 = split_rounds(d8);
+  return r8 <= 3 && split_rounds(d12) < r8 ? run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s)
+                                           : run_apply_waves<D, BLEND, KIND, SUM, 8>(q, wq, partials, state, out, blend_in, blend_r, p, d8, s);
 }
 
 template <int D, bool SUM>

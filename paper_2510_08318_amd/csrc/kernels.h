@@ -124,6 +124,10 @@ __host__ __device__ inline Share first_share(const Split& s, int gx, int gy) {
   r.rest = split_lo(s, gx); r.hi = split_lo(s, gx + 1);
   return next_share(s, gx, r);
 }
+// the most units a workgroup gets
+inline int split_rounds(const Split& s) {
+  return s.share ? (s.ntile + s.share - 1) / s.share : (int)((s.T + s.G - 1) / s.G);
+}
 inline dim3 grid_of(const Split& s) { return s.share ? dim3(s.share, s.G / s.share) : dim3(s.G); }
 
 // The deal of a kernel that builds a head's operand images in its prologue: `per_head` units of each head to at most kCUs workgroups,

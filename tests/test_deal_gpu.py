@@ -14,11 +14,13 @@ from paper_2510_08318_amd import synth
 
 pytestmark = pytest.mark.gpu
 REL_R = 0.37
+SHARED = (43, 3, 600)          # heads, batch items, tokens
 
 
 @functools.lru_cache(None)
-def _case(d, dtype):
-    return synth.generate("C5", n=600, H=43, B=3, d=d, dtype=dtype)
+def _case(d, dtype, shape):
+    H, B, n = shape
+    return synth.generate("C5", n=n, H=H, B=B, d=d, dtype=dtype)
 
 
 def _softmax_branch(x):
@@ -26,8 +28,8 @@ def _softmax_branch(x):
 
 
 @functools.lru_cache(None)
-def _reference(d, dtype, form):
-    x = _case(d, dtype)
+def _reference(d, dtype, form, shape):
+    x = _case(d, dtype, shape)
     if form == "relu":
         return (("out", R.relu_fwd_bh(x.q, x.k, x.v)), *zip(("dq", "dk", "dv"), R.relu_bwd_bh(x.q, x.k, x.v, x.dout)))
     names = ("dq", "dk", "dv", "dwq", "dwk")
@@ -42,14 +44,25 @@ def _reference(d, dtype, form):
 @pytest.mark.parametrize("form", ["weight gradients", "frozen map", "blend", "centred", "relu"])
 @pytest.mark.parametrize("mode,d", [("bf16", 64), ("bf16", 128), ("f32math", 64), ("f32math", 128), ("f32", 64), ("f32", 128)])
 def test_step_with_heads_that_share_workgroups(mode, d, form, layout):
-    import torch
-    from paper_2510_08318_amd import torch_glue as G
     if form == "centred" and mode != "bf16":
         pytest.skip("the flag belongs to the bf16 mode")
     if layout == "bnhd" and form in ("frozen map", "centred"):
         pytest.skip("covered by the other forms")
+    _step(mode, d, form, layout, SHARED)
+
+
+# 100 heads of 640 tokens: two workgroups a head, two rounds of 8 wavefronts or one of 12, which the query pass takes then
+@pytest.mark.parametrize("form", ["frozen map", "blend", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_query_pass_of_twelve_wavefronts(d, form):
+    _step("bf16", d, form, "bhnd", (50, 2, 640 - 3))
+
+
+def _step(mode, d, form, layout, shape):
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
     relu, f32_math = form == "relu", mode == "f32math"
-    x = _case(d, "f32" if mode == "f32" else "bf16")
+    x = _case(d, "f32" if mode == "f32" else "bf16", shape)
     perm = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
     back = (lambda t: t.permute(0, 2, 1, 3)) if layout == "bnhd" else (lambda t: t)
     q, k, v, do = [perm(G.to_device(t)) for t in (x.q, x.k, x.v, x.dout)]
@@ -67,7 +80,7 @@ def test_step_with_heads_that_share_workgroups(mode, d, form, layout):
     if not relu and form != "frozen map":
         got.update(dwq=lay.dwq, dwk=lay.dwk)
     got = {name: G.to_host_f64(t) for name, t in got.items()}
-    ref = dict(_reference(d, x.dtype, form if form in ("relu", "blend") else "plain"))
+    ref = dict(_reference(d, x.dtype, form if form in ("relu", "blend") else "plain", shape))
     if form == "blend":
         # dL/dr is a sum of products of random sign: 1e-2 of its spread
         assert abs(float(dr) - ref.pop("dr")) <= 1e-2 * np.sqrt(np.square(O.to_f64(x.dout) * O.to_f64(s)).sum())
