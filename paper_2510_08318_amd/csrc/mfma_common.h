@@ -544,12 +544,15 @@ struct TokenRows {
 
 // Accumulators with tokens on the rows (lane (c,g), register r: token t0 + 8*(r/4) + 4g + r%4,
 // channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.
+// Non-temporal: a gradient's dirty tail in the last-level cache is otherwise written back under the kernels after it, and takes the place of rows
+// that they read.  Ordinary / non-temporal stores of dq, dk, dv, 12 heads x 32760 x 128, us: bwd_q 110 / 112, bwd_k 128 / 121, and the next
+// call's state pass 61 / 53 and query pass 54 / 50 (40 x 20000: state pass 110 / 85); ReLU map 91 / 87, 87 / 94, 44 / 44, 54 / 46.
 template <int D>
 __device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
                                                  const f32x16 (&acc)[D / 32], float mul, const float (&add)[D / 32]) {
   constexpr int MB = D / 32;
   static_assert(MB == 2 || MB == 4, "head width 64 or 128");
-  const TokenRows<2 * MB> rows(base, sn * 2, t0, n, lane);
+  const TokenRows<2 * MB, true> rows(base, sn * 2, t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     if constexpr (MB == 4) {

@@ -285,7 +285,7 @@ struct RowStore {
     for (int i = 0; i < 32 / RPI; ++i) {
       const int row = i * RPI + lane / CH, t = t0 + row;
       const uint4 x = *reinterpret_cast<const uint4*>(buf + row * D * 2 + ((c ^ swz<D>(row)) * 16));
-      *reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c) = x;
+      st_nt(reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c), x);
     }
     __builtin_amdgcn_wave_barrier();
   }
