@@ -62,7 +62,7 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   // for three), and calls that have always been accepted would be refused.
   off = up(off + (size_t)BH * (4 * d * d + 2 * (d / 16) * (d / 32 + 1) * 1024 + 8) + (size_t)H * 4 * d * d);
   r.off_centre = off;   off = up(off + ((size_t)BH * 3 * d + (size_t)BH * r.P * (d + 8)) * sizeof(float));
-  r.off_drpart = off;   off = up(off + ((size_t)BH * r.P + kDotParts) * sizeof(float));
+  r.off_drpart = off;   off = up(off + ((size_t)BH * r.P + kDrSlack) * sizeof(float));
   r.bytes_no_wgrads = off;
   r.off_dwpart = off;   off = up(off + (size_t)BH * (r.P + (r.P > r.KP ? r.P : r.KP)) * d * (d / 2) * sizeof(float));
   // the fp32-arithmetic modes keep dL/du as fp32 rows for a separate dW~ pass; the bf16 kernels accumulate dW~ where du is made
@@ -183,7 +183,7 @@ int run_fwd(const linattn_phi_desc& desc, const Plan& plan, const void* q, const
   if (e != hipSuccess) return LINATTN_E_HIP;
   ev.mark(1, s);
   if (f32_math || !sum_in_apply(plan)) {
-    e = launch_state_reduce_split(partials, state, plan, s);
+    e = launch_state_reduce_split(partials, state, plan, DrSum{}, s);
     if (e != hipSuccess) return LINATTN_E_HIP;
   }
   ev.mark(2, s);

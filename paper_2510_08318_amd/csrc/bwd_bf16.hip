@@ -56,7 +56,7 @@ __device__ __forceinline__ float build_query_state(const float* __restrict__ sta
   R S;
   S.load(state, tid);
   float* part = scratch;
-  float* vb = part + R::FO * D;
+  float* vb = part + R::FO * D;                             // (read by the acc wavefronts of bwd_q_kernel as well)
   float* red = vb + D;
   if (tid < D) sZ[tid] = state[D * D + tid];
   S.octet_sums(part);
@@ -344,9 +344,11 @@ struct DwTile {
 // LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use (one more for g).
 constexpr int QAHEAD = 3;
 constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
-// BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives
-// (1 - r') dout, and the workgroup's part of -sum dout . o goes to dr_part (dL/dr = sum dout . (s - o);
-// the sum dout . s is a separate streaming dot product, taken only when dL/dr is asked for).
+// BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  If dL/dr = sum dout . (s - o) is asked
+// for (blend not null), the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
+// wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
+// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it is hidden
+// (bwd_q 114 either way; centred and with dW~, where it spills, 41 -> 47 at 12 x 8190 for a pass of 10).
 // DW: dW~_q is accumulated here as well (DwTile).
 //
 // Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
@@ -363,8 +365,8 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
                                                     const uint16_t* __restrict__ wq, const float* __restrict__ state,
                                                     float* __restrict__ vbar, uint16_t* __restrict__ dq,
                                                     float* __restrict__ partials, float* __restrict__ dw_part,
-                                                    const float* __restrict__ rptr, float* __restrict__ dr_part,
-                                                    float* __restrict__ cs_part,
+                                                    const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
+                                                    float* __restrict__ dr_part, float* __restrict__ cs_part,
                                                     int H, int n, int P, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
@@ -393,6 +395,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;      // 1 - r'
   const float* sb = state + (size_t)bh * (D + 1) * D;
   const int ntile = (n + kTile - 1) / kTile;
+  float dr_acc = 0.f;
 
   build_w_image<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
   build_w_image_t<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
@@ -415,7 +418,6 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     const uint16_t* dob = dout + head_base(rw, bh, H);
     uint16_t* dqb = dq + head_base(rw, bh, H);
     const int prow = 32 * pw + (lane % 32);
-    float dr_acc = 0.f;
     float z_mean = 0.f;                                    // mean * the sum of z over the lane's features
     if constexpr (CENTRE) {
       for (int j = 0; j < C::LOC; ++j) z_mean += sZ[g * C::LOC + j] + sZ[C::HALF + g * C::LOC + j];
@@ -617,10 +619,6 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         __syncthreads();
       }
     }
-    if constexpr (BLEND) {
-      for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
-      if (lane == 0) sRed[pw] = dr_acc;                  // (read for the last time before the last tile's second barrier)
-    }
   } else {
     float csum[WMN], wsum = 0.f;                         // column sums of the dO/den operand, sum of the -delta/den operand
 #pragma unroll
@@ -647,7 +645,38 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
     DWT dwt;
     if constexpr (DW) dwt.init(pw);
+    // BLEND: the thread's chunk column of s and dout, vbar there (left in LDS by the prologue until the first tile is parked)
+    constexpr int PER = kTile * C::CH / 256;
+    const int crow = (tid - 256) / C::CH, ccol = (tid - 256) % C::CH;
+    float vb[8];
+    if constexpr (BLEND) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) vb[i] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + 8 * ccol + i];
+    }
     for (int tile = p; tile < ntile; tile += P) {
+      if constexpr (BLEND) {
+        if (blend != nullptr) {
+          const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
+          const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
+          uint4 sv[PER], dv[PER];
+#pragma unroll
+          for (int i = 0; i < PER; ++i) {
+            const int t = tile * kTile + crow + i * (256 / C::CH);
+            const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+            sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
+            dv[i] = *reinterpret_cast<const uint4*>(drow + at);
+          }
+#pragma unroll
+          for (int i = 0; i < PER; ++i) {
+            float a[8], b[8], t = 0.f;
+            unpack_bf16x8(sv[i], a);
+            unpack_bf16x8(dv[i], b);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
+            if (tile * kTile + crow + i * (256 / C::CH) < n) dr_acc += t;
+          }
+        }
+      }
       __syncthreads();
       const float ratio = next_gamma();
       if (ratio != 1.f) {                                // this tile is larger than every earlier one
@@ -707,8 +736,12 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     }
   }
   if constexpr (BLEND) {
+    for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
+    __syncthreads();                                       // the last tile's slots have been read
+    if (lane == 0) sRed[w] = dr_acc;
     __syncthreads();
-    if (tid == 0) dr_part[(size_t)bh * P + p] = (sRed[0] + sRed[1]) + (sRed[2] + sRed[3]);
+    if (tid == 0)
+      dr_part[(size_t)bh * P + p] = ((sRed[0] + sRed[1]) + (sRed[2] + sRed[3])) + ((sRed[4] + sRed[5]) + (sRed[6] + sRed[7]));
   }
 }
 
@@ -911,21 +944,18 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
     decltype(kernel)::value<<<dim3(p.P, p.BH), NTQ, smem, s>>>(
-        (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state, a.vbar, (uint16_t*)a.dq, a.partials, a.dw_part, a.blend_r, a.blend_in ? a.dr_part : nullptr, a.cs_part, p.H, p.n, p.P, p.rows);
+        (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state, a.vbar, (uint16_t*)a.dq, a.partials, a.dw_part,
+        (const uint16_t*)(a.blend_dr ? a.blend_in : nullptr), a.blend_r, a.dr_part, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
   if (a.blend_in) {
     e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, true, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, true, CENTRE, false>>{});
     if (e != hipSuccess) return e;
-    if (a.blend_dr) {
-      if ((e = launch_dot_centred_bf16(a.dout, a.blend_in, a.vbar, a.dr_part + (size_t)p.BH * p.P, p, s)) != hipSuccess) return e;
-      if ((e = launch_dr_reduce(a.dr_part, p.BH * p.P + kDotParts, a.blend_r, a.blend_dr, s)) != hipSuccess) return e;
-    }
   } else {
     e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, false, CENTRE, false>>{});
     if (e != hipSuccess) return e;
   }
-  if ((e = launch_state_reduce(a.partials, a.dstate, p, s)) != hipSuccess) return e;
+  if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
   auto launch_k = [&](auto kernel, size_t smem) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;

@@ -602,9 +602,8 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   else
     e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, false>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
   if (e != hipSuccess) return e;
-  if (a.blend_in && a.blend_dr && (e = launch_dr_reduce(a.dr_part, p.BH * p.KP, a.blend_r, a.blend_dr, s)) != hipSuccess) return e;
   if ((e = run_state_pass<D, KIND, T, true>(a.q, a.dout, a.wq, weights, a.partials, p, s)) != hipSuccess) return e;
-  if ((e = launch_state_reduce_split(a.partials, a.dstate, p, s)) != hipSuccess) return e;
+  if ((e = launch_state_reduce_split(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.KP, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
   e = grad(KernelTag<grad_f32_kernel<D, KIND, T, false, false>>{}, a.k, a.v, a.wk, a.dstate, a.dk, du_k);
   if (e != hipSuccess) return e;
   if constexpr (KIND == kPhiHedgehog) {

@@ -19,8 +19,8 @@ constexpr int kCUs = 256;
 // kReluEps.
 constexpr int kPhiHedgehog = 1, kPhiRelu = 2;
 constexpr float kReluEps = 1e-6f;
-// Workgroups (= partial sums) of the streaming dot product sum(dout * s) of the mixed attention's dL/dr.
-constexpr int kDotParts = 1024;
+// Parts of dL/dr beyond one per workgroup of the bf16 query side: the fp32-arithmetic gradient kernel may have more workgroups.
+constexpr int kDrSlack = 1024;
 
 // Where the rows of q, k, v, out (and dout, dq, dk, dv) sit in memory, in elements: element
 // (b, h, t, c) is at b*sb + h*sh + t*sn + c.  [B,H,n,d]: sb = H*n*d, sh = n*d, sn = d;
@@ -170,7 +170,7 @@ struct Plan {
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
   size_t off_centre;      // bf16 backward: fp32 [BH][3][d] (mean value row vbar; the other two rows unused), then
                           // [BH][P][d+8] per-workgroup column sums of dO/den (d) and the sum of -delta/den (1)
-  size_t off_drpart;      // fp32 [BH][P] + [kDotParts]: per-workgroup parts of dL/dr (mixed attention, Eq. 6)
+  size_t off_drpart;      // fp32 [BH][P] + [kDrSlack]: per-workgroup parts of dL/dr (mixed attention, Eq. 6)
   size_t off_dwpart;      // fp32 [BH][P][d*d/2] partial dW~_q, then [BH][max(P, KP)][d*d/2] partial dW~_k (weight gradients only)
   size_t du_bytes;        // bytes of one dL/du region (0 in bf16 mode: dW~ is accumulated where du is made)
   size_t off_du_q;        // dL/du of the query side (weight gradients, fp32 arithmetic only): fp32 [BH][n][d/2]
@@ -225,10 +225,17 @@ hipError_t launch_state_partials_bf16(const void* k, const void* v, const void* 
                                       const Plan& p, hipStream_t s);
 // The same for the ReLU map (bf16); partial slots per head follow Plan::split as well.
 hipError_t launch_relu_state_bf16(const void* k, const void* v, float* partials, const Plan& p, hipStream_t s);
-// Fixed-order sum of the partials into the exported state layout [BH][d+1][d] fp32.
-hipError_t launch_state_reduce(const float* partials, float* state, const Plan& p, hipStream_t s);
+// dL/dr of the mixed attention: *dr = the count parts summed in a fixed order if 0 <= *r <= 1, else 0 (Eq. 6, clipped r); off where dr is null.
+struct DrSum {
+  const float* part;
+  int count;
+  const float* r;
+  float* dr;
+};
+// Fixed-order sum of the partials into the exported state layout [BH][d+1][d] fp32, and (one workgroup more) dL/dr.
+hipError_t launch_state_reduce(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s);
 // The same for the partials of the bf16 forward state pass (slots per head follow Plan::split).
-hipError_t launch_state_reduce_split(const float* partials, float* state, const Plan& p, hipStream_t s);
+hipError_t launch_state_reduce_split(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s);
 // phi(Q) S / (phi(Q) . z) and the store of out (Eq. 3, right-hand side).
 hipError_t launch_apply_f32(const void* q, const void* wq, const float* state, void* out,
                             const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s);
@@ -244,10 +251,5 @@ hipError_t launch_dw_reduce2(const float* part0, float* dw0, int P0, const float
 hipError_t launch_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
 hipError_t launch_bwd_f32(const BwdArgs& a, const Plan& p, hipStream_t s);
 hipError_t launch_relu_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
-// part[0 .. kDotParts-1] = partial sums of sum_i a[i] * (b[i] - vbar[bh(i)][channel(i)]) over two bf16 token tensors in the
-// plan's layout; vbar fp32 [BH][d].
-hipError_t launch_dot_centred_bf16(const void* a, const void* b, const float* vbar, float* part, const Plan& p, hipStream_t s);
-// dr = sum of the count parts in a fixed order if 0 <= *r <= 1, else 0 (Eq. 6, clipped r).
-hipError_t launch_dr_reduce(const float* part, int count, const float* r, float* dr, hipStream_t s);
 
 }  // namespace linattn

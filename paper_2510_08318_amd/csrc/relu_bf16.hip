@@ -641,7 +641,7 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   relu_bwd_q_kernel<D><<<dim3(p.P, p.BH), NTQ, q_smem<D>(), s>>>((const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, a.vbar,
                                                                 (uint16_t*)a.dq, a.partials, p.H, p.n, p.P, p.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_state_reduce(a.partials, a.dstate, p, s)) != hipSuccess) return e;
+  if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{}, s)) != hipSuccess) return e;
   if ((e = set_smem_once<relu_bwd_k_kernel<D>>(k_smem<D>())) != hipSuccess) return e;
   relu_bwd_k_kernel<D><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>((const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar,
                                                                  (uint16_t*)a.dk, (uint16_t*)a.dv, p.H, p.n, p.rows);

@@ -5,15 +5,37 @@
 namespace linattn {
 namespace {
 
+// The parts of dL/dr (Eq. 6) summed in a fixed order by one workgroup of 256; zero outside the clip's range [0, 1].
+__device__ __forceinline__ void sum_dr(const DrSum& d) {
+  __shared__ float red[256];
+  float acc = 0.f;
+  for (int i = threadIdx.x; i < d.count; i += 256) acc += d.part[i];
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int m = 128; m >= 1; m >>= 1) {
+    if ((int)threadIdx.x < m) red[threadIdx.x] += red[threadIdx.x + m];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const float rv = *d.r;
+    *d.dr = (rv >= 0.f && rv <= 1.f) ? red[0] : 0.f;
+  }
+}
+
 // state[bh][e] = sum over the slots p of partials[bh][p][e], four adjacent elements per thread.  GROUPS threads share an element:
 // each sums a contiguous share of the slots, eight loads in flight and added pairwise, and the shares are combined pairwise
 // through LDS; the order is fixed by the shape, so the result is reproducible, and the longest chain of roundings is short
 // (256 slots: 2 + 3 + 4 levels where one running sum has 256).
 // SPLIT: the slots of head bh are those of the workgroups whose tile ranges touch it (Split), of sp.PS allocated; otherwise P.
+// Workgroup (columns, 0), if there is one, takes dL/dr (as a launch of its own 4.7 us).
 template <int GROUPS, bool SPLIT>
 __global__ __launch_bounds__(256) void state_reduce_kernel(const float4* __restrict__ partials, float4* __restrict__ state,
-                                                           Split sp, int P, int elems4) {
+                                                           Split sp, int P, int elems4, int columns, DrSum dr) {
   constexpr int EL = 256 / GROUPS;
+  if ((int)blockIdx.x == columns) {
+    if (blockIdx.y == 0) sum_dr(dr);
+    return;
+  }
   __shared__ float4 red[GROUPS > 1 ? 256 : 1];
   const int el = threadIdx.x % EL, grp = threadIdx.x / EL;
   const int e = blockIdx.x * EL + el;
@@ -86,111 +108,37 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict_
   dw[(size_t)h * elems + e] = acc;
 }
 
-// dL/dr of the mixed attention (Eq. 6): the per-workgroup parts summed in a fixed order by one
-// workgroup; zero outside the clip's range [0, 1].
-__global__ __launch_bounds__(256) void dr_reduce_kernel(const float* __restrict__ part, int count,
-                                                        const float* __restrict__ r, float* __restrict__ dr) {
-  __shared__ float red[256];
-  float acc = 0.f;
-  for (int i = threadIdx.x; i < count; i += 256) acc += part[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int m = 128; m >= 1; m >>= 1) {
-    if ((int)threadIdx.x < m) red[threadIdx.x] += red[threadIdx.x + m];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const float rv = *r;
-    *dr = (rv >= 0.f && rv <= 1.f) ? red[0] : 0.f;
-  }
-}
-
-__device__ __forceinline__ uint4 ld_nt16(const uint4* p) {
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-}
-
-// part[blockIdx.x] = sum over this workgroup's share of a[i] * (b[i] - vbar[bh(i)][ch(i)]), for bf16 a, b
-// in the layout `rw` of the token tensors (d a power of two).  The query-side backward works with the output
-// minus vbar; this is the matching form of the sum dout . s of the mixed attention's dL/dr.
-__global__ __launch_bounds__(256) void dot_centred_bf16_kernel(const uint4* __restrict__ a, const uint4* __restrict__ b,
-                                                               const float* __restrict__ vbar, size_t n16,
-                                                               float* __restrict__ part, int n, int H, int d, int bnhd) {
-  __shared__ float red[4];
-  float acc = 0.f;
-  const int dshift = d == 128 ? 7 : 6;
-  auto term = [&](uint4 x, uint4 y, size_t i) {
-    const size_t e0 = i * 8, row = e0 >> dshift;
-    const int ch = (int)(e0 & (size_t)(d - 1));
-    size_t bh;
-    if (bnhd) { const size_t bt = row / (size_t)H; bh = (bt / (size_t)n) * H + (row - bt * H); }
-    else bh = row / (size_t)n;
-    const float* vb = vbar + bh * d + ch;
-    const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      acc = fmaf(__builtin_bit_cast(float, xs[j] << 16), __builtin_bit_cast(float, ys[j] << 16) - vb[2 * j], acc);
-      acc = fmaf(__builtin_bit_cast(float, xs[j] & 0xffff0000u), __builtin_bit_cast(float, ys[j] & 0xffff0000u) - vb[2 * j + 1], acc);
-    }
-  };
-  const size_t stride = (size_t)gridDim.x * 256;
-  size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  for (; i + 3 * stride < n16; i += 4 * stride) {
-    uint4 x[4], y[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) { x[u] = ld_nt16(a + i + u * stride); y[u] = ld_nt16(b + i + u * stride); }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) term(x[u], y[u], i + u * stride);
-  }
-  for (; i < n16; i += stride) term(a[i], b[i], i);
-  for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
 }  // namespace
-
-hipError_t launch_dot_centred_bf16(const void* a, const void* b, const float* vbar, float* part, const Plan& p, hipStream_t s) {
-  const size_t elems = (size_t)p.BH * p.n * p.d;
-  dot_centred_bf16_kernel<<<kDotParts, 256, 0, s>>>((const uint4*)a, (const uint4*)b, vbar, elems / 8, part, p.n, p.H, p.d,
-                                                    p.rows.sn != (size_t)p.d);
-  return hipGetLastError();
-}
-
-hipError_t launch_dr_reduce(const float* part, int count, const float* r, float* dr, hipStream_t s) {
-  dr_reduce_kernel<<<1, 256, 0, s>>>(part, count, r, dr);
-  return hipGetLastError();
-}
 
 namespace {
 template <int GROUPS, bool SPLIT>
-void run_state_reduce(const float* partials, float* state, const Plan& p, hipStream_t s) {
+void run_state_reduce(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s) {
   const int elems4 = (int)(p.state_elems / 4);      // (d+1) d is a multiple of 4; both buffers are 16-byte aligned
   constexpr int EL = 256 / GROUPS;
-  state_reduce_kernel<GROUPS, SPLIT><<<dim3((elems4 + EL - 1) / EL, p.BH), 256, 0, s>>>(
-      reinterpret_cast<const float4*>(partials), reinterpret_cast<float4*>(state), p.split, p.P, elems4);
+  const int columns = (elems4 + EL - 1) / EL;
+  state_reduce_kernel<GROUPS, SPLIT><<<dim3(columns + (dr.dr != nullptr), p.BH), 256, 0, s>>>(
+      reinterpret_cast<const float4*>(partials), reinterpret_cast<float4*>(state), p.split, p.P, elems4, columns, dr);
 }
 // One thread per four elements while its slots fit one batch of loads, more threads with more slots.  Measured after a fresh
 // write of the partials, with about 4 us of event overhead, one / four / sixteen threads, width 128: 40 heads of 8 slots 7.9 /
 // 8.8 / 15.6 us; 20 of 14: 8.0 / 7.7 / 10.4; 12 of 22: 7.8 / 7.4 / 9.1; 4 of 64: 8.6 / 7.6 / 7.5; 2 of 128: 11.9 / 8.3 / 7.3;
 // 1 of 256: 18.0 / 9.1 / 7.5.
 template <bool SPLIT>
-hipError_t state_reduce_any(const float* partials, float* state, const Plan& p, hipStream_t s) {
+hipError_t state_reduce_any(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s) {
   const int slots = SPLIT ? p.split.PS : p.P;
-  if (slots <= 8) run_state_reduce<1, SPLIT>(partials, state, p, s);
-  else if (slots <= 32) run_state_reduce<4, SPLIT>(partials, state, p, s);
-  else run_state_reduce<16, SPLIT>(partials, state, p, s);
+  if (slots <= 8) run_state_reduce<1, SPLIT>(partials, state, p, dr, s);
+  else if (slots <= 32) run_state_reduce<4, SPLIT>(partials, state, p, dr, s);
+  else run_state_reduce<16, SPLIT>(partials, state, p, dr, s);
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_state_reduce(const float* partials, float* state, const Plan& p, hipStream_t s) {
-  return state_reduce_any<false>(partials, state, p, s);
+hipError_t launch_state_reduce(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s) {
+  return state_reduce_any<false>(partials, state, p, dr, s);
 }
 
-hipError_t launch_state_reduce_split(const float* partials, float* state, const Plan& p, hipStream_t s) {
-  return state_reduce_any<true>(partials, state, p, s);
+hipError_t launch_state_reduce_split(const float* partials, float* state, const Plan& p, const DrSum& dr, hipStream_t s) {
+  return state_reduce_any<true>(partials, state, p, dr, s);
 }
 
 hipError_t launch_dw_reduce2(const float* part0, float* dw0, int P0, const float* part1, float* dw1, int P1, const Plan& p, hipStream_t s) {
