@@ -175,6 +175,15 @@ constexpr size_t grad_smem() {
   return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * GImage<D, false>::IMG) * sizeof(uint4) + (D + 2 * NT8 / 64) * sizeof(float);
 }
 
+// dL/du rows: non-temporal where both sides' would push each other and the rows that follow out of the last-level cache (256 MB) before
+// dw_f32_kernel reads them.  Ordinary / non-temporal, us: 12 heads x 32760 x 128 (201 MB) dw 99.5 / 86, key side 149 / 147, query side 101 / 102; 5 x
+// 20000 x 128 (51 MB) dw 47 / 49, gradients 147 / 144.
+constexpr size_t kDuStreamBytes = 128u << 20;
+__device__ __forceinline__ void put_du(float4* p, float4 v, int stream) {
+  if (stream) st_nt(reinterpret_cast<uint4*>(p), __builtin_bit_cast(uint4, v));
+  else *p = v;
+}
+
 // 8 wavefronts, one workgroup per compute unit, each wavefront on its own 32-token blocks (a lane pair owns a token).
 // QSIDE: x = q, y = dO, M = (S, z); leaves the weights of the sum over tokens, {om / den, -om delta / den}, in weights[bh][t] and
 // (BLEND, dr_part not null) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.  s is read for
@@ -185,7 +194,7 @@ constexpr size_t grad_smem() {
 template <int D, int KIND, typename T, bool QSIDE, bool BLEND>
 __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
                                                        const float* __restrict__ state, T* __restrict__ dx, T* __restrict__ dv,
-                                                       float* __restrict__ du_ws,
+                                                       float* __restrict__ du_ws, int du_stream,
                                                        float2* __restrict__ weights, const T* __restrict__ blend,
                                                        const float* __restrict__ rptr, float* __restrict__ dr_part,
                                                        int H, int n, Rows rw) {
@@ -388,7 +397,7 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
         float4* dst = reinterpret_cast<float4*>(du_ws + ((size_t)bh * n + b * 32) * C::HALF);
         const int nb = n - b * 32 < 32 ? n - b * 32 : 32;
 #pragma unroll
-        for (int j = 0; j < C::LOC / 4; ++j) dst[(2 * j + g) * nb + c] = make_float4(du[4 * j], du[4 * j + 1], du[4 * j + 2], du[4 * j + 3]);
+        for (int j = 0; j < C::LOC / 4; ++j) put_du(dst + (2 * j + g) * nb + c, make_float4(du[4 * j], du[4 * j + 1], du[4 * j + 2], du[4 * j + 3]), du_stream);
       }
       // dx = du W~^T, tokens on the accumulator rows
       f32x16 xa[1][MB];
@@ -591,7 +600,7 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   auto grad = [&](auto kernel, const void* x, const void* y, const void* wx, const float* state, void* dx, float* du) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
-    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, (T*)a.dv, du, weights,
+    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, (T*)a.dv, du, 2 * p.du_bytes > kDuStreamBytes, weights,
                                                     (const T*)a.blend_in, a.blend_r, a.blend_dr ? a.dr_part : nullptr, p.H, p.n, p.rows);
     return hipGetLastError();
   };
