@@ -10,6 +10,7 @@
 #include "f32_split.h"
 #include "f32_plain.h"
 #include "f32_state.h"
+#include "f32_apply.h"
 
 namespace linattn {
 namespace {
@@ -170,6 +171,9 @@ struct GImage {
   }
 };
 
+// Where an even deal of the gradient kernels is considered: fp32 rows of width 128 have no registers for its loop, and width 64 has little to gain.
+template <int D, typename T> constexpr bool grad_even = D == 128 && kPieces<T> == 1;
+
 template <int D, int KIND, typename T>
 constexpr size_t grad_smem() {
   return ((KIND == kPhiRelu ? 0 : kPieces<T> * WImage<D>::IMG) + 3 * GImage<D, false>::IMG) * sizeof(uint4) + (D + 2 * NT8 / 64) * sizeof(float);
@@ -191,13 +195,13 @@ __device__ __forceinline__ void put_du(float4* p, float4 v, int stream) {
 // Key side: x = k, y = v, M = (dS, dz); dv = phi(k) dS as well, from the same image.  As a pass of its own it read k, formed phi and built an
 // image once more; two passes / this one, us: 12 heads x 32760 x 128 with bf16 tensors 97 + 80 / 161, 5 x 20000 x 128 fp32 61 + 37 / 84, 2 x
 // 1024 x 64 fp32 12.3 + 7.8 / 15.4.  du_ws (nullable): dL/du rows for dW~.
-template <int D, int KIND, typename T, bool QSIDE, bool BLEND>
+template <int D, int KIND, typename T, bool QSIDE, bool BLEND, bool EVEN>
 __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
                                                        const float* __restrict__ state, T* __restrict__ dx, T* __restrict__ dv,
                                                        float* __restrict__ du_ws, int du_stream,
                                                        float2* __restrict__ weights, const T* __restrict__ blend,
                                                        const float* __restrict__ rptr, float* __restrict__ dr_part,
-                                                       int H, int n, Rows rw) {
+                                                       int H, int n, Split deal, Rows rw) {
   using C = Cfg<D>;
   using L = ApplyLayout<D>;
   using W = WImage<D>;
@@ -210,240 +214,247 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
   float* sRed = sZ + D;
   int* sPlain = reinterpret_cast<int*>(sRed + NT8 / 64);   // [8] the wavefront has met a state value that does not split (f32_plain.h)
 
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32, c = lane % 32;
-  const int bh = blockIdx.y, h = bh % H;
-  const T* xb = x + head_base(rw, bh, H);
-  const T* yb = y + head_base(rw, bh, H);
-  T* dxb = dx + head_base(rw, bh, H);
-  T* dvb = QSIDE ? nullptr : dv + head_base(rw, bh, H);
-  const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;
-  float dr_acc = 0.f;
-  const float* sb = state + (size_t)bh * (D + 1) * D;
+  float dr_sum = 0.f;
+  // EVEN: the deal may give the workgroup parts of two heads
+  for (Share sh = EVEN ? first_share(deal, blockIdx.x, blockIdx.y) : head_share(deal, blockIdx.x, blockIdx.y); sh.there;
+       sh = EVEN ? next_share(deal, blockIdx.x, sh) : Share{}) {
+    // (from a thread index that the optimiser cannot hoist: what depends on it would be held, or spilled, across the loop)
+    const int tid = EVEN ? (threadIdx.x + opaque_zero()) & (NT8 - 1) : threadIdx.x, lane = tid % 64, g = lane / 32, c = lane % 32;
+    const int bh = sh.bh, h = bh % H;
+    const T* xb = x + head_base(rw, bh, H);
+    const T* yb = y + head_base(rw, bh, H);
+    T* dxb = dx + head_base(rw, bh, H);
+    T* dvb = QSIDE ? nullptr : dv + head_base(rw, bh, H);
+    const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+    float dr_acc = 0.f;
+    const float* sb = state + (size_t)bh * (D + 1) * D;
 
-  const int nblk = (n + 31) / 32, stride = gridDim.x * (NT8 / 64);
-  RowOctets<D, T> xr, yr;
-  auto row_of = [&](const T* base, int b) {
-    const int t = b * 32 + c;
-    return base + (size_t)(t < n ? t : n - 1) * rw.sn;
-  };
-  int b = blockIdx.x * (NT8 / 64) + w;
-  const int b_first = b < nblk ? b : nblk - 1;
-  xr.load(row_of(xb, b_first), g);
-  if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
-  const bool state_splits = GI::template build<KIND, NT8>(sb, sG, tid);
-  if (lane == 0) sPlain[w] = 0;
-  if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
-  build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
-  __syncthreads();
+    const int all = (n + 31) / 32, nblk = all < sh.end * (NT8 / 64) ? all : sh.end * (NT8 / 64), stride = sh.step * (NT8 / 64);
+    RowOctets<D, T> xr, yr;
+    auto row_of = [&](const T* base, int b) {
+      const int t = b * 32 + c;
+      return base + (size_t)(t < n ? t : n - 1) * rw.sn;
+    };
+    int b = sh.u * (NT8 / 64) + w;
+    const int b_first = b < nblk ? b : nblk - 1;
+    xr.load(row_of(xb, b_first), g);
+    if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
+    const bool state_splits = GI::template build<KIND, NT8>(sb, sG, tid);
+    if (lane == 0) sPlain[w] = 0;
+    if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
+    build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
+    __syncthreads();
 
-  const int b_own = b;
-  const bool state_plain = any_of_8(sPlain);
-  float chk = 0.f;                                         // NaN once the lane has met what does not split
-  for (; b < nblk; b += stride) {
-    const int t = b * 32 + c;
-    const bool valid = t < n;
-    if constexpr (QSIDE || NX == 1) yr.load(row_of(yb, b), g);
-    float ds = 0.f;                                                // dO . s on the lane's channels, while few registers are live
-    if constexpr (BLEND) {
-      if (dr_part != nullptr) {
-        // two octets at a time: a third row beside those of x and y does not fit the registers
-        const T* srow = row_of(bb, b);
-        RowOctets<D, T> sr;
-#pragma unroll
-        for (int k0 = 0; k0 < D / 16; k0 += 2) {
-          sr.load(srow, g, k0, k0 + 2);
-#pragma unroll
-          for (int ks = k0; ks < k0 + 2; ++ks) {
-            float a[8], s8[8];
-            yr.values(ks, a);
-            sr.values(ks, s8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ds = fmaf(a[e], s8[e], ds);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    float f[D / 2];
-    if constexpr (KIND == kPhiHedgehog) {
-      f32x16 u[C::UM][1];
-      W::template project<T>(xr, sW, lane + opaque_zero(), u);
-      softmax_octets<D>(u, f);
-    } else {
-      phi_octets<D, KIND, T>(xr, nullptr, lane, f);
-    }
-    if constexpr (!QSIDE) {
-      f32x16 o[1][MB];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) o[0][mb] = zero16();
-      const int base = GI::column_base(lane + opaque_zero());
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        uint4 a[1][3], m[MB][3];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int i = 0; i < 3; ++i) m[mb][i] = GI::column_operand(sG, i, ks, mb, base);
-        split8(f + 8 * ks, a[0]);
-        mfma_pieces<3, 3>(a, m, o);
-      }
-      if constexpr (KIND == kPhiRelu) {
-        // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
-#pragma unroll
-        for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
-      }
-      // (fp32 rows do not fit the registers beside the accumulators; before the stores: a wait for them must not wait for the stores)
-      if constexpr (NX != 1) yr.load(row_of(yb, b), g);
-      store_rows<D, T>(dvb, rw.sn, b * 32, n, (lane & 32) + GI::column(c), [&](int r, int mb) { return o[0][mb][r]; });
-    }
-    float inv = 0.f;
-    const float* z = sZ + opaque_zero();
-    if constexpr (QSIDE) inv = 1.0f / (octet_dot<D>(f, z, g) + (KIND == kPhiRelu ? kReluEps : 0.f));
-
-    // G = y M^T on the lane's features
-    f32x16 ga[MB][1];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) ga[mb][0] = zero16();
-    const int lg = lane + opaque_zero();
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      uint4 a[MB][3], yp[1][NX];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) a[mb][i] = GI::row_operand(sG, i, ks, mb, lg);
-      GI::template y_pieces<T>(yr, ks, yp[0]);
-      mfma_pieces<3, NX>(a, yp, ga);
-    }
-    // a y that does not split makes every feature of its token NaN or Inf, phi from an x that does not is NaN: one value tells
-    // (Hedgehog: the sums of the Jacobian, below)
-    if constexpr (KIND == kPhiRelu) chk = fmaf(ga[0][0][0], 0.f, chk);
-    // dL/dphi / gscale.  The factor om / den of the query side is applied to du: fewer products, and the gr that the sums of the Jacobian take
-    // is the one they are subtracted from (a product fused into that subtraction is not), so that a saturated token's du is zero.
-    float gr[D / 2], gscale = 1.f;
-    if constexpr (QSIDE) {
-      float part = 0.f;
-#pragma unroll
-      for (int i = 0; i < D / 2; ++i) part = fmaf(f[i], ga[i / 16][0][i % 16], part);
-      part *= inv;
+    const int b_own = b;
+    const bool state_plain = any_of_8(sPlain);
+    float chk = 0.f;                                         // NaN once the lane has met what does not split
+    for (; b < nblk; b += stride) {
+      const int t = b * 32 + c;
+      const bool valid = t < n;
+      if constexpr (QSIDE || NX == 1) yr.load(row_of(yb, b), g);
+      float ds = 0.f;                                                // dO . s on the lane's channels, while few registers are live
       if constexpr (BLEND) {
-        if (valid) dr_acc += ds - part;
+        if (dr_part != nullptr) {
+          // two octets at a time: a third row beside those of x and y does not fit the registers
+          const T* srow = row_of(bb, b);
+          RowOctets<D, T> sr;
+#pragma unroll
+          for (int k0 = 0; k0 < D / 16; k0 += 2) {
+            sr.load(srow, g, k0, k0 + 2);
+#pragma unroll
+            for (int ks = k0; ks < k0 + 2; ++ks) {
+              float a[8], s8[8];
+              yr.values(ks, a);
+              sr.values(ks, s8);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) ds = fmaf(a[e], s8[e], ds);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
-      float lo, hi;
-      pair32(part, lo, hi);
-      const float delta = lo + hi;
-      if constexpr (KIND == kPhiRelu) chk = fmaf(delta, 0.f, chk);
-      const float a = inv * om;
-      if (valid && g == 0) weights[(size_t)bh * n + t] = make_float2(a, -delta * a);
+      float f[D / 2];
+      if constexpr (KIND == kPhiHedgehog) {
+        f32x16 u[C::UM][1];
+        W::template project<T>(xr, sW, lane + opaque_zero(), u);
+        softmax_octets<D>(u, f);
+      } else {
+        phi_octets<D, KIND, T>(xr, nullptr, lane, f);
+      }
+      if constexpr (!QSIDE) {
+        f32x16 o[1][MB];
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int i = 8 * ks + e;
-          gr[i] = ga[i / 16][0][i % 16] - delta * z[(2 * ks + g) * 8 + e];
-        }
-      gscale = a;
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int i = 8 * ks + e;
-          gr[i] = ga[i / 16][0][i % 16] + z[(2 * ks + g) * 8 + e];
-        }
-    }
-
-    if constexpr (KIND == kPhiRelu) {
-      // the derivative of max(x, 0) at 0 is 0; the lane's octets of its own row
-      if (valid) {
-        T* row = dxb + (size_t)t * rw.sn;
+        for (int mb = 0; mb < MB; ++mb) o[0][mb] = zero16();
+        const int base = GI::column_base(lane + opaque_zero());
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) {
-          float v[8];
+          uint4 a[1][3], m[MB][3];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] > 0.f ? (QSIDE ? gr[8 * ks + e] * gscale : gr[8 * ks + e]) : 0.f;
-          uint4* dst = reinterpret_cast<uint4*>(row + 16 * ks + 8 * g);
-          if constexpr (sizeof(T) == 2) {
-            *dst = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-          } else {
-            float4* d4 = reinterpret_cast<float4*>(dst);
-            d4[0] = make_float4(v[0], v[1], v[2], v[3]);
-            d4[1] = make_float4(v[4], v[5], v[6], v[7]);
-          }
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) m[mb][i] = GI::column_operand(sG, i, ks, mb, base);
+          split8(f + 8 * ks, a[0]);
+          mfma_pieces<3, 3>(a, m, o);
         }
+        if constexpr (KIND == kPhiRelu) {
+          // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
+#pragma unroll
+          for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
+        }
+        // (fp32 rows do not fit the registers beside the accumulators; before the stores: a wait for them must not wait for the stores)
+        if constexpr (NX != 1) yr.load(row_of(yb, b), g);
+        store_rows<D, T>(dvb, rw.sn, b * 32, n, (lane & 32) + GI::column(c), [&](int r, int mb) { return o[0][mb][r]; });
       }
-      xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
-    } else {
-      xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
-      // softmax Jacobian of Eq. 5
-      float cp = 0.f, cm = 0.f;
+      float inv = 0.f;
+      const float* z = sZ + opaque_zero();
+      if constexpr (QSIDE) inv = 1.0f / (octet_dot<D>(f, z, g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+
+      // G = y M^T on the lane's features
+      f32x16 ga[MB][1];
 #pragma unroll
-      for (int j = 0; j < C::LOC; ++j) { cp = fmaf(gr[j], f[j], cp); cm = fmaf(gr[C::LOC + j], f[C::LOC + j], cm); }
-      float lo, hi;
-      pair32(cp, lo, hi); cp = lo + hi;
-      pair32(cm, lo, hi); cm = lo + hi;
-      chk = fmaf(cp + cm, 0.f, chk);
-      float du[C::LOC];
+      for (int mb = 0; mb < MB; ++mb) ga[mb][0] = zero16();
+      const int lg = lane + opaque_zero();
 #pragma unroll
-      for (int j = 0; j < C::LOC; ++j) {
-        du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
-        if constexpr (QSIDE) du[j] *= gscale;
-      }
-      if (du_ws != nullptr && valid) {
-        // blocks of 32 tokens as the lanes hold them, 1 KB a store (see dw_f32_kernel)
-        float4* dst = reinterpret_cast<float4*>(du_ws + ((size_t)bh * n + b * 32) * C::HALF);
-        const int nb = n - b * 32 < 32 ? n - b * 32 : 32;
-#pragma unroll
-        for (int j = 0; j < C::LOC / 4; ++j) put_du(dst + (2 * j + g) * nb + c, make_float4(du[4 * j], du[4 * j + 1], du[4 * j + 2], du[4 * j + 3]), du_stream);
-      }
-      // dx = du W~^T, tokens on the accumulator rows
-      f32x16 xa[1][MB];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) xa[0][mb] = zero16();
-      const int lz = lane + opaque_zero();
-#pragma unroll
-      for (int ks = 0; ks < W::KS; ++ks) {
-        uint4 a[1][3], wb[MB][NX];
+      for (int ks = 0; ks < D / 16; ++ks) {
+        uint4 a[MB][3], yp[1][NX];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int i = 0; i < NX; ++i) wb[mb][i] = sW[i * W::IMG + W::place(ks, mb, lz)];
-        split8(du + 8 * ks, a[0]);
-        mfma_pieces<3, NX>(a, wb, xa);
+          for (int i = 0; i < 3; ++i) a[mb][i] = GI::row_operand(sG, i, ks, mb, lg);
+        GI::template y_pieces<T>(yr, ks, yp[0]);
+        mfma_pieces<3, NX>(a, yp, ga);
       }
-      store_rows<D, T>(dxb, rw.sn, b * 32, n, lane, [&](int r, int mb) { return xa[0][mb][r]; });
+      // a y that does not split makes every feature of its token NaN or Inf, phi from an x that does not is NaN: one value tells
+      // (Hedgehog: the sums of the Jacobian, below)
+      if constexpr (KIND == kPhiRelu) chk = fmaf(ga[0][0][0], 0.f, chk);
+      // dL/dphi / gscale.  The factor om / den of the query side is applied to du: fewer products, and the gr that the sums of the Jacobian take
+      // is the one they are subtracted from (a product fused into that subtraction is not), so that a saturated token's du is zero.
+      float gr[D / 2], gscale = 1.f;
+      if constexpr (QSIDE) {
+        float part = 0.f;
+#pragma unroll
+        for (int i = 0; i < D / 2; ++i) part = fmaf(f[i], ga[i / 16][0][i % 16], part);
+        part *= inv;
+        if constexpr (BLEND) {
+          if (valid) dr_acc += ds - part;
+        }
+        float lo, hi;
+        pair32(part, lo, hi);
+        const float delta = lo + hi;
+        if constexpr (KIND == kPhiRelu) chk = fmaf(delta, 0.f, chk);
+        const float a = inv * om;
+        if (valid && g == 0) weights[(size_t)bh * n + t] = make_float2(a, -delta * a);
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int i = 8 * ks + e;
+            gr[i] = ga[i / 16][0][i % 16] - delta * z[(2 * ks + g) * 8 + e];
+          }
+        gscale = a;
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int i = 8 * ks + e;
+            gr[i] = ga[i / 16][0][i % 16] + z[(2 * ks + g) * 8 + e];
+          }
+      }
+
+      if constexpr (KIND == kPhiRelu) {
+        // the derivative of max(x, 0) at 0 is 0; the lane's octets of its own row
+        if (valid) {
+          T* row = dxb + (size_t)t * rw.sn;
+#pragma unroll
+          for (int ks = 0; ks < D / 16; ++ks) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] > 0.f ? (QSIDE ? gr[8 * ks + e] * gscale : gr[8 * ks + e]) : 0.f;
+            uint4* dst = reinterpret_cast<uint4*>(row + 16 * ks + 8 * g);
+            if constexpr (sizeof(T) == 2) {
+              *dst = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+            } else {
+              float4* d4 = reinterpret_cast<float4*>(dst);
+              d4[0] = make_float4(v[0], v[1], v[2], v[3]);
+              d4[1] = make_float4(v[4], v[5], v[6], v[7]);
+            }
+          }
+        }
+        xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
+      } else {
+        xr.load(row_of(xb, b + stride < nblk ? b + stride : b), g);
+        // softmax Jacobian of Eq. 5
+        float cp = 0.f, cm = 0.f;
+#pragma unroll
+        for (int j = 0; j < C::LOC; ++j) { cp = fmaf(gr[j], f[j], cp); cm = fmaf(gr[C::LOC + j], f[C::LOC + j], cm); }
+        float lo, hi;
+        pair32(cp, lo, hi); cp = lo + hi;
+        pair32(cm, lo, hi); cm = lo + hi;
+        chk = fmaf(cp + cm, 0.f, chk);
+        float du[C::LOC];
+#pragma unroll
+        for (int j = 0; j < C::LOC; ++j) {
+          du[j] = f[j] * (gr[j] - cp) - f[C::LOC + j] * (gr[C::LOC + j] - cm);
+          if constexpr (QSIDE) du[j] *= gscale;
+        }
+        if (du_ws != nullptr && valid) {
+          // blocks of 32 tokens as the lanes hold them, 1 KB a store (see dw_f32_kernel)
+          float4* dst = reinterpret_cast<float4*>(du_ws + ((size_t)bh * n + b * 32) * C::HALF);
+          const int nb = n - b * 32 < 32 ? n - b * 32 : 32;
+#pragma unroll
+          for (int j = 0; j < C::LOC / 4; ++j) put_du(dst + (2 * j + g) * nb + c, make_float4(du[4 * j], du[4 * j + 1], du[4 * j + 2], du[4 * j + 3]), du_stream);
+        }
+        // dx = du W~^T, tokens on the accumulator rows
+        f32x16 xa[1][MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) xa[0][mb] = zero16();
+        const int lz = lane + opaque_zero();
+#pragma unroll
+        for (int ks = 0; ks < W::KS; ++ks) {
+          uint4 a[1][3], wb[MB][NX];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < NX; ++i) wb[mb][i] = sW[i * W::IMG + W::place(ks, mb, lz)];
+          split8(du + 8 * ks, a[0]);
+          mfma_pieces<3, NX>(a, wb, xa);
+        }
+        store_rows<D, T>(dxb, rw.sn, b * 32, n, lane, [&](int r, int mb) { return xa[0][mb][r]; });
+      }
     }
-  }
-  if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
-    __threadfence();                                       // what is stored above is written again
-    dr_acc = 0.f;
-    float dr = 0.f;
+    if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
+      __threadfence();                                       // what is stored above is written again
+      dr_acc = 0.f;
+      float dr = 0.f;
 #pragma unroll 1
-    for (b = b_own; b < nblk; b += stride)
+      for (b = b_own; b < nblk; b += stride)
 #pragma unroll 1
-      for (int tt = 0; tt < 32 && 32 * b + tt < n; ++tt) {
-        const int t = 32 * b + tt;
-        const size_t at = (size_t)t * rw.sn;
-        float* du = du_ws != nullptr ? du_ws + ((size_t)bh * n + b * 32) * C::HALF + 4 * tt : nullptr;
-        Plain<D, KIND, T>::template grad<QSIDE, BLEND>(xb + at, yb + at, wx + (size_t)h * D * C::HALF, sb, dxb + at, du,
-                                                       n - b * 32 < 32 ? n - b * 32 : 32, QSIDE ? weights + (size_t)bh * n + t : nullptr,
-                                                       BLEND && dr_part != nullptr ? bb + at : nullptr, om, &dr, lane);
-        if constexpr (!QSIDE)
-          Plain<D, KIND, T>::template apply<false, false>(xb + at, wx + (size_t)h * D * C::HALF, sb, dvb + at, nullptr, 0.f, lane);
-      }
-    if (lane == 0) dr_acc = dr;
+        for (int tt = 0; tt < 32 && 32 * b + tt < n; ++tt) {
+          const int t = 32 * b + tt;
+          const size_t at = (size_t)t * rw.sn;
+          float* du = du_ws != nullptr ? du_ws + ((size_t)bh * n + b * 32) * C::HALF + 4 * tt : nullptr;
+          Plain<D, KIND, T>::template grad<QSIDE, BLEND>(xb + at, yb + at, wx + (size_t)h * D * C::HALF, sb, dxb + at, du,
+                                                         n - b * 32 < 32 ? n - b * 32 : 32, QSIDE ? weights + (size_t)bh * n + t : nullptr,
+                                                         BLEND && dr_part != nullptr ? bb + at : nullptr, om, &dr, lane);
+          if constexpr (!QSIDE)
+            Plain<D, KIND, T>::template apply<false, false>(xb + at, wx + (size_t)h * D * C::HALF, sb, dvb + at, nullptr, 0.f, lane);
+        }
+      if (lane == 0) dr_acc = dr;
+    }
+    if constexpr (BLEND) dr_sum += dr_acc;
+    if (EVEN && sh.rest < sh.hi) __syncthreads();        // the next head's images take the place of these
   }
   if (BLEND && dr_part != nullptr) {
-    for (int m = 32; m >= 1; m >>= 1) dr_acc += __shfl_xor(dr_acc, m, 64);
-    if (lane == 0) sRed[w] = dr_acc;
+    for (int m = 32; m >= 1; m >>= 1) dr_sum += __shfl_xor(dr_sum, m, 64);
+    if (threadIdx.x % 64 == 0) sRed[w] = dr_sum;
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
       float s = 0.f;
       for (int i = 0; i < NT8 / 64; ++i) s += sRed[i];
-      dr_part[(size_t)bh * gridDim.x + blockIdx.x] = s;
+      dr_part[gridDim.x * blockIdx.y + blockIdx.x] = s;
     }
   }
 }
@@ -593,27 +604,32 @@ constexpr size_t dw_smem() { return (size_t)4 * (D / 32) * (D / 64) * 16 * 64 * 
 template <int D, int KIND, typename T>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  const dim3 grid(p.KP, p.BH);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), grad_even<D, T> ? kF32Prologue : kNeverEven);
   constexpr size_t smem = grad_smem<D, KIND, T>();
   // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which the last pass writes
   float2* weights = static_cast<float2*>(a.dv);
-  auto grad = [&](auto kernel, const void* x, const void* y, const void* wx, const float* state, void* dx, float* du) -> hipError_t {
-    hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
-    if (e2 != hipSuccess) return e2;
-    decltype(kernel)::value<<<grid, NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, (T*)a.dv, du, 2 * p.du_bytes > kDuStreamBytes, weights,
-                                                    (const T*)a.blend_in, a.blend_r, a.blend_dr ? a.dr_part : nullptr, p.H, p.n, p.rows);
-    return hipGetLastError();
+  auto grad = [&](auto by_head, auto even, const void* x, const void* y, const void* wx, const float* state, void* dx, float* du) -> hipError_t {
+    auto launch = [&](auto kernel) -> hipError_t {
+      hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
+      if (e2 != hipSuccess) return e2;
+      decltype(kernel)::value<<<grid_of(deal), NT8, smem, s>>>((const T*)x, (const T*)y, (const T*)wx, state, (T*)dx, (T*)a.dv, du,
+                                                      2 * p.du_bytes > kDuStreamBytes, weights, (const T*)a.blend_in, a.blend_r,
+                                                      a.blend_dr ? a.dr_part : nullptr, p.H, p.n, deal, p.rows);
+      return hipGetLastError();
+    };
+    return deal.share ? launch(by_head) : launch(even);
   };
+  constexpr bool EV = grad_even<D, T>;
   float* du_q = a.dwq ? a.du_q : nullptr;
   float* du_k = a.dwk ? a.du_k : nullptr;
   if (KIND == kPhiHedgehog && a.blend_in)
-    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, KIND == kPhiHedgehog>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
+    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, KIND == kPhiHedgehog, false>>{}, KernelTag<grad_f32_kernel<D, KIND, T, true, KIND == kPhiHedgehog, EV>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
   else
-    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, false>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
+    e = grad(KernelTag<grad_f32_kernel<D, KIND, T, true, false, false>>{}, KernelTag<grad_f32_kernel<D, KIND, T, true, false, EV>>{}, a.q, a.dout, a.wq, a.state, a.dq, du_q);
   if (e != hipSuccess) return e;
   if ((e = run_state_pass<D, KIND, T, true>(a.q, a.dout, a.wq, weights, a.partials, p, s)) != hipSuccess) return e;
-  if ((e = launch_state_reduce_split(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.KP, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
-  e = grad(KernelTag<grad_f32_kernel<D, KIND, T, false, false>>{}, a.k, a.v, a.wk, a.dstate, a.dk, du_k);
+  if ((e = launch_state_reduce_split(a.partials, a.dstate, p, DrSum{a.dr_part, deal.G, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
+  e = grad(KernelTag<grad_f32_kernel<D, KIND, T, false, false, false>>{}, KernelTag<grad_f32_kernel<D, KIND, T, false, false, EV>>{}, a.k, a.v, a.wk, a.dstate, a.dk, du_k);
   if (e != hipSuccess) return e;
   if constexpr (KIND == kPhiHedgehog) {
     if (du_q || du_k) {

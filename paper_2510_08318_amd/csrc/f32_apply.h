@@ -14,11 +14,11 @@ template <int D, int KIND, typename T>
 constexpr size_t apply_smem() {
   return ((KIND == kPhiRelu ? 0 : kPieces<T> * Cfg<D>::W_IMG) + 3 * ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64) * sizeof(uint4) + (D + NT8 / 64) * sizeof(float);
 }
-template <int D, int KIND, typename T, bool BLEND>
+template <int D, int KIND, typename T, bool BLEND, bool EVEN>
 __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q, const T* __restrict__ wq,
                                                         const float* __restrict__ state, T* __restrict__ out,
                                                         const T* __restrict__ blend, const float* __restrict__ rptr,
-                                                        int H, int n, Rows rw) {
+                                                        int H, int n, Split deal, Rows rw) {
   using L = ApplyLayout<D>;
   constexpr int IMG = L::KS * L::MB * 64;
   extern __shared__ uint4 smem[];
@@ -27,97 +27,110 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
   float* sZ = reinterpret_cast<float*>(sS + 3 * IMG);
   int* sPlain = reinterpret_cast<int*>(sZ + D);            // [8] the wavefront has met a state value that does not split (f32_plain.h)
 
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32, c = lane % 32;
-  const int bh = blockIdx.y, h = bh % H;
-  const T* qb = q + head_base(rw, bh, H);
-  T* ob = out + head_base(rw, bh, H);
-  // mixed attention (Eq. 6): out = r' s + (1 - r') o with r' = clip(r, 0, 1)
-  const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
-  const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
-  const float* sb = state + (size_t)bh * (D + 1) * D;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  // EVEN: the deal may give the workgroup parts of two heads
+  for (Share sh = EVEN ? first_share(deal, blockIdx.x, blockIdx.y) : head_share(deal, blockIdx.x, blockIdx.y); sh.there;
+       sh = EVEN ? next_share(deal, blockIdx.x, sh) : Share{}) {
+    // (from a thread index that the optimiser cannot hoist: what depends on it would be held, or spilled, across the loop)
+    const int tid = EVEN ? (threadIdx.x + opaque_zero()) & (NT8 - 1) : threadIdx.x, lane = tid % 64, g = lane / 32, c = lane % 32;
+    const int bh = sh.bh, h = bh % H;
+    const T* qb = q + head_base(rw, bh, H);
+    T* ob = out + head_base(rw, bh, H);
+    // mixed attention (Eq. 6): out = r' s + (1 - r') o with r' = clip(r, 0, 1)
+    const T* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
+    const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
+    const float* sb = state + (size_t)bh * (D + 1) * D;
 
-  const int nblk = (n + 31) / 32, stride = gridDim.x * (NT8 / 64);
-  RowOctets<D, T> x;
-  auto load = [&](int b) {
-    const int t = b * 32 + c;
-    x.load(qb + (size_t)(t < n ? t : n - 1) * rw.sn, g);
-  };
-  int b = blockIdx.x * (NT8 / 64) + w;
-  load(b < nblk ? b : nblk - 1);
-  if constexpr (KIND == kPhiHedgehog) build_w_pieces<D, T, NT8>(wq + (size_t)h * D * (D / 2), sW, tid);
-  const bool state_splits = build_s_pieces<D, KIND, NT8>(sb, sS, tid);
-  if (lane == 0) sPlain[w] = 0;
-  if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
-  build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
-  __syncthreads();
+    const int all = (n + 31) / 32, nblk = all < sh.end * (NT8 / 64) ? all : sh.end * (NT8 / 64), stride = sh.step * (NT8 / 64);
+    RowOctets<D, T> x;
+    auto load = [&](int b) {
+      const int t = b * 32 + c;
+      x.load(qb + (size_t)(t < n ? t : n - 1) * rw.sn, g);
+    };
+    int b = sh.u * (NT8 / 64) + w;
+    load(b < nblk ? b : nblk - 1);
+    if constexpr (KIND == kPhiHedgehog) build_w_pieces<D, T, NT8>(wq + (size_t)h * D * (D / 2), sW, tid);
+    const bool state_splits = build_s_pieces<D, KIND, NT8>(sb, sS, tid);
+    if (lane == 0) sPlain[w] = 0;
+    if (!state_splits) sPlain[w] = 1;                        // (after lane 0's store: one wavefront's LDS operations are in order)
+    build_octet_vector<D, KIND, NT8>(sb + D * D, sZ, tid);
+    __syncthreads();
 
-  const int b_own = b;
-  const bool state_plain = any_of_8(sPlain);
-  float chk = 0.f;                                         // NaN once the lane has met what does not split
-  for (; b < nblk; b += stride) {
-    float f[D / 2];
-    phi_octets<D, KIND, T>(x, sW, lane, f);
-    load(b + stride < nblk ? b + stride : b);
-    const float inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
-    // phi is at most 1 and splits, unless an x or u that did not made its half NaN (and with it den)
-    if constexpr (KIND == kPhiHedgehog) chk = fmaf(inv * 0x1p8f, 0.f, chk);
-    f32x16 o[1][L::MB];
+    const int b_own = b;
+    const bool state_plain = any_of_8(sPlain);
+    float chk = 0.f;                                         // NaN once the lane has met what does not split
+    for (; b < nblk; b += stride) {
+      float f[D / 2];
+      phi_octets<D, KIND, T>(x, sW, lane, f);
+      load(b + stride < nblk ? b + stride : b);
+      const float inv = 1.0f / (octet_dot<D>(f, sZ + opaque_zero(), g) + (KIND == kPhiRelu ? kReluEps : 0.f));
+      // phi is at most 1 and splits, unless an x or u that did not made its half NaN (and with it den)
+      if constexpr (KIND == kPhiHedgehog) chk = fmaf(inv * 0x1p8f, 0.f, chk);
+      f32x16 o[1][L::MB];
 #pragma unroll
-    for (int mb = 0; mb < L::MB; ++mb) o[0][mb] = zero16();
-    const uint4* ss = sS + lane + opaque_zero();
+      for (int mb = 0; mb < L::MB; ++mb) o[0][mb] = zero16();
+      const uint4* ss = sS + lane + opaque_zero();
 #pragma unroll
-    for (int ks = 0; ks < L::KS; ++ks) {
-      uint4 a[1][3], s[L::MB][3];
+      for (int ks = 0; ks < L::KS; ++ks) {
+        uint4 a[1][3], s[L::MB][3];
 #pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
+        for (int mb = 0; mb < L::MB; ++mb)
 #pragma unroll
-        for (int i = 0; i < 3; ++i) s[mb][i] = ss[i * IMG + (ks * L::MB + mb) * 64];
-      float v[8];
+          for (int i = 0; i < 3; ++i) s[mb][i] = ss[i * IMG + (ks * L::MB + mb) * 64];
+        float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] * inv;
-      split8(v, a[0]);
-      mfma_pieces<3, 3>(a, s, o);
-    }
-    if constexpr (KIND == kPhiRelu) {
-      // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
-#pragma unroll
-      for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
-    }
-    if constexpr (BLEND) {
-      const int t0 = b * 32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int t = t0 + 8 * (r / 4) + 4 * g + (r % 4);
-        const T* srow = bb + (size_t)(t < n ? t : n - 1) * rw.sn + L::MB * c;
-#pragma unroll
-        for (int mb = 0; mb < L::MB; ++mb) o[0][mb][r] = fmaf(rb, ldf(srow, mb) - o[0][mb][r], o[0][mb][r]);
+        for (int e = 0; e < 8; ++e) v[e] = f[8 * ks + e] * inv;
+        split8(v, a[0]);
+        mfma_pieces<3, 3>(a, s, o);
       }
-    }
-    store_rows<D, T>(ob, rw.sn, b * 32, n, lane, [&](int r, int mb) { return o[0][mb][r]; });
-  }
-  if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
-    __threadfence();                                       // the rows stored above are written again
-#pragma unroll 1
-    for (b = b_own; b < nblk; b += stride)
-#pragma unroll 1
-      for (int t = 32 * b; t < 32 * b + 32 && t < n; ++t) {
-        const size_t at = (size_t)t * rw.sn;
-        Plain<D, KIND, T>::template apply<true, BLEND>(qb + at, wq + (size_t)h * D * (D / 2), sb, ob + at, BLEND ? bb + at : nullptr, rb, lane);
+      if constexpr (KIND == kPhiRelu) {
+        // a feature that does not split makes all of its token's row NaN or Inf: one channel a row tells
+#pragma unroll
+        for (int r = 0; r < 16; ++r) chk = fmaf(o[0][0][r], 0.f, chk);
       }
+      if constexpr (BLEND) {
+        const int t0 = b * 32;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int t = t0 + 8 * (r / 4) + 4 * g + (r % 4);
+          const T* srow = bb + (size_t)(t < n ? t : n - 1) * rw.sn + L::MB * c;
+#pragma unroll
+          for (int mb = 0; mb < L::MB; ++mb) o[0][mb][r] = fmaf(rb, ldf(srow, mb) - o[0][mb][r], o[0][mb][r]);
+        }
+      }
+      store_rows<D, T>(ob, rw.sn, b * 32, n, lane, [&](int r, int mb) { return o[0][mb][r]; });
+    }
+    if (__builtin_expect(state_plain || __any(chk != chk), 0)) {
+      __threadfence();                                       // the rows stored above are written again
+#pragma unroll 1
+      for (b = b_own; b < nblk; b += stride)
+#pragma unroll 1
+        for (int t = 32 * b; t < 32 * b + 32 && t < n; ++t) {
+          const size_t at = (size_t)t * rw.sn;
+          Plain<D, KIND, T>::template apply<true, BLEND>(qb + at, wq + (size_t)h * D * (D / 2), sb, ob + at, BLEND ? bb + at : nullptr, rb, lane);
+        }
+    }
+    if (EVEN && sh.rest < sh.hi) __syncthreads();        // the next head's images take the place of these
   }
 }
 
+// Prologue of the passes with images of pieces, in eighths of a unit (make_deal).  Head-wise / even deal at 12 heads x 32760 (7 / 6 rounds), us: query
+// pass 119.5 / 116.7 (fp32), 85.6 / 82.0 (bf16 tensors), gradients 153 / 145 and 100 / 99.  A pass with heads of their own keeps
+// the loop-free form (EVEN = false): the loop over a workgroup's heads costs it up to half a microsecond.
+constexpr int kF32Prologue = 3;
 template <int D, int KIND, typename T, bool BLEND>
 hipError_t run_apply_pass(const void* q, const void* wq, const float* state, void* out,
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
-  const hipError_t e = set_smem_once<apply_f32_kernel<D, KIND, T, BLEND>>(smem);
-  if (e != hipSuccess) return e;
-  apply_f32_kernel<D, KIND, T, BLEND><<<dim3(p.KP, p.BH), NT8, smem, s>>>(
-      (const T*)q, (const T*)wq, state, (T*)out, (const T*)blend_in, blend_r, p.H, p.n, p.rows);
-  return hipGetLastError();
+  constexpr bool EV = D == 128;                            // (width 64 has little to gain)
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), EV ? kF32Prologue : kNeverEven);
+  auto launch = [&](auto kernel) -> hipError_t {
+    const hipError_t e = set_smem_once<decltype(kernel)::value>(smem);
+    if (e != hipSuccess) return e;
+    decltype(kernel)::value<<<grid_of(deal), NT8, smem, s>>>((const T*)q, (const T*)wq, state, (T*)out, (const T*)blend_in, blend_r, p.H, p.n, deal, p.rows);
+    return hipGetLastError();
+  };
+  return deal.share ? launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, false>>{}) : launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, EV>>{});
 }
 
 }  // namespace f32

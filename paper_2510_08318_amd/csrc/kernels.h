@@ -114,13 +114,15 @@ __host__ __device__ inline Share next_share(const Split& s, int g, const Share& 
 }
 // gx, gy: the workgroup's place in the grid that grid_of(s) is.  (With one grid dimension, and the head divided out of it, a pass of 8 us takes 0.4
 // us longer.)
-__host__ __device__ inline Share first_share(const Split& s, int gx, int gy) {
+__host__ __device__ inline Share head_share(const Split& s, int gx, int gy) {      // where s.share is known not to be 0
   Share r{};
-  if (s.share) {
-    r.there = true;
-    r.bh = gy; r.u = gx; r.step = s.share; r.end = s.ntile;
-    return r;
-  }
+  r.there = true;
+  r.bh = gy; r.u = gx; r.step = s.share; r.end = s.ntile;
+  return r;
+}
+__host__ __device__ inline Share first_share(const Split& s, int gx, int gy) {
+  if (s.share) return head_share(s, gx, gy);
+  Share r{};
   r.rest = split_lo(s, gx); r.hi = split_lo(s, gx + 1);
   return next_share(s, gx, r);
 }
@@ -134,6 +136,7 @@ inline dim3 grid_of(const Split& s) { return s.share ? dim3(s.share, s.G / s.sha
 // either the same number of workgroups to every head (each then has one head) or the units of all heads evenly (a workgroup may
 // then have the end of one head and the start of the next, and builds images twice).  prologue8: what a prologue takes, in eighths
 // of a unit's time.
+constexpr int kNeverEven = 1 << 20;        // as a prologue: always the first form
 inline Split make_deal(int BH, int per_head, int prologue8) {
   Split s{};
   s.ntile = per_head;
