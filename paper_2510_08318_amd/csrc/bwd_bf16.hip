@@ -753,8 +753,11 @@ constexpr int NTK = 512;     // 8 wavefronts, one workgroup per compute unit
 constexpr int KAHEAD = 0;
 
 // DW: dW~_k is accumulated here as well (DwTile).  The eight wavefronts then walk their blocks in step: after each
-// round of eight blocks the wavefronts 0-3 park their k rows (read again) and du, all eight contract over those
-// 128 tokens (one 32 x 32 block of dW~_k each), then the same for the blocks of the wavefronts 4-7.
+// round of eight blocks the wavefronts 0-3 park their k rows and du, all eight contract over those
+// 128 tokens (one 32 x 32 block of dW~_k each), then the same for the blocks of the wavefronts 4-7.  The k rows stay in 32 registers from the
+// projection on (256 in all, 3 spilled with CENTRE): read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute
+// units passes, and the kernel is bound by its rows: 117 us, now 105 (12 heads x 32760 x 128), 211 / 192 (40 x 20000), 40.3 / 37.9 (centred, 12 x
+// 8190), 25.4 / 23.2 (7 x 20000 x 64).
 template <int D, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                     const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
@@ -831,6 +834,11 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
     load_v(b);                                        // wanted after the projection, the softmax and dv
     f32x16 u[C::UM];
     project<D>(xk, sWA, lane, u);
+    uint4 xr[C::UK];
+    if constexpr (DW) {
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xk[ks];
+    }
     if constexpr (!DW) {
       if (b + stride < nblk) load_k(b + stride);      // next block's k flies during this one
     }
@@ -892,13 +900,9 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
       uint32_t dub[C::LOC / 2];
       float blk_its = 0.f;
       du_to_dx<D, KAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
-      uint4 xr[C::UK];
-      if constexpr (DW) {
-        // the next block's k rows (with the dW~ accumulator resident they do not fit beside the middle of the chain) and
-        // this block's rows once more; both before the dk stores: a wait for them must not wait for the stores
-        load_k(b + stride);
-        load_rows(xr, b);
-      }
+      // the next block's k rows (with the dW~ accumulator resident they do not fit beside the middle of the chain), before the dk
+      // stores: a wait for them must not wait for the stores
+      if constexpr (DW) load_k(b + stride);
       store_token_rows<D>(dkb, rw.sn, b * 32, n, lane, xa, its);
       if constexpr (DW) {
 #pragma unroll
