@@ -123,14 +123,16 @@ hipError_t run_apply_pass(const void* q, const void* wq, const float* state, voi
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
   constexpr bool EV = D == 128;                            // (width 64 has little to gain)
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), EV ? kF32Prologue : kNeverEven);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Prologue, EV);
   auto launch = [&](auto kernel) -> hipError_t {
     const hipError_t e = set_smem_once<decltype(kernel)::value>(smem);
     if (e != hipSuccess) return e;
     decltype(kernel)::value<<<grid_of(deal), NT8, smem, s>>>((const T*)q, (const T*)wq, state, (T*)out, (const T*)blend_in, blend_r, p.H, p.n, deal, p.rows);
     return hipGetLastError();
   };
-  return deal.share ? launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, false>>{}) : launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, EV>>{});
+  if constexpr (EV)
+    if (!deal.share) return launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, true>>{});
+  return launch(KernelTag<apply_f32_kernel<D, KIND, T, BLEND, false>>{});
 }
 
 }  // namespace f32

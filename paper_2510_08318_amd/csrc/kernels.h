@@ -132,19 +132,19 @@ inline int split_rounds(const Split& s) {
 }
 inline dim3 grid_of(const Split& s) { return s.share ? dim3(s.share, s.G / s.share) : dim3(s.G); }
 
-// The deal of a kernel that builds a head's operand images in its prologue: `per_head` units of each head to at most kCUs workgroups,
-// either the same number of workgroups to every head (each then has one head) or the units of all heads evenly (a workgroup may
-// then have the end of one head and the start of the next, and builds images twice).  prologue8: what a prologue takes, in eighths
-// of a unit's time.
-constexpr int kNeverEven = 1 << 20;        // as a prologue: always the first form
-inline Split make_deal(int BH, int per_head, int prologue8) {
+// The deal of a kernel that builds a head's operand images in its prologue: `per_head` units of each head to one workgroup per compute
+// unit (one per head where there are more heads), either the same number of workgroups to every head (each then has one head) or the
+// units of all heads evenly (a workgroup may then have the end of one head and the start of the next, and builds images twice).
+// prologue8: what a prologue takes, in eighths of a unit's time.  may_even = false: always the first form, for kernels without a loop over
+// a workgroup's heads.
+inline Split make_deal(int BH, int per_head, int prologue8, bool may_even = true) {
   Split s{};
   s.ntile = per_head;
   s.T = (long long)BH * per_head;
   s.PS = 1;
   s.share = kCUs / BH < per_head ? (BH < kCUs ? kCUs / BH : 1) : per_head;
   s.G = BH * s.share;
-  if (BH < kCUs) {
+  if (may_even && BH < kCUs) {
     const int even = s.T < kCUs ? (int)s.T : kCUs;
     const long long cost_share = 8LL * ((per_head + s.share - 1) / s.share) + prologue8;
     const long long cost_even = 8 * ((s.T + even - 1) / even) + 2 * prologue8;

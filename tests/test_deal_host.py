@@ -74,6 +74,16 @@ int main() {
           bad += !s.share && 8 * most_units(s) + c >= 8 * by_head;        // the second prologue has to pay
         }
       }
+  // kernels without the loop over a workgroup's heads: a head to a workgroup at every length up to the largest n (2^30 tokens), where the even deal would
+  // save any number of rounds
+  for (int BH : heads)
+    for (int per : {1, 2, 3, 255, 256, 1000, 1 << 17, 1 << 18, 1 << 20, 1 << 22}) {
+      const Split s = make_deal(BH, per, 3, false);
+      bad += s.share < 1 || s.G != BH * s.share;
+      if (s.share < 1) continue;
+      arithmetic(s);
+      if (s.T < 400000) cover(s);
+    }
   for (int k = 0; k < 3000; ++k) {                       // large counts: only the arithmetic
     Split s{};
     s.ntile = 1 + rand() % 33554432;
