@@ -344,11 +344,12 @@ struct DwTile {
 // LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use (one more for g).
 constexpr int QAHEAD = 3;
 constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
-// BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  If dL/dr = sum dout . (s - o) is asked
-// for (blend not null), the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
+// BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
+// asked for, and the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
 // wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
 // its own read dout once more and took 36 us (12 heads x 32760 x 128); here it is hidden
-// (bwd_q 114 either way; centred and with dW~, where it spills, 41 -> 47 at 12 x 8190 for a pass of 10).
+// (bwd_q 114 either way; centred and with dW~, where it spills 13 registers, 41 -> 47 at 12 x 8190 for a pass of 10).  An instance of its
+// own: as a condition at run time its registers were spilled in blended calls without dL/dr too.
 // DW: dW~_q is accumulated here as well (DwTile).
 //
 // Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
@@ -360,7 +361,7 @@ constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
 // one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO / den are parked between two barriers and dS contracts them
 // while du and dx are formed; (DW) x takes phi's place and du its tile between two more, and dW~ contracts those beside the next
 // tile's first half.
-template <int D, bool BLEND, bool CENTRE, bool DW>
+template <int D, bool BLEND, bool DR, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
                                                     const uint16_t* __restrict__ wq, const float* __restrict__ state,
                                                     float* __restrict__ vbar, uint16_t* __restrict__ dq,
@@ -535,7 +536,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       const float inv_r = lo + hi > 0.f ? __builtin_amdgcn_rcpf(lo + hi) : inv_den;
       // 1 / (scale * stok * den), in an order that keeps in range what is; scale and stok are powers of two
       const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);
-      if constexpr (BLEND) {
+      if constexpr (DR) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
         // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
         if (valid) dr_acc -= (ap + am) * r0;
@@ -645,36 +646,36 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
     DWT dwt;
     if constexpr (DW) dwt.init(pw);
-    // BLEND: the thread's chunk column of s and dout, vbar there (left in LDS by the prologue until the first tile is parked)
+    // DR: the thread's chunk column of s and dout, vbar there (left in LDS by the prologue until the first tile is parked)
     constexpr int PER = kTile * C::CH / 256;
     const int crow = (tid - 256) / C::CH, ccol = (tid - 256) % C::CH;
     float vb[8];
-    if constexpr (BLEND) {
+    if constexpr (DR) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) vb[i] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + 8 * ccol + i];
     }
     for (int tile = p; tile < ntile; tile += P) {
-      if constexpr (BLEND) {
-        if (blend != nullptr) {
-          const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
-          const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
-          uint4 sv[PER], dv[PER];
+      // (blend is never null here: as a branch the section keeps its registers to itself; without one, 97 are spilled with CENTRE and DW where 13
+      // are, and 10 with DW alone where none is)
+      if (DR && blend != nullptr) {
+        const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
+        const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
+        uint4 sv[PER], dv[PER];
 #pragma unroll
-          for (int i = 0; i < PER; ++i) {
-            const int t = tile * kTile + crow + i * (256 / C::CH);
-            const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
-            sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
-            dv[i] = *reinterpret_cast<const uint4*>(drow + at);
-          }
+        for (int i = 0; i < PER; ++i) {
+          const int t = tile * kTile + crow + i * (256 / C::CH);
+          const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+          sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
+          dv[i] = *reinterpret_cast<const uint4*>(drow + at);
+        }
 #pragma unroll
-          for (int i = 0; i < PER; ++i) {
-            float a[8], b[8], t = 0.f;
-            unpack_bf16x8(sv[i], a);
-            unpack_bf16x8(dv[i], b);
+        for (int i = 0; i < PER; ++i) {
+          float a[8], b[8], t = 0.f;
+          unpack_bf16x8(sv[i], a);
+          unpack_bf16x8(dv[i], b);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
-            if (tile * kTile + crow + i * (256 / C::CH) < n) dr_acc += t;
-          }
+          for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
+          if (tile * kTile + crow + i * (256 / C::CH) < n) dr_acc += t;
         }
       }
       __syncthreads();
@@ -735,7 +736,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
     }
   }
-  if constexpr (BLEND) {
+  if constexpr (DR) {
     for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
     __syncthreads();                                       // the last tile's slots have been read
     if (lane == 0) sRed[w] = dr_acc;
@@ -949,16 +950,16 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
     if (e2 != hipSuccess) return e2;
     decltype(kernel)::value<<<dim3(p.P, p.BH), NTQ, smem, s>>>(
         (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state, a.vbar, (uint16_t*)a.dq, a.partials, a.dw_part,
-        (const uint16_t*)(a.blend_dr ? a.blend_in : nullptr), a.blend_r, a.dr_part, a.cs_part, p.H, p.n, p.P, p.rows);
+        (const uint16_t*)a.blend_in, a.blend_r, a.dr_part, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
-  if (a.blend_in) {
-    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, true, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, true, CENTRE, false>>{});
-    if (e != hipSuccess) return e;
-  } else {
-    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, false, CENTRE, false>>{});
-    if (e != hipSuccess) return e;
-  }
+  if (a.blend_in && a.blend_dr)
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, true, true, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, true, true, CENTRE, false>>{});
+  else if (a.blend_in)
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, true, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, true, false, CENTRE, false>>{});
+  else
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, false, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, false, false, CENTRE, false>>{});
+  if (e != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
   auto launch_k = [&](auto kernel, size_t smem) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);

@@ -107,3 +107,27 @@ def test_blend_off_again_restores_plain_output():
     torch.cuda.synchronize()
     assert torch.equal(plain, again) and not torch.equal(plain, mixed)
     lay.close()
+
+
+@pytest.mark.parametrize("centred", [False, True])
+@pytest.mark.parametrize("wgrads", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_gradients_are_the_same_without_dr(d, wgrads, centred):
+    """The query-side gradient kernel has an instance with dL/dr and one without: the same gradients, bit for bit (700 tokens: five whole
+    tiles and a ragged one)."""
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    x = synth.generate("C5", n=700, H=3, d=d)
+    q, k, v, do = [G.to_device(t) for t in (x.q, x.k, x.v, x.dout)]
+    s, r = G.to_device(_softmax_branch(x, 5)), torch.tensor([0.37], device="cuda")
+    lay = G.Layer(G.to_device(x.wq), G.to_device(x.wk), x.B, x.n, want_wgrads=wgrads, centred=centred)
+    got = []
+    for dr in (torch.full((1,), 123.0, device="cuda"), None):
+        lay.set_blend(s, r, dr)
+        lay.forward(q, k, v)
+        grads = [t.clone() for t in lay.backward(q, k, v, do)]
+        got.append(grads + ([lay.dwq.clone(), lay.dwk.clone()] if wgrads else []))
+        if dr is not None:
+            assert dr.item() != 123.0
+    lay.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
