@@ -10,16 +10,16 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblinattn.so")
 PROBE_LIB = os.path.join(HERE, "libmembw_probe.so")      # bench.py's streaming-rate probe, a library of its own
 PROBE_SOURCE = "membw_probe.hip"
-SOURCES = ["api.cpp", "fwd_f32.hip", "fwd_bf16.hip", "state_reduce.hip", "bwd_bf16.hip", "bwd_f32.hip", "relu_bf16.hip"]
+SOURCES = ["api.cpp", "fwd_f32.hip", "fwd_bf16.hip", "state_reduce.hip", "bwd_bf16.hip", "bwd_bf16_stream.hip", "bwd_f32.hip", "relu_bf16.hip"]
 # Packed-fp32 VALU forms are switched off for every device compilation.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-# Per-file extras.  bwd_bf16.hip: MFMA results go to ordinary registers where they fit instead of
+# Per-file extras.  The bf16 backward: MFMA results go to ordinary registers where they fit instead of
 # always to the accumulation registers (measured on the query-side backward kernel when it used all 512
 # registers of a lane and spent a quarter of its vector instructions moving results between the two files:
 # 149 -> 134 us at 12 heads x 32760 x 128; neutral or slightly worse for the other files).
-EXTRA = {"bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = dict.fromkeys(("bwd_bf16.hip", "bwd_bf16_stream.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form"])
 
 
 def build(verbose: bool = False) -> str:

@@ -1,0 +1,988 @@
+// bf16-I/O backward path on gfx950 MFMA.  The paper trains through the converted layers
+// (Sec. 5.1) but prints no gradient formula; these kernels apply the chain rule to Eq. 3 and Eq. 5.
+// With S, z from the forward, den_i = phi(q_i).z, o_i = phi(q_i) S / den_i, delta_i = dO_i.o_i:
+//
+//   query side   g_i  = dL/dphi(q_i) = (dO_i S^T - delta_i z) / den_i
+//                dS   = sum_i phi(q_i)^T dO_i / den_i          dz = -sum_i phi(q_i) delta_i / den_i
+//   key side     g_j  = dL/dphi(k_j) = v_j dS^T + dz           dv_j = phi(k_j) dS
+//   through phi  du = p+ (g+ - <g+,p+>) - p- (g- - <g-,p->),   dx = du W~^T,   dW~ = sum x^T du
+//
+// bwd_q_kernel    : per 128-token tile: phi(Q), G = dO S^T, delta, du, dq; dS, dz partials (split-n); dW~_q partials
+// bwd_k_kernel    : per 32-token block: phi(K), g, du, dk, dv; dW~_k partials
+// (the partials are reduced in state_reduce.hip)
+//
+// Precision: every 16-bit MFMA operand except the stored bf16 q, k (projection) is fp16.
+// Operands that belong to one token only (dO_i for g_i, du_i for dx_i) are scaled by a per-token
+// power of two taken from their largest magnitude, so any gradient scale is safe.  Operands of
+// the sums over tokens (dO_i/den_i, delta_i/den_i, du for dW~) are scaled by one power of two per
+// workgroup that follows the running maximum over its tiles (largest magnitude so far in [16, 32));
+// when a tile raises the maximum the fp32 accumulators are rescaled by the exact ratio, so neither a
+// late large tile nor leading all-zero tiles can overflow or flush fp16; within a tile values down
+// to 2^-18 of the running maximum keep full precision.  Accumulation is fp32 everywhere; partial
+// sums are combined in a fixed order.
+#pragma once
+#include "kernels.h"
+#include "mfma_common.h"
+
+namespace linattn {
+namespace {
+
+// ---- operand images ------------------------------------------------------------------------
+// Each workgroup of the two main kernels builds the images it needs in LDS, straight from the fp32 state and W~: the state is held
+// in registers (StateRegs) while the statistics below are taken, a microsecond or two of prologue.  As kernels of their own, once
+// per head, the images cost 11.5 + 11.5 us per call (12 heads of width 128, latency) and the main kernels as long a prologue to
+// copy them in.
+// Both sides centre the state before it is rounded to fp16 operands (exact in real arithmetic; the roundings
+// then act on what the gradients are made of instead of on a common part that cancels):
+//   query side:   S^c = S - z vbar^T with vbar = sum_j v_j / n (the + half of S sums to sum_j v_j, the + half
+//                 of z to n).  The kernel then has delta^c = delta - dO . vbar, g is unchanged, and its dz comes
+//                 out as dz^c = dz + dS vbar.
+//   key side:     dz is completed against the ROUNDED image: dzc[f] = dz^c[f] - vbar . r(dS[f]), so
+//                 that v_j . r(dS[f]) + dzc[f] = (v_j - vbar) . r(dS[f]) + dz^c[f] holds exactly and the rounding
+//                 of the image acts on v_j - vbar, not on v_j (values with a common offset cost nothing).
+//   CENTRE (LINATTN_FLAG_CENTRED): the query-side kernel accumulated dS' = sum (phi - 2/D)^T dO/den and dz' likewise;
+//                 (2/D) x its column sums (cs_part) complete them: dS = dS' + (2/D) 1 colsum^T (constant over the
+//                 features: it only enters the row that dv gets back), dz^c = dz' + (2/D) wsum.  In addition the
+//                 mean over each half's features is taken out of dS' and of dz^c: the softmax Jacobian drops what
+//                 is constant over a half, and dv gets the constant row mean_+ + mean_- back.  (Without the flag
+//                 this last step is left out: where phi is spiky the rows of dS differ by orders of magnitude and
+//                 a common shift only adds rounding error to the small ones.)
+
+// Query side: image of S^c, z in sZ[D]; returns the image's scale.  vbar_out: non-null in one workgroup per head.
+// scratch: FO*D + D + NTHREADS/64 floats of LDS.  Ends before the barrier that the caller needs after building its images.
+template <int D, int NTHREADS>
+__device__ __forceinline__ float build_query_state(const float* __restrict__ state, uint4* sGA, float* sZ, float* scratch,
+                                                   float* __restrict__ vbar_out, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(state, tid);
+  float* part = scratch;
+  float* vb = part + R::FO * D;                             // (read by the acc wavefronts of bwd_q_kernel as well)
+  float* red = vb + D;
+  if (tid < D) sZ[tid] = state[D * D + tid];
+  S.octet_sums(part);
+  __syncthreads();
+  if (tid < D) {
+    // column sums of the + half of S; the + half of z sums to n
+    float sv = 0.f, nt = 0.f;
+#pragma unroll
+    for (int o = 0; o < R::FO / 2; ++o) sv += part[o * D + tid];
+#pragma unroll
+    for (int q = 0; q < D / 8; ++q) {
+      const float4 z = reinterpret_cast<const float4*>(sZ)[q];
+      nt += (z.x + z.y) + (z.z + z.w);
+    }
+    const float c = sv / nt;
+    vb[tid] = c;
+    if (vbar_out != nullptr) vbar_out[tid] = c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S.v[e][i] -= sZ[8 * S.fo + e] * vb[4 * S.cq + i];
+  if (!S.active) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S.v[e][i] = 0.f;
+  }
+  const float scale = S.scale(red, tid);
+  S.write_grad_image(sGA, scale);
+  return scale;
+}
+
+// Key side: the two images of dS, the matched dz in sZ[D], the constant row of dv in sRow[D] (zero without CENTRE); returns the scale.
+// scratch: FO*D + 4*D + NTHREADS/64 + 4 floats of LDS.
+template <int D, int NTHREADS, bool CENTRE>
+__device__ __forceinline__ float build_key_state(const float* __restrict__ dstate, uint4* sVA, uint4* sGA, float* sZ, float* sRow,
+                                                 float* scratch, const float* __restrict__ vbar, const float* __restrict__ cs_part,
+                                                 int P, int tid) {
+  using R = StateRegs<D, NTHREADS>;
+  R S;
+  S.load(dstate, tid);
+  float* part = scratch;
+  float* vb = part + R::FO * D;
+  float* m0 = vb + D;
+  float* m1 = m0 + D;
+  float* cB = m1 + D;
+  float* red = cB + D;                                      // [NTHREADS/64], then wsum and the two means of dz
+  float* misc = red + NTHREADS / 64;
+  if (tid < D) {
+    vb[tid] = vbar[tid];
+    cB[tid] = dstate[D * D + tid];
+  }
+  if constexpr (CENTRE) {
+    // column sums and wsum of the query-side workgroups, in a fixed order
+    float colsum = 0.f;
+    if (tid <= D)
+      for (int p = 0; p < P; p += 8) {
+        float t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = p + i < P ? cs_part[(size_t)(p + i) * (D + 8) + tid] : 0.f;
+        colsum += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+      }
+    if (tid == D) misc[0] = colsum;
+    S.octet_sums(part);
+    __syncthreads();
+    const float wsum = misc[0];
+    if (tid < D) {
+      float a = 0.f, b = 0.f;
+#pragma unroll
+      for (int o = 0; o < R::FO / 2; ++o) { a += part[o * D + tid]; b += part[(R::FO / 2 + o) * D + tid]; }
+      a *= 2.0f / D; b *= 2.0f / D;
+      m0[tid] = a; m1[tid] = b;
+      sRow[tid] = (a + b) + (4.0f / D) * colsum;
+      cB[tid] += (2.0f / D) * wsum;
+    }
+    __syncthreads();
+    if (tid < 128) {
+      // the mean of each half of dz^c, one wavefront each
+      float t = tid % 64 < D / 2 ? cB[(tid / 64) * (D / 2) + tid % 64] : 0.f;
+      for (int k = 32; k >= 1; k >>= 1) t += __shfl_xor(t, k, 64);
+      if (tid % 64 == 0) misc[1 + tid / 64] = t * (2.0f / D);
+    }
+    const float* m = S.fo < R::FO / 2 ? m0 : m1;
+    if (S.active) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S.v[e][i] -= m[4 * S.cq + i];
+    }
+  } else {
+    if (tid < D) sRow[tid] = 0.f;
+  }
+  const float scale = S.scale(red, tid);                    // (its barrier covers vb, cB and misc as well)
+  S.write_grad_image(sGA, scale);
+  S.template write_apply_image<ApplyLayout<D>::MB>(sVA, scale);
+  const float inv = __builtin_amdgcn_rcpf(scale);           // exact: a power of two
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dot = fmaf((float)(_Float16)(scale * S.v[e][i]), vb[4 * S.cq + i], dot);
+    for (int k = R::CQ / 2; k >= 1; k >>= 1) dot += __shfl_xor(dot, k, 64);
+    const int f = 8 * S.fo + e;
+    if (S.active && S.cq == 0) sZ[f] = cB[f] - (CENTRE ? misc[f < D / 2 ? 1 : 2] : 0.f) - dot * inv;
+  }
+  return scale;
+}
+
+// Softmax Jacobian of Eq. 5 for one token spread over a lane pair: gacc holds g in the GradLayout
+// row order (first GM/2 blocks the softmax(+u) half, then the softmax(-u) half), already scaled.
+template <int D>
+__device__ __forceinline__ void phi_jacobian(const float (&gp)[Cfg<D>::LOC], const float (&gm)[Cfg<D>::LOC],
+                                             const float (&pp)[Cfg<D>::LOC], const float (&pm)[Cfg<D>::LOC],
+                                             float (&du)[Cfg<D>::LOC]) {
+  using C = Cfg<D>;
+  float cp = 0.f, cm = 0.f;
+#pragma unroll
+  for (int j = 0; j < C::LOC; ++j) { cp = fmaf(gp[j], pp[j], cp); cm = fmaf(gm[j], pm[j], cm); }
+  float lo, hi;
+  pair32(cp, lo, hi); cp = lo + hi;
+  pair32(cm, lo, hi); cm = lo + hi;
+#pragma unroll
+  for (int j = 0; j < C::LOC; ++j) du[j] = pp[j] * (gp[j] - cp) - pm[j] * (gm[j] - cm);
+}
+
+// dx = du W~^T for one block of 32 tokens, tokens on the accumulator rows: du is scaled by one power
+// of two per block (its largest magnitude lands in [1,2)), cast to fp16 and fed as the A operand
+// (lane (t,g) holds features g*LOC + 8ks + e of token t); the B operands are the W~ image.
+// acc[mb][r] of lane (c,g) is its * dx[token 8*(r/4) + 4g + r%4][channel MB*c + mb].
+//
+// dub receives the scaled fp16 du as packed (lane (t,g): features g*LOC .. g*LOC + LOC-1 of token t; zero for tokens
+// that do not exist), blk_its the inverse scale (0 for an all-zero block): what the dW~ contraction parks.
+// AHEAD: lookahead of the W~ operand reads of dx (pipelined_operands).
+template <int D, int AHEAD>
+__device__ __forceinline__ void du_to_dx(const float (&du)[Cfg<D>::LOC], const uint4* sWB, int lane, bool valid,
+                                         f32x16 (&acc)[D / 32], float& its, uint32_t (&dub)[Cfg<D>::LOC / 2], float& blk_its) {
+  using C = Cfg<D>;
+  using L = ApplyLayout<D>;
+  constexpr int DK = C::LOC / 8;
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < C::LOC; ++j) m = fmaxf(m, fabsf(du[j]));
+  if (!valid) m = 0.f;
+  float lo, hi;
+  pair32(m, lo, hi); m = fmaxf(lo, hi);
+  m = wave_max_paired(m);
+  const float ts = valid ? pow2_normaliser(m) : 0.f;
+#pragma unroll
+  for (int j = 0; j < C::LOC / 2; ++j) dub[j] = pack_f16x2(du[2 * j] * ts, du[2 * j + 1] * ts);
+  its = __builtin_amdgcn_rcpf(pow2_normaliser(m));     // exact: a power of two
+  blk_its = m > 0.f ? its : 0.f;
+#pragma unroll
+  for (int mb = 0; mb < L::MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
+  const uint4* wb = sWB + lane + opaque_zero();
+  pipelined_operands<DK * L::MB, AHEAD>(
+      [&](int i) { return wb[i * 64]; },
+      [&](int i, uint4 b) {
+        const int ks = i / L::MB, mb = i % L::MB;
+        uint4 aq; aq.x = dub[4 * ks]; aq.y = dub[4 * ks + 1]; aq.z = dub[4 * ks + 2]; aq.w = dub[4 * ks + 3];
+        acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(aq), as_f16x8(b), acc[mb], 0, 0, 0);
+      });
+}
+
+// ---- dW~ = sum_i x_i^T du_i, accumulated inside the kernels that make du ---------------------
+// The workgroup parks 128 tokens in LDS as two fp16 tiles, x [kTile][D] and du [kTile][D/2] (rows swizzled
+// like the phi tile; a 32-token block of du carries the power-of-two scale du_to_dx gave it, with the
+// inverse scales beside the tile).  Its NW wavefronts then contract over the tokens with transposing
+// reads of both tiles: wavefront w owns the feature block w % NB and RB 32-channel row blocks and brings
+// the blocks to one common power-of-two scale that follows the running maximum of the workgroup
+// (gamma_step; the accumulators are rescaled by the exact ratio when a tile raises it).  Partials per
+// workgroup are reduced in a fixed order afterwards.
+template <int D, int NW>
+struct DwTile {
+  static constexpr int HALF = D / 2;
+  static constexpr int LOC = D / 4;
+  static constexpr int RSX = D * 2;                        // bytes per row of the x tile
+  static constexpr int RSU = HALF * 2;                     // bytes per row of the du tile
+  static constexpr int NB = HALF / 32;                     // 32-column blocks of du
+  static constexpr int RB = (D / 32) * NB >= NW ? (D / 32) * NB / NW : 1;   // row blocks per wavefront
+  static constexpr int BPT = kTile / 32;                   // du blocks per parked tile
+  static constexpr int KSN = kTile / 16;
+  static constexpr int KBATCH = NW > 4 ? KSN / 2 : KSN / 4;     // k-steps whose operands are in flight together
+  static constexpr int DU_BYTES = kTile * RSU;
+  f32x16 acc[RB];
+  float gamma;
+  int fb, row0;
+  bool active;
+
+  __device__ __forceinline__ void init(int w) {
+    fb = w % NB; row0 = (w / NB) * RB;
+    active = row0 < D / 32;
+    gamma = kGammaUnset;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  }
+  // The x rows of block slot (0..3) as the projection holds them: lane (t,g) has the 16-byte chunks 2ks + g of token t.
+  static __device__ __forceinline__ void park_x(const uint4 (&xr)[D / 16], char* sX, int slot, int lane) {
+    const int row = 32 * slot + lane % 32, g = lane / 32;
+    char* rowp = sX + row * RSX;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      uint4 hv;
+      hv.x = bf16x2_to_f16x2(xr[ks].x); hv.y = bf16x2_to_f16x2(xr[ks].y);
+      hv.z = bf16x2_to_f16x2(xr[ks].z); hv.w = bf16x2_to_f16x2(xr[ks].w);
+      *reinterpret_cast<uint4*>(rowp + (((2 * ks + g) ^ swz<D>(row)) * 16)) = hv;
+    }
+  }
+  // The scaled fp16 du of block slot (0..3) of the parked tile, as du_to_dx packs it: lane (t,g) holds features
+  // g*LOC .. g*LOC + LOC-1 of token t.
+  static __device__ __forceinline__ void park_du(const uint32_t (&dub)[LOC / 2], float blk_its, char* sU, float* sIts, int slot, int lane) {
+    const int row = 32 * slot + lane % 32, g = lane / 32;
+    char* rowp = sU + row * RSU;
+#pragma unroll
+    for (int c = 0; c < LOC / 8; ++c) {
+      uint4 v; v.x = dub[4 * c]; v.y = dub[4 * c + 1]; v.z = dub[4 * c + 2]; v.w = dub[4 * c + 3];
+      *reinterpret_cast<uint4*>(rowp + (((g * (LOC / 8) + c) ^ swz<HALF>(row)) * 16)) = v;
+    }
+    if (lane == 0) sIts[slot] = blk_its;
+  }
+  // lane: pass lane + opaque_zero() from inside the tile loop: the read offsets are then worked out per tile (a few
+  // integer operations) instead of being held in registers, or spilled, across the whole loop
+  __device__ __forceinline__ void contract(const char* sX, const char* sU, const float* sIts, int lane) {
+    float its[BPT];
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) { its[i] = sIts[i]; m = fmaxf(m, its[i]); }
+    float gnext = gamma;
+    float ratio = gamma_step(gnext, gamma_for(m));
+    // the same in every lane: kept in scalar registers
+    gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
+    ratio = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
+    if (ratio != 1.f) {
+#pragma unroll
+      for (int j = 0; j < RB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] *= ratio;
+    }
+    if (!active) return;
+    int offA[RB][2], offB[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      offB[j] = tr_offset_g4<HALF>(32 * fb, lane, j);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) offA[i][j] = tr_offset_g4<D>(32 * (row0 + i), lane, j);
+    }
+    // the operands of KBATCH k-steps are requested before their first MFMA: one LDS latency per batch instead of one per k-step
+#pragma unroll
+    for (int k0 = 0; k0 < KSN; k0 += KBATCH) {
+      f16x8 a[KBATCH][RB], b[KBATCH];
+#pragma unroll
+      for (int ks = 0; ks < KBATCH; ++ks) {
+        b[ks] = read_tr(sU + (k0 + ks) * 16 * RSU, offB[0], offB[1]);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) a[ks][i] = read_tr(sX + (k0 + ks) * 16 * RSX, offA[i][0], offA[i][1]);
+      }
+#pragma unroll
+      for (int ks = 0; ks < KBATCH; ++ks) {
+        const _Float16 f = (_Float16)(gamma * its[(k0 + ks) / 2]);   // a power of two, or 0 for an all-zero block
+        const f16x8 bo = b[ks] * f;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks][i], bo, acc[i], 0, 0, 0);
+      }
+    }
+  }
+  // part: this workgroup's [D][HALF] partial
+  __device__ __forceinline__ void store(float* part, int lane) const {
+    if (!active) return;
+    const float ig = __builtin_amdgcn_rcpf(gamma);
+    const int c = lane % 32, g = lane / 32;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        part[(32 * (row0 + i) + 8 * (r / 4) + 4 * g + (r % 4)) * HALF + 32 * fb + c] = acc[i][r] * ig;
+  }
+};
+
+// ---- query side --------------------------------------------------------------------------
+// LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use (one more for g).
+constexpr int QAHEAD = 3;
+constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
+// BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
+// asked for, and the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
+// wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
+// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it is hidden
+// (bwd_q 114 either way; centred and with dW~, where it spills 13 registers, 41 -> 47 at 12 x 8190 for a pass of 10).  An instance of its
+// own: as a condition at run time its registers were spilled in blended calls without dL/dr too.
+// DW: dW~_q is accumulated here as well (DwTile).
+//
+// Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
+// A+- = sum G phi and Z+- = sum z phi over the two halves of the features, den = Z+ + Z-, delta = (A+ + A-) / den and the two sums
+// of the softmax Jacobian are combinations of the same four, so dots of what the lane holds in fp32 stand in for 40 of the
+// MFMAs and for a second image of S.  Wavefronts 4-7 ("acc") contract the tile's phi, dO / den and delta / den into dS, dz
+// and its x, du into dW~ meanwhile: the accumulators (112 registers) are theirs, so the tok wavefronts do with 256 registers and a
+// SIMD hosts one wavefront of each kind, whose MFMA and vector work overlap.  The tiles are single (64 KB of images leave room for
+// one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO / den are parked between two barriers and dS contracts them
+// while du and dx are formed; (DW) x takes phi's place and du its tile between two more, and dW~ contracts those beside the next
+// tile's first half.
+template <int D, bool STREAM, bool BLEND, bool DR, bool CENTRE, bool DW>
+__global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
+                                                    const uint16_t* __restrict__ wq, const float* __restrict__ state,
+                                                    float* __restrict__ vbar, uint16_t* __restrict__ dq,
+                                                    float* __restrict__ partials, float* __restrict__ dw_part,
+                                                    const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
+                                                    float* __restrict__ dr_part, float* __restrict__ cs_part,
+                                                    int H, int n, int P, Rows rw) {
+  using C = Cfg<D>;
+  using L = ApplyLayout<D>;
+  using G = GradLayout<D>;
+  constexpr int RS = D * 2;
+  constexpr int WMN = D / 64;
+  constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
+  constexpr float mean = CENTRE ? 2.0f / D : 0.f;          // what is taken out of phi before it is rounded: its mean over the features
+  using DWT = DwTile<D, 4>;
+  extern __shared__ uint4 smem[];
+  uint4* sWA = smem;
+  uint4* sGA = sWA + C::W_IMG;
+  uint4* sWB = sGA + G::IMG;
+  char* sPhi = reinterpret_cast<char*>(sWB + WB_IMG);      // [kTile][D] fp16: phi(q) (CENTRE: phi(q) - 2/D), then (DW) the q rows
+  char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: gamma * dO / den
+  uint16_t* sW16 = reinterpret_cast<uint16_t*>(sDO + kTile * RS);   // [kTile] fp16: -gamma * delta / den
+  float* sZ = reinterpret_cast<float*>(sW16 + kTile);      // [D] z, unscaled
+  float* sRed = sZ + D;                                    // [8]: 0..3 the tile's operand maxima, 4..7 the du blocks' inverse scales
+  char* sDU = reinterpret_cast<char*>(sRed + 8);           // DW: the tile's du, [kTile][D/2] fp16
+
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int role = w / 4, pw = w % 4;
+  const int g = lane / 32;
+  const int bh = blockIdx.y, p = blockIdx.x, h = bh % H;
+  const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;      // 1 - r'
+  const float* sb = state + (size_t)bh * (D + 1) * D;
+  const int ntile = (n + kTile - 1) / kTile;
+  float dr_acc = 0.f;
+
+  build_w_image<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
+  build_w_image_t<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
+  const float scale = build_query_state<D, NTQ>(sb, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
+  __syncthreads();
+
+  // running power-of-two scale of the sums over tokens, the same in every wavefront; returns the factor for the accumulators
+  float gamma = kGammaUnset;
+  auto next_gamma = [&]() -> float {
+    const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
+    float gnext = gamma;
+    const float ratio = gamma_step(gnext, gamma_for(m));
+    // the same in every lane: kept in scalar registers
+    gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
+  };
+
+  if (role == 0) {
+    const uint16_t* qb = q + head_base(rw, bh, H);
+    const uint16_t* dob = dout + head_base(rw, bh, H);
+    uint16_t* dqb = dq + head_base(rw, bh, H);
+    const int prow = 32 * pw + (lane % 32);
+    float z_mean = 0.f;                                    // mean * the sum of z over the lane's features
+    if constexpr (CENTRE) {
+      for (int j = 0; j < C::LOC; ++j) z_mean += sZ[g * C::LOC + j] + sZ[C::HALF + g * C::LOC + j];
+      z_mean *= mean;
+    }
+    uint4 xq[C::UK], xr[C::UK], dor[D / 16];
+    auto load_rows = [&](int tile) {
+      const int t = tile * kTile + prow;
+      const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+      const uint4* row = reinterpret_cast<const uint4*>(qb + at);
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) xq[ks] = row[2 * ks + g];
+    };
+    auto load_do = [&](int tile) {
+      const int t = tile * kTile + prow;
+      const uint4* drow = reinterpret_cast<const uint4*>(dob + (size_t)(t < n ? t : n - 1) * rw.sn);
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) dor[i] = drow[2 * i + g];
+    };
+    load_rows(p < ntile ? p : 0);
+    // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
+    // for the first tile too, would be a wait for the previous tile's stores
+#pragma unroll
+    for (int ks = 0; ks < C::UK; ++ks) asm volatile("" : "+v"(xq[ks].x), "+v"(xq[ks].y), "+v"(xq[ks].z), "+v"(xq[ks].w));
+    for (int tile = p; tile < ntile; tile += P) {
+      const int t = tile * kTile + prow;
+      const bool valid = t < n;
+      load_do(tile);
+      f32x16 u[C::UM];
+      project<D, QAHEAD>(xq, sWA, lane, u);
+      if constexpr (DW) {
+#pragma unroll
+        for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xq[ks];   // rows past n repeat row n - 1: their du is zero
+      }
+      float pp[C::LOC], pm[C::LOC];
+      {
+        uint32_t unused[C::NPK];
+        softmax_full<D>(u, pp, pm, unused);
+      }
+      if constexpr (CENTRE) {
+        // (as values of their own: folded with the mean taken out below, the unnormalised exponentials would be kept beside them)
+#pragma unroll
+        for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
+      }
+      // the token's largest |dO|: magnitudes of bf16 compare as integers
+      float dmax;
+      {
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        u16x2 m2 = {0, 0};
+        auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) { take(dor[i].x); take(dor[i].y); take(dor[i].z); take(dor[i].w); }
+        const uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
+        dmax = __builtin_bit_cast(float, m << 16);
+      }
+      float lo, hi;
+      pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
+      const float stok = pow2_normaliser(fminf(dmax, kTokenMax));
+
+      // G = dO S^T (times scale * stok), rows laid out like phi
+      f32x16 ga[G::GM];
+#pragma unroll
+      for (int mb = 0; mb < G::GM; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
+      const uint4* sga = sGA + lane + opaque_zero();
+      pipelined_operands<G::KS * G::GM, QAHEAD + 1>(
+          [&](int i) { return sga[i * 64]; },
+          [&](int i, uint4 a) {
+            const int ks = i / G::GM, mb = i % G::GM;
+            float f[8];
+            unpack_bf16x8(dor[ks], f);
+            uint4 bq;
+            bq.x = pack_f16x2(f[0] * stok, f[1] * stok); bq.y = pack_f16x2(f[2] * stok, f[3] * stok);
+            bq.z = pack_f16x2(f[4] * stok, f[5] * stok); bq.w = pack_f16x2(f[6] * stok, f[7] * stok);
+            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
+          });
+      // dO stays packed until it is parked: seen as the same values, its unpacked form would be kept (and spilled) from here to there
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) asm volatile("" : "+v"(dor[i].x), "+v"(dor[i].y), "+v"(dor[i].z), "+v"(dor[i].w));
+      // A+-, Z+-; feature g*LOC + j of each half
+      const int z_at = g * C::LOC / 4 + opaque_zero();
+      auto z4 = [&](int q) { return reinterpret_cast<const float4*>(sZ)[z_at + q]; };
+      // Zr: the normaliser of phi as the sum dS takes it, rounded to fp16 (CENTRE: rounded after its mean is taken out).  dS adds
+      // phi / den: with the same rounded phi above and below, what the roundings of a token's features have in common drops out
+      // (with den from the fp32 phi dW~_k was 1 % further off, 2 % with CENTRE).  dq has fp32 phi on both sides.
+      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f, Zr = z_mean;
+#pragma unroll
+      for (int q = 0; q < C::LOC / 4; ++q) {
+        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+        const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int j = 4 * q + i;
+          ap = fmaf(ga[j / 16][j % 16], pp[j], ap); am = fmaf(ga[G::GM / 2 + j / 16][j % 16], pm[j], am);
+          Zp = fmaf(zp[i], pp[j], Zp); Zm = fmaf(zm[i], pm[j], Zm);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const int j = 4 * q + i;
+          const f16x2 rp = __builtin_bit_cast(f16x2, pack_f16x2(pp[j] - mean, pp[j + 1] - mean));
+          const f16x2 rm = __builtin_bit_cast(f16x2, pack_f16x2(pm[j] - mean, pm[j + 1] - mean));
+          Zr = fmaf((float)rp[0], zp[i], Zr); Zr = fmaf((float)rp[1], zp[i + 1], Zr);
+          Zr = fmaf((float)rm[0], zm[i], Zr); Zr = fmaf((float)rm[1], zm[i + 1], Zr);
+        }
+      }
+      // (phi is rounded again when it is parked: seen as the same values, the 32 packed registers would be kept, and spilled)
+#pragma unroll
+      for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
+      pair32(Zp, lo, hi); Zp = lo + hi;
+      pair32(Zm, lo, hi); Zm = lo + hi;
+      pair32(Zr, lo, hi);
+      const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
+      // (a token whose features with a key behind them all round to zero adds nothing but must not spread Inf)
+      const float inv_r = lo + hi > 0.f ? __builtin_amdgcn_rcpf(lo + hi) : inv_den;
+      // 1 / (scale * stok * den), in an order that keeps in range what is; scale and stok are powers of two
+      const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);
+      if constexpr (DR) {
+        // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
+        // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
+        if (valid) dr_acc -= (ap + am) * r0;
+      }
+      pair32(ap, lo, hi); ap = lo + hi;
+      pair32(am, lo, hi); am = lo + hi;
+      const float delta = (ap + am) * r0;
+      {
+        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
+        float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_r * om : 0.f;
+        m = wave_max_paired(m);
+        if (lane == 0) sRed[pw] = m;
+      }
+      __syncthreads();                                   // the previous tile has been read
+      next_gamma();
+      {
+        // (addresses from a lane index that the optimiser cannot hoist: held across the loop they end up in scratch memory)
+        const int lz = lane + opaque_zero();
+        const int row = 32 * pw + lz % 32, psw = swz<D>(row), gz = lz / 32;
+        char* rowp = sPhi + row * RS;
+        constexpr int CPH = C::LOC / 8;
+        // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
+        // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
+        auto pack4 = [&](const float* f) {
+          return make_uint4(pack_f16x2(f[0] - mean, f[1] - mean), pack_f16x2(f[2] - mean, f[3] - mean),
+                            pack_f16x2(f[4] - mean, f[5] - mean), pack_f16x2(f[6] - mean, f[7] - mean));
+        };
+#pragma unroll
+        for (int c = 0; c < CPH; ++c) {
+          uint4 a = pack4(pp + 8 * c), b = pack4(pm + 8 * c);
+          if (!valid) { a = make_uint4(0, 0, 0, 0); b = a; }
+          *reinterpret_cast<uint4*>(rowp + (((gz * CPH + c) ^ psw) * 16)) = a;
+          *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + gz * CPH + c) ^ psw) * 16)) = b;
+        }
+        const float sc = valid ? inv_r * gamma * om : 0.f;
+        char* drowp = sDO + row * RS;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+          float f[8];
+          unpack_bf16x8(dor[c], f);
+          uint4 a;
+          a.x = pack_f16x2(f[0] * sc, f[1] * sc); a.y = pack_f16x2(f[2] * sc, f[3] * sc);
+          a.z = pack_f16x2(f[4] * sc, f[5] * sc); a.w = pack_f16x2(f[6] * sc, f[7] * sc);
+          *reinterpret_cast<uint4*>(drowp + (((2 * c + gz) ^ psw) * 16)) = a;
+        }
+        if (g == 0) sW16[row] = (uint16_t)(pack_f16x2(valid ? -delta * sc : 0.f, 0.f) & 0xffffu);
+      }
+      __syncthreads();
+      // g = (1 - r') (G - delta z) / den, its sums cp, cm against phi, and du
+      const float r1 = om * r0, r2 = om * inv_den * delta;
+      const float cp = ap * r1 - r2 * Zp, cm = am * r1 - r2 * Zm;
+      float du[C::LOC];
+#pragma unroll
+      for (int q = 0; q < C::LOC / 4; ++q) {
+        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+        const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int j = 4 * q + i;
+          const float gp = fmaf(ga[j / 16][j % 16], r1, fmaf(-r2, zp[i], -cp));
+          const float gm = fmaf(ga[G::GM / 2 + j / 16][j % 16], r1, fmaf(-r2, zm[i], -cm));
+          du[j] = pp[j] * gp - pm[j] * gm;
+        }
+      }
+      // The next tile's rows go out before the dq stores: loads and stores retire in order, and a wait for a load issued behind
+      // the stores would wait for the stores as well.
+      load_rows(tile + P < ntile ? tile + P : tile);
+      uint32_t dub[C::LOC / 2];
+      float blk_its = 0.f;
+      {
+        f32x16 xa[L::MB];
+        float its;
+        du_to_dx<D, QAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
+        store_token_rows<D, STREAM>(dqb, rw.sn, tile * kTile + 32 * pw, n, lane, xa, its);
+      }
+      if constexpr (DW) {
+        __syncthreads();                                 // dS has read the tile's phi
+        const int lz = lane + opaque_zero();
+        DWT::park_x(xr, sPhi, pw, lz);
+        DWT::park_du(dub, blk_its, sDU, sRed + 4, pw, lz);
+        __syncthreads();
+      }
+    }
+  } else {
+    float csum[WMN], wsum = 0.f;                         // column sums of the dO/den operand, sum of the -delta/den operand
+#pragma unroll
+    for (int j = 0; j < WMN; ++j) csum[j] = 0.f;
+    f32x16 s[WMN][WMN], zacc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      zacc[r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < WMN; ++i)
+#pragma unroll
+        for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
+    }
+    const int mi = pw / 2, ni = pw % 2;
+    const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
+    const bool do_z = (WMN == 2) || (ni == 0);
+    int offA[WMN][2], offB[WMN][2];
+#pragma unroll
+    for (int i = 0; i < WMN; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
+        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
+      }
+    DWT dwt;
+    if constexpr (DW) dwt.init(pw);
+    // DR: the thread's chunk column of s and dout, vbar there (left in LDS by the prologue until the first tile is parked)
+    constexpr int PER = kTile * C::CH / 256;
+    const int crow = (tid - 256) / C::CH, ccol = (tid - 256) % C::CH;
+    float vb[8];
+    if constexpr (DR) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) vb[i] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + 8 * ccol + i];
+    }
+    for (int tile = p; tile < ntile; tile += P) {
+      // (blend is never null here: as a branch the section keeps its registers to itself; without one, 97 are spilled with CENTRE and DW where 13
+      // are, and 10 with DW alone where none is)
+      if (DR && blend != nullptr) {
+        const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
+        const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
+        uint4 sv[PER], dv[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          const int t = tile * kTile + crow + i * (256 / C::CH);
+          const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+          sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
+          dv[i] = *reinterpret_cast<const uint4*>(drow + at);
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          float a[8], b[8], t = 0.f;
+          unpack_bf16x8(sv[i], a);
+          unpack_bf16x8(dv[i], b);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
+          if (tile * kTile + crow + i * (256 / C::CH) < n) dr_acc += t;
+        }
+      }
+      __syncthreads();
+      const float ratio = next_gamma();
+      if (ratio != 1.f) {                                // this tile is larger than every earlier one
+        if constexpr (CENTRE) {
+          wsum *= ratio;
+#pragma unroll
+          for (int j = 0; j < WMN; ++j) csum[j] *= ratio;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          zacc[r] *= ratio;
+#pragma unroll
+          for (int i = 0; i < WMN; ++i)
+#pragma unroll
+            for (int j = 0; j < WMN; ++j) s[i][j][r] *= ratio;
+        }
+      }
+      __syncthreads();
+      contract_tile<D, false, CENTRE>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
+                       [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); }, csum, &wsum);
+      if constexpr (DW) {
+        __syncthreads();
+        __syncthreads();
+        dwt.contract(sPhi, sDU, sRed + 4, lane + opaque_zero());
+      }
+    }
+    if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
+
+    const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
+    if constexpr (CENTRE) {
+      // column sums of dO/den (the wavefronts mi = 0 hold every channel block once) and the sum of -delta/den
+      float* cs = cs_part + ((size_t)bh * P + p) * (D + 8);
+#pragma unroll
+      for (int j = 0; j < WMN; ++j) {
+        float lo, hi;
+        pair32(csum[j], lo, hi);
+        if (mi == 0 && g == 0) cs[32 * (ni * WMN + j) + (lane % 32)] = (lo + hi) * ig;
+      }
+      float lo, hi;
+      pair32(wsum, lo, hi);
+      if (pw == 0 && lane == 0) cs[D] = (lo + hi) * ig;
+    }
+    float* dst = partials + ((size_t)bh * P + p) * (size_t)(D + 1) * D;
+    const int c = lane % 32;
+#pragma unroll
+    for (int i = 0; i < WMN; ++i)
+#pragma unroll
+      for (int j = 0; j < WMN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
+          dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
+        }
+    if (do_z && c == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
+    }
+  }
+  if constexpr (DR) {
+    for (int k = 32; k >= 1; k >>= 1) dr_acc += __shfl_xor(dr_acc, k, 64);
+    __syncthreads();                                       // the last tile's slots have been read
+    if (lane == 0) sRed[w] = dr_acc;
+    __syncthreads();
+    if (tid == 0)
+      dr_part[(size_t)bh * P + p] = ((sRed[0] + sRed[1]) + (sRed[2] + sRed[3])) + ((sRed[4] + sRed[5]) + (sRed[6] + sRed[7]));
+  }
+}
+
+// ---- key side ----------------------------------------------------------------------------
+constexpr int NTK = 512;     // 8 wavefronts, one workgroup per compute unit
+// Operand lookahead of the key-side MFMA phases.  With two wavefronts per SIMD the other wavefront
+// hides the LDS latency and registers are what is short: reading each operand right before its
+// MFMA (0) measured 101.5 us, one ahead 102.9, three ahead 106.7, the compiler's own order 105.
+constexpr int KAHEAD = 0;
+
+// DW: dW~_k is accumulated here as well (DwTile).  The eight wavefronts then walk their blocks in step: after each
+// round of eight blocks the wavefronts 0-3 park their k rows and du, all eight contract over those
+// 128 tokens (one 32 x 32 block of dW~_k each), then the same for the blocks of the wavefronts 4-7.  The k rows stay in 32 registers from the
+// projection on (256 in all, 3 spilled with CENTRE): read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute
+// units passes, and the kernel is bound by its rows: 117 us, now 105 (12 heads x 32760 x 128), 211 / 192 (40 x 20000), 40.3 / 37.9 (centred, 12 x
+// 8190), 25.4 / 23.2 (7 x 20000 x 64).
+template <int D, bool STREAM, bool CENTRE, bool DW>
+__global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                                                    const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
+                                                    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                                    float* __restrict__ dw_part,
+                                                    const float* __restrict__ vbar, const float* __restrict__ cs_part,
+                                                    int H, int n, int P, Rows rw) {
+  using C = Cfg<D>;
+  using L = ApplyLayout<D>;
+  using G = GradLayout<D>;
+  constexpr int NW = NTK / 64;
+  constexpr int SA_IMG = L::KS * L::MB * 64;
+  constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
+  using DWT = DwTile<D, NW>;
+  extern __shared__ uint4 smem[];
+  uint4* sWA = smem;
+  uint4* sVA = sWA + C::W_IMG;             // image of dS^T for dv (contraction over features)
+  uint4* sGA = sVA + SA_IMG;               // image of dS for g (contraction over channels)
+  uint4* sWB = sGA + G::IMG;
+  float* sZ = reinterpret_cast<float*>(sWB + WB_IMG);   // [D] dz, unscaled
+  float* sRed = sZ + D;                                 // [8]: DW: 0..3 the parked du blocks' inverse scales
+  float* sRow = sRed + 8;                               // [D] constant row of dv, then the scratch of the prologue
+  char* sX = reinterpret_cast<char*>(sRow + D);         // DW: [kTile][D] fp16, k rows of four blocks
+  char* sU = sX + kTile * D * 2;                        // DW: [kTile][D/2] fp16, their du
+
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int g = lane / 32;
+  const int bh = blockIdx.y, h = bh % H;
+  const uint16_t* kb = k + head_base(rw, bh, H);
+  const uint16_t* vb = v + head_base(rw, bh, H);
+  uint16_t* dkb = dk + head_base(rw, bh, H);
+  uint16_t* dvb = dv + head_base(rw, bh, H);
+
+  build_w_image<D, NTK>(wk + (size_t)h * D * C::HALF, sWA, tid);
+  build_w_image_t<D, NTK>(wk + (size_t)h * D * C::HALF, sWB, tid);
+  // sZ: dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the features)
+  const float scale = build_key_state<D, NTK, CENTRE>(dstate + (size_t)bh * (D + 1) * D, sVA, sGA, sZ, sRow, sRow + D, vbar + (size_t)bh * D,
+                                                      CENTRE ? cs_part + (size_t)bh * P * (D + 8) : nullptr, P, tid);
+  __syncthreads();
+  const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
+  float dv_add[L::MB];
+#pragma unroll
+  for (int mb = 0; mb < L::MB; ++mb) dv_add[mb] = CENTRE ? sRow[L::MB * (lane % 32) + mb] : 0.f;
+
+  const int nblk = (n + 31) / 32;
+  const int stride = gridDim.x * NW;
+  uint4 xk[C::UK], vr[D / 16];
+  auto load_rows = [&](uint4 (&x)[C::UK], int b) {
+    const int t = b * 32 + (lane % 32);
+    const int tc = t < n ? t : (n - 1);
+    const uint4* row = reinterpret_cast<const uint4*>(kb + (size_t)tc * rw.sn);
+#pragma unroll
+    for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
+  };
+  auto load_k = [&](int b) { load_rows(xk, b); };
+  auto load_v = [&](int b) {
+    const int t = b * 32 + (lane % 32);
+    const int tc = t < n ? t : (n - 1);
+    const uint4* vrow = reinterpret_cast<const uint4*>(vb + (size_t)tc * rw.sn);
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) vr[i] = vrow[2 * i + g];
+  };
+  DWT dwt;
+  if constexpr (DW) dwt.init(w);
+  // DW: every wavefront of the workgroup makes the same number of rounds (there are barriers inside); a wavefront
+  // whose block does not exist works on tokens past n: its loads repeat row n - 1, its du is zero, its stores are
+  // out of bounds
+  int b = blockIdx.x * NW + w;
+  if (DW || b < nblk) load_k(b);
+  for (int b0 = blockIdx.x * NW; DW ? b0 < nblk : b < nblk; b0 += stride, b += stride) {
+    const int t = b * 32 + (lane % 32);
+    const bool valid = t < n;
+    load_v(b);                                        // wanted after the projection, the softmax and dv
+    f32x16 u[C::UM];
+    project<D>(xk, sWA, lane, u);
+    uint4 xr[C::UK];
+    if constexpr (DW) {
+#pragma unroll
+      for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xk[ks];
+    }
+    if constexpr (!DW) {
+      if (b + stride < nblk) load_k(b + stride);      // next block's k flies during this one
+    }
+    float pp[C::LOC], pm[C::LOC];
+    uint32_t pk[C::NPK];
+    softmax_full<D>(u, pp, pm, pk);
+
+    // dv = phi(k) dS, tokens on the accumulator rows
+    {
+      f32x16 va[L::MB];
+#pragma unroll
+      for (int mb = 0; mb < L::MB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) va[mb][r] = 0.f;
+      const uint4* sva = sVA + lane + opaque_zero();
+      pipelined_operands<L::KS * L::MB, KAHEAD>(
+          [&](int i) { return sva[i * 64]; },
+          [&](int i, uint4 b) {
+            const int ks = i / L::MB, mb = i % L::MB;
+            uint4 aq; aq.x = pk[4 * ks]; aq.y = pk[4 * ks + 1]; aq.z = pk[4 * ks + 2]; aq.w = pk[4 * ks + 3];
+            va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(aq), as_f16x8(b), va[mb], 0, 0, 0);
+          });
+      store_token_rows<D, STREAM>(dvb, rw.sn, b * 32, n, lane, va, inv_scale, dv_add);
+    }
+
+    // g = v dS^T + dz, rows laid out like phi
+    float gp[C::LOC], gm[C::LOC];
+    {
+      f32x16 ga[G::GM];
+#pragma unroll
+      for (int mb = 0; mb < G::GM; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
+      const uint4* sga = sGA + lane + opaque_zero();
+      pipelined_operands<G::KS * G::GM, KAHEAD>(
+          [&](int i) { return sga[i * 64]; },
+          [&](int i, uint4 a) {
+            const int ks = i / G::GM, mb = i % G::GM;
+            uint4 bq;
+            bq.x = bf16x2_to_f16x2(vr[ks].x); bq.y = bf16x2_to_f16x2(vr[ks].y);
+            bq.z = bf16x2_to_f16x2(vr[ks].z); bq.w = bf16x2_to_f16x2(vr[ks].w);
+            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
+          });
+#pragma unroll
+      for (int mb = 0; mb < G::GM; ++mb) {
+        const int f0 = (mb < G::GM / 2 ? 0 : C::HALF) + g * C::LOC + 16 * (mb % (G::GM / 2));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float val = fmaf(ga[mb][r], inv_scale, sZ[f0 + r]);
+          if (mb < G::GM / 2) gp[16 * mb + r] = val; else gm[16 * (mb - G::GM / 2) + r] = val;
+        }
+      }
+    }
+    float du[C::LOC];
+    phi_jacobian<D>(gp, gm, pp, pm, du);
+    {
+      f32x16 xa[L::MB];
+      float its;
+      uint32_t dub[C::LOC / 2];
+      float blk_its = 0.f;
+      du_to_dx<D, KAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
+      // the next block's k rows (with the dW~ accumulator resident they do not fit beside the middle of the chain), before the dk
+      // stores: a wait for them must not wait for the stores
+      if constexpr (DW) load_k(b + stride);
+      store_token_rows<D, STREAM>(dkb, rw.sn, b * 32, n, lane, xa, its);
+      if constexpr (DW) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          __syncthreads();                             // the tiles' previous readers are done
+          if (w / 4 == half) {
+            // (addresses worked out here, from a lane index the optimiser cannot hoist: held across the loop they end up
+            // in scratch memory, and a wait for a scratch load also waits for the dk stores just issued)
+            const int lz = lane + opaque_zero();
+            DWT::park_x(xr, sX, w % 4, lz);
+            DWT::park_du(dub, blk_its, sU, sRed, w % 4, lz);
+          }
+          __syncthreads();
+          dwt.contract(sX, sU, sRed, lane + opaque_zero());
+        }
+      }
+    }
+  }
+  if constexpr (DW) dwt.store(dw_part + ((size_t)bh * gridDim.x + blockIdx.x) * (size_t)D * C::HALF, lane);
+}
+
+template <int D, bool DW>
+constexpr size_t q_smem() {
+  return sizeof(uint4) * (Cfg<D>::W_IMG + GradLayout<D>::IMG + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64)
+       + 2 * (size_t)kTile * D * 2 + kTile * 2 + (D + 8) * sizeof(float) + (DW ? DwTile<D, 4>::DU_BYTES : 0);
+}
+template <int D, bool DW>
+constexpr size_t k_smem() {
+  // the prologue's scratch lies where the DW tiles are afterwards
+  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + NTK / 64 + 4) * sizeof(float);
+  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, NTK / 64>::DU_BYTES : 0;
+  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64 + GradLayout<D>::IMG
+                          + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64) + (2 * D + 8) * sizeof(float)
+       + (scratch > tiles ? scratch : tiles);
+}
+template <int D, bool CENTRE, bool STREAM>
+hipError_t run_bwd_as(const BwdArgs& a, const Plan& p, hipStream_t s) {
+  hipError_t e;
+  // dW~ partials: [BH][P] blocks of the query side, then [BH][KP] of the key side
+  const size_t side_elems = (size_t)p.BH * p.P * D * (D / 2);
+  auto launch_q = [&](auto kernel) -> hipError_t {
+    const size_t smem = a.dwq ? q_smem<D, true>() : q_smem<D, false>();
+    hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
+    if (e2 != hipSuccess) return e2;
+    decltype(kernel)::value<<<dim3(p.P, p.BH), NTQ, smem, s>>>(
+        (const uint16_t*)a.q, (const uint16_t*)a.dout, (const uint16_t*)a.wq, a.state, a.vbar, (uint16_t*)a.dq, a.partials, a.dw_part,
+        (const uint16_t*)a.blend_in, a.blend_r, a.dr_part, a.cs_part, p.H, p.n, p.P, p.rows);
+    return hipGetLastError();
+  };
+  if (a.blend_in && a.blend_dr)
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, STREAM, true, true, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, STREAM, true, true, CENTRE, false>>{});
+  else if (a.blend_in)
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, STREAM, true, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, STREAM, true, false, CENTRE, false>>{});
+  else
+    e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, STREAM, false, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, STREAM, false, false, CENTRE, false>>{});
+  if (e != hipSuccess) return e;
+  if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
+  auto launch_k = [&](auto kernel, size_t smem) -> hipError_t {
+    hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
+    if (e2 != hipSuccess) return e2;
+    decltype(kernel)::value<<<dim3(p.KP, p.BH), NTK, smem, s>>>(
+        (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.wk, a.dstate, (uint16_t*)a.dk, (uint16_t*)a.dv,
+        a.dw_part + side_elems, a.vbar, a.cs_part, p.H, p.n, p.P, p.rows);
+    return hipGetLastError();
+  };
+  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, true>>{}, k_smem<D, true>()) : launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, false>>{}, k_smem<D, false>());
+  if (e != hipSuccess) return e;
+  if (a.dwq || a.dwk) {
+    if ((e = launch_dw_reduce2(a.dwq ? a.dw_part : nullptr, a.dwq, p.P, a.dwk ? a.dw_part + side_elems : nullptr, a.dwk, p.KP, p, s)) != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+template <bool STREAM>
+hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
+  if (p.centred) return p.d == 128 ? run_bwd_as<128, true, STREAM>(a, p, s) : run_bwd_as<64, true, STREAM>(a, p, s);
+  return p.d == 128 ? run_bwd_as<128, false, STREAM>(a, p, s) : run_bwd_as<64, false, STREAM>(a, p, s);
+}
+
+}  // namespace
+
+}  // namespace linattn

@@ -1,5 +1,5 @@
 // fp32-arithmetic backward path, on fp32 tensors (the 1e-5 accuracy contract) or on bf16 tensors (LINATTN_BF16_F32MATH), every
-// product on exact bf16 pieces (f32_split.h).  Same mathematics as bwd_bf16.hip (chain rule through Eq. 3 and Eq. 5):
+// product on exact bf16 pieces (f32_split.h).  Same mathematics as bwd_bf16.h (chain rule through Eq. 3 and Eq. 5):
 //   grad_f32_kernel, query side : phi(q), den, G = dO S^T, delta = phi . G / den, dL/dphi = (G - delta z) / den, du, dq
 //   state_f32_kernel (weighted) : dS = sum phi(q)^T dO / den, dz = -sum phi(q) delta / den; split-n partials, reduced
 //   grad_f32_kernel, key side   : phi(k), dv = phi(k) dS, dL/dphi = v dS^T + dz, du, dk

@@ -276,7 +276,7 @@ __device__ __forceinline__ float octet_dot(const float (&f)[D / 2], const float*
 template <int D, typename T, typename Value>
 __device__ __forceinline__ void store_rows(T* base, size_t sn, int t0, int n, int lane, Value value) {
   constexpr int MB = D / 32;
-  const TokenRows<MB * (int)sizeof(T), true> rows(base, sn * sizeof(T), t0, n, lane);
+  const TokenRows<MB * (int)sizeof(T)> rows(base, sn * sizeof(T), t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     float y[MB];
@@ -287,11 +287,11 @@ __device__ __forceinline__ void store_rows(T* base, size_t sn, int t0, int n, in
       vec v;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) v[mb] = y[mb];
-      rows.store(r, v);
+      rows.template store<true>(r, v);
     } else if constexpr (MB == 4) {
-      rows.store(r, make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])));
+      rows.template store<true>(r, make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])));
     } else {
-      rows.store(r, pack_bf16x2(y[0], y[1]));
+      rows.template store<true>(r, pack_bf16x2(y[0], y[1]));
     }
   }
 }

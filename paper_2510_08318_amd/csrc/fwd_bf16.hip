@@ -256,9 +256,9 @@ __global__ __launch_bounds__(64 * NW, NW == 12 ? (D == 64 && !BLEND && !SUM ? 4 
         // stores the tail of out stays dirty in the last-level cache and is written back under
         // whatever kernel runs next (measured: the next call's state pass loses 30 us, this pass
         // gains 20 us)
-        const TokenRows<sizeof(Piece), true> rows(ob, rw.sn * 2, b * 32, n, lane);
+        const TokenRows<sizeof(Piece)> rows(ob, rw.sn * 2, b * 32, n, lane);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) rows.store(r, word[r]);
+        for (int r = 0; r < 16; ++r) rows.template store<true>(r, word[r]);
       }
     }
     if (sh.rest < sh.hi) __syncthreads();                // the next head's images take the place of these

@@ -201,6 +201,14 @@ struct BwdArgs {
   float* dr_part;
 };
 
+// Whether the bf16 backward stores its gradients non-temporally (the ReLU map: dq and dk): where the three take more than half of the
+// last-level cache (256 MB).  Left dirty there, large ones are written back under the kernels that follow and displace the rows these
+// read; small ones serve whoever reads them next.  Ordinary / non-temporal, us.  A training step and then one pass over each gradient: 12
+// heads x 4133 x 64 (6 MB a gradient) 65.6 / 69.9, 12 x 8190 x 128 (25 MB) 150 / 156, ReLU 147 / 154; 12 x 16000 (49 MB) 234 / 231, ReLU
+// 210 / 209; 12 x 32760 (100 MB) 428 / 423, ReLU 377 / 374; 40 x 20000 (205 MB) 812 / 809, ReLU 737 / 728.  The step alone, whose
+// forward is then the next to run: 51.0 / 49.9, 120.5 / 118.3, 184 / 175, 340 / 324, 603 / 587.
+inline bool stream_gradients(const Plan& p) { return (size_t)p.BH * p.n * p.d * 2 * 3 > ((size_t)128 << 20); }
+
 // A kernel instantiation as a value, for launch code shared by several.
 template <auto Kernel>
 struct KernelTag {
@@ -252,6 +260,7 @@ hipError_t launch_apply_bf16(const void* q, const void* wq, const float* partial
 // triple whose output is null is skipped.
 hipError_t launch_dw_reduce2(const float* part0, float* dw0, int P0, const float* part1, float* dw1, int P1, const Plan& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
+hipError_t launch_bwd_bf16_stream(const BwdArgs& a, const Plan& p, hipStream_t s);      // its form with non-temporal gradients
 hipError_t launch_bwd_f32(const BwdArgs& a, const Plan& p, hipStream_t s);
 hipError_t launch_relu_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s);
 

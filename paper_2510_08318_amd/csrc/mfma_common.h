@@ -519,8 +519,8 @@ __device__ __forceinline__ float half_wave_sum(float x) {
 // stores as well), and one vector instruction for an address.  Choosing between the row and a sink by a select took five, 64 more a block: a pass
 // of 4 x 1000 x 64 8.5 us, now 8.0, of 12 x 4133 x 64 7.7, now 6.9; the fp32-arithmetic key side, which that kept from spilling, 164 -> 156
 // at 12 x 32760 x 128; nothing where the memory or the barriers of dW~ are what is waited for.
-// All arguments but the lane are uniform.  NT: non-temporal.
-template <int PIECE, bool NT = false>
+// All arguments but the lane are uniform.
+template <int PIECE>
 struct TokenRows {
   __amdgpu_buffer_rsrc_t rows;
   uint32_t at, pitch;
@@ -531,11 +531,11 @@ struct TokenRows {
     const int lz = lane + opaque_zero();                   // (the sixteen offsets are not held across a caller's loop)
     at = (uint32_t)(4 * (lz / 32)) * pitch + (uint32_t)(PIECE * (lz % 32));
   }
-  template <typename V>
+  template <bool STREAM, typename V>                       // STREAM: non-temporal
   __device__ __forceinline__ void store(int r, V v) const {
     static_assert(sizeof(V) == PIECE, "a lane's piece of a row");
     const uint32_t off = at + (uint32_t)(8 * (r / 4) + r % 4) * pitch;
-    constexpr int aux = NT ? 2 : 0;
+    constexpr int aux = STREAM ? 2 : 0;
     if constexpr (PIECE == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rows, off, 0, aux);
     else if constexpr (PIECE == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rows, off, 0, aux);
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, off, 0, aux);
@@ -543,36 +543,33 @@ struct TokenRows {
 };
 
 // Accumulators with tokens on the rows (lane (c,g), register r: token t0 + 8*(r/4) + 4g + r%4,
-// channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.
-// Non-temporal: a gradient's dirty tail in the last-level cache is otherwise written back under the kernels after it, and takes the place of rows
-// that they read.  Ordinary / non-temporal stores of dq, dk, dv, 12 heads x 32760 x 128, us: bwd_q 110 / 112, bwd_k 128 / 121, and the next
-// call's state pass 61 / 53 and query pass 54 / 50 (40 x 20000: state pass 110 / 85); ReLU map 91 / 87, 87 / 94, 44 / 44, 54 / 46.
-template <int D>
+// channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.  STREAM: non-temporal (stream_gradients).
+template <int D, bool STREAM>
 __device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
                                                  const f32x16 (&acc)[D / 32], float mul, const float (&add)[D / 32]) {
   constexpr int MB = D / 32;
   static_assert(MB == 2 || MB == 4, "head width 64 or 128");
-  const TokenRows<2 * MB, true> rows(base, sn * 2, t0, n, lane);
+  const TokenRows<2 * MB> rows(base, sn * 2, t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     if constexpr (MB == 4) {
       uint2 v;
       v.x = pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1]));
       v.y = pack_bf16x2(fmaf(acc[2][r], mul, add[2]), fmaf(acc[3][r], mul, add[3]));
-      rows.store(r, v);
+      rows.template store<STREAM>(r, v);
     } else {
-      rows.store(r, pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1])));
+      rows.template store<STREAM>(r, pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1])));
     }
   }
 }
 
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
                                                  const f32x16 (&acc)[D / 32], float mul) {
   float zero[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) zero[i] = 0.f;
-  store_token_rows<D>(base, sn, t0, n, lane, acc, mul, zero);
+  store_token_rows<D, STREAM>(base, sn, t0, n, lane, acc, mul, zero);
 }
 
 // 32x32x16 MFMA on operands carried as f16x8 registers whose bits are fp16 or (BF16) bf16.

@@ -14,7 +14,7 @@
 //   den_i = phi(q_i).z + eps, o_i = phi(q_i) S / den_i, delta_i = dO_i . o_i
 //   dphi(q_i) = (S dO_i - delta_i z) / den_i;  dS = sum_i phi(q_i)^T dO_i / den_i;  dz = -sum_i phi(q_i) delta_i / den_i
 //   dphi(k_j) = dS v_j + dz;  dv_j = dS^T phi(k_j)
-// Operands that are gradients are scaled by powers of two before the cast to fp16, as in bwd_bf16.hip.
+// Operands that are gradients are scaled by powers of two before the cast to fp16, as in bwd_bf16.h.
 #include "kernels.h"
 #include "mfma_common.h"
 
@@ -278,6 +278,7 @@ struct RowStore {
     const int row = lane % 32;
     *reinterpret_cast<uint4*>(buf + row * D * 2 + (((2 * ks + lane / 32) ^ swz<D>(row)) * 16)) = x;
   }
+  template <bool STREAM>                                    // non-temporal
   __device__ __forceinline__ void flush(uint16_t* base, size_t sn, int t0, int n) const {
     __builtin_amdgcn_wave_barrier();
     const int c = lane % CH;
@@ -285,7 +286,9 @@ struct RowStore {
     for (int i = 0; i < 32 / RPI; ++i) {
       const int row = i * RPI + lane / CH, t = t0 + row;
       const uint4 x = *reinterpret_cast<const uint4*>(buf + row * D * 2 + ((c ^ swz<D>(row)) * 16));
-      st_nt(reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c), x);
+      uint4* dst = reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c);
+      if constexpr (STREAM) st_nt(dst, x);
+      else *dst = x;
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -300,7 +303,7 @@ struct RowStore {
 // at the memory's rate): with four wavefronts that did all of this one after another, read q a second time for the mask and summed delta
 // across lanes it took 119 us at 12 heads x 32760 x 128, 91 now.
 constexpr int NTQ = 512;
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
                                                          const float* __restrict__ state, float* __restrict__ mean_row,
                                                          uint16_t* __restrict__ dq, float* __restrict__ partials,
@@ -470,7 +473,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
         for (int e = 0; e < 8; ++e) v[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], r1, -(r2 * z[e])) : 0.f;
         out.put(ks, make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])));
       }
-      out.flush(dqb, rw.sn, tile * kTile + 32 * pw, n);
+      out.template flush<STREAM>(dqb, rw.sn, tile * kTile + 32 * pw, n);
     }
   } else {
     f32x16 s[WMN][WMN], zacc;
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
 // 128 (81 + 9 for the images in a kernel of their own, with k read twice); the rows take 69 us at the memory's rate.  The next block's
 // rows requested a block ahead: 93 us.
 constexpr int NTK = 512;
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                          const float* __restrict__ dstate, const float* __restrict__ mean_row,
                                                          uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
@@ -589,7 +592,7 @@ __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restr
         for (int mb = 0; mb < L::MB; ++mb)
           va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(sc[(ks * L::MB + mb) * 64]), va[mb], 0, 0, 0);
       }
-      store_token_rows<D>(dvb, rw.sn, b * 32, n, lane, va, inv_scale);
+      store_token_rows<D, false>(dvb, rw.sn, b * 32, n, lane, va, inv_scale);
     }
     {
       f32x16 ga[G::GM];
@@ -608,7 +611,7 @@ __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restr
         for (int e = 0; e < 8; ++e) u[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], inv_scale, z[e]) : 0.f;
         out.put(ks, make_uint4(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]), pack_bf16x2(u[6], u[7])));
       }
-      out.flush(dkb, rw.sn, b * 32, n);
+      out.template flush<STREAM>(dkb, rw.sn, b * 32, n);
     }
   }
 }
@@ -634,16 +637,16 @@ hipError_t run_state(const void* k, const void* v, float* partials, const Plan& 
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, bool STREAM>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  if ((e = set_smem_once<relu_bwd_q_kernel<D>>(q_smem<D>())) != hipSuccess) return e;
-  relu_bwd_q_kernel<D><<<dim3(p.P, p.BH), NTQ, q_smem<D>(), s>>>((const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, a.vbar,
+  if ((e = set_smem_once<relu_bwd_q_kernel<D, STREAM>>(q_smem<D>())) != hipSuccess) return e;
+  relu_bwd_q_kernel<D, STREAM><<<dim3(p.P, p.BH), NTQ, q_smem<D>(), s>>>((const uint16_t*)a.q, (const uint16_t*)a.dout, a.state, a.vbar,
                                                                 (uint16_t*)a.dq, a.partials, p.H, p.n, p.P, p.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{}, s)) != hipSuccess) return e;
-  if ((e = set_smem_once<relu_bwd_k_kernel<D>>(k_smem<D>())) != hipSuccess) return e;
-  relu_bwd_k_kernel<D><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>((const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar,
+  if ((e = set_smem_once<relu_bwd_k_kernel<D, STREAM>>(k_smem<D>())) != hipSuccess) return e;
+  relu_bwd_k_kernel<D, STREAM><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>((const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar,
                                                                  (uint16_t*)a.dk, (uint16_t*)a.dv, p.H, p.n, p.rows);
   return hipGetLastError();
 }
@@ -655,7 +658,8 @@ hipError_t launch_relu_state_bf16(const void* k, const void* v, float* partials,
 }
 
 hipError_t launch_relu_bwd_bf16(const BwdArgs& a, const Plan& p, hipStream_t s) {
-  return p.d == 128 ? run_bwd<128>(a, p, s) : run_bwd<64>(a, p, s);
+  if (stream_gradients(p)) return p.d == 128 ? run_bwd<128, true>(a, p, s) : run_bwd<64, true>(a, p, s);
+  return p.d == 128 ? run_bwd<128, false>(a, p, s) : run_bwd<64, false>(a, p, s);
 }
 
 }  // namespace linattn
