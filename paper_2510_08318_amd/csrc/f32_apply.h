@@ -117,13 +117,13 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
 // Prologue of the passes with images of pieces, in eighths of a unit (make_deal).  Head-wise / even deal at 12 heads x 32760 (7 / 6 rounds), us: query
 // pass 119.5 / 116.7 (fp32), 85.6 / 82.0 (bf16 tensors), gradients 153 / 145 and 100 / 99.  A pass with heads of their own keeps
 // the loop-free form (EVEN = false): the loop over a workgroup's heads costs it up to half a microsecond.
-constexpr int kF32Prologue = 3;
+constexpr DealCost kF32Cost{3};
 template <int D, int KIND, typename T, bool BLEND>
 hipError_t run_apply_pass(const void* q, const void* wq, const float* state, void* out,
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
   constexpr bool EV = D == 128;                            // (width 64 has little to gain)
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Prologue, EV);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost, EV);
   auto launch = [&](auto kernel) -> hipError_t {
     const hipError_t e = set_smem_once<decltype(kernel)::value>(smem);
     if (e != hipSuccess) return e;

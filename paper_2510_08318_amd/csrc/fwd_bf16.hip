@@ -602,8 +602,15 @@ namespace {
 // 19.4 / 17.2; 5 x 15000 x 128 2 / 1, 14.6 / 13.2; 7 x 20000 x 64 3 / 2, 10.3 / 10.3, with blend 14.6 / 13.9; but 12 x 8190 x 128 2 / 2, 15.5 / 15.4;
 // 26 x 2222 x 64 1 / 1, 7.2 / 7.7; 3 x 500 x 128 1 / 1, 9.7 / 11.7; 4 x 1000 x 64 1 / 1, 8.0 / 8.8; 12 x 32760 x 128 6 / 5, with blend 67 / 73,
 // ReLU 36.7 / 37.7.
-// The prologue in eighths of a unit: 3 to 4 us against 8 at 12 heads x 32760 x 128.
-constexpr int kApplyPrologue = 3;
+// The costs of the deal lose least, among 960 sets of them, over 355 calls of 1 to 255 heads with every form timed.  Calls, head by head / evenly, us:
+// 153 heads x 763 x 128 47.0 / 50.0 (3 rounds for 153 compute units, 2 for all), 40 x 20000 x 128 179.9 / 181.9, 30 x 17550 x 64 61.1 / 62.4; but 12 x 32760 x
+// 128 99.8 / 97.6, 160 x 4000 x 128 158.9 / 154.5, 40 x 75600 x 128 631 / 626.  The blended pass of width 128, whose rounds are the longest, gains
+// more: 138 x 1563 89.6 / 79.9, 154 x 1102 73.9 / 69.1.
+// 12 wavefronts with an even deal, two prologues around one round each, pay in that pass alone, and where a head's last unit is short: head by head
+// with 8 / evenly with 12 where it has 8 of 12 blocks, 155 x 1019 69.5 / 66.2; evenly with 8 / with 12 where it has 9 or more, 144 x 1051 65.9 / 68.8,
+// 54 x 3451 71.5 / 75.7 (without blend 24 x 7995 58.3 / 61.5).
+template <int D, bool BLEND>
+constexpr DealCost kApplyCost = D == 128 && BLEND ? DealCost{3} : DealCost{4, 2, 5, 240};
 template <int D, bool BLEND, int KIND, bool SUM, int NW>
 hipError_t run_apply_waves(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                            const float* blend_r, const Plan& p, const Split& deal, hipStream_t s) {
@@ -618,7 +625,8 @@ template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   const int blocks = (p.n + 31) / 32;
-  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyPrologue), d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyPrologue);
+  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>);
+  const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, D == 128 && BLEND && (blocks + 11) % 12 < 8);
   const int r8 = split_rounds(d8);
   return r8 <= 3 && split_rounds(d12) < r8 ? run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s)
                                            : run_apply_waves<D, BLEND, KIND, SUM, 8>(q, wq, partials, state, out, blend_in, blend_r, p, d8, s);

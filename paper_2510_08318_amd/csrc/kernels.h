@@ -135,20 +135,29 @@ inline dim3 grid_of(const Split& s) { return s.share ? dim3(s.share, s.G / s.sha
 // The deal of a kernel that builds a head's operand images in its prologue: `per_head` units of each head to one workgroup per compute
 // unit (one per head where there are more heads), either the same number of workgroups to every head (each then has one head) or the
 // units of all heads evenly (a workgroup may then have the end of one head and the start of the next, and builds images twice).
-// prologue8: what a prologue takes, in eighths of a unit's time.  may_even = false: always the first form, for kernels without a loop over
-// a workgroup's heads.
-inline Split make_deal(int BH, int per_head, int prologue8, bool may_even = true) {
+// may_even = false: always the first form, for kernels without a loop over a workgroup's heads.
+// What the forms cost, in eighths of a round in which every compute unit has a unit: a prologue; a round with units for a part of the compute
+// units, `fixed` and in proportion to that part up to `full` of them, at least `least` (the memory system serves fewer faster; the defaults,
+// 8 for any part, where arithmetic bounds a round).
+struct DealCost {
+  int prologue, fixed = 8, least = 8, full = kCUs;
+};
+inline Split make_deal(int BH, int per_head, DealCost cost, bool may_even = true) {
   Split s{};
   s.ntile = per_head;
   s.T = (long long)BH * per_head;
   s.PS = 1;
   s.share = kCUs / BH < per_head ? (BH < kCUs ? kCUs / BH : 1) : per_head;
   s.G = BH * s.share;
-  if (may_even && BH < kCUs) {
-    const int even = s.T < kCUs ? (int)s.T : kCUs;
-    const long long cost_share = 8LL * ((per_head + s.share - 1) / s.share) + prologue8;
-    const long long cost_even = 8 * ((s.T + even - 1) / even) + 2 * prologue8;
-    if (cost_even < cost_share) { s.G = even; s.share = 0; }
+  if (may_even && s.T > kCUs && BH < kCUs) {
+    auto round = [&](long long units) {                    // times full
+      const long long t = cost.fixed * cost.full + (8 - cost.fixed) * (units < cost.full ? units : cost.full);
+      return t > cost.least * cost.full ? t : (long long)cost.least * cost.full;
+    };
+    const long long rounds = (per_head + s.share - 1) / s.share, whole = (s.T - 1) / kCUs;
+    const long long by_head = (rounds - 1) * round(s.G) + round(BH * (per_head - (rounds - 1) * s.share)) + cost.prologue * cost.full;
+    const long long even = whole * round(kCUs) + round(s.T - whole * kCUs) + 2 * cost.prologue * cost.full;
+    if (even < by_head) { s.G = kCUs; s.share = 0; }
   }
   finish_split(s);
   return s;

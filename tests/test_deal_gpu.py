@@ -51,11 +51,28 @@ def test_step_with_heads_that_share_workgroups(mode, d, form, layout):
     _step(mode, d, form, layout, SHARED)
 
 
+# The bf16 query pass, whose rounds on a part of the compute units cost less, has 600 tokens dealt head by head (the blended one of width 128
+# evenly); 1050 tokens, five units a head, it deals evenly: 2 to 3 a workgroup.
+@pytest.mark.parametrize("form", ["frozen map", "blend", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_query_pass_with_heads_that_share_workgroups(d, form):
+    _step("bf16", d, form, "bhnd", (43, 3, 1050))
+
+
 # 100 heads of 640 tokens: two workgroups a head, two rounds of 8 wavefronts or one of 12, which the query pass takes then
 @pytest.mark.parametrize("form", ["frozen map", "blend", "relu"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_query_pass_of_twelve_wavefronts(d, form):
     _step("bf16", d, form, "bhnd", (50, 2, 640 - 3))
+
+
+# Twelve wavefronts in the forms that these miss.  103 heads of 1140 tokens, width 64: nine tiles, so the state comes from a reduction; two
+# workgroups a head, three rounds of 8 wavefronts or two of 12.  155 heads of 1019 tokens with blend, width 128: three units of 12 to a
+# head, the last with 8 blocks, dealt evenly over all compute units.
+@pytest.mark.parametrize("d,form,shape", [(64, "frozen map", (103, 1, 1140)), (64, "blend", (103, 1, 1140)), (64, "relu", (103, 1, 1140)),
+                                          (128, "blend", (31, 5, 1019))])
+def test_other_query_passes_of_twelve_wavefronts(d, form, shape):
+    _step("bf16", d, form, "bhnd", shape)
 
 
 def _step(mode, d, form, layout, shape):

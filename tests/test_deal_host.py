@@ -16,7 +16,7 @@ PROGRAM = r"""
 #include <vector>
 using namespace linattn;
 typedef __int128 wide;
-static long bad = 0, even_deals = 0;
+static long bad = 0, even_deals = 0, part_deals = 0;
 static void arithmetic(const Split& s) {
   for (int k = 0; k < 40; ++k) {
     const int g = k == 0 ? 0 : k == 1 ? s.G : rand() % (s.G + 1);
@@ -64,7 +64,7 @@ int main() {
   for (int BH : heads)
     for (int per : units)
       for (int c : {0, 3, 8}) {
-        const Split s = make_deal(BH, per, c);
+        const Split s = make_deal(BH, per, {c});
         arithmetic(s);
         even_deals += !s.share;
         if (s.T < 400000) cover(s);
@@ -74,11 +74,23 @@ int main() {
           bad += !s.share && 8 * most_units(s) + c >= 8 * by_head;        // the second prologue has to pay
         }
       }
+  // rounds for a part of the compute units that cost less: still every unit once, and never more units to a workgroup than head by head
+  for (int BH : heads)
+    for (int per : units) {
+      const Split s = make_deal(BH, per, {4, 2, 5, 240});
+      arithmetic(s);
+      if (s.T >= 400000) continue;
+      cover(s);
+      if (BH >= kCUs) continue;
+      const int share = kCUs / BH < per ? kCUs / BH : per, by_head = (per + share - 1) / share;
+      bad += s.G > kCUs || most_units(s) > by_head;
+      part_deals += s.share != make_deal(BH, per, {4}).share;
+    }
   // kernels without the loop over a workgroup's heads: a head to a workgroup at every length up to the largest n (2^30 tokens), where the even deal would
   // save any number of rounds
   for (int BH : heads)
     for (int per : {1, 2, 3, 255, 256, 1000, 1 << 17, 1 << 18, 1 << 20, 1 << 22}) {
-      const Split s = make_deal(BH, per, 3, false);
+      const Split s = make_deal(BH, per, {3}, false);
       bad += s.share < 1 || s.G != BH * s.share;
       if (s.share < 1) continue;
       arithmetic(s);
@@ -93,8 +105,8 @@ int main() {
     finish_split(s);
     arithmetic(s);
   }
-  printf("bad %ld even %ld\n", bad, even_deals);
-  return bad != 0 || even_deals == 0;
+  printf("bad %ld even %ld part %ld\n", bad, even_deals, part_deals);
+  return bad != 0 || even_deals == 0 || part_deals == 0;
 }
 """
 
