@@ -35,12 +35,12 @@ __device__ __forceinline__ uint32_t piece_word(const uint32_t& p, int) { return 
 __device__ __forceinline__ void set_piece_word(uint2& p, int i, uint32_t v) { if (i) p.y = v; else p.x = v; }
 __device__ __forceinline__ void set_piece_word(uint32_t& p, int, uint32_t v) { p = v; }
 
-// The state of head bh as the sum of its workgroups' partials, pairwise, to sum[(D+1)*D/4] in LDS and, if given, to dst.  16 loads of
+// The state of head bh as the sum of its workgroups' partials, pairwise, to sum[(D+1)*D/4] in LDS and, if given, to dst.  Up to 20 loads of
 // a thread are in flight; those of a missing slot repeat the last one's and count as zero (branch-free).
 template <int D> constexpr int kSumSlots = D == 64 ? 8 : 2;      // see sum_in_apply
 template <int N, int NTHREADS, int NS>
 __device__ __forceinline__ void sum_slots_of(const float4* __restrict__ src, int cnt, float4* sum, float4* __restrict__ dst, int tid) {
-  constexpr int EB = 16 / NS;
+  constexpr int ALL = (N + NTHREADS - 1) / NTHREADS, EB = ALL * NS <= 20 ? ALL : 16 / NS;      // elements at a time: all of a thread's, if they fit
   auto add = [](float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
 #pragma unroll 1
   for (int e0 = tid; e0 < N; e0 += EB * NTHREADS) {
@@ -80,6 +80,10 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
   sum_slots_of<N, NTHREADS, 2>(src, cnt, sum, dst, tid);
 }
 
+// Which query passes may have their units dealt evenly (run_apply); the others have no loop over a workgroup's heads.
+template <int D, bool BLEND, bool SUM, int NW>
+constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
+
 // The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
 // us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 keeps the loop's schedule from spreading
 // into the prologue's registers: without it the CogVideoX-2B shape loses 2 us.
@@ -109,7 +113,9 @@ __global__ __launch_bounds__(64 * NW, NW == 12 ? (D == 64 && !BLEND && !SUM ? 4 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 32;
-  for (Share sh = first_share(deal, blockIdx.x, blockIdx.y); sh.there; sh = next_share(deal, blockIdx.x, sh)) {
+  constexpr bool EVEN = apply_even<D, BLEND, SUM, NW>;
+  for (Share sh = EVEN ? first_share(deal, blockIdx.x, blockIdx.y) : head_share(deal, blockIdx.x, blockIdx.y); sh.there;
+       sh = EVEN ? next_share(deal, blockIdx.x, sh) : Share{}) {
     const int bh = sh.bh, h = bh % H;
     const uint16_t* qb = q + head_base(rw, bh, H);
     uint16_t* ob = out + head_base(rw, bh, H);
@@ -261,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, NW == 12 ? (D == 64 && !BLEND && !SUM ? 4 
         for (int r = 0; r < 16; ++r) rows.template store<true>(r, word[r]);
       }
     }
-    if (sh.rest < sh.hi) __syncthreads();                // the next head's images take the place of these
+    if (EVEN && sh.rest < sh.hi) __syncthreads();        // the next head's images take the place of these
   }
 }
 
@@ -625,11 +631,14 @@ template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   const int blocks = (p.n + 31) / 32;
-  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>);
-  const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, D == 128 && BLEND && (blocks + 11) % 12 < 8);
-  const int r8 = split_rounds(d8);
-  return r8 <= 3 && split_rounds(d12) < r8 ? run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s)
-                                           : run_apply_waves<D, BLEND, KIND, SUM, 8>(q, wq, partials, state, out, blend_in, blend_r, p, d8, s);
+  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>, apply_even<D, BLEND, SUM, 8>);
+  if constexpr (!SUM || kSumSlots<D> * kTile > 8 * 32) {   // (one unit of 8 a head otherwise)
+    const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, apply_even<D, BLEND, SUM, 12> && (blocks + 11) % 12 < 8);
+    const int r8 = split_rounds(d8);
+    if (r8 <= 3 && split_rounds(d12) < r8)
+      return run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s);
+  }
+  return run_apply_waves<D, BLEND, KIND, SUM, 8>(q, wq, partials, state, out, blend_in, blend_r, p, d8, s);
 }
 
 template <int D, bool SUM>
