@@ -653,10 +653,15 @@ hipError_t pick_apply(const void* q, const void* wq, const float* partials, floa
 }  // namespace
 
 // Short calls, where a launch is a fifth of the time: the query pass sums the partials itself, up to eight tiles a head at width 64 and
-// two at 128 (at least as many as slots), where each of the at most three workgroups of a head reads them.  A call, reduction launched / summed
-// here, us: width 64, 4 heads x 1000 15.4 / 13.7, 128 x 1000 24.9 / 21.5, 1 x 100 15.0 / 12.9; width 128, 1 x 100 15.6 / 14.4,
-// 128 x 100 24.4 / 17.8; but 4 x 300 21.1 / 21.5 and 12 x 1000 24.7 / 28.7: a state of 66 KB takes a workgroup that long to sum.
-bool sum_in_apply(const Plan& p) { return p.split.ntile <= (p.d == 64 ? kSumSlots<64> : kSumSlots<128>); }
+// two at 128 (at least as many as slots), where each of the at most four workgroups of a head (one at 128) reads them.  A call, reduction
+// launched / summed here, us: width 64, 1 head x 100 10.0 / 8.4, 30 x 500 13.4 / 11.9, 24 x 768 14.1 / 12.9, 4 x 1000 12.1 / 11.3, 128 x 1000 23.1 / 20.5,
+// 36 x 1024 18.5 / 17.9; but where each of eight tiles has a slot of its own and the heads are many, 16 x 1024 13.1 / 13.3, 30 x 1000 15.3 / 16.1, 12 x 1024
+// 12.9 / 12.6; nine to sixteen tiles 12 x 2000 15.1 / 17.1, 128 x 2000 33.1 / 31.4.  Width 128: 1 x 100 15.0 / 14.0, 128 x 100 23.7 / 17.2, 255 x 256 36.2 / 31.7; three
+// or four tiles, a state of 66 KB each, 4 x 500 17.9 / 18.5, 128 x 500 32.8 / 30.1.
+bool sum_in_apply(const Plan& p) {
+  if (p.d == 128) return p.split.ntile <= kSumSlots<128>;
+  return p.split.ntile < kSumSlots<64> || (p.split.ntile == kSumSlots<64> && (p.BH <= 12 || p.split.T > kSlots));
+}
 
 hipError_t launch_apply_bf16(const void* q, const void* wq, const float* partials, float* state, void* out,
                              const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {

@@ -76,6 +76,12 @@ def test_query_pass_that_sums_the_partials(n, H, d, relu):
     _check(synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16"), relu=relu)
 
 
+# eight tiles a head, a slot each: summed by the query pass up to 12 heads, by a launch for 13 to 32, by the query pass again beyond
+@pytest.mark.parametrize("H", [12, 13, 32, 33])
+def test_query_pass_at_eight_tiles_a_head(H):
+    _check(synth.generate("C5", n=1001, H=H, B=1, d=64, dtype="bf16"), wgrads=False)
+
+
 @pytest.mark.parametrize("n,d", [(100, 128), (200, 128), (257, 128), (1000, 64)])
 def test_mixed_attention_where_the_query_pass_sums_the_partials(n, d):
     import torch
