@@ -604,7 +604,7 @@ constexpr size_t dw_smem() { return (size_t)4 * (D / 32) * (D / 64) * 16 * 64 * 
 template <int D, int KIND, typename T>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost, grad_even<D, T>);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost<KIND, T, false>, grad_even<D, T>);
   constexpr size_t smem = grad_smem<D, KIND, T>();
   // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which the last pass writes
   float2* weights = static_cast<float2*>(a.dv);

@@ -114,16 +114,20 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
   }
 }
 
-// Prologue of the passes with images of pieces, in eighths of a unit (make_deal).  Head-wise / even deal at 12 heads x 32760 (7 / 6 rounds), us: query
-// pass 119.5 / 116.7 (fp32), 85.6 / 82.0 (bf16 tensors), gradients 153 / 145 and 100 / 99.  A pass with heads of their own keeps
-// the loop-free form (EVEN = false): the loop over a workgroup's heads costs it up to half a microsecond.
-constexpr DealCost kF32Cost{3};
+// What the deal of the passes with images of pieces costs.  Arithmetic bounds a round: query pass, a forward call head by head / evenly, us, bf16
+// tensors 12 heads x 32760 (7 / 6 rounds) 151.8 / 149.5, 160 x 1555 (7 / 5) 118.2 / 113.6, ReLU 161 x 1598 96.4 / 91.8, fp32 tensors 12 x 32760 271.8 /
+// 266.9, 24 x 8000 (4 / 3) 151.5 / 142.0, 153 x 763 (3 / 2) 120 / 117.  With fp32 tensors and no projection (ReLU) or one tensor more (blend) the memory
+// system does: ReLU 169 x 731 88.6 / 91.7, 153 x 763 89.4 / 91.6, with blend 142 x 1013 (4 / 3) 137.1 / 139.3, 151 x 607 90.9 / 95.1; but ReLU 12 x 32760
+// 209.1 / 204.5, with blend 168 x 2213 (9 / 6) 297.5 / 291.2.  A pass with heads of its own keeps the loop-free form (EVEN = false): the loop over a
+// workgroup's heads costs it up to half a microsecond.
+template <int KIND, typename T, bool BLEND>
+constexpr DealCost kF32Cost = sizeof(T) == 4 && (KIND == kPhiRelu || BLEND) ? DealCost{3, 2, 5} : DealCost{3};
 template <int D, int KIND, typename T, bool BLEND>
 hipError_t run_apply_pass(const void* q, const void* wq, const float* state, void* out,
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
   constexpr bool EV = D == 128;                            // (width 64 has little to gain)
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost, EV);
+  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost<KIND, T, BLEND>, EV);
   auto launch = [&](auto kernel) -> hipError_t {
     const hipError_t e = set_smem_once<decltype(kernel)::value>(smem);
     if (e != hipSuccess) return e;

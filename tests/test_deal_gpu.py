@@ -59,6 +59,12 @@ def test_query_pass_with_heads_that_share_workgroups(d, form):
     _step("bf16", d, form, "bhnd", (43, 3, 1050))
 
 
+# The same of the fp32 query passes that are bound by the memory system.
+@pytest.mark.parametrize("form", ["blend", "relu"])
+def test_fp32_query_pass_with_heads_that_share_workgroups(form):
+    _step("f32", 128, form, "bhnd", (43, 3, 1050))
+
+
 # 100 heads of 640 tokens: two workgroups a head, two rounds of 8 wavefronts or one of 12, which the query pass takes then
 @pytest.mark.parametrize("form", ["frozen map", "blend", "relu"])
 @pytest.mark.parametrize("d", [64, 128])
