@@ -13,6 +13,7 @@ from paper_2510_08318_amd import synth
 
 pytestmark = pytest.mark.gpu
 HUGE = 3.4e38            # finite in fp32, Inf when rounded to bf16
+BF16_MAX = (2 - 2.0 ** -7) * 2.0 ** 127
 INF = np.inf
 
 
@@ -245,3 +246,94 @@ def test_tiny_values_keep_what_their_pieces_hold(exponent, bar):
     out, state = _forward(x, False)
     _same(got["out"], out, bar, "out")
     _same(got["state"][:, :, :128], state[:, :, :128], bar, "state")
+
+
+def _shared_workgroup(heads, units):
+    """The two heads of a workgroup that has the end of one and the start of the next, when 256 workgroups take even shares."""
+    for g in range(100, 256):
+        lo, hi = g * heads * units // 256, (g + 1) * heads * units // 256
+        if lo // units != (hi - 1) // units:
+            return lo // units
+    raise AssertionError
+
+
+def _heads(x, first):
+    """The heads first, first + 1 (of all batch items in a row) as a problem of their own."""
+    import copy
+    y = copy.copy(x)
+    y.B, y.H = 1, 2
+    bh = np.arange(first, first + 2)
+    for name in ("q", "k", "v", "dout"):
+        setattr(y, name, getattr(x, name).reshape(-1, x.n, x.d)[bh][None])
+    for name in ("wq", "wk"):
+        setattr(y, name, getattr(x, name)[bh % x.H])
+    return y
+
+
+def _pair(t, first):
+    return t.reshape(-1, *t.shape[2:])[first:first + 2][None]
+
+
+# 129 heads: 3 units of 8 blocks each (600 tokens), 5 (1050), dealt evenly to 256 workgroups, so that most have parts of two heads.  The values
+# that the pieces cannot carry are in one of the two; both heads have to come out right.
+@pytest.mark.parametrize("second", [False, True], ids=["first head", "second head"])
+@pytest.mark.parametrize("dtype,n", [("f32", 1050), ("bf16", 600)])
+def test_huge_state_in_a_workgroup_of_two_heads(dtype, n, second):
+    """ReLU: two tokens whose only feature is 1 leave a state value of 3.3995e38, finite, Inf in bf16."""
+    x = synth.generate("C5", n=n, H=43, B=3, d=128, dtype=dtype)
+    first = _shared_workgroup(129, -(-n // 256))
+    b, h = divmod(first + second, 43)
+    for t, value in ((7, BF16_MAX), (n - 1, 1e36)):
+        _set(x, "k", (b, h, t), 0.0)
+        _set(x, "k", (b, h, t, 0), 1.0)
+        _set(x, "v", (b, h, t, 5), value)
+    got = {name: _pair(t, first) for name, t in _run(x, True).items()}
+    y = _heads(x, first)
+    out = R.relu_fwd_bh(y.q, y.k, y.v)
+    assert got["state"][0, int(second), 0, 5] > (2 - 2.0 ** -8) * 2.0 ** 127     # from here on a value rounds to Inf as bf16
+    _same(got["out"], out, BARS[dtype], "out")
+    # The head with the value: dk is dz but for a few bits, a sum over n tokens of terms of either sign.  Rounding is relative to the terms: with
+    # fp32 terms and sums, a few times 2^-24 of their absolute sum, which is 20 times the root mean square of dz over the features (1.2e33 / 5.4e31, 1050
+    # tokens), so a few times 1.2e-6 of the largest; single features cancel to any degree.  Held to the largest of the head.
+    hit, bar = int(second), max(BARS[dtype], 2e-5)
+    for name, r in zip(("dq", "dk", "dv"), R.relu_bwd_bh(y.q, y.k, y.v, y.dout)):
+        _same(got[name][:, 1 - hit], r[:, 1 - hit], bar, name)
+        assert np.isfinite(got[name]).all() and np.abs(got[name][0, hit] - r[0, hit]).max() <= bar * np.abs(r[0, hit]).max(), name
+
+
+@pytest.mark.parametrize("blend", [False, True], ids=["plain", "blend"])
+@pytest.mark.parametrize("second", [False, True], ids=["first head", "second head"])
+def test_infinite_gradient_in_a_workgroup_of_two_heads(second, blend):
+    """bf16 tensors: an infinity in dout is met by the query side's rows and, in dS, by the key side's image.  dL/dr, a sum over all heads, is not
+    finite; the other head does not see it, nor do dq of the other tokens and dv of the other channels."""
+    import torch
+    from paper_2510_08318_amd import torch_glue as G
+    x = synth.generate("C5", n=600, H=43, B=3, d=128)
+    first = _shared_workgroup(129, 3)
+    b, h = divmod(first + second, 43)
+    t = 599 if not second else 3                             # a token of the workgroup's unit of that head
+    s = synth._pack((np.random.default_rng(1).standard_normal(x.q.shape) * 0.1).astype(np.float32), x.dtype)
+    clean = _heads(x, first)
+    _set(x, "dout", (b, h, t, 5), INF)
+    lay = _layer(x, False)
+    dr = torch.zeros(1, device="cuda")
+    if blend:
+        lay.set_blend(G.to_device(s), torch.tensor([0.37], device="cuda"), dr)
+    q, k, v, do = [G.to_device(a) for a in (x.q, x.k, x.v, x.dout)]
+    lay.forward(q, k, v)
+    got = {name: _pair(G.to_host_f64(a), first) for name, a in zip(("dq", "dk", "dv"), lay.backward(q, k, v, do))}
+    lay.close()
+    if blend:
+        assert not np.isfinite(dr.item())
+        ref = O.blend_bwd_bh(clean.q, clean.k, clean.v, clean.wq, clean.wk, _pair(s, first), 0.37, clean.dout)[:3]
+    else:
+        ref = O.bwd_bh(clean.q, clean.k, clean.v, clean.wq, clean.wk, clean.dout)[:3]
+    hit, other = int(second), int(not second)
+    for name, r in zip(("dq", "dk", "dv"), ref):
+        _same(got[name][:, other], r[:, other], BARS["bf16"], name)
+    dq, _, dv = ref
+    keep = np.arange(600) != t
+    _same(got["dq"][0, hit][keep], dq[0, hit][keep], BARS["bf16"], "dq")
+    assert not np.isfinite(got["dk"][0, hit]).any() and np.isposinf(got["dv"][0, hit, :, 5]).all()
+    channels = np.arange(128) != 5
+    _same(got["dv"][0, hit][:, channels], dv[0, hit][:, channels], BARS["bf16"], "dv")
