@@ -808,14 +808,13 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
   const int nblk = (n + 31) / 32;
   const int stride = gridDim.x * NW;
   uint4 xk[C::UK], vr[D / 16];
-  auto load_rows = [&](uint4 (&x)[C::UK], int b) {
+  auto load_k = [&](int b) {
     const int t = b * 32 + (lane % 32);
     const int tc = t < n ? t : (n - 1);
     const uint4* row = reinterpret_cast<const uint4*>(kb + (size_t)tc * rw.sn);
 #pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
+    for (int ks = 0; ks < C::UK; ++ks) xk[ks] = row[2 * ks + g];
   };
-  auto load_k = [&](int b) { load_rows(xk, b); };
   auto load_v = [&](int b) {
     const int t = b * 32 + (lane % 32);
     const int tc = t < n ? t : (n - 1);

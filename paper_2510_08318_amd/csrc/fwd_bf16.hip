@@ -84,9 +84,15 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
 template <int D, bool BLEND, bool SUM, int NW>
 constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
 
+// Wavefronts to a SIMD that the register limit leaves room for: those of the workgroup, two or three.  Four at width 64: the
+// limit keeps the loop's schedule from spreading into the prologue's registers (without it the CogVideoX-2B shape
+// loses 2 us).  Not with blend, whose pieces of s need the registers (they spill), nor where 12 wavefronts sum the state (so does their
+// prologue).
+template <int D, bool BLEND, bool SUM, int NW>
+constexpr int kApplyOccupancy = D == 64 && !BLEND && !(SUM && NW == 12) ? 4 : NW / 4;
+
 // The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
-// us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).  The register limit at width 64 keeps the loop's schedule from spreading
-// into the prologue's registers: without it the CogVideoX-2B shape loses 2 us.
+// us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).
 // BLEND: mixed attention (Sec. 4.1, Eq. 6): out = r' s + (1 - r') o with the softmax-branch output
 // s read in the same pieces as out is stored, and r' = clip(*rptr, 0, 1).
 // KIND = kPhiRelu: phi(q) = max(q, 0) straight from the loaded rows (no projection, no W~), features
@@ -94,7 +100,7 @@ constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
 // SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
 // sum_in_apply); the first workgroup of a head writes it to `state`.
 template <int D, bool BLEND, int KIND, bool SUM, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 12 ? (D == 64 && !BLEND && !SUM ? 4 : 3) : D == 64 && !BLEND ? 4 : 2) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+__global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, SUM, NW>)) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ partials, float* __restrict__ state,
                                                          uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
