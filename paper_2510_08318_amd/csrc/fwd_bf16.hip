@@ -80,7 +80,9 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
   sum_slots_of<N, NTHREADS, 2>(src, cnt, sum, dst, tid);
 }
 
-// Which query passes may have their units dealt evenly (run_apply); the others have no loop over a workgroup's heads.
+// Which query passes may have their units dealt evenly (run_apply).  Those that have take the instance with a loop over a workgroup's heads (EVEN);
+// carried by the others it cost them 0.2 to 0.6 us: 12 heads x 4133 x 64 18.4 us a call, 18.1 without, 12 x 8190 x 128 37.3 / 36.8, 30 x 1000 x 64 15.5 /
+// 15.0.
 template <int D, bool BLEND, bool SUM, int NW>
 constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
 
@@ -99,7 +101,7 @@ constexpr int kApplyOccupancy = D == 64 && !BLEND && !(SUM && NW == 12) ? 4 : NW
 // in channel order, kReluEps in the denominator.
 // SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
 // sum_in_apply); the first workgroup of a head writes it to `state`.
-template <int D, bool BLEND, int KIND, bool SUM, int NW>
+template <int D, bool BLEND, int KIND, bool SUM, int NW, bool EVEN>
 __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, SUM, NW>)) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ partials, float* __restrict__ state,
                                                          uint16_t* __restrict__ out,
@@ -119,7 +121,6 @@ __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, SUM, NW>)) void
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 32;
-  constexpr bool EVEN = apply_even<D, BLEND, SUM, NW>;
   for (Share sh = EVEN ? first_share(deal, blockIdx.x, blockIdx.y) : head_share(deal, blockIdx.x, blockIdx.y); sh.there;
        sh = EVEN ? next_share(deal, blockIdx.x, sh) : Share{}) {
     const int bh = sh.bh, h = bh % H;
@@ -623,15 +624,22 @@ namespace {
 // 54 x 3451 71.5 / 75.7 (without blend 24 x 7995 58.3 / 61.5).
 template <int D, bool BLEND>
 constexpr DealCost kApplyCost = D == 128 && BLEND ? DealCost{3} : DealCost{4, 2, 5, 240};
-template <int D, bool BLEND, int KIND, bool SUM, int NW>
-hipError_t run_apply_waves(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
+template <int D, bool BLEND, int KIND, bool SUM, int NW, bool EVEN>
+hipError_t run_apply_as(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                            const float* blend_r, const Plan& p, const Split& deal, hipStream_t s) {
   hipError_t e;
   constexpr size_t smem = apply_smem<D>(SUM);
-  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM, NW>>(smem)) != hipSuccess) return e;
-  apply_bf16_kernel<D, BLEND, KIND, SUM, NW><<<grid_of(deal), 64 * NW, smem, s>>>(
+  if ((e = set_smem_once<apply_bf16_kernel<D, BLEND, KIND, SUM, NW, EVEN>>(smem)) != hipSuccess) return e;
+  apply_bf16_kernel<D, BLEND, KIND, SUM, NW, EVEN><<<grid_of(deal), 64 * NW, smem, s>>>(
       (const uint16_t*)q, (const uint16_t*)wq, partials, state, (uint16_t*)out, (const uint16_t*)blend_in, blend_r, p.H, p.n, deal, p.split, p.rows);
   return hipGetLastError();
+}
+template <int D, bool BLEND, int KIND, bool SUM, int NW>
+hipError_t run_apply_waves(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
+                           const float* blend_r, const Plan& p, const Split& deal, hipStream_t s) {
+  if constexpr (apply_even<D, BLEND, SUM, NW>)
+    if (!deal.share) return run_apply_as<D, BLEND, KIND, SUM, NW, true>(q, wq, partials, state, out, blend_in, blend_r, p, deal, s);
+  return run_apply_as<D, BLEND, KIND, SUM, NW, false>(q, wq, partials, state, out, blend_in, blend_r, p, deal, s);
 }
 template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
