@@ -89,9 +89,10 @@ constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
 // Wavefronts to a SIMD that the register limit leaves room for: those of the workgroup, two or three.  Four at width 64: the
 // limit keeps the loop's schedule from spreading into the prologue's registers (without it the CogVideoX-2B shape
 // loses 2 us).  Not with blend, whose pieces of s need the registers (they spill), nor where 12 wavefronts sum the state (so does their
-// prologue).
-template <int D, bool BLEND, bool SUM, int NW>
-constexpr int kApplyOccupancy = D == 64 && !BLEND && !(SUM && NW == 12) ? 4 : NW / 4;
+// prologue).  Five (96 registers) for long calls of the Hedgehog map without the loop over heads: as scheduled for four, with 99, 24 heads x 20000 x 64
+// [B,n,H,d] takes 65.4 us a call, so 63.0; 30 x 17550 63.8 / 62.6; 12 x 8190 22.1 / 22.3; ReLU 55.8 / 56.3.
+template <int D, bool BLEND, int KIND, bool SUM, int NW, bool EVEN>
+constexpr int kApplyOccupancy = D == 128 || BLEND || (SUM && NW == 12) ? NW / 4 : KIND == kPhiHedgehog && !SUM && NW == 8 && !EVEN ? 5 : 4;
 
 // The prologue holds the state in registers (StateRegs): staged in LDS first, the pass took 2-3 us longer per launch (57.5 -> 54.5
 // us at 12 heads x 32760 x 128, 7.6 -> 7.2 at 4 x 1000 x 64).
@@ -102,7 +103,7 @@ constexpr int kApplyOccupancy = D == 64 && !BLEND && !(SUM && NW == 12) ? 4 : NW
 // SUM: the state is summed here, from the partials of at most kSumSlots<D> state-pass workgroups a head (the rule is at
 // sum_in_apply); the first workgroup of a head writes it to `state`.
 template <int D, bool BLEND, int KIND, bool SUM, int NW, bool EVEN>
-__global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, SUM, NW>)) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
+__global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, KIND, SUM, NW, EVEN>)) void apply_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ wq,
                                                          const float* __restrict__ partials, float* __restrict__ state,
                                                          uint16_t* __restrict__ out,
                                                          const uint16_t* __restrict__ blend, const float* __restrict__ rptr,
