@@ -760,6 +760,7 @@ constexpr int KAHEAD = 0;
 // projection on (256 in all, 3 spilled with CENTRE): read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute
 // units passes, and the kernel is bound by its rows: 117 us, now 105 (12 heads x 32760 x 128), 211 / 192 (40 x 20000), 40.3 / 37.9 (centred, 12 x
 // 8190), 25.4 / 23.2 (7 x 20000 x 64).
+// STREAM: dv is stored non-temporally, as dk always is (stream_gradients).
 template <int D, bool STREAM, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                     const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
@@ -904,7 +905,7 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
       // the next block's k rows (with the dW~ accumulator resident they do not fit beside the middle of the chain), before the dk
       // stores: a wait for them must not wait for the stores
       if constexpr (DW) load_k(b + stride);
-      store_token_rows<D, STREAM>(dkb, rw.sn, b * 32, n, lane, xa, its);
+      store_token_rows<D, true>(dkb, rw.sn, b * 32, n, lane, xa, its);
       if constexpr (DW) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {

@@ -1,4 +1,4 @@
-// bf16-I/O backward with non-temporal gradient stores (see bwd_bf16.hip).
+// bf16-I/O backward with dq and dv stored non-temporally (see bwd_bf16.hip).
 #include "bwd_bf16.h"
 
 namespace linattn {

@@ -210,12 +210,14 @@ struct BwdArgs {
   float* dr_part;
 };
 
-// Whether the bf16 backward stores its gradients non-temporally (the ReLU map: dq and dk): where the three take more than half of the
-// last-level cache (256 MB).  Left dirty there, large ones are written back under the kernels that follow and displace the rows these
-// read; small ones serve whoever reads them next.  Ordinary / non-temporal, us.  A training step and then one pass over each gradient: 12
-// heads x 4133 x 64 (6 MB a gradient) 65.6 / 69.9, 12 x 8190 x 128 (25 MB) 150 / 156, ReLU 147 / 154; 12 x 16000 (49 MB) 234 / 231, ReLU
-// 210 / 209; 12 x 32760 (100 MB) 428 / 423, ReLU 377 / 374; 40 x 20000 (205 MB) 812 / 809, ReLU 737 / 728.  The step alone, whose
-// forward is then the next to run: 51.0 / 49.9, 120.5 / 118.3, 184 / 175, 340 / 324, 603 / 587.
+// Whether the bf16 backward stores dq and dv non-temporally (the ReLU map: dq and dk, dv never): where the three gradients take more than half of
+// the last-level cache (256 MB).  Left dirty there, large ones are written back under the kernels that follow and displace the rows these
+// read; small ones serve whoever reads them next.  dk of the Hedgehog map is always non-temporal: written last together with dv, it makes room for
+// the next kernel's rows, which is worth what its reader loses.  Us, all non-temporal / dk alone / none: a training step and then one pass over each
+// gradient, 12 heads x 4133 x 64 (6 MB a gradient) 69.1 / 65.3 / 64.1, 12 x 8190 x 128 (25 MB) 160 / 155 / 153; the step alone, whose forward is then the
+// next to run, 50.1 / 50.0 / 50.7 and 124 / 122 / 124.  All / none: 12 x 16000 (49 MB) 231 / 234 and 175 / 184; 12 x 32760 (100 MB) 423 / 428 and 324 / 340;
+// 40 x 20000 (205 MB) 809 / 812 and 587 / 603.  ReLU, dq and dk / none: 12 x 4133 x 64 65.6 / 62.8 and 47.4 / 47.8; 12 x 8190 151 / 147 and 117 / 119; 12 x
+// 16000 209 / 210 and 158 / 165; 12 x 32760 374 / 377 and 279 / 284, with dv too 382 and 280 (relu_bwd_k 87 -> 94); 40 x 20000 728 / 737 and 509 / 519.
 inline bool stream_gradients(const Plan& p) { return (size_t)p.BH * p.n * p.d * 2 * 3 > ((size_t)128 << 20); }
 
 // A kernel instantiation as a value, for launch code shared by several.

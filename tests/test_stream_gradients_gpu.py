@@ -1,4 +1,4 @@
-"""The bf16 backward stores its gradients through the caches where the three fit half of the last-level cache (3 x 2 bytes x 128 channels x
+"""The bf16 backward stores dq and dv (ReLU: dq and dk) through the caches where the three gradients fit half of the last-level cache (3 x 2 bytes x 128 channels x
 174762 tokens are the most) and past them above; the fp32-arithmetic one its dL/du rows (2 sides x 4 bytes x 64 features x 262144
 tokens): one head of width 128 on both sides of the lines, the last block ragged.
 
