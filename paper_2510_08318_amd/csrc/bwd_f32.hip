@@ -180,7 +180,7 @@ constexpr size_t grad_smem() {
 }
 
 // dL/du rows: non-temporal where both sides' would push each other and the rows that follow out of the last-level cache (256 MB) before
-// dw_f32_kernel reads them.  Ordinary / non-temporal, us: 12 heads x 32760 x 128 (201 MB) dw 99.5 / 86, key side 149 / 147, query side 101 / 102; 5 x
+// dw_f32_kernel reads them.  Ordinary / non-temporal, us: 12 heads x 32760 x 128 (201 MB) dw 99.5 / 86, key side 149 / 147, query side 101 / 102 (both head by head); 5 x
 // 20000 x 128 (51 MB) dw 47 / 49, gradients 147 / 144.
 constexpr size_t kDuStreamBytes = 128u << 20;
 __device__ __forceinline__ void put_du(float4* p, float4 v, int stream) {
@@ -193,8 +193,8 @@ __device__ __forceinline__ void put_du(float4* p, float4 v, int stream) {
 // (BLEND, dr_part not null) the workgroup's part of dL/dr = sum dO . (s - o) in dr_part; om = 1 - r' of the mixed attention.  s is read for
 // that alone.
 // Key side: x = k, y = v, M = (dS, dz); dv = phi(k) dS as well, from the same image.  As a pass of its own it read k, formed phi and built an
-// image once more; two passes / this one, us: 12 heads x 32760 x 128 with bf16 tensors 97 + 80 / 161, 5 x 20000 x 128 fp32 61 + 37 / 84, 2 x
-// 1024 x 64 fp32 12.3 + 7.8 / 15.4.  du_ws (nullable): dL/du rows for dW~.
+// image once more; two passes / this one, us, as it was first: 12 heads x 32760 x 128 with bf16 tensors 97 + 80 / 161 (147 now), 5 x 20000 x 128 fp32 61 +
+// 37 / 84, 2 x 1024 x 64 fp32 12.3 + 7.8 / 15.4 (14.9).  du_ws (nullable): dL/du rows for dW~.
 template <int D, int KIND, typename T, bool QSIDE, bool BLEND, bool EVEN>
 __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ wx,
                                                        const float* __restrict__ state, T* __restrict__ dx, T* __restrict__ dv,

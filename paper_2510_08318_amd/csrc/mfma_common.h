@@ -517,8 +517,8 @@ __device__ __forceinline__ float half_wave_sum(float x) {
 // The stores are buffer stores bounded to the rows that exist: the hardware drops those past n.  No branch (behind one the compiler cannot count the
 // stores in flight, and a later wait for a load that was requested before them, the next block's rows, turns into a wait for the
 // stores as well), and one vector instruction for an address.  Choosing between the row and a sink by a select took five, 64 more a block: a pass
-// of 4 x 1000 x 64 8.5 us, now 8.0, of 12 x 4133 x 64 7.7, now 6.9; the fp32-arithmetic key side, which that kept from spilling, 164 -> 156
-// at 12 x 32760 x 128; nothing where the memory or the barriers of dW~ are what is waited for.
+// of 4 x 1000 x 64 took 8.5 us in place of 8.0, of 12 x 4133 x 64 7.7 in place of 6.9, the fp32-arithmetic key side (12 x 32760 x 128, bf16 tensors),
+// which that kept from spilling, 164 in place of 156, each with the kernel of that time; nothing where the memory or the barriers of dW~ are what is waited for.
 // All arguments but the lane are uniform.
 template <int PIECE>
 struct TokenRows {

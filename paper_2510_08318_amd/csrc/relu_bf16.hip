@@ -267,8 +267,8 @@ __device__ __forceinline__ void relu_grad(const uint4* img, int lane, Piece x, f
 
 // A lane's row pieces (bf16, channels 16ks + 8g .. of its token) -> 32 rows of base, a wavefront's tokens t0 ..: through `buf`
 // ([32][D] bf16 of LDS, the wavefront's own), so that an instruction stores 1 KB of whole rows.  Stored as the lanes hold them,
-// 32 bytes of a row at a time, the query side took 95 us and the key side 96 where they take 91 and 88 (12 heads x
-// 32760 x 128).  Rows past n hold the bits of row n - 1 and go there.
+// 32 bytes of a row at a time, the query side took 95 us and the key side 96 where they took 91 and 88 (12 heads x
+// 32760 x 128, ordinary stores).  Rows past n hold the bits of row n - 1 and go there.
 template <int D>
 struct RowStore {
   static constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks of a row, rows per store
@@ -301,7 +301,7 @@ struct RowStore {
 // leaves in the pieces in which q came.  They park phi(q) and gamma * dO / den as fp16 and form dq while wavefronts 4-7 ("acc") contract
 // the tile over its tokens into dS (dz: one more MFMA per k-step).  The kernel is bound by its instruction stream (its rows take 51 us
 // at the memory's rate): with four wavefronts that did all of this one after another, read q a second time for the mask and summed delta
-// across lanes it took 119 us at 12 heads x 32760 x 128, 91 now.
+// across lanes it took 119 us at 12 heads x 32760 x 128, 88 to 93 now.
 constexpr int NTQ = 512;
 template <int D, bool STREAM>
 __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
 // ---- key side of the backward ---------------------------------------------------------------------
 // grid (KP, BH), 8 wavefronts, each on its own 32-token blocks: dv = phi(k) dS with the tokens on the accumulator rows, and
 // g = v dS^T + dz with the tokens on the columns (relu_grad), dk = g where k > 0 in the pieces in which k came.  88 us at 12 heads x 32760 x
-// 128 (81 + 9 for the images in a kernel of their own, with k read twice); the rows take 69 us at the memory's rate.  The next block's
+// 128, dk non-temporal and dv not (81 + 9 for the images in a kernel of their own, with k read twice); the rows take 69 us at the memory's rate.  The next block's
 // rows requested a block ahead: 93 us.
 constexpr int NTK = 512;
 template <int D, bool STREAM>
