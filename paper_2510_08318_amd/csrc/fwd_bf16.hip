@@ -80,11 +80,11 @@ __device__ __forceinline__ void sum_slots(const float* __restrict__ partials, fl
   sum_slots_of<N, NTHREADS, 2>(src, cnt, sum, dst, tid);
 }
 
-// Which query passes may have their units dealt evenly (run_apply).  Those that have take the instance with a loop over a workgroup's heads (EVEN);
+// Which query passes may have their units dealt evenly (run_apply): not those that sum, with few units a head.  Those that have take the instance with a loop over a workgroup's heads (EVEN);
 // carried by the others it cost them 0.2 to 0.6 us: 12 heads x 4133 x 64 18.4 us a call, 18.1 without, 12 x 8190 x 128 37.3 / 36.8, 30 x 1000 x 64 15.5 /
 // 15.0.
-template <int D, bool BLEND, bool SUM, int NW>
-constexpr bool apply_even = !SUM && (NW == 8 || (D == 128 && BLEND));
+template <bool SUM>
+constexpr bool apply_even = !SUM;
 
 // Wavefronts to a SIMD that the register limit leaves room for: those of the workgroup, two or three.  Four at width 64: the
 // limit keeps the loop's schedule from spreading into the prologue's registers (without it the CogVideoX-2B shape
@@ -620,9 +620,10 @@ namespace {
 // 153 heads x 763 x 128 47.0 / 50.0 (3 rounds for 153 compute units, 2 for all), 40 x 20000 x 128 179.9 / 181.9, 30 x 17550 x 64 61.1 / 62.4; but 12 x 32760 x
 // 128 99.8 / 97.6, 160 x 4000 x 128 158.9 / 154.5, 40 x 75600 x 128 631 / 626.  The blended pass of width 128, whose rounds are the longest, gains
 // more: 138 x 1563 89.6 / 79.9, 154 x 1102 73.9 / 69.1.
-// 12 wavefronts with an even deal, two prologues around one round each, pay in that pass alone, and where a head's last unit is short: head by head
-// with 8 / evenly with 12 where it has 8 of 12 blocks, 155 x 1019 69.5 / 66.2; evenly with 8 / with 12 where it has 9 or more, 144 x 1051 65.9 / 68.8,
-// 54 x 3451 71.5 / 75.7 (without blend 24 x 7995 58.3 / 61.5).
+// 12 wavefronts with an even deal, two prologues around one round each, pay where a head's last unit is short and 8 would be dealt evenly too, in the
+// blended pass of width 128 also where they would not: evenly with 8 / with 12, last unit of up to 8 of 12 blocks, 6 x 32283 56.4 / 54.2, 30 x 6203
+// 60.4 / 57.2, 46 x 3931 61.5 / 57.8; of 9 or more, 24 x 7995 58.3 / 61.5, with blend 144 x 1051 65.9 / 68.8; head by head with 8 / evenly with 12, with
+// blend 155 x 1019 69.5 / 66.2, but without 136 x 827 47.1 / 48.8.
 template <int D, bool BLEND>
 constexpr DealCost kApplyCost = D == 128 && BLEND ? DealCost{3} : DealCost{4, 2, 5, 240};
 template <int D, bool BLEND, int KIND, bool SUM, int NW, bool EVEN>
@@ -638,7 +639,7 @@ hipError_t run_apply_as(const void* q, const void* wq, const float* partials, fl
 template <int D, bool BLEND, int KIND, bool SUM, int NW>
 hipError_t run_apply_waves(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                            const float* blend_r, const Plan& p, const Split& deal, hipStream_t s) {
-  if constexpr (apply_even<D, BLEND, SUM, NW>)
+  if constexpr (apply_even<SUM>)
     if (!deal.share) return run_apply_as<D, BLEND, KIND, SUM, NW, true>(q, wq, partials, state, out, blend_in, blend_r, p, deal, s);
   return run_apply_as<D, BLEND, KIND, SUM, NW, false>(q, wq, partials, state, out, blend_in, blend_r, p, deal, s);
 }
@@ -646,9 +647,10 @@ template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   const int blocks = (p.n + 31) / 32;
-  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>, apply_even<D, BLEND, SUM, 8>);
+  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>, apply_even<SUM>);
   if constexpr (!SUM || kSumSlots<D> * kTile > 8 * 32) {   // (one unit of 8 a head otherwise)
-    const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, apply_even<D, BLEND, SUM, 12> && (blocks + 11) % 12 < 8);
+    const bool even12 = apply_even<SUM> && ((D == 128 && BLEND) || !d8.share) && (blocks + 11) % 12 < 8;
+    const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, even12);
     const int r8 = split_rounds(d8);
     if (r8 <= 3 && split_rounds(d12) < r8)
       return run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s);

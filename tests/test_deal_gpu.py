@@ -112,3 +112,9 @@ def _step(mode, d, form, layout, shape):
         if name in got:
             bar = (2e-5 if name in ("dwq", "dwk") else 1e-5) if mode == "f32" or (f32_math and name in ("dwq", "dwk")) else 1e-2
             assert O.err_metric(got[name], r)[0] <= bar, name
+
+
+# 45 heads of 3870 tokens without blend: 16 units of 8 blocks or 11 of 12 a head, both dealt evenly, three rounds or two; a head's last unit of 12 has one block
+@pytest.mark.parametrize("d,form", [(64, "frozen map"), (128, "frozen map"), (128, "relu")])
+def test_twelve_wavefronts_dealt_evenly(d, form):
+    _step("bf16", d, form, "bhnd", (45, 1, 3870))
