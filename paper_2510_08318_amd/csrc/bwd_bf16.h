@@ -12,17 +12,16 @@
 // (the partials are reduced in state_reduce.hip)
 //
 // Precision: every 16-bit MFMA operand except the stored bf16 q, k (projection) is fp16.
-// Operands that belong to one token only (dO_i for g_i, du_i for dx_i) are scaled by a per-token
-// power of two taken from their largest magnitude, so any gradient scale is safe.  Operands of
-// the sums over tokens (dO_i/den_i, delta_i/den_i, du for dW~) are scaled by one power of two per
-// workgroup that follows the running maximum over its tiles (largest magnitude so far in [16, 32));
+// Operands that belong to one token or block only (dO_i for g_i, du_i for dx_i) are scaled by a
+// power of two taken from their largest magnitude, so any gradient scale is safe; bf16 values scaled so are exact in fp16.  In the sums over
+// tokens the weight 1/den_i goes into phi_i, with one power of two per workgroup that follows the running maximum of |dO_i|/den_i over its
+// tiles (largest magnitude so far in [16, 32)), and du for dW~ is scaled likewise;
 // when a tile raises the maximum the fp32 accumulators are rescaled by the exact ratio, so neither a
-// late large tile nor leading all-zero tiles can overflow or flush fp16; within a tile values down
-// to 2^-18 of the running maximum keep full precision.  Accumulation is fp32 everywhere; partial
+// late large tile nor leading all-zero tiles can overflow or flush fp16.  delta enters dz in fp32.  Accumulation is fp32 everywhere; partial
 // sums are combined in a fixed order.
 #pragma once
 #include "kernels.h"
-#include "mfma_common.h"
+#include "mfma16.h"
 
 namespace linattn {
 namespace {
@@ -88,7 +87,7 @@ __device__ __forceinline__ float build_query_state(const float* __restrict__ sta
       for (int i = 0; i < 4; ++i) S.v[e][i] = 0.f;
   }
   const float scale = S.scale(red, tid);
-  S.write_grad_image(sGA, scale);
+  write_grad_image16<D, NTHREADS>(S, sGA, scale);
   return scale;
 }
 
@@ -233,7 +232,7 @@ __device__ __forceinline__ void du_to_dx(const float (&du)[Cfg<D>::LOC], const u
 // the blocks to one common power-of-two scale that follows the running maximum of the workgroup
 // (gamma_step; the accumulators are rescaled by the exact ratio when a tile raises it).  Partials per
 // workgroup are reduced in a fixed order afterwards.
-template <int D, int NW>
+template <int D, int NW, int BLK = 32>
 struct DwTile {
   static constexpr int HALF = D / 2;
   static constexpr int LOC = D / 4;
@@ -241,7 +240,7 @@ struct DwTile {
   static constexpr int RSU = HALF * 2;                     // bytes per row of the du tile
   static constexpr int NB = HALF / 32;                     // 32-column blocks of du
   static constexpr int RB = (D / 32) * NB >= NW ? (D / 32) * NB / NW : 1;   // row blocks per wavefront
-  static constexpr int BPT = kTile / 32;                   // du blocks per parked tile
+  static constexpr int BPT = kTile / BLK;                  // du blocks (each with a scale of its own) per parked tile
   static constexpr int KSN = kTile / 16;
   static constexpr int KBATCH = NW > 4 ? KSN / 2 : KSN / 4;     // k-steps whose operands are in flight together
   static constexpr int DU_BYTES = kTile * RSU;
@@ -283,7 +282,7 @@ struct DwTile {
     }
     if (lane == 0) sIts[slot] = blk_its;
   }
-  // lane: pass lane + opaque_zero() from inside the tile loop: the read offsets are then worked out per tile (a few
+  // lane: pass opaque_lane() from inside the tile loop: the read offsets are then worked out per tile (a few
   // integer operations) instead of being held in registers, or spilled, across the whole loop
   __device__ __forceinline__ void contract(const char* sX, const char* sU, const float* sIts, int lane) {
     float its[BPT];
@@ -302,12 +301,12 @@ struct DwTile {
         for (int r = 0; r < 16; ++r) acc[j][r] *= ratio;
     }
     if (!active) return;
-    int offA[RB][2], offB[2];
+    uint32_t offA[RB][2], offB[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      offB[j] = tr_offset_g4<HALF>(32 * fb, lane, j);
+      offB[j] = tr_base(sU, tr_offset_g4<HALF>(32 * fb, lane, j));
 #pragma unroll
-      for (int i = 0; i < RB; ++i) offA[i][j] = tr_offset_g4<D>(32 * (row0 + i), lane, j);
+      for (int i = 0; i < RB; ++i) offA[i][j] = tr_base(sX, tr_offset_g4<D>(32 * (row0 + i), lane, j));
     }
     // the operands of KBATCH k-steps are requested before their first MFMA: one LDS latency per batch instead of one per k-step
 #pragma unroll
@@ -315,13 +314,13 @@ struct DwTile {
       f16x8 a[KBATCH][RB], b[KBATCH];
 #pragma unroll
       for (int ks = 0; ks < KBATCH; ++ks) {
-        b[ks] = read_tr(sU + (k0 + ks) * 16 * RSU, offB[0], offB[1]);
+        b[ks] = read_tr(offB[0] + (k0 + ks) * 16 * RSU, offB[1] + (k0 + ks) * 16 * RSU);
 #pragma unroll
-        for (int i = 0; i < RB; ++i) a[ks][i] = read_tr(sX + (k0 + ks) * 16 * RSX, offA[i][0], offA[i][1]);
+        for (int i = 0; i < RB; ++i) a[ks][i] = read_tr(offA[i][0] + (k0 + ks) * 16 * RSX, offA[i][1] + (k0 + ks) * 16 * RSX);
       }
 #pragma unroll
       for (int ks = 0; ks < KBATCH; ++ks) {
-        const _Float16 f = (_Float16)(gamma * its[(k0 + ks) / 2]);   // a power of two, or 0 for an all-zero block
+        const _Float16 f = (_Float16)(gamma * its[(k0 + ks) * 16 / BLK]);   // a power of two, or 0 for an all-zero block
         const f16x8 bo = b[ks] * f;
 #pragma unroll
         for (int i = 0; i < RB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks][i], bo, acc[i], 0, 0, 0);
@@ -341,27 +340,83 @@ struct DwTile {
   }
 };
 
+// ---- sums over the tokens of a tile ----------------------------------------------------------
+// A 128-token tile of dS and dz: s[i][j] += P_i^T Y_j with P = phi f (per token f = (1 - r') / (den stok), times the running scale) and Y = stok dO as fp16
+// tiles [kTile][D] in LDS, and z += P_0 . w with w = -stok delta in fp32, feature lane%32 of the first block over the tokens that the lane
+// holds (eight of a k-step; the lane 32 further has the others): as MFMA blocks the z sums took a fifth of the MFMAs and 16 registers.
+// The operands of k-step ks+1 are requested before the MFMAs of k-step ks.
+// SUMS (centred): also csum[j] += sum f Y, the lane's column of block j, and wsum += sum f w, over the same tokens.
+// w, f: the lane's first token of k-step 0.
+template <int D, bool SUMS>
+__device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x16 (&s)[D / 64][D / 64], float& z, const float* w, const float* f,
+                                                float (&csum)[D / 64], float& wsum) {
+  constexpr int RS = D * 2, WMN = D / 64, KSN = kTile / 16;
+  f16x8 a[KSN][WMN], b[KSN][WMN];
+  auto request = [&](int kn) {
+#pragma unroll
+    for (int i = 0; i < WMN; ++i) a[kn][i] = read_tr(rd.a[i][0] + kn * 16 * RS, rd.a[i][1] + kn * 16 * RS);
+#pragma unroll
+    for (int j = 0; j < WMN; ++j) b[kn][j] = read_tr(rd.b[j][0] + kn * 16 * RS, rd.b[j][1] + kn * 16 * RS);
+  };
+  request(0);
+#pragma unroll
+  for (int ks = 0; ks < KSN; ++ks) {
+    float4 wv[2], fv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      wv[i] = *reinterpret_cast<const float4*>(w + 16 * ks + 4 * i);
+      if constexpr (SUMS) fv[i] = *reinterpret_cast<const float4*>(f + 16 * ks + 4 * i);
+    }
+    if (ks + 1 < KSN) request(ks + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < WMN; ++i)
+#pragma unroll
+      for (int j = 0; j < WMN; ++j) s[i][j] = mfma16<false>(a[ks][i], b[ks][j], s[i][j]);
+    const float wt[8] = {wv[0].x, wv[0].y, wv[0].z, wv[0].w, wv[1].x, wv[1].y, wv[1].z, wv[1].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z = fmaf((float)a[ks][0][e], wt[e], z);
+    if constexpr (SUMS) {
+      const float ft[8] = {fv[0].x, fv[0].y, fv[0].z, fv[0].w, fv[1].x, fv[1].y, fv[1].z, fv[1].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+#pragma unroll
+        for (int j = 0; j < WMN; ++j) csum[j] = fmaf((float)b[ks][j][e], ft[e], csum[j]);
+        wsum = fmaf(wt[e], ft[e], wsum);
+      }
+#pragma unroll
+      for (int j = 0; j < WMN; ++j) asm volatile("" : "+v"(csum[j]));
+      asm volatile("" : "+v"(wsum));
+    }
+    // (the sums are taken here, and not after the branches that follow the tile, with every operand kept until there)
+    asm volatile("" : "+v"(z));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // ---- query side --------------------------------------------------------------------------
-// LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use (one more for g).
-constexpr int QAHEAD = 3;
-constexpr int NTQ = 512;     // 8 wavefronts, one workgroup per compute unit
+// LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use.
+constexpr int QAHEAD = 4;
+constexpr int NTQ = 768;     // 12 wavefronts, one workgroup per compute unit
 // BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
 // asked for, and the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
 // wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
-// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it is hidden
-// (bwd_q 114 either way; centred and with dW~, where it spills 13 registers, 41 -> 47 at 12 x 8190 for a pass of 10).  An instance of its
-// own: as a condition at run time its registers were spilled in blended calls without dL/dr too.
+// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it costs 13.  An instance of its
+// own: as a condition at run time its registers were spilled in blended calls without dL/dr too (centred, width 128, with dW~: 10, no other instance any).
 // DW: dW~_q is accumulated here as well (DwTile).
 //
-// Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
+// Wavefronts 0-7 ("tok") each own 16 tokens of a 128-token tile: phi, G = dO S^T, delta, du, dq.  o = phi S is not needed: with
 // A+- = sum G phi and Z+- = sum z phi over the two halves of the features, den = Z+ + Z-, delta = (A+ + A-) / den and the two sums
 // of the softmax Jacobian are combinations of the same four, so dots of what the lane holds in fp32 stand in for 40 of the
-// MFMAs and for a second image of S.  Wavefronts 4-7 ("acc") contract the tile's phi, dO / den and delta / den into dS, dz
-// and its x, du into dW~ meanwhile: the accumulators (112 registers) are theirs, so the tok wavefronts do with 256 registers and a
-// SIMD hosts one wavefront of each kind, whose MFMA and vector work overlap.  The tiles are single (64 KB of images leave room for
-// one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO / den are parked between two barriers and dS contracts them
+// MFMAs and for a second image of S.  Wavefronts 8-11 ("acc") contract the tile's phi, dO and delta into dS, dz
+// and its x, du into dW~ meanwhile.  The tiles are single (64 KB of images leave room for
+// one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO are parked between two barriers and dS contracts them
 // while du and dx are formed; (DW) x takes phi's place and du its tile between two more, and dW~ contracts those beside the next
 // tile's first half.
+// What bounds it is the issue of vector and matrix instructions, which overlap little: a SIMD has two tok wavefronts (730 vector instructions and 64
+// MFMAs a tile each) and one acc (300 and 48), 11 of the tile's 14 thousand cycles.  Four tok wavefronts of 32 tokens, one to a SIMD, left a third of the
+// issue slots empty and had 1700 instructions a tile: 111 us, now 94 (12 heads x 32760 x 128 with dW~), 41 / 36 (centred, 12 x 8190), 114 / 108 with
+// dL/dr.  For a 16-token form to gain, nothing may be spilled: nine spilled addresses of the acc wavefronts, a scratch access to a k-step, took back all of it.
 template <int D, bool STREAM, bool BLEND, bool DR, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
                                                     const uint16_t* __restrict__ wq, const float* __restrict__ state,
@@ -371,43 +426,45 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
                                                     float* __restrict__ dr_part, float* __restrict__ cs_part,
                                                     int H, int n, int P, Rows rw) {
   using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  using G = GradLayout<D>;
+  using K = Tok16<D>;
   constexpr int RS = D * 2;
   constexpr int WMN = D / 64;
-  constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
+  constexpr int NTOK = kTile / 16;                         // token wavefronts
   constexpr float mean = CENTRE ? 2.0f / D : 0.f;          // what is taken out of phi before it is rounded: its mean over the features
-  using DWT = DwTile<D, 4>;
+  using DWT = DwTile<D, 4, 16>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
-  uint4* sGA = sWA + C::W_IMG;
-  uint4* sWB = sGA + G::IMG;
-  char* sPhi = reinterpret_cast<char*>(sWB + WB_IMG);      // [kTile][D] fp16: phi(q) (CENTRE: phi(q) - 2/D), then (DW) the q rows
-  char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: gamma * dO / den
-  uint16_t* sW16 = reinterpret_cast<uint16_t*>(sDO + kTile * RS);   // [kTile] fp16: -gamma * delta / den
-  float* sZ = reinterpret_cast<float*>(sW16 + kTile);      // [D] z, unscaled
-  float* sRed = sZ + D;                                    // [8]: 0..3 the tile's operand maxima, 4..7 the du blocks' inverse scales
-  char* sDU = reinterpret_cast<char*>(sRed + 8);           // DW: the tile's du, [kTile][D/2] fp16
+  uint4* sGA = sWA + K::W_IMG;
+  uint4* sWB = sGA + K::G_IMG;
+  char* sPhi = reinterpret_cast<char*>(sWB + K::T_IMG);    // [kTile][D] fp16: f phi(q) (CENTRE: f (phi(q) - 2/D)), then (DW) the q rows
+  char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: stok dO
+  float* sW = reinterpret_cast<float*>(sDO + kTile * RS);  // [kTile] -stok delta
+  float* sF = sW + kTile;                                  // [kTile] f (CENTRE)
+  float* sVb = sF + kTile;                                 // [D] vbar (DR)
+  float* sZ = sVb + D;                                     // [D] z, unscaled
+  float* sRed = sZ + D;                                    // [16]: 0..7 the tile's operand maxima, 8..15 the du blocks' inverse scales
+  char* sDU = reinterpret_cast<char*>(sRed + 16);          // DW: the tile's du, [kTile][D/2] fp16
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int role = w / 4, pw = w % 4;
-  const int g = lane / 32;
   const int bh = blockIdx.y, p = blockIdx.x, h = bh % H;
   const float om = BLEND ? 1.f - fminf(fmaxf(*rptr, 0.f), 1.f) : 1.f;      // 1 - r'
   const float* sb = state + (size_t)bh * (D + 1) * D;
   const int ntile = (n + kTile - 1) / kTile;
   float dr_acc = 0.f;
 
-  build_w_image<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
-  build_w_image_t<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
+  build_w_image16<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
+  build_w_image_t16<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
   const float scale = build_query_state<D, NTQ>(sb, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
+  if (DR && tid < D) sVb[tid] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + tid];
   __syncthreads();
 
   // running power-of-two scale of the sums over tokens, the same in every wavefront; returns the factor for the accumulators
   float gamma = kGammaUnset;
   auto next_gamma = [&]() -> float {
-    const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
+    float m = sRed[0];
+#pragma unroll
+    for (int i = 1; i < NTOK; ++i) m = fmaxf(m, sRed[i]);
     float gnext = gamma;
     const float ratio = gamma_step(gnext, gamma_for(m));
     // the same in every lane: kept in scalar registers
@@ -415,209 +472,206 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
   };
 
-  if (role == 0) {
+  if (w < NTOK) {
+    const int ql = lane / 16;
     const uint16_t* qb = q + head_base(rw, bh, H);
     const uint16_t* dob = dout + head_base(rw, bh, H);
     uint16_t* dqb = dq + head_base(rw, bh, H);
-    const int prow = 32 * pw + (lane % 32);
-    float z_mean = 0.f;                                    // mean * the sum of z over the lane's features
-    if constexpr (CENTRE) {
-      for (int j = 0; j < C::LOC; ++j) z_mean += sZ[g * C::LOC + j] + sZ[C::HALF + g * C::LOC + j];
-      z_mean *= mean;
-    }
-    uint4 xq[C::UK], xr[C::UK], dor[D / 16];
-    auto load_rows = [&](int tile) {
-      const int t = tile * kTile + prow;
-      const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
-      const uint4* row = reinterpret_cast<const uint4*>(qb + at);
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) xq[ks] = row[2 * ks + g];
-    };
-    auto load_do = [&](int tile) {
-      const int t = tile * kTile + prow;
-      const uint4* drow = reinterpret_cast<const uint4*>(dob + (size_t)(t < n ? t : n - 1) * rw.sn);
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) dor[i] = drow[2 * i + g];
-    };
-    load_rows(p < ntile ? p : 0);
+    const int prow = 16 * w + lane % 16;
+    uint4 xq[K::KS], xr[K::KS], dor[K::KS];
+    const float zero = opaque_zero_scalar();
+    const TileRows<D> qrows(qb, rw.sn, n, prow, ql), drows(dob, rw.sn, n, prow, ql);
+    qrows.load(xq, p);
     // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
     // for the first tile too, would be a wait for the previous tile's stores
 #pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) asm volatile("" : "+v"(xq[ks].x), "+v"(xq[ks].y), "+v"(xq[ks].z), "+v"(xq[ks].w));
+    for (int ks = 0; ks < K::KS; ++ks) asm volatile("" : "+v"(xq[ks].x), "+v"(xq[ks].y), "+v"(xq[ks].z), "+v"(xq[ks].w));
     for (int tile = p; tile < ntile; tile += P) {
       const int t = tile * kTile + prow;
       const bool valid = t < n;
-      load_do(tile);
-      f32x16 u[C::UM];
-      project<D, QAHEAD>(xq, sWA, lane, u);
+      drows.load(dor, tile);
+      f32x4 u[K::UB];
+#pragma unroll
+      for (int mb = 0; mb < K::UB; ++mb) u[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const uint4* wa = sWA + lane + opaque_zero();
+      pipelined_operands<K::KS * K::UB, QAHEAD>([&](int i) { return wa[i * 64]; },
+                                                [&](int i, uint4 a) { u[i % K::UB] = mfma_bf16_16(a, xq[i / K::UB], u[i % K::UB]); });
       if constexpr (DW) {
 #pragma unroll
-        for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xq[ks];   // rows past n repeat row n - 1: their du is zero
+        for (int ks = 0; ks < K::KS; ++ks) xr[ks] = xq[ks];
       }
-      float pp[C::LOC], pm[C::LOC];
-      {
-        uint32_t unused[C::NPK];
-        softmax_full<D>(u, pp, pm, unused);
-      }
-      if constexpr (CENTRE) {
-        // (as values of their own: folded with the mean taken out below, the unnormalised exponentials would be kept beside them)
+      // phi up to its normalisers ip, im, which go into the factors of what is linear in phi
+      float ep[K::FL], em[K::FL];
+      float mx = u[0][0], mn = -u[0][0];
 #pragma unroll
-        for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
+      for (int j = 0; j < K::FL; ++j) { mx = fmaxf(mx, u[j / 4][j % 4]); mn = fmaxf(mn, -u[j / 4][j % 4]); }
+      quad2<MaxOp>(mx, mn);
+      float ip = 0.f, im = 0.f;
+#pragma unroll
+      for (int j = 0; j < K::FL; ++j) {
+        ep[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], kLog2e, -mx * kLog2e));
+        em[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], -kLog2e, -mn * kLog2e));
+        ip += ep[j]; im += em[j];
       }
-      // the token's largest |dO|: magnitudes of bf16 compare as integers
-      float dmax;
+      quad2<SumOp>(ip, im);
+      ip = __builtin_amdgcn_rcpf(ip); im = __builtin_amdgcn_rcpf(im);
+      // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that
+      float dmax, stok;
+      uint4 bq[K::KS];
       {
+        // (magnitudes of bf16 compare as integers)
         typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
         u16x2 m2 = {0, 0};
         auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) { take(dor[i].x); take(dor[i].y); take(dor[i].z); take(dor[i].w); }
+        for (int ks = 0; ks < K::KS; ++ks) { take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w); }
         const uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
-        dmax = __builtin_bit_cast(float, m << 16);
+        dmax = quad<MagOp>(__builtin_bit_cast(float, m << 16));
+        stok = pow2_normaliser(fminf(dmax, kTokenMax));
+#pragma unroll
+        for (int ks = 0; ks < K::KS; ++ks) {
+          float f[8];
+          unpack_bf16x8(dor[ks], f);
+          bq[ks] = make_uint4(mul_pack_f16x2(f[0], f[1], stok, zero), mul_pack_f16x2(f[2], f[3], stok, zero),
+                              mul_pack_f16x2(f[4], f[5], stok, zero), mul_pack_f16x2(f[6], f[7], stok, zero));
+        }
       }
-      float lo, hi;
-      pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
-      const float stok = pow2_normaliser(fminf(dmax, kTokenMax));
+      const float istok = __builtin_amdgcn_rcpf(stok);     // exact
 
       // G = dO S^T (times scale * stok), rows laid out like phi
-      f32x16 ga[G::GM];
+      f32x4 ga[K::GB];
 #pragma unroll
-      for (int mb = 0; mb < G::GM; ++mb)
+      for (int mb = 0; mb < K::GB; ++mb) ga[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int gl = grad16_lane<D>(opaque_lane(lane));
+      pipelined_operands<K::KS * K::GB, QAHEAD>([&](int i) { return sGA[i * 64 + (gl ^ (4 * (i / K::GB)))]; },
+                                                [&](int i, uint4 a) { ga[i % K::GB] = mfma_f16_16(a, bq[i / K::GB], ga[i % K::GB]); });
+      // (dO stays packed until it is parked)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
-      const uint4* sga = sGA + lane + opaque_zero();
-      pipelined_operands<G::KS * G::GM, QAHEAD + 1>(
-          [&](int i) { return sga[i * 64]; },
-          [&](int i, uint4 a) {
-            const int ks = i / G::GM, mb = i % G::GM;
-            float f[8];
-            unpack_bf16x8(dor[ks], f);
-            uint4 bq;
-            bq.x = pack_f16x2(f[0] * stok, f[1] * stok); bq.y = pack_f16x2(f[2] * stok, f[3] * stok);
-            bq.z = pack_f16x2(f[4] * stok, f[5] * stok); bq.w = pack_f16x2(f[6] * stok, f[7] * stok);
-            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
-          });
-      // dO stays packed until it is parked: seen as the same values, its unpacked form would be kept (and spilled) from here to there
+      for (int ks = 0; ks < K::KS; ++ks) asm volatile("" : "+v"(bq[ks].x), "+v"(bq[ks].y), "+v"(bq[ks].z), "+v"(bq[ks].w));
+      // A+-, Z+-; feature ql*FL + j of each half
+      const int z_at = ql * K::FL / 4 + opaque_zero();
+      auto z4 = [&](int i) { return reinterpret_cast<const float4*>(sZ)[z_at + i]; };
+      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f;
 #pragma unroll
-      for (int i = 0; i < D / 16; ++i) asm volatile("" : "+v"(dor[i].x), "+v"(dor[i].y), "+v"(dor[i].z), "+v"(dor[i].w));
-      // A+-, Z+-; feature g*LOC + j of each half
-      const int z_at = g * C::LOC / 4 + opaque_zero();
-      auto z4 = [&](int q) { return reinterpret_cast<const float4*>(sZ)[z_at + q]; };
-      // Zr: the normaliser of phi as the sum dS takes it, rounded to fp16 (CENTRE: rounded after its mean is taken out).  dS adds
-      // phi / den: with the same rounded phi above and below, what the roundings of a token's features have in common drops out
-      // (with den from the fp32 phi dW~_k was 1 % further off, 2 % with CENTRE).  dq has fp32 phi on both sides.
-      float ap = 0.f, am = 0.f, Zp = 0.f, Zm = 0.f, Zr = z_mean;
-#pragma unroll
-      for (int q = 0; q < C::LOC / 4; ++q) {
-        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+      for (int i4 = 0; i4 < K::FL / 4; ++i4) {
+        const float4 vp = z4(i4), vm = z4(C::HALF / 4 + i4);
         const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int j = 4 * q + i;
-          ap = fmaf(ga[j / 16][j % 16], pp[j], ap); am = fmaf(ga[G::GM / 2 + j / 16][j % 16], pm[j], am);
-          Zp = fmaf(zp[i], pp[j], Zp); Zm = fmaf(zm[i], pm[j], Zm);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {
-          const int j = 4 * q + i;
-          const f16x2 rp = __builtin_bit_cast(f16x2, pack_f16x2(pp[j] - mean, pp[j + 1] - mean));
-          const f16x2 rm = __builtin_bit_cast(f16x2, pack_f16x2(pm[j] - mean, pm[j + 1] - mean));
-          Zr = fmaf((float)rp[0], zp[i], Zr); Zr = fmaf((float)rp[1], zp[i + 1], Zr);
-          Zr = fmaf((float)rm[0], zm[i], Zr); Zr = fmaf((float)rm[1], zm[i + 1], Zr);
+          const int j = 4 * i4 + i;
+          ap = fmaf(ga[i4][i], ep[j], ap); am = fmaf(ga[K::GB / 2 + i4][i], em[j], am);
+          Zp = fmaf(zp[i], ep[j], Zp); Zm = fmaf(zm[i], em[j], Zm);
         }
       }
-      // (phi is rounded again when it is parked: seen as the same values, the 32 packed registers would be kept, and spilled)
-#pragma unroll
-      for (int j = 0; j < C::LOC; ++j) asm volatile("" : "+v"(pp[j]), "+v"(pm[j]));
-      pair32(Zp, lo, hi); Zp = lo + hi;
-      pair32(Zm, lo, hi); Zm = lo + hi;
-      pair32(Zr, lo, hi);
+      ap *= ip; am *= im; Zp *= ip; Zm *= im;
+      float own = ap + am;                                 // this lane's share
+      quad4<SumOp>(ap, am, Zp, Zm);
       const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
-      // (a token whose features with a key behind them all round to zero adds nothing but must not spread Inf)
-      const float inv_r = lo + hi > 0.f ? __builtin_amdgcn_rcpf(lo + hi) : inv_den;
       // 1 / (scale * stok * den), in an order that keeps in range what is; scale and stok are powers of two
-      const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * __builtin_amdgcn_rcpf(stok);
+      const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * istok;
       if constexpr (DR) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
         // o - vbar: the other part of the sum is taken as dout . (s - vbar) to match
-        if (valid) dr_acc -= (ap + am) * r0;
+        if (valid) dr_acc -= own * r0;
       }
-      pair32(ap, lo, hi); ap = lo + hi;
-      pair32(am, lo, hi); am = lo + hi;
       const float delta = (ap + am) * r0;
       {
-        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
-        float m = valid ? fmaxf(dmax, fabsf(delta)) * inv_r * om : 0.f;
-        m = wave_max_paired(m);
-        if (lane == 0) sRed[pw] = m;
+        // the tile's largest |dO_i| / den_i
+        const float m = row_max_mag(fmaxf(valid ? dmax * inv_den * om : 0.f, 0.f));
+        if (lane == 0) sRed[w] = m;
       }
       __syncthreads();                                   // the previous tile has been read
       next_gamma();
       {
         // (addresses from a lane index that the optimiser cannot hoist: held across the loop they end up in scratch memory)
-        const int lz = lane + opaque_zero();
-        const int row = 32 * pw + lz % 32, psw = swz<D>(row), gz = lz / 32;
+        const unsigned lz = opaque_lane(lane);
+        const int row = 16 * w + lz % 16, psw = swz<D>(lz % 16), qz = lz / 16;
         char* rowp = sPhi + row * RS;
-        constexpr int CPH = C::LOC / 8;
+        // The weight of the token is in phi, which is rounded anyway; dO, scaled by powers of two only, enters exactly.  (With the weight in dO
+        // both operands were rounded, half of the variance of dS.)
+        // (A token whose dO vanishes, or flushes in fp16, may have any f that phi f holds; one whose dO is not finite makes the sums NaN.)
+        const float f = valid ? fminf(inv_den * gamma * om * istok, 64.f) + (dmax - dmax) : 0.f;
         // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
         // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
-        auto pack4 = [&](const float* f) {
-          return make_uint4(pack_f16x2(f[0] - mean, f[1] - mean), pack_f16x2(f[2] - mean, f[3] - mean),
-                            pack_f16x2(f[4] - mean, f[5] - mean), pack_f16x2(f[6] - mean, f[7] - mean));
+        const float fp = f * ip, fm = f * im, c0 = CENTRE ? -mean * f : zero;
+        auto pack8 = [&](const float* e, float m) {
+          return make_uint4(mul_pack_f16x2(e[0], e[1], m, c0), mul_pack_f16x2(e[2], e[3], m, c0), mul_pack_f16x2(e[4], e[5], m, c0),
+                            mul_pack_f16x2(e[6], e[7], m, c0));
         };
 #pragma unroll
-        for (int c = 0; c < CPH; ++c) {
-          uint4 a = pack4(pp + 8 * c), b = pack4(pm + 8 * c);
-          if (!valid) { a = make_uint4(0, 0, 0, 0); b = a; }
-          *reinterpret_cast<uint4*>(rowp + (((gz * CPH + c) ^ psw) * 16)) = a;
-          *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + gz * CPH + c) ^ psw) * 16)) = b;
+        for (int c = 0; c < K::DK; ++c) {
+          *reinterpret_cast<uint4*>(rowp + (((qz * K::DK + c) ^ psw) * 16)) = pack8(ep + 8 * c, fp);
+          *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + qz * K::DK + c) ^ psw) * 16)) = pack8(em + 8 * c, fm);
         }
-        const float sc = valid ? inv_r * gamma * om : 0.f;
         char* drowp = sDO + row * RS;
 #pragma unroll
-        for (int c = 0; c < D / 16; ++c) {
-          float f[8];
-          unpack_bf16x8(dor[c], f);
-          uint4 a;
-          a.x = pack_f16x2(f[0] * sc, f[1] * sc); a.y = pack_f16x2(f[2] * sc, f[3] * sc);
-          a.z = pack_f16x2(f[4] * sc, f[5] * sc); a.w = pack_f16x2(f[6] * sc, f[7] * sc);
-          *reinterpret_cast<uint4*>(drowp + (((2 * c + gz) ^ psw) * 16)) = a;
+        for (int ks = 0; ks < K::KS; ++ks) *reinterpret_cast<uint4*>(drowp + (((4 * ks + qz) ^ psw) * 16)) = bq[ks];
+        if (lane < 16) {
+          sW[row] = -delta * stok;
+          if constexpr (CENTRE) sF[row] = f;
         }
-        if (g == 0) sW16[row] = (uint16_t)(pack_f16x2(valid ? -delta * sc : 0.f, 0.f) & 0xffffu);
       }
       __syncthreads();
       // g = (1 - r') (G - delta z) / den, its sums cp, cm against phi, and du
       const float r1 = om * r0, r2 = om * inv_den * delta;
       const float cp = ap * r1 - r2 * Zp, cm = am * r1 - r2 * Zm;
-      float du[C::LOC];
+      const float r1p = r1 * ip, r2p = r2 * ip, cpp = cp * ip, r1m = r1 * im, r2m = r2 * im, cmm = cm * im;
+      float du[K::FL];
 #pragma unroll
-      for (int q = 0; q < C::LOC / 4; ++q) {
-        const float4 vp = z4(q), vm = z4(C::HALF / 4 + q);
+      for (int i4 = 0; i4 < K::FL / 4; ++i4) {
+        const float4 vp = z4(i4), vm = z4(C::HALF / 4 + i4);
         const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int j = 4 * q + i;
-          const float gp = fmaf(ga[j / 16][j % 16], r1, fmaf(-r2, zp[i], -cp));
-          const float gm = fmaf(ga[G::GM / 2 + j / 16][j % 16], r1, fmaf(-r2, zm[i], -cm));
-          du[j] = pp[j] * gp - pm[j] * gm;
+          const int j = 4 * i4 + i;
+          const float gp = fmaf(ga[i4][i], r1p, fmaf(-r2p, zp[i], -cpp));
+          const float gm = fmaf(ga[K::GB / 2 + i4][i], r1m, fmaf(-r2m, zm[i], -cmm));
+          du[j] = ep[j] * gp - em[j] * gm;
         }
       }
       // The next tile's rows go out before the dq stores: loads and stores retire in order, and a wait for a load issued behind
       // the stores would wait for the stores as well.
-      load_rows(tile + P < ntile ? tile + P : tile);
-      uint32_t dub[C::LOC / 2];
-      float blk_its = 0.f;
+      qrows.load(xq, tile + P);
+      // dx = du W~^T, tokens on the accumulator rows; du enters scaled by one power of two for the wavefront's tokens
+      uint32_t dub[K::FL / 2];
+      float blk_its;
       {
-        f32x16 xa[L::MB];
-        float its;
-        du_to_dx<D, QAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
-        store_token_rows<D, STREAM>(dqb, rw.sn, tile * kTile + 32 * pw, n, lane, xa, its);
+        float m = 0.f;
+#pragma unroll
+        for (int j = 0; j < K::FL; ++j) m = fmaxf(m, fabsf(du[j]));
+        m = row_max_mag(quad<MagOp>(valid ? m : 0.f));
+        const float pw2 = pow2_normaliser(m), ts = valid ? pw2 : 0.f;
+#pragma unroll
+        for (int j = 0; j < K::FL / 2; ++j) dub[j] = mul_pack_f16x2(du[2 * j], du[2 * j + 1], ts, zero);
+        const float its = __builtin_amdgcn_rcpf(pw2);      // exact: a power of two
+        blk_its = m > 0.f ? its : 0.f;
+        f32x4 xa[K::MB];
+#pragma unroll
+        for (int mb = 0; mb < K::MB; ++mb) xa[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const uint4* wb = sWB + lane + opaque_zero();
+        pipelined_operands<K::DK * K::MB, QAHEAD>(
+            [&](int i) { return wb[i * 64]; },
+            [&](int i, uint4 b) {
+              const uint32_t* a = dub + 4 * (i / K::MB);
+              xa[i % K::MB] = mfma_f16_16(make_uint4(a[0], a[1], a[2], a[3]), b, xa[i % K::MB]);
+            });
+        store_token_rows16<D, STREAM>(dqb, rw.sn, tile * kTile + 16 * w, n, lane, xa, its);
       }
       if constexpr (DW) {
         __syncthreads();                                 // dS has read the tile's phi
-        const int lz = lane + opaque_zero();
-        DWT::park_x(xr, sPhi, pw, lz);
-        DWT::park_du(dub, blk_its, sDU, sRed + 4, pw, lz);
+        const unsigned lz = opaque_lane(lane);
+        const int row = 16 * w + lz % 16, qz = lz / 16;
+        char* rowp = sPhi + row * RS;
+#pragma unroll
+        for (int ks = 0; ks < K::KS; ++ks)
+          *reinterpret_cast<uint4*>(rowp + (((4 * ks + qz) ^ swz<D>(lz % 16)) * 16)) =
+              make_uint4(bf16x2_to_f16x2(xr[ks].x), bf16x2_to_f16x2(xr[ks].y), bf16x2_to_f16x2(xr[ks].z), bf16x2_to_f16x2(xr[ks].w));
+        char* urow = sDU + row * DWT::RSU;
+#pragma unroll
+        for (int c = 0; c < K::DK; ++c)
+          *reinterpret_cast<uint4*>(urow + (((qz * K::DK + c) ^ swz<C::HALF>(lz % 16)) * 16)) =
+              make_uint4(dub[4 * c], dub[4 * c + 1], dub[4 * c + 2], dub[4 * c + 3]);
+        if (lane == 0) sRed[8 + w] = blk_its;
         __syncthreads();
       }
     }
@@ -625,58 +679,51 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     float csum[WMN], wsum = 0.f;                         // column sums of the dO/den operand, sum of the -delta/den operand
 #pragma unroll
     for (int j = 0; j < WMN; ++j) csum[j] = 0.f;
-    f32x16 s[WMN][WMN], zacc;
+    f32x16 s[WMN][WMN];
+    float zacc = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      zacc[r] = 0.f;
+    for (int r = 0; r < 16; ++r)
 #pragma unroll
       for (int i = 0; i < WMN; ++i)
 #pragma unroll
         for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
-    }
-    const int mi = pw / 2, ni = pw % 2;
-    const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
-    const bool do_z = (WMN == 2) || (ni == 0);
-    int offA[WMN][2], offB[WMN][2];
-#pragma unroll
-    for (int i = 0; i < WMN; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
-        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
-      }
+    const int pw = w - NTOK, g = lane / 32;
+    const Quadrant<D> qd(pw);
     DWT dwt;
     if constexpr (DW) dwt.init(pw);
-    // DR: the thread's chunk column of s and dout, vbar there (left in LDS by the prologue until the first tile is parked)
+    // DR: the thread's chunk column of s and dout
     constexpr int PER = kTile * C::CH / 256;
-    const int crow = (tid - 256) / C::CH, ccol = (tid - 256) % C::CH;
-    float vb[8];
-    if constexpr (DR) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) vb[i] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + 8 * ccol + i];
-    }
+    const int crow = (tid - 64 * NTOK) / C::CH, ccol = (tid - 64 * NTOK) % C::CH;
     for (int tile = p; tile < ntile; tile += P) {
       // (blend is never null here: as a branch the section keeps its registers to itself; without one, 97 are spilled with CENTRE and DW where 13
       // are, and 10 with DW alone where none is)
       if (DR && blend != nullptr) {
         const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
         const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
-        uint4 sv[PER], dv[PER];
+        // (width 128: two batches, all at once they are spilled)
+        constexpr int BATCH = D == 128 ? PER / 2 : PER;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          const int t = tile * kTile + crow + i * (256 / C::CH);
-          const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
-          sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
-          dv[i] = *reinterpret_cast<const uint4*>(drow + at);
-        }
+        for (int i0 = 0; i0 < PER; i0 += BATCH) {
+          uint4 sv[BATCH], dv[BATCH];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          float a[8], b[8], t = 0.f;
-          unpack_bf16x8(sv[i], a);
-          unpack_bf16x8(dv[i], b);
+          for (int i = 0; i < BATCH; ++i) {
+            const int t = tile * kTile + crow + (i0 + i) * (256 / C::CH);
+            const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;
+            sv[i] = ld_nt(reinterpret_cast<const uint4*>(srow + at));
+            dv[i] = *reinterpret_cast<const uint4*>(drow + at);
+          }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
-          if (tile * kTile + crow + i * (256 / C::CH) < n) dr_acc += t;
+          for (int i = 0; i < BATCH; ++i) {
+            const float4 v0 = reinterpret_cast<const float4*>(sVb)[2 * ccol], v1 = reinterpret_cast<const float4*>(sVb)[2 * ccol + 1];
+            const float vb[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+            float a[8], b[8], t = 0.f;
+            unpack_bf16x8(sv[i], a);
+            unpack_bf16x8(dv[i], b);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t = fmaf(b[e], a[e] - vb[e], t);
+            if (tile * kTile + crow + (i0 + i) * (256 / C::CH) < n) dr_acc += t;
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       __syncthreads();
@@ -687,35 +734,36 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 #pragma unroll
           for (int j = 0; j < WMN; ++j) csum[j] *= ratio;
         }
+        zacc *= ratio;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          zacc[r] *= ratio;
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
           for (int i = 0; i < WMN; ++i)
 #pragma unroll
             for (int j = 0; j < WMN; ++j) s[i][j][r] *= ratio;
-        }
       }
+      // (worked out per tile: held across the loop these addresses end up in scratch memory, and every k-step waits for one)
+      const int lz = opaque_lane(lane);
+      const QuadrantReads<D> rd(qd, sPhi, sDO, lz);
       __syncthreads();
-      contract_tile<D, false, CENTRE>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
-                       [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); }, csum, &wsum);
+      contract_tokens<D, CENTRE>(rd, s, zacc, sW + 8 * (lz / 32), sF + 8 * (lz / 32), csum, wsum);
       if constexpr (DW) {
         __syncthreads();
         __syncthreads();
-        dwt.contract(sPhi, sDU, sRed + 4, lane + opaque_zero());
+        dwt.contract(sPhi, sDU, sRed + 8, opaque_lane(lane));
       }
     }
     if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
 
     const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
     if constexpr (CENTRE) {
-      // column sums of dO/den (the wavefronts mi = 0 hold every channel block once) and the sum of -delta/den
+      // column sums of dO/den (the wavefronts qd.mi = 0 hold every channel block once) and the sum of -delta/den
       float* cs = cs_part + ((size_t)bh * P + p) * (D + 8);
 #pragma unroll
       for (int j = 0; j < WMN; ++j) {
         float lo, hi;
         pair32(csum[j], lo, hi);
-        if (mi == 0 && g == 0) cs[32 * (ni * WMN + j) + (lane % 32)] = (lo + hi) * ig;
+        if (qd.mi == 0 && g == 0) cs[32 * qd.cblk(j) + (lane % 32)] = (lo + hi) * ig;
       }
       float lo, hi;
       pair32(wsum, lo, hi);
@@ -729,12 +777,13 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       for (int j = 0; j < WMN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
-          dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
+          const int f = 32 * qd.fblk(i) + 8 * (r / 4) + 4 * g + (r % 4);
+          dst[f * D + 32 * qd.cblk(j) + c] = s[i][j][r] * ig;
         }
-    if (do_z && c == 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
+    {
+      float lo, hi;
+      pair32(zacc, lo, hi);
+      if (qd.do_z() && g == 0) dst[D * D + 32 * qd.zblk() + c] = (lo + hi) * ig;
     }
   }
   if constexpr (DR) {
@@ -743,7 +792,8 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     if (lane == 0) sRed[w] = dr_acc;
     __syncthreads();
     if (tid == 0)
-      dr_part[(size_t)bh * P + p] = ((sRed[0] + sRed[1]) + (sRed[2] + sRed[3])) + ((sRed[4] + sRed[5]) + (sRed[6] + sRed[7]));
+      dr_part[(size_t)bh * P + p] = (((sRed[0] + sRed[1]) + (sRed[2] + sRed[3])) + ((sRed[4] + sRed[5]) + (sRed[6] + sRed[7])))
+                                    + ((sRed[8] + sRed[9]) + (sRed[10] + sRed[11]));
   }
 }
 
@@ -918,7 +968,7 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
             DWT::park_du(dub, blk_its, sU, sRed, w % 4, lz);
           }
           __syncthreads();
-          dwt.contract(sX, sU, sRed, lane + opaque_zero());
+          dwt.contract(sX, sU, sRed, opaque_lane(lane));
         }
       }
     }
@@ -928,8 +978,8 @@ __global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__
 
 template <int D, bool DW>
 constexpr size_t q_smem() {
-  return sizeof(uint4) * (Cfg<D>::W_IMG + GradLayout<D>::IMG + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64)
-       + 2 * (size_t)kTile * D * 2 + kTile * 2 + (D + 8) * sizeof(float) + (DW ? DwTile<D, 4>::DU_BYTES : 0);
+  return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG)
+       + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4, 16>::DU_BYTES : 0);
 }
 template <int D, bool DW>
 constexpr size_t k_smem() {

@@ -1,0 +1,219 @@
+// Blocks of 16 tokens to a wavefront: v_mfma_f32_16x16x32_{bf16,f16}, tokens along N as in the 32-token form, four lanes to a token.
+//   lane l = (m, q) with m = l % 16, q = l / 16
+//   A: lane holds A[m][8q .. 8q+7],  B: lane holds B[8q .. 8q+7][m],  D: lane holds D[4q + r][m] for r = 0..3
+// A lane has half of what a lane of the 32-token form has, so that a SIMD holds twice the wavefronts: with one or two, a chain of MFMAs,
+// exponentials and exchanges leaves a third of the issue slots empty.  What it costs is LDS reads: an operand of an image serves 16
+// tokens instead of 32.
+#pragma once
+#include "mfma_common.h"
+
+namespace linattn {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+
+// Lane (t, q) owns FL consecutive features of each half of phi, q*FL .. q*FL + FL-1; row block mb, register r of an accumulator over the
+// features <-> feature q*FL + 4*mb + r, so operand row m of block mb is feature (m/4)*FL + 4*mb + m%4.
+template <int D>
+struct Tok16 {
+  static constexpr int HALF = D / 2;
+  static constexpr int FL = D / 8;        // features of a half that a lane owns
+  static constexpr int UB = HALF / 16;    // row blocks of U^T
+  static constexpr int KS = D / 32;       // k-steps over the channels
+  static constexpr int GB = D / 16;       // row blocks over the D features of phi
+  static constexpr int DK = FL / 8;       // k-steps over the d/2 pre-softmax features (element (q, e) of k-step ks: feature q*FL + 8*ks + e)
+  static constexpr int MB = D / 16;       // column blocks over the channels (column c of block mb: channel MB*c + mb)
+  static constexpr int W_IMG = KS * UB * 64, G_IMG = KS * GB * 64, T_IMG = DK * MB * 64;      // uint4 entries of the images
+  __device__ static constexpr int feature(int mb, int m) { return (m / 4) * FL + 4 * mb + m % 4; }
+};
+
+__device__ __forceinline__ f32x4 mfma_bf16_16(uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_f16_16(uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0);
+}
+
+// W~ [D][D/2] bf16 (one head) -> LDS image of the A operands of U^T = W~^T X^T: entry (ks, mb, lane = (m, q)) holds
+// W~[32ks + 8q + e][feature(mb, m)].  A thread reads four adjacent features of eight channels and writes the four entries they fill.
+template <int D, int NTHREADS>
+__device__ __forceinline__ void build_w_image16(const uint16_t* __restrict__ w, uint4* img, int tid) {
+  using K = Tok16<D>;
+  for (int it = tid; it < K::W_IMG / 4; it += NTHREADS) {
+    const int mq = it % 4, mb = (it / 4) % K::UB, q = (it / (4 * K::UB)) % 4, ks = it / (16 * K::UB);
+    const uint16_t* src = w + (32 * ks + 8 * q) * K::HALF + K::feature(mb, 4 * mq);
+    uint2 r[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = *reinterpret_cast<const uint2*>(src + e * K::HALF);
+    auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
+    auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
+    uint4* dst = img + (ks * K::UB + mb) * 64 + 16 * q + 4 * mq;
+    dst[0] = make_uint4(lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x));
+    dst[1] = make_uint4(hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x));
+    dst[2] = make_uint4(lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y));
+    dst[3] = make_uint4(hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y));
+  }
+}
+
+// W~ -> LDS image (fp16, exact) of the B operands of dX = dU W~^T, tokens on the accumulator rows: entry (ks, mb, lane = (c, q)) holds
+// W~[MB*c + mb][q*FL + 8ks + e].
+template <int D, int NTHREADS>
+__device__ __forceinline__ void build_w_image_t16(const uint16_t* __restrict__ w, uint4* img, int tid) {
+  using K = Tok16<D>;
+  for (int idx = tid; idx < K::T_IMG; idx += NTHREADS) {
+    const int c = idx % 16, q = (idx / 16) % 4, mb = (idx / 64) % K::MB, ks = idx / (64 * K::MB);
+    const uint4 r = *reinterpret_cast<const uint4*>(w + (K::MB * c + mb) * K::HALF + q * K::FL + 8 * ks);
+    img[idx] = make_uint4(bf16x2_to_f16x2(r.x), bf16x2_to_f16x2(r.y), bf16x2_to_f16x2(r.z), bf16x2_to_f16x2(r.w));
+  }
+}
+
+// A operands of G^T = S Y^T: entry (ks, mb, lane = (m, q)) holds scale * S[f][32ks + 8q + e], f = feature(mb, m) of the + half for mb < GB/2,
+// of the - half otherwise.  The entry of lane (m, q) lies at 16q + (m ^ (4ks + q)): eight lanes of the writing wavefront have the
+// same m, and would all hit the same banks.
+template <int D>
+__device__ __forceinline__ int grad16_lane(int lane) { return lane ^ (lane / 16); }        // the place in k-step 0; ^ 4ks in k-step ks
+template <int D, int NTHREADS>
+__device__ __forceinline__ void write_grad_image16(const StateRegs<D, NTHREADS>& S, uint4* img, float sc) {
+  using K = Tok16<D>;
+  if (!S.active) return;
+  const int ks = S.cq / 8, q = (S.cq / 2) % 4;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int f = 8 * S.fo + e, half = f / K::HALF, fl = f % K::HALF, j = fl % K::FL;
+    const int mb = half * (K::GB / 2) + j / 4, m = 4 * (fl / K::FL) + j % 4;
+    uint2* dst = reinterpret_cast<uint2*>(img + (ks * K::GB + mb) * 64 + 16 * q + (m ^ (4 * ks + q))) + S.cq % 2;
+    *dst = make_uint2(pack_f16x2(sc * S.v[e][0], sc * S.v[e][1]), pack_f16x2(sc * S.v[e][2], sc * S.v[e][3]));
+  }
+}
+
+// The lane index as a value that the optimiser cannot hoist out of a loop, in a range that it knows (addresses made from it are worked out where
+// they are used instead of being held, or spilled, across the loop).
+__device__ __forceinline__ unsigned opaque_lane(int lane) { return (unsigned)(lane + opaque_zero()) & 63u; }
+
+// A zero in a scalar register that the optimiser cannot see through.
+__device__ __forceinline__ float opaque_zero_scalar() {
+  float z = 0.f;
+  asm volatile("" : "+s"(z));
+  return z;
+}
+// a*s + c, b*s + c rounded to fp16, a mixed-precision instruction each (two multiplications and a conversion are three for two; with a c that it sees
+// is zero the compiler takes those).
+__device__ __forceinline__ uint32_t mul_pack_f16x2(float a, float b, float s, float c) {
+  const f16x2 r = {(_Float16)fmaf(a, s, c), (_Float16)fmaf(b, s, c)};
+  return __builtin_bit_cast(uint32_t, r);
+}
+__device__ __forceinline__ uint32_t mul_pack_f16x2(uint32_t ab, float s, float c) {
+  const f16x2 v = __builtin_bit_cast(f16x2, ab);
+  const f16x2 r = {(_Float16)fmaf((float)v[0], s, c), (_Float16)fmaf((float)v[1], s, c)};
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// Rows of a tile as operands: lane (t, q) reads the 16-byte chunks 4ks + q of row `row` (0 .. kTile-1) of the tile.  Bounded buffer loads: the
+// address is one register that never changes, and rows past n read as zeros.
+template <int D>
+struct TileRows {
+  uint32_t at, pitch;
+  const char* base;
+  int n;
+  __device__ __forceinline__ TileRows(const uint16_t* head, size_t sn, int n_, int row, int q) : base((const char*)head), n(n_) {
+    pitch = (uint32_t)sn * 2;
+    at = (uint32_t)row * pitch + 16 * q;
+  }
+  __device__ __forceinline__ void load(uint4 (&x)[D / 32], int tile) const {
+    const int left = n - tile * kTile < kTile ? n - tile * kTile : kTile;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (size_t)tile * kTile * pitch, 0,
+                                                                       left > 0 ? (uint32_t)left * pitch : 0, 0x00020000);
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) x[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, at + 64 * ks, 0, 0));
+  }
+};
+
+// Reductions over the four lanes of a token, every one of them receives the result.  Two or four at a time: a swap of two quantities
+// combines both in one operation.
+struct SumOp { static __device__ __forceinline__ float of(float a, float b) { return a + b; } };
+struct MaxOp { static __device__ __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
+// a, b -> [a of the low 32 lanes, b of the low 32], [a of the high 32, b of the high 32]
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+// rows of 16 lanes: a, b -> [a0, b0, a2, b2], [a1, b1, a3, b3]
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+template <typename Op>
+__device__ __forceinline__ float quad(float a) {
+  float b = a;
+  swap32(a, b); a = b = Op::of(a, b);
+  swap16(a, b); return Op::of(a, b);
+}
+template <typename Op>
+__device__ __forceinline__ void quad2(float& a, float& b) {
+  swap32(a, b);
+  float s = Op::of(a, b), t = s;
+  swap16(s, t); a = b = Op::of(s, t);
+  swap32(a, b);
+}
+template <typename Op>
+__device__ __forceinline__ void quad4(float& a, float& b, float& c, float& d) {
+  swap32(a, b); swap32(c, d);
+  float s = Op::of(a, b), t = Op::of(c, d);
+  swap16(s, t);
+  a = b = Op::of(s, t);                  // rows: a, c, b, d
+  swap32(a, b);
+  c = a; d = b;
+  swap16(a, c); swap16(b, d);
+}
+// Maxima of magnitudes, which compare as integers (a floating-point maximum of exchanged values first quiets both): over the four lanes of a token, and
+// over the 16 lanes of a row.
+struct MagOp {
+  static __device__ __forceinline__ float of(float a, float b) {
+    const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+    return __builtin_bit_cast(float, x > y ? x : y);
+  }
+};
+__device__ __forceinline__ float row_max_mag(float x) {
+  x = MagOp::of(x, dpp_move<0xB1>(x));      // quad_perm [1,0,3,2]
+  x = MagOp::of(x, dpp_move<0x4E>(x));      // quad_perm [2,3,0,1]
+  x = MagOp::of(x, dpp_move<0x124>(x));     // row_ror 4
+  return MagOp::of(x, dpp_move<0x128>(x));  // row_ror 8
+}
+
+// The 16 rows from token t0 of a head of n tokens: lane (c, q), register r has PIECE bytes of token t0 + 4q + r, at byte PIECE*c of the row.
+// Buffer stores bounded to the rows that exist, as in TokenRows.
+template <int PIECE>
+struct TokenRows16 {
+  __amdgpu_buffer_rsrc_t rows;
+  uint32_t at, pitch;
+  __device__ __forceinline__ TokenRows16(void* base, size_t pitch_bytes, int t0, int n, int lane) {
+    const int left = n - t0 < 16 ? n - t0 : 16;
+    pitch = (uint32_t)pitch_bytes;
+    rows = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(base) + (size_t)t0 * pitch_bytes, 0, left > 0 ? (uint32_t)left * pitch : 0, 0x00020000);
+    const unsigned lz = opaque_lane(lane);
+    at = (uint32_t)(4 * (lz / 16)) * pitch + (uint32_t)(PIECE * (lz % 16));
+  }
+  template <bool STREAM, typename V>
+  __device__ __forceinline__ void store(int r, V v) const {
+    static_assert(sizeof(V) == PIECE, "a lane's piece of a row");
+    const uint32_t off = at + (uint32_t)r * pitch;
+    constexpr int aux = STREAM ? 2 : 0;
+    if constexpr (PIECE == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rows, off, 0, aux);
+    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, off, 0, aux);
+  }
+};
+// acc[mb][r] of lane (c, q): token 4q + r, channel MB*c + mb  ->  mul * acc as bf16 rows of base
+template <int D, bool STREAM>
+__device__ __forceinline__ void store_token_rows16(uint16_t* base, size_t sn, int t0, int n, int lane, const f32x4 (&acc)[D / 16], float mul) {
+  constexpr int MB = D / 16;
+  const TokenRows16<2 * MB> rows(base, sn * 2, t0, n, lane);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    uint32_t w[MB / 2];
+#pragma unroll
+    for (int i = 0; i < MB / 2; ++i) w[i] = pack_bf16x2(acc[2 * i][r] * mul, acc[2 * i + 1][r] * mul);
+    if constexpr (MB == 8) rows.template store<STREAM>(r, make_uint4(w[0], w[1], w[2], w[3]));
+    else rows.template store<STREAM>(r, make_uint2(w[0], w[1]));
+  }
+}
+
+}  // namespace linattn

@@ -405,12 +405,16 @@ struct StateRegs {
 // address of row s/4, columns 4*(s%4)..+3, and receives column s of the four rows.
 // tr_offset() is the lane's byte offset for row0 = 0 and the first (j = 0) or second (j = 1)
 // group of four rows; row0 = 16*ks adds 16*ks*RS bytes (the swizzle repeats every 16 rows).
+// The 32-column block and the group enter by exclusive-or: a block's chunk numbers differ from block 0's in bits that the lane's part leaves 0,
+// and row r + 4 (r + 8 below) changes one bit of the swizzle.
+template <int D, int ROWS>      // ROWS: tile rows between the lane groups of 32
+__device__ __forceinline__ int tr_lane(unsigned lane) {
+  const unsigned r = ROWS * (lane / 32) + (lane % 16) / 4;
+  return (int)(r * (D * 2) + (((2 * (lane / 16 % 2) + lane % 4 / 2) ^ (unsigned)swz<D>((int)r)) * 16) + lane % 2 * 8);
+}
 template <int D>
-__device__ __forceinline__ int tr_offset(int col0, int lane, int j) {
-  constexpr int RS = D * 2;
-  const int r = 8 * (lane / 32) + ((lane % 16) / 4) + 4 * j;
-  const int col = col0 + 16 * ((lane / 16) % 2) + 4 * (lane % 4);    // element column, multiple of 4
-  return r * RS + (((col / 8) ^ swz<D>(r)) * 16) + (col % 8) * 2;
+__device__ __forceinline__ int tr_offset(int col0, int lane, int j) {      // col0: a multiple of 32
+  return (tr_lane<D, 8>((unsigned)lane) ^ (2 * col0) ^ (j && D > 32 ? 16 : 0)) + j * 4 * (D * 2);
 }
 
 // Byte offset of this lane's address for a transposing read of an operand of k-step 0 in the
@@ -418,16 +422,28 @@ __device__ __forceinline__ int tr_offset(int col0, int lane, int j) {
 // j = 0: tile rows 4g .. 4g+3, j = 1: rows 8+4g .. 8+4g+3 (g = lane/32); columns col0 + lane%32.
 template <int D>
 __device__ __forceinline__ int tr_offset_g4(int col0, int lane, int j) {
-  constexpr int RS = D * 2;
-  const int r = 4 * (lane / 32) + ((lane % 16) / 4) + 8 * j;
-  const int col = col0 + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-  return r * RS + (((col / 8) ^ swz<D>(r)) * 16) + (col % 8) * 2;
+  return (tr_lane<D, 4>((unsigned)lane) ^ (2 * col0) ^ (j && D > 32 ? 32 : 0)) + j * 8 * (D * 2);
 }
 
+// LDS addresses as 32-bit integers.  tr_base() puts a tile's base into the register that an offset is in, where the optimiser cannot take it out
+// again: what is left to add, the k-step, then fits the instruction's 16-bit offset.  With the base (the tiles lie above 64 KB) among the
+// constants every read had an addition of its own, 126 in the contractions of a tile of the query-side backward.
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
+__device__ __forceinline__ uint32_t tr_base(const char* tile, int off) {
+  uint32_t a = lds_address(tile) + (uint32_t)off;
+  asm volatile("" : "+v"(a));
+  return a;
+}
 __device__ __forceinline__ f16x8 read_tr(const char* tile, int off0, int off1) {
   struct { s16x4 lo, hi; } v;
   v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tile + off0));
   v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tile + off1));
+  return __builtin_bit_cast(f16x8, v);
+}
+__device__ __forceinline__ f16x8 read_tr(uint32_t at0, uint32_t at1) {
+  struct { s16x4 lo, hi; } v;
+  v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at0);
+  v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at1);
   return __builtin_bit_cast(f16x8, v);
 }
 
@@ -436,7 +452,9 @@ __device__ __forceinline__ f16x8 read_tr(const char* tile, int off0, int off1) {
 // a saturated softmax leaves in du) the exact normaliser is not representable, and such values are
 // zero against anything they are added to, so they may flush in the fp16 operand.
 __device__ __forceinline__ float pow2_normaliser(float m) {
-  return (m >= 0x1p-100f && m < 3.0e38f) ? ldexpf(1.0f, -ilogbf(m)) : 1.0f;
+  // 2^-ilogb(m), from the exponent; 2^-127 for m from 2^127 is subnormal
+  const uint32_t e = 0x7f000000u - (__builtin_bit_cast(uint32_t, m) & 0x7f800000u);
+  return m >= 0x1p-100f && m < 3.0e38f ? __builtin_bit_cast(float, e > 0x00400000u ? e : 0x00400000u) : 1.0f;
 }
 
 // A token's largest gradient is normalised as if it were no larger than this: the scale is then at least 2^-126, a normal number whose
@@ -581,26 +599,48 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
-// One 128-token tile of a split-n sum over tokens: s[i][j] += A_i^T B_j and zacc += A_z^T w, with A
+// Wavefront pw (of four) owns D/64 x D/64 blocks of 32 features x 32 channels of a state: feature blocks fblk(0 ..), channel blocks cblk(0 ..).  The
+// first of its feature blocks, zblk, is the one whose z it sums (width 64: two wavefronts have it, do_z is one of them).
+template <int D>
+struct Quadrant {
+  static constexpr int WMN = D / 64;
+  int mi, ni;
+  __device__ __forceinline__ explicit Quadrant(int pw) : mi(pw / 2), ni(pw % 2) {}
+  __device__ __forceinline__ int fblk(int i) const { return mi * WMN + (WMN == 2 ? i ^ ni : i); }
+  __device__ __forceinline__ int cblk(int j) const { return ni * WMN + j; }
+  __device__ __forceinline__ int zblk() const { return fblk(0); }
+  __device__ __forceinline__ bool do_z() const { return WMN == 2 || ni == 0; }
+};
+// Where a lane's transposing reads of k-step 0 of its blocks start (tr_offset): tiles sA (features) and sB (channels).
+template <int D>
+struct QuadrantReads {
+  uint32_t a[D / 64][2], b[D / 64][2];
+  __device__ __forceinline__ QuadrantReads(const Quadrant<D>& qd, const char* sA, const char* sB, int lane) {
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        a[i][j] = tr_base(sA, tr_offset<D>(32 * qd.fblk(i), lane, j));
+        b[i][j] = tr_base(sB, tr_offset<D>(32 * qd.cblk(i), lane, j));
+      }
+  }
+};
+
+// One 128-token tile of a split-n sum over tokens: s[i][j] += A_i^T B_j and zacc += A_0^T w, with A
 // and B fp16 tiles [kTile][D] in LDS (swizzled 16-byte chunks) read by transposing reads, the
 // operands of k-step ks+1 requested before the MFMAs of k-step ks.  wop(ks) returns the B operand
-// of the z sum for that k-step (per-token weights, the same in every column); z_hi picks which of
-// the wavefront's A blocks feeds it, do_z whether this wavefront owns a z block at all.
+// of the z sum for that k-step (per-token weights, the same in every column); do_z whether this wavefront owns a z block at all.
 // BF16: the tiles and wop's operands hold bf16 instead of fp16 (same bits per element, bf16 MFMA).
-// SUMS: also accumulate csum[j] += the sum over the tile's tokens of the B operand's column of this lane
-// (a lane holds 8 tokens of one channel per k-step) and *wsum += the sum of wop's operand (fp16 tiles only).
-template <int D, bool BF16 = false, bool SUMS = false, typename WOp>
-__device__ __forceinline__ void contract_tile(const char* sA, const char* sB, const int (&offA)[D / 64][2],
-                                              const int (&offB)[D / 64][2], f32x16 (&s)[D / 64][D / 64],
-                                              f32x16& zacc, bool z_hi, bool do_z, WOp wop,
-                                              float* csum = nullptr, float* wsum = nullptr) {
+template <int D, bool BF16 = false, typename WOp>
+__device__ __forceinline__ void contract_tile(const QuadrantReads<D>& rd, f32x16 (&s)[D / 64][D / 64],
+                                              f32x16& zacc, bool do_z, WOp wop) {
   constexpr int RS = D * 2, WMN = D / 64, KSN = kTile / 16;
   f16x8 a[KSN][WMN], b[KSN][WMN], wv[KSN];
   auto request = [&](int kn) {
 #pragma unroll
-    for (int i = 0; i < WMN; ++i) a[kn][i] = read_tr(sA + kn * 16 * RS, offA[i][0], offA[i][1]);
+    for (int i = 0; i < WMN; ++i) a[kn][i] = read_tr(rd.a[i][0] + kn * 16 * RS, rd.a[i][1] + kn * 16 * RS);
 #pragma unroll
-    for (int j = 0; j < WMN; ++j) b[kn][j] = read_tr(sB + kn * 16 * RS, offB[j][0], offB[j][1]);
+    for (int j = 0; j < WMN; ++j) b[kn][j] = read_tr(rd.b[j][0] + kn * 16 * RS, rd.b[j][1] + kn * 16 * RS);
     wv[kn] = wop(kn);
   };
   request(0);
@@ -612,25 +652,7 @@ __device__ __forceinline__ void contract_tile(const char* sA, const char* sB, co
     for (int i = 0; i < WMN; ++i)
 #pragma unroll
       for (int j = 0; j < WMN; ++j) s[i][j] = mfma16<BF16>(a[ks][i], b[ks][j], s[i][j]);
-    if (WMN == 2) {
-      // a select, not a branch: branches inside the loop make the compiler's waits conservative
-      const f16x8 az = z_hi ? a[ks][WMN - 1] : a[ks][0];
-      zacc = mfma16<BF16>(az, wv[ks], zacc);
-    } else if (do_z) {
-      zacc = mfma16<BF16>(a[ks][0], wv[ks], zacc);
-    }
-    if constexpr (SUMS) {
-#pragma unroll
-      for (int j = 0; j < WMN; ++j) {
-        const uint4 q = __builtin_bit_cast(uint4, b[ks][j]);
-        csum[j] = add_pair_f16(q.x, csum[j]); csum[j] = add_pair_f16(q.y, csum[j]);
-        csum[j] = add_pair_f16(q.z, csum[j]); csum[j] = add_pair_f16(q.w, csum[j]);
-      }
-      const uint4 q = __builtin_bit_cast(uint4, wv[ks]);
-      float t = *wsum;
-      t = add_pair_f16(q.x, t); t = add_pair_f16(q.y, t); t = add_pair_f16(q.z, t); t = add_pair_f16(q.w, t);
-      *wsum = t;
-    }
+    if (WMN == 2 || do_z) zacc = mfma16<BF16>(a[ks][0], wv[ks], zacc);
     __builtin_amdgcn_sched_barrier(0);
   }
 }

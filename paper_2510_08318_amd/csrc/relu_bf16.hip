@@ -41,7 +41,7 @@ __device__ __forceinline__ void relu_state_segment(const uint16_t* __restrict__ 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
   const int g = lane / 32;
-  const int mi = w / 2, ni = w % 2;
+  const Quadrant<D> qd(w);
   const int tile_end = tile0 + nt;
 
   f32x16 s[WMN][WMN], zacc;
@@ -53,16 +53,7 @@ __device__ __forceinline__ void relu_state_segment(const uint16_t* __restrict__ 
 #pragma unroll
       for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
   }
-  const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;      // the 32-feature block whose z this wavefront sums
-  const bool do_z = (WMN == 2) || (ni == 0);
-  int offA[WMN][2], offB[WMN][2];
-#pragma unroll
-  for (int i = 0; i < WMN; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
-      offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
-    }
+  const QuadrantReads<D> rd(qd, sK, sV, lane);
   uint4 ones;
   ones.x = ones.y = ones.z = ones.w = 0x3F803F80u;      // bf16 1.0
   const f16x8 one_op = as_f16x8(ones);
@@ -123,7 +114,7 @@ __device__ __forceinline__ void relu_state_segment(const uint16_t* __restrict__ 
     }
     load_tile(kx, vx, tile + DEPTH);
     __syncthreads();
-    contract_tile<D, true>(sK, sV, offA, offB, s, zacc, ni != 0, do_z, [&](int) { return one_op; });
+    contract_tile<D, true>(rd, s, zacc, qd.do_z(), [&](int) { return one_op; });
   };
 #pragma unroll
   for (int j = 0; j < DEPTH; ++j) load_tile(kr[j], vr[j], tile0 + j);
@@ -143,12 +134,12 @@ __device__ __forceinline__ void relu_state_segment(const uint16_t* __restrict__ 
     for (int j = 0; j < WMN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
-        dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r];
+        const int f = 32 * qd.fblk(i) + 8 * (r / 4) + 4 * g + (r % 4);
+        dst[f * D + 32 * qd.cblk(j) + c] = s[i][j][r];
       }
-  if (do_z && c == 0) {
+  if (qd.do_z() && c == 0) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r];
+    for (int r = 0; r < 16; ++r) dst[D * D + 32 * qd.zblk() + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r];
   }
   __syncthreads();                               // the next segment reuses the LDS tiles
 }
@@ -485,17 +476,8 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
 #pragma unroll
         for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
     }
-    const int mi = pw / 2, ni = pw % 2;
-    const int zmb = (WMN == 2) ? (2 * mi + ni) : mi;
-    const bool do_z = (WMN == 2) || (ni == 0);
-    int offA[WMN][2], offB[WMN][2];
-#pragma unroll
-    for (int i = 0; i < WMN; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        offA[i][j] = tr_offset<D>(32 * (mi * WMN + i), lane, j);
-        offB[i][j] = tr_offset<D>(32 * (ni * WMN + i), lane, j);
-      }
+    const Quadrant<D> qd(pw);
+    const QuadrantReads<D> rd(qd, sPhi, sDO, lane);
     for (int tile = p; tile < ntile; tile += P) {
       __syncthreads();
       const float ratio = next_gamma();
@@ -510,7 +492,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
         }
       }
       __syncthreads();
-      contract_tile<D>(sPhi, sDO, offA, offB, s, zacc, ni != 0, do_z,
+      contract_tile<D>(rd, s, zacc, qd.do_z(),
                        [&](int ks) { return as_f16x8(*reinterpret_cast<const uint4*>(sW16 + 16 * ks + 8 * g)); });
     }
     const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
@@ -522,12 +504,12 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
       for (int j = 0; j < WMN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int f = 32 * (mi * WMN + i) + 8 * (r / 4) + 4 * g + (r % 4);
-          dst[f * D + 32 * (ni * WMN + j) + c] = s[i][j][r] * ig;
+          const int f = 32 * qd.fblk(i) + 8 * (r / 4) + 4 * g + (r % 4);
+          dst[f * D + 32 * qd.cblk(j) + c] = s[i][j][r] * ig;
         }
-    if (do_z && c == 0) {
+    if (qd.do_z() && c == 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dst[D * D + 32 * zmb + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
+      for (int r = 0; r < 16; ++r) dst[D * D + 32 * qd.zblk() + 8 * (r / 4) + 4 * g + (r % 4)] = zacc[r] * ig;
     }
   }
 }

@@ -1,0 +1,64 @@
+"""The query-side backward's wavefronts of 16 tokens: lengths around a wavefront's, a tile's and a workgroup's share, and tokens whose upstream
+gradient vanishes, is far below its neighbours' or is not finite, which the per-token weights of the sums dS and dz have to carry.
+
+Bar: 1e-2 element by element, the bar of the bf16 mode."""
+import numpy as np
+import pytest
+
+from oracle import linattn_oracle as O
+from paper_2510_08318_amd import synth
+from tests.test_bf16_paths_gpu import _check, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [15, 16, 17, 63, 113, 127, 129, 256 * 128 + 5])
+def test_lengths(n, d):
+    _check(synth.generate("C5", n=n, H=1, B=1, d=d, dtype="bf16"), centred=n == 113)
+
+
+def _with_gradient(d, edit, n=333):
+    x = synth.generate("C5", n=n, H=2, B=1, d=d, dtype="bf16")
+    do = O.to_f64(x.dout).astype(np.float32)
+    edit(do)
+    x.dout = synth._pack(do, x.dtype)
+    return x
+
+
+@pytest.mark.parametrize("centred", [False, True], ids=["plain", "centred"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_tokens_without_or_with_tiny_gradients(d, centred):
+    def edit(do):
+        do[:, :, ::3] = 0.0                    # in every wavefront
+        do[:, :, 128:256] = 0.0                # a whole tile
+        do[:, :, 1::5] *= 2.0 ** -8            # below the others of their wavefront, whose du share a scale: fp16 has 11 bits down to 2^-14
+        do[:, :, 300:] *= 2.0 ** -110          # below what fp16 holds at any scale of a token
+    x = _with_gradient(d, edit)
+    ref = O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)
+    got = _run(x, False, True, centred)
+    for name, r in zip(("dk", "dv", "dwq", "dwk"), (ref[1], ref[2], ref[3], ref[4])):
+        assert O.err_metric(got[name], r)[0] <= 1e-2, name
+    # dq is proportional to a token's dO: each magnitude against its own floor
+    for rows in (slice(0, 1), slice(2, 128, 15), slice(1, 128, 15)):
+        r = ref[0][:, :, rows]
+        if not r.any():
+            assert not got["dq"][:, :, rows].any()
+        else:
+            assert O.err_metric(got["dq"][:, :, rows], r)[0] <= 1e-2, rows
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_gradient_that_is_not_finite(value):
+    """One entry of head 0: dk of that head sums it into every row, the other head has none of it."""
+    def edit(do):
+        do[0, 0, 40, 3] = value
+    x = _with_gradient(128, edit)
+    got = _run(x, False, True)
+    ref = O.bwd_bh(x.q[:, 1:], x.k[:, 1:], x.v[:, 1:], x.wq[1:], x.wk[1:], x.dout[:, 1:])
+    assert not np.isfinite(got["dk"][0, 0]).any() and not np.isfinite(got["dv"][0, 0, :, 3]).any()
+    assert not np.isfinite(got["dq"][0, 0, 40]).any()
+    finite = np.delete(np.arange(x.n), 40)
+    assert np.isfinite(got["dq"][0, 0][finite]).all()
+    for name, r in zip(("dq", "dk", "dv"), ref):
+        assert O.err_metric(got[name][:, 1:], r)[0] <= 1e-2, name
