@@ -8,7 +8,7 @@
 //   through phi  du = p+ (g+ - <g+,p+>) - p- (g- - <g-,p->),   dx = du W~^T,   dW~ = sum x^T du
 //
 // bwd_q_kernel    : per 128-token tile: phi(Q), G = dO S^T, delta, du, dq; dS, dz partials (split-n); dW~_q partials
-// bwd_k_kernel    : per 32-token block: phi(K), g, du, dk, dv; dW~_k partials
+// bwd_k_kernel    : per 16-token block: phi(K), g, du, dk, dv; dW~_k partials
 // (the partials are reduced in state_reduce.hip)
 //
 // Precision: every 16-bit MFMA operand except the stored bf16 q, k (projection) is fp16.
@@ -152,8 +152,8 @@ __device__ __forceinline__ float build_key_state(const float* __restrict__ dstat
     if (tid < D) sRow[tid] = 0.f;
   }
   const float scale = S.scale(red, tid);                    // (its barrier covers vb, cB and misc as well)
-  S.write_grad_image(sGA, scale);
-  S.template write_apply_image<ApplyLayout<D>::MB>(sVA, scale);
+  write_grad_image16<D, NTHREADS>(S, sGA, scale);
+  write_apply_image16<D, NTHREADS>(S, sVA, scale);
   const float inv = __builtin_amdgcn_rcpf(scale);           // exact: a power of two
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -165,63 +165,6 @@ __device__ __forceinline__ float build_key_state(const float* __restrict__ dstat
     if (S.active && S.cq == 0) sZ[f] = cB[f] - (CENTRE ? misc[f < D / 2 ? 1 : 2] : 0.f) - dot * inv;
   }
   return scale;
-}
-
-// Softmax Jacobian of Eq. 5 for one token spread over a lane pair: gacc holds g in the GradLayout
-// row order (first GM/2 blocks the softmax(+u) half, then the softmax(-u) half), already scaled.
-template <int D>
-__device__ __forceinline__ void phi_jacobian(const float (&gp)[Cfg<D>::LOC], const float (&gm)[Cfg<D>::LOC],
-                                             const float (&pp)[Cfg<D>::LOC], const float (&pm)[Cfg<D>::LOC],
-                                             float (&du)[Cfg<D>::LOC]) {
-  using C = Cfg<D>;
-  float cp = 0.f, cm = 0.f;
-#pragma unroll
-  for (int j = 0; j < C::LOC; ++j) { cp = fmaf(gp[j], pp[j], cp); cm = fmaf(gm[j], pm[j], cm); }
-  float lo, hi;
-  pair32(cp, lo, hi); cp = lo + hi;
-  pair32(cm, lo, hi); cm = lo + hi;
-#pragma unroll
-  for (int j = 0; j < C::LOC; ++j) du[j] = pp[j] * (gp[j] - cp) - pm[j] * (gm[j] - cm);
-}
-
-// dx = du W~^T for one block of 32 tokens, tokens on the accumulator rows: du is scaled by one power
-// of two per block (its largest magnitude lands in [1,2)), cast to fp16 and fed as the A operand
-// (lane (t,g) holds features g*LOC + 8ks + e of token t); the B operands are the W~ image.
-// acc[mb][r] of lane (c,g) is its * dx[token 8*(r/4) + 4g + r%4][channel MB*c + mb].
-//
-// dub receives the scaled fp16 du as packed (lane (t,g): features g*LOC .. g*LOC + LOC-1 of token t; zero for tokens
-// that do not exist), blk_its the inverse scale (0 for an all-zero block): what the dW~ contraction parks.
-// AHEAD: lookahead of the W~ operand reads of dx (pipelined_operands).
-template <int D, int AHEAD>
-__device__ __forceinline__ void du_to_dx(const float (&du)[Cfg<D>::LOC], const uint4* sWB, int lane, bool valid,
-                                         f32x16 (&acc)[D / 32], float& its, uint32_t (&dub)[Cfg<D>::LOC / 2], float& blk_its) {
-  using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  constexpr int DK = C::LOC / 8;
-  float m = 0.f;
-#pragma unroll
-  for (int j = 0; j < C::LOC; ++j) m = fmaxf(m, fabsf(du[j]));
-  if (!valid) m = 0.f;
-  float lo, hi;
-  pair32(m, lo, hi); m = fmaxf(lo, hi);
-  m = wave_max_paired(m);
-  const float ts = valid ? pow2_normaliser(m) : 0.f;
-#pragma unroll
-  for (int j = 0; j < C::LOC / 2; ++j) dub[j] = pack_f16x2(du[2 * j] * ts, du[2 * j + 1] * ts);
-  its = __builtin_amdgcn_rcpf(pow2_normaliser(m));     // exact: a power of two
-  blk_its = m > 0.f ? its : 0.f;
-#pragma unroll
-  for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
-  const uint4* wb = sWB + lane + opaque_zero();
-  pipelined_operands<DK * L::MB, AHEAD>(
-      [&](int i) { return wb[i * 64]; },
-      [&](int i, uint4 b) {
-        const int ks = i / L::MB, mb = i % L::MB;
-        uint4 aq; aq.x = dub[4 * ks]; aq.y = dub[4 * ks + 1]; aq.z = dub[4 * ks + 2]; aq.w = dub[4 * ks + 3];
-        acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(aq), as_f16x8(b), acc[mb], 0, 0, 0);
-      });
 }
 
 // ---- dW~ = sum_i x_i^T du_i, accumulated inside the kernels that make du ---------------------
@@ -257,30 +200,6 @@ struct DwTile {
     for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-  }
-  // The x rows of block slot (0..3) as the projection holds them: lane (t,g) has the 16-byte chunks 2ks + g of token t.
-  static __device__ __forceinline__ void park_x(const uint4 (&xr)[D / 16], char* sX, int slot, int lane) {
-    const int row = 32 * slot + lane % 32, g = lane / 32;
-    char* rowp = sX + row * RSX;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      uint4 hv;
-      hv.x = bf16x2_to_f16x2(xr[ks].x); hv.y = bf16x2_to_f16x2(xr[ks].y);
-      hv.z = bf16x2_to_f16x2(xr[ks].z); hv.w = bf16x2_to_f16x2(xr[ks].w);
-      *reinterpret_cast<uint4*>(rowp + (((2 * ks + g) ^ swz<D>(row)) * 16)) = hv;
-    }
-  }
-  // The scaled fp16 du of block slot (0..3) of the parked tile, as du_to_dx packs it: lane (t,g) holds features
-  // g*LOC .. g*LOC + LOC-1 of token t.
-  static __device__ __forceinline__ void park_du(const uint32_t (&dub)[LOC / 2], float blk_its, char* sU, float* sIts, int slot, int lane) {
-    const int row = 32 * slot + lane % 32, g = lane / 32;
-    char* rowp = sU + row * RSU;
-#pragma unroll
-    for (int c = 0; c < LOC / 8; ++c) {
-      uint4 v; v.x = dub[4 * c]; v.y = dub[4 * c + 1]; v.z = dub[4 * c + 2]; v.w = dub[4 * c + 3];
-      *reinterpret_cast<uint4*>(rowp + (((g * (LOC / 8) + c) ^ swz<HALF>(row)) * 16)) = v;
-    }
-    if (lane == 0) sIts[slot] = blk_its;
   }
   // lane: pass opaque_lane() from inside the tile loop: the read offsets are then worked out per tile (a few
   // integer operations) instead of being held in registers, or spilled, across the whole loop
@@ -477,44 +396,25 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     const uint16_t* qb = q + head_base(rw, bh, H);
     const uint16_t* dob = dout + head_base(rw, bh, H);
     uint16_t* dqb = dq + head_base(rw, bh, H);
-    const int prow = 16 * w + lane % 16;
     uint4 xq[K::KS], xr[K::KS], dor[K::KS];
     const float zero = opaque_zero_scalar();
-    const TileRows<D> qrows(qb, rw.sn, n, prow, ql), drows(dob, rw.sn, n, prow, ql);
-    qrows.load(xq, p);
+    const LoadRows16<D> qrows(qb, rw.sn, n, lane), drows(dob, rw.sn, n, lane);
+    qrows.load(xq, p * kTile + 16 * w);
     // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
     // for the first tile too, would be a wait for the previous tile's stores
-#pragma unroll
-    for (int ks = 0; ks < K::KS; ++ks) asm volatile("" : "+v"(xq[ks].x), "+v"(xq[ks].y), "+v"(xq[ks].z), "+v"(xq[ks].w));
+    qrows.arrived(xq);
     for (int tile = p; tile < ntile; tile += P) {
-      const int t = tile * kTile + prow;
-      const bool valid = t < n;
-      drows.load(dor, tile);
+      const int t0 = tile * kTile + 16 * w;
+      const bool valid = t0 + lane % 16 < n;
+      drows.load(dor, t0);
       f32x4 u[K::UB];
-#pragma unroll
-      for (int mb = 0; mb < K::UB; ++mb) u[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const uint4* wa = sWA + lane + opaque_zero();
-      pipelined_operands<K::KS * K::UB, QAHEAD>([&](int i) { return wa[i * 64]; },
-                                                [&](int i, uint4 a) { u[i % K::UB] = mfma_bf16_16(a, xq[i / K::UB], u[i % K::UB]); });
+      project16<D, QAHEAD>(xq, sWA, lane, u);
       if constexpr (DW) {
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) xr[ks] = xq[ks];
       }
-      // phi up to its normalisers ip, im, which go into the factors of what is linear in phi
-      float ep[K::FL], em[K::FL];
-      float mx = u[0][0], mn = -u[0][0];
-#pragma unroll
-      for (int j = 0; j < K::FL; ++j) { mx = fmaxf(mx, u[j / 4][j % 4]); mn = fmaxf(mn, -u[j / 4][j % 4]); }
-      quad2<MaxOp>(mx, mn);
-      float ip = 0.f, im = 0.f;
-#pragma unroll
-      for (int j = 0; j < K::FL; ++j) {
-        ep[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], kLog2e, -mx * kLog2e));
-        em[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], -kLog2e, -mn * kLog2e));
-        ip += ep[j]; im += em[j];
-      }
-      quad2<SumOp>(ip, im);
-      ip = __builtin_amdgcn_rcpf(ip); im = __builtin_amdgcn_rcpf(im);
+      float ep[K::FL], em[K::FL], ip, im;
+      softmax16<D>(u, ep, em, ip, im);
       // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that
       float dmax, stok;
       uint4 bq[K::KS];
@@ -631,47 +531,19 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
       // The next tile's rows go out before the dq stores: loads and stores retire in order, and a wait for a load issued behind
       // the stores would wait for the stores as well.
-      qrows.load(xq, tile + P);
-      // dx = du W~^T, tokens on the accumulator rows; du enters scaled by one power of two for the wavefront's tokens
+      qrows.load(xq, t0 + P * kTile);
       uint32_t dub[K::FL / 2];
       float blk_its;
       {
-        float m = 0.f;
-#pragma unroll
-        for (int j = 0; j < K::FL; ++j) m = fmaxf(m, fabsf(du[j]));
-        m = row_max_mag(quad<MagOp>(valid ? m : 0.f));
-        const float pw2 = pow2_normaliser(m), ts = valid ? pw2 : 0.f;
-#pragma unroll
-        for (int j = 0; j < K::FL / 2; ++j) dub[j] = mul_pack_f16x2(du[2 * j], du[2 * j + 1], ts, zero);
-        const float its = __builtin_amdgcn_rcpf(pw2);      // exact: a power of two
-        blk_its = m > 0.f ? its : 0.f;
         f32x4 xa[K::MB];
-#pragma unroll
-        for (int mb = 0; mb < K::MB; ++mb) xa[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const uint4* wb = sWB + lane + opaque_zero();
-        pipelined_operands<K::DK * K::MB, QAHEAD>(
-            [&](int i) { return wb[i * 64]; },
-            [&](int i, uint4 b) {
-              const uint32_t* a = dub + 4 * (i / K::MB);
-              xa[i % K::MB] = mfma_f16_16(make_uint4(a[0], a[1], a[2], a[3]), b, xa[i % K::MB]);
-            });
-        store_token_rows16<D, STREAM>(dqb, rw.sn, tile * kTile + 16 * w, n, lane, xa, its);
+        float its;
+        du_to_dx16<D, QAHEAD>(du, sWB, lane, valid, zero, xa, its, dub, blk_its);
+        const float none[K::MB] = {};
+        store_token_rows16<D, STREAM, false>(dqb, rw.sn, t0, n, lane, xa, its, none);
       }
       if constexpr (DW) {
         __syncthreads();                                 // dS has read the tile's phi
-        const unsigned lz = opaque_lane(lane);
-        const int row = 16 * w + lz % 16, qz = lz / 16;
-        char* rowp = sPhi + row * RS;
-#pragma unroll
-        for (int ks = 0; ks < K::KS; ++ks)
-          *reinterpret_cast<uint4*>(rowp + (((4 * ks + qz) ^ swz<D>(lz % 16)) * 16)) =
-              make_uint4(bf16x2_to_f16x2(xr[ks].x), bf16x2_to_f16x2(xr[ks].y), bf16x2_to_f16x2(xr[ks].z), bf16x2_to_f16x2(xr[ks].w));
-        char* urow = sDU + row * DWT::RSU;
-#pragma unroll
-        for (int c = 0; c < K::DK; ++c)
-          *reinterpret_cast<uint4*>(urow + (((qz * K::DK + c) ^ swz<C::HALF>(lz % 16)) * 16)) =
-              make_uint4(dub[4 * c], dub[4 * c + 1], dub[4 * c + 2], dub[4 * c + 3]);
-        if (lane == 0) sRed[8 + w] = blk_its;
+        park_dw16<D>(xr, dub, blk_its, sPhi, sDU, sRed + 8, w, lane);
         __syncthreads();
       }
     }
@@ -798,182 +670,160 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 }
 
 // ---- key side ----------------------------------------------------------------------------
-constexpr int NTK = 512;     // 8 wavefronts, one workgroup per compute unit
-// Operand lookahead of the key-side MFMA phases.  With two wavefronts per SIMD the other wavefront
-// hides the LDS latency and registers are what is short: reading each operand right before its
-// MFMA (0) measured 101.5 us, one ahead 102.9, three ahead 106.7, the compiler's own order 105.
-constexpr int KAHEAD = 0;
+// LDS operands of the MFMA phases are requested KAHEAD MFMAs before their use.
+constexpr int KAHEAD = 3;
+// One workgroup per compute unit, 12 wavefronts; 8 at width 64 without dW~, where the rows are what is waited for (12 or 16 wavefronts 47.4 us at 24 heads x
+// 20000, 8: 46.2, 8 of 32 tokens: 47.2).
+template <int D, bool DW>
+constexpr int kKeyThreads = D == 64 && !DW ? 512 : 768;
 
-// DW: dW~_k is accumulated here as well (DwTile).  The eight wavefronts then walk their blocks in step: after each
-// round of eight blocks the wavefronts 0-3 park their k rows and du, all eight contract over those
-// 128 tokens (one 32 x 32 block of dW~_k each), then the same for the blocks of the wavefronts 4-7.  The k rows stay in 32 registers from the
-// projection on (256 in all, 3 spilled with CENTRE): read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute
-// units passes, and the kernel is bound by its rows: 117 us, now 105 (12 heads x 32760 x 128), 211 / 192 (40 x 20000), 40.3 / 37.9 (centred, 12 x
-// 8190), 25.4 / 23.2 (7 x 20000 x 64).
+// Every wavefront takes blocks of 16 tokens.  DW: dW~_k is accumulated here as well (DwTile): wavefronts 0-7 walk 128-token tiles in step and park their
+// k rows (kept in registers: read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute
+// units passes) and du, and wavefronts 8-11 contract those over the tokens while the next tile is under way.
 // STREAM: dv is stored non-temporally, as dk always is (stream_gradients).
+// Eight wavefronts of 32 tokens, two to a SIMD, filled 40 % of its vector issue: 107 us, now 87 (12 heads x 32760 x 128 with dW~; 403 MB of rows, 4.6
+// TB/s), in [B,n,H,d] 118 / 90, centred 12 x 8190 36 / 31, 12 x 1000 16.1 / 13.5.
 template <int D, bool STREAM, bool CENTRE, bool DW>
-__global__ __launch_bounds__(NTK) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+__global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                     const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
                                                     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                     float* __restrict__ dw_part,
                                                     const float* __restrict__ vbar, const float* __restrict__ cs_part,
                                                     int H, int n, int P, Rows rw) {
-  using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  using G = GradLayout<D>;
-  constexpr int NW = NTK / 64;
-  constexpr int SA_IMG = L::KS * L::MB * 64;
-  constexpr int WB_IMG = (C::LOC / 8) * L::MB * 64;
-  using DWT = DwTile<D, NW>;
+  using K = Tok16<D>;
+  constexpr int NTK = kKeyThreads<D, DW>, NW = NTK / 64, NTOK = DW ? kTile / 16 : NW;
+  using DWT = DwTile<D, NW - kTile / 16, 16>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
-  uint4* sVA = sWA + C::W_IMG;             // image of dS^T for dv (contraction over features)
-  uint4* sGA = sVA + SA_IMG;               // image of dS for g (contraction over channels)
-  uint4* sWB = sGA + G::IMG;
-  float* sZ = reinterpret_cast<float*>(sWB + WB_IMG);   // [D] dz, unscaled
-  float* sRed = sZ + D;                                 // [8]: DW: 0..3 the parked du blocks' inverse scales
-  float* sRow = sRed + 8;                               // [D] constant row of dv, then the scratch of the prologue
-  char* sX = reinterpret_cast<char*>(sRow + D);         // DW: [kTile][D] fp16, k rows of four blocks
+  uint4* sVA = sWA + K::W_IMG;             // image of dS for dv (contraction over features)
+  uint4* sGA = sVA + K::A_IMG;             // image of dS for g (contraction over channels)
+  uint4* sWB = sGA + K::G_IMG;
+  float* sZ = reinterpret_cast<float*>(sWB + K::T_IMG); // [D] dz, unscaled
+  float* sIts = sZ + D;                                 // [8]: DW: the parked du blocks' inverse scales
+  float* sRow = sIts + 8;                               // [D] constant row of dv, then the scratch of the prologue
+  char* sX = reinterpret_cast<char*>(sRow + D);         // DW: [kTile][D] fp16, a tile's k rows
   char* sU = sX + kTile * D * 2;                        // DW: [kTile][D/2] fp16, their du
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32;
   const int bh = blockIdx.y, h = bh % H;
-  const uint16_t* kb = k + head_base(rw, bh, H);
-  const uint16_t* vb = v + head_base(rw, bh, H);
-  uint16_t* dkb = dk + head_base(rw, bh, H);
-  uint16_t* dvb = dv + head_base(rw, bh, H);
+  const uint16_t* wkh = wk + (size_t)h * D * K::HALF;
 
-  build_w_image<D, NTK>(wk + (size_t)h * D * C::HALF, sWA, tid);
-  build_w_image_t<D, NTK>(wk + (size_t)h * D * C::HALF, sWB, tid);
+  build_w_image16<D, NTK>(wkh, sWA, tid);
+  build_w_image_t16<D, NTK>(wkh, sWB, tid);
   // sZ: dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the features)
   const float scale = build_key_state<D, NTK, CENTRE>(dstate + (size_t)bh * (D + 1) * D, sVA, sGA, sZ, sRow, sRow + D, vbar + (size_t)bh * D,
                                                       CENTRE ? cs_part + (size_t)bh * P * (D + 8) : nullptr, P, tid);
   __syncthreads();
-  const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
-  float dv_add[L::MB];
-#pragma unroll
-  for (int mb = 0; mb < L::MB; ++mb) dv_add[mb] = CENTRE ? sRow[L::MB * (lane % 32) + mb] : 0.f;
 
-  const int nblk = (n + 31) / 32;
-  const int stride = gridDim.x * NW;
-  uint4 xk[C::UK], vr[D / 16];
-  auto load_k = [&](int b) {
-    const int t = b * 32 + (lane % 32);
-    const int tc = t < n ? t : (n - 1);
-    const uint4* row = reinterpret_cast<const uint4*>(kb + (size_t)tc * rw.sn);
+  const int step = 16 * NTOK * gridDim.x;
+  if (w < NTOK) {
+    const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
+    const int ql = lane / 16;
+    uint16_t* dkb = dk + head_base(rw, bh, H);
+    uint16_t* dvb = dv + head_base(rw, bh, H);
+    const float zero = opaque_zero_scalar();
+    const LoadRows16<D> krows(k + head_base(rw, bh, H), rw.sn, n, lane), vrows(v + head_base(rw, bh, H), rw.sn, n, lane);
+    float dv_add[K::MB];
 #pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) xk[ks] = row[2 * ks + g];
-  };
-  auto load_v = [&](int b) {
-    const int t = b * 32 + (lane % 32);
-    const int tc = t < n ? t : (n - 1);
-    const uint4* vrow = reinterpret_cast<const uint4*>(vb + (size_t)tc * rw.sn);
-#pragma unroll
-    for (int i = 0; i < D / 16; ++i) vr[i] = vrow[2 * i + g];
-  };
-  DWT dwt;
-  if constexpr (DW) dwt.init(w);
-  // DW: every wavefront of the workgroup makes the same number of rounds (there are barriers inside); a wavefront
-  // whose block does not exist works on tokens past n: its loads repeat row n - 1, its du is zero, its stores are
-  // out of bounds
-  int b = blockIdx.x * NW + w;
-  if (DW || b < nblk) load_k(b);
-  for (int b0 = blockIdx.x * NW; DW ? b0 < nblk : b < nblk; b0 += stride, b += stride) {
-    const int t = b * 32 + (lane % 32);
-    const bool valid = t < n;
-    load_v(b);                                        // wanted after the projection, the softmax and dv
-    f32x16 u[C::UM];
-    project<D>(xk, sWA, lane, u);
-    uint4 xr[C::UK];
-    if constexpr (DW) {
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) xr[ks] = xk[ks];
-    }
-    if constexpr (!DW) {
-      if (b + stride < nblk) load_k(b + stride);      // next block's k flies during this one
-    }
-    float pp[C::LOC], pm[C::LOC];
-    uint32_t pk[C::NPK];
-    softmax_full<D>(u, pp, pm, pk);
-
-    // dv = phi(k) dS, tokens on the accumulator rows
-    {
-      f32x16 va[L::MB];
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) va[mb][r] = 0.f;
-      const uint4* sva = sVA + lane + opaque_zero();
-      pipelined_operands<L::KS * L::MB, KAHEAD>(
-          [&](int i) { return sva[i * 64]; },
-          [&](int i, uint4 b) {
-            const int ks = i / L::MB, mb = i % L::MB;
-            uint4 aq; aq.x = pk[4 * ks]; aq.y = pk[4 * ks + 1]; aq.z = pk[4 * ks + 2]; aq.w = pk[4 * ks + 3];
-            va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(aq), as_f16x8(b), va[mb], 0, 0, 0);
-          });
-      store_token_rows<D, STREAM>(dvb, rw.sn, b * 32, n, lane, va, inv_scale, dv_add);
-    }
-
-    // g = v dS^T + dz, rows laid out like phi
-    float gp[C::LOC], gm[C::LOC];
-    {
-      f32x16 ga[G::GM];
-#pragma unroll
-      for (int mb = 0; mb < G::GM; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
-      const uint4* sga = sGA + lane + opaque_zero();
-      pipelined_operands<G::KS * G::GM, KAHEAD>(
-          [&](int i) { return sga[i * 64]; },
-          [&](int i, uint4 a) {
-            const int ks = i / G::GM, mb = i % G::GM;
-            uint4 bq;
-            bq.x = bf16x2_to_f16x2(vr[ks].x); bq.y = bf16x2_to_f16x2(vr[ks].y);
-            bq.z = bf16x2_to_f16x2(vr[ks].z); bq.w = bf16x2_to_f16x2(vr[ks].w);
-            ga[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(bq), ga[mb], 0, 0, 0);
-          });
-#pragma unroll
-      for (int mb = 0; mb < G::GM; ++mb) {
-        const int f0 = (mb < G::GM / 2 ? 0 : C::HALF) + g * C::LOC + 16 * (mb % (G::GM / 2));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float val = fmaf(ga[mb][r], inv_scale, sZ[f0 + r]);
-          if (mb < G::GM / 2) gp[16 * mb + r] = val; else gm[16 * (mb - G::GM / 2) + r] = val;
-        }
-      }
-    }
-    float du[C::LOC];
-    phi_jacobian<D>(gp, gm, pp, pm, du);
-    {
-      f32x16 xa[L::MB];
-      float its;
-      uint32_t dub[C::LOC / 2];
-      float blk_its = 0.f;
-      du_to_dx<D, KAHEAD>(du, sWB, lane, valid, xa, its, dub, blk_its);
-      // the next block's k rows (with the dW~ accumulator resident they do not fit beside the middle of the chain), before the dk
-      // stores: a wait for them must not wait for the stores
-      if constexpr (DW) load_k(b + stride);
-      store_token_rows<D, true>(dkb, rw.sn, b * 32, n, lane, xa, its);
+    for (int mb = 0; mb < K::MB; ++mb) dv_add[mb] = CENTRE ? sRow[K::MB * (lane % 16) + mb] : 0.f;
+    uint4 xk[K::KS], xr[K::KS], vr[K::KS];
+    int t0 = 16 * (blockIdx.x * NTOK + w);
+    krows.load(xk, t0);
+    // DW: every token wavefront makes the same number of rounds (there are barriers inside); one whose block does not exist works on zeros
+    for (; (DW ? t0 - 16 * w : t0) < n; t0 += step) {
+      const bool valid = t0 + lane % 16 < n;
+      vrows.load(vr, t0);                               // wanted after the projection, the softmax and dv
+      f32x4 u[K::UB];
+      project16<D, KAHEAD>(xk, sWA, lane, u);
       if constexpr (DW) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          __syncthreads();                             // the tiles' previous readers are done
-          if (w / 4 == half) {
-            // (addresses worked out here, from a lane index the optimiser cannot hoist: held across the loop they end up
-            // in scratch memory, and a wait for a scratch load also waits for the dk stores just issued)
-            const int lz = lane + opaque_zero();
-            DWT::park_x(xr, sX, w % 4, lz);
-            DWT::park_du(dub, blk_its, sU, sRed, w % 4, lz);
+        for (int ks = 0; ks < K::KS; ++ks) xr[ks] = xk[ks];
+      } else {
+        krows.load(xk, t0 + step);                      // the next block's k flies during this one
+      }
+      float ep[K::FL], em[K::FL], ip, im;
+      softmax16<D>(u, ep, em, ip, im);
+
+      // dv = phi(k) dS, tokens on the accumulator rows
+      {
+        uint32_t pk[K::FL];
+#pragma unroll
+        for (int j = 0; j < K::FL / 2; ++j) {
+          pk[j] = mul_pack_f16x2(ep[2 * j], ep[2 * j + 1], ip, zero);
+          pk[K::FL / 2 + j] = mul_pack_f16x2(em[2 * j], em[2 * j + 1], im, zero);
+        }
+        f32x4 va[K::MB];
+#pragma unroll
+        for (int mb = 0; mb < K::MB; ++mb) va[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const uint4* sva = sVA + lane + opaque_zero();
+        pipelined_operands<2 * K::DK * K::MB, KAHEAD>(
+            [&](int i) { return sva[i * 64]; },
+            [&](int i, uint4 b) {
+              const uint32_t* a = pk + 4 * (i / K::MB);
+              va[i % K::MB] = mfma_f16_16(make_uint4(a[0], a[1], a[2], a[3]), b, va[i % K::MB]);
+            });
+        store_token_rows16<D, STREAM, CENTRE>(dvb, rw.sn, t0, n, lane, va, inv_scale, dv_add);
+      }
+
+      // g = v dS^T + dz, rows laid out like phi, and its sums against phi
+      float gp[K::FL], gm[K::FL], cp = 0.f, cm = 0.f;
+      {
+        uint4 bq[K::KS];
+#pragma unroll
+        for (int ks = 0; ks < K::KS; ++ks)
+          bq[ks] = make_uint4(bf16x2_to_f16x2(vr[ks].x), bf16x2_to_f16x2(vr[ks].y), bf16x2_to_f16x2(vr[ks].z), bf16x2_to_f16x2(vr[ks].w));
+        f32x4 ga[K::GB];
+#pragma unroll
+        for (int mb = 0; mb < K::GB; ++mb) ga[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int gl = grad16_lane<D>(opaque_lane(lane));
+        pipelined_operands<K::KS * K::GB, KAHEAD>([&](int i) { return sGA[i * 64 + (gl ^ (4 * (i / K::GB)))]; },
+                                                  [&](int i, uint4 a) { ga[i % K::GB] = mfma_f16_16(a, bq[i / K::GB], ga[i % K::GB]); });
+        const int z_at = ql * K::FL / 4 + opaque_zero();
+#pragma unroll
+        for (int i4 = 0; i4 < K::FL / 4; ++i4) {
+          const float4 vp = reinterpret_cast<const float4*>(sZ)[z_at + i4], vm = reinterpret_cast<const float4*>(sZ)[z_at + K::HALF / 4 + i4];
+          const float zp[4] = {vp.x, vp.y, vp.z, vp.w}, zm[4] = {vm.x, vm.y, vm.z, vm.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int j = 4 * i4 + i;
+            gp[j] = fmaf(ga[i4][i], inv_scale, zp[i]);
+            gm[j] = fmaf(ga[K::GB / 2 + i4][i], inv_scale, zm[i]);
+            cp = fmaf(gp[j], ep[j], cp); cm = fmaf(gm[j], em[j], cm);
           }
-          __syncthreads();
-          dwt.contract(sX, sU, sRed, opaque_lane(lane));
         }
       }
+      quad2<SumOp>(cp, cm);
+      cp *= ip * ip; cm *= im * im;
+      float du[K::FL];
+#pragma unroll
+      for (int j = 0; j < K::FL; ++j) du[j] = ep[j] * fmaf(gp[j], ip, -cp) - em[j] * fmaf(gm[j], im, -cm);
+      uint32_t dub[K::FL / 2];
+      float blk_its;
+      {
+        f32x4 xa[K::MB];
+        float its;
+        du_to_dx16<D, KAHEAD>(du, sWB, lane, valid, zero, xa, its, dub, blk_its);
+        // DW: the next block's k rows, before the dk stores: a wait for them must not wait for the stores
+        if constexpr (DW) krows.load(xk, t0 + step);
+        store_token_rows16<D, true, false>(dkb, rw.sn, t0, n, lane, xa, its, dv_add);
+      }
+      if constexpr (DW) {
+        __syncthreads();                                // the tiles' previous readers are done
+        park_dw16<D>(xr, dub, blk_its, sX, sU, sIts, w, lane);
+        __syncthreads();
+      }
     }
+  } else if constexpr (DW) {
+    DWT dwt;
+    dwt.init(w - NTOK);
+    for (int t0 = 16 * NTOK * blockIdx.x; t0 < n; t0 += step) {
+      __syncthreads();
+      __syncthreads();
+      dwt.contract(sX, sU, sIts, opaque_lane(lane));
+    }
+    dwt.store(dw_part + ((size_t)bh * gridDim.x + blockIdx.x) * (size_t)D * K::HALF, lane);
   }
-  if constexpr (DW) dwt.store(dw_part + ((size_t)bh * gridDim.x + blockIdx.x) * (size_t)D * C::HALF, lane);
 }
 
 template <int D, bool DW>
@@ -984,16 +834,15 @@ constexpr size_t q_smem() {
 template <int D, bool DW>
 constexpr size_t k_smem() {
   // the prologue's scratch lies where the DW tiles are afterwards
-  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + NTK / 64 + 4) * sizeof(float);
-  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, NTK / 64>::DU_BYTES : 0;
-  return sizeof(uint4) * (Cfg<D>::W_IMG + ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64 + GradLayout<D>::IMG
-                          + (Cfg<D>::LOC / 8) * ApplyLayout<D>::MB * 64) + (2 * D + 8) * sizeof(float)
+  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + kKeyThreads<D, DW> / 64 + 4) * sizeof(float);
+  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, 4, 16>::DU_BYTES : 0;
+  return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::A_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG) + (2 * D + 8) * sizeof(float)
        + (scratch > tiles ? scratch : tiles);
 }
 template <int D, bool CENTRE, bool STREAM>
 hipError_t run_bwd_as(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  // dW~ partials: [BH][P] blocks of the query side, then [BH][KP] of the key side
+  // dW~ partials: [BH][P] blocks of the query side, then as many of the key side
   const size_t side_elems = (size_t)p.BH * p.P * D * (D / 2);
   auto launch_q = [&](auto kernel) -> hipError_t {
     const size_t smem = a.dwq ? q_smem<D, true>() : q_smem<D, false>();
@@ -1012,18 +861,23 @@ hipError_t run_bwd_as(const BwdArgs& a, const Plan& p, hipStream_t s) {
     e = a.dwq ? launch_q(KernelTag<bwd_q_kernel<D, STREAM, false, false, CENTRE, true>>{}) : launch_q(KernelTag<bwd_q_kernel<D, STREAM, false, false, CENTRE, false>>{});
   if (e != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
-  auto launch_k = [&](auto kernel, size_t smem) -> hipError_t {
+  // with dW~_k a workgroup takes 128-token tiles, and the partials are laid out like the query side's; else 16 tokens a wavefront
+  constexpr int UNIT = kKeyThreads<D, false> / 4;
+  const int units = (p.n + UNIT - 1) / UNIT, per_head = p.BH < kCUs ? kCUs / p.BH : 1;
+  const int groups = a.dwk ? p.P : units < per_head ? units : per_head;
+  auto launch_k = [&](auto kernel, int threads, size_t smem) -> hipError_t {
     hipError_t e2 = set_smem_once<decltype(kernel)::value>(smem);
     if (e2 != hipSuccess) return e2;
-    decltype(kernel)::value<<<dim3(p.KP, p.BH), NTK, smem, s>>>(
+    decltype(kernel)::value<<<dim3(groups, p.BH), threads, smem, s>>>(
         (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.wk, a.dstate, (uint16_t*)a.dk, (uint16_t*)a.dv,
         a.dw_part + side_elems, a.vbar, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
-  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, true>>{}, k_smem<D, true>()) : launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, false>>{}, k_smem<D, false>());
+  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, true>>{}, kKeyThreads<D, true>, k_smem<D, true>()) :
+      launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, false>>{}, kKeyThreads<D, false>, k_smem<D, false>());
   if (e != hipSuccess) return e;
   if (a.dwq || a.dwk) {
-    if ((e = launch_dw_reduce2(a.dwq ? a.dw_part : nullptr, a.dwq, p.P, a.dwk ? a.dw_part + side_elems : nullptr, a.dwk, p.KP, p, s)) != hipSuccess) return e;
+    if ((e = launch_dw_reduce2(a.dwq ? a.dw_part : nullptr, a.dwq, p.P, a.dwk ? a.dw_part + side_elems : nullptr, a.dwk, groups, p, s)) != hipSuccess) return e;
   }
   return hipSuccess;
 }

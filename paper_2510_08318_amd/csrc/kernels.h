@@ -178,7 +178,7 @@ struct Plan {
   size_t off_state;       // fp32 [BH][(d+1)*d]   (used when the caller gave no state buffer)
   size_t fwd_bytes;       // end of the two regions above: all the scratch a forward call touches
   // backward only
-  int KP;                 // workgroups per (b,h) of the passes with 8 wavefronts, each on its own 32-token blocks
+  int KP;                 // workgroups per (b,h) of the ReLU key side: 8 wavefronts, each on its own 32-token blocks
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
   size_t off_centre;      // bf16 backward: fp32 [BH][3][d] (mean value row vbar; the other two rows unused), then
                           // [BH][P][d+8] per-workgroup column sums of dO/den (d) and the sum of -delta/den (1)

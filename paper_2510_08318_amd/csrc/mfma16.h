@@ -22,7 +22,7 @@ struct Tok16 {
   static constexpr int GB = D / 16;       // row blocks over the D features of phi
   static constexpr int DK = FL / 8;       // k-steps over the d/2 pre-softmax features (element (q, e) of k-step ks: feature q*FL + 8*ks + e)
   static constexpr int MB = D / 16;       // column blocks over the channels (column c of block mb: channel MB*c + mb)
-  static constexpr int W_IMG = KS * UB * 64, G_IMG = KS * GB * 64, T_IMG = DK * MB * 64;      // uint4 entries of the images
+  static constexpr int W_IMG = KS * UB * 64, G_IMG = KS * GB * 64, T_IMG = DK * MB * 64, A_IMG = 2 * DK * MB * 64;      // uint4 entries of the images
   __device__ static constexpr int feature(int mb, int m) { return (m / 4) * FL + 4 * mb + m % 4; }
 };
 
@@ -85,6 +85,22 @@ __device__ __forceinline__ void write_grad_image16(const StateRegs<D, NTHREADS>&
   }
 }
 
+// B operands of Y = phi S, tokens on the accumulator rows: entry (ks, mb, lane = (c, q)) holds scale * S[f + e][MB*c + mb], f = q*FL + 8*(ks % DK)
+// of the + half for ks < DK, of the - half otherwise.
+template <int D, int NTHREADS>
+__device__ __forceinline__ void write_apply_image16(const StateRegs<D, NTHREADS>& S, uint4* img, float sc) {
+  using K = Tok16<D>;
+  if (!S.active) return;
+  const int f = 8 * S.fo, fl = f % K::HALF, q = fl / K::FL, ks = f / K::HALF * K::DK + fl % K::FL / 8;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int ch = 4 * S.cq + i;
+    img[(ks * K::MB + ch % K::MB) * 64 + 16 * q + ch / K::MB] =
+        make_uint4(pack_f16x2(sc * S.v[0][i], sc * S.v[1][i]), pack_f16x2(sc * S.v[2][i], sc * S.v[3][i]),
+                   pack_f16x2(sc * S.v[4][i], sc * S.v[5][i]), pack_f16x2(sc * S.v[6][i], sc * S.v[7][i]));
+  }
+}
+
 // The lane index as a value that the optimiser cannot hoist out of a loop, in a range that it knows (addresses made from it are worked out where
 // they are used instead of being held, or spilled, across the loop).
 __device__ __forceinline__ unsigned opaque_lane(int lane) { return (unsigned)(lane + opaque_zero()) & 63u; }
@@ -107,23 +123,28 @@ __device__ __forceinline__ uint32_t mul_pack_f16x2(uint32_t ab, float s, float c
   return __builtin_bit_cast(uint32_t, r);
 }
 
-// Rows of a tile as operands: lane (t, q) reads the 16-byte chunks 4ks + q of row `row` (0 .. kTile-1) of the tile.  Bounded buffer loads: the
-// address is one register that never changes, and rows past n read as zeros.
+// The 16 rows from token t0 of a head of n tokens as operands: lane (t, q) reads the 16-byte chunks 4ks + q of row t0 + t.  Bounded buffer loads: the
+// address is one register that never changes, and rows past n read as zeros.  All arguments but the lane are uniform.
 template <int D>
-struct TileRows {
+struct LoadRows16 {
   uint32_t at, pitch;
   const char* base;
   int n;
-  __device__ __forceinline__ TileRows(const uint16_t* head, size_t sn, int n_, int row, int q) : base((const char*)head), n(n_) {
+  __device__ __forceinline__ LoadRows16(const uint16_t* head, size_t sn, int n_, int lane) : base((const char*)head), n(n_) {
     pitch = (uint32_t)sn * 2;
-    at = (uint32_t)row * pitch + 16 * q;
+    at = (uint32_t)(lane % 16) * pitch + 16 * (lane / 16);
   }
-  __device__ __forceinline__ void load(uint4 (&x)[D / 32], int tile) const {
-    const int left = n - tile * kTile < kTile ? n - tile * kTile : kTile;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (size_t)tile * kTile * pitch, 0,
+  __device__ __forceinline__ void load(uint4 (&x)[D / 32], int t0) const {
+    const int left = n - t0 < 16 ? n - t0 : 16;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (size_t)t0 * pitch, 0,
                                                                        left > 0 ? (uint32_t)left * pitch : 0, 0x00020000);
 #pragma unroll
     for (int ks = 0; ks < D / 32; ++ks) x[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, at + 64 * ks, 0, 0));
+  }
+  // wait for the rows here (see where it is used)
+  static __device__ __forceinline__ void arrived(uint4 (&x)[D / 32]) {
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) asm volatile("" : "+v"(x[ks].x), "+v"(x[ks].y), "+v"(x[ks].z), "+v"(x[ks].w));
   }
 };
 
@@ -201,19 +222,98 @@ struct TokenRows16 {
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, off, 0, aux);
   }
 };
-// acc[mb][r] of lane (c, q): token 4q + r, channel MB*c + mb  ->  mul * acc as bf16 rows of base
-template <int D, bool STREAM>
-__device__ __forceinline__ void store_token_rows16(uint16_t* base, size_t sn, int t0, int n, int lane, const f32x4 (&acc)[D / 16], float mul) {
+// acc[mb][r] of lane (c, q): token 4q + r, channel MB*c + mb  ->  mul * acc (ADD: + add[mb]) as bf16 rows of base
+template <int D, bool STREAM, bool ADD>
+__device__ __forceinline__ void store_token_rows16(uint16_t* base, size_t sn, int t0, int n, int lane, const f32x4 (&acc)[D / 16], float mul,
+                                                   const float (&add)[D / 16]) {
   constexpr int MB = D / 16;
   const TokenRows16<2 * MB> rows(base, sn * 2, t0, n, lane);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     uint32_t w[MB / 2];
 #pragma unroll
-    for (int i = 0; i < MB / 2; ++i) w[i] = pack_bf16x2(acc[2 * i][r] * mul, acc[2 * i + 1][r] * mul);
+    for (int i = 0; i < MB / 2; ++i)
+      w[i] = ADD ? pack_bf16x2(fmaf(acc[2 * i][r], mul, add[2 * i]), fmaf(acc[2 * i + 1][r], mul, add[2 * i + 1]))
+                 : pack_bf16x2(acc[2 * i][r] * mul, acc[2 * i + 1][r] * mul);
     if constexpr (MB == 8) rows.template store<STREAM>(r, make_uint4(w[0], w[1], w[2], w[3]));
     else rows.template store<STREAM>(r, make_uint2(w[0], w[1]));
   }
+}
+
+// First half of Eq. 5 for 16 tokens: u[j / 4][j % 4] = pre-softmax feature q*FL + j of the lane's token.  x is dead afterwards.
+template <int D, int AHEAD>
+__device__ __forceinline__ void project16(const uint4 (&x)[D / 32], const uint4* sWA, int lane, f32x4 (&u)[Tok16<D>::UB]) {
+  using K = Tok16<D>;
+#pragma unroll
+  for (int mb = 0; mb < K::UB; ++mb) u[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint4* wa = sWA + lane + opaque_zero();
+  pipelined_operands<K::KS * K::UB, AHEAD>([&](int i) { return wa[i * 64]; },
+                                           [&](int i, uint4 a) { u[i % K::UB] = mfma_bf16_16(a, x[i / K::UB], u[i % K::UB]); });
+}
+
+// Second half of Eq. 5, up to the normalisers ip, im, which go into the factors of what is linear in phi.
+template <int D>
+__device__ __forceinline__ void softmax16(const f32x4 (&u)[Tok16<D>::UB], float (&ep)[D / 8], float (&em)[D / 8], float& ip, float& im) {
+  float mx = u[0][0], mn = -u[0][0];
+#pragma unroll
+  for (int j = 0; j < D / 8; ++j) { mx = fmaxf(mx, u[j / 4][j % 4]); mn = fmaxf(mn, -u[j / 4][j % 4]); }
+  quad2<MaxOp>(mx, mn);
+  ip = im = 0.f;
+#pragma unroll
+  for (int j = 0; j < D / 8; ++j) {
+    ep[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], kLog2e, -mx * kLog2e));
+    em[j] = __builtin_amdgcn_exp2f(fmaf(u[j / 4][j % 4], -kLog2e, -mn * kLog2e));
+    ip += ep[j]; im += em[j];
+  }
+  quad2<SumOp>(ip, im);
+  ip = __builtin_amdgcn_rcpf(ip); im = __builtin_amdgcn_rcpf(im);
+}
+
+// dx = du W~^T for 16 tokens, tokens on the accumulator rows: du enters as fp16, scaled by one power of two that brings the wavefront's largest into
+// [1, 2) (dub; zero for tokens that do not exist), and acc is to be multiplied by its, the inverse.  blk_its: the same, 0 where all are zero.
+template <int D, int AHEAD>
+__device__ __forceinline__ void du_to_dx16(const float (&du)[D / 8], const uint4* sWB, int lane, bool valid, float zero, f32x4 (&acc)[D / 16],
+                                           float& its, uint32_t (&dub)[D / 16], float& blk_its) {
+  using K = Tok16<D>;
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < K::FL; ++j) m = fmaxf(m, fabsf(du[j]));
+  m = row_max_mag(quad<MagOp>(valid ? m : 0.f));
+  const float s = pow2_normaliser(m), ts = valid ? s : 0.f;
+#pragma unroll
+  for (int j = 0; j < K::FL / 2; ++j) dub[j] = mul_pack_f16x2(du[2 * j], du[2 * j + 1], ts, zero);
+  its = __builtin_amdgcn_rcpf(s);      // exact: a power of two
+  blk_its = m > 0.f ? its : 0.f;
+#pragma unroll
+  for (int mb = 0; mb < K::MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint4* wb = sWB + lane + opaque_zero();
+  pipelined_operands<K::DK * K::MB, AHEAD>(
+      [&](int i) { return wb[i * 64]; },
+      [&](int i, uint4 b) {
+        const uint32_t* a = dub + 4 * (i / K::MB);
+        acc[i % K::MB] = mfma_f16_16(make_uint4(a[0], a[1], a[2], a[3]), b, acc[i % K::MB]);
+      });
+}
+
+// What the dW~ contraction reads (DwTile): the rows x as fp16 into rows 16*slot .. of the tile sX [kTile][D], du (as du_to_dx16 packs it) into sU
+// [kTile][D/2], its inverse scale into sIts[slot].
+template <int D>
+__device__ __forceinline__ void park_dw16(const uint4 (&x)[D / 32], const uint32_t (&dub)[D / 16], float blk_its, char* sX, char* sU, float* sIts,
+                                          int slot, int lane) {
+  using K = Tok16<D>;
+  const unsigned lz = opaque_lane(lane), q = lz / 16, t = lz % 16;
+  const int row = 16 * slot + (int)t;
+  char* rowp = sX + row * (D * 2);
+#pragma unroll
+  for (int ks = 0; ks < K::KS; ++ks)
+    *reinterpret_cast<uint4*>(rowp + (((4 * ks + q) ^ (unsigned)swz<D>((int)t)) * 16)) =
+        make_uint4(bf16x2_to_f16x2(x[ks].x), bf16x2_to_f16x2(x[ks].y), bf16x2_to_f16x2(x[ks].z), bf16x2_to_f16x2(x[ks].w));
+  char* urow = sU + row * D;
+#pragma unroll
+  for (int c = 0; c < K::DK; ++c)
+    *reinterpret_cast<uint4*>(urow + (((q * K::DK + c) ^ (unsigned)swz<D / 2>((int)t)) * 16)) =
+        make_uint4(dub[4 * c], dub[4 * c + 1], dub[4 * c + 2], dub[4 * c + 3]);
+  if (lane == 0) sIts[slot] = blk_its;
 }
 
 }  // namespace linattn

@@ -103,8 +103,7 @@ __device__ __forceinline__ void pipelined_operands(Load load, Use use) {
 // xb[ks] is this lane's B operand (8 channels of its token per k-step).  On return the lane holds
 // u[mb][r] = pre-softmax feature g*LOC + 16*mb + r of its token.  xb is dead afterwards, so the
 // caller can refill it with the next block while the softmax runs.
-// AHEAD > 0: the W~ operands are requested that many MFMAs ahead (pipelined_operands).
-template <int D, int AHEAD = 0>
+template <int D>
 __device__ __forceinline__ void project(const uint4 (&xb)[Cfg<D>::UK], const uint4* sWA, int lane,
                                         f32x16 (&u)[Cfg<D>::UM]) {
   using C = Cfg<D>;
@@ -113,14 +112,6 @@ __device__ __forceinline__ void project(const uint4 (&xb)[Cfg<D>::UK], const uin
 #pragma unroll
     for (int r = 0; r < 16; ++r) u[mb][r] = 0.f;
   const uint4* wa = sWA + lane + opaque_zero();
-  if constexpr (AHEAD > 0) {
-    pipelined_operands<C::UK * C::UM, AHEAD>(
-        [&](int i) { return wa[i * 64]; },
-        [&](int i, uint4 a) {
-          u[i % C::UM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(xb[i / C::UM]), u[i % C::UM], 0, 0, 0);
-        });
-    return;
-  }
 #pragma unroll
   for (int ks = 0; ks < C::UK; ++ks) {
     const bf16x8 b = as_bf16x8(xb[ks]);
@@ -183,42 +174,6 @@ __device__ __forceinline__ void softmax_pair(const f32x16 (&u)[Cfg<D>::UM], bool
 #pragma unroll
     for (int j = 0; j < C::LOC / 2; ++j) pk[half * (C::LOC / 2) + j] = pack_f16x2(e[2 * j] * inv, e[2 * j + 1] * inv);
     }
-  }
-}
-
-// Eq. 5 with the normalised values kept in fp32 as well (the backward needs them for the softmax
-// Jacobian): pp[j], pm[j] = softmax(+u), softmax(-u) of feature g*LOC + j; pk as in softmax_pair.
-template <int D>
-__device__ __forceinline__ void softmax_full(const f32x16 (&u)[Cfg<D>::UM], float (&pp)[Cfg<D>::LOC],
-                                             float (&pm)[Cfg<D>::LOC], uint32_t (&pk)[Cfg<D>::NPK]) {
-  using C = Cfg<D>;
-  float mx = u[0][0], mn = u[0][0];
-#pragma unroll
-  for (int mb = 0; mb < C::UM; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { mx = fmaxf(mx, u[mb][r]); mn = fminf(mn, u[mb][r]); }
-  float lo, hi;
-  pair32(mx, lo, hi); mx = fmaxf(lo, hi);
-  pair32(mn, lo, hi); mn = fminf(lo, hi);
-  float sp = 0.f, sm = 0.f;
-#pragma unroll
-  for (int mb = 0; mb < C::UM; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float a = __builtin_amdgcn_exp2f(fmaf(u[mb][r], kLog2e, -mx * kLog2e));
-      const float b = __builtin_amdgcn_exp2f(fmaf(u[mb][r], -kLog2e, mn * kLog2e));
-      pp[16 * mb + r] = a; pm[16 * mb + r] = b;
-      sp += a; sm += b;
-    }
-  pair32(sp, lo, hi); sp = lo + hi;
-  pair32(sm, lo, hi); sm = lo + hi;
-  const float ip = __builtin_amdgcn_rcpf(sp), im = __builtin_amdgcn_rcpf(sm);
-#pragma unroll
-  for (int j = 0; j < C::LOC; ++j) { pp[j] *= ip; pm[j] *= im; }
-#pragma unroll
-  for (int j = 0; j < C::LOC / 2; ++j) {
-    pk[j] = pack_f16x2(pp[2 * j], pp[2 * j + 1]);
-    pk[C::LOC / 2 + j] = pack_f16x2(pm[2 * j], pm[2 * j + 1]);
   }
 }
 
@@ -294,20 +249,6 @@ struct GradLayout {
     return (mb < GM / 2 ? 0 : HALF) + gg * LOC + 16 * (mb % (GM / 2)) + r;
   }
 };
-
-// W~ [D][D/2] bf16 (one head) -> LDS image (fp16, exact) of the B operands of dX = dU W~^T
-// (contraction over the d/2 pre-softmax features, tokens on the accumulator rows): entry
-// (ks, mb, lane=(c,g)) holds W~[channel_cols(mb,c)][g*LOC + 8ks + e], e = 0..7; ks < LOC/8, mb < D/32.
-template <int D, int NTHREADS>
-__device__ __forceinline__ void build_w_image_t(const uint16_t* __restrict__ w, uint4* sWB, int tid) {
-  using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  for (int idx = tid; idx < (C::LOC / 8) * L::MB * 64; idx += NTHREADS) {
-    const int lane = idx % 64, mb = (idx / 64) % L::MB, ks = idx / (64 * L::MB);
-    const uint4 r = *reinterpret_cast<const uint4*>(w + L::channel_cols(mb, lane % 32) * C::HALF + (lane / 32) * C::LOC + 8 * ks);
-    sWB[idx] = make_uint4(bf16x2_to_f16x2(r.x), bf16x2_to_f16x2(r.y), bf16x2_to_f16x2(r.z), bf16x2_to_f16x2(r.w));
-  }
-}
 
 // A state (S, dS) [D][D] fp32 of one head in the registers of a workgroup: thread tid < ITEMS holds features 8*fo .. +7 x channels
 // 4*cq .. +3, the others zeros.  Eight 16-byte loads in flight per thread, and every operand image is written from here: the statistics an image

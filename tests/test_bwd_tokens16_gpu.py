@@ -62,3 +62,17 @@ def test_gradient_that_is_not_finite(value):
     assert np.isfinite(got["dq"][0, 0][finite]).all()
     for name, r in zip(("dq", "dk", "dv"), ref):
         assert O.err_metric(got[name][:, 1:], r)[0] <= 1e-2, name
+
+
+# the key side without dW~ deals blocks of 16 tokens to 12 (width 128) or 8 (64) wavefronts, with dW~ 128-token tiles
+@pytest.mark.parametrize("wgrads", [False, True], ids=["frozen", "wgrads"])
+@pytest.mark.parametrize("n,H,d", [(1, 2, 128), (15, 2, 64), (17, 2, 128), (191, 2, 128), (193, 2, 128), (127, 2, 64), (129, 2, 64), (400, 255, 64),
+                                   (193, 300, 128)])
+def test_key_side_lengths(n, H, d, wgrads):
+    x = synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16")
+    if n == 1:        # the output does not depend on k
+        got = _run(x, False, wgrads)
+        dv = O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)[2]
+        assert O.err_metric(got["dv"], dv)[0] <= 1e-2 and np.abs(got["dk"]).max() <= 1e-2 * np.abs(dv).max()
+        return
+    _check(x, wgrads=wgrads)
