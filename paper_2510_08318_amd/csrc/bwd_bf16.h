@@ -49,16 +49,15 @@ namespace {
 
 // Query side: image of S^c, z in sZ[D]; returns the image's scale.  vbar_out: non-null in one workgroup per head.
 // scratch: FO*D + D + NTHREADS/64 floats of LDS.  Ends before the barrier that the caller needs after building its images.
+// S: the state, loaded; z: element tid < D of its row z.
 template <int D, int NTHREADS>
-__device__ __forceinline__ float build_query_state(const float* __restrict__ state, uint4* sGA, float* sZ, float* scratch,
+__device__ __forceinline__ float build_query_state(StateRegs<D, NTHREADS>& S, float z, uint4* sGA, float* sZ, float* scratch,
                                                    float* __restrict__ vbar_out, int tid) {
   using R = StateRegs<D, NTHREADS>;
-  R S;
-  S.load(state, tid);
   float* part = scratch;
-  float* vb = part + R::FO * D;                             // (read by the acc wavefronts of bwd_q_kernel as well)
+  float* vb = part + R::FO * D;                             // (bwd_q_kernel keeps it with DR)
   float* red = vb + D;
-  if (tid < D) sZ[tid] = state[D * D + tid];
+  if (tid < D) sZ[tid] = z;
   S.octet_sums(part);
   __syncthreads();
   if (tid < D) {
@@ -93,13 +92,11 @@ __device__ __forceinline__ float build_query_state(const float* __restrict__ sta
 
 // Key side: the two images of dS, the matched dz in sZ[D], the constant row of dv in sRow[D] (zero without CENTRE); returns the scale.
 // scratch: FO*D + 4*D + NTHREADS/64 + 4 floats of LDS.
+// S: dS, loaded; dz, vb_own: element tid < D of its row dz and of vbar.
 template <int D, int NTHREADS, bool CENTRE>
-__device__ __forceinline__ float build_key_state(const float* __restrict__ dstate, uint4* sVA, uint4* sGA, float* sZ, float* sRow,
-                                                 float* scratch, const float* __restrict__ vbar, const float* __restrict__ cs_part,
-                                                 int P, int tid) {
+__device__ __forceinline__ float build_key_state(StateRegs<D, NTHREADS>& S, float dz, float vb_own, uint4* sVA, uint4* sGA, float* sZ, float* sRow,
+                                                 float* scratch, const float* __restrict__ cs_part, int P, int tid) {
   using R = StateRegs<D, NTHREADS>;
-  R S;
-  S.load(dstate, tid);
   float* part = scratch;
   float* vb = part + R::FO * D;
   float* m0 = vb + D;
@@ -108,8 +105,8 @@ __device__ __forceinline__ float build_key_state(const float* __restrict__ dstat
   float* red = cB + D;                                      // [NTHREADS/64], then wsum and the two means of dz
   float* misc = red + NTHREADS / 64;
   if (tid < D) {
-    vb[tid] = vbar[tid];
-    cB[tid] = dstate[D * D + tid];
+    vb[tid] = vb_own;
+    cB[tid] = dz;
   }
   if constexpr (CENTRE) {
     // column sums and wsum of the query-side workgroups, in a fixed order
@@ -160,7 +157,7 @@ __device__ __forceinline__ float build_key_state(const float* __restrict__ dstat
     float dot = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) dot = fmaf((float)(_Float16)(scale * S.v[e][i]), vb[4 * S.cq + i], dot);
-    for (int k = R::CQ / 2; k >= 1; k >>= 1) dot += __shfl_xor(dot, k, 64);
+    dot = D == 128 ? half_wave_sum(dot) : row_sum(dot);     // over the CQ lanes that share the octet of features
     const int f = 8 * S.fo + e;
     if (S.active && S.cq == 0) sZ[f] = cB[f] - (CENTRE ? misc[f < D / 2 ? 1 : 2] : 0.f) - dot * inv;
   }
@@ -372,9 +369,18 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   const int ntile = (n + kTile - 1) / kTile;
   float dr_acc = 0.f;
 
-  build_w_image16<D, NTQ>(wq + (size_t)h * D * C::HALF, sWA, tid);
-  build_w_image_t16<D, NTQ>(wq + (size_t)h * D * C::HALF, sWB, tid);
-  const float scale = build_query_state<D, NTQ>(sb, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
+  // Everything the prologue reads is requested before any of it is waited for.  (The first rows as well: registers of the acc wavefronts are spilled.)
+  float scale;
+  {
+    StateRegs<D, NTQ> S;
+    WImages16<D, NTQ> W;
+    S.load(sb, tid);
+    const float z = sb[D * D + (tid < D ? tid : 0)];
+    W.load(wq + (size_t)h * D * C::HALF, tid);
+    __builtin_amdgcn_sched_barrier(0);
+    W.write(sWA, sWB, tid);
+    scale = build_query_state<D, NTQ>(S, z, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
+  }
   if (DR && tid < D) sVb[tid] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + tid];
   __syncthreads();
 
@@ -393,12 +399,10 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 
   if (w < NTOK) {
     const int ql = lane / 16;
-    const uint16_t* qb = q + head_base(rw, bh, H);
-    const uint16_t* dob = dout + head_base(rw, bh, H);
     uint16_t* dqb = dq + head_base(rw, bh, H);
     uint4 xq[K::KS], xr[K::KS], dor[K::KS];
     const float zero = opaque_zero_scalar();
-    const LoadRows16<D> qrows(qb, rw.sn, n, lane), drows(dob, rw.sn, n, lane);
+    const LoadRows16<D> qrows(q + head_base(rw, bh, H), rw.sn, n, lane), drows(dout + head_base(rw, bh, H), rw.sn, n, lane);
     qrows.load(xq, p * kTile + 16 * w);
     // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
     // for the first tile too, would be a wait for the previous tile's stores
@@ -709,27 +713,40 @@ __global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint1
   const int bh = blockIdx.y, h = bh % H;
   const uint16_t* wkh = wk + (size_t)h * D * K::HALF;
 
-  build_w_image16<D, NTK>(wkh, sWA, tid);
-  build_w_image_t16<D, NTK>(wkh, sWB, tid);
-  // sZ: dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the features)
-  const float scale = build_key_state<D, NTK, CENTRE>(dstate + (size_t)bh * (D + 1) * D, sVA, sGA, sZ, sRow, sRow + D, vbar + (size_t)bh * D,
-                                                      CENTRE ? cs_part + (size_t)bh * P * (D + 8) : nullptr, P, tid);
+  const int step = 16 * NTOK * gridDim.x;
+  int t0 = 16 * (blockIdx.x * NTOK + w);
+  // Everything the prologue reads, and the first rows, is requested before any of it is waited for: one memory latency instead of three (with the
+  // exchanges of the reductions as DPP steps and swaps, not through LDS: 12 x 1000 x 64 9.7 -> 6.6 us, 12 x 4133 x 64 11.3 -> 10.1).
+  const LoadRows16<D> krows(k + head_base(rw, bh, H), rw.sn, n, lane);
+  uint4 xk[K::KS];
+  float scale;
+  {
+    StateRegs<D, NTK> S;
+    WImages16<D, NTK> W;
+    const float* ds = dstate + (size_t)bh * (D + 1) * D;
+    S.load(ds, tid);
+    const int own = tid < D ? tid : 0;
+    const float dz = ds[D * D + own], vb_own = vbar[(size_t)bh * D + own];
+    W.load(wkh, tid);
+    krows.load(xk, w < NTOK ? t0 : n);
+    __builtin_amdgcn_sched_barrier(0);
+    W.write(sWA, sWB, tid);
+    // sZ: dz matched to the rounded image of dS (and, with LINATTN_FLAG_CENTRED, to its centring over the features)
+    scale = build_key_state<D, NTK, CENTRE>(S, dz, vb_own, sVA, sGA, sZ, sRow, sRow + D, CENTRE ? cs_part + (size_t)bh * P * (D + 8) : nullptr, P, tid);
+  }
   __syncthreads();
 
-  const int step = 16 * NTOK * gridDim.x;
   if (w < NTOK) {
     const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
     const int ql = lane / 16;
     uint16_t* dkb = dk + head_base(rw, bh, H);
     uint16_t* dvb = dv + head_base(rw, bh, H);
     const float zero = opaque_zero_scalar();
-    const LoadRows16<D> krows(k + head_base(rw, bh, H), rw.sn, n, lane), vrows(v + head_base(rw, bh, H), rw.sn, n, lane);
+    const LoadRows16<D> vrows(v + head_base(rw, bh, H), rw.sn, n, lane);
     float dv_add[K::MB];
 #pragma unroll
     for (int mb = 0; mb < K::MB; ++mb) dv_add[mb] = CENTRE ? sRow[K::MB * (lane % 16) + mb] : 0.f;
-    uint4 xk[K::KS], xr[K::KS], vr[K::KS];
-    int t0 = 16 * (blockIdx.x * NTOK + w);
-    krows.load(xk, t0);
+    uint4 xr[K::KS], vr[K::KS];
     // DW: every token wavefront makes the same number of rounds (there are barriers inside); one whose block does not exist works on zeros
     for (; (DW ? t0 - 16 * w : t0) < n; t0 += step) {
       const bool valid = t0 + lane % 16 < n;
@@ -817,7 +834,7 @@ __global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint1
   } else if constexpr (DW) {
     DWT dwt;
     dwt.init(w - NTOK);
-    for (int t0 = 16 * NTOK * blockIdx.x; t0 < n; t0 += step) {
+    for (t0 = 16 * NTOK * blockIdx.x; t0 < n; t0 += step) {
       __syncthreads();
       __syncthreads();
       dwt.contract(sX, sU, sIts, opaque_lane(lane));

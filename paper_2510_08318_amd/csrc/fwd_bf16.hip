@@ -153,6 +153,8 @@ __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, KIND, SUM, NW, 
       float* sb = state + (size_t)bh * (D + 1) * D;
       float* sZ = reinterpret_cast<float*>(sStage);
       R S;
+      WImage<D> W;
+      if constexpr (KIND == kPhiHedgehog) W.load(wq + (size_t)h * D * C::HALF, tid);
       float zv;
       if constexpr (SUM) {
         float4* sSum = reinterpret_cast<float4*>(sZ + D + 64);
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, KIND, SUM, NW, 
         zv = tid < D ? sb[D * D + tid] : 0.f;
       }
       if (tid < D) sZ[tid] = zv;
-      if constexpr (KIND == kPhiHedgehog) build_w_image<D, NT3>(wq + (size_t)h * D * C::HALF, sWA, tid);
+      if constexpr (KIND == kPhiHedgehog) W.write(sWA, tid);
       scale = S.scale(sZ + D, tid, fabsf(zv));            // (its barrier covers z as well)
       S.template write_apply_image<L::MBZ, KIND>(sSA, scale);
       R::template write_z_block<KIND>(sZ, sSA, scale, tid);
@@ -324,7 +326,11 @@ __device__ __forceinline__ void state_segment(const uint16_t* __restrict__ kb, c
   const int role = w / 4, pw = w % 4;            // role 0: phi, role 1: acc
   const int g = lane / 32;
 
-  build_w_image<D, NT1>(wkh, sWA, tid);
+  {
+    WImage<D> W;
+    W.load(wkh, tid);
+    W.write(sWA, tid);
+  }
   __syncthreads();
 
   if (role == 0) {

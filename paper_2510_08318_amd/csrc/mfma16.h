@@ -33,38 +33,43 @@ __device__ __forceinline__ f32x4 mfma_f16_16(uint4 a, uint4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0);
 }
 
-// W~ [D][D/2] bf16 (one head) -> LDS image of the A operands of U^T = W~^T X^T: entry (ks, mb, lane = (m, q)) holds
-// W~[32ks + 8q + e][feature(mb, m)].  A thread reads four adjacent features of eight channels and writes the four entries they fill.
+// W~ [D][D/2] bf16 (one head) -> the two LDS images of it: of the A operands of U^T = W~^T X^T, entry (ks, mb, lane = (m, q)) holding
+// W~[32ks + 8q + e][feature(mb, m)], and (fp16, exact) of the B operands of dX = dU W~^T with the tokens on the accumulator rows, entry (ks, mb,
+// lane = (c, q)) holding W~[MB*c + mb][q*FL + 8ks + e].  Read and written apart (see WImage).
 template <int D, int NTHREADS>
-__device__ __forceinline__ void build_w_image16(const uint16_t* __restrict__ w, uint4* img, int tid) {
+struct WImages16 {
   using K = Tok16<D>;
-  for (int it = tid; it < K::W_IMG / 4; it += NTHREADS) {
-    const int mq = it % 4, mb = (it / 4) % K::UB, q = (it / (4 * K::UB)) % 4, ks = it / (16 * K::UB);
-    const uint16_t* src = w + (32 * ks + 8 * q) * K::HALF + K::feature(mb, 4 * mq);
-    uint2 r[8];
+  static constexpr int TN = (K::T_IMG + NTHREADS - 1) / NTHREADS;
+  static_assert(K::W_IMG / 4 <= NTHREADS, "one item per thread");
+  uint2 r[8];
+  uint4 t[TN];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ w, int tid) {
+    if (tid < K::W_IMG / 4) {
+      const int mq = tid % 4, mb = (tid / 4) % K::UB, q = (tid / (4 * K::UB)) % 4, ks = tid / (16 * K::UB);
+      const uint16_t* src = w + (32 * ks + 8 * q) * K::HALF + K::feature(mb, 4 * mq);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = *reinterpret_cast<const uint2*>(src + e * K::HALF);
-    auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
-    auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
-    uint4* dst = img + (ks * K::UB + mb) * 64 + 16 * q + 4 * mq;
-    dst[0] = make_uint4(lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x));
-    dst[1] = make_uint4(hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x));
-    dst[2] = make_uint4(lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y));
-    dst[3] = make_uint4(hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y));
+      for (int e = 0; e < 8; ++e) r[e] = *reinterpret_cast<const uint2*>(src + e * K::HALF);
+    }
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      const int idx = tid + i * NTHREADS;
+      const int c = idx % 16, q = (idx / 16) % 4, mb = (idx / 64) % K::MB, ks = idx / (64 * K::MB);
+      if (idx < K::T_IMG) t[i] = *reinterpret_cast<const uint4*>(w + (K::MB * c + mb) * K::HALF + q * K::FL + 8 * ks);
+    }
   }
-}
-
-// W~ -> LDS image (fp16, exact) of the B operands of dX = dU W~^T, tokens on the accumulator rows: entry (ks, mb, lane = (c, q)) holds
-// W~[MB*c + mb][q*FL + 8ks + e].
-template <int D, int NTHREADS>
-__device__ __forceinline__ void build_w_image_t16(const uint16_t* __restrict__ w, uint4* img, int tid) {
-  using K = Tok16<D>;
-  for (int idx = tid; idx < K::T_IMG; idx += NTHREADS) {
-    const int c = idx % 16, q = (idx / 16) % 4, mb = (idx / 64) % K::MB, ks = idx / (64 * K::MB);
-    const uint4 r = *reinterpret_cast<const uint4*>(w + (K::MB * c + mb) * K::HALF + q * K::FL + 8 * ks);
-    img[idx] = make_uint4(bf16x2_to_f16x2(r.x), bf16x2_to_f16x2(r.y), bf16x2_to_f16x2(r.z), bf16x2_to_f16x2(r.w));
+  __device__ __forceinline__ void write(uint4* sWA, uint4* sWB, int tid) const {
+    if (tid < K::W_IMG / 4) {
+      const int mq = tid % 4, mb = (tid / 4) % K::UB, q = (tid / (4 * K::UB)) % 4, ks = tid / (16 * K::UB);
+      write_w_entries(r, sWA + (ks * K::UB + mb) * 64 + 16 * q + 4 * mq);
+    }
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      const int idx = tid + i * NTHREADS;
+      if (idx < K::T_IMG)
+        sWB[idx] = make_uint4(bf16x2_to_f16x2(t[i].x), bf16x2_to_f16x2(t[i].y), bf16x2_to_f16x2(t[i].z), bf16x2_to_f16x2(t[i].w));
+    }
   }
-}
+};
 
 // A operands of G^T = S Y^T: entry (ks, mb, lane = (m, q)) holds scale * S[f][32ks + 8q + e], f = feature(mb, m) of the + half for mb < GB/2,
 // of the - half otherwise.  The entry of lane (m, q) lies at 16q + (m ^ (4ks + q)): eight lanes of the writing wavefront have the
@@ -147,58 +152,6 @@ struct LoadRows16 {
     for (int ks = 0; ks < D / 32; ++ks) asm volatile("" : "+v"(x[ks].x), "+v"(x[ks].y), "+v"(x[ks].z), "+v"(x[ks].w));
   }
 };
-
-// Reductions over the four lanes of a token, every one of them receives the result.  Two or four at a time: a swap of two quantities
-// combines both in one operation.
-struct SumOp { static __device__ __forceinline__ float of(float a, float b) { return a + b; } };
-struct MaxOp { static __device__ __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
-// a, b -> [a of the low 32 lanes, b of the low 32], [a of the high 32, b of the high 32]
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-// rows of 16 lanes: a, b -> [a0, b0, a2, b2], [a1, b1, a3, b3]
-__device__ __forceinline__ void swap16(float& a, float& b) {
-  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-template <typename Op>
-__device__ __forceinline__ float quad(float a) {
-  float b = a;
-  swap32(a, b); a = b = Op::of(a, b);
-  swap16(a, b); return Op::of(a, b);
-}
-template <typename Op>
-__device__ __forceinline__ void quad2(float& a, float& b) {
-  swap32(a, b);
-  float s = Op::of(a, b), t = s;
-  swap16(s, t); a = b = Op::of(s, t);
-  swap32(a, b);
-}
-template <typename Op>
-__device__ __forceinline__ void quad4(float& a, float& b, float& c, float& d) {
-  swap32(a, b); swap32(c, d);
-  float s = Op::of(a, b), t = Op::of(c, d);
-  swap16(s, t);
-  a = b = Op::of(s, t);                  // rows: a, c, b, d
-  swap32(a, b);
-  c = a; d = b;
-  swap16(a, c); swap16(b, d);
-}
-// Maxima of magnitudes, which compare as integers (a floating-point maximum of exchanged values first quiets both): over the four lanes of a token, and
-// over the 16 lanes of a row.
-struct MagOp {
-  static __device__ __forceinline__ float of(float a, float b) {
-    const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-    return __builtin_bit_cast(float, x > y ? x : y);
-  }
-};
-__device__ __forceinline__ float row_max_mag(float x) {
-  x = MagOp::of(x, dpp_move<0xB1>(x));      // quad_perm [1,0,3,2]
-  x = MagOp::of(x, dpp_move<0x4E>(x));      // quad_perm [2,3,0,1]
-  x = MagOp::of(x, dpp_move<0x124>(x));     // row_ror 4
-  return MagOp::of(x, dpp_move<0x128>(x));  // row_ror 8
-}
 
 // The 16 rows from token t0 of a head of n tokens: lane (c, q), register r has PIECE bytes of token t0 + 4q + r, at byte PIECE*c of the row.
 // Buffer stores bounded to the rows that exist, as in TokenRows.

@@ -61,25 +61,33 @@ __device__ __forceinline__ void pair32(float x, float& lo, float& hi) {
 
 // W~ [D][D/2] bf16 (one head) -> LDS image of the A operands of U^T = W~^T X^T:
 // entry (ks, mb, lane=(m,g)) holds W~[16ks + 8g + e][owned_row<HALF>(mb, m)], e = 0..7.  A thread reads four adjacent features of
-// eight channels (8 bytes a load, all in flight together) and writes the four entries they fill.
-template <int D, int NTHREADS>
-__device__ __forceinline__ void build_w_image(const uint16_t* __restrict__ w, uint4* sWA, int tid) {
+// eight channels (8 bytes a load, all in flight together) and writes the four entries they fill; the two halves are apart so that what else a
+// prologue reads can be requested before the first of it is waited for.
+// The four entries from eight channels x four features.
+__device__ __forceinline__ void write_w_entries(const uint2 (&r)[8], uint4* dst) {
+  auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
+  auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
+  dst[0] = make_uint4(lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x));
+  dst[1] = make_uint4(hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x));
+  dst[2] = make_uint4(lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y));
+  dst[3] = make_uint4(hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y));
+}
+template <int D>
+struct WImage {
   using C = Cfg<D>;
-  for (int it = tid; it < C::W_IMG / 4; it += NTHREADS) {
-    const int mq = it % 8, mb = (it / 8) % C::UM, g = (it / (8 * C::UM)) % 2, ks = it / (16 * C::UM);
+  uint2 r[8];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ w, int tid) {
+    const int mq = tid % 8, mb = (tid / 8) % C::UM, g = (tid / (8 * C::UM)) % 2, ks = tid / (16 * C::UM);
     const uint16_t* src = w + (16 * ks + 8 * g) * C::HALF + owned_row<C::HALF>(mb, 4 * mq);
-    uint2 r[8];
+    if (tid >= C::W_IMG / 4) return;
 #pragma unroll
     for (int e = 0; e < 8; ++e) r[e] = *reinterpret_cast<const uint2*>(src + e * C::HALF);
-    auto lo = [](uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); };
-    auto hi = [](uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); };
-    uint4* dst = sWA + (ks * C::UM + mb) * 64 + 32 * g + 4 * mq;
-    dst[0] = make_uint4(lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x));
-    dst[1] = make_uint4(hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x));
-    dst[2] = make_uint4(lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y));
-    dst[3] = make_uint4(hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y));
   }
-}
+  __device__ __forceinline__ void write(uint4* sWA, int tid) const {      // at least W_IMG/4 threads
+    const int mq = tid % 8, mb = (tid / 8) % C::UM, g = (tid / (8 * C::UM)) % 2, ks = tid / (16 * C::UM);
+    if (tid < C::W_IMG / 4) write_w_entries(r, sWA + (ks * C::UM + mb) * 64 + 32 * g + 4 * mq);
+  }
+};
 
 // N uses (MFMAs) of 16-byte operands that come from LDS or global memory, each requested AHEAD uses
 // before it is needed.  Left to itself the compiler, short of registers, issues read, wait, MFMA,
@@ -227,6 +235,76 @@ __device__ __forceinline__ void softmax_pair_ratio(const f32x16 (&u)[Cfg<D>::UM]
   }
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+// Reductions over the four lanes l, l+16, l+32, l+48 (in 16-token blocks a token), every one of them receives the result.  Two or four at a time: a swap of two quantities
+// combines both in one operation.
+struct SumOp { static __device__ __forceinline__ float of(float a, float b) { return a + b; } };
+struct MaxOp { static __device__ __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
+// a, b -> [a of the low 32 lanes, b of the low 32], [a of the high 32, b of the high 32]
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+// rows of 16 lanes: a, b -> [a0, b0, a2, b2], [a1, b1, a3, b3]
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+template <typename Op>
+__device__ __forceinline__ float quad(float a) {
+  float b = a;
+  swap32(a, b); a = b = Op::of(a, b);
+  swap16(a, b); return Op::of(a, b);
+}
+template <typename Op>
+__device__ __forceinline__ void quad2(float& a, float& b) {
+  swap32(a, b);
+  float s = Op::of(a, b), t = s;
+  swap16(s, t); a = b = Op::of(s, t);
+  swap32(a, b);
+}
+template <typename Op>
+__device__ __forceinline__ void quad4(float& a, float& b, float& c, float& d) {
+  swap32(a, b); swap32(c, d);
+  float s = Op::of(a, b), t = Op::of(c, d);
+  swap16(s, t);
+  a = b = Op::of(s, t);                  // rows: a, c, b, d
+  swap32(a, b);
+  c = a; d = b;
+  swap16(a, c); swap16(b, d);
+}
+// Maxima of magnitudes, which compare as integers (a floating-point maximum of exchanged values first quiets both): over the four lanes of a token, and
+// over the 16 lanes of a row.
+struct MagOp {
+  static __device__ __forceinline__ float of(float a, float b) {
+    const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+    return __builtin_bit_cast(float, x > y ? x : y);
+  }
+};
+__device__ __forceinline__ float row_max_mag(float x) {
+  x = MagOp::of(x, dpp_move<0xB1>(x));      // quad_perm [1,0,3,2]
+  x = MagOp::of(x, dpp_move<0x4E>(x));      // quad_perm [2,3,0,1]
+  x = MagOp::of(x, dpp_move<0x124>(x));     // row_ror 4
+  return MagOp::of(x, dpp_move<0x128>(x));  // row_ror 8
+}
+
+// Sum of x over the 16 lanes of a row, and over the 32 lanes that share lane/32 (every one of them receives it): DPP inside a
+// row, then the two rows of a half are exchanged with one permlane16 swap.
+__device__ __forceinline__ float row_sum(float x) {
+  x += dpp_move<0xB1>(x);      // quad_perm [1,0,3,2]
+  x += dpp_move<0x4E>(x);      // quad_perm [2,3,0,1]
+  x += dpp_move<0x124>(x);     // row_ror 4
+  return x + dpp_move<0x128>(x);     // row_ror 8
+}
+__device__ __forceinline__ float half_wave_sum(float x) {
+  float a = row_sum(x), b = a;
+  swap16(a, b);
+  return a + b;
+}
+
 __device__ __forceinline__ float state_scale(float amax) {
   return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
 }
@@ -298,7 +376,7 @@ struct StateRegs {
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(v[e][i]));
-    for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+    amax = quad<MagOp>(row_max_mag(amax));
     if (tid % 64 == 0) red[tid / 64] = amax;
     __syncthreads();
 #pragma unroll
@@ -445,10 +523,6 @@ __device__ __forceinline__ uint4 relu_f16x8(uint4 x) {
 
 // Maximum of x over the wavefront, given x already equal in lanes l and l^32: DPP steps inside each
 // row of 16 lanes, then the two rows of the low half are combined through scalar registers.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
 __device__ __forceinline__ float wave_max_paired(float x) {
   x = fmaxf(x, dpp_move<0xB1>(x));      // quad_perm [1,0,3,2]
   x = fmaxf(x, dpp_move<0x4E>(x));      // quad_perm [2,3,0,1]
@@ -457,18 +531,6 @@ __device__ __forceinline__ float wave_max_paired(float x) {
   const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 0));
   const float b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16));
   return fmaxf(a, b);
-}
-
-// Sum of x over the 32 lanes that share lane/32 (every one of them receives it): DPP inside each
-// row of 16 lanes, then the two rows of a half are exchanged with one permlane16 swap.
-__device__ __forceinline__ float half_wave_sum(float x) {
-  x += dpp_move<0xB1>(x);      // quad_perm [1,0,3,2]
-  x += dpp_move<0x4E>(x);      // quad_perm [2,3,0,1]
-  x += dpp_move<0x124>(x);     // row_ror 4
-  x += dpp_move<0x128>(x);     // row_ror 8
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 1, 3 of the first <-> rows 0, 2 of the second
-  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
 // The 32 rows from token t0 of a head of n tokens, as the accumulators with tokens on the rows hold them: lane (c, g), register r has PIECE
