@@ -231,13 +231,14 @@ __global__ __launch_bounds__(NT8) void grad_f32_kernel(const T* __restrict__ x, 
     float dr_acc = 0.f;
     const float* sb = state + (size_t)bh * (D + 1) * D;
 
-    const int all = (n + 31) / 32, nblk = all < sh.end * (NT8 / 64) ? all : sh.end * (NT8 / 64), stride = sh.step * (NT8 / 64);
+    const Blocks own = blocks_of(deal, sh, w, (n + 31) / 32);
+    const int nblk = own.end, stride = own.stride;
     RowOctets<D, T> xr, yr;
     auto row_of = [&](const T* base, int b) {
       const int t = b * 32 + c;
       return base + (size_t)(t < n ? t : n - 1) * rw.sn;
     };
-    int b = sh.u * (NT8 / 64) + w;
+    int b = own.first;
     const int b_first = b < nblk ? b : nblk - 1;
     xr.load(row_of(xb, b_first), g);
     if constexpr (KIND == kPhiHedgehog) W::template build<T, NT8>(wx + (size_t)h * D * C::HALF, sW, tid);
@@ -604,7 +605,7 @@ constexpr size_t dw_smem() { return (size_t)4 * (D / 32) * (D / 64) * 16 * 64 * 
 template <int D, int KIND, typename T>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost<KIND, T, false>, grad_even<D, T>);
+  const Split deal = make_deal_of_blocks(p.BH, (p.n + 31) / 32, NT8 / 64, kF32Cost<KIND, T, false>, grad_even<D, T>);
   constexpr size_t smem = grad_smem<D, KIND, T>();
   // the per-token weights of the sum over tokens: dv's memory (at least 128 bytes per token), which the last pass writes
   float2* weights = static_cast<float2*>(a.dv);

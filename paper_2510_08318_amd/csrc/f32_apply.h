@@ -41,13 +41,14 @@ __global__ __launch_bounds__(NT8) void apply_f32_kernel(const T* __restrict__ q,
     const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
     const float* sb = state + (size_t)bh * (D + 1) * D;
 
-    const int all = (n + 31) / 32, nblk = all < sh.end * (NT8 / 64) ? all : sh.end * (NT8 / 64), stride = sh.step * (NT8 / 64);
+    const Blocks own = blocks_of(deal, sh, w, (n + 31) / 32);
+    const int nblk = own.end, stride = own.stride;
     RowOctets<D, T> x;
     auto load = [&](int b) {
       const int t = b * 32 + c;
       x.load(qb + (size_t)(t < n ? t : n - 1) * rw.sn, g);
     };
-    int b = sh.u * (NT8 / 64) + w;
+    int b = own.first;
     load(b < nblk ? b : nblk - 1);
     if constexpr (KIND == kPhiHedgehog) build_w_pieces<D, T, NT8>(wq + (size_t)h * D * (D / 2), sW, tid);
     const bool state_splits = build_s_pieces<D, KIND, NT8>(sb, sS, tid);
@@ -127,7 +128,7 @@ hipError_t run_apply_pass(const void* q, const void* wq, const float* state, voi
                      const void* blend_in, const float* blend_r, const Plan& p, hipStream_t s) {
   constexpr size_t smem = apply_smem<D, KIND, T>();
   constexpr bool EV = D == 128;                            // (width 64 has little to gain)
-  const Split deal = make_deal(p.BH, ((p.n + 31) / 32 + NT8 / 64 - 1) / (NT8 / 64), kF32Cost<KIND, T, BLEND>, EV);
+  const Split deal = make_deal_of_blocks(p.BH, (p.n + 31) / 32, NT8 / 64, kF32Cost<KIND, T, BLEND>, EV);
   auto launch = [&](auto kernel) -> hipError_t {
     const hipError_t e = set_smem_once<decltype(kernel)::value>(smem);
     if (e != hipSuccess) return e;

@@ -21,7 +21,7 @@ namespace linattn {
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// Query pass.  Units of NW 32-token blocks, one to a wavefront, are dealt to one workgroup per compute unit (make_deal), and
+// Query pass.  Units of 32-token blocks, one to a wavefront, are dealt to one workgroup per compute unit (make_deal_of_blocks), and
 // the workgroups of a head sweep its tokens together (next_share).  Per block: load Q rows straight into the
 // B operand of the projection (a lane owns a token), phi; phi then is the A operand of
 // out = phi S, which puts the tokens on the accumulator rows and the channels on the lanes: a lane
@@ -130,8 +130,8 @@ __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, KIND, SUM, NW, 
     const uint16_t* bb = BLEND ? blend + head_base(rw, bh, H) : nullptr;
     const float rb = BLEND ? fminf(fmaxf(*rptr, 0.f), 1.f) : 0.f;
 
-    const int nblk = (n + 31) / 32 < sh.end * NW ? (n + 31) / 32 : sh.end * NW;
-    const int stride = sh.step * NW;
+    const Blocks own = blocks_of(deal, sh, w, (n + 31) / 32);
+    const int nblk = own.end, stride = own.stride;
     const int c = lane % 32;
     const uint32_t lane_off = ((uint32_t)(4 * g) * (uint32_t)rw.sn + (uint32_t)(L::MB * c)) * 2u;   // bytes
 
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64 * NW, (kApplyOccupancy<D, BLEND, KIND, SUM, NW, 
       for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
     };
     // the first block's rows are requested before the prologue, so that they arrive under it
-    int b = sh.u * NW + w;
+    int b = own.first;
     if (b < nblk) load_block(b);
 
     float scale;
@@ -653,10 +653,10 @@ template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   const int blocks = (p.n + 31) / 32;
-  const Split d8 = make_deal(p.BH, (blocks + 7) / 8, kApplyCost<D, BLEND>, apply_even<SUM>);
+  const Split d8 = make_deal_of_blocks(p.BH, blocks, 8, kApplyCost<D, BLEND>, apply_even<SUM>);
   if constexpr (!SUM || kSumSlots<D> * kTile > 8 * 32) {   // (one unit of 8 a head otherwise)
     const bool even12 = apply_even<SUM> && ((D == 128 && BLEND) || !d8.share) && (blocks + 11) % 12 < 8;
-    const Split d12 = make_deal(p.BH, (blocks + 11) / 12, kApplyCost<D, BLEND>, even12);
+    const Split d12 = make_deal_of_blocks(p.BH, blocks, 12, kApplyCost<D, BLEND>, even12);
     const int r8 = split_rounds(d8);
     if (r8 <= 3 && split_rounds(d12) < r8)
       return run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s);

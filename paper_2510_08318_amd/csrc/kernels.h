@@ -47,6 +47,7 @@ struct Split {
   // instructions each, thousands with their copies, which the instruction cache has to bring in) it took 0.5 us of a state pass and
   // 1.3 us of a kernel that calls next_share.
   int share;        // not 0: G = B*H*share and no workgroup has tiles of two heads (next_share)
+  int blocks;       // make_deal_of_blocks: 32-token blocks to a unit, the first wavefronts of the workgroup one each
   int quot, rem;    // T / G, T % G
   float inv_G, per_T, inv_ntile;      // 1 / G, G / T, 1 / ntile
 };
@@ -161,6 +162,31 @@ inline Split make_deal(int BH, int per_head, DealCost cost, bool may_even = true
   }
   finish_split(s);
   return s;
+}
+
+// The deal of `blocks` 32-token blocks a head to workgroups of `waves` wavefronts, a block to a wavefront.  Where every unit of four, or two, gets a
+// compute unit of its own the units are four or two: in so short a call most of the chip is empty, its time is the latency of a block, and a
+// wavefront that shares its SIMD (or the LDS) with fewer others is done with it sooner.  Us, units of 8 / 4 / 2: bf16 query pass 4 heads x 1000 x 64 7.2 / 6.0 / 5.85, 3 x
+// 300 x 128 9.3 / 7.3 / 6.7, 12 x 1000 x 128 9.7 / 8.1 (200 units of 2: the same rule), ReLU 4 x 2000 x 64 5.0 / 4.1; fp32 arithmetic, 2 x 1024 x 64: query pass 8.9 / 7.4 /
+// 6.8, gradients 15.1 + 12.8 / 12.2 + 10.7 / 10.2 + 10.4; 4 x 1500 x 128, bf16 tensors: 13.9 / 10.7, 23.2 + 17.1 / 17.6 + 14.5.
+inline Split make_deal_of_blocks(int BH, int blocks, int waves, DealCost cost, bool may_even = true) {
+  int unit = waves;
+  for (int u = 4; u >= 2; u /= 2)
+    if ((long long)BH * ((blocks + u - 1) / u) <= kCUs) unit = u;
+  Split s = make_deal(BH, (blocks + unit - 1) / unit, cost, may_even);
+  s.blocks = unit;
+  return s;
+}
+// A wavefront's blocks of a share: first, stride and end (of `all` blocks a head); a wavefront beyond the unit's blocks has none.
+struct Blocks {
+  int first, stride, end;
+};
+__host__ __device__ inline Blocks blocks_of(const Split& s, const Share& sh, int w, int all) {
+  Blocks r;
+  r.end = all < sh.end * s.blocks ? all : sh.end * s.blocks;
+  r.stride = sh.step * s.blocks;
+  r.first = w < s.blocks ? sh.u * s.blocks + w : r.end;
+  return r;
 }
 
 // How one call is cut into workgroups and where its scratch regions sit in the workspace.

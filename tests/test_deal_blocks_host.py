@@ -1,0 +1,51 @@
+"""The deal of 32-token blocks to wavefronts (kernels.h: make_deal_of_blocks, blocks_of): every block to one wavefront, units of two or four blocks
+only where every unit has a compute unit of its own."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from tests.test_deal_host import ROCM, ROOT
+
+PROGRAM = r"""
+#include "kernels.h"
+#include <cstdio>
+#include <vector>
+using namespace linattn;
+int main() {
+  long bad = 0, units[9] = {};
+  for (int BH : {1, 2, 3, 12, 50, 87, 128, 255, 256, 257, 300})
+    for (int blocks : {1, 2, 3, 4, 5, 7, 8, 9, 10, 11, 31, 32, 33, 64, 129, 255, 512, 513, 1024, 1025})
+      for (int waves : {8, 12})
+        for (bool even : {false, true}) {
+          const Split s = make_deal_of_blocks(BH, blocks, waves, {4, 2, 5, 240}, even);
+          bad += s.blocks != 2 && s.blocks != 4 && s.blocks != waves;
+          bad += s.blocks < waves && (s.G > kCUs || !s.share || split_rounds(s) != 1);
+          if (s.blocks < 8) ++units[s.blocks];
+          std::vector<unsigned char> seen((size_t)BH * blocks, 0);
+          const dim3 grid = grid_of(s);
+          for (int gy = 0; gy < (int)grid.y; ++gy)
+            for (int gx = 0; gx < (int)grid.x; ++gx)
+              for (Share sh = first_share(s, gx, gy); sh.there; sh = next_share(s, gx, sh))
+                for (int w = 0; w < waves; ++w) {
+                  const Blocks b = blocks_of(s, sh, w, blocks);
+                  bad += b.end > blocks || b.stride < 1 || b.first < 0;
+                  for (int i = b.first; i < b.end && i >= 0; i += b.stride) ++seen[(size_t)sh.bh * blocks + i];
+                }
+          for (unsigned char c : seen) bad += c != 1;
+        }
+  printf("bad %ld two %ld four %ld\n", bad, units[2], units[4]);
+  return bad != 0 || units[2] == 0 || units[4] == 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_block_is_dealt_once(tmp_path):
+    src, exe = tmp_path / "deal.cpp", tmp_path / "deal"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    "-I", os.path.join(ROOT, "paper_2510_08318_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
