@@ -12,6 +12,12 @@ import torch
 from . import binding as B_
 
 
+def _current_stream() -> int:
+    """Handle of the current device's current stream.  torch.cuda.current_stream() makes a Stream object for it, 2.8 us of a forward call of
+    13.5; the handle alone takes 0.2."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def to_device(stored: np.ndarray, device="cuda") -> torch.Tensor:
     """Stored numpy tensor (float32, or uint16 bf16 bit patterns) -> device tensor of that dtype."""
     if stored.dtype == np.uint16:
@@ -62,7 +68,7 @@ class ReluLayer:
     def forward(self, q, k, v, out=None):
         self._check(q, k, v)
         out = torch.empty_like(q) if out is None else out
-        B_.linattn_fwd(q, k, v, out, self.B, self.H, self.n, self.d, self.phi_id, torch.cuda.current_stream().cuda_stream)
+        B_.linattn_fwd(q, k, v, out, self.B, self.H, self.n, self.d, self.phi_id, _current_stream())
         return out
 
     def backward(self, q, k, v, dout, dq=None, dk=None, dv=None):
@@ -70,8 +76,7 @@ class ReluLayer:
         dq = torch.empty_like(q) if dq is None else dq
         dk = torch.empty_like(q) if dk is None else dk
         dv = torch.empty_like(q) if dv is None else dv
-        B_.linattn_bwd(q, k, v, dout, dq, dk, dv, self.B, self.H, self.n, self.d, self.phi_id,
-                       torch.cuda.current_stream().cuda_stream)
+        B_.linattn_bwd(q, k, v, dout, dq, dk, dv, self.B, self.H, self.n, self.d, self.phi_id, _current_stream())
         return dq, dk, dv
 
 
@@ -130,9 +135,6 @@ class Layer:
         except Exception:
             pass
 
-    def _stream(self):
-        return torch.cuda.current_stream().cuda_stream
-
     def _dims(self, t):
         if self.layout == "bnhd":
             Bq, n, H, d = t.shape
@@ -147,7 +149,7 @@ class Layer:
             assert t.is_cuda and t.is_contiguous() and t.dtype == self.wq.dtype and t.shape == q.shape
         if out is None:
             out = torch.empty_like(q)
-        B_.linattn_fwd(q, k, v, out, Bq, H, n, d, self.phi_id, self._stream())
+        B_.linattn_fwd(q, k, v, out, Bq, H, n, d, self.phi_id, _current_stream())
         return out
 
     def backward(self, q, k, v, dout, dq=None, dk=None, dv=None):
@@ -157,5 +159,5 @@ class Layer:
         dq = torch.empty_like(q) if dq is None else dq
         dk = torch.empty_like(q) if dk is None else dk
         dv = torch.empty_like(q) if dv is None else dv
-        B_.linattn_bwd(q, k, v, dout, dq, dk, dv, Bq, H, n, d, self.phi_id, self._stream())
+        B_.linattn_bwd(q, k, v, dout, dq, dk, dv, Bq, H, n, d, self.phi_id, _current_stream())
         return dq, dk, dv
