@@ -30,6 +30,7 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   int tiles_per = (tiles + P - 1) / P;
   r.P = (tiles + tiles_per - 1) / tiles_per;
   r.state_elems = (size_t)(d + 1) * d;
+  int slots;
   {
     Split sp{};
     sp.ntile = tiles;
@@ -42,10 +43,10 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
       if (cnt > sp.PS) sp.PS = cnt;
     }
     r.split = sp;
+    slots = r.P > sp.PS ? r.P : sp.PS;
   }
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = 0;
-  const int slots = r.P > r.split.PS ? r.P : r.split.PS;
   r.off_partials = off; off = up(off + (size_t)BH * slots * r.state_elems * sizeof(float));
   r.off_state = off;    off = up(off + (size_t)BH * r.state_elems * sizeof(float));
   r.fwd_bytes = off;
@@ -139,6 +140,8 @@ int check_call(const void* const* tensors, int n_tensors, int B, int H, int n, i
   if (!make_plan(B, H, n, d, desc->dtype, desc->layout, plan)) return LINATTN_E_SHAPE;
   plan->kind = desc->kind;
   plan->centred = (desc->flags & LINATTN_FLAG_CENTRED) != 0;
+  plan->bf16_math = desc->dtype == LINATTN_BF16;
+  deal_state_pass(plan);
   for (int i = 0; i < n_tensors; ++i)
     if (!aligned16(tensors[i])) return LINATTN_E_ALIGN;
   const size_t need = (want_wgrads && (desc->dwq || desc->dwk)) ? plan->total_bytes : plan->bytes_no_wgrads;

@@ -193,6 +193,7 @@ __host__ __device__ inline Blocks blocks_of(const Split& s, const Share& sh, int
 struct Plan {
   int B, H, n, d;
   int kind;         // kPhiHedgehog or kPhiRelu (set by the dispatch, not by make_plan)
+  bool bf16_math;    // bf16 arithmetic (set by the dispatch)
   bool bf16_storage; // the fp32-arithmetic kernels read and write bf16 tensors (LINATTN_BF16_F32MATH)
   bool centred;      // LINATTN_FLAG_CENTRED (set by the dispatch): phi minus its mean in the sums over tokens, centred operand images
   int BH;
@@ -220,6 +221,22 @@ struct Plan {
 // Pure host arithmetic; returns false if the shape is unsupported or overflows.
 // total_bytes includes the weight-gradient regions, bytes_no_wgrads does not.
 bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p);
+// The workgroups of the state passes.  The split of make_plan, by which the workspace is sized, gives every workgroup the same number of tiles, and some
+// of them tiles of two heads: two prologues, two partial states, the loads in flight drained between them.  Head by head no workgroup has two, and
+// no head more partials; it is taken where the busiest workgroup has no more tiles for it, or, of eight and more, one more (but for the bf16 ReLU pass, which has no
+// image to build).  Evenly / head by head, us: 12 heads x 4133 x 64 (2 tiles either way) 8.6 / 7.55, x 128 14.9 / 13.5, 30 x 3000 x 64 (3) 10.4 / 9.4, 7 x 20000 x
+// 128 (5) 25.4 / 21.9, 30 x 17550 x 64 (17 / 18) 29.4 / 27.7, 12 x 32760 x 128 (12 / 13) 50.9 / 48.8; but 12 x 8190 x 128 (3 / 4) 18.3 / 18.7, ReLU 12 x 32760 x
+// 128 44.2 / 47.3.
+inline void deal_state_pass(Plan* p) {
+  const int m = p->BH < kSlots ? kSlots / p->BH : 1;
+  if (m > p->split.ntile) return;
+  const int even = split_rounds(p->split), by_head = (p->split.ntile + m - 1) / m;
+  const bool one_more = even >= 8 && !(p->kind == kPhiRelu && p->bf16_math);
+  if (by_head > even + one_more) return;
+  p->split.G = p->BH * m;
+  p->split.PS = m;
+  finish_split(p->split);
+}
 
 // Everything one backward call touches (device pointers; workspace regions already resolved).
 struct BwdArgs {

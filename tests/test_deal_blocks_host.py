@@ -1,5 +1,5 @@
 """The deal of 32-token blocks to wavefronts (kernels.h: make_deal_of_blocks, blocks_of): every block to one wavefront, units of two or four blocks
-only where every unit has a compute unit of its own."""
+only where every unit has a compute unit of its own; and the state passes' workgroups (deal_state_pass)."""
 import os
 import shutil
 import subprocess
@@ -35,6 +35,41 @@ int main() {
                 }
           for (unsigned char c : seen) bad += c != 1;
         }
+  // the state passes: every tile once, partial slots within those of the even split, two heads to a workgroup only where that saves tiles
+  long by_head = 0;
+  for (int BH : {1, 2, 3, 5, 7, 12, 13, 24, 30, 40, 87, 127, 128, 129, 255, 256, 300})
+    for (int tiles : {1, 2, 3, 5, 8, 16, 21, 22, 33, 64, 138, 157, 256, 591})
+      for (int relu : {0, 1}) {
+        Plan p{};
+        p.BH = BH;
+        p.kind = relu ? kPhiRelu : kPhiHedgehog;
+        p.bf16_math = true;
+        Split& s = p.split;
+        s.ntile = tiles;
+        s.T = (long long)BH * tiles;
+        s.G = BH > kSlots ? BH : (int)(s.T < kSlots ? s.T : kSlots);
+        finish_split(s);
+        auto slots = [&] {
+          int most = 1;
+          for (long long bh = 0; bh < BH; ++bh) {
+            const int cnt = split_owner(s, (bh + 1) * tiles - 1) - split_owner(s, bh * tiles) + 1;
+            most = cnt > most ? cnt : most;
+          }
+          return most;
+        };
+        const int even_slots = s.PS = slots(), rounds = split_rounds(s), G = s.G;
+        deal_state_pass(&p);
+        by_head += s.G != G;
+        bad += s.PS < slots() || s.PS > even_slots || split_rounds(s) > rounds + (rounds >= 8 && !relu);
+        long long next = 0;
+        for (int g = 0; g < s.G; ++g) {
+          bad += split_lo(s, g) != next;
+          next = split_lo(s, g + 1);
+          bad += s.G != G && split_head(s, split_lo(s, g)) != split_head(s, next - 1);
+        }
+        bad += next != s.T;
+      }
+  bad += by_head == 0;
   printf("bad %ld two %ld four %ld\n", bad, units[2], units[4]);
   return bad != 0 || units[2] == 0 || units[4] == 0;
 }
