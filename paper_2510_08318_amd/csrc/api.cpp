@@ -50,13 +50,10 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   r.off_partials = off; off = up(off + (size_t)BH * slots * r.state_elems * sizeof(float));
   r.off_state = off;    off = up(off + (size_t)BH * r.state_elems * sizeof(float));
   r.fwd_bytes = off;
-  {
-    const int nblk = (n + 31) / 32;
-    int KP = kCUs / (int)BH;
-    if (KP < 1) KP = 1;
-    if (KP > (nblk + 7) / 8) KP = (nblk + 7) / 8;
-    r.KP = KP;
-  }
+  // room for the partials of dW~_k: at least one per 256 tokens
+  int KP = kCUs / (int)BH;
+  if (KP < 1) KP = 1;
+  if (KP > (n + 255) / 256) KP = (n + 255) / 256;
   r.off_dstate = off;   off = up(off + (size_t)BH * r.state_elems * sizeof(float));
   // A reserve that nothing is stored in, proportional to the heads.  A descriptor sized for a batch serves smaller ones, but the need
   // without it is not monotone in B: fewer heads get more partial slots each (87 heads of width 64: 14.6 MB for two items, 13.2
@@ -65,7 +62,7 @@ bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p) {
   r.off_centre = off;   off = up(off + ((size_t)BH * 3 * d + (size_t)BH * r.P * (d + 8)) * sizeof(float));
   r.off_drpart = off;   off = up(off + ((size_t)BH * r.P + kDrSlack) * sizeof(float));
   r.bytes_no_wgrads = off;
-  r.off_dwpart = off;   off = up(off + (size_t)BH * (r.P + (r.P > r.KP ? r.P : r.KP)) * d * (d / 2) * sizeof(float));
+  r.off_dwpart = off;   off = up(off + (size_t)BH * (r.P + (r.P > KP ? r.P : KP)) * d * (d / 2) * sizeof(float));
   // the fp32-arithmetic modes keep dL/du as fp32 rows for a separate dW~ pass; the bf16 kernels accumulate dW~ where du is made
   r.du_bytes = dtype == LINATTN_BF16 ? 0 : (size_t)BH * n * (d / 2) * sizeof(float);
   r.off_du_q = off;     off = up(off + r.du_bytes);

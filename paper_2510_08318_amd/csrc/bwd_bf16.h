@@ -676,10 +676,10 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 // ---- key side ----------------------------------------------------------------------------
 // LDS operands of the MFMA phases are requested KAHEAD MFMAs before their use.
 constexpr int KAHEAD = 3;
-// One workgroup per compute unit, 12 wavefronts; 8 at width 64 without dW~, where the rows are what is waited for (12 or 16 wavefronts 47.4 us at 24 heads x
-// 20000, 8: 46.2, 8 of 32 tokens: 47.2).
+// One workgroup per compute unit: with dW~ 12 wavefronts, without 8, whose prologue is shorter and whose rows arrive no later: 12 / 8 wavefronts, us, 4 heads x
+// 1000 x 128 11.7 / 9.9, 12 x 2000 13.3 / 11.8, 12 x 4133 20.8 / 18.3, 12 x 16000 40.7 / 40.2, 24 x 20000 x 64 47.4 / 46.2 (8 of 32 tokens: 47.2).
 template <int D, bool DW>
-constexpr int kKeyThreads = D == 64 && !DW ? 512 : 768;
+constexpr int kKeyThreads = DW ? 768 : 512;
 
 // Every wavefront takes blocks of 16 tokens.  DW: dW~_k is accumulated here as well (DwTile): wavefronts 0-7 walk 128-token tiles in step and park their
 // k rows (kept in registers: read again at the end of a block they came from beyond the L2, whose 4 MB a round of 32 compute

@@ -205,12 +205,11 @@ struct Plan {
   size_t off_state;       // fp32 [BH][(d+1)*d]   (used when the caller gave no state buffer)
   size_t fwd_bytes;       // end of the two regions above: all the scratch a forward call touches
   // backward only
-  int KP;                 // workgroups per (b,h) of the ReLU key side: 8 wavefronts, each on its own 32-token blocks
   size_t off_dstate;      // fp32 [BH][(d+1)*d]   dS, dz
   size_t off_centre;      // bf16 backward: fp32 [BH][3][d] (mean value row vbar; the other two rows unused), then
                           // [BH][P][d+8] per-workgroup column sums of dO/den (d) and the sum of -delta/den (1)
   size_t off_drpart;      // fp32 [BH][P] + [kDrSlack]: per-workgroup parts of dL/dr (mixed attention, Eq. 6)
-  size_t off_dwpart;      // fp32 [BH][P][d*d/2] partial dW~_q, then [BH][max(P, KP)][d*d/2] partial dW~_k (weight gradients only)
+  size_t off_dwpart;      // fp32 [BH][P][d*d/2] partial dW~_q, then as many of dW~_k, in room for 256 / BH of them a head (weight gradients only)
   size_t du_bytes;        // bytes of one dL/du region (0 in bf16 mode: dW~ is accumulated where du is made)
   size_t off_du_q;        // dL/du of the query side (weight gradients, fp32 arithmetic only): fp32 [BH][n][d/2]
   size_t off_du_k;        // the same for the key side
@@ -223,15 +222,14 @@ struct Plan {
 bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p);
 // The workgroups of the state passes.  The split of make_plan, by which the workspace is sized, gives every workgroup the same number of tiles, and some
 // of them tiles of two heads: two prologues, two partial states, the loads in flight drained between them.  Head by head no workgroup has two, and
-// no head more partials; it is taken where the busiest workgroup has no more tiles for it, or, of eight and more, one more (but for the bf16 ReLU pass, which has no
-// image to build).  Evenly / head by head, us: 12 heads x 4133 x 64 (2 tiles either way) 8.6 / 7.55, x 128 14.9 / 13.5, 30 x 3000 x 64 (3) 10.4 / 9.4, 7 x 20000 x
+// no head more partials; it is taken where the busiest workgroup has no more tiles for it, or, of eight and more in the bf16 Hedgehog pass, one more.  Evenly / head by head, us: 12 heads x 4133 x 64 (2 tiles either way) 8.6 / 7.55, x 128 14.9 / 13.5, 30 x 3000 x 64 (3) 10.4 / 9.4, 7 x 20000 x
 // 128 (5) 25.4 / 21.9, 30 x 17550 x 64 (17 / 18) 29.4 / 27.7, 12 x 32760 x 128 (12 / 13) 50.9 / 48.8; but 12 x 8190 x 128 (3 / 4) 18.3 / 18.7, ReLU 12 x 32760 x
-// 128 44.2 / 47.3.
+// 128 44.2 / 47.3, a forward call of fp32 tensors there 271 / 275.
 inline void deal_state_pass(Plan* p) {
   const int m = p->BH < kSlots ? kSlots / p->BH : 1;
   if (m > p->split.ntile) return;
   const int even = split_rounds(p->split), by_head = (p->split.ntile + m - 1) / m;
-  const bool one_more = even >= 8 && !(p->kind == kPhiRelu && p->bf16_math);
+  const bool one_more = even >= 8 && p->kind == kPhiHedgehog && p->bf16_math;
   if (by_head > even + one_more) return;
   p->split.G = p->BH * m;
   p->split.PS = m;

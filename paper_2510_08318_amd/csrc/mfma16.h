@@ -76,7 +76,9 @@ struct WImages16 {
 // same m, and would all hit the same banks.
 template <int D>
 __device__ __forceinline__ int grad16_lane(int lane) { return lane ^ (lane / 16); }        // the place in k-step 0; ^ 4ks in k-step ks
-template <int D, int NTHREADS>
+// KIND = kPhiRelu: the rows are ordered so that register r of block mb in a lane of group q is feature 32*(mb/2) + 8q + 4*(mb%2) + r, element
+// 4*(mb%2) + r of the piece mb/2 which that lane holds of its token's row.
+template <int D, int NTHREADS, int KIND = kPhiHedgehog>
 __device__ __forceinline__ void write_grad_image16(const StateRegs<D, NTHREADS>& S, uint4* img, float sc) {
   using K = Tok16<D>;
   if (!S.active) return;
@@ -84,7 +86,8 @@ __device__ __forceinline__ void write_grad_image16(const StateRegs<D, NTHREADS>&
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int f = 8 * S.fo + e, half = f / K::HALF, fl = f % K::HALF, j = fl % K::FL;
-    const int mb = half * (K::GB / 2) + j / 4, m = 4 * (fl / K::FL) + j % 4;
+    const int mb = KIND == kPhiRelu ? 2 * (S.fo / 4) + e / 4 : half * (K::GB / 2) + j / 4;
+    const int m = KIND == kPhiRelu ? 4 * (S.fo % 4) + e % 4 : 4 * (fl / K::FL) + j % 4;
     uint2* dst = reinterpret_cast<uint2*>(img + (ks * K::GB + mb) * 64 + 16 * q + (m ^ (4 * ks + q))) + S.cq % 2;
     *dst = make_uint2(pack_f16x2(sc * S.v[e][0], sc * S.v[e][1]), pack_f16x2(sc * S.v[e][2], sc * S.v[e][3]));
   }
@@ -92,11 +95,13 @@ __device__ __forceinline__ void write_grad_image16(const StateRegs<D, NTHREADS>&
 
 // B operands of Y = phi S, tokens on the accumulator rows: entry (ks, mb, lane = (c, q)) holds scale * S[f + e][MB*c + mb], f = q*FL + 8*(ks % DK)
 // of the + half for ks < DK, of the - half otherwise.
-template <int D, int NTHREADS>
+// KIND = kPhiRelu: the features are the channels in their plain order, 32ks + 8q + e.
+template <int D, int NTHREADS, int KIND = kPhiHedgehog>
 __device__ __forceinline__ void write_apply_image16(const StateRegs<D, NTHREADS>& S, uint4* img, float sc) {
   using K = Tok16<D>;
   if (!S.active) return;
-  const int f = 8 * S.fo, fl = f % K::HALF, q = fl / K::FL, ks = f / K::HALF * K::DK + fl % K::FL / 8;
+  const int f = 8 * S.fo, fl = f % K::HALF;
+  const int q = KIND == kPhiRelu ? S.fo % 4 : fl / K::FL, ks = KIND == kPhiRelu ? S.fo / 4 : f / K::HALF * K::DK + fl % K::FL / 8;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int ch = 4 * S.cq + i;

@@ -308,33 +308,12 @@ __device__ __forceinline__ float half_wave_sum(float x) {
 __device__ __forceinline__ float state_scale(float amax) {
   return (amax >= 0x1p-100f && amax < 3.0e38f) ? ldexpf(1.0f, 13 - ilogbf(amax)) : 1.0f;   // the scale itself stays finite
 }
-// Index maps of G^T = S Y^T (contraction over the d channels; rows = features of phi), used by the
-// backward kernels.  The B operand is a token's row as the projections read it: lane (t, g) feeds channels
-// 16*ks + 8*g + e in k-step ks, so that a load instruction reads 32 adjacent bytes of each of 32 rows (with half rows per lane
-// group, 16 bytes of 64 lines, the lines of two tensors did not survive in the L1 until their last piece was read).  The accumulator rows are laid out like phi itself: lane (t, g),
-// row block mb, register r holds the softmax(+u) feature g*LOC + 16*mb + r for mb < GM/2 and
-// the softmax(-u) feature HALF + g*LOC + 16*(mb - GM/2) + r otherwise.
-template <int D>
-struct GradLayout {
-  static constexpr int HALF = D / 2;
-  static constexpr int LOC = D / 4;
-  static constexpr int KS = D / 16;       // k-steps over the channels
-  static constexpr int GM = D / 32;       // row blocks over the D features
-  static constexpr int IMG = KS * GM * 64;
-  __device__ static constexpr int channel(int ks, int g, int e) { return 16 * ks + 8 * g + e; }
-  __device__ static constexpr int feature(int mb, int m) {
-    const int gg = (m / 4) % 2, r = 4 * (m / 8) + (m % 4);
-    return (mb < GM / 2 ? 0 : HALF) + gg * LOC + 16 * (mb % (GM / 2)) + r;
-  }
-};
-
 // A state (S, dS) [D][D] fp32 of one head in the registers of a workgroup: thread tid < ITEMS holds features 8*fo .. +7 x channels
 // 4*cq .. +3, the others zeros.  Eight 16-byte loads in flight per thread, and every operand image is written from here: the statistics an image
 // needs first (means, the largest magnitude) are taken on the registers, with no pass through LDS or memory for the state itself.
 template <int D, int NTHREADS>
 struct StateRegs {
   using L = ApplyLayout<D>;
-  using G = GradLayout<D>;
   static constexpr int CQ = D / 4, FO = D / 8, ITEMS = CQ * FO;
   static_assert(ITEMS <= NTHREADS, "one item per thread");
   float v[8][4];
@@ -382,23 +361,6 @@ struct StateRegs {
 #pragma unroll
     for (int i = 0; i < NTHREADS / 64; ++i) amax = fmaxf(amax, red[i]);
     return state_scale(amax);
-  }
-  // A operands of G^T = S Y^T (GradLayout): entry (ks, mb, lane = (m, g)) holds scale * S[feature(mb, m)][channel(ks, g, 0) ..].
-  // KIND = kPhiRelu: the rows are ordered so that register r of block mb in a lane of group g is feature 16*(2mb + r/8) + 8g + r%8,
-  // the channels which that lane holds of its token's row.
-  template <int KIND = kPhiHedgehog>
-  __device__ __forceinline__ void write_grad_image(uint4* img, float sc) const {
-    if (!active) return;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int f = 8 * fo + e, q = f % (D / 4);
-      const int r = KIND == kPhiRelu ? 8 * ((fo / 2) % 2) + e : q % 16;
-      const int mb = KIND == kPhiRelu ? fo / 4 : f / (D / 2) * (G::GM / 2) + q / 16;
-      const int m = 8 * (r / 4) + 4 * (KIND == kPhiRelu ? fo % 2 : (f / (D / 4)) % 2) + r % 4;
-      const int ks = cq / 4, g = (cq / 2) % 2;
-      uint2* dst = reinterpret_cast<uint2*>(img + (ks * G::GM + mb) * 64 + 32 * g + m) + cq % 2;
-      *dst = make_uint2(pack_f16x2(sc * v[e][0], sc * v[e][1]), pack_f16x2(sc * v[e][2], sc * v[e][3]));
-    }
   }
   // B operands of Y = phi S (contraction over the features of phi, tokens on the accumulator rows): entry (ks, mb, lane = (c, g)), MBS
   // column blocks to a k-step, holds scale * S[feature(ks, g, e)][channel_cols(mb, c)].
@@ -521,18 +483,6 @@ __device__ __forceinline__ uint4 relu_f16x8(uint4 x) {
   return r;
 }
 
-// Maximum of x over the wavefront, given x already equal in lanes l and l^32: DPP steps inside each
-// row of 16 lanes, then the two rows of the low half are combined through scalar registers.
-__device__ __forceinline__ float wave_max_paired(float x) {
-  x = fmaxf(x, dpp_move<0xB1>(x));      // quad_perm [1,0,3,2]
-  x = fmaxf(x, dpp_move<0x4E>(x));      // quad_perm [2,3,0,1]
-  x = fmaxf(x, dpp_move<0x124>(x));     // row_ror 4
-  x = fmaxf(x, dpp_move<0x128>(x));     // row_ror 8
-  const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 0));
-  const float b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16));
-  return fmaxf(a, b);
-}
-
 // The 32 rows from token t0 of a head of n tokens, as the accumulators with tokens on the rows hold them: lane (c, g), register r has PIECE
 // bytes of token t0 + 8*(r/4) + 4g + r%4, at byte PIECE*c of the row, so that every store instruction writes two whole rows.
 // The stores are buffer stores bounded to the rows that exist: the hardware drops those past n.  No branch (behind one the compiler cannot count the
@@ -562,36 +512,6 @@ struct TokenRows {
     else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, off, 0, aux);
   }
 };
-
-// Accumulators with tokens on the rows (lane (c,g), register r: token t0 + 8*(r/4) + 4g + r%4,
-// channels MB*c .. MB*c + MB-1 in acc[0..MB-1]) -> mul * acc as bf16 rows of base.  STREAM: non-temporal (stream_gradients).
-template <int D, bool STREAM>
-__device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
-                                                 const f32x16 (&acc)[D / 32], float mul, const float (&add)[D / 32]) {
-  constexpr int MB = D / 32;
-  static_assert(MB == 2 || MB == 4, "head width 64 or 128");
-  const TokenRows<2 * MB> rows(base, sn * 2, t0, n, lane);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    if constexpr (MB == 4) {
-      uint2 v;
-      v.x = pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1]));
-      v.y = pack_bf16x2(fmaf(acc[2][r], mul, add[2]), fmaf(acc[3][r], mul, add[3]));
-      rows.template store<STREAM>(r, v);
-    } else {
-      rows.template store<STREAM>(r, pack_bf16x2(fmaf(acc[0][r], mul, add[0]), fmaf(acc[1][r], mul, add[1])));
-    }
-  }
-}
-
-template <int D, bool STREAM>
-__device__ __forceinline__ void store_token_rows(uint16_t* base, size_t sn, int t0, int n, int lane,
-                                                 const f32x16 (&acc)[D / 32], float mul) {
-  float zero[D / 32];
-#pragma unroll
-  for (int i = 0; i < D / 32; ++i) zero[i] = 0.f;
-  store_token_rows<D, STREAM>(base, sn, t0, n, lane, acc, mul, zero);
-}
 
 // 32x32x16 MFMA on operands carried as f16x8 registers whose bits are fp16 or (BF16) bf16.
 template <bool BF16>

@@ -16,7 +16,7 @@
 //   dphi(k_j) = dS v_j + dz;  dv_j = dS^T phi(k_j)
 // Operands that are gradients are scaled by powers of two before the cast to fp16, as in bwd_bf16.h.
 #include "kernels.h"
-#include "mfma_common.h"
+#include "mfma16.h"
 
 namespace linattn {
 namespace {
@@ -182,10 +182,11 @@ __device__ __forceinline__ float build_relu_query_state(const float* __restrict_
   using R = StateRegs<D, NTHREADS>;
   R S;
   S.load(state, tid);
+  const float z_own = state[D * D + (tid < D ? tid : 0)];
   float* part = scratch;
   float* mean = part + R::FO * D;
   float* red = mean + D;
-  if (tid < D) sZ[tid] = state[D * D + tid];
+  if (tid < D) sZ[tid] = z_own;
   S.octet_sums(part);
   __syncthreads();
   if (tid < D) {
@@ -209,7 +210,7 @@ __device__ __forceinline__ float build_relu_query_state(const float* __restrict_
       for (int i = 0; i < 4; ++i) S.v[e][i] -= sZ[8 * S.fo + e] * mean[4 * S.cq + i];
   }
   const float scale = S.scale(red, tid);
-  S.template write_grad_image<kPhiRelu>(sG, scale);
+  write_grad_image16<D, NTHREADS, kPhiRelu>(S, sG, scale);
   return scale;
 }
 
@@ -221,101 +222,92 @@ __device__ __forceinline__ float build_relu_key_state(const float* __restrict__ 
   R S;
   S.load(dstate, tid);
   const float4 cm = *reinterpret_cast<const float4*>(mean + 4 * S.cq);
+  float dz[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) dz[e] = dstate[D * D + 8 * S.fo + e];
   const float scale = S.scale(red, tid);
-  S.template write_grad_image<kPhiRelu>(sG, scale);
-  S.template write_apply_image<ApplyLayout<D>::MB, kPhiRelu>(sC, scale);
+  write_grad_image16<D, NTHREADS, kPhiRelu>(S, sG, scale);
+  write_apply_image16<D, NTHREADS, kPhiRelu>(S, sC, scale);
   const float inv = __builtin_amdgcn_rcpf(scale);           // exact: a power of two
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     auto img = [&](int i) { return (float)(_Float16)(scale * S.v[e][i]); };
     float dot = fmaf(img(3), cm.w, fmaf(img(2), cm.z, fmaf(img(1), cm.y, img(0) * cm.x)));
-    for (int k = R::CQ / 2; k >= 1; k >>= 1) dot += __shfl_xor(dot, k, 64);
-    const int f = 8 * S.fo + e;
-    if (S.active && S.cq == 0) sZ[f] = dstate[D * D + f] - dot * inv;
+    dot = D == 128 ? half_wave_sum(dot) : row_sum(dot);     // over the CQ lanes that share the octet of features
+    if (S.active && S.cq == 0) sZ[8 * S.fo + e] = dz[e] - dot * inv;
   }
   return scale;
 }
 
-// G^T = M X^T for the 32 tokens of a wavefront: x(ks) is the lane's piece of its token's row (fp16, channels 16ks + 8g ..) and img an
-// image of write_grad_image<kPhiRelu>; register 8*(ks%2) + e of ga[ks/2] is then feature 16ks + 8g + e of the lane's token, the element e
-// of piece ks.
-template <int D, int AHEAD, typename Piece>
-__device__ __forceinline__ void relu_grad(const uint4* img, int lane, Piece x, f32x16 (&ga)[D / 32]) {
-  constexpr int MB = D / 32;
+// G^T = M Y^T for the 16 tokens of a wavefront: y[ks] is the lane's piece of its token's row (fp16, channels 32ks + 8q ..) and img an
+// image of write_grad_image16<.., kPhiRelu>; register r of ga[2*ks + h] is then feature 32ks + 8q + 4h + r of the lane's token, element 4h + r of piece ks.
+template <int D, int AHEAD>
+__device__ __forceinline__ void relu_grad(const uint4* img, int lane, const uint4 (&y)[D / 32], f32x4 (&ga)[D / 16]) {
+  using K = Tok16<D>;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) ga[mb][r] = 0.f;
-  const uint4* a = img + lane + opaque_zero();
-  uint4 b;
-  pipelined_operands<(D / 16) * MB, AHEAD>(
-      [&](int i) { return a[i * 64]; },
-      [&](int i, uint4 op) {
-        if (i % MB == 0) b = x(i / MB);
-        ga[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(op), as_f16x8(b), ga[i % MB], 0, 0, 0);
-      });
+  for (int mb = 0; mb < K::GB; ++mb) ga[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int gl = grad16_lane<D>(opaque_lane(lane));
+  pipelined_operands<K::KS * K::GB, AHEAD>([&](int i) { return img[i * 64 + (gl ^ (4 * (i / K::GB)))]; },
+                                           [&](int i, uint4 a) { ga[i % K::GB] = mfma_f16_16(a, y[i / K::GB], ga[i % K::GB]); });
 }
 
-// A lane's row pieces (bf16, channels 16ks + 8g .. of its token) -> 32 rows of base, a wavefront's tokens t0 ..: through `buf`
-// ([32][D] bf16 of LDS, the wavefront's own), so that an instruction stores 1 KB of whole rows.  Stored as the lanes hold them,
-// 32 bytes of a row at a time, the query side took 95 us and the key side 96 where they took 91 and 88 (12 heads x
-// 32760 x 128, ordinary stores).  Rows past n hold the bits of row n - 1 and go there.
+// A lane's row pieces (bf16, channels 32ks + 8q .. of its token) -> 16 rows of base, a wavefront's tokens t0 ..: through `buf`
+// ([16][D] bf16 of LDS, the wavefront's own), so that an instruction stores 1 KB of whole rows, with bounded buffer stores as in TokenRows.
 template <int D>
 struct RowStore {
   static constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks of a row, rows per store
   char* buf;
   int lane;
   __device__ __forceinline__ void put(int ks, uint4 x) const {
-    const int row = lane % 32;
-    *reinterpret_cast<uint4*>(buf + row * D * 2 + (((2 * ks + lane / 32) ^ swz<D>(row)) * 16)) = x;
+    const int row = lane % 16;
+    *reinterpret_cast<uint4*>(buf + row * D * 2 + (((4 * ks + lane / 16) ^ swz<D>(row)) * 16)) = x;
   }
   template <bool STREAM>                                    // non-temporal
   __device__ __forceinline__ void flush(uint16_t* base, size_t sn, int t0, int n) const {
     __builtin_amdgcn_wave_barrier();
+    const int left = n - t0 < 16 ? n - t0 : 16;
+    const uint32_t pitch = (uint32_t)sn * 2;
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(base) + (size_t)t0 * pitch, 0,
+                                                                          left > 0 ? (uint32_t)left * pitch : 0, 0x00020000);
     const int c = lane % CH;
 #pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-      const int row = i * RPI + lane / CH, t = t0 + row;
+    for (int i = 0; i < 16 / RPI; ++i) {
+      const int row = i * RPI + lane / CH;
       const uint4 x = *reinterpret_cast<const uint4*>(buf + row * D * 2 + ((c ^ swz<D>(row)) * 16));
-      uint4* dst = reinterpret_cast<uint4*>(base + (size_t)(t < n ? t : n - 1) * sn + 8 * c);
-      if constexpr (STREAM) st_nt(dst, x);
-      else *dst = x;
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rows, (uint32_t)row * pitch + 16 * c, 0, STREAM ? 2 : 0);
     }
     __builtin_amdgcn_wave_barrier();
   }
 };
 
 // ---- query side of the backward -------------------------------------------------------------------
-// grid (P, BH), 8 wavefronts, one workgroup per compute unit.  Wavefronts 0-3 ("tok") each own 32 tokens of a 128-token tile, two
+// grid (P, BH), 12 wavefronts, one workgroup per compute unit.  Wavefronts 0-7 ("tok") each own 16 tokens of a 128-token tile, four
 // lanes a token: G = dO S^T with the tokens on the accumulator columns and the features in the order in which the lane holds
 // its token's channels, so den = phi . z and delta = phi . G / den are dots of registers, the mask of dq is the lane's own row and dq
-// leaves in the pieces in which q came.  They park phi(q) and gamma * dO / den as fp16 and form dq while wavefronts 4-7 ("acc") contract
-// the tile over its tokens into dS (dz: one more MFMA per k-step).  The kernel is bound by its instruction stream (its rows take 51 us
-// at the memory's rate): with four wavefronts that did all of this one after another, read q a second time for the mask and summed delta
-// across lanes it took 119 us at 12 heads x 32760 x 128, 88 to 93 now.
-constexpr int NTQ = 512;
+// leaves in the pieces in which q came.  They park phi(q) and gamma * dO / den as fp16 and form dq while wavefronts 8-11 ("acc") contract
+// the tile over its tokens into dS (dz: one more MFMA per k-step).  Bound by its instruction stream (its rows take 51 us
+// at the memory's rate): 75 us at 12 heads x 32760 x 128, 11.5 at 12 x 4133 x 64; with four token wavefronts of 32 tokens 89 and 12.6.
+constexpr int NTQ = 768;
 template <int D, bool STREAM>
 __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
                                                          const float* __restrict__ state, float* __restrict__ mean_row,
                                                          uint16_t* __restrict__ dq, float* __restrict__ partials,
                                                          int H, int n, int P, Rows rw) {
-  using C = Cfg<D>;
-  using G = GradLayout<D>;
+  using K = Tok16<D>;
   constexpr int RS = D * 2;
   constexpr int WMN = D / 64;
+  constexpr int NTOK = kTile / 16;
   extern __shared__ uint4 smem[];
-  uint4* sG = smem;                                        // [KS][GM][64] image of S^c
-  char* sPhi = reinterpret_cast<char*>(sG + G::IMG);       // [kTile][D] fp16: phi(q)
+  uint4* sG = smem;                                        // image of S^c
+  char* sPhi = reinterpret_cast<char*>(sG + K::G_IMG);     // [kTile][D] fp16: phi(q)
   char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: gamma * dO / den
   uint16_t* sW16 = reinterpret_cast<uint16_t*>(sDO + kTile * RS);   // [kTile] fp16: -gamma * delta / den
   float* sZ = reinterpret_cast<float*>(sW16 + kTile);      // [D] z, unscaled
-  float* sRed = sZ + D;                                    // [4] the tile's operand maxima
-  char* sOut = reinterpret_cast<char*>(sRed + 4);          // [4][32][D] bf16: RowStore
+  float* sRed = sZ + D;                                    // [8] the tile's operand maxima
+  char* sOut = reinterpret_cast<char*>(sRed + NTOK);       // [8][16][D] bf16: RowStore
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int role = w / 4, pw = w % 4;
-  const int g = lane / 32;
   const int bh = blockIdx.y, p = blockIdx.x;
   const int ntile = (n + kTile - 1) / kTile;
 
@@ -327,144 +319,130 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
   // accumulators
   float gamma = kGammaUnset;
   auto next_gamma = [&]() -> float {
-    const float m = fmaxf(fmaxf(sRed[0], sRed[1]), fmaxf(sRed[2], sRed[3]));
+    float m = sRed[0];
+#pragma unroll
+    for (int i = 1; i < NTOK; ++i) m = fmaxf(m, sRed[i]);
     float gnext = gamma;
     const float ratio = gamma_step(gnext, gamma_for(m));
     gamma = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, gnext)));
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ratio)));
   };
 
-  if (role == 0) {
-    const uint16_t* qb = q + head_base(rw, bh, H);
-    const uint16_t* dob = dout + head_base(rw, bh, H);
+  if (w < NTOK) {
+    const int ql = lane / 16;
     uint16_t* dqb = dq + head_base(rw, bh, H);
-    const int prow = 32 * pw + (lane % 32);
-    // Rows past n read as row n - 1, and their lanes store its dq once more: the same bits.
-    auto row_at = [&](int tile) {
-      const int t = tile * kTile + prow;
-      return (size_t)(t < n ? t : n - 1) * rw.sn;
-    };
-    uint4 xq[C::UK], dor[C::UK], xn[C::UK];
-    auto load = [&](const uint16_t* base, int tile, uint4 (&x)[C::UK]) {
-      const uint4* row = reinterpret_cast<const uint4*>(base + row_at(tile));
-#pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) x[ks] = row[2 * ks + g];
-    };
-    load(qb, p < ntile ? p : 0, xn);
-    load(dob, p < ntile ? p : 0, dor);
+    const float zero = opaque_zero_scalar();
+    const LoadRows16<D> qrows(q + head_base(rw, bh, H), rw.sn, n, lane), drows(dout + head_base(rw, bh, H), rw.sn, n, lane);
+    uint4 xq[K::KS], dor[K::KS], xn[K::KS];
+    qrows.load(xn, p * kTile + 16 * w);
+    drows.load(dor, p * kTile + 16 * w);
     // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
     // for the first tile too, would be a wait for the previous tile's stores
-#pragma unroll
-    for (int ks = 0; ks < C::UK; ++ks) {
-      asm volatile("" : "+v"(xn[ks].x), "+v"(xn[ks].y), "+v"(xn[ks].z), "+v"(xn[ks].w));
-      asm volatile("" : "+v"(dor[ks].x), "+v"(dor[ks].y), "+v"(dor[ks].z), "+v"(dor[ks].w));
-    }
+    qrows.arrived(xn);
+    drows.arrived(dor);
     for (int tile = p; tile < ntile; tile += P) {
-      const bool valid = tile * kTile + prow < n;
+      const int t0 = tile * kTile + 16 * w;                // (rows past n are zeros)
       // phi(q); whether it has any feature above zero; the token's largest |dO| (magnitudes of bf16 compare as integers)
       uint32_t any = 0;
       typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
       u16x2 m2 = {0, 0};
       auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
+      for (int ks = 0; ks < K::KS; ++ks) {
         xq[ks] = make_uint4(relu_bf16x2(xn[ks].x), relu_bf16x2(xn[ks].y), relu_bf16x2(xn[ks].z), relu_bf16x2(xn[ks].w));
         any |= (xq[ks].x | xq[ks].y) | (xq[ks].z | xq[ks].w);
         take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w);
       }
-      float lo, hi;
-      float dmax = __builtin_bit_cast(float, (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16);
-      pair32(dmax, lo, hi); dmax = fmaxf(lo, hi);
-      const float stok = pow2_normaliser(fminf(dmax, kTokenMax));
+      float dmax = __builtin_bit_cast(float, (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16), any_of = __builtin_bit_cast(float, any);
+      quad2<MagOp>(dmax, any_of);
+      const float stok = pow2_normaliser(fminf(dmax, kTokenMax)), istok = __builtin_amdgcn_rcpf(stok);
       // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
       // common scale gamma and push every other token's operand into the fp16 subnormals
-      auto any2 = __builtin_amdgcn_permlane32_swap(any, any, false, false);
-      const bool live = valid && ((uint32_t)any2[0] | (uint32_t)any2[1]) != 0;
-
-      // G (times scale * stok)
-      f32x16 ga[G::GM];
-      relu_grad<D, 4>(sG, lane, [&](int ks) {
+      const bool live = __builtin_bit_cast(uint32_t, any_of) != 0;
+      // dO scaled by a power of two: exact in fp16 down to 2^-17 of the token's largest
+      uint4 bq[K::KS];
+#pragma unroll
+      for (int ks = 0; ks < K::KS; ++ks) {
         float f[8];
         unpack_bf16x8(dor[ks], f);
-        return make_uint4(pack_f16x2(f[0] * stok, f[1] * stok), pack_f16x2(f[2] * stok, f[3] * stok),
-                          pack_f16x2(f[4] * stok, f[5] * stok), pack_f16x2(f[6] * stok, f[7] * stok));
-      }, ga);
+        bq[ks] = make_uint4(mul_pack_f16x2(f[0], f[1], stok, zero), mul_pack_f16x2(f[2], f[3], stok, zero),
+                            mul_pack_f16x2(f[4], f[5], stok, zero), mul_pack_f16x2(f[6], f[7], stok, zero));
+      }
+
+      // G (times scale * stok)
+      f32x4 ga[K::GB];
+      relu_grad<D, 4>(sG, lane, bq, ga);
       // the rows stay packed until their next use: seen as the same values, their unpacked form would be kept (and spilled)
-      auto repack = [&](uint4 (&x)[C::UK]) {
+      auto repack = [&](uint4 (&x)[K::KS]) {
 #pragma unroll
-        for (int ks = 0; ks < C::UK; ++ks) asm volatile("" : "+v"(x[ks].x), "+v"(x[ks].y), "+v"(x[ks].z), "+v"(x[ks].w));
+        for (int ks = 0; ks < K::KS; ++ks) asm volatile("" : "+v"(x[ks].x), "+v"(x[ks].y), "+v"(x[ks].z), "+v"(x[ks].w));
       };
-      repack(dor);
-      const int z_at = 2 * g + opaque_zero();
+      repack(bq);
+      const int z_at = 2 * ql + opaque_zero();
       auto z8 = [&](int ks, float (&z)[8]) {
-        const float4 a = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks], b = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks + 1];
+        const float4 a = reinterpret_cast<const float4*>(sZ)[z_at + 8 * ks], b = reinterpret_cast<const float4*>(sZ)[z_at + 8 * ks + 1];
         z[0] = a.x; z[1] = a.y; z[2] = a.z; z[3] = a.w; z[4] = b.x; z[5] = b.y; z[6] = b.z; z[7] = b.w;
       };
-      float A[2] = {0.f, 0.f}, Z[2] = {0.f, 0.f};
+      float a_sum = 0.f, Z = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
+      for (int ks = 0; ks < K::KS; ++ks) {
         float f[8], z[8];
         unpack_bf16x8(xq[ks], f);
         z8(ks, z);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          A[e % 2] = fmaf(ga[ks / 2][8 * (ks % 2) + e], f[e], A[e % 2]);
-          Z[e % 2] = fmaf(z[e], f[e], Z[e % 2]);
+          a_sum = fmaf(ga[2 * ks + e / 4][e % 4], f[e], a_sum);
+          Z = fmaf(z[e], f[e], Z);
         }
       }
       repack(xq);
-      pair32(A[0] + A[1], lo, hi); const float a_sum = lo + hi;
-      pair32(Z[0] + Z[1], lo, hi);
-      const float inv_den = __builtin_amdgcn_rcpf((lo + hi) + kReluEps);
+      quad2<SumOp>(a_sum, Z);
+      const float inv_den = __builtin_amdgcn_rcpf(Z + kReluEps);
       // 1 / (scale * stok * den); scale and stok are powers of two
-      const float r1 = (inv_den * __builtin_amdgcn_rcpf(scale)) * __builtin_amdgcn_rcpf(stok);
+      const float r1 = (inv_den * __builtin_amdgcn_rcpf(scale)) * istok;
       const float delta = a_sum * r1;
       {
         // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
-        float m = live ? fmaxf(dmax, fabsf(delta)) * inv_den : 0.f;
-        m = wave_max_paired(m);
-        if (lane == 0) sRed[pw] = m;
+        const float m = row_max_mag(fmaxf(live ? fmaxf(dmax, fabsf(delta)) * inv_den : 0.f, 0.f));
+        if (lane == 0) sRed[w] = m;
       }
       __syncthreads();                                   // the previous tile has been read
       next_gamma();
       {
-        const int lz = lane + opaque_zero();
-        const int row = 32 * pw + lz % 32, psw = swz<D>(row), gz = lz / 32;
+        const unsigned lz = opaque_lane(lane);
+        const int row = 16 * w + lz % 16, psw = swz<D>(lz % 16), qz = lz / 16;
         char* rowp = sPhi + row * RS;
         char* drowp = sDO + row * RS;
-        const float sc = live ? inv_den * gamma : 0.f;
+        // (a gradient that is not finite makes the sums NaN)
+        const float sc = live ? inv_den * gamma : 0.f, so = sc * istok + (dmax - dmax);
 #pragma unroll
-        for (int ks = 0; ks < C::UK; ++ks) {
-          uint4 a = make_uint4(bf16x2_to_f16x2(xq[ks].x), bf16x2_to_f16x2(xq[ks].y), bf16x2_to_f16x2(xq[ks].z), bf16x2_to_f16x2(xq[ks].w));
-          if (!live) a = make_uint4(0, 0, 0, 0);
-          *reinterpret_cast<uint4*>(rowp + (((2 * ks + gz) ^ psw) * 16)) = a;
-          float f[8];
-          unpack_bf16x8(dor[ks], f);
-          *reinterpret_cast<uint4*>(drowp + (((2 * ks + gz) ^ psw) * 16)) =
-              make_uint4(pack_f16x2(f[0] * sc, f[1] * sc), pack_f16x2(f[2] * sc, f[3] * sc),
-                         pack_f16x2(f[4] * sc, f[5] * sc), pack_f16x2(f[6] * sc, f[7] * sc));
+        for (int ks = 0; ks < K::KS; ++ks) {
+          *reinterpret_cast<uint4*>(rowp + (((4 * ks + qz) ^ psw) * 16)) =
+              make_uint4(bf16x2_to_f16x2(xq[ks].x), bf16x2_to_f16x2(xq[ks].y), bf16x2_to_f16x2(xq[ks].z), bf16x2_to_f16x2(xq[ks].w));
+          *reinterpret_cast<uint4*>(drowp + (((4 * ks + qz) ^ psw) * 16)) =
+              make_uint4(mul_pack_f16x2(bq[ks].x, so, zero), mul_pack_f16x2(bq[ks].y, so, zero), mul_pack_f16x2(bq[ks].z, so, zero),
+                         mul_pack_f16x2(bq[ks].w, so, zero));
         }
-        if (g == 0) sW16[row] = (uint16_t)(pack_f16x2(live ? -delta * sc : 0.f, 0.f) & 0xffffu);
+        if (lane < 16) sW16[row] = (uint16_t)(pack_f16x2(live ? -delta * sc : 0.f, 0.f) & 0xffffu);
       }
       repack(xq);
       // the next tile's rows, before the dq stores: loads and stores retire in order
-      const int next = tile + P < ntile ? tile + P : tile;
-      load(qb, next, xn);
-      load(dob, next, dor);
+      qrows.load(xn, t0 + P * kTile);
+      drows.load(dor, t0 + P * kTile);
       __syncthreads();
       // dq = (G - delta z) / den where q > 0
       const float r2 = inv_den * delta;
-      const RowStore<D> out{sOut + pw * 32 * RS, lane + opaque_zero()};
+      const RowStore<D> out{sOut + w * 16 * RS, (int)opaque_lane(lane)};
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
+      for (int ks = 0; ks < K::KS; ++ks) {
         float f[8], z[8], v[8];
         unpack_bf16x8(xq[ks], f);
         z8(ks, z);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], r1, -(r2 * z[e])) : 0.f;
+        for (int e = 0; e < 8; ++e) v[e] = f[e] > 0.f ? fmaf(ga[2 * ks + e / 4][e % 4], r1, -(r2 * z[e])) : 0.f;
         out.put(ks, make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])));
       }
-      out.template flush<STREAM>(dqb, rw.sn, tile * kTile + 32 * pw, n);
+      out.template flush<STREAM>(dqb, rw.sn, t0, n);
     }
   } else {
     f32x16 s[WMN][WMN], zacc;
@@ -476,7 +454,8 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
 #pragma unroll
         for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
     }
-    const Quadrant<D> qd(pw);
+    const int g = lane / 32;
+    const Quadrant<D> qd(w - NTOK);
     const QuadrantReads<D> rd(qd, sPhi, sDO, lane);
     for (int tile = p; tile < ntile; tile += P) {
       __syncthreads();
@@ -515,85 +494,75 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
 }
 
 // ---- key side of the backward ---------------------------------------------------------------------
-// grid (KP, BH), 8 wavefronts, each on its own 32-token blocks: dv = phi(k) dS with the tokens on the accumulator rows, and
-// g = v dS^T + dz with the tokens on the columns (relu_grad), dk = g where k > 0 in the pieces in which k came.  88 us at 12 heads x 32760 x
-// 128, dk non-temporal and dv not (81 + 9 for the images in a kernel of their own, with k read twice); the rows take 69 us at the memory's rate.  The next block's
-// rows requested a block ahead: 93 us.
-constexpr int NTK = 512;
-template <int D, bool STREAM>
+// Wavefronts on 16-token blocks of their own: dv = phi(k) dS with the tokens on the accumulator rows, and
+// g = v dS^T + dz with the tokens on the columns (relu_grad), dk = g where k > 0 in the pieces in which k came.
+// NTK: 12 wavefronts where a workgroup has several rounds of width 128, else 8, whose prologue is the shorter: 8 / 12 / 16 wavefronts, us, 12 heads x 32760 x
+// 128 80.4 / 77.5 / 82.6, 4 x 1000 x 128 8.3 / 9.6 / 11.3, 12 x 16000 x 64 21.7 / 22.3 / 22.7, 12 x 4133 x 64 9.7 / 9.95 / 9.75.  (Eight wavefronts of 32 tokens: 88.6,
+// 15.1, 23.7 and 10.8; the rows take 69 at 12 x 32760 x 128.)
+template <int D, bool STREAM, int NTK>
 __global__ __launch_bounds__(NTK) void relu_bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                          const float* __restrict__ dstate, const float* __restrict__ mean_row,
                                                          uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                          int H, int n, Rows rw) {
-  using C = Cfg<D>;
-  using L = ApplyLayout<D>;
-  using G = GradLayout<D>;
+  using K = Tok16<D>;
   constexpr int NW = NTK / 64;
   extern __shared__ uint4 smem[];
-  uint4* sC = smem;                                        // [KS][MB][64] image of dS for dv
-  uint4* sG = sC + L::KS * L::MB * 64;                     // image of dS for g
-  float* sZ = reinterpret_cast<float*>(sG + G::IMG);       // [D] dzc
+  uint4* sC = smem;                                        // image of dS for dv
+  uint4* sG = sC + K::A_IMG;                               // image of dS for g
+  float* sZ = reinterpret_cast<float*>(sG + K::G_IMG);     // [D] dzc
   float* sRed = sZ + D;                                    // [NW]
-  char* sOut = reinterpret_cast<char*>(sRed + NW);         // [NW][32][D] bf16: RowStore
+  char* sOut = reinterpret_cast<char*>(sRed + NW);         // [NW][16][D] bf16: RowStore
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int g = lane / 32;
+  const int ql = lane / 16;
   const int bh = blockIdx.y;
-  const uint16_t* kb = k + head_base(rw, bh, H);
-  const uint16_t* vb = v + head_base(rw, bh, H);
   uint16_t* dkb = dk + head_base(rw, bh, H);
   uint16_t* dvb = dv + head_base(rw, bh, H);
+  const LoadRows16<D> krows(k + head_base(rw, bh, H), rw.sn, n, lane), vrows(v + head_base(rw, bh, H), rw.sn, n, lane);
   const float scale = build_relu_key_state<D, NTK>(dstate + (size_t)bh * (D + 1) * D, sC, sG, sZ, sRed, mean_row + (size_t)bh * D, tid);
   const float inv_scale = __builtin_amdgcn_rcpf(scale);    // exact: power of two
   __syncthreads();
 
-  const int nblk = (n + 31) / 32;
-  const int stride = gridDim.x * NW;
-  for (int b = blockIdx.x * NW + w; b < nblk; b += stride) {
-    const int t = b * 32 + (lane % 32);
-    const size_t at = (size_t)(t < n ? t : n - 1) * rw.sn;   // rows past n: row n - 1 once more, the same bits
-    uint4 xk[C::UK], xv[C::UK];
+  const int step = 16 * NW * gridDim.x;
+  for (int t0 = 16 * (blockIdx.x * NW + w); t0 < n; t0 += step) {
+    uint4 xk[K::KS], xv[K::KS];
+    krows.load(xk, t0);
+    vrows.load(xv, t0);
     {
-      const uint4* row = reinterpret_cast<const uint4*>(kb + at);
-      const uint4* vrow = reinterpret_cast<const uint4*>(vb + at);
+      f32x4 va[K::MB];
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) { xk[ks] = row[2 * ks + g]; xv[ks] = vrow[2 * ks + g]; }
-    }
-    {
-      f32x16 va[L::MB];
-#pragma unroll
-      for (int mb = 0; mb < L::MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) va[mb][r] = 0.f;
+      for (int mb = 0; mb < K::MB; ++mb) va[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
       const uint4* sc = sC + lane + opaque_zero();
-#pragma unroll
-      for (int ks = 0; ks < L::KS; ++ks) {
-        const f16x8 aop = as_f16x8(relu_f16x8(xk[ks]));
-#pragma unroll
-        for (int mb = 0; mb < L::MB; ++mb)
-          va[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, as_f16x8(sc[(ks * L::MB + mb) * 64]), va[mb], 0, 0, 0);
-      }
-      store_token_rows<D, false>(dvb, rw.sn, b * 32, n, lane, va, inv_scale);
+      uint4 a;
+      pipelined_operands<K::KS * K::MB, 3>([&](int i) { return sc[i * 64]; },
+                                           [&](int i, uint4 b) {
+                                             if (i % K::MB == 0) a = relu_f16x8(xk[i / K::MB]);
+                                             va[i % K::MB] = mfma_f16_16(a, b, va[i % K::MB]);
+                                           });
+      const float none[K::MB] = {};
+      store_token_rows16<D, false, false>(dvb, rw.sn, t0, n, lane, va, inv_scale, none);
     }
     {
-      f32x16 ga[G::GM];
-      relu_grad<D, 0>(sG, lane, [&](int ks) {
-        return make_uint4(bf16x2_to_f16x2(xv[ks].x), bf16x2_to_f16x2(xv[ks].y), bf16x2_to_f16x2(xv[ks].z), bf16x2_to_f16x2(xv[ks].w));
-      }, ga);
-      const RowStore<D> out{sOut + w * 32 * D * 2, lane + opaque_zero()};
-      const int z_at = 2 * g + opaque_zero();
+      uint4 y[K::KS];
 #pragma unroll
-      for (int ks = 0; ks < C::UK; ++ks) {
-        const float4 za = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks], zb = reinterpret_cast<const float4*>(sZ)[z_at + 4 * ks + 1];
+      for (int ks = 0; ks < K::KS; ++ks)
+        y[ks] = make_uint4(bf16x2_to_f16x2(xv[ks].x), bf16x2_to_f16x2(xv[ks].y), bf16x2_to_f16x2(xv[ks].z), bf16x2_to_f16x2(xv[ks].w));
+      f32x4 ga[K::GB];
+      relu_grad<D, 3>(sG, lane, y, ga);
+      const RowStore<D> out{sOut + w * 16 * D * 2, (int)opaque_lane(lane)};
+      const int z_at = 2 * ql + opaque_zero();
+#pragma unroll
+      for (int ks = 0; ks < K::KS; ++ks) {
+        const float4 za = reinterpret_cast<const float4*>(sZ)[z_at + 8 * ks], zb = reinterpret_cast<const float4*>(sZ)[z_at + 8 * ks + 1];
         const float z[8] = {za.x, za.y, za.z, za.w, zb.x, zb.y, zb.z, zb.w};
         float f[8], u[8];
         unpack_bf16x8(xk[ks], f);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = f[e] > 0.f ? fmaf(ga[ks / 2][8 * (ks % 2) + e], inv_scale, z[e]) : 0.f;
+        for (int e = 0; e < 8; ++e) u[e] = f[e] > 0.f ? fmaf(ga[2 * ks + e / 4][e % 4], inv_scale, z[e]) : 0.f;
         out.put(ks, make_uint4(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]), pack_bf16x2(u[4], u[5]), pack_bf16x2(u[6], u[7])));
       }
-      out.template flush<STREAM>(dkb, rw.sn, b * 32, n);
+      out.template flush<STREAM>(dkb, rw.sn, t0, n);
     }
   }
 }
@@ -602,12 +571,11 @@ template <int D>
 constexpr size_t state_smem() { return 2 * (size_t)kTile * D * 2; }
 template <int D>
 constexpr size_t q_smem() {
-  return sizeof(uint4) * GradLayout<D>::IMG + 3 * (size_t)kTile * D * 2 + kTile * 2 + (D + 4) * sizeof(float);
+  return sizeof(uint4) * Tok16<D>::G_IMG + 3 * (size_t)kTile * D * 2 + kTile * 2 + (D + kTile / 16) * sizeof(float);
 }
-template <int D>
+template <int D, int NTK>
 constexpr size_t k_smem() {
-  return sizeof(uint4) * (ApplyLayout<D>::KS * ApplyLayout<D>::MB * 64 + GradLayout<D>::IMG) + (D + NTK / 64) * sizeof(float)
-       + (NTK / 64) * 32 * (size_t)D * 2;
+  return sizeof(uint4) * (Tok16<D>::A_IMG + Tok16<D>::G_IMG) + (D + NTK / 64) * sizeof(float) + (NTK / 64) * 16 * (size_t)D * 2;
 }
 
 template <int D>
@@ -619,6 +587,17 @@ hipError_t run_state(const void* k, const void* v, float* partials, const Plan& 
   return hipGetLastError();
 }
 
+template <int D, bool STREAM, int NTK>
+hipError_t run_bwd_k(const BwdArgs& a, const Plan& p, int per_head, hipStream_t s) {
+  constexpr size_t smem = k_smem<D, NTK>();
+  const hipError_t e = set_smem_once<relu_bwd_k_kernel<D, STREAM, NTK>>(smem);
+  if (e != hipSuccess) return e;
+  const int units = (p.n + NTK / 4 - 1) / (NTK / 4);       // 16 tokens a wavefront
+  relu_bwd_k_kernel<D, STREAM, NTK><<<dim3(units < per_head ? units : per_head, p.BH), NTK, smem, s>>>(
+      (const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar, (uint16_t*)a.dk, (uint16_t*)a.dv, p.H, p.n, p.rows);
+  return hipGetLastError();
+}
+
 template <int D, bool STREAM>
 hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
   hipError_t e;
@@ -627,10 +606,10 @@ hipError_t run_bwd(const BwdArgs& a, const Plan& p, hipStream_t s) {
                                                                 (uint16_t*)a.dq, a.partials, p.H, p.n, p.P, p.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{}, s)) != hipSuccess) return e;
-  if ((e = set_smem_once<relu_bwd_k_kernel<D, STREAM>>(k_smem<D>())) != hipSuccess) return e;
-  relu_bwd_k_kernel<D, STREAM><<<dim3(p.KP, p.BH), NTK, k_smem<D>(), s>>>((const uint16_t*)a.k, (const uint16_t*)a.v, a.dstate, a.vbar,
-                                                                 (uint16_t*)a.dk, (uint16_t*)a.dv, p.H, p.n, p.rows);
-  return hipGetLastError();
+  const int per_head = p.BH < kCUs ? kCUs / p.BH : 1;
+  if constexpr (D == 128)
+    if ((p.n + 191) / 192 > per_head) return run_bwd_k<D, STREAM, 768>(a, p, per_head, s);
+  return run_bwd_k<D, STREAM, 512>(a, p, per_head, s);
 }
 
 }  // namespace
