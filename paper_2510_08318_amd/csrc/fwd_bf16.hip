@@ -432,11 +432,17 @@ __device__ __forceinline__ void state_segment(const uint16_t* __restrict__ kb, c
 #pragma unroll
         for (int j = 0; j < WMN; ++j) s[i][j][r] = 0.f;
     auto fblk = [&](int i) { return mi * WMN + ((WMN == 2) ? (i ^ ni) : i); };
+    // (tr_offset_g4 by its definition: from its exclusive-or form the accumulate loop has 28 vector instructions fewer a tile, the phi wavefronts of its SIMD
+    // fall behind, and the pass takes 294 us in place of 289 at 40 heads x 75600 x 128, 50.3 / 49.6 at 12 x 32760)
     int offB[WMN][2];
 #pragma unroll
     for (int i = 0; i < WMN; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) offB[i][j] = tr_offset_g4<D>(32 * (ni * WMN + i), lane, j) + kTile * RS;
+      for (int j = 0; j < 2; ++j) {
+        const int r = 4 * (lane / 32) + ((lane % 16) / 4) + 8 * j;
+        const int col = 32 * (ni * WMN + i) + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+        offB[i][j] = r * RS + (((col / 8) ^ swz<D>(r)) * 16) + (col % 8) * 2 + kTile * RS;
+      }
     auto load_v = [&](uint4 (&vr)[VPT], int tile) {
       const int t0 = tile * kTile;
 #pragma unroll
