@@ -182,7 +182,7 @@ struct DwTile {
   static constexpr int RB = (D / 32) * NB >= NW ? (D / 32) * NB / NW : 1;   // row blocks per wavefront
   static constexpr int BPT = kTile / BLK;                  // du blocks (each with a scale of its own) per parked tile
   static constexpr int KSN = kTile / 16;
-  static constexpr int KBATCH = NW > 4 ? KSN / 2 : KSN / 4;     // k-steps whose operands are in flight together
+  static constexpr int KBATCH = D == 64 ? KSN : KSN / 4;        // k-steps whose operands are in flight together
   static constexpr int DU_BYTES = kTile * RSU;
   f32x16 acc[RB];
   float gamma;
@@ -266,7 +266,7 @@ struct DwTile {
 template <int D, bool SUMS>
 __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x16 (&s)[D / 64][D / 64], float& z, const float* w, const float* f,
                                                 float (&csum)[D / 64], float& wsum) {
-  constexpr int RS = D * 2, WMN = D / 64, KSN = kTile / 16;
+  constexpr int RS = D * 2, WMN = D / 64, KSN = kTile / 16, AHEAD = D == 64 ? 4 : 1;
   f16x8 a[KSN][WMN], b[KSN][WMN];
   auto request = [&](int kn) {
 #pragma unroll
@@ -274,7 +274,8 @@ __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x
 #pragma unroll
     for (int j = 0; j < WMN; ++j) b[kn][j] = read_tr(rd.b[j][0] + kn * 16 * RS, rd.b[j][1] + kn * 16 * RS);
   };
-  request(0);
+#pragma unroll
+  for (int ks = 0; ks < AHEAD; ++ks) request(ks);
 #pragma unroll
   for (int ks = 0; ks < KSN; ++ks) {
     float4 wv[2], fv[2];
@@ -283,7 +284,7 @@ __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x
       wv[i] = *reinterpret_cast<const float4*>(w + 16 * ks + 4 * i);
       if constexpr (SUMS) fv[i] = *reinterpret_cast<const float4*>(f + 16 * ks + 4 * i);
     }
-    if (ks + 1 < KSN) request(ks + 1);
+    if (ks + AHEAD < KSN) request(ks + AHEAD);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < WMN; ++i)
@@ -314,6 +315,10 @@ __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x
 // LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use.
 constexpr int QAHEAD = 4;
 constexpr int NTQ = 768;     // 12 wavefronts, one workgroup per compute unit
+// DW: whether a tile's q rows have a place of their own in LDS.  Else (width 128, whose images and tiles fill it) they take phi's when dS has read it, with one
+// more barrier to a tile.
+template <int D>
+constexpr bool kOwnX = D == 64;
 // BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
 // asked for, and the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
 // wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
@@ -360,6 +365,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   float* sZ = sVb + D;                                     // [D] z, unscaled
   float* sRed = sZ + D;                                    // [16]: 0..7 the tile's operand maxima, 8..15 the du blocks' inverse scales
   char* sDU = reinterpret_cast<char*>(sRed + 16);          // DW: the tile's du, [kTile][D/2] fp16
+  char* sX = kOwnX<D> ? sDU + DWT::DU_BYTES : sPhi;        // DW: its q rows
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int w = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -546,8 +552,8 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         store_token_rows16<D, STREAM, false>(dqb, rw.sn, t0, n, lane, xa, its, none);
       }
       if constexpr (DW) {
-        __syncthreads();                                 // dS has read the tile's phi
-        park_dw16<D>(xr, dub, blk_its, sPhi, sDU, sRed + 8, w, lane);
+        if constexpr (!kOwnX<D>) __syncthreads();        // dS has read the tile's phi
+        park_dw16<D>(xr, dub, blk_its, sX, sDU, sRed + 8, w, lane);
         __syncthreads();
       }
     }
@@ -624,9 +630,9 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       __syncthreads();
       contract_tokens<D, CENTRE>(rd, s, zacc, sW + 8 * (lz / 32), sF + 8 * (lz / 32), csum, wsum);
       if constexpr (DW) {
+        if constexpr (!kOwnX<D>) __syncthreads();
         __syncthreads();
-        __syncthreads();
-        dwt.contract(sPhi, sDU, sRed + 8, opaque_lane(lane));
+        dwt.contract(sX, sDU, sRed + 8, opaque_lane(lane));
       }
     }
     if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
@@ -846,7 +852,7 @@ __global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint1
 template <int D, bool DW>
 constexpr size_t q_smem() {
   return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG)
-       + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4, 16>::DU_BYTES : 0);
+       + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4, 16>::DU_BYTES + (kOwnX<D> ? (size_t)kTile * D * 2 : 0) : 0);
 }
 template <int D, bool DW>
 constexpr size_t k_smem() {
