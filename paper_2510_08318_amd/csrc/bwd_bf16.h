@@ -166,7 +166,7 @@ __device__ __forceinline__ float build_key_state(StateRegs<D, NTHREADS>& S, floa
 
 // ---- dW~ = sum_i x_i^T du_i, accumulated inside the kernels that make du ---------------------
 // The workgroup parks 128 tokens in LDS as two fp16 tiles, x [kTile][D] and du [kTile][D/2] (rows swizzled
-// like the phi tile; a 32-token block of du carries the power-of-two scale du_to_dx gave it, with the
+// like the phi tile; a 16-token block of du carries the power-of-two scale du_to_dx16 gave it, with the
 // inverse scales beside the tile).  Its NW wavefronts then contract over the tokens with transposing
 // reads of both tiles: wavefront w owns the feature block w % NB and RB 32-channel row blocks and brings
 // the blocks to one common power-of-two scale that follows the running maximum of the workgroup
@@ -499,8 +499,10 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         char* rowp = sPhi + row * RS;
         // The weight of the token is in phi, which is rounded anyway; dO, scaled by powers of two only, enters exactly.  (With the weight in dO
         // both operands were rounded, half of the variance of dS.)
-        // (A token whose dO vanishes, or flushes in fp16, may have any f that phi f holds; one whose dO is not finite makes the sums NaN.)
-        const float f = valid ? fminf(inv_den * gamma * om * istok, 64.f) + (dmax - dmax) : 0.f;
+        // A token whose dO vanishes or flushes in fp16 may have any f that phi f holds.  Above 64 otherwise f stands for a |dO| / den past the largest fp32,
+        // for which gamma makes no room: the sums become NaN, as for a dO that is not finite.
+        const float f0 = inv_den * gamma * om * istok;
+        const float f = valid ? (f0 <= 64.f ? f0 : dmax < 0x1p-100f ? 64.f : __builtin_nanf("")) + (dmax - dmax) : 0.f;
         // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
         // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
         const float fp = f * ip, fm = f * im, c0 = CENTRE ? -mean * f : zero;

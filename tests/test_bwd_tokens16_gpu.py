@@ -76,3 +76,18 @@ def test_key_side_lengths(n, H, d, wgrads):
         assert O.err_metric(got["dv"], dv)[0] <= 1e-2 and np.abs(got["dk"]).max() <= 1e-2 * np.abs(dv).max()
         return
     _check(x, wgrads=wgrads)
+
+
+@pytest.mark.parametrize("scale", [1e36, 3e38])
+def test_gradients_whose_quotient_by_the_normaliser_passes_fp32(scale):
+    """One token: den = phi(q) . phi(k) is far below 1, |dO| / den above the largest fp32 for the larger of the two.  dv = dO there; what cannot
+    be summed must not come out finite and wrong."""
+    x = synth.generate("C5", n=1, H=4, B=1, d=128, dtype="bf16")
+    do = np.sign(O.to_f64(x.dout).astype(np.float32)) * np.float32(scale)
+    x.dout = synth._pack(do, x.dtype)
+    dv = _run(x, False, False)["dv"]
+    ref = O.to_f64(x.dout)
+    for h in range(4):
+        assert not np.isfinite(dv[0, h]).all() or O.err_metric(dv[:, h:h + 1], ref[:, h:h + 1])[0] <= 1e-2
+    if scale == 1e36:
+        assert O.err_metric(dv, ref)[0] <= 1e-2
