@@ -13,9 +13,10 @@
 //
 // Precision: every 16-bit MFMA operand except the stored bf16 q, k (projection) is fp16.
 // Operands that belong to one token or block only (dO_i for g_i, du_i for dx_i) are scaled by a
-// power of two taken from their largest magnitude, so any gradient scale is safe; bf16 values scaled so are exact in fp16.  In the sums over
-// tokens the weight 1/den_i goes into phi_i, with one power of two per workgroup that follows the running maximum of |dO_i|/den_i over its
-// tiles (largest magnitude so far in [16, 32)), and du for dW~ is scaled likewise;
+// power of two taken from their largest magnitude, so any gradient scale is safe; bf16 values scaled so are exact in fp16 (in dO_i
+// with a factor of up to three bits beside it).  In the sums over
+// tokens the weight 1/den_i goes into phi_i (where phi's roundings have too much in common into dO_i, see kSharedRounding), with one power of two per
+// workgroup that follows the running maximum of |dO_i|/den_i over its tiles (largest magnitude so far in [16, 32)), and du for dW~ is scaled likewise;
 // when a tile raises the maximum the fp32 accumulators are rescaled by the exact ratio, so neither a
 // late large tile nor leading all-zero tiles can overflow or flush fp16.  delta enters dz in fp32.  Accumulation is fp32 everywhere; partial
 // sums are combined in a fixed order.
@@ -256,9 +257,12 @@ struct DwTile {
   }
 };
 
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ float uniform(float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); }
+
 // ---- sums over the tokens of a tile ----------------------------------------------------------
-// A 128-token tile of dS and dz: s[i][j] += P_i^T Y_j with P = phi f (per token f = (1 - r') / (den stok), times the running scale) and Y = stok dO as fp16
-// tiles [kTile][D] in LDS, and z += P_0 . w with w = -stok delta in fp32, feature lane%32 of the first block over the tokens that the lane
+// A 128-token tile of dS and dz: s[i][j] += P_i^T Y_j with P = kPhiUnit f phi and Y = y stok dO as fp16 tiles [kTile][D] in LDS (per token f y = (1 - r') / (den stok),
+// times the running scale), and z += P_0 . w with w = -y stok delta in fp32, feature lane%32 of the first block over the tokens that the lane
 // holds (eight of a k-step; the lane 32 further has the others): as MFMA blocks the z sums took a fifth of the MFMAs and 16 registers.
 // The operands of k-step ks+1 are requested before the MFMAs of k-step ks.
 // SUMS (centred): also csum[j] += sum f Y, the lane's column of block j, and wsum += sum f w, over the same tokens.
@@ -311,6 +315,37 @@ __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x
   }
 }
 
+// What phi enters that sum with: a power of two that keeps small features out of the fp16 subnormals (f is at most 32).
+constexpr float kPhiUnit = 0x1p10f;
+// The relative error of phi . z from rounded phi above which a token's weight is formed with it.  A single feature's rounding gives up to 2^-11; tokens of
+// ordinary maps stay below (rms 3e-5, of sharp ones with a feature of 0.2 of den 6e-5), and 1.7e-4 in four ways of rounding is what the other operands'
+// roundings leave of tokens with the same query.  dS of such heads, rms: 2e-4 without, 7e-5 now, and 6e-5 with the normaliser from rounded phi for every token,
+// which has the weight in dO and rounds both operands.  It costs 1 % of a training step (bwd_q 12 heads x 32760 x 128 with dW~ 94 -> 97 us).
+constexpr float kSharedRounding = 0x1.6p-13f;
+
+// z in fp16 pieces, as the A operands of the product that gives the token wavefronts phi . z from phi in fp16: piece r of scale * z, 12 bits
+// below the one before it, in the rows 4q + r, so that a lane receives its token's four sums in its four accumulator registers and no exchange is needed.
+template <int D>
+struct ZPieces {
+  using K = Tok16<D>;
+  static constexpr int IMG = 2 * K::DK * 16;      // uint4 entries: (ks, q, r), eight features as in Tok16
+  // z is at most n in each feature (and a sum of states over a few thousand devices fits)
+  static __device__ __forceinline__ float scale(int n) { return 16.f * pow2_normaliser((float)n); }
+  static __device__ __forceinline__ void write(const float* z, uint4* img, float sc, int tid) {      // at least 8*IMG threads
+    if (tid >= 8 * IMG) return;
+    const int e = tid % 8, r = tid / 8 % 4, q = tid / 32 % 4, ks = tid / 128;
+    float left = sc * z[ks / K::DK * K::HALF + q * K::FL + 8 * (ks % K::DK) + e], piece = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      piece = i <= r ? (float)(_Float16)left : piece;
+      left = (left - piece) * 0x1p12f;
+    }
+    reinterpret_cast<_Float16*>(img)[tid] = (_Float16)piece;
+  }
+  static __device__ __forceinline__ uint4 operand(const uint4* img, int ks, unsigned lane) { return img[16 * ks + 4 * (lane / 16) + lane % 4]; }
+  static __device__ __forceinline__ float sum(const f32x4& s) { return fmaf(fmaf(fmaf(s[3], 0x1p-12f, s[2]), 0x1p-12f, s[1]), 0x1p-12f, s[0]); }
+};
+
 // ---- query side --------------------------------------------------------------------------
 // LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use.
 constexpr int QAHEAD = 4;
@@ -357,9 +392,10 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   uint4* sWA = smem;
   uint4* sGA = sWA + K::W_IMG;
   uint4* sWB = sGA + K::G_IMG;
-  char* sPhi = reinterpret_cast<char*>(sWB + K::T_IMG);    // [kTile][D] fp16: f phi(q) (CENTRE: f (phi(q) - 2/D)), then (DW) the q rows
-  char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: stok dO
-  float* sW = reinterpret_cast<float*>(sDO + kTile * RS);  // [kTile] -stok delta
+  uint4* sZP = sWB + K::T_IMG;                             // z in fp16 pieces (ZPieces)
+  char* sPhi = reinterpret_cast<char*>(sZP + ZPieces<D>::IMG);      // [kTile][D] fp16: kPhiUnit f phi(q) (CENTRE: phi(q) - 2/D), then (DW) the q rows
+  char* sDO = sPhi + kTile * RS;                           // [kTile][D] fp16: y stok dO
+  float* sW = reinterpret_cast<float*>(sDO + kTile * RS);  // [kTile] -y stok delta
   float* sF = sW + kTile;                                  // [kTile] f (CENTRE)
   float* sVb = sF + kTile;                                 // [D] vbar (DR)
   float* sZ = sVb + D;                                     // [D] z, unscaled
@@ -388,6 +424,8 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     scale = build_query_state<D, NTQ>(S, z, sGA, sZ, reinterpret_cast<float*>(sPhi), p == 0 ? vbar + (size_t)bh * D : nullptr, tid);
   }
   if (DR && tid < D) sVb[tid] = reinterpret_cast<const float*>(sPhi)[D / 8 * D + tid];
+  const float zs = ZPieces<D>::scale(n);
+  ZPieces<D>::write(sZ, sZP, zs, tid);
   __syncthreads();
 
   // running power-of-two scale of the sums over tokens, the same in every wavefront; returns the factor for the accumulators
@@ -408,8 +446,17 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     uint16_t* dqb = dq + head_base(rw, bh, H);
     uint4 xq[K::KS], xr[K::KS], dor[K::KS];
     const float zero = opaque_zero_scalar();
+    const float unit_z = uniform(__builtin_amdgcn_rcpf(kPhiUnit * zs));      // exact
     const LoadRows16<D> qrows(q + head_base(rw, bh, H), rw.sn, n, lane), drows(dout + head_base(rw, bh, H), rw.sn, n, lane);
     qrows.load(xq, p * kTile + 16 * w);
+    uint4 zop[2 * K::DK];
+#pragma unroll
+    for (int ks = 0; ks < 2 * K::DK; ++ks) zop[ks] = ZPieces<D>::operand(sZP, ks, lane);
+    float z_mean = 0.f;                                  // mean * the sum of z
+    if constexpr (CENTRE) {
+      for (int j = 0; j < D / 64; ++j) z_mean += sZ[64 * j + lane];
+      z_mean = uniform(mean * quad<SumOp>(row_sum(z_mean)));
+    }
     // the first rows have arrived before the loop: with them still out, the compiler's wait at the top of a tile, which has to hold
     // for the first tile too, would be a wait for the previous tile's stores
     qrows.arrived(xq);
@@ -425,6 +472,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       }
       float ep[K::FL], em[K::FL], ip, im;
       softmax16<D>(u, ep, em, ip, im);
+      __builtin_amdgcn_sched_barrier(0);                   // (nothing waits for dO any earlier)
       // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that
       float dmax, stok;
       uint4 bq[K::KS];
@@ -437,7 +485,9 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         for (int ks = 0; ks < K::KS; ++ks) { take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w); }
         const uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
         dmax = quad<MagOp>(__builtin_bit_cast(float, m << 16));
-        stok = pow2_normaliser(fminf(dmax, kTokenMax));
+        // (times 1, 1.25, 1.5 or 1.75, eight bits times three: still exact.  The weight that goes into phi is divided by it, so that tokens whose queries are
+        // alike round in four ways)
+        stok = pow2_normaliser(fminf(dmax, kTokenMax)) * fmaf((float)(((uint32_t)(t0 + lane % 16) * 0x165667b1u) >> 30), 0.25f, 1.f);
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) {
           float f[8];
@@ -446,7 +496,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
                               mul_pack_f16x2(f[4], f[5], stok, zero), mul_pack_f16x2(f[6], f[7], stok, zero));
         }
       }
-      const float istok = __builtin_amdgcn_rcpf(stok);     // exact
+      const float istok = __builtin_amdgcn_rcpf(stok);
 
       // G = dO S^T (times scale * stok), rows laid out like phi
       f32x4 ga[K::GB];
@@ -477,7 +527,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       float own = ap + am;                                 // this lane's share
       quad4<SumOp>(ap, am, Zp, Zm);
       const float inv_den = __builtin_amdgcn_rcpf(Zp + Zm);
-      // 1 / (scale * stok * den), in an order that keeps in range what is; scale and stok are powers of two
+      // 1 / (scale * stok * den), in an order that keeps in range what is; scale is a power of two
       const float r0 = inv_den * __builtin_amdgcn_rcpf(scale) * istok;
       if constexpr (DR) {
         // the -dout . o part of dout . (s - o), this lane's share; the images are centred, so o here is
@@ -497,29 +547,49 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         const unsigned lz = opaque_lane(lane);
         const int row = 16 * w + lz % 16, psw = swz<D>(lz % 16), qz = lz / 16;
         char* rowp = sPhi + row * RS;
-        // The weight of the token is in phi, which is rounded anyway; dO, scaled by powers of two only, enters exactly.  (With the weight in dO
-        // both operands were rounded, half of the variance of dS.)
-        // A token whose dO vanishes or flushes in fp16 may have any f that phi f holds.  Above 64 otherwise f stands for a |dO| / den past the largest fp32,
-        // for which gamma makes no room: the sums become NaN, as for a dO that is not finite.
-        const float f0 = inv_den * gamma * om * istok;
-        const float f = valid ? (f0 <= 64.f ? f0 : dmax < 0x1p-100f ? 64.f : __builtin_nanf("")) + (dmax - dmax) : 0.f;
-        // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
-        // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
-        const float fp = f * ip, fm = f * im, c0 = CENTRE ? -mean * f : zero;
-        auto pack8 = [&](const float* e, float m) {
-          return make_uint4(mul_pack_f16x2(e[0], e[1], m, c0), mul_pack_f16x2(e[2], e[3], m, c0), mul_pack_f16x2(e[4], e[5], m, c0),
-                            mul_pack_f16x2(e[6], e[7], m, c0));
-        };
+        // The weight of the token, (1 - r') / den times the running scale, goes into phi, which is rounded anyway, and dO enters exactly.  (With the weight in
+        // dO both operands are rounded, twice the variance of dS.)  A token whose dO vanishes or flushes in fp16 has none.
+        const float wt = dmax < 0x1p-100f ? 0.f : inv_den * om * gamma * istok + (dmax - dmax);
+        auto park_phi = [&](float f) {                   // the packed features; returns their sum over z / f
+          // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
+          // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side
+          const float fu = kPhiUnit * f, up = fu * ip, um = fu * im, c0 = CENTRE ? -mean * fu : zero;
+          auto pack8 = [&](const float* e, float m) {
+            return make_uint4(mul_pack_f16x2(e[0], e[1], m, c0), mul_pack_f16x2(e[2], e[3], m, c0), mul_pack_f16x2(e[4], e[5], m, c0),
+                              mul_pack_f16x2(e[6], e[7], m, c0));
+          };
+          f32x4 zr = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < K::DK; ++c) {
-          *reinterpret_cast<uint4*>(rowp + (((qz * K::DK + c) ^ psw) * 16)) = pack8(ep + 8 * c, fp);
-          *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + qz * K::DK + c) ^ psw) * 16)) = pack8(em + 8 * c, fm);
-        }
+          for (int c = 0; c < K::DK; ++c) {
+            const uint4 a = pack8(ep + 8 * c, up), b = pack8(em + 8 * c, um);
+            *reinterpret_cast<uint4*>(rowp + (((qz * K::DK + c) ^ psw) * 16)) = a;
+            *reinterpret_cast<uint4*>(rowp + (((C::CH / 2 + qz * K::DK + c) ^ psw) * 16)) = b;
+            zr = mfma_f16_16(zop[c], a, zr);
+            zr = mfma_f16_16(zop[K::DK + c], b, zr);
+          }
+          return fmaf(ZPieces<D>::sum(zr), unit_z, f * z_mean);
+        };
         char* drowp = sDO + row * RS;
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) *reinterpret_cast<uint4*>(drowp + (((4 * ks + qz) ^ psw) * 16)) = bq[ks];
+        float y = 1.f, f = wt;
+        const float den = Zp + Zm, all = wt * den;
+        const bool off = fabsf(park_phi(wt) - all) > kSharedRounding * all;
+        if (__any(off)) {
+          // What the roundings of a token's features have in common does not average out over tokens whose queries are alike.  Where it is large, phi is
+          // rounded without the weight, and the weight, in dO, has the normaliser of phi as it was rounded.  (One that is off by a factor of two is of a token
+          // whose features with a key behind them round to next to nothing.)
+          f = off ? 1.f : wt;
+          const float den_r = park_phi(f);
+          if (off) y = wt * (den_r > 0.5f * den && den_r < 2.f * den ? den * __builtin_amdgcn_rcpf(den_r) : 1.f);
+#pragma unroll
+          for (int ks = 0; ks < K::KS; ++ks)
+            *reinterpret_cast<uint4*>(drowp + (((4 * ks + qz) ^ psw) * 16)) =
+                make_uint4(mul_pack_f16x2(bq[ks].x, y, zero), mul_pack_f16x2(bq[ks].y, y, zero), mul_pack_f16x2(bq[ks].z, y, zero),
+                           mul_pack_f16x2(bq[ks].w, y, zero));
+        }
         if (lane < 16) {
-          sW[row] = -delta * stok;
+          sW[row] = -delta * stok * y;
           if constexpr (CENTRE) sF[row] = f;
         }
       }
@@ -639,7 +709,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     }
     if constexpr (DW) dwt.store(dw_part + ((size_t)bh * P + p) * (size_t)D * C::HALF, lane);
 
-    const float ig = __builtin_amdgcn_rcpf(gamma);    // exact: gamma is a power of two
+    const float ig = __builtin_amdgcn_rcpf(gamma), ip = ig * (1.f / kPhiUnit);      // exact: gamma is a power of two
     if constexpr (CENTRE) {
       // column sums of dO/den (the wavefronts qd.mi = 0 hold every channel block once) and the sum of -delta/den
       float* cs = cs_part + ((size_t)bh * P + p) * (D + 8);
@@ -662,12 +732,12 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int f = 32 * qd.fblk(i) + 8 * (r / 4) + 4 * g + (r % 4);
-          dst[f * D + 32 * qd.cblk(j) + c] = s[i][j][r] * ig;
+          dst[f * D + 32 * qd.cblk(j) + c] = s[i][j][r] * ip;
         }
     {
       float lo, hi;
       pair32(zacc, lo, hi);
-      if (qd.do_z() && g == 0) dst[D * D + 32 * qd.zblk() + c] = (lo + hi) * ig;
+      if (qd.do_z() && g == 0) dst[D * D + 32 * qd.zblk() + c] = (lo + hi) * ip;
     }
   }
   if constexpr (DR) {
@@ -853,7 +923,7 @@ __global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint1
 
 template <int D, bool DW>
 constexpr size_t q_smem() {
-  return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG)
+  return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG + ZPieces<D>::IMG)
        + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4, 16>::DU_BYTES + (kOwnX<D> ? (size_t)kTile * D * 2 : 0) : 0);
 }
 template <int D, bool DW>
