@@ -473,18 +473,15 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       float ep[K::FL], em[K::FL], ip, im;
       softmax16<D>(u, ep, em, ip, im);
       __builtin_amdgcn_sched_barrier(0);                   // (nothing waits for dO any earlier)
-      // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that
+      // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that.  (The largest of those that
+      // are finite: an infinity or NaN then stays in its own channel of dS.)
       float dmax, stok;
       uint4 bq[K::KS];
       {
-        // (magnitudes of bf16 compare as integers)
-        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-        u16x2 m2 = {0, 0};
-        auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
+        FiniteMax16 most;
 #pragma unroll
-        for (int ks = 0; ks < K::KS; ++ks) { take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w); }
-        const uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
-        dmax = quad<MagOp>(__builtin_bit_cast(float, m << 16));
+        for (int ks = 0; ks < K::KS; ++ks) most.take(dor[ks]);
+        dmax = quad<MagOp>(most.value());
         // (times 1, 1.25, 1.5 or 1.75, eight bits times three: still exact.  The weight that goes into phi is divided by it, so that tokens whose queries are
         // alike round in four ways)
         stok = pow2_normaliser(fminf(dmax, kTokenMax)) * fmaf((float)(((uint32_t)(t0 + lane % 16) * 0x165667b1u) >> 30), 0.25f, 1.f);
@@ -549,7 +546,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         char* rowp = sPhi + row * RS;
         // The weight of the token, (1 - r') / den times the running scale, goes into phi, which is rounded anyway, and dO enters exactly.  (With the weight in
         // dO both operands are rounded, twice the variance of dS.)  A token whose dO vanishes or flushes in fp16 has none.
-        const float wt = dmax < 0x1p-100f ? 0.f : inv_den * om * gamma * istok + (dmax - dmax);
+        const float wt = dmax < 0x1p-100f ? 0.f : inv_den * om * gamma * istok;
         auto park_phi = [&](float f) {                   // the packed features; returns their sum over z / f
           // CENTRE: phi minus its mean over the features, rounded after the subtraction: the fp16 rounding then acts
           // on the deviation from the uniform map; (2/D) x the column sums are added back on the key side

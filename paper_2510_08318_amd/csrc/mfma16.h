@@ -133,6 +133,22 @@ __device__ __forceinline__ uint32_t mul_pack_f16x2(uint32_t ab, float s, float c
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// The largest magnitude of bf16 values, of those that are finite.  2x + 2^8 in 16 bits drops the sign, orders the finite ones and wraps the others round
+// to below 2^8.
+struct FiniteMax16 {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 m = {0x100, 0x100}, two = {2, 2};
+  __device__ __forceinline__ FiniteMax16() { asm volatile("" : "+s"(two)); }      // (one v_pk_mad_u16; seen as a shift and an addition they are two)
+  __device__ __forceinline__ void take(uint32_t pair) {
+    const u16x2 bias = {0x100, 0x100};
+    m = __builtin_elementwise_max(m, (u16x2)(__builtin_bit_cast(u16x2, pair) * two + bias));
+  }
+  __device__ __forceinline__ void take(const uint4& x) { take(x.x); take(x.y); take(x.z); take(x.w); }
+  __device__ __forceinline__ float value() const {
+    return __builtin_bit_cast(float, (uint32_t)((m[0] > m[1] ? m[0] : m[1]) - 0x100) << 15);
+  }
+};
+
 // The 16 rows from token t0 of a head of n tokens as operands: lane (t, q) reads the 16-byte chunks 4ks + q of row t0 + t.  Bounded buffer loads: the
 // address is one register that never changes, and rows past n read as zeros.  All arguments but the lane are uniform.
 template <int D>

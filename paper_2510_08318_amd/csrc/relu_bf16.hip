@@ -342,18 +342,16 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
     drows.arrived(dor);
     for (int tile = p; tile < ntile; tile += P) {
       const int t0 = tile * kTile + 16 * w;                // (rows past n are zeros)
-      // phi(q); whether it has any feature above zero; the token's largest |dO| (magnitudes of bf16 compare as integers)
+      // phi(q); whether it has any feature above zero; the token's largest finite |dO|
       uint32_t any = 0;
-      typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-      u16x2 m2 = {0, 0};
-      auto take = [&](uint32_t v) { m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, v & 0x7fff7fffu)); };
+      FiniteMax16 most;
 #pragma unroll
       for (int ks = 0; ks < K::KS; ++ks) {
         xq[ks] = make_uint4(relu_bf16x2(xn[ks].x), relu_bf16x2(xn[ks].y), relu_bf16x2(xn[ks].z), relu_bf16x2(xn[ks].w));
         any |= (xq[ks].x | xq[ks].y) | (xq[ks].z | xq[ks].w);
-        take(dor[ks].x); take(dor[ks].y); take(dor[ks].z); take(dor[ks].w);
+        most.take(dor[ks]);
       }
-      float dmax = __builtin_bit_cast(float, (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16), any_of = __builtin_bit_cast(float, any);
+      float dmax = most.value(), any_of = __builtin_bit_cast(float, any);
       quad2<MagOp>(dmax, any_of);
       const float stok = pow2_normaliser(fminf(dmax, kTokenMax)), istok = __builtin_amdgcn_rcpf(stok);
       // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
@@ -402,8 +400,9 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
       const float r1 = (inv_den * __builtin_amdgcn_rcpf(scale)) * istok;
       const float delta = a_sum * r1;
       {
-        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i
-        const float m = row_max_mag(fmaxf(live ? fmaxf(dmax, fabsf(delta)) * inv_den : 0.f, 0.f));
+        // the tile's largest operand of the two sums, |dO_i| / den_i or |delta_i| / den_i, of those that are finite
+        const float ad = fabsf(delta);
+        const float m = row_max_mag(fmaxf(live ? fmaxf(dmax, ad < __builtin_inff() ? ad : 0.f) * inv_den : 0.f, 0.f));
         if (lane == 0) sRed[w] = m;
       }
       __syncthreads();                                   // the previous tile has been read
@@ -413,8 +412,7 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
         const int row = 16 * w + lz % 16, psw = swz<D>(lz % 16), qz = lz / 16;
         char* rowp = sPhi + row * RS;
         char* drowp = sDO + row * RS;
-        // (a gradient that is not finite makes the sums NaN)
-        const float sc = live ? inv_den * gamma : 0.f, so = sc * istok + (dmax - dmax);
+        const float sc = live ? inv_den * gamma : 0.f, so = sc * istok;
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) {
           *reinterpret_cast<uint4*>(rowp + (((4 * ks + qz) ^ psw) * 16)) =

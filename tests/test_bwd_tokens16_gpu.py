@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import linattn_oracle as O
+from oracle import relu_oracle as R
 from paper_2510_08318_amd import synth
 from tests.test_bf16_paths_gpu import _check, _run
 
@@ -62,6 +63,28 @@ def test_gradient_that_is_not_finite(value):
     assert np.isfinite(got["dq"][0, 0][finite]).all()
     for name, r in zip(("dq", "dk", "dv"), ref):
         assert O.err_metric(got[name][:, 1:], r)[0] <= 1e-2, name
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("token", [40, 300])
+def test_gradient_that_is_not_finite_stays_in_its_channel_of_dv(token, d, relu, value):
+    """dv_j = phi(k_j) dS takes channel c of dout into channel c alone; and dq of the other tokens does not take that token's dout."""
+    def edit(do):
+        do[0, 0, token, 3] = value
+    x = _with_gradient(d, edit)
+    got = _run(x, relu, False)
+    def zeroed(do):
+        do[0, 0, token, 3] = 0.0
+    y = _with_gradient(d, zeroed)
+    ref = R.relu_bwd_bh(y.q, y.k, y.v, y.dout) if relu else O.bwd_bh(y.q, y.k, y.v, y.wq, y.wk, y.dout)
+    others, tokens = np.delete(np.arange(d), 3), np.delete(np.arange(x.n), token)
+    # (ReLU: a key without a positive channel has dv = 0, or 0 times an infinity)
+    dead = (O.to_f64(x.k)[0, 0] <= 0).all(-1) if relu else np.zeros(x.n, bool)
+    assert not np.isfinite(got["dv"][0, 0, ~dead, 3]).any()
+    assert O.err_metric(got["dv"][:, :1, :, others], ref[2][:, :1, :, others])[0] <= 1e-2
+    assert O.err_metric(got["dq"][:, :1, tokens], ref[0][:, :1, tokens])[0] <= 1e-2
 
 
 # the key side without dW~ deals blocks of 16 tokens to 12 (width 128) or 8 (64) wavefronts, with dW~ 128-token tiles
