@@ -315,8 +315,8 @@ __device__ __forceinline__ void contract_tokens(const QuadrantReads<D>& rd, f32x
   }
 }
 
-// What phi enters that sum with: a power of two that keeps small features out of the fp16 subnormals (f is at most 32).
-constexpr float kPhiUnit = 0x1p10f;
+// What phi enters that sum with: a power of two that keeps small features out of the fp16 subnormals (f is at most 1, or 32 / kTokenUnit).
+constexpr float kPhiUnit = 0x1p14f;
 // The relative error of phi . z from rounded phi above which a token's weight is formed with it.  A single feature's rounding gives up to 2^-11; tokens of
 // ordinary maps stay below (rms 3e-5, of sharp ones with a feature of 0.2 of den 6e-5), and 1.7e-4 in four ways of rounding is what the other operands'
 // roundings leave of tokens with the same query.  dS of such heads, rms: 2e-4 without, 7e-5 now, and 6e-5 with the normaliser from rounded phi for every token,
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
       float ep[K::FL], em[K::FL], ip, im;
       softmax16<D>(u, ep, em, ip, im);
       __builtin_amdgcn_sched_barrier(0);                   // (nothing waits for dO any earlier)
-      // dO scaled by a power of two that brings the token's largest magnitude into [1, 2): exact in fp16 down to 2^-17 of that.  (The largest of those that
+      // dO scaled by a power of two that brings the token's largest magnitude into [kTokenUnit, 2 kTokenUnit): exact in fp16 down to 2^-27 of that.  (The largest of those that
       // are finite: an infinity or NaN then stays in its own channel of dS.)
       float dmax, stok;
       uint4 bq[K::KS];
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
         dmax = quad<MagOp>(most.value());
         // (times 1, 1.25, 1.5 or 1.75, eight bits times three: still exact.  The weight that goes into phi is divided by it, so that tokens whose queries are
         // alike round in four ways)
-        stok = pow2_normaliser(fminf(dmax, kTokenMax)) * fmaf((float)(((uint32_t)(t0 + lane % 16) * 0x165667b1u) >> 30), 0.25f, 1.f);
+        stok = pow2_normaliser(fminf(dmax, kTokenMax)) * fmaf((float)(((uint32_t)(t0 + lane % 16) * 0x165667b1u) >> 30), 0.25f * kTokenUnit, kTokenUnit);
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) {
           float f[8];

@@ -439,8 +439,9 @@ __device__ __forceinline__ float pow2_normaliser(float m) {
 }
 
 // A token's largest gradient is normalised as if it were no larger than this: the scale is then at least 2^-126, a normal number whose
-// reciprocal v_rcp_f32 gives exactly (values from 2^127 would ask for 2^-127), and the operand stays below 8.
-constexpr float kTokenMax = 0x1.8p126f;
+// reciprocal v_rcp_f32 gives exactly (values from 2^127 would ask for 2^-127), and the operand stays below 8 times the unit it is brought to.  At
+// that unit, entries down to 2^-24 of the token's largest are normal fp16 numbers; with 1, those from 2^-14 on lost their low bits.
+constexpr float kTokenMax = 0x1.8p126f, kTokenUnit = 0x1p10f;
 
 // Running power-of-two scale of a workgroup's sums over tokens (fp16 MFMA operands, fp32
 // accumulators).  A tile whose largest operand magnitude is m wants the scale gamma_for(m), which

@@ -353,11 +353,11 @@ __global__ __launch_bounds__(NTQ) void relu_bwd_q_kernel(const uint16_t* __restr
       }
       float dmax = most.value(), any_of = __builtin_bit_cast(float, any);
       quad2<MagOp>(dmax, any_of);
-      const float stok = pow2_normaliser(fminf(dmax, kTokenMax)), istok = __builtin_amdgcn_rcpf(stok);
+      const float stok = kTokenUnit * pow2_normaliser(fminf(dmax, kTokenMax)), istok = __builtin_amdgcn_rcpf(stok);
       // a query with phi(q) = 0 adds nothing to dS and dz, but its 1 / den = 1 / eps would set the
       // common scale gamma and push every other token's operand into the fp16 subnormals
       const bool live = __builtin_bit_cast(uint32_t, any_of) != 0;
-      // dO scaled by a power of two: exact in fp16 down to 2^-17 of the token's largest
+      // dO scaled by a power of two: exact in fp16 down to 2^-27 of the token's largest
       uint4 bq[K::KS];
 #pragma unroll
       for (int ks = 0; ks < K::KS; ++ks) {

@@ -87,6 +87,21 @@ def test_gradient_that_is_not_finite_stays_in_its_channel_of_dv(token, d, relu, 
     assert O.err_metric(got["dq"][:, :1, tokens], ref[0][:, :1, tokens])[0] <= 1e-2
 
 
+@pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_channels_of_the_gradient_far_below_the_others(d, relu):
+    """A channel of dv comes from that channel of dout alone.  The largest operand of a workgroup's sum dS is scaled to 2^4, so one 2^-18 below it lies at
+    2^-14, the smallest with 11 bits, and those of tokens with less weight have fewer: of the ReLU map, whose 1 / den spreads most, a few binades, 2^-9 of
+    the sum; beside the bf16 store (2^-9), 2^-8 in 2-norm."""
+    def edit(do):
+        do[..., 5::16] *= 2.0 ** -18
+    x = _with_gradient(d, edit)
+    ref = R.relu_bwd_bh(x.q, x.k, x.v, x.dout)[2] if relu else O.bwd_bh(x.q, x.k, x.v, x.wq, x.wk, x.dout)[2]
+    dv = _run(x, relu, False)["dv"]
+    a, r = dv[..., 5::16], ref[..., 5::16]
+    assert np.linalg.norm(a - r) <= 2.0 ** -8 * np.linalg.norm(r)
+
+
 # the key side without dW~ deals blocks of 16 tokens to 12 (width 128) or 8 (64) wavefronts, with dW~ 128-token tiles
 @pytest.mark.parametrize("wgrads", [False, True], ids=["frozen", "wgrads"])
 @pytest.mark.parametrize("n,H,d", [(1, 2, 128), (15, 2, 64), (17, 2, 128), (191, 2, 128), (193, 2, 128), (127, 2, 64), (129, 2, 64), (400, 255, 64),
