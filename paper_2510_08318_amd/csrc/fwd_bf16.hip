@@ -659,10 +659,15 @@ template <int D, bool BLEND, int KIND, bool SUM>
 hipError_t run_apply(const void* q, const void* wq, const float* partials, float* state, void* out, const void* blend_in,
                      const float* blend_r, const Plan& p, hipStream_t s) {
   const int blocks = (p.n + 31) / 32;
-  const Split d8 = make_deal_of_blocks(p.BH, blocks, 8, kApplyCost<D, BLEND>, apply_even<SUM>);
-  if constexpr (!SUM || kSumSlots<D> * kTile > 8 * 32) {   // (one unit of 8 a head otherwise)
+  // Every workgroup of a pass that sums reads all of its head's partials.  A call, us, units of 8 / 4 / 2: width 64, 24 heads x 500 (4 partials) 11.5 / 11.3 / 12.4, 48
+  // x 500 13.6 / 14.1 / 14.1, 4 x 500 10.1 / 9.5 / 9.4, 24 x 768 (6) 13.4 / 13.9 / 13.9, 12 x 768 11.9 / 11.5 / 11.6, and one tile 32 x 100 8.7 / 8.8 / 9.2; width 128, 128 x 100 (1)
+  // 18.2 / 18.1 / 22.8, 12 x 100 14.4 / 14.4 / 14.5, 4 x 100 14.2 / 14.4 / 14.0, 64 x 256 (2) 22.7 / 20.8 / 26.1, 4 x 256 17.0 / 15.1 / 14.6, 128 x 256 23.6 / 24.2.
+  const UnitLimits most = SUM ? UnitLimits{240, D == 128 ? 16 : p.split.ntile > 1 ? 64 : 0} : UnitLimits();
+  const int read = SUM ? p.split.PS : 1;
+  const Split d8 = make_deal_of_blocks(p.BH, blocks, 8, kApplyCost<D, BLEND>, apply_even<SUM>, read, most);
+  if constexpr (!SUM || kSumSlots<D> * kTile > 8 * 32) {   // (at most 8 blocks a head otherwise)
     const bool even12 = apply_even<SUM> && ((D == 128 && BLEND) || !d8.share) && (blocks + 11) % 12 < 8;
-    const Split d12 = make_deal_of_blocks(p.BH, blocks, 12, kApplyCost<D, BLEND>, even12);
+    const Split d12 = make_deal_of_blocks(p.BH, blocks, 12, kApplyCost<D, BLEND>, even12, read, most);
     const int r8 = split_rounds(d8);
     if (r8 <= 3 && split_rounds(d12) < r8)
       return run_apply_waves<D, BLEND, KIND, SUM, 12>(q, wq, partials, state, out, blend_in, blend_r, p, d12, s);
@@ -681,15 +686,16 @@ hipError_t pick_apply(const void* q, const void* wq, const float* partials, floa
 
 }  // namespace
 
-// Short calls, where a launch is a fifth of the time: the query pass sums the partials itself, up to eight tiles a head at width 64 and
-// two at 128 (at least as many as slots), where each of the at most four workgroups of a head (one at 128) reads them.  A call, reduction
-// launched / summed here, us: width 64, 1 head x 100 10.0 / 8.4, 30 x 500 13.4 / 11.9, 24 x 768 14.1 / 12.9, 4 x 1000 12.1 / 11.3, 128 x 1000 23.1 / 20.5,
-// 36 x 1024 18.5 / 17.9; but where each of eight tiles has a slot of its own and the heads are many, 16 x 1024 13.1 / 13.3, 30 x 1000 15.3 / 16.1, 12 x 1024
-// 12.9 / 12.6; nine to sixteen tiles 12 x 2000 15.1 / 17.1, 128 x 2000 33.1 / 31.4.  Width 128: 1 x 100 15.0 / 14.0, 128 x 100 23.7 / 17.2, 255 x 256 36.2 / 31.7; three
-// or four tiles, a state of 66 KB each, 4 x 500 17.9 / 18.5, 128 x 500 32.8 / 30.1.
+// Short calls, where a launch is a fifth of the time: the query pass sums the partials itself, up to six tiles a head at width 64 and two at 128 (at least
+// as many as partials), and up to eight where the heads are few or so many that each has few partials.  Every workgroup of a head, up to
+// sixteen (four at 128), reads all of them.  A call, reduction launched / summed here, with the units that each takes, us: width 64, 1 head x 100 9.7 / 8.0, 32 x 300
+// 12.4 / 10.7, 64 x 500 16.0 / 15.2, 12 x 768 12.1 / 11.5, 32 x 768 14.7 / 14.5, but 48 x 640 15.1 / 15.5; seven and eight tiles 4 x 1000 10.9 / 10.7, 8 x 1000 11.5 / 11.8, 12 x
+// 1000 12.0 / 12.7, 48 x 900 17.8 / 18.8, 64 x 1000 18.4 / 18.4, 100 x 1000 22.2 / 19.5, 200 x 1024 33.9 / 30.3.  Width 128: 1 x 100 14.2 / 13.7, 128 x 100 25.4 /
+// 18.1, 48 x 256 22.7 / 19.7, 200 x 256 31.4 / 26.1.  With units of eight blocks: nine to sixteen tiles 12 x 2000 x 64 15.1 / 17.1, 128 x 2000 x 64 33.1 / 31.4, three
+// or four at 128, a state of 66 KB each, 4 x 500 17.9 / 18.5, 128 x 500 32.8 / 30.1.
 bool sum_in_apply(const Plan& p) {
   if (p.d == 128) return p.split.ntile <= kSumSlots<128>;
-  return p.split.ntile < kSumSlots<64> || (p.split.ntile == kSumSlots<64> && (p.BH <= 12 || p.split.T > kSlots));
+  return p.split.ntile <= 6 || (p.split.ntile <= kSumSlots<64> && (p.BH <= 4 || p.split.T > 2 * kSlots));
 }
 
 hipError_t launch_apply_bf16(const void* q, const void* wq, const float* partials, float* state, void* out,

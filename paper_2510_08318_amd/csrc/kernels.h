@@ -164,15 +164,31 @@ inline Split make_deal(int BH, int per_head, DealCost cost, bool may_even = true
   return s;
 }
 
-// The deal of `blocks` 32-token blocks a head to workgroups of `waves` wavefronts, a block to a wavefront.  Where every unit of four, or two, gets a
-// compute unit of its own the units are four or two: in so short a call most of the chip is empty, its time is the latency of a block, and a
-// wavefront that shares its SIMD (or the LDS) with fewer others is done with it sooner.  Us, units of 8 / 4 / 2: bf16 query pass 4 heads x 1000 x 64 7.2 / 6.0 / 5.85, 3 x
-// 300 x 128 9.3 / 7.3 / 6.7, 12 x 1000 x 128 9.7 / 8.1 (200 units of 2: the same rule), ReLU 4 x 2000 x 64 5.0 / 4.1; fp32 arithmetic, 2 x 1024 x 64: query pass 8.9 / 7.4 /
-// 6.8, gradients 15.1 + 12.8 / 12.2 + 10.7 / 10.2 + 10.4; 4 x 1500 x 128, bf16 tensors: 13.9 / 10.7, 23.2 + 17.1 / 17.6 + 14.5.
-inline Split make_deal_of_blocks(int BH, int blocks, int waves, DealCost cost, bool may_even = true) {
+// The deal of `blocks` 32-token blocks a head to workgroups of `waves` wavefronts, a block to a wavefront.  Units are of four or two blocks where every unit
+// gets a compute unit of its own: in so short a call most of the chip is empty, its time is the latency of a block, and a wavefront that shares its SIMD
+// (or the LDS) with fewer others is done with it sooner.  Us, units of 8 / 4 / 2: bf16 query pass 4 heads x 1000 x 64 7.2 / 6.0 / 5.85, 3 x
+// 300 x 128 9.3 / 7.3 / 6.7, ReLU 4 x 2000 x 64 5.0 / 4.1; fp32 arithmetic, 2 x 1024 x 64: query pass 8.9 / 7.4 / 6.8, gradients 15.1 + 12.8 / 12.2 + 10.7 / 10.2 +
+// 10.4.
+// More workgroups also bring more copies of a head's state into the eight L2s, one to each XCD (workgroups are dealt to them in turn) or to each workgroup
+// of a head that has fewer.  With many heads of few blocks that costs more than the smaller unit saves: a call, bf16, 48 heads x 300 x 128 25.2 / 23.1 / 23.9 (96
+// copies more for units of two), 32 x 300 x 128 22.7 / 21.0 / 21.5 (64), 16 x 300 x 128 20.0 / 18.3 / 18.2 (32); bf16 tensors in fp32 arithmetic 64 x 128 x 128 26.5 /
+// 26.4 / 27.8 (64), 16 x 256 x 128 25.3 / 22.6 / 22.4 (32).  Units of four pay wherever they fit.  A query pass that sums reads `partials` states a copy and has limits of its
+// own (run_apply).
+constexpr int kXCDs = 8;
+struct UnitLimits {
+  long long four = 1 << 30, two = 48;      // the most states more than with the next larger unit, for units of four and of two
+};
+constexpr UnitLimits kNoUnitLimits{1 << 30, 1 << 30};
+inline Split make_deal_of_blocks(int BH, int blocks, int waves, DealCost cost, bool may_even = true, int partials = 1, UnitLimits most = UnitLimits()) {
+  auto states = [&](int u) {
+    const int per_head = (blocks + u - 1) / u;
+    return (long long)BH * (per_head < kXCDs ? per_head : kXCDs) * partials;
+  };
   int unit = waves;
-  for (int u = 4; u >= 2; u /= 2)
-    if ((long long)BH * ((blocks + u - 1) / u) <= kCUs) unit = u;
+  for (int u = 4; u >= 2; u /= 2) {
+    if ((long long)BH * ((blocks + u - 1) / u) > kCUs || states(u) - states(unit) > (u == 4 ? most.four : most.two)) break;
+    unit = u;
+  }
   Split s = make_deal(BH, (blocks + unit - 1) / unit, cost, may_even);
   s.blocks = unit;
   return s;

@@ -59,7 +59,8 @@ def test_backward_workgroups_of_several_tiles(d, mode):
 
 
 @pytest.mark.parametrize("relu", [False, True], ids=["hedgehog", "relu"])
-@pytest.mark.parametrize("n,H,d", [(1, 1, 64), (129, 2, 64), (300, 3, 64), (640, 2, 64), (1024, 5, 64), (1025, 5, 64), (1000, 100, 64),
+@pytest.mark.parametrize("n,H,d", [(1, 1, 64), (129, 2, 64), (300, 3, 64), (640, 2, 64), (1024, 5, 64), (1025, 5, 64), (1000, 100, 64), (768, 6, 64), (769, 6, 64), (1024, 4, 64),
+                                   (1000, 64, 64), (1000, 65, 64), (500, 33, 64),
                                    (128, 3, 128), (256, 3, 128), (257, 3, 128), (200, 300, 128)])
 def test_query_pass_that_sums_the_partials(n, H, d, relu):
     if n == 1:        # one token: the state is phi(k)^T v; out is v whatever q and k are, so dq and dk vanish (ReLU: up to its eps)

@@ -76,6 +76,48 @@ int main() {
 """
 
 
+UNITS = r"""
+#include "kernels.h"
+#include <cstdio>
+using namespace linattn;
+// states that the workgroups of a call bring into the L2s of eight XCDs
+static long long states(const Split& s, int BH, int blocks, int partials) {
+  const long long per_head = (blocks + s.blocks - 1) / s.blocks;
+  return BH * (per_head < 8 ? per_head : 8) * partials;
+}
+int main() {
+  long bad = 0, held = 0;
+  for (int BH : {1, 2, 4, 8, 16, 24, 48, 64, 100, 128, 200, 255})
+    for (int blocks : {1, 2, 3, 4, 8, 10, 16, 20, 24, 32, 64, 100})
+      for (int partials : {1, 2, 4, 8})
+        for (UnitLimits most : {UnitLimits(), UnitLimits{240, 64}, UnitLimits{240, 16}, UnitLimits{240, 0}}) {
+          const Split s = make_deal_of_blocks(BH, blocks, 8, {4, 2, 5, 240}, false, partials, most);
+          Split t = s, l = s;
+          t.blocks = 2 * s.blocks;
+          if (s.blocks < 8) bad += states(s, BH, blocks, partials) - states(t, BH, blocks, partials) > (s.blocks == 4 ? most.four : most.two);
+          // and no larger than the limits ask for
+          l.blocks = s.blocks / 2;
+          if (s.blocks > 2 && BH * ((blocks + l.blocks - 1) / l.blocks) <= kCUs) {
+            ++held;
+            bad += states(l, BH, blocks, partials) - states(s, BH, blocks, partials) <= (l.blocks == 4 ? most.four : most.two);
+          }
+        }
+  printf("bad %ld held %ld\n", bad, held);
+  return bad != 0 || held == 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_smaller_units_only_where_the_states_they_read_allow_it(tmp_path):
+    src, exe = tmp_path / "units.cpp", tmp_path / "units"
+    src.write_text(UNITS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    "-I", os.path.join(ROOT, "paper_2510_08318_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_every_block_is_dealt_once(tmp_path):
     src, exe = tmp_path / "deal.cpp", tmp_path / "deal"
