@@ -238,15 +238,27 @@ struct Plan {
 bool make_plan(int B, int H, int n, int d, int dtype, int layout, Plan* p);
 // The workgroups of the state passes.  The split of make_plan, by which the workspace is sized, gives every workgroup the same number of tiles, and some
 // of them tiles of two heads: two prologues, two partial states, the loads in flight drained between them.  Head by head no workgroup has two, and
-// no head more partials; it is taken where the busiest workgroup has no more tiles for it, or, of eight and more in the bf16 Hedgehog pass, one more.  Evenly / head by head, us: 12 heads x 4133 x 64 (2 tiles either way) 8.6 / 7.55, x 128 14.9 / 13.5, 30 x 3000 x 64 (3) 10.4 / 9.4, 7 x 20000 x
-// 128 (5) 25.4 / 21.9, 30 x 17550 x 64 (17 / 18) 29.4 / 27.7, 12 x 32760 x 128 (12 / 13) 50.9 / 48.8; but 12 x 8190 x 128 (3 / 4) 18.3 / 18.7, ReLU 12 x 32760 x
-// 128 44.2 / 47.3, a forward call of fp32 tensors there 271 / 275.
+// no head more partials; it is taken where the busiest workgroup has no more tiles for it, or, of four and more in the bf16 Hedgehog pass, one more.  Evenly /
+// head by head, us a pass: 12 heads x 4133 x 64 (2 tiles either way) 8.6 / 7.55, x 128 14.9 / 13.5, 30 x 3000 x 64 (3) 10.4 / 9.4, 7 x 20000 x
+// 128 (5) 25.4 / 21.9, 30 x 17550 x 64 (17 / 18) 29.4 / 27.7, 12 x 32760 x 128 (12 / 13) 50.9 / 48.8.  Of 364 forward calls of 5 to 200 heads with one tile more, all
+// 28 of four tiles gain (0.1 to 4 us of 23 to 51), those of five to ten 0.9 to 2.7 us on average, of three at width 128 6 of 12 (12 x 8190 loses 0.75 of 40); but ReLU
+// 12 x 32760 x 128 44.2 / 47.3, a forward call of fp32 tensors there 271 / 275.
+// Where the even split gives no workgroup tiles of two heads there is nothing to save, and the head-wise one, if its workgroups to a head are odd, ends the
+// pass later at width 64: those with a tile more, the last of each head, then lie on all XCDs and not on one of them.  A forward call, us, evenly / head by head:
+// 13 heads x 2560 x 64 16.9 / 18.3, 12 x 2816 17.1 / 18.3, 48 x 768 16.0 / 17.1, 26 x 1280 16.7 / 17.9, 5 x 6656 17.1 / 17.6; but even numbers 30 x 1152 17.7 / 16.4, 52 x
+// 640 16.2 / 15.0, 9 x 3712 17.7 / 17.1, and at width 128 48 x 768 29.6 / 29.0, 13 x 2560 29.2 / 29.2.
 inline void deal_state_pass(Plan* p) {
-  const int m = p->BH < kSlots ? kSlots / p->BH : 1;
+  const int m = p->BH < kSlots ? kSlots / p->BH : 1, G = p->split.G;
   if (m > p->split.ntile) return;
+  const bool hedgehog = p->kind == kPhiHedgehog && p->bf16_math;
   const int even = split_rounds(p->split), by_head = (p->split.ntile + m - 1) / m;
-  const bool one_more = even >= 8 && p->kind == kPhiHedgehog && p->bf16_math;
-  if (by_head > even + one_more) return;
+  if (by_head > even + (even >= 4 && hedgehog)) return;
+  if (p->d == 64 && hedgehog && m % 2 && p->BH < G) {
+    // head h starts at workgroup ceil(h G / BH), which starts at its first tile if (-h G mod BH) tiles-a-head are below G
+    int a = G, b = p->BH;
+    while (b) { const int r = a % b; a = b; b = r; }
+    if ((long long)(p->BH - a) * p->split.ntile < G) return;
+  }
   p->split.G = p->BH * m;
   p->split.PS = m;
   finish_split(p->split);
