@@ -173,15 +173,14 @@ __device__ __forceinline__ float build_key_state(StateRegs<D, NTHREADS>& S, floa
 // the blocks to one common power-of-two scale that follows the running maximum of the workgroup
 // (gamma_step; the accumulators are rescaled by the exact ratio when a tile raises it).  Partials per
 // workgroup are reduced in a fixed order afterwards.
-template <int D, int NW, int BLK = 32>
+template <int D, int NW>
 struct DwTile {
   static constexpr int HALF = D / 2;
-  static constexpr int LOC = D / 4;
   static constexpr int RSX = D * 2;                        // bytes per row of the x tile
   static constexpr int RSU = HALF * 2;                     // bytes per row of the du tile
   static constexpr int NB = HALF / 32;                     // 32-column blocks of du
   static constexpr int RB = (D / 32) * NB >= NW ? (D / 32) * NB / NW : 1;   // row blocks per wavefront
-  static constexpr int BPT = kTile / BLK;                  // du blocks (each with a scale of its own) per parked tile
+  static constexpr int BPT = kTile / 16;                   // du blocks (each with a scale of its own) per parked tile
   static constexpr int KSN = kTile / 16;
   static constexpr int KBATCH = D == 64 ? KSN : KSN / 4;        // k-steps whose operands are in flight together
   static constexpr int DU_BYTES = kTile * RSU;
@@ -237,7 +236,7 @@ struct DwTile {
       }
 #pragma unroll
       for (int ks = 0; ks < KBATCH; ++ks) {
-        const _Float16 f = (_Float16)(gamma * its[(k0 + ks) * 16 / BLK]);   // a power of two, or 0 for an all-zero block
+        const _Float16 f = (_Float16)(gamma * its[k0 + ks]);   // a power of two, or 0 for an all-zero block
         const f16x8 bo = b[ks] * f;
 #pragma unroll
         for (int i = 0; i < RB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks][i], bo, acc[i], 0, 0, 0);
@@ -350,8 +349,8 @@ struct ZPieces {
 // LDS operands of the token wavefronts' MFMA phases are requested QAHEAD MFMAs before their use.
 constexpr int QAHEAD = 4;
 constexpr int NTQ = 768;     // 12 wavefronts, one workgroup per compute unit
-// DW: whether a tile's q rows have a place of their own in LDS.  Else (width 128, whose images and tiles fill it) they take phi's when dS has read it, with one
-// more barrier to a tile.
+// Whether a tile's q rows, which dW~ contracts, have a place of their own in LDS.  Else (width 128, whose images and tiles fill it) they take phi's when dS
+// has read it, with one more barrier to a tile.
 template <int D>
 constexpr bool kOwnX = D == 64;
 // BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
@@ -387,7 +386,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
   constexpr int WMN = D / 64;
   constexpr int NTOK = kTile / 16;                         // token wavefronts
   constexpr float mean = CENTRE ? 2.0f / D : 0.f;          // what is taken out of phi before it is rounded: its mean over the features
-  using DWT = DwTile<D, 4, 16>;
+  using DWT = DwTile<D, 4>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
   uint4* sGA = sWA + K::W_IMG;
@@ -646,8 +645,8 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
     constexpr int PER = kTile * C::CH / 256;
     const int crow = (tid - 64 * NTOK) / C::CH, ccol = (tid - 64 * NTOK) % C::CH;
     for (int tile = p; tile < ntile; tile += P) {
-      // (blend is never null here: as a branch the section keeps its registers to itself; without one, 97 are spilled with CENTRE and DW where 13
-      // are, and 10 with DW alone where none is)
+      // (blend is never null here: as a branch the section keeps its registers to itself; without one, 97 are spilled with CENTRE and DW where 3
+      // are, and 75 with DW alone where none is)
       if (DR && blend != nullptr) {
         const uint16_t* srow = blend + head_base(rw, bh, H) + 8 * ccol;
         const uint16_t* drow = dout + head_base(rw, bh, H) + 8 * ccol;
@@ -753,7 +752,7 @@ __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__
 constexpr int KAHEAD = 3;
 // One workgroup per compute unit: with dW~ 12 wavefronts, without 8, whose prologue is shorter and whose rows arrive no later: 12 / 8 wavefronts, us, 4 heads x
 // 1000 x 128 11.7 / 9.9, 12 x 2000 13.3 / 11.8, 12 x 4133 20.8 / 18.3, 12 x 16000 40.7 / 40.2, 24 x 20000 x 64 47.4 / 46.2 (8 of 32 tokens: 47.2).
-template <int D, bool DW>
+template <bool DW>
 constexpr int kKeyThreads = DW ? 768 : 512;
 
 // Every wavefront takes blocks of 16 tokens.  DW: dW~_k is accumulated here as well (DwTile): wavefronts 0-7 walk 128-token tiles in step and park their
@@ -763,15 +762,15 @@ constexpr int kKeyThreads = DW ? 768 : 512;
 // Eight wavefronts of 32 tokens, two to a SIMD, filled 40 % of its vector issue: 107 us, now 87 (12 heads x 32760 x 128 with dW~; 403 MB of rows, 4.6
 // TB/s), in [B,n,H,d] 118 / 90, centred 12 x 8190 36 / 31, 12 x 1000 16.1 / 13.5.
 template <int D, bool STREAM, bool CENTRE, bool DW>
-__global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+__global__ __launch_bounds__(kKeyThreads<DW>) void bwd_k_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                     const uint16_t* __restrict__ wk, const float* __restrict__ dstate,
                                                     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                                                     float* __restrict__ dw_part,
                                                     const float* __restrict__ vbar, const float* __restrict__ cs_part,
                                                     int H, int n, int P, Rows rw) {
   using K = Tok16<D>;
-  constexpr int NTK = kKeyThreads<D, DW>, NW = NTK / 64, NTOK = DW ? kTile / 16 : NW;
-  using DWT = DwTile<D, NW - kTile / 16, 16>;
+  constexpr int NTK = kKeyThreads<DW>, NW = NTK / 64, NTOK = DW ? kTile / 16 : NW;
+  using DWT = DwTile<D, NW - kTile / 16>;
   extern __shared__ uint4 smem[];
   uint4* sWA = smem;
   uint4* sVA = sWA + K::W_IMG;             // image of dS for dv (contraction over features)
@@ -921,13 +920,13 @@ __global__ __launch_bounds__((kKeyThreads<D, DW>)) void bwd_k_kernel(const uint1
 template <int D, bool DW>
 constexpr size_t q_smem() {
   return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG + ZPieces<D>::IMG)
-       + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4, 16>::DU_BYTES + (kOwnX<D> ? (size_t)kTile * D * 2 : 0) : 0);
+       + 2 * (size_t)kTile * D * 2 + (2 * kTile + 2 * D + 16) * sizeof(float) + (DW ? DwTile<D, 4>::DU_BYTES + (kOwnX<D> ? (size_t)kTile * D * 2 : 0) : 0);
 }
 template <int D, bool DW>
 constexpr size_t k_smem() {
   // the prologue's scratch lies where the DW tiles are afterwards
-  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + kKeyThreads<D, DW> / 64 + 4) * sizeof(float);
-  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, 4, 16>::DU_BYTES : 0;
+  constexpr size_t scratch = ((size_t)(D / 8) * D + 4 * D + kKeyThreads<DW> / 64 + 4) * sizeof(float);
+  constexpr size_t tiles = DW ? (size_t)kTile * D * 2 + DwTile<D, 4>::DU_BYTES : 0;
   return sizeof(uint4) * (Tok16<D>::W_IMG + Tok16<D>::A_IMG + Tok16<D>::G_IMG + Tok16<D>::T_IMG) + (2 * D + 8) * sizeof(float)
        + (scratch > tiles ? scratch : tiles);
 }
@@ -954,7 +953,7 @@ hipError_t run_bwd_as(const BwdArgs& a, const Plan& p, hipStream_t s) {
   if (e != hipSuccess) return e;
   if ((e = launch_state_reduce(a.partials, a.dstate, p, DrSum{a.dr_part, p.BH * p.P, a.blend_r, a.blend_dr}, s)) != hipSuccess) return e;
   // with dW~_k a workgroup takes 128-token tiles, and the partials are laid out like the query side's; else 16 tokens a wavefront
-  constexpr int UNIT = kKeyThreads<D, false> / 4;
+  constexpr int UNIT = kKeyThreads<false> / 4;
   const int units = (p.n + UNIT - 1) / UNIT, per_head = p.BH < kCUs ? kCUs / p.BH : 1;
   const int groups = a.dwk ? p.P : units < per_head ? units : per_head;
   auto launch_k = [&](auto kernel, int threads, size_t smem) -> hipError_t {
@@ -965,8 +964,8 @@ hipError_t run_bwd_as(const BwdArgs& a, const Plan& p, hipStream_t s) {
         a.dw_part + side_elems, a.vbar, a.cs_part, p.H, p.n, p.P, p.rows);
     return hipGetLastError();
   };
-  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, true>>{}, kKeyThreads<D, true>, k_smem<D, true>()) :
-      launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, false>>{}, kKeyThreads<D, false>, k_smem<D, false>());
+  e = a.dwk ? launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, true>>{}, kKeyThreads<true>, k_smem<D, true>()) :
+      launch_k(KernelTag<bwd_k_kernel<D, STREAM, CENTRE, false>>{}, kKeyThreads<false>, k_smem<D, false>());
   if (e != hipSuccess) return e;
   if (a.dwq || a.dwk) {
     if ((e = launch_dw_reduce2(a.dwq ? a.dw_part : nullptr, a.dwq, p.P, a.dwk ? a.dw_part + side_elems : nullptr, a.dwk, groups, p, s)) != hipSuccess) return e;

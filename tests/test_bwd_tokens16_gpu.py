@@ -102,10 +102,10 @@ def test_channels_of_the_gradient_far_below_the_others(d, relu):
     assert np.linalg.norm(a - r) <= 2.0 ** -8 * np.linalg.norm(r)
 
 
-# the key side without dW~ deals blocks of 16 tokens to 12 (width 128) or 8 (64) wavefronts, with dW~ 128-token tiles
+# the key side deals 128 tokens to a workgroup: without dW~ blocks of 16 to 8 wavefronts, with it tiles to 8 beside 4 that contract them
 @pytest.mark.parametrize("wgrads", [False, True], ids=["frozen", "wgrads"])
 @pytest.mark.parametrize("n,H,d", [(1, 2, 128), (15, 2, 64), (17, 2, 128), (191, 2, 128), (193, 2, 128), (127, 2, 64), (129, 2, 64), (400, 255, 64),
-                                   (193, 300, 128)])
+                                   (193, 300, 128), (127, 2, 128), (128, 2, 128), (129, 2, 128), (128, 2, 64)])
 def test_key_side_lengths(n, H, d, wgrads):
     x = synth.generate("C5", n=n, H=H, B=1, d=d, dtype="bf16")
     if n == 1:        # the output does not depend on k
