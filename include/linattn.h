@@ -33,11 +33,15 @@
  * Numeric domain of the bf16 mode (the fp32 mode computes in fp32 throughout)
  *   - q, k enter the projection of Eq. 5 as stored; phi, v, dout and the states S, dS enter the
  *     matrix cores as fp16 (11-bit significand) with fp32 accumulation.  phi, the states, dout and
- *     every gradient operand are rescaled by exact powers of two first (per token, per 32-token
+ *     every gradient operand are rescaled by exact powers of two first (per token, per 16-token
  *     block, per head, or per workgroup following the running maximum), so their magnitude does
- *     not matter: any finite bf16 dout is in the domain, and any finite q, k with |x W~| below 2^26 (the
+ *     not matter: any finite bf16 dout is in the domain whose quotient |dout_i| / (phi(q_i) . z) stays
+ *     below the largest fp32 (with a larger one dk, dv and dW~ of its head may come out infinite or NaN, never finite
+ *     and wrong), and any finite q, k with |x W~| below 2^26 (the
  *     exponent of the softmax, u log2 e minus its maximum, is rounded once at that magnitude; the
  *     fp32-arithmetic modes take the difference first and have no such limit).
+ *   - An entry of dout that is an infinity or NaN makes dq of its token, dv of its channel, and dk and dW~
+ *     of its head not finite; dq of the other tokens and dv of the other channels do not depend on it.
  *   - v is widened to fp16 unscaled: |v| must be below 65504 (fp16's largest finite value).  Larger
  *     entries become infinite inside the kernels and the call returns LINATTN_OK with Inf/NaN in
  *     out, state and the gradients; the library does not scan for them.  Entries with
@@ -57,7 +61,7 @@
  *   - LINATTN_BF16_F32MATH reads and writes the same bf16 tensors but does all arithmetic in fp32
  *     (the kernels of the fp32 mode, no fp16 operands): none of the limits above applies, |v| may be
  *     any finite bf16 value, and the only rounding that matters is the bf16 store of the results.  A
- *     training step costs about 1.7x LINATTN_BF16, a forward call 1.5x (Wan-1.3B 480p shape).
+ *     training step costs about twice LINATTN_BF16, a forward call 1.6x (Wan-1.3B 480p shape).
  *   - fp32 arithmetic (this mode and LINATTN_F32) runs on the matrix cores as sums of exact products of bf16
  *     pieces with fp32 accumulation.  Operands below 2^-110 lose the bits below 2^-133.  What the pieces cannot
  *     carry (finite values above 3.3895e38, which round to Inf as bf16, infinities and NaN) comes out as plain fp32 FMA

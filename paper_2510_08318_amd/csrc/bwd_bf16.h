@@ -319,7 +319,8 @@ constexpr float kPhiUnit = 0x1p14f;
 // The relative error of phi . z from rounded phi above which a token's weight is formed with it.  A single feature's rounding gives up to 2^-11; tokens of
 // ordinary maps stay below (rms 3e-5, of sharp ones with a feature of 0.2 of den 6e-5), and 1.7e-4 in four ways of rounding is what the other operands'
 // roundings leave of tokens with the same query.  dS of such heads, rms: 2e-4 without, 7e-5 now, and 6e-5 with the normaliser from rounded phi for every token,
-// which has the weight in dO and rounds both operands.  It costs 1 % of a training step (bwd_q 12 heads x 32760 x 128 with dW~ 94 -> 97 us).
+// which has the weight in dO and rounds both operands.  It costs 1 % of a training step (bwd_q 12 heads x 32760 x 128 with dW~ 92.2 -> 95.7 us; 5 % of
+// a backward call of maps so sharp that most tokens are parked twice).
 constexpr float kSharedRounding = 0x1.6p-13f;
 
 // z in fp16 pieces, as the A operands of the product that gives the token wavefronts phi . z from phi in fp16: piece r of scale * z, 12 bits
@@ -356,7 +357,7 @@ constexpr bool kOwnX = D == 64;
 // BLEND: dout is the gradient of the mixed output of Eq. 6; the linear branch receives (1 - r') dout.  DR: dL/dr = sum dout . (s - o) is
 // asked for, and the workgroup's part goes to dr_part: the token wavefronts have dout . (o - vbar) as their delta, and the accumulate
 // wavefronts, which wait for phi in the first half of a tile, read s and dout for dout . (s - vbar).  That sum as a streaming kernel of
-// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it costs 13.  An instance of its
+// its own read dout once more and took 36 us (12 heads x 32760 x 128); here it costs 13 to 20.  An instance of its
 // own: as a condition at run time its registers were spilled in blended calls without dL/dr too (centred, width 128, with dW~: 10, no other instance any).
 // DW: dW~_q is accumulated here as well (DwTile).
 //
@@ -368,9 +369,9 @@ constexpr bool kOwnX = D == 64;
 // one phi, dO and du tile).  A tile: phi, G and the sums; phi and dO are parked between two barriers and dS contracts them
 // while du and dx are formed; (DW) x takes phi's place and du its tile between two more, and dW~ contracts those beside the next
 // tile's first half.
-// What bounds it is the issue of vector and matrix instructions, which overlap little: a SIMD has two tok wavefronts (730 vector instructions and 64
+// What bounds it is the issue of vector and matrix instructions, which overlap little: a SIMD has two tok wavefronts (750 vector instructions and 68
 // MFMAs a tile each) and one acc (300 and 48), 11 of the tile's 14 thousand cycles.  Four tok wavefronts of 32 tokens, one to a SIMD, left a third of the
-// issue slots empty and had 1700 instructions a tile: 111 us, now 94 (12 heads x 32760 x 128 with dW~), 41 / 36 (centred, 12 x 8190), 114 / 108 with
+// issue slots empty and had 1700 instructions a tile: 111 us, now 96 (12 heads x 32760 x 128 with dW~), 41 / 34 (centred, 12 x 8190), 114 / 108 to 117 with
 // dL/dr.  For a 16-token form to gain, nothing may be spilled: nine spilled addresses of the acc wavefronts, a scratch access to a k-step, took back all of it.
 template <int D, bool STREAM, bool BLEND, bool DR, bool CENTRE, bool DW>
 __global__ __launch_bounds__(NTQ) void bwd_q_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ dout,
